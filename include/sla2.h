@@ -168,7 +168,7 @@ int sla2_router_static(const sla2_params* params, const void* q, const void* k, 
 
 /* SoftTop-k form of the router (Sec. 6: the differentiable operator that replaces Top-k in the
  * first training stage):  mask[b,h,i,j] = sigmoid(P_c[i,j] / tau + lambda_i), P_c the row softmax
- * of the router scores of Eq. 16 (with the 1/sqrt(d) of Alg. 2), lambda_i found by bisection so that
+ * of the router scores of Eq. 16 (with the 1/sqrt(d) of Alg. 2), lambda_i the root (to fp64 rounding) at which
  * row i sums to k = sla2_num_selected(params); k = 0 gives zeros, k = T_n ones.  fp64 inside.
  *   q, k, router_w  as for sla2_router;  tau > 0 (the paper uses 0.1)
  *   mask_out        DEVICE float [B, H, T_m, T_n], written

@@ -1,0 +1,147 @@
+// Router scores of 16 query blocks of one head against all of its key blocks (Eq. 16), fp64 on the matrix cores;
+// shared by the hard selection (sla2_router.hip) and the soft one (sla2_router_soft.hip).
+//
+//   R[i][j] = proj_q(Qbar_i) . proj_k(Kbar_j) / sqrt(d),   proj(x) = x W
+//
+// Two identities keep the work small.  (1) R = (Qbar M) Kbar^T with M = Wq Wk^T / sqrt(d), a d x d matrix formed once
+// per call (fold_router_row, run by spare workgroups of the pooling launch): only the 16 query rows of a workgroup are
+// projected, the pooled keys are used as they are.  (2) Kbar is pooled from K - colmean(K), which shifts every score
+// of a row by the same amount, (Qbar Wq Wk^T) . colmean(K): neither a row-wise top-k nor a row softmax sees it, so the
+// raw block sums of K are scored and the mean never enters.  The scores formed here therefore differ from R by one
+// constant per row.
+//
+// A workgroup has 16 waves.  Scores are formed (v_mfma_f64_16x16x4) 256 key blocks at a time: wave w multiplies the
+// projected 16 x d tile with key blocks [256 r + 16 w, +16), parks its 16 x 16 result in LDS, and wave i then picks up
+// row i, so that after the last round every wave holds one complete score row in registers (4 values per lane and
+// round).  Scores never touch HBM.
+#pragma once
+#include "common.h"
+
+namespace sla2 {
+
+constexpr int kRouterRows = 16;                       // query blocks per workgroup = waves per workgroup
+constexpr int kColsPerRound = 256;                    // key blocks scored per round (16 waves x 16)
+typedef __attribute__((ext_vector_type(2))) double f64x2;
+
+template <int D> constexpr size_t router_lds_bytes() {
+  return sizeof(double) * (kRouterRows * (D + 2) + kRouterRows * (kColsPerRound + 8));
+}
+
+// C[16][D] = A[16][D] M on the matrix cores, M fp64 [D][D] row-major in global memory.  All 16 waves
+// work: wave w forms columns [16 (w % (D/16)), +16) over a 1/(16 / (D/16)) share of the contraction
+// range; the shares are written side by side (C has room for kShares copies) and added by the reader.
+template <int D> struct ProjGeom {
+  static constexpr int kNt = D / 16;                 // column tiles
+  static constexpr int kShares = 16 / kNt;           // waves per column tile: 2 (D = 128) or 4 (D = 64)
+  static constexpr int kSteps = D / 4 / kShares;     // 4-wide contraction steps per wave
+};
+template <int D>
+__device__ __forceinline__ void project16_fetch(double (&b)[ProjGeom<D>::kSteps], const double* __restrict__ M, int wave,
+                                                int lane) {
+  typedef ProjGeom<D> G;
+  const int n = 16 * (wave % G::kNt) + lane % 16, share = wave / G::kNt;
+#pragma unroll
+  for (int i = 0; i < G::kSteps; i++) b[i] = M[(size_t)(4 * (share * G::kSteps + i) + lane / 16) * D + n];
+}
+template <int D>
+__device__ __forceinline__ void project16(const double (*A)[D + 2], double (*C)[D + 2] /* [kShares*16][D+2] */,
+                                          const double (&b)[ProjGeom<D>::kSteps], int wave, int lane) {
+  typedef ProjGeom<D> G;
+  const int nt = wave % G::kNt, share = wave / G::kNt;
+  const int n = 16 * nt + lane % 16;
+  f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int i = 0; i < G::kSteps; i++)
+    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(A[lane % 16][4 * (share * G::kSteps + i) + lane / 16], b[i], acc, 0, 0, 0);
+#pragma unroll
+  for (int v = 0; v < 4; v++) C[share * 16 + lane / 16 + 4 * v][n] = acc[v];
+}
+
+// Leaves row (row0 + wave) in `score`: slot 4 r + x of lane l is key block 256 r + 64 x + l (slots past T_n hold
+// -infinity).  All 16 waves of the workgroup call it; `lds` holds router_lds_bytes<D>().
+template <int D, int SLOTS>
+__device__ __forceinline__ void router_scores(double (&score)[SLOTS], const double* __restrict__ q_sum,
+                                              const double* __restrict__ k_sum, const double* __restrict__ M, double* lds,
+                                              int bh, int row0, int N, int bq, int bk, int Tm, int Tn) {
+  // LDS: xa [16][D+2] pooled queries, later Qbar M | tile [16][264] one round of scores (the partial projections
+  // before the first round)
+  double (*xa)[D + 2] = reinterpret_cast<double (*)[D + 2]>(lds);
+  double (*tile)[kColsPerRound + 8] = reinterpret_cast<double (*)[kColsPerRound + 8]>(lds + kRouterRows * (D + 2));
+  static_assert(ProjGeom<D>::kShares * (D + 2) <= kColsPerRound + 8, "projection shares must fit the score tile");
+  double (*xb)[D + 2] = reinterpret_cast<double (*)[D + 2]>(&tile[0][0]);   // partial Qbar M; dead before the first round
+  const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+  const int rounds = (Tn + kColsPerRound - 1) / kColsPerRound;
+
+  // Operand B of a round: lane l feeds key block col0 + l % 16.  The contraction runs in an order of its own (the
+  // same for both operands): product 2 j + x takes channels 8 j + 2 (l / 16) + x, so that one 16-byte load serves two
+  // products and the four lanes of a row cover 64 consecutive bytes.  The loads go straight to registers, kBatch of
+  // them ahead of the products (staging them through LDS for fully coalesced rows takes the same time and 70 KB more of
+  // LDS per workgroup).
+  constexpr int kLoads = D / 8, kBatch = SLOTS > 16 ? 4 : 8;
+  f64x2 pre[2][kBatch];
+  const double* kb = k_sum + (size_t)bh * Tn * D + 2 * (lane / 16);
+  auto fetch = [&](int r, int batch) {
+    const int col = min(r * kColsPerRound + wave * 16 + lane % 16, Tn - 1);    // past the end: the last key block again
+    const double* p = kb + (size_t)col * D + 8 * kBatch * batch;
+#pragma unroll
+    for (int i = 0; i < kBatch; i++) pre[batch & 1][i] = *reinterpret_cast<const f64x2*>(p + 8 * i);
+  };
+
+  double mb[ProjGeom<D>::kSteps];
+  project16_fetch<D>(mb, M, wave, lane);               // operands of the projection, in flight during the Qbar load
+  for (int e = threadIdx.x; e < kRouterRows * D; e += 1024) {
+    const int r = e / D, c = e % D;
+    const int row = min(row0 + r, Tm - 1);             // rows past the end repeat the last one; never stored
+    const int rows = min(bq, N - row * bq);
+    xa[r][c] = q_sum[((size_t)bh * Tm + row) * D + c] / (double)rows;     // mean pooling (Eq. 15)
+  }
+  __syncthreads();
+  project16<D>(xa, xb, mb, wave, lane);                                   // Qbar (Wq Wk^T / sqrt(d)), in shares
+  fetch(0, 0);
+  __syncthreads();
+  for (int e = threadIdx.x; e < kRouterRows * D; e += 1024) {
+    const int r = e / D, c = e % D;
+    double v = xb[r][c];
+#pragma unroll
+    for (int sh = 1; sh < ProjGeom<D>::kShares; sh++) v += xb[sh * 16 + r][c];
+    xa[r][c] = v;
+  }
+  __syncthreads();
+
+#pragma unroll
+  for (int s = 0; s < SLOTS; s++) score[s] = -INFINITY;
+  const double last_cnt = (double)(N - (Tn - 1) * bk);
+#pragma unroll
+  for (int r = 0; r < SLOTS / 4; r++) {
+    if (r < rounds) {
+      f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+      if (r * kColsPerRound + wave * 16 < Tn) {        // uniform per wave
+#pragma unroll
+        for (int b = 0; b < kLoads / kBatch; b++) {
+          if (b + 1 < kLoads / kBatch) fetch(r, b + 1);
+#pragma unroll
+          for (int i = 0; i < kBatch; i++) {
+            const f64x2 a = *reinterpret_cast<const f64x2*>(&xa[lane % 16][8 * (b * kBatch + i) + 2 * (lane / 16)]);
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[0], pre[b & 1][i][0], acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[1], pre[b & 1][i][1], acc, 0, 0, 0);
+          }
+        }
+      }
+      if (r + 1 < rounds) fetch(r + 1, 0);
+      // result layout: lane l, register v holds C[l/16 + 4 v][l%16]
+#pragma unroll
+      for (int v = 0; v < 4; v++) tile[lane / 16 + 4 * v][wave * 16 + lane % 16] = acc[v];
+      __syncthreads();
+      // wave i collects row i; block sums -> block means (only a ragged last block differs)
+#pragma unroll
+      for (int x = 0; x < 4; x++) {
+        const int col = r * kColsPerRound + x * kWave + lane;
+        const double sc = tile[wave][x * kWave + lane] / (col == Tn - 1 ? last_cnt : (double)bk);
+        score[4 * r + x] = col < Tn ? sc : -INFINITY;
+      }
+      __syncthreads();
+    }
+  }
+}
+
+}  // namespace sla2

@@ -56,6 +56,21 @@ def test_soft_router_matches_oracle(w, tau):
             np.testing.assert_allclose(got[b, h].astype(np.float64).sum(axis=1), k, rtol=0, atol=1e-4 * max(1, k))
 
 
+@pytest.mark.parametrize("w,tau", [
+    (W.TINY.replace(name="2048-blocks", grid=(32, 64, 64), dtype="bf16", H=1, topk_frac=0.01), 0.1),      # the longest row
+    (W.TINY.replace(name="257-blocks", grid=(16, 32, 32), H=1, topk_frac=0.03, extra_tokens=1), 0.05),    # one block into the second round
+    (W.TINY.replace(name="steep", H=1), 1e-6),                        # row spread above 600: sigmoids taken from exponents
+    (W.TINY.replace(name="one-of-two", grid=(1, 8, 13), H=1, topk_frac=0.5), 0.1),                        # T_n = 2
+], ids=lambda x: x.name if hasattr(x, "name") else str(x))
+def test_soft_router_row_lengths_and_steep_rows(w, tau):
+    import torch
+    from paper_2602_12675_amd import api
+    inp = W.generate(w)
+    got, k = run_soft(api, torch, inp, tau)
+    want = oracle_soft(inp, 0, 0, k, tau)
+    np.testing.assert_allclose(got[0, 0], want, rtol=0, atol=1e-6)
+
+
 @pytest.mark.parametrize("frac,value", [(0.0, 0.0), (1.0, 1.0)])
 def test_soft_router_limits(frac, value):
     import torch
