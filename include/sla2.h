@@ -126,8 +126,8 @@ typedef struct sla2_ws_layout {
   size_t o_l;       /* dtype  [BH, N, d]     linear-branch output O^l (fp32 tensors only; 0 bytes for bf16 tensors, whose
                        backward pass rebuilds what it needs of O^l from the state kept in `bwd`) */
   size_t lse;       /* float  [BH, N]        L_i of Alg. 2 (log-sum-exp of the kept scores; -inf when k = 0) */
-  size_t bwd;       /* scratch of sla2_backward; for bf16 tensors sla2_forward also leaves the state of the
-                       linear branch of every query block here (H_i^T as bf16, Z_i) */
+  size_t bwd;       /* scratch of sla2_backward; sla2_forward also leaves the state of the linear branch of every
+                       query block here (bf16 tensors: H_i^T as bf16, fp32 tensors: H_i as fp32; Z_i) */
   size_t total;     /* = sla2_workspace_bytes() */
 } sla2_ws_layout;
 

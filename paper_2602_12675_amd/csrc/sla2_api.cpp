@@ -79,10 +79,9 @@ static BwdLayout make_bwd_layout(const Shape& s) {
   BwdLayout B;
   size_t off = 0, BH = (size_t)s.BH, d = (size_t)s.d;
   auto take = [&](size_t bytes) { size_t o = off; off = align256(off + bytes); return o; };
-  // dH_i, dZ_i, d alpha parts: one slot per query block (bf16 tensors; dH_i as bf16) or per 64 query rows (fp32)
-  const size_t slots = BH * s.Tm * (size_t)(s.bf16 ? 1 : s.bq / 64);
+  const size_t slots = BH * s.Tm, esz = s.bf16 ? 2 : 4;   // dH_i, dZ_i, H_i, Z_i, d alpha parts: one slot per query block
   B.ds = take(BH * (size_t)s.N * sizeof(float));
-  B.dh = take(slots * d * d * (s.bf16 ? 2 : sizeof(float)));
+  B.dh = take(slots * d * d * esz);
   B.dz = take(slots * d * sizeof(float));
   B.dh_total = take(BH * d * d * sizeof(float));
   B.dz_total = take(BH * d * sizeof(float));
@@ -93,10 +92,9 @@ static BwdLayout make_bwd_layout(const Shape& s) {
   B.col_idx = take(BH * s.Tm * (size_t)(s.k > 0 ? s.k : 1) * sizeof(int32_t));
   B.col_cnt = take(BH * (size_t)s.Tn * sizeof(int32_t));
   B.mask_bits = take(BH * s.Tm * (size_t)((s.Tn + 31) / 32) * sizeof(uint32_t));
-  // bf16 tensors: the forward kernel leaves H_i^T (bf16) and Z_i per query block here; L on the raw keys
-  B.h_i = take(s.bf16 ? BH * s.Tm * d * d * 2 : 0);
-  B.z_i = take(s.bf16 ? BH * s.Tm * d * sizeof(float) : 0);
-  B.lraw = take(s.bf16 ? BH * (size_t)s.N * sizeof(float) : 0);
+  B.h_i = take(slots * d * d * esz);                 // left here by the forward kernel
+  B.z_i = take(slots * d * sizeof(float));
+  B.lraw = take(BH * (size_t)s.N * sizeof(float));
   B.total = off;
   return B;
 }
@@ -308,12 +306,10 @@ int sla2_forward(const sla2_params* params, const void* q, const void* k, const 
   SavedForBackward sv{nullptr, nullptr, nullptr, nullptr, nullptr};
   if (s.save) {
     sv = SavedForBackward{at<void>(workspace, L.o_s), at<void>(workspace, L.o_l), at<float>(workspace, L.lse), nullptr, nullptr};
-    if (s.bf16) {
-      sv.o_l = nullptr;
-      const BwdLayout B = make_bwd_layout(s);
-      sv.h_i = (uint16_t*)(at<char>(workspace, L.bwd) + B.h_i);
-      sv.z_i = (float*)(at<char>(workspace, L.bwd) + B.z_i);
-    }
+    if (s.bf16) sv.o_l = nullptr;
+    const BwdLayout B = make_bwd_layout(s);
+    sv.h_i = (void*)(at<char>(workspace, L.bwd) + B.h_i);
+    sv.z_i = (float*)(at<char>(workspace, L.bwd) + B.z_i);
   }
   float* k_stats = at<float>(workspace, L.k_stats);
   float* h_total = at<float>(workspace, L.h_total);
@@ -384,7 +380,7 @@ int sla2_backward(const sla2_params* params, const void* q, const void* k, const
   a.block_idx = at<int32_t>(workspace, L.block_idx);
   a.alpha = alpha;
   a.dq = dq; a.dk = dk; a.dv = dv; a.dalpha = dalpha;
-  a.h_i = (const uint16_t*)(bw + B.h_i); a.z_i = (const float*)(bw + B.z_i); a.lraw = (float*)(bw + B.lraw);
+  a.h_i = (const void*)(bw + B.h_i); a.z_i = (const float*)(bw + B.z_i); a.lraw = (float*)(bw + B.lraw);
   a.ds = (float*)(bw + B.ds); a.dh = (void*)(bw + B.dh); a.dz = (float*)(bw + B.dz);
   a.dh_total = (float*)(bw + B.dh_total); a.dz_total = (float*)(bw + B.dz_total);
   a.colsum = (float*)(bw + B.colsum); a.dk_mean = (float*)(bw + B.dk_mean);

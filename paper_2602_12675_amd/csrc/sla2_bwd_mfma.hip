@@ -404,7 +404,7 @@ static hipError_t launch_bwd_q_mfma(const Shape& s, const BwdArgs& a, hipStream_
   const int grid = ((s.Tm + kXcds - 1) / kXcds) * kXcds * s.BH;
   bwd_q_mfma_kernel<D, BQ><<<dim3((unsigned)grid), BQ * 2, smem, stream>>>(
       (const uint16_t*)a.q, (const uint16_t*)a.k, (const uint16_t*)a.v, (const uint16_t*)a.dout, (const uint16_t*)a.o_s,
-      a.lse, a.k_mean, a.h_i, a.z_i, a.block_idx, a.alpha, (uint16_t*)a.dq, a.ds, a.lraw,
+      a.lse, a.k_mean, (const uint16_t*)a.h_i, a.z_i, a.block_idx, a.alpha, (uint16_t*)a.dq, a.ds, a.lraw,
       (uint16_t*)a.dh, a.dz, a.dalpha_part, s.sin, s.sout, s.H, s.N, s.Tm, s.Tn, s.k, s.alpha_per_block ? 1 : 0);
   return hipGetLastError();
 }

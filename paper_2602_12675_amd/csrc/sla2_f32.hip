@@ -1,21 +1,17 @@
-// fp32 path of the SLA2 forward pass (Alg. 2 of the paper): plain fp32 FMA kernels with
-// LDS-staged tiles, used when q, k, v are stored in fp32.  The data flow is the one of the
-// bf16 / FP8 path - per-head totals of h_j, z_j first, then one pass per query block that
-// runs the sparse branch over the selected key/value blocks, rebuilds the h_j, z_j of exactly
-// those blocks, subtracts them from the totals, and mixes the two branches - so this file
-// also serves as the readable statement of that flow.
-#include "common.h"
+// fp32 path of the SLA2 forward pass (Alg. 2 of the paper), used when q, k, v are stored in fp32.  The data flow is the
+// one of the bf16 / FP8 path - per-head totals of h_j, z_j first, then one pass per query block that runs the sparse
+// branch over the selected key/value blocks, rebuilds the h_j, z_j of exactly those blocks, subtracts them from the
+// totals, and mixes the two branches - in fp32 throughout: products on the fp32 matrix instruction (f32_tiles.h).
+#include "f32_tiles.h"
 
 namespace sla2 {
-
-constexpr int kBK = 64;           // key/value block (b_kv)
-constexpr int kRowsF32 = 64;      // query rows per workgroup in the fp32 attention kernel
 
 // ---------------------------------------------------------------------------------------------
 // kv_state_f32: for a chunk of key blocks of one head
 //   k' = k - colmean(K);  stats[token] = lnZ = log sum_c exp(k'_c);
 //   K^phi = softmax_d(k');  partial h += (K^phi_j)^T V_j,  partial z += colsum(K^phi_j)
-// (Alg. 2: K^phi, h, z).  Tokens past N contribute nothing.
+// (Alg. 2: K^phi, h, z).  Tokens past N contribute nothing.  A token's channels sit on neighbouring lanes, 4 each, so
+// the softmax is taken in registers on the way into LDS.
 // ---------------------------------------------------------------------------------------------
 template <int D>
 __global__ __launch_bounds__(256) void kv_state_f32_kernel(const float* __restrict__ k, const float* __restrict__ v,
@@ -23,77 +19,72 @@ __global__ __launch_bounds__(256) void kv_state_f32_kernel(const float* __restri
                                                            float* __restrict__ k_stats, float* __restrict__ partial,
                                                            Strides sin, int H, int N, int Tn, int chunks,
                                                            int blocks_per_chunk) {
-  constexpr int LD = D + 1;       // odd stride: a column of tokens falls into distinct banks
-  constexpr int MT = D / 16;      // micro-tile edge: each thread owns MT x MT entries of h
-  extern __shared__ float smem[];
-  float* ks = smem;                 // [64][LD]  K' tile, then K^phi tile
-  float* vs = smem + kBK * LD;      // [64][LD]  V tile
-  __shared__ float mu_s[D];
+  constexpr int LD = kF32Ld<D>;
+  typedef ChunkMap<D, 256, kF32Tokens> CM;
+  typedef StateSplit<D, 4> SS;
+  extern __shared__ __attribute__((aligned(16))) float smem[];
+  float* kp = smem;                       // [64][LD]  K^phi tile
+  float* vs = smem + kF32Tokens * LD;     // [64][LD]  V tile
   const int bh = blockIdx.x / chunks, chunk = blockIdx.x % chunks;
-  if (threadIdx.x < D) mu_s[threadIdx.x] = (float)k_mean[(size_t)bh * D + threadIdx.x];
-  __syncthreads();
-  const int tid = threadIdx.x, tx = tid % 16, ty = tid / 16;
+  const int tid = threadIdx.x, lane = tid % kWave, g = lane / 32, w = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int ch = tid % CM::kChunks, trow = tid / CM::kChunks;
   const float* kh = k + head_offset(sin, bh, H);
   const float* vh = v + head_offset(sin, bh, H);
   const int j0 = chunk * blocks_per_chunk, j1 = min(Tn, j0 + blocks_per_chunk);
-
-  float hacc[MT][MT];
+  f32x4 mu;
 #pragma unroll
-  for (int a = 0; a < MT; a++)
-#pragma unroll
-    for (int b = 0; b < MT; b++) hacc[a][b] = 0.f;
-  float zacc = 0.f;
+  for (int x = 0; x < 4; x++) mu[x] = (float)k_mean[(size_t)bh * D + 4 * ch + x];
 
+  f32x16 hacc[SS::kTiles];
+#pragma unroll
+  for (int x = 0; x < SS::kTiles; x++) hacc[x] = zero16();
+  f32x4 zacc = {0.f, 0.f, 0.f, 0.f};
+  f32x4 kr[CM::kLoads], vr[CM::kLoads];
+  auto fetch = [&](int j) {
+    const int t0 = j * kF32Tokens, valid = min(kF32Tokens, N - t0);
+    CM::load(kr, kh + (size_t)t0 * sin.n, sin.n, valid, tid);
+    CM::load(vr, vh + (size_t)t0 * sin.n, sin.n, valid, tid);
+  };
+  if (j0 < j1) fetch(j0);
   for (int j = j0; j < j1; j++) {
-    const int t0 = j * kBK, valid = min(kBK, N - t0);
-    for (int idx = tid; idx < kBK * D; idx += 256) {
-      int t = idx / D, c = idx % D;
-      bool ok = t < valid;
-      ks[t * LD + c] = ok ? kh[(size_t)(t0 + t) * sin.n + c] - mu_s[c] : 0.f;
-      vs[t * LD + c] = ok ? vh[(size_t)(t0 + t) * sin.n + c] : 0.f;
-    }
-    __syncthreads();
-    {  // softmax over the channels of each token, 4 threads per token
-      const int t = tid / 4, sub = tid % 4;
-      float m = -INFINITY;
-      for (int c = sub; c < D; c += 4) m = fmaxf(m, ks[t * LD + c]);
-      m = fmaxf(m, __shfl_xor(m, 1));
-      m = fmaxf(m, __shfl_xor(m, 2));
-      float sum = 0.f;
-      for (int c = sub; c < D; c += 4) {
-        float e = __expf(ks[t * LD + c] - m);
-        ks[t * LD + c] = e;
-        sum += e;
-      }
-      sum += __shfl_xor(sum, 1);
-      sum += __shfl_xor(sum, 2);
-      const float inv = 1.f / sum;
+    const int t0 = j * kF32Tokens, valid = min(kF32Tokens, N - t0);
+    __syncthreads();                      // previous tile fully consumed
+#pragma unroll
+    for (int i = 0; i < CM::kLoads; i++) {
+      const int t = trow + i * CM::kRows;
       const bool ok = t < valid;
-      for (int c = sub; c < D; c += 4) ks[t * LD + c] = ok ? ks[t * LD + c] * inv : 0.f;
-      if (ok && sub == 0) k_stats[(size_t)bh * N + t0 + t] = m + __logf(sum);
+      f32x4 x = kr[i] - mu;
+      const float m = CM::row_max(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])));
+      f32x4 e;
+#pragma unroll
+      for (int c = 0; c < 4; c++) e[c] = exp2_f32((x[c] - m) * kLog2e);
+      const float sum = CM::row_sum((e[0] + e[1]) + (e[2] + e[3]));
+      const float inv = ok ? 1.f / sum : 0.f;
+      e *= inv;
+      zacc += e;
+      *reinterpret_cast<f32x4*>(kp + t * LD + 4 * ch) = e;
+      *reinterpret_cast<f32x4*>(vs + t * LD + 4 * ch) = vr[i];
+      if (ok && ch == 0) k_stats[(size_t)bh * N + t0 + t] = m + __log2f(sum) * kLn2;
     }
+    if (j + 1 < j1) fetch(j + 1);
     __syncthreads();
-    for (int t = 0; t < kBK; t++) {
-      float kv[MT], vv[MT];
-#pragma unroll
-      for (int a = 0; a < MT; a++) kv[a] = ks[t * LD + MT * ty + a];
-#pragma unroll
-      for (int b = 0; b < MT; b++) vv[b] = vs[t * LD + tx + 16 * b];
-#pragma unroll
-      for (int a = 0; a < MT; a++)
-#pragma unroll
-        for (int b = 0; b < MT; b++) hacc[a][b] += kv[a] * vv[b];
-    }
-    if (tid < D)
-      for (int t = 0; t < kBK; t++) zacc += ks[t * LD + tid];
-    __syncthreads();
+    state_product<D, 4>(hacc, kp, vs, kF32Tokens, w, lane);
   }
   float* ph = partial + (size_t)blockIdx.x * (D * D + D);
 #pragma unroll
-  for (int a = 0; a < MT; a++)
+  for (int x = 0; x < SS::kTiles; x++)
 #pragma unroll
-    for (int b = 0; b < MT; b++) ph[(MT * ty + a) * D + tx + 16 * b] = hacc[a][b];
-  if (tid < D) ph[D * D + tid] = zacc;
+    for (int e = 0; e < 16; e++)
+      ph[(32 * SS::mt(w) + 8 * (e / 4) + 4 * g + e % 4) * D + 32 * (SS::nt(w) + x) + lane % 32] = hacc[x][e];
+  __syncthreads();                        // the last tile fully consumed: its place takes the column sums
+  *reinterpret_cast<f32x4*>(kp + trow * D + 4 * ch) = zacc;
+  __syncthreads();
+  if (tid < D) {
+    float z = 0.f;
+#pragma unroll
+    for (int r = 0; r < CM::kRows; r++) z += kp[r * D + tid];
+    ph[D * D + tid] = z;
+  }
 }
 
 // Totals over the chunks of a head (Alg. 2's sums of h_j and z_j over all key blocks).  Each workgroup
@@ -127,268 +118,281 @@ hipError_t launch_kv_total(const Shape& s, const float* partial, float* h_total,
   return hipGetLastError();
 }
 
-hipError_t launch_kv_state_f32(const Shape& s, const float* k, const float* v, const double* k_mean, float* k_stats,
-                               float* partial, hipStream_t stream) {
-  dim3 grid((unsigned)(s.BH * s.chunks));
-  const size_t smem = (size_t)2 * kBK * (s.d + 1) * sizeof(float);
+template <int D>
+static hipError_t launch_kv_state_f32_t(const Shape& s, const float* k, const float* v, const double* k_mean, float* k_stats,
+                                        float* partial, hipStream_t stream) {
+  constexpr int smem = 2 * kF32Tokens * kF32Ld<D> * (int)sizeof(float);
   static OncePerDevice once;
-  if (hipError_t e0 = allow_dynamic_lds(once, (const void*)kv_state_f32_kernel<128>, 2 * kBK * 129 * (int)sizeof(float)); e0 != hipSuccess) return e0;
-  if (s.d == 128)
-    kv_state_f32_kernel<128><<<grid, 256, smem, stream>>>(k, v, k_mean, k_stats, partial, s.sin, s.H, s.N, s.Tn, s.chunks,
-                                                          s.blocks_per_chunk);
-  else
-    kv_state_f32_kernel<64><<<grid, 256, smem, stream>>>(k, v, k_mean, k_stats, partial, s.sin, s.H, s.N, s.Tn, s.chunks,
-                                                         s.blocks_per_chunk);
+  if (hipError_t e = allow_dynamic_lds(once, (const void*)kv_state_f32_kernel<D>, smem); e != hipSuccess) return e;
+  kv_state_f32_kernel<D><<<dim3((unsigned)(s.BH * s.chunks)), 256, smem, stream>>>(k, v, k_mean, k_stats, partial, s.sin, s.H, s.N,
+                                                                                s.Tn, s.chunks, s.blocks_per_chunk);
   return hipGetLastError();
 }
+hipError_t launch_kv_state_f32(const Shape& s, const float* k, const float* v, const double* k_mean, float* k_stats,
+                               float* partial, hipStream_t stream) {
+  return s.d == 128 ? launch_kv_state_f32_t<128>(s, k, v, k_mean, k_stats, partial, stream)
+                    : launch_kv_state_f32_t<64>(s, k, v, k_mean, k_stats, partial, stream);
+}
 
 // ---------------------------------------------------------------------------------------------
-// attn_f32: one workgroup per 64 query rows of query block i.
-//   sparse branch  : for j in sel(i), ascending: S = Q_i K'_j^T / sqrt(d), online softmax, O += P V_j
+// attn_f32: one workgroup per query block i, BQ / 16 waves.
+//   sparse branch  : for j in sel(i), ascending: S^T = K'_j Q_i^T / sqrt(d), online softmax, O^T += V_j^T P^T
 //   linear branch  : H_i = H_total - sum_{j in sel(i)} h_j (h_j rebuilt from the staged tiles and the
-//                    per-token log-partition lnZ), Z_i likewise; O_l = Q^phi H_i / (Q^phi Z_i)
+//                    per-token log-partition lnZ), Z_i likewise; O_l^T = H_i^T Q^phi^T
 //   mix            : out = alpha O_s / l + (1 - alpha) O_l                                   (Eq. 13)
+// Wave (rg, kh) owns query rows 32 rg.. and, in the sparse branch, keys 32 kh.. of every tile: the two waves of a row
+// group keep running maxima of their own and meet once, after the loop, like two halves of a split softmax.  A lane owns
+// one query row, so its probabilities feed O^T += V^T P^T from registers.  The bound is the fp32 matrix rate: on 12 heads
+// of 4,096 tokens (d = 128, 10 % kept) 12 GFLOP.
 // ---------------------------------------------------------------------------------------------
-template <int D>
-__global__ __launch_bounds__(256) void attn_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
-                                                       const float* __restrict__ v, const double* __restrict__ k_mean,
-                                                       const float* __restrict__ k_stats,
-                                                       const float* __restrict__ h_total,
-                                                       const float* __restrict__ z_total,
-                                                       const int32_t* __restrict__ block_idx,
-                                                       const float* __restrict__ alpha, float* __restrict__ out,
-                                                       float* __restrict__ lse, float* __restrict__ o_s_save,
-                                                       float* __restrict__ o_l_save, float* __restrict__ lse_save,
-                                                       Strides sin, Strides sout, int H, int N, int bq, int Tm, int Tn,
-                                                       int ksel, int alpha_per_block) {
-  constexpr int LD = D + 1;
-  constexpr int LP = kBK + 1;
-  constexpr int MT = D / 16;       // h micro-tile edge
-  constexpr int OC = D / 16;       // output columns per thread
-  extern __shared__ float smem[];
-  float* qs = smem;                       // [64][LD]  Q rows, later Q^phi
-  float* ks = qs + kRowsF32 * LD;         // [64][LD]  K' tile, then K^phi tile
-  float* vs = ks + kBK * LD;              // [64][LD]  V tile
-  float* ps = vs + kBK * LD;              // [64][LP]  P tile
-  float* zs = ps + kRowsF32 * LP;         // [D]       Z_i
-  float* hs = ks;                         // [D][D]    H_i in the epilogue (covers ks and vs)
+template <int D, int BQ> struct AttnF32Smem {
+  static constexpr int NW = BQ / 16, NT = NW * kWave;
+  static constexpr int kTile = kF32Tokens * kF32Ld<D>;                     // floats
+  static constexpr int kState = D * kF32Ld<D>;                             // H_i, over the K' and K^phi tiles
+  static_assert(kState <= 2 * kTile, "H_i takes the place of the K' and K^phi tiles");
+  static constexpr int kSwap = NW * (D / 64) * 16 * kWave;                 // half of every wave's O^T tiles
+  static constexpr int kSwapOff = 2 * kTile;                               // over the V tile and behind it
+  static constexpr int kZred = NT * 4;                                     // column sums of K^phi, before the swap
+  static constexpr int kBig = kTile > kSwap ? (kTile > kZred ? kTile : kZred) : (kSwap > kZred ? kSwap : kZred);
+  static constexpr int kMlOff = kSwapOff + kBig;                           // [NW][2][32] m and l
+  static constexpr int kZsOff = kMlOff + NW * 64;                          // [D] Z_i
+  static constexpr int kBytes = (kZsOff + D) * (int)sizeof(float);
+};
 
-  const int parts = bq / kRowsF32;
-  int bid = blockIdx.x;
-  const int part = bid % parts; bid /= parts;
-  const int i = bid % Tm;
-  const int bh = bid / Tm;
-  const int h = bh % H;
-  const int tid = threadIdx.x, tx = tid % 16, ty = tid / 16;
-  const int row0 = i * bq + part * kRowsF32;          // first query row of this workgroup
-  const int rows_valid = max(0, min(kRowsF32, min(N, (i + 1) * bq) - row0));
-  const float* qh = q + head_offset(sin, bh, H);
-  const float* kh = k + head_offset(sin, bh, H);
+template <int D, int BQ>
+__global__ __launch_bounds__(BQ * 4, BQ / 64) void attn_f32_kernel(
+    const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v, const double* __restrict__ k_mean,
+    const float* __restrict__ k_stats, const float* __restrict__ h_total, const float* __restrict__ z_total,
+    const int32_t* __restrict__ block_idx, const float* __restrict__ alpha, float* __restrict__ out, float* __restrict__ lse,
+    float* __restrict__ o_s_save, float* __restrict__ o_l_save, float* __restrict__ lse_save, float* __restrict__ h_save,
+    float* __restrict__ z_save, Strides sin, Strides sout, int H, int N, int Tm, int Tn, int ksel, int alpha_per_block) {
+  typedef AttnF32Smem<D, BQ> SM;
+  constexpr int NW = SM::NW, NT = SM::NT, LD = kF32Ld<D>, ET = D / 32, J = D / 8;
+  typedef ChunkMap<D, NT, kF32Tokens> CM;
+  typedef StateSplit<D, NW> SS;
+  extern __shared__ __attribute__((aligned(16))) float smem[];
+  float* ks = smem;                       // [64][LD]  K' tile
+  float* kp = smem + SM::kTile;           // [64][LD]  K^phi tile
+  float* vs = smem + 2 * SM::kTile;       // [64][LD]  V tile
+  float* hs = smem;                       // [D][LD]   H_i
+  float* swap = smem + SM::kSwapOff;
+  float* ml = smem + SM::kMlOff;
+  float* zs = smem + SM::kZsOff;
+
+  const int i = blockIdx.x % Tm, bh = blockIdx.x / Tm, h = bh % H;
+  const int tid = threadIdx.x, lane = tid % kWave, g = lane / 32, w = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int rg = w >> 1, kh = w & 1;
+  const int ch = tid % CM::kChunks, trow = tid / CM::kChunks;
+  const int row0 = i * BQ, rows_valid = min(BQ, N - row0);
+  const int qrow = 32 * rg + lane % 32;
+  const bool row_ok = qrow < rows_valid;
+  const float* kh_ = k + head_offset(sin, bh, H);
   const float* vh = v + head_offset(sin, bh, H);
   const int32_t* sel = block_idx + ((size_t)bh * Tm + i) * ksel;
-  const float rscale = rsqrtf((float)D);
-  if (rows_valid == 0) return;                        // second half of a short last query block
 
-  for (int idx = tid; idx < kRowsF32 * D; idx += 256) {
-    int r = idx / D, c = idx % D;
-    qs[r * LD + c] = r < rows_valid ? qh[(size_t)(row0 + r) * sin.n + c] : 0.f;
+  f32x4 kr[CM::kLoads], vr[CM::kLoads];
+  float zr[CM::kLoads];
+  auto fetch = [&](int j) {
+    const int t0 = j * kF32Tokens, valid = min(kF32Tokens, N - t0);
+    CM::load(kr, kh_ + (size_t)t0 * sin.n, sin.n, valid, tid);
+    CM::load(vr, vh + (size_t)t0 * sin.n, sin.n, valid, tid);
+#pragma unroll
+    for (int x = 0; x < CM::kLoads; x++) zr[x] = k_stats[(size_t)bh * N + t0 + min(trow + x * CM::kRows, valid - 1)];
+  };
+  if (ksel > 0) fetch(sel[0]);
+  f32x4 qf[J];                            // this lane's query row, channels 8 j + 4 g ..
+  {
+    const float* src = q + head_offset(sin, bh, H) + (size_t)(row0 + min(qrow, rows_valid - 1)) * sin.n + 4 * g;
+#pragma unroll
+    for (int j = 0; j < J; j++) qf[j] = *reinterpret_cast<const f32x4*>(src + 8 * j);
   }
+  f32x4 mu;
+#pragma unroll
+  for (int x = 0; x < 4; x++) mu[x] = (float)k_mean[(size_t)bh * D + 4 * ch + x];
 
-  float m_run[4], l_run[4], oacc[4][OC], hacc[MT][MT];
+  f32x16 oacc[ET], hacc[SS::kTiles];
 #pragma unroll
-  for (int a = 0; a < 4; a++) {
-    m_run[a] = -INFINITY; l_run[a] = 0.f;
+  for (int e = 0; e < ET; e++) oacc[e] = zero16();
 #pragma unroll
-    for (int b = 0; b < OC; b++) oacc[a][b] = 0.f;
-  }
-#pragma unroll
-  for (int a = 0; a < MT; a++)
-#pragma unroll
-    for (int b = 0; b < MT; b++) hacc[a][b] = 0.f;
-  float zacc = 0.f;
+  for (int x = 0; x < SS::kTiles; x++) hacc[x] = zero16();
+  f32x4 zacc = {0.f, 0.f, 0.f, 0.f};
+  float m_run = -INFINITY, l_run = 0.f;   // this lane's row over this wave's keys, log2 domain
+  const float c0 = kLog2e * rsqrtf((float)D);
 
   for (int s = 0; s < ksel; s++) {
-    const int j = sel[s];
-    const int t0 = j * kBK, valid = min(kBK, N - t0);
-    __syncthreads();                                  // previous tile fully consumed (and qs written)
-    for (int idx = tid; idx < kBK * D; idx += 256) {
-      int t = idx / D, c = idx % D;
-      bool ok = t < valid;
-      ks[t * LD + c] = ok ? kh[(size_t)(t0 + t) * sin.n + c] - (float)k_mean[(size_t)bh * D + c] : 0.f;
-      vs[t * LD + c] = ok ? vh[(size_t)(t0 + t) * sin.n + c] : 0.f;
+    const int valid = min(kF32Tokens, N - sel[s] * kF32Tokens);
+    __syncthreads();                      // previous tile fully consumed
+#pragma unroll
+    for (int x = 0; x < CM::kLoads; x++) {
+      const int t = trow + x * CM::kRows;
+      const bool ok = t < valid;
+      f32x4 a = kr[x] - mu, e;
+#pragma unroll
+      for (int c = 0; c < 4; c++) e[c] = ok ? exp2_f32((a[c] - zr[x]) * kLog2e) : 0.f;
+      zacc += e;
+      *reinterpret_cast<f32x4*>(ks + t * LD + 4 * ch) = a;
+      *reinterpret_cast<f32x4*>(kp + t * LD + 4 * ch) = e;
+      *reinterpret_cast<f32x4*>(vs + t * LD + 4 * ch) = vr[x];   // rows past the end: finite, weighted with 0
     }
+    if (s + 1 < ksel) fetch(sel[s + 1]);
     __syncthreads();
-    // S = Q K'^T / sqrt(d): rows 4 ty + a, key tokens tx + 16 b
-    float sacc[4][4];
+    f32x16 sacc = channel_product<D>(ks + (32 * kh + lane % 32) * LD, qf, zero16(), g);
+    float mx = -INFINITY;
 #pragma unroll
-    for (int a = 0; a < 4; a++)
-#pragma unroll
-      for (int b = 0; b < 4; b++) sacc[a][b] = 0.f;
-    for (int c = 0; c < D; c++) {
-      float qv[4], kv[4];
-#pragma unroll
-      for (int a = 0; a < 4; a++) qv[a] = qs[(4 * ty + a) * LD + c];
-#pragma unroll
-      for (int b = 0; b < 4; b++) kv[b] = ks[(tx + 16 * b) * LD + c];
-#pragma unroll
-      for (int a = 0; a < 4; a++)
-#pragma unroll
-        for (int b = 0; b < 4; b++) sacc[a][b] += qv[a] * kv[b];
+    for (int e = 0; e < 16; e++) {
+      const bool ok = 32 * kh + 8 * (e / 4) + 4 * g + e % 4 < valid;
+      sacc[e] = ok ? sacc[e] * c0 : -INFINITY;
+      mx = fmaxf(mx, sacc[e]);
     }
-    float corr[4];
+    mx = both_halves_max(mx);
+    const float m_new = fmaxf(m_run, mx);
+    const float m_ref = m_new == -INFINITY ? 0.f : m_new;        // no key of this half seen yet (short last block)
+    const float corr = exp2_f32(m_run - m_ref);
+    float rs = 0.f;
 #pragma unroll
-    for (int a = 0; a < 4; a++) {
-      float mx = -INFINITY;
-#pragma unroll
-      for (int b = 0; b < 4; b++) {
-        sacc[a][b] = (tx + 16 * b) < valid ? sacc[a][b] * rscale : -INFINITY;
-        mx = fmaxf(mx, sacc[a][b]);
-      }
-#pragma unroll
-      for (int o = 1; o < 16; o <<= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
-      const float m_new = fmaxf(m_run[a], mx);        // finite: every block holds at least one token
-      float rs = 0.f;
-#pragma unroll
-      for (int b = 0; b < 4; b++) {
-        float p = __expf(sacc[a][b] - m_new);
-        ps[(4 * ty + a) * LP + tx + 16 * b] = p;
-        rs += p;
-      }
-#pragma unroll
-      for (int o = 1; o < 16; o <<= 1) rs += __shfl_xor(rs, o);
-      corr[a] = __expf(m_run[a] - m_new);             // exp(-inf) = 0 on the first block
-      l_run[a] = l_run[a] * corr[a] + rs;
-      m_run[a] = m_new;
+    for (int e = 0; e < 16; e++) {
+      sacc[e] = exp2_f32(sacc[e] - m_ref);
+      rs += sacc[e];
     }
-    __syncthreads();                                  // ps complete; ks no longer read as K'
-    // K' -> K^phi in place, from the per-token statistics
-    for (int idx = tid; idx < kBK * D; idx += 256) {
-      int t = idx / D, c = idx % D;
-      float kp = 0.f;
-      if (t < valid) kp = __expf(ks[t * LD + c] - k_stats[(size_t)bh * N + t0 + t]);
-      ks[t * LD + c] = kp;
-    }
-    // O = diag(corr) O + P V
+    l_run = l_run * corr + both_halves_sum(rs);
+    m_run = m_new;
 #pragma unroll
-    for (int a = 0; a < 4; a++)
+    for (int et = 0; et < ET; et++) oacc[et] *= corr;
+    const float* va = vs + (32 * kh + 4 * g) * LD + lane % 32;
 #pragma unroll
-      for (int b = 0; b < OC; b++) oacc[a][b] *= corr[a];
-    for (int t = 0; t < kBK; t++) {
-      float pv[4], vv[OC];
+    for (int e = 0; e < 16; e++)
 #pragma unroll
-      for (int a = 0; a < 4; a++) pv[a] = ps[(4 * ty + a) * LP + t];
-#pragma unroll
-      for (int b = 0; b < OC; b++) vv[b] = vs[t * LD + tx + 16 * b];
-#pragma unroll
-      for (int a = 0; a < 4; a++)
-#pragma unroll
-        for (int b = 0; b < OC; b++) oacc[a][b] += pv[a] * vv[b];
-    }
-    __syncthreads();                                  // K^phi complete
-    for (int t = 0; t < kBK; t++) {
-      float kv[MT], vv[MT];
-#pragma unroll
-      for (int a = 0; a < MT; a++) kv[a] = ks[t * LD + MT * ty + a];
-#pragma unroll
-      for (int b = 0; b < MT; b++) vv[b] = vs[t * LD + tx + 16 * b];
-#pragma unroll
-      for (int a = 0; a < MT; a++)
-#pragma unroll
-        for (int b = 0; b < MT; b++) hacc[a][b] += kv[a] * vv[b];
-    }
-    if (tid < D)
-      for (int t = 0; t < kBK; t++) zacc += ks[t * LD + tid];
+      for (int et = 0; et < ET; et++) oacc[et] = mfma_f32(va[(8 * (e / 4) + e % 4) * LD + 32 * et], sacc[e], oacc[et]);
+    if (SS::active(w)) state_product<D, NW>(hacc, kp, vs, kF32Tokens, w, lane);
   }
   __syncthreads();
 
-  // ---- linear branch ----
-  const bool all_selected = ksel >= Tn;               // nothing left for the linear branch: O_l = 0
-  const float* ht = h_total + (size_t)bh * D * D;
+  // ---- H_i = H_total - sum, Z_i likewise; the two key halves exchange m and l ----
+  if (SS::active(w)) {
+    const float* ht = h_total + (size_t)bh * D * D;
+    float* hsv = h_save != nullptr ? h_save + ((size_t)bh * Tm + i) * D * D : nullptr;
 #pragma unroll
-  for (int a = 0; a < MT; a++)
+    for (int x = 0; x < SS::kTiles; x++)
 #pragma unroll
-    for (int b = 0; b < MT; b++) {
-      int c = MT * ty + a, e = tx + 16 * b;
-      hs[c * D + e] = ht[c * D + e] - hacc[a][b];
-    }
-  if (tid < D) zs[tid] = z_total[(size_t)bh * D + tid] - zacc;
-  {  // Q^phi = softmax_d(Q) in place, 4 threads per row
-    const int r = tid / 4, sub = tid % 4;
-    float m = -INFINITY;
-    for (int c = sub; c < D; c += 4) m = fmaxf(m, qs[r * LD + c]);
-    m = fmaxf(m, __shfl_xor(m, 1));
-    m = fmaxf(m, __shfl_xor(m, 2));
-    float sum = 0.f;
-    for (int c = sub; c < D; c += 4) {
-      float e = __expf(qs[r * LD + c] - m);
-      qs[r * LD + c] = e;
-      sum += e;
-    }
-    sum += __shfl_xor(sum, 1);
-    sum += __shfl_xor(sum, 2);
-    const float inv = 1.f / sum;
-    for (int c = sub; c < D; c += 4) qs[r * LD + c] *= inv;
+      for (int e = 0; e < 16; e++) {
+        const int c = 32 * SS::mt(w) + 8 * (e / 4) + 4 * g + e % 4, col = 32 * (SS::nt(w) + x) + lane % 32;
+        const float y = ht[c * D + col] - hacc[x][e];
+        hs[c * LD + col] = y;
+        if (hsv != nullptr) hsv[c * D + col] = y;
+      }
+  }
+  *reinterpret_cast<f32x4*>(swap + trow * D + 4 * ch) = zacc;
+  if (g == 0) {
+    ml[w * 64 + lane] = m_run;
+    ml[w * 64 + 32 + lane] = l_run;
   }
   __syncthreads();
-  float lacc[4][OC], den[4];
+  if (tid < D) {
+    float z = 0.f;
 #pragma unroll
-  for (int a = 0; a < 4; a++) {
-    den[a] = 0.f;
-#pragma unroll
-    for (int b = 0; b < OC; b++) lacc[a][b] = 0.f;
+    for (int r = 0; r < CM::kRows; r++) z += swap[r * D + tid];
+    z = z_total[(size_t)bh * D + tid] - z;
+    zs[tid] = z;
+    if (z_save != nullptr) z_save[((size_t)bh * Tm + i) * D + tid] = z;
   }
-  for (int c = 0; c < D; c++) {
-    float qv[4], hv[OC];
-    const float zc = zs[c];
+  const float m_o = ml[(w ^ 1) * 64 + lane % 32], l_o = ml[(w ^ 1) * 64 + 32 + lane % 32];
+  const float m_all = fmaxf(m_run, m_o), m_ref = m_all == -INFINITY ? 0.f : m_all;
+  const float mine = exp2_f32(m_run - m_ref), l = l_run * mine + l_o * exp2_f32(m_o - m_ref);
 #pragma unroll
-    for (int a = 0; a < 4; a++) qv[a] = qs[(4 * ty + a) * LD + c];
+  for (int et = 0; et < ET; et++) oacc[et] *= mine;
+  // Q^phi = softmax_d(Q) of this lane's row
+  float qm = -INFINITY;
 #pragma unroll
-    for (int b = 0; b < OC; b++) hv[b] = hs[c * D + tx + 16 * b];
+  for (int j = 0; j < J; j++)
 #pragma unroll
-    for (int a = 0; a < 4; a++) {
-      den[a] += qv[a] * zc;
+    for (int x = 0; x < 4; x++) qm = fmaxf(qm, qf[j][x]);
+  qm = both_halves_max(qm);
+  float qs = 0.f;
 #pragma unroll
-      for (int b = 0; b < OC; b++) lacc[a][b] += qv[a] * hv[b];
+  for (int j = 0; j < J; j++)
+#pragma unroll
+    for (int x = 0; x < 4; x++) {
+      qf[j][x] = exp2_f32((qf[j][x] - qm) * kLog2e);
+      qs += qf[j][x];
     }
+  const float qinv = 1.f / both_halves_sum(qs);
+#pragma unroll
+  for (int j = 0; j < J; j++) qf[j] *= qinv;
+  __syncthreads();                        // Z_i visible, the column sums have been read
+  float den = 0.f;
+#pragma unroll
+  for (int j = 0; j < J; j++) {
+    const f32x4 z = *reinterpret_cast<const f32x4*>(zs + 8 * j + 4 * g);
+#pragma unroll
+    for (int x = 0; x < 4; x++) den += qf[j][x] * z[x];
   }
-  // ---- mix and store ----
+  den = both_halves_sum(den);
+  const bool all_selected = ksel >= Tn;   // nothing left for the linear branch: O_l = 0
+  const float inv_l = l > 0.f ? 1.f / l : 0.f, inv_den = all_selected ? 0.f : 1.f / den;
   const float al = alpha[alpha_per_block ? (size_t)h * Tm + i : (size_t)h];
+
+  // Each of the two waves of a row group finishes half of the channel tiles: it hands the other half of its O^T over.
+  float* mine_out = swap + (size_t)w * (ET / 2) * 16 * kWave + lane;
+  const float* other = swap + (size_t)(w ^ 1) * (ET / 2) * 16 * kWave + lane;
+  auto finish = [&](auto half) {
+    constexpr int E0 = decltype(half)::value * (ET / 2), F0 = ET / 2 - E0;      // own tiles, tiles handed over
 #pragma unroll
-  for (int a = 0; a < 4; a++) {
-    const int r = 4 * ty + a;
-    if (r >= rows_valid) continue;
-    const float inv_l = l_run[a] > 0.f ? 1.f / l_run[a] : 0.f;
-    const float inv_den = all_selected ? 0.f : 1.f / den[a];
-    float* o = out + head_offset(sout, bh, H) + (size_t)(row0 + r) * sout.n;
+    for (int x = 0; x < ET / 2; x++)
 #pragma unroll
-    for (int b = 0; b < OC; b++) o[tx + 16 * b] = al * oacc[a][b] * inv_l + (1.f - al) * lacc[a][b] * inv_den;
-    const float L = l_run[a] > 0.f ? m_run[a] + __logf(l_run[a]) : -INFINITY;
-    if (lse && tx == 0) lse[(size_t)bh * N + row0 + r] = L;
-    if (o_s_save) {                                   // the two branches and L, kept for the backward pass
-      const size_t at = ((size_t)bh * N + row0 + r) * D;
+      for (int e = 0; e < 16; e++) mine_out[(x * 16 + e) * kWave] = oacc[F0 + x][e];
+    __syncthreads();
 #pragma unroll
-      for (int b = 0; b < OC; b++) {
-        o_s_save[at + tx + 16 * b] = oacc[a][b] * inv_l;
-        o_l_save[at + tx + 16 * b] = lacc[a][b] * inv_den;
+    for (int x = 0; x < ET / 2; x++) {
+      constexpr int et0 = E0;
+      const int et = et0 + x;
+#pragma unroll
+      for (int e = 0; e < 16; e++) oacc[et][e] += other[(x * 16 + e) * kWave];
+      f32x16 lacc = zero16();
+      const float* ha = hs + 4 * g * LD + 32 * et + lane % 32;
+#pragma unroll
+      for (int j = 0; j < J; j++)
+#pragma unroll
+        for (int y = 0; y < 4; y++) lacc = mfma_f32(ha[(8 * j + y) * LD], qf[j][y], lacc);
+      if (row_ok) {
+        float* o = out + head_offset(sout, bh, H) + (size_t)(row0 + qrow) * sout.n + 32 * et + 4 * g;
+        const size_t at = ((size_t)bh * N + row0 + qrow) * D + 32 * et + 4 * g;
+#pragma unroll
+        for (int v4 = 0; v4 < 4; v4++) {
+          f32x4 os, ol;
+#pragma unroll
+          for (int r = 0; r < 4; r++) {
+            os[r] = oacc[et][4 * v4 + r] * inv_l;
+            ol[r] = lacc[4 * v4 + r] * inv_den;
+          }
+          *reinterpret_cast<f32x4*>(o + 8 * v4) = al * os + (1.f - al) * ol;
+          if (o_s_save != nullptr) {      // the two branches, kept for the backward pass
+            *reinterpret_cast<f32x4*>(o_s_save + at + 8 * v4) = os;
+            *reinterpret_cast<f32x4*>(o_l_save + at + 8 * v4) = ol;
+          }
+        }
       }
-      if (tx == 0) lse_save[(size_t)bh * N + row0 + r] = L;
     }
+  };
+  if (kh == 0) finish(std::integral_constant<int, 0>());
+  else finish(std::integral_constant<int, 1>());
+  if (kh == 0 && g == 0 && row_ok) {
+    const float L = l > 0.f ? (m_all + __log2f(l)) * kLn2 : -INFINITY;
+    if (lse != nullptr) lse[(size_t)bh * N + row0 + qrow] = L;
+    if (lse_save != nullptr) lse_save[(size_t)bh * N + row0 + qrow] = L;
   }
 }
 
-template <int D>
+template <int D, int BQ>
 static hipError_t launch_attn_f32_t(const Shape& s, const float* q, const float* k, const float* v,
                                     const double* k_mean, const float* k_stats, const float* h_total,
                                     const float* z_total, const int32_t* block_idx, const float* alpha, float* out,
                                     float* lse, const SavedForBackward& sv, hipStream_t stream) {
-  size_t smem = ((size_t)3 * 64 * (D + 1) + 64 * 65 + D) * sizeof(float);
+  constexpr int smem = AttnF32Smem<D, BQ>::kBytes;
   static OncePerDevice once;
-  if (hipError_t e = allow_dynamic_lds(once, (const void*)attn_f32_kernel<D>, (int)smem); e != hipSuccess) return e;
-  dim3 grid((unsigned)((size_t)s.BH * s.Tm * (s.bq / kRowsF32)));
-  attn_f32_kernel<D><<<grid, 256, smem, stream>>>(q, k, v, k_mean, k_stats, h_total, z_total, block_idx, alpha, out,
-                                                  lse, (float*)sv.o_s, (float*)sv.o_l, sv.lse, s.sin, s.sout, s.H, s.N,
-                                                  s.bq, s.Tm, s.Tn, s.k,
-                                                  s.alpha_per_block ? 1 : 0);
+  if (hipError_t e = allow_dynamic_lds(once, (const void*)attn_f32_kernel<D, BQ>, smem); e != hipSuccess) return e;
+  attn_f32_kernel<D, BQ><<<dim3((unsigned)(s.BH * s.Tm)), BQ * 4, smem, stream>>>(
+      q, k, v, k_mean, k_stats, h_total, z_total, block_idx, alpha, out, lse, (float*)sv.o_s, (float*)sv.o_l, sv.lse,
+      (float*)sv.h_i, sv.z_i, s.sin, s.sout, s.H, s.N, s.Tm, s.Tn, s.k, s.alpha_per_block ? 1 : 0);
   return hipGetLastError();
 }
 
@@ -396,9 +400,13 @@ hipError_t launch_attn_f32(const Shape& s, const float* q, const float* k, const
                            const float* k_stats, const float* h_total, const float* z_total, const int32_t* block_idx,
                            const float* alpha, float* out, float* lse, const SavedForBackward& sv,
                            hipStream_t stream) {
-  if (s.d == 128)
-    return launch_attn_f32_t<128>(s, q, k, v, k_mean, k_stats, h_total, z_total, block_idx, alpha, out, lse, sv, stream);
-  return launch_attn_f32_t<64>(s, q, k, v, k_mean, k_stats, h_total, z_total, block_idx, alpha, out, lse, sv, stream);
+#define SLA2_F32(DD, QQ) \
+  return launch_attn_f32_t<DD, QQ>(s, q, k, v, k_mean, k_stats, h_total, z_total, block_idx, alpha, out, lse, sv, stream)
+  if (s.d == 128 && s.bq == 128) SLA2_F32(128, 128);
+  if (s.d == 128) SLA2_F32(128, 64);
+  if (s.bq == 128) SLA2_F32(64, 128);
+  SLA2_F32(64, 64);
+#undef SLA2_F32
 }
 
 }  // namespace sla2
