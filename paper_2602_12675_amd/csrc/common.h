@@ -23,6 +23,7 @@ typedef __attribute__((ext_vector_type(4))) int i32x4;            // operand of 
 typedef __attribute__((ext_vector_type(16))) int i32x16;          // its 32 x 32 accumulator
 
 constexpr int kWave = 64;
+constexpr int kXcds = 8;                // L2 domains; workgroups are dealt to them round-robin
 constexpr int kMaxKeyBlocks = 2048;   // router keeps a whole score row in registers
 constexpr float kE4M3Max = 448.0f;
 constexpr float kInt8Max = 127.0f;   // symmetric INT8 code range of Q and K
@@ -107,9 +108,10 @@ struct BwdArgs {
   // scratch.  dh: one d x d slot per query block, element type of the tensors; lraw: L log2(e) per row (bf16: on the raw keys)
   float *ds, *lraw, *dz, *dh_total, *dz_total, *colsum, *dk_mean, *dalpha_part;
   void* dh;
-  int32_t *col_ptr, *col_idx, *col_cnt;
-  uint32_t* mask_bits;                       // M_c as bits, [BH, T_m, ceil(T_n / 32)]
+  int32_t *col_ptr, *col_idx, *col_cnt;      // per key block the query blocks that selected it: offsets, lists, lengths
+  int32_t* order;                            // [bwd_kv_grid] the key block (bh kMaxKeyBlocks + j, or -1) of every bwd_kv workgroup
 };
+inline size_t bwd_kv_grid(const Shape& s) { return (size_t)s.BH * kXcds * ((s.Tn + kXcds - 1) / kXcds); }
 // the backward pass in the order it runs: lists, query side, totals, key side, finish
 hipError_t launch_bwd_lists(const Shape& s, const BwdArgs& a, hipStream_t stream);
 hipError_t launch_bwd_q(const Shape& s, const BwdArgs& a, hipStream_t stream);

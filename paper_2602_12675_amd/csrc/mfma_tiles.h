@@ -16,7 +16,6 @@
 namespace sla2 {
 
 constexpr int kTileTokens = 64;                    // b_kv
-constexpr int kXcds = 8;                           // L2 domains; workgroups are dealt to them round-robin
 constexpr int kVmcnt0 = 0x0F70;                    // s_waitcnt vmcnt(0), other counters untouched
 
 // lanes l and l ^ 32 combine their values; both get the same bits

@@ -73,14 +73,14 @@ int make_shape(const sla2_params* p, Shape* s) {
 
 // scratch of the backward pass, carved out of the `bwd` region of the workspace
 struct BwdLayout {
-  size_t ds, dh, dz, dh_total, dz_total, colsum, dk_mean, dalpha_part, col_ptr, col_idx, col_cnt, mask_bits, h_i, z_i, lraw, total;
+  size_t ds, dh, dz, dh_total, dz_total, colsum, dk_mean, dalpha_part, col_ptr, col_idx, col_cnt, order, h_i, z_i, lraw, total;
 };
 static BwdLayout make_bwd_layout(const Shape& s) {
   BwdLayout B;
   size_t off = 0, BH = (size_t)s.BH, d = (size_t)s.d;
   auto take = [&](size_t bytes) { size_t o = off; off = align256(off + bytes); return o; };
   const size_t slots = BH * s.Tm, esz = s.bf16 ? 2 : 4;   // dH_i, dZ_i, H_i, Z_i, d alpha parts: one slot per query block
-  B.ds = take(BH * (size_t)s.N * sizeof(float));
+  B.ds = take(slots * s.bq * sizeof(float));           // ds, lraw: whole query blocks
   B.dh = take(slots * d * d * esz);
   B.dz = take(slots * d * sizeof(float));
   B.dh_total = take(BH * d * d * sizeof(float));
@@ -91,10 +91,10 @@ static BwdLayout make_bwd_layout(const Shape& s) {
   B.col_ptr = take(BH * (size_t)(s.Tn + 1) * sizeof(int32_t));
   B.col_idx = take(BH * s.Tm * (size_t)(s.k > 0 ? s.k : 1) * sizeof(int32_t));
   B.col_cnt = take(BH * (size_t)s.Tn * sizeof(int32_t));
-  B.mask_bits = take(BH * s.Tm * (size_t)((s.Tn + 31) / 32) * sizeof(uint32_t));
+  B.order = take(bwd_kv_grid(s) * sizeof(int32_t));
   B.h_i = take(slots * d * d * esz);                 // left here by the forward kernel
   B.z_i = take(slots * d * sizeof(float));
-  B.lraw = take(BH * (size_t)s.N * sizeof(float));
+  B.lraw = take(slots * s.bq * sizeof(float));
   B.total = off;
   return B;
 }
@@ -386,7 +386,7 @@ int sla2_backward(const sla2_params* params, const void* q, const void* k, const
   a.colsum = (float*)(bw + B.colsum); a.dk_mean = (float*)(bw + B.dk_mean);
   a.dalpha_part = (float*)(bw + B.dalpha_part);
   a.col_ptr = (int32_t*)(bw + B.col_ptr); a.col_idx = (int32_t*)(bw + B.col_idx);
-  a.mask_bits = (uint32_t*)(bw + B.mask_bits); a.col_cnt = (int32_t*)(bw + B.col_cnt);
+  a.col_cnt = (int32_t*)(bw + B.col_cnt); a.order = (int32_t*)(bw + B.order);
   hipStream_t st = (hipStream_t)hip_stream;
   count_call();
   if (SLA2_STAGE(SLA2_STAGE_BWD_LISTS, launch_bwd_lists(s, a, st)) != hipSuccess) return SLA2_EHIP;

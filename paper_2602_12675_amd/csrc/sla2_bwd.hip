@@ -5,129 +5,135 @@
 // This file holds the launch sequence and the small kernels every tensor type shares (deterministic: no float atomics,
 // fixed summation orders); the two heavy steps are in sla2_bwd_mfma.hip (bf16 tensors) and sla2_bwd_f32.hip.
 //
-//   bwd_mask_bits, bwd_col_count / _scan / _fill
-//                  M_c as bits, then for every key block j the ascending list of query blocks i with
-//                  M_c[i, j] = 1
+//   bwd_columns    for every key block j the ascending list of query blocks i with M_c[i, j] = 1
 //   (bwd_q)        per query block: D^s, D^l, d alpha parts, dQ, dH_i, dZ_i
-//   bwd_sum        dH_total = sum_i dH_i, dZ_total = sum_i dZ_i
+//   bwd_totals     dH_total = sum_i dH_i, dZ_total = sum_i dZ_i; the order in which bwd_kv takes the key blocks
 //   (bwd_kv)       per key block: dK', dV, column sums of dK'
-//   bwd_colmean, bwd_unsmooth, bwd_dalpha
-//                  dK = dK' - colmean(dK') (gradient of the smoothing), d alpha summed over its parts
+//   bwd_finish     colmean(dK'); d alpha summed over its parts
+//   bwd_unsmooth   dK = dK' - colmean(dK') (gradient of the smoothing)
+//
+// A launch costs 4.6 us however little it does, so what does not depend on each other shares one: this took eleven
+// launches before, 45 us of the 210 us of the pass on 32 heads of 4,096 tokens (d = 64).
 #include "common.h"
 
 namespace sla2 {
 
 // ---------------------------------------------------------------------------------------------
-// M_c as bits: row (bh, i) -> ceil(T_n / 32) words, bit j % 32 of word j / 32 set iff block j is selected
-__global__ __launch_bounds__(64) void bwd_mask_bits_kernel(const int32_t* __restrict__ block_idx,
-                                                           uint32_t* __restrict__ bits, int Tn, int ksel) {
-  __shared__ uint32_t words[kMaxKeyBlocks / 32];
-  const int W = (Tn + 31) / 32, tid = threadIdx.x;
-  for (int x = tid; x < W; x += 64) words[x] = 0u;
+// For every key block j of head bh: the ascending list of query blocks i with M_c[i, j] = 1, as offsets
+// col_ptr[bh][0..T_n] into col_idx[bh][.], and its length.  One workgroup per 64 columns of a head reads all index lists
+// of the head: entries of its own columns become bits (column x, bit i), those of earlier columns are counted - the
+// offset of its first list.  Then every thread writes out the bits of a few 32-row words at their places.
+__global__ __launch_bounds__(256) void bwd_columns_kernel(const int32_t* __restrict__ block_idx, int32_t* __restrict__ col_ptr,
+                                                          int32_t* __restrict__ col_idx, int32_t* __restrict__ counts, int Tm,
+                                                          int Tn, int ksel) {
+  extern __shared__ uint32_t words[];                 // [64][LW] bits, LW = W | 1 (odd: no bank conflicts down a column)
+  const int W = (Tm + 31) / 32, LW = W | 1;           // W <= 64
+  uint16_t* place = reinterpret_cast<uint16_t*>(words + 64 * LW);   // [64][LW] set bits of the column before the word
+  __shared__ int before[4], first[64];
+  const int j0 = blockIdx.x * 64, bh = blockIdx.y, tid = threadIdx.x, cols = min(64, Tn - j0);
+  const int lane = tid % kWave, wave = tid / kWave;
+  for (int x = tid; x < 64 * LW; x += 256) words[x] = 0u;
   __syncthreads();
-  const int32_t* row = block_idx + (size_t)blockIdx.x * ksel;
-  for (int s = tid; s < ksel; s += 64) {
-    const int j = row[s];
-    atomicOr(&words[j >> 5], 1u << (j & 31));         // OR: the result does not depend on the order
-  }
-  __syncthreads();
-  for (int x = tid; x < W; x += 64) bits[(size_t)blockIdx.x * W + x] = words[x];
-}
-
-// For every key block j of head bh: the ascending list of query blocks i with M_c[i, j] = 1, as
-// offsets col_ptr[bh][0..T_n] into col_idx[bh][.].  Three small kernels: column counts, their
-// exclusive scan, and the fill.  Counts and fill run one wave per (head, 32-column word): the wave
-// walks the bit rows 64 at a time, one ballot per column; the rank of a set bit inside the ballot
-// plus the running count of the column is its place in the (ascending) list.
-__global__ __launch_bounds__(64) void bwd_col_count_kernel(const uint32_t* __restrict__ bits, int32_t* __restrict__ counts,
-                                                           int Tm, int Tn) {
-  const int W = (Tn + 31) / 32, x = blockIdx.x, bh = blockIdx.y, lane = threadIdx.x;
-  const uint32_t* rows = bits + (size_t)bh * Tm * W + x;
-  int run[32];
-#pragma unroll
-  for (int b = 0; b < 32; b++) run[b] = 0;
-  for (int i0 = 0; i0 < Tm; i0 += 64) {
-    const int i = i0 + lane;
-    const uint32_t word = i < Tm ? rows[(size_t)i * W] : 0u;
-#pragma unroll
-    for (int b = 0; b < 32; b++) run[b] += __popcll(__ballot((word >> b) & 1u));
-  }
-  int mine = 0;
-#pragma unroll
-  for (int b = 0; b < 32; b++) mine = lane == b ? run[b] : mine;
-  const int j = 32 * x + lane;
-  if (lane < 32 && j < Tn) counts[(size_t)bh * Tn + j] = mine;
-}
-
-__global__ __launch_bounds__(256) void bwd_col_scan_kernel(const int32_t* __restrict__ counts, int32_t* __restrict__ col_ptr,
-                                                           int Tn) {
-  constexpr int PER = kMaxKeyBlocks / 256;
-  __shared__ int part[256];
-  const int bh = blockIdx.x, tid = threadIdx.x;
-  int v[PER], sum = 0;
-#pragma unroll
-  for (int y = 0; y < PER; y++) {
-    const int j = tid * PER + y;
-    v[y] = j < Tn ? counts[(size_t)bh * Tn + j] : 0;
-    sum += v[y];
-  }
-  part[tid] = sum;
-  __syncthreads();
-  if (tid == 0) {                                     // exclusive scan of the 256 partial sums, in place
-    int run = 0;
-    for (int t = 0; t < 256; t++) {
-      const int c = part[t];
-      part[t] = run;
-      run += c;
+  const int32_t* idx = block_idx + (size_t)bh * Tm * ksel;
+  const unsigned entries = (unsigned)Tm * (unsigned)ksel;
+  int earlier = 0;
+#pragma unroll 8
+  for (unsigned e = tid; e < entries; e += 256) {
+    const int j = idx[e] - j0;
+    earlier += j < 0;
+    if (j >= 0 && j < 64) {
+      const unsigned i = e / (unsigned)ksel;
+      atomicOr(&words[j * LW + (i >> 5)], 1u << (i & 31));   // OR: the result does not depend on the order
     }
   }
+#pragma unroll
+  for (int o = 1; o < kWave; o <<= 1) earlier += __shfl_xor(earlier, o);
+  if (lane == 0) before[wave] = earlier;
   __syncthreads();
-  int run = part[tid];
+  if (wave == 0) {                                    // one lane per column: places of its words, list length and offset
+    int n = 0;
+    for (int x = 0; x < W; x++) {
+      place[lane * LW + x] = (uint16_t)n;
+      n += __popc(words[lane * LW + x]);
+    }
+    int at = n;
 #pragma unroll
-  for (int y = 0; y < PER; y++) {
-    const int j = tid * PER + y;
-    if (j < Tn) col_ptr[(size_t)bh * (Tn + 1) + j] = run;
-    run += v[y];
-    if (j == Tn - 1) col_ptr[(size_t)bh * (Tn + 1) + Tn] = run;
+    for (int o = 1; o < kWave; o <<= 1) {
+      const int y = __shfl_up(at, o);
+      if (lane >= o) at += y;
+    }
+    at += before[0] + before[1] + before[2] + before[3];
+    first[lane] = at - n;
+    if (lane < cols) {
+      counts[(size_t)bh * Tn + j0 + lane] = n;
+      col_ptr[(size_t)bh * (Tn + 1) + j0 + lane + 1] = at;
+    }
+    if (j0 == 0 && lane == 0) col_ptr[(size_t)bh * (Tn + 1)] = 0;
   }
-}
-
-__global__ __launch_bounds__(64) void bwd_col_fill_kernel(const uint32_t* __restrict__ bits, const int32_t* __restrict__ col_ptr,
-                                                          int32_t* __restrict__ col_idx, int Tm, int Tn, int ksel) {
-  const int W = (Tn + 31) / 32, x = blockIdx.x, bh = blockIdx.y, lane = threadIdx.x;
-  const uint32_t* rows = bits + (size_t)bh * Tm * W + x;
+  __syncthreads();
   int32_t* out = col_idx + (size_t)bh * Tm * ksel;
-  int run[32];
-#pragma unroll
-  for (int b = 0; b < 32; b++) run[b] = 32 * x + b < Tn ? col_ptr[(size_t)bh * (Tn + 1) + 32 * x + b] : 0;
-  const unsigned long long below = (1ull << lane) - 1ull;
-  for (int i0 = 0; i0 < Tm; i0 += 64) {
-    const int i = i0 + lane;
-    const uint32_t word = i < Tm ? rows[(size_t)i * W] : 0u;
-#pragma unroll
-    for (int b = 0; b < 32; b++) {
-      const unsigned long long m = __ballot((word >> b) & 1u);
-      if ((word >> b) & 1u) out[run[b] + __popcll(m & below)] = i;
-      run[b] += __popcll(m);
+  for (int x = tid; x < 64 * W; x += 256) {
+    const int c = x % 64, y = x / 64;
+    uint32_t word = words[c * LW + y];
+    int at = first[c] + place[c * LW + y];
+    while (word) {
+      out[at++] = 32 * y + __ffs(word) - 1;
+      word &= word - 1u;
     }
   }
 }
 
 // ---------------------------------------------------------------------------------------------
-// dst[bh][e] = sum over b < count of src[bh][b][e].  A workgroup covers 256 consecutive e: 32 threads
-// of 8 elements each, times 8 interleaved subsets of b that are combined in a fixed order.
+// The order in which bwd_kv takes the key blocks.  Its work on a key block is proportional to the length of the block's
+// list, which varies a lot (mean 7.5, longest 38 on 512 key blocks): a long list that starts last runs on alone.  So long
+// ones go first - but only among blocks that would share a cache anyway: neighbouring key blocks are selected by the same
+// query blocks, whose rows they gather.  Every head is cut into 8 runs of consecutive key blocks, one per XCD (workgroup p
+// runs on XCD p % 8), and the runs of a group of heads are each taken longest list first (a counting sort on the length,
+// cut off at 255).  The order decides when a block is worked on, never what is summed.
+__device__ void order_group(const int32_t* __restrict__ counts, int32_t* __restrict__ order, int h0, int h1, int Tn,
+                            int* hist /* LDS [8 x 256] */) {
+  const int tid = threadIdx.x, per_head = (Tn + kXcds - 1) / kXcds, n = (h1 - h0) * Tn;
+  int32_t* out = order + (size_t)h0 * kXcds * per_head;
+  for (int x = tid; x < kXcds * 256; x += 256) hist[x] = 0;
+  for (int x = tid; x < (h1 - h0) * kXcds * per_head; x += 256) out[x] = -1;   // places a short last run leaves empty
+  __syncthreads();
+  auto bin = [&](int e) { return (e % Tn) / per_head * 256 + 255 - min(counts[(size_t)h0 * Tn + e], 255); };
+  for (int e = tid; e < n; e += 256) atomicAdd(&hist[bin(e)], 1);
+  __syncthreads();
+  for (int x = tid / kWave; x < kXcds; x += 4) {      // per XCD an exclusive scan of its 256 bins, 4 per lane
+    const int lane = tid % kWave;
+    int c[4], sum = 0;
+#pragma unroll
+    for (int y = 0; y < 4; y++) { c[y] = hist[256 * x + 4 * lane + y]; sum += c[y]; }
+    int run = sum;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+      const int y = __shfl_up(run, o);
+      if (lane >= o) run += y;
+    }
+    run -= sum;
+#pragma unroll
+    for (int y = 0; y < 4; y++) { hist[256 * x + 4 * lane + y] = run; run += c[y]; }
+  }
+  __syncthreads();
+  for (int e = tid; e < n; e += 256) {
+    const int b = bin(e);
+    out[kXcds * atomicAdd(&hist[b], 1) + b / 256] = (h0 + e / Tn) * kMaxKeyBlocks + e % Tn;
+  }
+}
+
+// dst[e] = sum over b < count of src[b][e] for the 256 entries from e0 on.  32 threads of 8 elements each, times 8
+// interleaved subsets of b that are combined in a fixed order.
 template <typename S>
-__global__ __launch_bounds__(256) void bwd_sum_kernel(const S* __restrict__ src, float* __restrict__ dst, int count,
-                                                      int len) {
-  __shared__ float part[8][256];
-  const int bh = blockIdx.y, tid = threadIdx.x, col = tid % 32, sub = tid / 32;
-  const int e0 = blockIdx.x * 256 + 8 * col;
+__device__ void sum_slots(const S* __restrict__ src, float* __restrict__ dst, int count, int len, int first, float (*part)[256]) {
+  const int tid = threadIdx.x, col = tid % 32, sub = tid / 32;
+  const int e0 = first + 8 * col;
   float acc[8];
 #pragma unroll
   for (int x = 0; x < 8; x++) acc[x] = 0.f;
   if (e0 < len) {
-    const S* p = src + (size_t)bh * count * len + e0;
-#pragma unroll 4
+    const S* p = src + e0;
+#pragma unroll 8
     for (int b = sub; b < count; b += 8) {
       float v[8];
       if constexpr (sizeof(S) == 2) {
@@ -146,31 +152,76 @@ __global__ __launch_bounds__(256) void bwd_sum_kernel(const S* __restrict__ src,
 #pragma unroll
   for (int x = 0; x < 8; x++) part[sub][8 * col + x] = acc[x];
   __syncthreads();
-  const int e = blockIdx.x * 256 + tid;
-  if (e < len) {
+  if (first + tid < len) {
     float t = 0.f;
 #pragma unroll
     for (int g = 0; g < 8; g++) t += part[g][tid];
-    dst[(size_t)bh * len + e] = t;
+    dst[first + tid] = t;
   }
 }
 
-// ---------------------------------------------------------------------------------------------
-// mean[bh][c] = sum_j colsum[bh][j][c] / N: 1024 / d interleaved subsets of j, combined in a fixed order
-__global__ __launch_bounds__(1024) void bwd_colmean_kernel(const float* __restrict__ colsum, float* __restrict__ mean,
-                                                           int Tn, int N, int d) {
-  __shared__ float part[1024];
-  const int bh = blockIdx.x, tid = threadIdx.x, c = tid % d, sub = tid / d, subs = 1024 / d;
-  float s = 0.f;
-#pragma unroll 4
-  for (int j = sub; j < Tn; j += subs) s += colsum[((size_t)bh * Tn + j) * d + c];
-  part[tid] = s;
-  __syncthreads();
-  if (tid < d) {
-    float t = 0.f;
-    for (int g = 0; g < subs; g++) t += part[g * d + tid];
-    mean[(size_t)bh * d + tid] = t / (float)N;
+// workgroups: `groups` of order_group, then per head the 256-entry slices of dH_total and one for dZ_total
+template <typename S>
+__global__ __launch_bounds__(256) void bwd_totals_kernel(const S* __restrict__ dh, const float* __restrict__ dz,
+                                                         float* __restrict__ dh_total, float* __restrict__ dz_total,
+                                                         const int32_t* __restrict__ counts, int32_t* __restrict__ order,
+                                                         int groups, int heads_per_group, int BH, int Tm, int Tn, int d) {
+  __shared__ float part[8][256];
+  if ((int)blockIdx.x < groups) {
+    const int h0 = blockIdx.x * heads_per_group, h1 = min(BH, h0 + heads_per_group);
+    order_group(counts, order, h0, h1, Tn, reinterpret_cast<int*>(&part[0][0]));
+    return;
   }
+  const int slices = d * d / 256 + 1, id = blockIdx.x - groups, bh = id / slices, x = id % slices;
+  if (x + 1 < slices) sum_slots<S>(dh + (size_t)bh * Tm * d * d, dh_total + (size_t)bh * d * d, Tm, d * d, 256 * x, part);
+  else sum_slots<float>(dz + (size_t)bh * Tm * d, dz_total + (size_t)bh * d, Tm, d, 0, part);
+}
+
+// ---------------------------------------------------------------------------------------------
+// workgroups: per head d / 32 for mean[bh][c] = sum_j colsum[bh][j][c] / N, 32 channels and 32 interleaved subsets of j
+// each; then d alpha, per head [H] (one workgroup per head: sum over batch and query blocks) or per query block [H, T_m]
+// (1,024 outputs per workgroup: sum over batch).  Sums are combined in a fixed order.
+__global__ __launch_bounds__(1024) void bwd_finish_kernel(const float* __restrict__ colsum, float* __restrict__ mean,
+                                                          const float* __restrict__ part, float* __restrict__ dalpha,
+                                                          int mean_blocks, int B, int H, int N, int Tm, int Tn, int d,
+                                                          int alpha_per_block) {
+  __shared__ float red[1024];
+  const int tid = threadIdx.x;
+  if ((int)blockIdx.x < mean_blocks) {
+    const int per_head = d / 32, bh = blockIdx.x / per_head, c = 32 * (blockIdx.x % per_head) + tid % 32, sub = tid / 32;
+    float s = 0.f;
+#pragma unroll 8
+    for (int j = sub; j < Tn; j += 32) s += colsum[((size_t)bh * Tn + j) * d + c];
+    red[tid] = s;
+    __syncthreads();
+    if (tid < 32) {
+      float t = 0.f;
+#pragma unroll
+      for (int g = 0; g < 32; g++) t += red[g * 32 + tid];
+      mean[(size_t)bh * d + c] = t / (float)N;
+    }
+    return;
+  }
+  const int x = blockIdx.x - mean_blocks;
+  if (alpha_per_block) {
+    const int o = x * 1024 + tid;                     // output h T_m + i
+    if (o < H * Tm) {
+      float s = 0.f;
+      for (int b = 0; b < B; b++) s += part[(size_t)b * H * Tm + o];
+      dalpha[o] = s;
+    }
+    return;
+  }
+  float s = 0.f;
+  for (int y = tid; y < B * Tm; y += 1024) s += part[((size_t)(y / Tm) * H + x) * Tm + y % Tm];
+  red[tid] = s;
+  __syncthreads();
+#pragma unroll
+  for (int o = 512; o > 0; o >>= 1) {
+    if (tid < o) red[tid] += red[tid + o];
+    __syncthreads();
+  }
+  if (tid == 0) dalpha[x] = red[0];
 }
 
 // dK = dK' - colmean(dK'): the gradient of K' = K - colmean(K); 8 elements (of one row) per thread
@@ -194,36 +245,12 @@ __global__ __launch_bounds__(256) void bwd_unsmooth_kernel(T* __restrict__ dk, c
   }
 }
 
-// d alpha: per head [H] (sum over batch and query blocks) or per query block [H, T_m] (over batch).  One workgroup per output; thread t adds the parts t, t + 256, .. and thread 0 the 256 sums.
-__global__ __launch_bounds__(256) void bwd_dalpha_kernel(const float* __restrict__ part, float* __restrict__ dalpha, int B,
-                                                         int H, int Tm, int alpha_per_block) {
-  __shared__ float red[256];
-  const int x = blockIdx.x, tid = threadIdx.x;
-  const int h = alpha_per_block ? x / Tm : x;
-  const int per_b = alpha_per_block ? 1 : Tm;                      // consecutive parts of one batch entry
-  float s = 0.f;
-  for (int y = tid; y < B * per_b; y += 256) {
-    const int b = y / per_b, z = y % per_b;
-    const size_t first = (size_t)(b * H + h) * Tm + (alpha_per_block ? x % Tm : 0);
-    s += part[first + z];
-  }
-  red[tid] = s;
-  __syncthreads();
-  if (tid == 0) {
-    float t = 0.f;
-    for (int y = 0; y < 256; y++) t += red[y];
-    dalpha[x] = t;
-  }
-}
-
 // ---------------------------------------------------------------------------------------------
 hipError_t launch_bwd_lists(const Shape& s, const BwdArgs& a, hipStream_t stream) {
-  // k = 0: every list is empty (the bit rows are all zero)
-  bwd_mask_bits_kernel<<<dim3((unsigned)(s.BH * s.Tm)), 64, 0, stream>>>(a.block_idx, a.mask_bits, s.Tn, s.k);
-  const dim3 words((unsigned)((s.Tn + 31) / 32), (unsigned)s.BH);
-  bwd_col_count_kernel<<<words, 64, 0, stream>>>(a.mask_bits, a.col_cnt, s.Tm, s.Tn);
-  bwd_col_scan_kernel<<<dim3((unsigned)s.BH), 256, 0, stream>>>(a.col_cnt, a.col_ptr, s.Tn);
-  bwd_col_fill_kernel<<<words, 64, 0, stream>>>(a.mask_bits, a.col_ptr, a.col_idx, s.Tm, s.Tn, s.k);
+  // k = 0: every column is empty
+  const size_t smem = (size_t)64 * (((s.Tm + 31) / 32) | 1) * (sizeof(uint32_t) + sizeof(uint16_t));   // at most 25 KB (T_m <= 2048)
+  bwd_columns_kernel<<<dim3((unsigned)((s.Tn + 63) / 64), (unsigned)s.BH), 256, smem, stream>>>(a.block_idx, a.col_ptr, a.col_idx,
+                                                                                               a.col_cnt, s.Tm, s.Tn, s.k);
   return hipGetLastError();
 }
 
@@ -232,11 +259,22 @@ hipError_t launch_bwd_q(const Shape& s, const BwdArgs& a, hipStream_t stream) {
 }
 
 hipError_t launch_bwd_totals(const Shape& s, const BwdArgs& a, hipStream_t stream) {
-  const int D = s.d, count = s.Tm;
-  const dim3 grid_h((unsigned)((D * D + 255) / 256), (unsigned)s.BH), grid_z((unsigned)((D + 255) / 256), (unsigned)s.BH);
-  if (s.bf16) bwd_sum_kernel<uint16_t><<<grid_h, 256, 0, stream>>>((const uint16_t*)a.dh, a.dh_total, count, D * D);
-  else bwd_sum_kernel<float><<<grid_h, 256, 0, stream>>>((const float*)a.dh, a.dh_total, count, D * D);
-  bwd_sum_kernel<float><<<grid_z, 256, 0, stream>>>(a.dz, a.dz_total, count, D);
+  // Heads per order group.  What a head's key blocks gather: the Q and dO rows and the dH_i slots.  A group of more heads
+  // ends in fewer stragglers, one of fewer keeps what is in flight closer to the caches; the sum of both is flat around
+  // 48 MB a group (two heads of 32,760 tokens, d = 128: training step 1,801 us against 1,827 with one and 1,863 with four;
+  // one head of 75,600: bwd_kv 11.9 ms against 12.8 with eight; 32 heads of 4,096, d = 64: 246 us against 263 with one).
+  // fp32 products take long enough that only the stragglers count.
+  const size_t head_bytes = ((size_t)2 * s.N * s.d + (size_t)s.Tm * s.d * s.d) * (s.bf16 ? 2 : 4);
+  const size_t fit = ((size_t)(s.bf16 ? 48 : 192) << 20) / head_bytes;
+  const int heads = fit < 1 ? 1 : fit > (size_t)s.BH ? s.BH : (int)fit;
+  const int groups = (s.BH + heads - 1) / heads;
+  const dim3 grid((unsigned)(groups + s.BH * (s.d * s.d / 256 + 1)));
+  if (s.bf16)
+    bwd_totals_kernel<uint16_t><<<grid, 256, 0, stream>>>((const uint16_t*)a.dh, a.dz, a.dh_total, a.dz_total, a.col_cnt, a.order,
+                                                          groups, heads, s.BH, s.Tm, s.Tn, s.d);
+  else
+    bwd_totals_kernel<float><<<grid, 256, 0, stream>>>((const float*)a.dh, a.dz, a.dh_total, a.dz_total, a.col_cnt, a.order, groups,
+                                                       heads, s.BH, s.Tm, s.Tn, s.d);
   return hipGetLastError();
 }
 
@@ -245,16 +283,15 @@ hipError_t launch_bwd_kv(const Shape& s, const BwdArgs& a, hipStream_t stream) {
 }
 
 hipError_t launch_bwd_finish(const Shape& s, const BwdArgs& a, hipStream_t stream) {
-  const int D = s.d;
+  const int D = s.d, mean_blocks = s.smooth ? s.BH * (D / 32) : 0;
+  const int alpha_blocks = s.alpha_per_block ? (s.H * s.Tm + 1023) / 1024 : s.H;
+  bwd_finish_kernel<<<dim3((unsigned)(mean_blocks + alpha_blocks)), 1024, 0, stream>>>(
+      a.colsum, a.dk_mean, a.dalpha_part, a.dalpha, mean_blocks, s.B, s.H, s.N, s.Tm, s.Tn, D, s.alpha_per_block ? 1 : 0);
   if (s.smooth) {
-    bwd_colmean_kernel<<<dim3((unsigned)s.BH), 1024, 0, stream>>>(a.colsum, a.dk_mean, s.Tn, s.N, D);
     const dim3 grid((unsigned)(((size_t)s.N * D / 8 + 255) / 256), (unsigned)s.BH);
     if (s.bf16) bwd_unsmooth_kernel<uint16_t><<<grid, 256, 0, stream>>>((uint16_t*)a.dk, a.dk_mean, s.sin, s.H, s.N, D);
     else bwd_unsmooth_kernel<float><<<grid, 256, 0, stream>>>((float*)a.dk, a.dk_mean, s.sin, s.H, s.N, D);
   }
-  const int n_alpha = s.alpha_per_block ? s.H * s.Tm : s.H;
-  bwd_dalpha_kernel<<<dim3((unsigned)n_alpha), 256, 0, stream>>>(a.dalpha_part, a.dalpha, s.B, s.H, s.Tm,
-                                                                 s.alpha_per_block ? 1 : 0);
   return hipGetLastError();
 }
 

@@ -130,9 +130,9 @@ __global__ __launch_bounds__(BQ * 4, BQ / 64) void bwd_q_f32_kernel(
   }
   const float Ds = al * rows[qrow], Dl = (1.f - al) * rows[BQ + qrow];
   const float L2 = lse[(size_t)bh * N + row0 + min(qrow, rows_valid - 1)] * kLog2e;
-  if (kh == 0 && g == 0 && row_ok) {      // as the key-side kernel uses them
-    ds_out[(size_t)bh * N + row0 + qrow] = Ds;
-    l2_out[(size_t)bh * N + row0 + qrow] = L2;
+  if (kh == 0 && g == 0) {                // as the key-side kernel uses them: rows past the end get exp2(-inf) = 0 there
+    ds_out[slot * BQ + qrow] = row_ok ? Ds : 0.f;
+    l2_out[slot * BQ + qrow] = row_ok ? L2 : INFINITY;
   }
 
   f32x16 dqacc[ET];
@@ -321,7 +321,7 @@ template <int D, int BQ>
 __global__ __launch_bounds__(256, 1) void bwd_kv_f32_kernel(
     const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v, const float* __restrict__ dout,
     const float* __restrict__ l2_in, const float* __restrict__ ds_in, const double* __restrict__ k_mean,
-    const float* __restrict__ k_stats, const int32_t* __restrict__ col_ptr, const int32_t* __restrict__ col_idx,
+    const float* __restrict__ k_stats, const int32_t* __restrict__ col_ptr, const int32_t* __restrict__ col_idx, const int32_t* __restrict__ order,
     const float* __restrict__ dh_in, const float* __restrict__ dz_in, const float* __restrict__ dh_total,
     const float* __restrict__ dz_total, const float* __restrict__ alpha, float* __restrict__ dk, float* __restrict__ dv,
     float* __restrict__ colsum, Strides sin, Strides sout, int H, int N, int Tm, int Tn, int ksel, int alpha_per_block) {
@@ -338,7 +338,9 @@ __global__ __launch_bounds__(256, 1) void bwd_kv_f32_kernel(
   float* dzs = smem + SM::kDzOff;
   float* dots = smem + SM::kDotOff;
 
-  const int j = blockIdx.x % Tn, bh = blockIdx.x / Tn, h = bh % H;
+  const int entry = __builtin_amdgcn_readfirstlane(order[blockIdx.x]);
+  if (entry < 0) return;
+  const int j = entry & (kMaxKeyBlocks - 1), bh = entry / kMaxKeyBlocks, h = bh % H;
   const int tid = threadIdx.x, lane = tid % kWave, g = lane / 32, w = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int kh = w >> 1, rh = w & 1;      // 32 keys of the block, 32 rows of a step
   const int ch = tid % CM::kChunks, trow = tid / CM::kChunks;
@@ -350,20 +352,19 @@ __global__ __launch_bounds__(256, 1) void bwd_kv_f32_kernel(
   const float rscale = rsqrtf((float)D), c0 = kLog2e * rscale;
 
   const int32_t* cp = col_ptr + (size_t)bh * (Tn + 1);
-  const int32_t* ci = col_idx + (size_t)bh * Tm * ksel;
-  const int l0 = __builtin_amdgcn_readfirstlane(cp[j]), l1 = __builtin_amdgcn_readfirstlane(cp[j + 1]);
-  const int nsteps = (l1 - l0) * HP;
-  // Step t: rows [64 (t % HP), +64) of query block ci[l0 + t / HP]; a half block without rows runs on the block's first
-  // row with every probability masked.
+  const int l0 = __builtin_amdgcn_readfirstlane(cp[j]), listed = __builtin_amdgcn_readfirstlane(cp[j + 1]) - l0;
+  const int32_t* ci = col_idx + (size_t)bh * Tm * ksel + l0;   // the query blocks that selected this key block
+  const int nsteps = listed * HP;
+  // Step t: rows [64 (t % HP), +64) of query block ci[t / HP].  Rows past the end repeat an existing one; their L is
+  // +inf, so their probabilities are 0.
   f32x4 qr[CM::kLoads], gr[CM::kLoads];
   float lr = 0.f, dr = 0.f;
-  auto row0_of = [&](int t) { return ci[l0 + t / HP] * BQ + 64 * (t % HP); };
-  auto fetch = [&](int t) {
-    const int i = ci[l0 + t / HP], r0 = i * BQ + 64 * (t % HP), n = min(64, N - r0), src = n > 0 ? r0 : i * BQ;
-    CM::load(qr, qh + (size_t)src * sin.n, sin.n, max(n, 1), tid);
-    CM::load(gr, doh + (size_t)src * sout.n, sout.n, max(n, 1), tid);
+    auto fetch = [&](int t) {
+    const int i = ci[t / HP], r0 = i * BQ + 64 * (t % HP), src = r0 < N ? r0 : i * BQ, n = max(1, min(64, N - r0));
+    CM::load(qr, qh + (size_t)src * sin.n, sin.n, n, tid);
+    CM::load(gr, doh + (size_t)src * sout.n, sout.n, n, tid);
     if (tid < 64) {
-      const size_t at = (size_t)bh * N + src + min(tid, max(n, 1) - 1);
+      const size_t at = (size_t)bh * Tm * BQ + r0 + tid;
       lr = l2_in[at];
       dr = ds_in[at];
     }
@@ -387,7 +388,7 @@ __global__ __launch_bounds__(256, 1) void bwd_kv_f32_kernel(
   for (int e = 0; e < ET; e++) { dvacc[e] = zero16(); dkacc[e] = zero16(); }
 
   for (int t = 0; t < nsteps; t++) {
-    const int i = ci[l0 + t / HP], n = max(0, min(64, N - row0_of(t)));
+    const int i = ci[t / HP];
     const float al = alpha[alpha_per_block ? (size_t)h * Tm + i : (size_t)h];
     __syncthreads();                      // previous step fully consumed
 #pragma unroll
@@ -411,7 +412,7 @@ __global__ __launch_bounds__(256, 1) void bwd_kv_f32_kernel(
 #pragma unroll
       for (int y = 0; y < 4; y++) {
         const int e = 4 * v4 + y;
-        const float pv = key_ok && r + y < n ? exp2_f32(p[e] * c0 - l4[y]) : 0.f;
+        const float pv = exp2_f32(p[e] * c0 - l4[y]);   // keys past the end: columns of their own, not stored
         ds[e] = pv * (al * ds[e] - d4[y]);
         p[e] = al * pv;
       }
@@ -464,7 +465,7 @@ __global__ __launch_bounds__(256, 1) void bwd_kv_f32_kernel(
 #pragma unroll
     for (int x = 0; x < NC; x++) acc[x] = *reinterpret_cast<const f32x4*>(tot + 4 * NT * x);
     float dz = tid < D ? dz_total[(size_t)bh * D + tid] : 0.f;
-    for (int l = l0; l < l1; l++) {
+    for (int l = 0; l < listed; l++) {
       const size_t slot = (size_t)bh * Tm + ci[l];
       const float* src = dh_in + slot * D * D + 4 * tid;
 #pragma unroll
@@ -554,9 +555,9 @@ static hipError_t launch_kv(const Shape& s, const BwdArgs& a, hipStream_t stream
   constexpr int smem = BwdKvF32Smem<D>::kBytes;
   static OncePerDevice once;
   if (hipError_t e = allow_dynamic_lds(once, (const void*)bwd_kv_f32_kernel<D, BQ>, smem); e != hipSuccess) return e;
-  bwd_kv_f32_kernel<D, BQ><<<dim3((unsigned)(s.BH * s.Tn)), 256, smem, stream>>>(
-      (const float*)a.q, (const float*)a.k, (const float*)a.v, (const float*)a.dout, a.lraw, a.ds, a.k_mean, a.k_stats, a.col_ptr,
-      a.col_idx, (const float*)a.dh, a.dz, a.dh_total, a.dz_total, a.alpha, (float*)a.dk, (float*)a.dv, a.colsum, s.sin, s.sout,
+  bwd_kv_f32_kernel<D, BQ><<<dim3((unsigned)bwd_kv_grid(s)), 256, smem, stream>>>(
+      (const float*)a.q, (const float*)a.k, (const float*)a.v, (const float*)a.dout, a.lraw, a.ds, a.k_mean, a.k_stats,
+      a.col_ptr, a.col_idx, a.order, (const float*)a.dh, a.dz, a.dh_total, a.dz_total, a.alpha, (float*)a.dk, (float*)a.dv, a.colsum, s.sin, s.sout,
       s.H, s.N, s.Tm, s.Tn, s.k, s.alpha_per_block ? 1 : 0);
   return hipGetLastError();
 }

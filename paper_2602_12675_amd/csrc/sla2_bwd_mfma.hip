@@ -128,9 +128,9 @@ __global__ __launch_bounds__(BQ * 2, 2) void bwd_q_mfma_kernel(
   qmu = half_sum(qmu);
   const float Lraw = L + qmu * rscale;
   const float L2 = Lraw * kLog2e;
-  if (g == 0 && row_ok) {
-    ds_out[(size_t)bh * N + row0 + qrow] = Ds;
-    lraw_out[(size_t)bh * N + row0 + qrow] = L2;      // as the key-side kernel uses it: L on the raw keys, times log2(e)
+  if (g == 0) {                                      // as the key-side kernel uses them: L on the raw keys, times log2(e);
+    ds_out[slot * BQ + qrow] = row_ok ? Ds : 0.f;    // rows past the end get a probability of exp2(-inf) = 0 there
+    lraw_out[slot * BQ + qrow] = row_ok ? L2 : INFINITY;
   }
 
   // LDS byte offsets of this lane's operand reads inside a K or V tile: row-wise reads (key row
@@ -425,24 +425,27 @@ template <int D> struct BwdKvSmem {
 
 // Scores are computed as S = Q K^T (query rows x keys) here: a lane of the result then owns one key
 // and 16 of the 32 query rows of the tile, which is the B-operand layout of the products that contract
-// over query rows (dV^T += dO^T P, dK^T += Q^T dS) - P and dS never leave registers.  Wave w owns the
-// key half kh = w % 2 and the channel tiles of group w / 2; it computes the scores of all 64 rows of a
-// step against its 32 keys (the two waves of a key half repeat that work: cheaper than passing P and dS
-// through LDS with a barrier in between).  K_j and V_j live in registers as operand fragments.
+// over query rows (dV^T += dO^T P, dK^T += Q^T dS) - P and dS never leave registers.  Wave (kh, rh) owns the
+// key half kh and, of every 64-row step, the row half rh: it forms 32 x 32 scores and contracts over its 32 rows
+// into all channels; the two waves of a key half add their dV^T, dK^T once, after the loop, and share the channel
+// tiles of the linear branch.  (Owning 64 rows and half of the channels instead, a wave formed every score twice:
+// 48 products and 32 exponentials per lane and step where 32 and 16 do, and read 48 KB of operands from LDS instead
+// of 32: LDS feeds 128 bytes a cycle, one operand per product and SIMD.)  The price is registers: 128 accumulators
+// next to the 64 of the K_j, V_j fragments, so the operand reads run only a few ahead.
 template <int D, int BQ>
 __global__ __launch_bounds__(256, 2) void bwd_kv_mfma_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const uint16_t* __restrict__ dout, const float* __restrict__ lraw2, const float* __restrict__ ds_in,
-    const double* __restrict__ k_mean, const float* __restrict__ k_stats, const int32_t* __restrict__ col_ptr,
-    const int32_t* __restrict__ col_idx, const uint16_t* __restrict__ dh_in, const float* __restrict__ dz_in,
+    const double* __restrict__ k_mean, const float* __restrict__ k_stats, const int32_t* __restrict__ col_ptr, const int32_t* __restrict__ col_idx,
+    const int32_t* __restrict__ order, const uint16_t* __restrict__ dh_in, const float* __restrict__ dz_in,
     const float* __restrict__ dh_total, const float* __restrict__ dz_total, const float* __restrict__ alpha,
     uint16_t* __restrict__ dk, uint16_t* __restrict__ dv, float* __restrict__ colsum, Strides sin, Strides sout, int H,
     int N, int Tm, int Tn, int ksel, int alpha_per_block) {
   constexpr int NW = 4, NT = 256;
   constexpr int LD = D + 8, KS = D / 16, ET = D / 32;
   constexpr int HP = BQ / 64;                        // 64-row steps per query block
-  constexpr int CT = ET / 2;                         // 32-channel tiles of dV^T / dK^T per wave
-  typedef SwizzledLayout<D> SL;
+  constexpr int CT = ET / 2;                         // 32-channel tiles a wave finishes after the loop
+  typedef typename std::conditional<D == 128, SwizzledLayoutB<128>, SwizzledLayout<64>>::type SL;   // no bank conflicts
   typedef PaddedLayout<D> PL;
   typedef BwdKvSmem<D> SM;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
@@ -453,14 +456,12 @@ __global__ __launch_bounds__(256, 2) void bwd_kv_mfma_kernel(
   float* dzs = reinterpret_cast<float*>(smem + SM::kDzOff);
   float* dred = reinterpret_cast<float*>(smem + SM::kDotOff);
 
-  // the same dealing for key blocks: 8 runs of consecutive key blocks per head, one per XCD
-  const int per_head = (Tn + kXcds - 1) / kXcds;
-  const int bh = (blockIdx.x / kXcds) / per_head, j = (blockIdx.x % kXcds) * per_head + (blockIdx.x / kXcds) % per_head;
-  if (j >= Tn) return;
-  const int h = bh % H;
+  const int entry = __builtin_amdgcn_readfirstlane(order[blockIdx.x]);
+  if (entry < 0) return;
+  const int j = entry & (kMaxKeyBlocks - 1), bh = entry / kMaxKeyBlocks, h = bh % H;   // longest lists first, see sla2_bwd.hip
   const int tid = threadIdx.x, lane = tid % kWave, g = lane / 32;
   const int w = __builtin_amdgcn_readfirstlane(tid / kWave);
-  const int kh = w & 1, cgrp = w >> 1;
+  const int kh = w >> 1, rh = w & 1;                 // rh: also the half of the channel tiles finished after the loop
   const int t0 = j * kTileTokens, valid = min(kTileTokens, N - t0);
   const int mykey = 32 * kh + lane % 32;             // this lane's key inside the block
   const bool key_ok = mykey < valid;
@@ -489,38 +490,33 @@ __global__ __launch_bounds__(256, 2) void bwd_kv_mfma_kernel(
   const int l0 = __builtin_amdgcn_readfirstlane(cp[j]), l1 = __builtin_amdgcn_readfirstlane(cp[j + 1]);
   const int nsteps = (l1 - l0) * HP;
 
-  // Step t covers rows [64 (t % HP), +64) of query block ci[l0 + t / HP].  A half block with no rows
-  // (short last query block) still runs, on the block's first rows with every probability masked.
+  // Step t covers rows [64 (t % HP), +64) of query block ci[l0 + t / HP].  Rows past the end (a short last query block)
+  // repeat an existing one; their L is +inf, so their probabilities are 0.
   // The rows of step t + 1 (and L log2 e, D^s of those rows) are requested at the start of step t,
   // straight into LDS; the query block index is read one step before that.
-  struct Step { int rows, src0; float al; };
+  struct Step { int i, row0; float al; };
   auto block_of = [&](int t) { return ci[l0 + min(t, nsteps - 1) / HP]; };
   auto place = [&](int t, int i) {
-    Step st;
-    const int row0 = i * BQ + 64 * (t % HP);
-    st.rows = max(0, min(64, N - row0));
-    st.src0 = st.rows > 0 ? row0 : i * BQ;
-    st.al = alpha[alpha_per_block ? (size_t)h * Tm + i : (size_t)h];
-    return st;
+    return Step{i, i * BQ + 64 * (t % HP), alpha[alpha_per_block ? (size_t)h * Tm + i : (size_t)h]};
   };
   auto request = [&](const Step& st, int buf) {
-    const int dma_rows = max(st.rows, 1);
-    dma_tile<D, NW>(qh + (size_t)st.src0 * tok_stride, tok_stride, dma_rows, qbuf(buf), w, lane);
-    dma_tile<D, NW>(doh + (size_t)st.src0 * sout.n, sout.n, dma_rows, gbuf(buf), w, lane);
+    const int src = st.row0 < N ? st.row0 : st.i * BQ, rows = max(1, min(64, N - st.row0));
+    dma_tile<D, NW, SL>(qh + (size_t)src * tok_stride, tok_stride, rows, qbuf(buf), w, lane);
+    dma_tile<D, NW, SL>(doh + (size_t)src * sout.n, sout.n, rows, gbuf(buf), w, lane);
     // every wave fetches the same 2 x 64 floats (same values to the same place: the counts of
     // outstanding transfers stay equal across the waves)
-    const size_t at = (size_t)bh * N + st.src0 + min(lane, dma_rows - 1);
+    const size_t at = (size_t)bh * Tm * BQ + st.row0 + lane;
     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(lraw2 + at),
                                      (__attribute__((address_space(3))) void*)(stat + buf * 128), 4, 0, 0);
     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(ds_in + at),
                                      (__attribute__((address_space(3))) void*)(stat + buf * 128 + 64), 4, 0, 0);
   };
 
-  f32x16 dvacc[CT], dkacc[CT];
+  f32x16 dvall[ET], dkall[ET];
 #pragma unroll
-  for (int x = 0; x < CT; x++)
+  for (int x = 0; x < ET; x++)
 #pragma unroll
-    for (int e = 0; e < 16; e++) { dvacc[x][e] = 0.f; dkacc[x][e] = 0.f; }
+    for (int e = 0; e < 16; e++) { dvall[x][e] = 0.f; dkall[x][e] = 0.f; }
 
   Step cur{0, 0, 0.f};
   int i_nxt = 0;
@@ -534,15 +530,12 @@ __global__ __launch_bounds__(256, 2) void bwd_kv_mfma_kernel(
   for (int ks = 0; ks < KS; ks++) { settle(kfr[ks]); settle(vfr[ks]); }
   __syncthreads();                                   // step 0 and mus are in LDS for everyone
 
-  // LDS byte offsets of this lane's operand reads inside a Q or dO tile.  Row-wise reads: row
-  // l % 32 (+ 32 for the second row half), channel step ks at (offset of step 0) ^ 32 ks.
-  // Transposing reads (cf. read_tr4): the row swizzle depends on row % 8 only, so 16-row step ks
-  // sits at a fixed distance from step 0.
-  const unsigned b_off = (unsigned)SL::offset(lane % 32, 8 * g) * 2;
-  const int tr_row = 4 * g + (lane % 16) / 4, tr_col = 16 * ((lane / 16) % 2) + 4 * (lane % 4);
-  unsigned a_off[CT];
-#pragma unroll
-  for (int x = 0; x < CT; x++) a_off[x] = (unsigned)SL::offset(tr_row, 32 * (CT * cgrp + x) + tr_col) * 2;
+  // LDS byte offsets of this lane's operand reads inside a Q or dO tile.  Row-wise reads: row 32 rh + l % 32, channel
+  // step ks at (offset of step 0) ^ 32 ks.  Transposing reads (cf. read_tr4): rows 32 rh + 4 g + (l % 16) / 4 (lo) and
+  // 8 further (hi), channel tile et at (offset of tile 0) ^ 64 et, 16-row step ks 32 D ks further.
+  const unsigned b_off = (unsigned)SL::offset(32 * rh + lane % 32, 8 * g) * 2;
+  const int tr_row = 32 * rh + 4 * g + (lane % 16) / 4, tr_col = 16 * ((lane / 16) % 2) + 4 * (lane % 4);
+  const unsigned a_lo = (unsigned)SL::offset(tr_row, tr_col) * 2, a_hi = (unsigned)SL::offset(tr_row + 8, tr_col) * 2;
 
   for (int t = 0; t < nsteps; t++) {
     const int buf = t & 1;
@@ -553,23 +546,15 @@ __global__ __launch_bounds__(256, 2) void bwd_kv_mfma_kernel(
     }
     i_nxt = block_of(t + 2);
     const unsigned qa = lds_address(qbuf(buf)), ga = lds_address(gbuf(buf));
-    const float* st_l = stat + buf * 128;
-    // S = Q K^T and dP = dO V^T: rows 32 rh.. x this wave's 32 keys.  32 operand reads (this lane's
-    // rows of Q and dO), each feeding one product; 8 are kept in flight.
-    f32x16 sacc[2], dpacc[2];
+    const float* st_l = stat + buf * 128 + 32 * rh + 4 * g;
+    // S = Q K^T and dP = dO V^T: this wave's 32 rows x its 32 keys.  16 operand reads, each feeding one product.
+    f32x16 sacc, dpacc;
 #pragma unroll
-    for (int rh = 0; rh < 2; rh++)
-#pragma unroll
-      for (int e = 0; e < 16; e++) { sacc[rh][e] = 0.f; dpacc[rh][e] = 0.f; }
+    for (int e = 0; e < 16; e++) { sacc[e] = 0.f; dpacc[e] = 0.f; }
     {
-      constexpr int kItems = 4 * KS, kAhead = 8, kSlots = kAhead + 1;
+      constexpr int kItems = 2 * KS, kAhead = 4, kSlots = kAhead + 1;
       u32x4 ring[kSlots];
-      auto issue = [&](int n) {                      // item n: (Q | dO, row half, channel step)
-        const int grp = n / KS, ks = n % KS;
-        const unsigned base = (grp < 2 ? qa : ga) + b_off;
-        if (grp % 2 == 0) ring[n % kSlots] = lds_read16_untracked<0>(base ^ (32u * ks));
-        else ring[n % kSlots] = lds_read16_untracked<32 * D * 2>(base ^ (32u * ks));
-      };
+      auto issue = [&](int n) { ring[n % kSlots] = lds_read16_untracked<0>(((n < KS ? qa : ga) + b_off) ^ (32u * (n % KS))); };
 #pragma unroll
       for (int n = 0; n < kAhead; n++) issue(n);
 #pragma unroll
@@ -578,73 +563,84 @@ __global__ __launch_bounds__(256, 2) void bwd_kv_mfma_kernel(
         wait_lgkmcnt(n + kAhead < kItems ? kAhead : kItems - 1 - n);
         settle(ring[n % kSlots]);
         const bf16x8 a = __builtin_bit_cast(bf16x8, ring[n % kSlots]);
-        const int grp = n / KS, ks = n % KS;
-        if (grp < 2) sacc[grp] = mfma_bf16(a, kfr[ks], sacc[grp]);
-        else dpacc[grp - 2] = mfma_bf16(a, vfr[ks], dpacc[grp - 2]);
+        if (n < KS) sacc = mfma_bf16(a, kfr[n], sacc);
+        else dpacc = mfma_bf16(a, vfr[n - KS], dpacc);
       }
     }
-    // alpha P and dS = P (.) (alpha dP - D^s), as B-operand fragments over the 64 rows (token order);
-    // masked entries get exp2(-inf) = 0
-    bf16x8 pf[4], dsf[4];
-    auto probabilities = [&](auto masked) {          // masked: a short key block or a short last row block
+    // alpha P and dS = P (.) (alpha dP - D^s), as B-operand fragments over the 32 rows (token order).  Keys past the end
+    // of a short key block need no mask: their columns mix with no others and are not stored.
+    bf16x8 pf[2], dsf[2];
 #pragma unroll
-      for (int rh = 0; rh < 2; rh++)
+    for (int v4 = 0; v4 < 4; v4++) {
+      const f32x4 l4 = *reinterpret_cast<const f32x4*>(st_l + 8 * v4);
+      const f32x4 d4 = *reinterpret_cast<const f32x4*>(st_l + 64 + 8 * v4);
 #pragma unroll
-        for (int v4 = 0; v4 < 4; v4++) {
-          const f32x4 l4 = *reinterpret_cast<const f32x4*>(st_l + 32 * rh + 8 * v4 + 4 * g);
-          const f32x4 d4 = *reinterpret_cast<const f32x4*>(st_l + 64 + 32 * rh + 8 * v4 + 4 * g);
-#pragma unroll
-          for (int r = 0; r < 4; r++) {
-            float arg = sacc[rh][4 * v4 + r] * c0 - l4[r];
-            if constexpr (decltype(masked)::value)
-              arg = (!key_ok || 32 * rh + 8 * v4 + 4 * g + r >= cur.rows) ? -INFINITY : arg;
-            const float p = fast_exp2(arg);
-            pf[2 * rh + v4 / 2][4 * (v4 % 2) + r] = (__bf16)(cur.al * p);
-            dsf[2 * rh + v4 / 2][4 * (v4 % 2) + r] = (__bf16)(p * (cur.al * dpacc[rh][4 * v4 + r] - d4[r]));
-          }
-        }
-    };
-    if (cur.rows < 64 || valid < kTileTokens) probabilities(std::true_type{});
-    else probabilities(std::false_type{});
+      for (int r = 0; r < 4; r++) {
+        const int e = 4 * v4 + r;
+        const float p = fast_exp2(sacc[e] * c0 - l4[r]);
+        pf[v4 / 2][4 * (v4 % 2) + r] = (__bf16)(cur.al * p);
+        dsf[v4 / 2][4 * (v4 % 2) + r] = (__bf16)(p * (cur.al * dpacc[e] - d4[r]));
+      }
+    }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // nothing tracked is in flight when the counted reads below start
-    // dV^T += dO^T (alpha P), dK'^T += Q^T dS: contraction over the 64 rows of the step; the operand
-    // reads of the next 16-row step are in flight while the products of this one run
+    // dV^T += dO^T (alpha P), dK'^T += Q^T dS: contraction over the 32 rows.  Fragment n: 16-row step, tensor, channel tile.
     {
-      constexpr int kReads = 4 * CT;
-      u32x2 rg[2][CT][2], rq[2][CT][2];
-      auto issue = [&](int ks, int slot) {
-#pragma unroll
-        for (int x = 0; x < CT; x++)
-#pragma unroll
-          for (int hi = 0; hi < 2; hi++) {
-            rg[slot][x][hi] = lds_read_tr_untracked_at<16 * D>(ga + a_off[x], 2 * ks + hi);
-            rq[slot][x][hi] = lds_read_tr_untracked_at<16 * D>(qa + a_off[x], 2 * ks + hi);
-          }
+      constexpr int kFrags = 4 * ET, kAhead = 3, kSlots = kAhead + 1;
+      u32x2 lo[kSlots], hi[kSlots];
+      auto issue = [&](int n) {
+        const int ks = n / (2 * ET), et = n % ET;
+        const unsigned base = (n / ET) % 2 == 0 ? ga : qa;
+        lo[n % kSlots] = lds_read_tr_untracked_at<32 * D>((base + a_lo) ^ (64u * et), ks);
+        hi[n % kSlots] = lds_read_tr_untracked_at<32 * D>((base + a_hi) ^ (64u * et), ks);
       };
-      auto frag = [&](u32x2 (&r)[2]) {
-        settle(r[0]);
-        settle(r[1]);
-        const u32x4 v4 = {r[0][0], r[0][1], r[1][0], r[1][1]};
-        return __builtin_bit_cast(bf16x8, v4);
-      };
-      issue(0, 0);
 #pragma unroll
-      for (int ks = 0; ks < 4; ks++) {
-        const int slot = ks & 1;
-        if (ks + 1 < 4) issue(ks + 1, slot ^ 1);
-        wait_lgkmcnt(ks + 1 < 4 ? kReads : 0);
+      for (int n = 0; n < kAhead; n++) issue(n);
 #pragma unroll
-        for (int x = 0; x < CT; x++) {
-          dvacc[x] = mfma_bf16(frag(rg[slot][x]), pf[ks], dvacc[x]);
-          dkacc[x] = mfma_bf16(frag(rq[slot][x]), dsf[ks], dkacc[x]);
-        }
+      for (int n = 0; n < kFrags; n++) {
+        if (n + kAhead < kFrags) issue(n + kAhead);
+        wait_lgkmcnt(2 * (n + kAhead < kFrags ? kAhead : kFrags - 1 - n));
+        settle(lo[n % kSlots]);
+        settle(hi[n % kSlots]);
+        const u32x4 v4 = {lo[n % kSlots][0], lo[n % kSlots][1], hi[n % kSlots][0], hi[n % kSlots][1]};
+        const bf16x8 f = __builtin_bit_cast(bf16x8, v4);
+        const int ks = n / (2 * ET), et = n % ET;
+        if ((n / ET) % 2 == 0) dvall[et] = mfma_bf16(f, pf[ks], dvall[et]);
+        else dkall[et] = mfma_bf16(f, dsf[ks], dkall[et]);
       }
     }
     wait_vmcnt<0>();                                 // the next step's rows have landed ...
     asm volatile("s_barrier" ::: "memory");          // ... for everyone; this step's tiles are free
     cur = nxt;
   }
-  __syncthreads();
+
+  // the two row halves add up: each wave finishes half of the channel tiles and hands the other half over
+  f32x16 dvacc[CT], dkacc[CT];
+  {
+    float* mine = reinterpret_cast<float*>(smem) + (size_t)w * (2 * CT * 16 * kWave) + lane;
+    const float* other = reinterpret_cast<float*>(smem) + (size_t)(w ^ 1) * (2 * CT * 16 * kWave) + lane;
+    auto exchange = [&](auto half) {
+      constexpr int E0 = decltype(half)::value * CT, F0 = CT - E0;
+      __syncthreads();                               // the last step fully consumed
+#pragma unroll
+      for (int x = 0; x < CT; x++)
+#pragma unroll
+        for (int e = 0; e < 16; e++) {
+          mine[(x * 16 + e) * kWave] = dvall[F0 + x][e];
+          mine[((CT + x) * 16 + e) * kWave] = dkall[F0 + x][e];
+        }
+      __syncthreads();
+#pragma unroll
+      for (int x = 0; x < CT; x++)
+#pragma unroll
+        for (int e = 0; e < 16; e++) {
+          dvacc[x][e] = dvall[E0 + x][e] + other[(x * 16 + e) * kWave];
+          dkacc[x][e] = dkall[E0 + x][e] + other[((CT + x) * 16 + e) * kWave];
+        }
+    };
+    if (rh == 0) exchange(std::integral_constant<int, 0>());
+    else exchange(std::integral_constant<int, 1>());
+  }
+  __syncthreads();                                   // the halves have been read
 
   // ================= linear branch =================
   uint16_t* dht = reinterpret_cast<uint16_t*>(smem);                     // dH [c][e] as bf16, row stride LD
@@ -698,7 +694,7 @@ __global__ __launch_bounds__(256, 2) void bwd_kv_mfma_kernel(
         const float kp = key_ok ? fast_exp2(((float)kfr[ks][e] - (e < 4 ? m0[e] : m1[e - 4])) * kLog2e - lnz2) : 0.f;
         kfr[ks][e] = (__bf16)kp;
       }
-      if (cgrp == 0) *reinterpret_cast<bf16x8*>(kpt + mykey * LD + 16 * ks + 8 * g) = kfr[ks];
+      if (rh == 0) *reinterpret_cast<bf16x8*>(kpt + mykey * LD + 16 * ks + 8 * g) = kfr[ks];
     }
   }
   __syncthreads();
@@ -713,7 +709,7 @@ __global__ __launch_bounds__(256, 2) void bwd_kv_mfma_kernel(
   for (int ks = 0; ks < KS; ks++) {
 #pragma unroll
     for (int x = 0; x < CT; x++) {
-      const int ct = CT * cgrp + x;
+      const int ct = CT * rh + x;
       dkp[x] = mfma_bf16(row_fragment<PL>(dht, 32 * ct + lane % 32, 16 * ks + 8 * g), vfr[ks], dkp[x]);   // over e
       dvacc[x] = mfma_bf16(nat_fragment<PL>(dht, ks, 32 * ct, lane), kfr[ks], dvacc[x]);                 // over c
     }
@@ -722,7 +718,7 @@ __global__ __launch_bounds__(256, 2) void bwd_kv_mfma_kernel(
   float kp[CT][16];
 #pragma unroll
   for (int x = 0; x < CT; x++) {
-    const int ct = CT * cgrp + x;
+    const int ct = CT * rh + x;
     float part = 0.f;
 #pragma unroll
     for (int v4 = 0; v4 < 4; v4++) {
@@ -747,7 +743,7 @@ __global__ __launch_bounds__(256, 2) void bwd_kv_mfma_kernel(
     for (int c2 = 0; c2 < ET; c2++) dot += dred[c2 * 64 + mykey];
 #pragma unroll
     for (int x = 0; x < CT; x++) {
-      const int ct = CT * cgrp + x;
+      const int ct = CT * rh + x;
 #pragma unroll
       for (int v4 = 0; v4 < 4; v4++) {
         bf16x4 pk, pv;
@@ -785,10 +781,9 @@ static hipError_t launch_bwd_kv_mfma(const Shape& s, const BwdArgs& a, hipStream
   constexpr int smem = BwdKvSmem<D>::kBytes;
   static OncePerDevice once;
   if (hipError_t e = allow_dynamic_lds(once, (const void*)bwd_kv_mfma_kernel<D, BQ>, smem); e != hipSuccess) return e;
-  const int grid = ((s.Tn + kXcds - 1) / kXcds) * kXcds * s.BH;
-  bwd_kv_mfma_kernel<D, BQ><<<dim3((unsigned)grid), 256, smem, stream>>>(
+  bwd_kv_mfma_kernel<D, BQ><<<dim3((unsigned)bwd_kv_grid(s)), 256, smem, stream>>>(
       (const uint16_t*)a.q, (const uint16_t*)a.k, (const uint16_t*)a.v, (const uint16_t*)a.dout, a.lraw, a.ds, a.k_mean,
-      a.k_stats, a.col_ptr, a.col_idx, (const uint16_t*)a.dh, a.dz, a.dh_total, a.dz_total, a.alpha, (uint16_t*)a.dk,
+      a.k_stats, a.col_ptr, a.col_idx, a.order, (const uint16_t*)a.dh, a.dz, a.dh_total, a.dz_total, a.alpha, (uint16_t*)a.dk,
       (uint16_t*)a.dv, a.colsum, s.sin, s.sout, s.H, s.N, s.Tm, s.Tn, s.k, s.alpha_per_block ? 1 : 0);
   return hipGetLastError();
 }
