@@ -136,14 +136,14 @@ hipError_t launch_attn_f32(const Shape& s, const float* q, const float* k, const
                            const float* k_stats, const float* h_total, const float* z_total, const int32_t* block_idx,
                            const float* alpha, float* out, float* lse, const SavedForBackward& sv, hipStream_t stream);
 
-hipError_t launch_kv_total(const Shape& s, const float* partial, float* h_total, float* z_total, hipStream_t stream);
+hipError_t launch_kv_total(const Shape& s, const float* partial, float* h_total, float* z_total, float* h_frag, hipStream_t stream);
 hipError_t launch_kv_state_bf16(const Shape& s, const uint16_t* k, const uint16_t* v, const double* k_mean,
                                 float* k_stats, float* partial, uint16_t* k_phi, float* z_blocks, uint8_t* k_codes,
                                 float* k_scale, uint8_t* v_codes, float* v_scale, hipStream_t stream);
 hipError_t launch_attn_bf16(const Shape& s, const uint16_t* q, const uint16_t* k, const uint16_t* v,
                             const double* k_mean, const uint16_t* k_phi, const float* z_blocks, const uint8_t* k_codes,
                             const float* k_scale, const uint8_t* v_codes, const float* v_scale,
-                            const float* h_total, const float* z_total,
+                            const float* h_frag, const float* z_total,
                             const int32_t* block_idx, const float* alpha, uint16_t* out, float* lse,
                             const SavedForBackward& sv, hipStream_t stream);
 hipError_t launch_dense_pp(const Shape& s, const uint16_t* q, const uint16_t* k, const uint16_t* v, uint16_t* out,

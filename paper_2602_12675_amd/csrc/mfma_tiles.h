@@ -22,6 +22,55 @@ constexpr int kVmcnt0 = 0x0F70;                    // s_waitcnt vmcnt(0), other 
 __device__ __forceinline__ float half_sum(float x) { return x + __shfl_xor(x, 32); }
 __device__ __forceinline__ float half_max(float x) { return fmaxf(x, __shfl_xor(x, 32)); }
 
+// lanes l and l ^ 32 combine their values through v_permlane32_swap (a vector instruction: no LDS round trip,
+// whose latency a wave that has the vector unit to itself would sit out)
+__device__ __forceinline__ float swap_halves_max(float x) {
+  const unsigned u = __builtin_bit_cast(unsigned, x);
+  const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);   // r[0] = low half twice, r[1] = high half twice
+  return fmaxf(__builtin_bit_cast(float, (unsigned)r[0]), __builtin_bit_cast(float, (unsigned)r[1]));
+}
+__device__ __forceinline__ float swap_halves_sum(float x) {
+  const unsigned u = __builtin_bit_cast(unsigned, x);
+  const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  return __builtin_bit_cast(float, (unsigned)r[0]) + __builtin_bit_cast(float, (unsigned)r[1]);
+}
+// lanes 32..63 take the values of lanes 0..31
+__device__ __forceinline__ float low_half(float x) {
+  const unsigned u = __builtin_bit_cast(unsigned, x);
+  return __builtin_bit_cast(float, (unsigned)__builtin_amdgcn_permlane32_swap(u, u, false, false)[0]);
+}
+// Maximum over the wave, on every lane; vector instructions only.
+__device__ __forceinline__ float wave_max(float x) {
+  auto dpp = [&](auto ctrl) {
+    const int i = __builtin_bit_cast(int, x);
+    x = fmaxf(x, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(i, i, decltype(ctrl)::value, 0xf, 0xf, false)));
+  };
+  dpp(std::integral_constant<int, 0xB1>());          // quad_perm 1 0 3 2
+  dpp(std::integral_constant<int, 0x4E>());          // quad_perm 2 3 0 1
+  dpp(std::integral_constant<int, 0x141>());         // row_half_mirror
+  dpp(std::integral_constant<int, 0x140>());         // row_mirror
+  const unsigned u = __builtin_bit_cast(unsigned, x);
+  const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  x = fmaxf(__builtin_bit_cast(float, (unsigned)r[0]), __builtin_bit_cast(float, (unsigned)r[1]));
+  return swap_halves_max(x);
+}
+// Between two phases of a workgroup.  LDS is written by the tile transfers only (waited for through vmcnt where a phase
+// needs them), and every operand read is waited for by the product that consumes it, so the barrier itself
+// waits for nothing: reads issued before it stay in flight across it.
+__device__ __forceinline__ void phase_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
+// f(0), .., f(N - 1) with the index as a constant expression: for bodies that are too long for the unroller
+template <int N, class F> __device__ __forceinline__ void unrolled(F f) {
+  if constexpr (N > 0) {
+    unrolled<N - 1>(f);
+    f(std::integral_constant<int, N - 1>());
+  }
+}
+
 __device__ __forceinline__ f32x16 mfma_bf16(bf16x8 a, bf16x8 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
@@ -108,6 +157,33 @@ __device__ __forceinline__ bf16x8 row_fragment(const uint16_t* tile, int row, in
   return *reinterpret_cast<const bf16x8*>(tile + L::offset(row, col));
 }
 
+// 16 bytes per lane, global memory -> 1 KB of LDS (lane l's at lds + OFF + 16 l; completion: vmcnt): uniform base
+// address, 32-bit byte offset per lane, OFF added on both sides.  Written by hand because the compiler hoists the 64-bit
+// sums of address and lane offset out of the calling loop: two vector registers and a 64-bit vector addition per
+// transfer, in kernels that have no registers to spare.  It does not see a write to LDS here: every kernel waits for its
+// transfers itself.
+__device__ __forceinline__ unsigned lds_address(const void* p) {
+  return (unsigned)(size_t)(const __attribute__((address_space(3))) void*)p;
+}
+template <int OFF = 0>
+__device__ __forceinline__ void dma_lane16(const void* base, unsigned lane_off, unsigned lds) {
+  static_assert(OFF >= 0 && OFF < 4096, "12 bits of the instruction");
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 offset:%3"
+               ::"v"(lane_off), "s"(base), "s"(lds), "n"(OFF) : "memory");
+}
+// OFF = 1024 n (n < 4, a constant after unrolling)
+__device__ __forceinline__ void dma_lane16_at(const void* base, unsigned lane_off, unsigned lds, int n) {
+  switch (n) {
+    case 0: return dma_lane16<0>(base, lane_off, lds);
+    case 1: return dma_lane16<1024>(base, lane_off, lds);
+    case 2: return dma_lane16<2048>(base, lane_off, lds);
+    default: return dma_lane16<3072>(base, lane_off, lds);
+  }
+}
+__device__ __forceinline__ void dma_lane4(const void* base, unsigned lane_off, unsigned lds) {   // 4 bytes per lane, 256 bytes of LDS
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" ::"v"(lane_off), "s"(base), "s"(lds) : "memory");
+}
+
 // One 64 x D bf16 tile, global memory -> LDS without passing through registers.  NW waves cooperate;
 // each global_load_lds_dwordx4 moves 1 KB (64 lanes x 16 bytes) into consecutive LDS bytes.
 // Completion is counted by vmcnt.  Rows past `valid` (ragged last tile) repeat the last row.  One
@@ -115,7 +191,7 @@ __device__ __forceinline__ bf16x8 row_fragment(const uint16_t* tile, int row, in
 // the same on every path, which lets later waits be counted instead of draining everything.
 template <int D, int NW, class L = SwizzledLayout<D>>
 __device__ __forceinline__ void dma_tile(const uint16_t* src /* first row */, int row_stride /* elements */, int valid,
-                                         uint16_t* tile, int w, int lane) {
+                                         unsigned lds, int w, unsigned lane) {
   constexpr int kRowsPerInstr = 1024 / (D * 2);
   constexpr int kInstrs = kTileTokens / kRowsPerInstr / NW;
   static_assert((kRowsPerInstr * NW) % 16 == 0 || (std::is_same<L, SwizzledLayout<D>>::value && (kRowsPerInstr * NW) % 8 == 0),
@@ -126,27 +202,26 @@ __device__ __forceinline__ void dma_tile(const uint16_t* src /* first row */, in
 #pragma unroll
   for (int i = 0; i < kInstrs; i++) {
     const unsigned off = (unsigned)min(row_w + i * NW * kRowsPerInstr, valid - 1) * (unsigned)(row_stride * 2) + col_bytes;
-    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(base + off),
-                                     (__attribute__((address_space(3))) void*)(tile + (i * NW + w) * 512), 16, 0, 0);
+    dma_lane16(base, off, lds + (i * NW + w) * 1024);
   }
 }
 
 // The same for a tile whose 64 rows all exist: no clamping, and every address is a per-lane constant
 // plus a multiple of the instruction stride, which keeps the per-tile address arithmetic scalar.
-template <int D, int NW>
-__device__ __forceinline__ void dma_tile_full(const uint16_t* src, int row_stride /* elements */, uint16_t* tile, int w,
-                                              int lane) {
-  typedef SwizzledLayout<D> L;
+template <int D, int NW, class L = SwizzledLayout<D>>
+__device__ __forceinline__ unsigned tile_lane_off(int row_stride /* elements */, int w, unsigned lane) {
+  const int row_w = w * (1024 / (D * 2)) + lane / L::kChunks;
+  return (unsigned)row_w * (unsigned)(row_stride * 2) + 16u * (unsigned)((lane % L::kChunks) ^ L::swz(row_w));
+}
+template <int D, int NW, class L = SwizzledLayout<D>>
+__device__ __forceinline__ void dma_tile_full(const uint16_t* src, int row_stride /* elements */, unsigned lds, int w,
+                                              unsigned lane_off /* tile_lane_off */) {
   constexpr int kRowsPerInstr = 1024 / (D * 2);
   constexpr int kInstrs = kTileTokens / kRowsPerInstr / NW;
-  const int row_w = w * kRowsPerInstr + lane / L::kChunks;
-  const unsigned lane_off = (unsigned)row_w * (unsigned)(row_stride * 2) + 16u * (unsigned)((lane % L::kChunks) ^ L::swz(row_w));
   const char* base = reinterpret_cast<const char*>(src);
 #pragma unroll
   for (int i = 0; i < kInstrs; i++)
-    __builtin_amdgcn_global_load_lds(
-        (const __attribute__((address_space(1))) void*)(base + (size_t)i * (size_t)(NW * kRowsPerInstr * row_stride * 2) + lane_off),
-        (__attribute__((address_space(3))) void*)(tile + (i * NW + w) * 512), 16, 0, 0);
+    dma_lane16(base + (size_t)i * (unsigned)(NW * kRowsPerInstr * row_stride * 2), lane_off, lds + (i * NW + w) * 1024);
 }
 
 // The same for a 64 x D tile of e4m3 codes.  Rows of D bytes; the operand of the 64-deep FP8
@@ -161,20 +236,21 @@ template <int D> struct SwizzledLayout8 {
     return row * D + (((col >> 5) ^ swz(row)) << 5) + (col & 31);
   }
 };
+// The tile is contiguous on both sides: a wave moves consecutive kilobytes, one address for all of them.
+template <int D>
+__device__ __forceinline__ unsigned tile8_lane_off(unsigned lane) {
+  typedef SwizzledLayout8<D> L;
+  const unsigned row = lane / L::kChunks, pc = lane % L::kChunks;
+  return row * D + 16u * (pc ^ (2u * (unsigned)L::swz((int)row)));   // slot pc of a row holds chunk 2 ((pc / 2) ^ swz(row)) + pc % 2
+}
 template <int D, int NW>
-__device__ __forceinline__ void dma_tile8(const uint8_t* src, uint8_t* tile, int w, int lane) {
+__device__ __forceinline__ void dma_tile8(const uint8_t* src, unsigned lds, int w, unsigned off /* tile8_lane_off */) {
   typedef SwizzledLayout8<D> L;
   constexpr int kRowsPerInstr = 1024 / D;
   constexpr int kInstrs = kTileTokens / kRowsPerInstr / NW;
-  static_assert(kInstrs >= 1 && (kRowsPerInstr * NW) % 8 == 0, "unsupported tile split");
-  const int row_w = w * kRowsPerInstr + lane / L::kChunks;
-  const int pc = lane % L::kChunks;                  // chunk slot this lane fills; it fetches the chunk that belongs there
-  const int chunk = 2 * ((pc >> 1) ^ L::swz(row_w)) + (pc & 1);
-  const uint8_t* g = src + row_w * D + 16 * chunk;
+  static_assert(kInstrs >= 1 && kInstrs <= 4 && kRowsPerInstr % (2 * L::kPairs) == 0, "unsupported tile split");
 #pragma unroll
-  for (int i = 0; i < kInstrs; i++)
-    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(g + i * NW * kRowsPerInstr * D),
-                                     (__attribute__((address_space(3))) void*)(tile + (i * NW + w) * 1024), 16, 0, 0);
+  for (int i = 0; i < kInstrs; i++) dma_lane16_at(src + w * (kInstrs * 1024), off, lds + w * (kInstrs * 1024), i);
 }
 
 // A d x 64 tile of e4m3 codes of V, channel-major (rows of 64 bytes = the 64 tokens of a key block in
@@ -187,18 +263,14 @@ template <int D> struct SwizzledLayoutVq {
   __device__ static __forceinline__ int offset(int row, int chunk) { return row * kTileTokens + ((chunk ^ swz(row)) << 4); }
 };
 template <int D, int NW>
-__device__ __forceinline__ void dma_tile_vq(const uint8_t* src, uint8_t* tile, int w, int lane) {
+__device__ __forceinline__ void dma_tile_vq(const uint8_t* src, unsigned lds, int w, unsigned lane) {
   typedef SwizzledLayoutVq<D> L;
-  constexpr int kRowsPerInstr = 1024 / kTileTokens;           // 16 rows of 64 bytes per instruction
-  constexpr int kInstrs = D / kRowsPerInstr / NW;
-  static_assert(kInstrs >= 1, "unsupported tile split");
+  constexpr int kInstrs = D / (1024 / kTileTokens) / NW;      // 16 rows of 64 bytes per instruction
+  static_assert(kInstrs >= 1 && kInstrs <= 4, "unsupported tile split");
+  const unsigned row = lane / 4;                              // the slot a lane fills holds chunk (lane % 4) ^ swz(row)
+  const unsigned off = row * kTileTokens + 16u * ((lane % 4) ^ (unsigned)L::swz((int)row));
 #pragma unroll
-  for (int i = 0; i < kInstrs; i++) {
-    const int row = (i * NW + w) * kRowsPerInstr + lane / 4;  // the slot this lane fills holds chunk (lane % 4) ^ swz(row)
-    const uint8_t* g = src + row * kTileTokens + 16 * ((lane % 4) ^ L::swz(row));
-    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)g,
-                                     (__attribute__((address_space(3))) void*)(tile + (i * NW + w) * 1024), 16, 0, 0);
-  }
+  for (int i = 0; i < kInstrs; i++) dma_lane16_at(src + w * (kInstrs * 1024), off, lds + w * (kInstrs * 1024), i);
 }
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
@@ -273,6 +345,27 @@ __device__ __forceinline__ void wait_vmcnt() {
   static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit counter");
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
+// The same with a uniform base and a 32-bit byte offset per lane.
+__device__ __forceinline__ float load_untracked_at(const float* base, unsigned off) {
+  float r;
+  asm volatile("global_load_dword %0, %1, %2" : "=v"(r) : "v"(off), "s"(base) : "memory");
+  return r;
+}
+// 16 bytes at base + off + 1024 n (n < 4, a constant after unrolling)
+template <int OFF>
+__device__ __forceinline__ f32x4 load16_untracked(const float* base, unsigned off) {
+  f32x4 r;
+  asm volatile("global_load_dwordx4 %0, %1, %2 offset:%3" : "=v"(r) : "v"(off), "s"(base), "n"(OFF) : "memory");
+  return r;
+}
+__device__ __forceinline__ f32x4 load16_untracked_at(const float* base, unsigned off, int n) {
+  switch (n) {
+    case 0: return load16_untracked<0>(base, off);
+    case 1: return load16_untracked<1024>(base, off);
+    case 2: return load16_untracked<2048>(base, off);
+    default: return load16_untracked<3072>(base, off);
+  }
+}
 // Orders every later use of x after the preceding wait (volatile statements keep their order).
 template <class T>
 __device__ __forceinline__ void settle(T& x) { asm volatile("" : "+v"(x)); }
@@ -283,9 +376,6 @@ __device__ __forceinline__ void settle(T& x) { asm volatile("" : "+v"(x)); }
 // LDS counter retires in order, so "at most n outstanding" settles everything but the n youngest.
 // Another benefit: a tracked transposing read is treated as a possible alias of the tile transfer
 // in flight and is preceded by vmcnt(0).
-__device__ __forceinline__ unsigned lds_address(const void* p) {
-  return (unsigned)(size_t)(const __attribute__((address_space(3))) void*)p;
-}
 template <int OFF1>   // 8 bytes at addr and 8 bytes at addr + 512 OFF1
 __device__ __forceinline__ u32x4 lds_read2_untracked(unsigned addr) {
   u32x4 r;

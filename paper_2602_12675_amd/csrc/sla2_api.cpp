@@ -117,7 +117,7 @@ void make_layout(const Shape& s, sla2_ws_layout* L) {
   L->k_scale = take(s.quant ? BH * (size_t)s.Tn * sizeof(float) : 0);
   L->v_fp8 = take(s.quant == 3 ? BH * (size_t)s.Tn * s.bk * d : 0);
   L->v_scale = take(s.quant == 3 ? BH * (size_t)s.Tn * sizeof(float) : 0);
-  L->partial = take(BH * (size_t)s.chunks * (d * d + d) * sizeof(float));
+  L->partial = take(BH * ((size_t)s.chunks * (d * d + d) + (s.bf16 ? d * d : 0)) * sizeof(float));   // bf16: -h_total as fragments behind
   const size_t esz = s.bf16 ? 2 : 4;
   L->o_s = take(s.save ? BH * (size_t)s.N * d * esz : 0);
   L->o_l = take(s.save && !s.bf16 ? BH * (size_t)s.N * d * esz : 0);   // bf16 tensors: rebuilt from H_i in the backward pass
@@ -319,7 +319,7 @@ int sla2_forward(const sla2_params* params, const void* q, const void* k, const 
     if (SLA2_STAGE(SLA2_STAGE_KV_STATE, launch_kv_state_f32(s, (const float*)k, (const float*)v, k_mean, k_stats,
                                                             partial, st)) != hipSuccess)
       return SLA2_EHIP;
-    if (SLA2_STAGE(SLA2_STAGE_KV_TOTAL, launch_kv_total(s, partial, h_total, z_total, st)) != hipSuccess)
+    if (SLA2_STAGE(SLA2_STAGE_KV_TOTAL, launch_kv_total(s, partial, h_total, z_total, nullptr, st)) != hipSuccess)
       return SLA2_EHIP;
     if (SLA2_STAGE(SLA2_STAGE_ATTN,
                    launch_attn_f32(s, (const float*)q, (const float*)k, (const float*)v, k_mean, k_stats, h_total,
@@ -327,6 +327,7 @@ int sla2_forward(const sla2_params* params, const void* q, const void* k, const 
       return SLA2_EHIP;
     return SLA2_OK;
   }
+  float* h_frag = partial + (size_t)s.BH * s.chunks * (s.d * s.d + s.d);
   uint16_t* k_phi = at<uint16_t>(workspace, L.k_phi);
   float* z_blocks = at<float>(workspace, L.z_blocks);
   uint8_t* k_fp8 = at<uint8_t>(workspace, L.k_fp8);
@@ -337,11 +338,11 @@ int sla2_forward(const sla2_params* params, const void* q, const void* k, const 
                  launch_kv_state_bf16(s, (const uint16_t*)k, (const uint16_t*)v, k_mean, k_stats, partial, k_phi,
                                       z_blocks, k_fp8, k_scale, v_fp8, v_scale, st)) != hipSuccess)
     return SLA2_EHIP;
-  if (SLA2_STAGE(SLA2_STAGE_KV_TOTAL, launch_kv_total(s, partial, h_total, z_total, st)) != hipSuccess)
+  if (SLA2_STAGE(SLA2_STAGE_KV_TOTAL, launch_kv_total(s, partial, h_total, z_total, h_frag, st)) != hipSuccess)
     return SLA2_EHIP;
   if (SLA2_STAGE(SLA2_STAGE_ATTN,
                  launch_attn_bf16(s, (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, k_mean, k_phi,
-                                  z_blocks, k_fp8, k_scale, v_fp8, v_scale, h_total, z_total, idx, alpha, (uint16_t*)out,
+                                  z_blocks, k_fp8, k_scale, v_fp8, v_scale, h_frag, z_total, idx, alpha, (uint16_t*)out,
                                   lse_or_null, sv, st)) != hipSuccess)
     return SLA2_EHIP;
   return SLA2_OK;

@@ -87,8 +87,8 @@ __global__ __launch_bounds__(BQ * 2, 2) void bwd_q_mfma_kernel(
 
   auto dma = [&](int j, int buf) {
     const int t0 = j * kTileTokens, valid = min(kTileTokens, N - t0);
-    dma_tile<D, NW>(kh + (size_t)t0 * tok_stride, tok_stride, valid, kbuf(buf), w, lane);
-    dma_tile<D, NW>(vh + (size_t)t0 * tok_stride, tok_stride, valid, vbuf(buf), w, lane);
+    dma_tile<D, NW>(kh + (size_t)t0 * tok_stride, tok_stride, valid, lds_address(kbuf(buf)), w, lane);
+    dma_tile<D, NW>(vh + (size_t)t0 * tok_stride, tok_stride, valid, lds_address(vbuf(buf)), w, lane);
   };
   int j_cur = ntiles > 0 ? sel[0] : 0, j_nxt = ntiles > 1 ? sel[1] : 0;
   if (ntiles > 0) dma(j_cur, 0);
@@ -501,15 +501,13 @@ __global__ __launch_bounds__(256, 2) void bwd_kv_mfma_kernel(
   };
   auto request = [&](const Step& st, int buf) {
     const int src = st.row0 < N ? st.row0 : st.i * BQ, rows = max(1, min(64, N - st.row0));
-    dma_tile<D, NW, SL>(qh + (size_t)src * tok_stride, tok_stride, rows, qbuf(buf), w, lane);
-    dma_tile<D, NW, SL>(doh + (size_t)src * sout.n, sout.n, rows, gbuf(buf), w, lane);
+    dma_tile<D, NW, SL>(qh + (size_t)src * tok_stride, tok_stride, rows, lds_address(qbuf(buf)), w, lane);
+    dma_tile<D, NW, SL>(doh + (size_t)src * sout.n, sout.n, rows, lds_address(gbuf(buf)), w, lane);
     // every wave fetches the same 2 x 64 floats (same values to the same place: the counts of
     // outstanding transfers stay equal across the waves)
-    const size_t at = (size_t)bh * Tm * BQ + st.row0 + lane;
-    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(lraw2 + at),
-                                     (__attribute__((address_space(3))) void*)(stat + buf * 128), 4, 0, 0);
-    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(ds_in + at),
-                                     (__attribute__((address_space(3))) void*)(stat + buf * 128 + 64), 4, 0, 0);
+    const size_t at = (size_t)bh * Tm * BQ + st.row0;
+    dma_lane4(lraw2 + at, 4u * (unsigned)lane, lds_address(stat + buf * 128));
+    dma_lane4(ds_in + at, 4u * (unsigned)lane, lds_address(stat + buf * 128 + 64));
   };
 
   f32x16 dvall[ET], dkall[ET];

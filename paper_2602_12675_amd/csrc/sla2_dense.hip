@@ -26,27 +26,6 @@ template <int D> struct DenseSmem {
   static constexpr int kBytes = kLoop > kEpi ? kLoop : kEpi;
 };
 
-// lanes l and l ^ 32 combine their values through v_permlane32_swap (a vector instruction: no LDS round trip,
-// whose latency a wave that has the vector unit to itself would sit out)
-__device__ __forceinline__ float swap_halves_max(float x) {
-  const unsigned u = __builtin_bit_cast(unsigned, x);
-  const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);   // r[0] = low half twice, r[1] = high half twice
-  return fmaxf(__builtin_bit_cast(float, (unsigned)r[0]), __builtin_bit_cast(float, (unsigned)r[1]));
-}
-__device__ __forceinline__ float swap_halves_sum(float x) {
-  const unsigned u = __builtin_bit_cast(unsigned, x);
-  const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-  return __builtin_bit_cast(float, (unsigned)r[0]) + __builtin_bit_cast(float, (unsigned)r[1]);
-}
-// Between two phases.  LDS is written by the tile transfers only (waited for through vmcnt where a phase
-// needs them), and every operand read is waited for by the product that consumes it, so the barrier itself
-// waits for nothing: reads issued before it stay in flight across it.
-__device__ __forceinline__ void phase_barrier() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-}
-
 template <int D>
 __global__ __launch_bounds__(512, 1) void dense_pp_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                                                           const uint16_t* __restrict__ v, uint16_t* __restrict__ out,
@@ -74,8 +53,8 @@ __global__ __launch_bounds__(512, 1) void dense_pp_kernel(const uint16_t* __rest
   // tile t: K and V, 2 + 2 transfers of 1 KB per wave (rows past the end repeat the last one: their scores are masked)
   auto dma = [&](int t) {
     const int t0 = t * kTileTokens, valid = min(kTileTokens, N - t0);
-    dma_tile<D, NW, SL>(kh + (size_t)t0 * tok_stride, tok_stride, valid, kbuf(t), w, lane);
-    dma_tile<D, NW, SL>(vh + (size_t)t0 * tok_stride, tok_stride, valid, vbuf(t), w, lane);
+    dma_tile<D, NW, SL>(kh + (size_t)t0 * tok_stride, tok_stride, valid, lds_address(kbuf(t)), w, lane);
+    dma_tile<D, NW, SL>(vh + (size_t)t0 * tok_stride, tok_stride, valid, lds_address(vbuf(t)), w, lane);
   };
   dma(0);
   if (n > 1) dma(1);

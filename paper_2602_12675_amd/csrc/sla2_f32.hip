@@ -90,8 +90,11 @@ __global__ __launch_bounds__(256) void kv_state_f32_kernel(const float* __restri
 // Totals over the chunks of a head (Alg. 2's sums of h_j and z_j over all key blocks).  Each workgroup
 // owns 64 entries; its 4 thread groups walk the chunks 4 apart and meet in LDS, always in the same
 // order, so the totals are the same bits on every run.
+// h_frag (may be null): -h_total once more, as the accumulator fragments the bf16 attention kernel starts from:
+// [d/32 (c)][d/32 (e)][4][64 lanes][4], lane l of part x holding rows c = 8 x + 4 (l / 32) + 0..3 of column e = l % 32.
 __global__ __launch_bounds__(256) void kv_total_kernel(const float* __restrict__ partial, float* __restrict__ h_total,
-                                                       float* __restrict__ z_total, int d, int chunks) {
+                                                       float* __restrict__ z_total, float* __restrict__ h_frag, int d,
+                                                       int chunks) {
   __shared__ float red[256];
   const int per_head = d * d + d;
   const int bh = blockIdx.y;
@@ -106,15 +109,20 @@ __global__ __launch_bounds__(256) void kv_total_kernel(const float* __restrict__
   __syncthreads();
   if (cg == 0 && e < per_head) {
     const float tot = (red[threadIdx.x] + red[threadIdx.x + 64]) + (red[threadIdx.x + 128] + red[threadIdx.x + 192]);
-    if (e < d * d) h_total[(size_t)bh * d * d + e] = tot;
-    else z_total[(size_t)bh * d + (e - d * d)] = tot;
+    if (e < d * d) {
+      h_total[(size_t)bh * d * d + e] = tot;
+      const int row = e / d, col = e % d;
+      if (h_frag != nullptr)
+        h_frag[(size_t)bh * d * d + (((row / 32) * (d / 32) + col / 32) * 4 + row % 32 / 8) * 256 + (32 * (row % 8 / 4) + col % 32) * 4 +
+               row % 4] = -tot;
+    } else z_total[(size_t)bh * d + (e - d * d)] = tot;
   }
 }
 
-hipError_t launch_kv_total(const Shape& s, const float* partial, float* h_total, float* z_total, hipStream_t stream) {
+hipError_t launch_kv_total(const Shape& s, const float* partial, float* h_total, float* z_total, float* h_frag, hipStream_t stream) {
   int per_head = s.d * s.d + s.d;
   kv_total_kernel<<<dim3((unsigned)((per_head + 63) / 64), (unsigned)s.BH), 256, 0, stream>>>(partial, h_total, z_total,
-                                                                                             s.d, s.chunks);
+                                                                                             h_frag, s.d, s.chunks);
   return hipGetLastError();
 }
 

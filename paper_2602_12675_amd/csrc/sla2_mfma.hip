@@ -292,25 +292,41 @@ hipError_t launch_kv_state_bf16(const Shape& s, const uint16_t* k, const uint16_
 // =============================================================================================
 // attn_mfma
 // =============================================================================================
+// The lane index again, from the hardware: what a long loop derives from it does not stay in registers meanwhile.
+__device__ __forceinline__ unsigned lane_again() {
+  unsigned l;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+  return l;
+}
 enum AttnMode { kSparseBf16 = 0, kSparseFp8 = 1, kDenseBf16 = 2, kSparseInt8 = 3, kSparseFp8V = 4 };
 
 
-// LDS carve-up.  Loop: two buffers, each one K tile (bf16, or 8-bit codes), one V tile (bf16) and, when
-// V is quantised for the second product, one tile of its codes,
-// all in the swizzled layout the load unit fills directly.  Epilogue: H_i^T as bf16 [D][D+8] and the
-// output tile [BQ][D+8], overlaying the tile buffers.
-template <int D, int BQ, bool FP8, bool VQ = false> struct AttnSmem {
-  static constexpr int kLd = TileGeom<D>::kLd;
+// Whether the main loop is the pipelined one (see there); the others keep the plain loop: the dense comparator, and
+// d = 64 with 128-row blocks, whose waves own single tiles of the d x d state.
+template <int D, int BQ, int MODE> constexpr bool kPipelined = MODE != kDenseBf16 && HSplit<D, BQ / 32>::kNtw == D / 32;
+
+// LDS carve-up.  Loop, in this order: K^phi fragments of one tile, each wave's own (pipelined loop only); two V tiles
+// (bf16); codes of the first V tile (when V is quantised for the second product); two K tiles (bf16, or 8-bit codes);
+// codes of the second V tile - all in the layouts the load unit fills directly.  Before the loop the query rows of
+// waves 0, 1 pass through the place of the second V tile and those of waves 2, 3 through that from the second K tile on.
+// Epilogue, over the same memory: H_i^T as bf16 [D][D+8], the output tile [BQ][D+8] and Z_i as three bf16 rows.  At
+// d = 128 the loop takes at most 80 KB: two workgroups a CU.
+template <int D, int BQ, bool FP8, bool VQ, bool PIPE> struct AttnSmem {
+  static constexpr int kLd = TileGeom<D>::kLd, NW = BQ / 32;
   static constexpr int kVBytes = SwizzledLayout<D>::kTileBytes;
   static constexpr int kKBytes = FP8 ? SwizzledLayout8<D>::kTileBytes : kVBytes;
   static constexpr int kVqBytes = VQ ? SwizzledLayoutVq<D>::kTileBytes : 0;   // e4m3 codes of V, when P V is an FP8 product
-  static constexpr int kBufBytes = kKBytes + kVBytes + kVqBytes;
-  static constexpr int kLoopBytes = 2 * kBufBytes;
-  static constexpr int kEpiBytes = (D + BQ) * kLd * 2;
-  static constexpr int kTiles = kLoopBytes > kEpiBytes ? kLoopBytes : kEpiBytes;
-  static constexpr int kZsOff = kTiles;                             // float [D]: Z_i
-  static constexpr int kRedOff = kZsOff + D * 4;                    // float [4]: block-wide max
-  static constexpr int kBytes = kRedOff + 16;
+  static constexpr int kQBytes = 32 * D * 2;                        // query rows of one wave
+  static constexpr int kVOff = PIPE ? kTileTokens * D * 2 : 0;      // behind the K^phi fragments
+  static constexpr int kVq0Off = kVOff + 2 * kVBytes;
+  static constexpr int kKOff = kVq0Off + kVqBytes;
+  static constexpr int kVq1Off = kKOff + 2 * kKBytes;
+  static constexpr int kTiles = kVq1Off + kVqBytes, kQEnd = kKOff + kKBytes + (NW - 2) * kQBytes;
+  static constexpr int kLoopBytes = kTiles > kQEnd ? kTiles : kQEnd;
+  static constexpr int kZsOff = (D + BQ) * kLd * 2;                 // bf16 [3][D+8]: Z_i (epilogue)
+  static constexpr int kEpiBytes = kZsOff + 3 * kLd * 2;
+  static constexpr int kBytes = kLoopBytes > kEpiBytes ? kLoopBytes : kEpiBytes;
+  __device__ static unsigned q_rows(int w) { return w < 2 ? kVOff + kVBytes + w * kQBytes : kKOff + kKBytes + (w - 2) * kQBytes; }
 };
 
 
@@ -323,7 +339,7 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const double* __restrict__ k_mean, const uint16_t* __restrict__ k_phi, const float* __restrict__ z_blocks,
     const uint8_t* __restrict__ k_codes, const float* __restrict__ k_scale, const uint8_t* __restrict__ v_codes,
-    const float* __restrict__ v_scale, const float* __restrict__ h_total,
+    const float* __restrict__ v_scale, const float* __restrict__ h_frag,
     const float* __restrict__ z_total, const int32_t* __restrict__ block_idx, const float* __restrict__ alpha,
     uint16_t* __restrict__ out, float* __restrict__ lse, uint16_t* __restrict__ o_s_save,
     uint16_t* __restrict__ o_l_save, float* __restrict__ lse_save, uint16_t* __restrict__ h_save,
@@ -339,23 +355,27 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
   constexpr int KS = D / 16;            // contraction steps over the head dimension
   constexpr int ET = D / 32;            // 32-wide tiles over the head dimension
   typedef HSplit<D, NW> HS;
-  typedef AttnSmem<D, BQ, FP8, FP8V> SM;
-  typedef SwizzledLayout<D> SL;
+  constexpr bool PIPE = kPipelined<D, BQ, MODE>;
+  typedef AttnSmem<D, BQ, FP8, FP8V, PIPE> SM;
+  // the layout without bank conflicts where the tile transfers of a workgroup's waves allow it
+  typedef typename std::conditional<PIPE && D == 128 && NW == 4, SwizzledLayoutB<128>, SwizzledLayout<D>>::type SL;
   typedef SwizzledLayout8<D> SL8;
   // Loads and LDS reads of the main loop are issued untracked and waited for by count (see
   // load_untracked).  The one exception is the shape with the highest register pressure, bf16
   // operands at d = 128 with two workgroups per CU: holding reads in flight costs registers it
   // does not have, and the compiler-tracked form is the faster one there.
   constexpr bool kManual = FP8;
-  // global -> LDS transfers one wave issues per tile (1 KB each): V, and K in bf16 or e4m3
-  constexpr int kDmaOps = kTileTokens * D * 2 / 1024 / NW + kTileTokens * D * (FP8 ? 1 : 2) / 1024 / NW +
-                          (FP8V ? kTileTokens * D / 1024 / NW : 0);
+  // global -> LDS transfers (1 KB each) a wave issues per tile: K in bf16 or 8-bit codes, V with its codes, K^phi fragments
+  constexpr int kKOps = kTileTokens * D * (FP8 ? 1 : 2) / 1024 / NW;
+  constexpr int kVOps = kTileTokens * D * 2 / 1024 / NW + (FP8V ? kTileTokens * D / 1024 / NW : 0);
+  constexpr int kDmaOps = kKOps + kVOps;
+  constexpr int kSteps = kTileTokens / 16, kPhiOps = PIPE ? HS::kMtw * kSteps : 0;
+  constexpr int kQOps = SM::kQBytes / 1024;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-  float* zs = reinterpret_cast<float*>(smem + SM::kZsOff);
-  float* red = reinterpret_cast<float*>(smem + SM::kRedOff);
-  auto kbuf = [&](int buf) { return smem + buf * SM::kBufBytes; };
-  auto vbuf = [&](int buf) { return reinterpret_cast<uint16_t*>(smem + buf * SM::kBufBytes + SM::kKBytes); };
-  auto vqbuf = [&](int buf) { return smem + buf * SM::kBufBytes + SM::kKBytes + SM::kVBytes; };
+  const unsigned lds0 = lds_address(smem);
+  auto kbuf = [&](int buf) { return lds0 + SM::kKOff + buf * SM::kKBytes; };
+  auto vbuf = [&](int buf) { return lds0 + SM::kVOff + buf * SM::kVBytes; };
+  auto vqbuf = [&](int buf) { return lds0 + SM::kVq0Off + buf * (SM::kVq1Off - SM::kVq0Off); };
 
   // Workgroups are dealt round-robin to the 8 XCDs, each with its own L2.  Consecutive query blocks of
   // a head share key/value tiles: every head is cut into 8 runs of consecutive blocks, one per XCD, and
@@ -388,61 +408,126 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
   float sv_cur = 1.f, sv_prev = 1.f;
   if constexpr (FP8V) sv_cur = sv_prev = ntiles > 0 ? v_scale[blk0 + j_cur] : 1.f;
 
-  // tile s: global memory -> LDS buffer `buf`, no registers involved (completion: vmcnt)
+  // key block j: global memory -> LDS buffer `buf`, no registers involved (completion: vmcnt)
+  const uint8_t* k_codes_h = FP8 ? k_codes + blk0 * (kTileTokens * D) : nullptr;
+  const uint8_t* v_codes_h = FP8V ? v_codes + blk0 * (kTileTokens * D) : nullptr;
+  const uint16_t* k_phi_h = DENSE ? nullptr : k_phi + kphi_offset<D>(blk0, mt0, 0, 0);
+  const unsigned tile_stride = (unsigned)tok_stride * (kTileTokens * 2);   // bytes; below 2^31
+  auto rows_at = [&](const uint16_t* head, int j) { return (const uint16_t*)((const char*)head + (size_t)(unsigned)j * tile_stride); };
+  // what a lane adds to the base of its transfers; the pipelined loop keeps these in registers
+  unsigned lane16 = 16u * lane;                            // consecutive bytes: K^phi fragments
+  unsigned row_off = tile_lane_off<D, NW, SL>(tok_stride, w, lane);   // a whole tile of bf16 rows
+  unsigned code_off = FP8 ? tile8_lane_off<D>(lane) : 0u;  // a tile of 8-bit codes
+  auto dma_rows = [&](const uint16_t* head, int j, unsigned lds) {
+    const int valid = min(kTileTokens, N - j * kTileTokens);
+    if ((kManual || PIPE) && valid == kTileTokens) dma_tile_full<D, NW, SL>(rows_at(head, j), tok_stride, lds, w, row_off);
+    else dma_tile<D, NW, SL>(rows_at(head, j), tok_stride, valid, lds, w, PIPE ? lane_again() : lane);
+  };
+  auto dma_k = [&](int j, int buf) {
+    if constexpr (FP8) dma_tile8<D, NW>(k_codes_h + (unsigned)j * (kTileTokens * D), kbuf(buf), w, code_off);
+    else dma_rows(kh, j, kbuf(buf));
+  };
+  auto dma_v = [&](int j, int buf) {
+    dma_rows(vh, j, vbuf(buf));
+    if constexpr (FP8V) dma_tile_vq<D, NW>(v_codes_h + (unsigned)j * (kTileTokens * D), vqbuf(buf), w, PIPE ? lane_again() : lane);
+  };
   auto dma = [&](int j, int buf) {
-    const int t0 = j * kTileTokens, valid = min(kTileTokens, N - t0);
-    if constexpr (FP8) dma_tile8<D, NW>(k_codes + (blk0 + j) * kTileTokens * D, kbuf(buf), w, lane);
-    else if (kManual && valid == kTileTokens) dma_tile_full<D, NW>(kh + (size_t)t0 * tok_stride, tok_stride, reinterpret_cast<uint16_t*>(kbuf(buf)), w, lane);
-    else dma_tile<D, NW>(kh + (size_t)t0 * tok_stride, tok_stride, valid, reinterpret_cast<uint16_t*>(kbuf(buf)), w, lane);
-    if (kManual && valid == kTileTokens) dma_tile_full<D, NW>(vh + (size_t)t0 * tok_stride, tok_stride, vbuf(buf), w, lane);
-    else dma_tile<D, NW>(vh + (size_t)t0 * tok_stride, tok_stride, valid, vbuf(buf), w, lane);
-    if constexpr (FP8V) dma_tile_vq<D, NW>(v_codes + (blk0 + j) * kTileTokens * D, vqbuf(buf), w, lane);
+    dma_k(j, buf);
+    dma_v(j, buf);
+  };
+  // K^phi fragment (channel tile mt0 + a, 16-token step ks) of block j -> its place in this wave's part of LDS; the
+  // fragments of a channel tile are consecutive on both sides
+  const unsigned phi_lds = lds0 + w * (HS::kMtw * kSteps * 1024);
+  auto dma_phi = [&](int j, int a, int ks) {
+    dma_lane16_at(k_phi_h + (unsigned)j * (kTileTokens * D) + a * (kSteps * 512), lane16, phi_lds + a * (kSteps * 1024), ks);
+  };
+  // This wave's 32 query rows -> LDS at `lds` in the swizzled layout (whole lines of memory at a time; read as operand
+  // fragments from there, every lane would touch lines of its own); rows past the end repeat the last one; never stored.
+  auto dma_q = [&](unsigned lds) {
+    typedef SwizzledLayout<D> L;
+    constexpr int kRows = 1024 / (D * 2);
+    const unsigned l = lane_again();
+#pragma unroll
+    for (int n = 0; n < kQOps; n++) {
+      const int row = n * kRows + (int)l / L::kChunks;
+      const unsigned r = (unsigned)min(32 * w + row, rows_valid - 1);
+      dma_lane16(qh + (size_t)row0 * tok_stride, r * (unsigned)(tok_stride * 2) + 16u * (((int)l % L::kChunks) ^ L::swz(row)), lds + n * 1024);
+    }
+  };
+  // fragment ks of those rows (B operand of S^T = K Q^T): lane <- row l % 32, 8 columns from column 8 * (chunk ^ XOR(ks))
+  auto read_q = [&](unsigned lds, int chunk, int x) {
+    typedef SwizzledLayout<D> L;
+    const int row = (int)lane_again() % 32;
+    return lds_read16_untracked<0>((lds + row * (D * 2) + 16u * (chunk ^ L::swz(row))) ^ (16u * x));
   };
 
-  if (ntiles > 0) dma(j_cur, 0);
-
-  // Q fragments (B operand of S^T = K Q^T): lane <- Q[row0 + 32 w + l%32][16 ks + 8 g + 0..7]
-  bf16x8 qf[KS];
-  {
-    const int r = min(32 * w + lane % 32, rows_valid - 1);   // rows past the end repeat the last one; never stored
-    const uint16_t* src = qh + (size_t)(row0 + r) * tok_stride;
-    // bf16 product: fragment ks = columns 16 ks + 8 g + 0..7.  FP8 product (64 deep): the lane's
-    // operand of step ks2 is columns 64 ks2 + 32 g + 0..31, held as fragments 4 ks2 + 0..3.
-    // INT8 product (32 deep): columns 32 ks4 + 16 g + 0..15, fragments 2 ks4 + 0..1.
-#pragma unroll
-    for (int ks = 0; ks < KS; ks++)
-      qf[ks] = *reinterpret_cast<const bf16x8*>(
-          src + (INT8 ? 32 * (ks / 2) + 16 * g + 8 * (ks % 2) : FP8 ? 64 * (ks / 4) + 32 * g + 8 * (ks % 4) : 16 * ks + 8 * g));
-  }
+  // Requests in the order their results are needed and can be made: the query rows and the d x d total need nothing but
+  // the block index; the tiles need the block list.
+  dma_q(lds0 + SM::q_rows(w));
   // The state accumulators start at -H_total (and -Z_total): the loop adds the h_j and z_j of the selected
-  // blocks, which leaves -(H_total - sum) = -H_i.  The d x d total is read here, behind the first tile's
-  // transfer, instead of in the epilogue, where a wave would wait for it with nothing else to do.
-  f32x16 hacc[HS::kMtw][HS::kNtw];
+  // blocks, which leaves -(H_total - sum) = -H_i.  The total lies there negated and as accumulator fragments
+  // (kv_total): four 16-byte loads a tile.
+  f32x4 hq[HS::kMtw][HS::kNtw][4];
   float zsel[HS::kMtw];
-#pragma unroll
-  for (int a = 0; a < HS::kMtw; a++) {
-    zsel[a] = 0.f;
-#pragma unroll
-    for (int b = 0; b < HS::kNtw; b++)
-#pragma unroll
-      for (int e = 0; e < 16; e++) hacc[a][b][e] = 0.f;
-  }
   if constexpr (!DENSE) {
-    const float* htot = h_total + (size_t)bh * D * D;
 #pragma unroll
-    for (int a = 0; a < HS::kMtw; a++) {
+    for (int a = 0; a < HS::kMtw; a++)
 #pragma unroll
       for (int b = 0; b < HS::kNtw; b++)
 #pragma unroll
-        for (int e = 0; e < 16; e++)
-          hacc[a][b][e] = -htot[(32 * (mt0 + a) + 8 * (e / 4) + 4 * g + e % 4) * D + 32 * (nt0 + b) + lane % 32];
-      zsel[a] = -z_total[(size_t)bh * D + 32 * (mt0 + a) + lane % 32];
+        for (int x = 0; x < 4; x++)
+          hq[a][b][x] = load16_untracked_at(h_frag + (size_t)bh * D * D + ((mt0 + a) * ET + nt0 + b) * 1024, lane16, x);
+#pragma unroll
+    for (int a = 0; a < HS::kMtw; a++)
+      zsel[a] = load_untracked_at(z_total + (size_t)bh * D + 32 * (mt0 + a), 4u * (unsigned)(lane % 32));
+  }
+  if (ntiles > 0) {
+    dma(j_cur, 0);
+    if constexpr (PIPE) {
+#pragma unroll
+      for (int a = 0; a < HS::kMtw; a++)
+#pragma unroll
+        for (int ks = 0; ks < kSteps; ks++) dma_phi(j_cur, a, ks);
+    }
+    wait_vmcnt<kDmaOps + kPhiOps>();                 // query rows and totals are there
+  } else {
+    wait_vmcnt<0>();
+  }
+  f32x16 hacc[HS::kMtw][HS::kNtw];
+#pragma unroll
+  for (int a = 0; a < HS::kMtw; a++) {
+    if constexpr (!DENSE) {
+      settle(zsel[a]);
+      zsel[a] = -zsel[a];
+    }
+#pragma unroll
+    for (int b = 0; b < HS::kNtw; b++)
+      if constexpr (!DENSE) {
+#pragma unroll
+        for (int x = 0; x < 4; x++) {
+          settle(hq[a][b][x]);
+#pragma unroll
+          for (int e = 0; e < 4; e++) hacc[a][b][4 * x + e] = hq[a][b][x][e];
+        }
+        settle(hacc[a][b]);                          // one value from here on, not four
+      }
+  }
+  // bf16 product: fragment ks = columns 16 ks + 8 g + 0..7.  FP8 product (64 deep): the lane's
+  // operand of step ks2 is columns 64 ks2 + 32 g + 0..31, held as fragments 4 ks2 + 0..3.
+  // INT8 product (32 deep): columns 32 ks4 + 16 g + 0..15, fragments 2 ks4 + 0..1.
+  bf16x8 qf[KS];
+  {
+    u32x4 raw[KS];
+#pragma unroll
+    for (int ks = 0; ks < KS; ks++)
+      raw[ks] = read_q(lds0 + SM::q_rows(w), INT8 ? 2 * g : FP8 ? 4 * g : g, INT8 ? 4 * (ks / 2) + ks % 2 : FP8 ? 8 * (ks / 4) + ks % 4 : 2 * ks);
+    wait_lgkmcnt(0);
+#pragma unroll
+    for (int ks = 0; ks < KS; ks++) {
+      settle(raw[ks]);
+      qf[ks] = __builtin_bit_cast(bf16x8, raw[ks]);
     }
   }
-  // Everything issued so far is settled here, on every path into the main loop; a pending load
-  // left over from the prologue would otherwise put a vmcnt wait in front of every use of a Q
-  // fragment inside the loop and drain the tile prefetch with it.
-  __builtin_amdgcn_s_waitcnt(kVmcnt0);
   // FP8: quant(Q_i) with one scale for the whole query block (Sec. 5)
   long qf8[FP8 ? KS : 1];
   float s_q = 1.f;
@@ -452,13 +537,12 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
     for (int ks = 0; ks < KS; ks++)
 #pragma unroll
       for (int e = 0; e < 8; e++) amax = fmaxf(amax, fabsf((float)qf[ks][e]));
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) amax = fmaxf(amax, __shfl_xor(amax, o));
-    if (lane == 0) red[w] = amax;
+    amax = wave_max(amax);
+    if (lane == 0) *reinterpret_cast<float*>(smem + SM::q_rows(w)) = amax;   // (this wave has read its rows)
     __syncthreads();
-    amax = red[0];
+    amax = 0.f;
 #pragma unroll
-    for (int x = 1; x < NW; x++) amax = fmaxf(amax, red[x]);
+    for (int x = 0; x < NW; x++) amax = fmaxf(amax, *reinterpret_cast<const float*>(smem + SM::q_rows(x)));
     constexpr float kCodeMax = INT8 ? kInt8Max : kE4M3Max;
     const float inv = amax > 0.f ? kCodeMax / amax : 1.f;
     s_q = amax > 0.f ? amax / kCodeMax : 1.f;
@@ -480,8 +564,12 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
       qf8[ks] = (long)(((unsigned long)(unsigned)hi << 32) | (unsigned)lo);
     }
   }
+  if (PIPE && ntiles > 0) wait_vmcnt<kVOps + kPhiOps>();   // the first K tile (V and K^phi: in front of the loop)
+  else wait_vmcnt<0>();
   __syncthreads();                                   // tile 0 is in LDS for everyone
-
+  if constexpr (PIPE) {
+    if (ntiles > 1) dma_k(j_nxt, 1);                 // (its place held query rows until here)
+  }
   f32x16 oacc[ET];
 #pragma unroll
   for (int et = 0; et < ET; et++)
@@ -493,347 +581,731 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
   constexpr float kPShift = FP8 ? 8.f : 0.f;
   const float c0 = kLog2e * rsqrtf((float)D);        // scores are used as S * log2(e) / sqrt(d)
 
-  for (int s = 0; s < ntiles; s++) {
-    const int buf = s & 1;
-    const int j = j_cur;
-    const int valid = min(kTileTokens, N - j * kTileTokens);
-    const float sk = sk_cur;
-    const int j_nn = tile_block(s + 2);                // consumed in the next iteration
-    if constexpr (FP8) sk_cur = k_scale[blk0 + j_nxt];
-    const float sv = sv_cur;
-    if constexpr (FP8V) sv_cur = v_scale[blk0 + j_nxt];
-    // K^phi fragments and z_j of this tile straight from global memory into registers (no other
-    // wave needs them); they are consumed after the softmax.  They are issued before the next
-    // tile's transfer and, since vmcnt retires in order, are complete once at most kDmaOps
-    // operations are outstanding.  The loads are opaque to the compiler on purpose: its own
-    // bookkeeping across the conditional transfer below falls back to vmcnt(0) at their first
-    // use, which stalls every iteration on the tile that was just requested.
-    bf16x8 kphi[DENSE ? 1 : HS::kMtw][kTileTokens / 16];
-    float zj[DENSE ? 1 : HS::kMtw];
-    auto state_loads = [&]() {
-      if constexpr (!DENSE) {
+  // Q^phi = softmax_d(Q) of this lane's row, in the place of its fragments - without its normaliser, which cancels
+  // between Q^phi H_i and Q^phi Z_i.  In pieces: the pipelined loop has them between the products of its last tile.
+  // (The low-bit modes dropped the bf16 rows after quantisation; they come back through LDS, q_again.)
+  float qm = -INFINITY;
+  auto q_max = [&]() {
 #pragma unroll
-        for (int a = 0; a < HS::kMtw; a++) {
+    for (int ks = 0; ks < KS; ks++)
 #pragma unroll
-          for (int ks = 0; ks < kTileTokens / 16; ks++)
-            kphi[a][ks] = load_maybe_tracked<bf16x8, kManual>(k_phi + kphi_offset<D>(blk0 + j, mt0 + a, ks, lane));
-          zj[a] = load_maybe_tracked<float, kManual>(z_blocks + (blk0 + j) * D + 32 * (mt0 + a) + lane % 32);
-          if constexpr (!kManual) zsel[a] += zj[a];
-        }
-      }
-    };
-    auto next_tile = [&]() {
-      if (s + 1 < ntiles) dma(j_nxt, buf ^ 1);       // next tile -> other buffer
-    };
-    // With the reads under this kernel's own control (low-bit modes) the requests for the rest of the
-    // tile's data are placed inside the score product: the fragment loads behind its operand reads, the
-    // next tile's transfer behind its matrix instructions - some hundred instructions that otherwise
-    // stand in front of it, on a wave whose progress is bound by its own chain of dependent steps.
-    constexpr bool kRequestsInsideScores = kManual;
-    if constexpr (!kRequestsInsideScores) {
-      state_loads();
-      next_tile();
-    }
-    const uint16_t* vt = vbuf(buf);
-    // Two waves share a SIMD.  The one that is issuing matrix products is given the higher issue priority, so
-    // that the matrix pipe is fed while the other wave's softmax fills the gaps (measured: 2 % on the
-    // sparse modes; the dense comparator, all of whose waves are in step, loses with it).
-    if constexpr (!DENSE) __builtin_amdgcn_s_setprio(2);
-    // ---- S^T = K Q^T (keys x query rows), two 32-key halves ----
+      for (int e = 0; e < 8; e++) qm = fmaxf(qm, (float)qf[ks][e]);
+    qm = swap_halves_max(qm) * kLog2e;
+  };
+  auto q_exp = [&](int ks) {
+#pragma unroll
+    for (int e = 0; e < 8; e++) qf[ks][e] = (__bf16)fast_exp2((float)qf[ks][e] * kLog2e - qm);
+    settle(qf[ks]);
+  };
+  // where the query rows go at the last tile (V in vbuf(buf)): both K tiles and the other V tile are done with
+  auto q_again = [&](int buf) { return w < 2 ? vbuf(buf ^ 1) + w * SM::kQBytes : kbuf(0) + (w - 2) * SM::kQBytes; };
+
+  if constexpr (PIPE) {
+    // The pipelined loop.  Pass s forms S of tile s + 1, then runs the products of tile s, P V and K^phi^T V, with the
+    // softmax of tile s + 1 in between them: a matrix product holds the issue port of its SIMD for about a third of its
+    // time, and what fits into the rest - a wave's own vector instructions included - costs nothing (micro-benchmark: one
+    // product alone 33 cycles, with four multiply-adds behind it 34).  P replaces its predecessor 16 tokens at a time,
+    // right after the products that read it, so it takes no second set of registers.
+    // At d = 128 with 128-row blocks the kernel draws the card down to 1.6 GHz: what counts is work, not latency.  Measured
+    // on 12 heads of 32,760 tokens: bf16, 26 tiles a block 520 -> 480 us; FP8, 15 tiles 287 -> 276 us.
+    // Transfers, all global -> LDS: K of tile s + 2 and V of tile s + 1 are requested at the top of pass s, into places
+    // read for the last time before the barrier above, and have a whole pass to land; the K^phi fragments of tile s + 1
+    // are requested one by one as those of tile s leave the wave's part of LDS.  Counts: requests at the top are older
+    // than the kPhiOps fragment requests of the same pass and younger than those of the pass before.
+    // What the lanes derive from their index stays in registers too; the compiler would work it out again in every pass.
+    unsigned k_lane = FP8 ? SL8::offset(lane % 32, (INT8 ? 16 : 32) * g) : 2 * SL::offset(lane % 32, 8 * g);
+    constexpr bool kPeel = FP8;
+    // A V fragment is two transposing reads, 8 rows apart: the row permutation is the same there, or differs in one bit.
+    unsigned v_lane = 2 * SL::offset(4 * g + (lane % 16) / 4, 16 * ((lane / 16) % 2) + 4 * (lane % 4));
+    constexpr unsigned kHiXor = std::is_same<SL, SwizzledLayout<D>>::value ? 0u : 32u;
+    settle(lane16);
+    settle(row_off);
+    if constexpr (FP8) settle(code_off);
+    settle(k_lane);
+    settle(v_lane);
     f32x16 sacc[2];
+    // S^T = K Q^T of the tile in kbuf(buf), two 32-key halves
+    auto scores = [&](int buf) {
+      const unsigned ka = kbuf(buf) + k_lane;
+      if constexpr (INT8) {
+        // 32-deep integer products (v_mfma_i32_32x32x32_i8: lane l holds row l % 32, contraction indices
+        // 16 (l / 32) + 0..15): the operand of (step ks4, key half mt) is 16 consecutive codes of key row
+        // 32 mt + l % 32 - one 16-byte read at (address of step 0) ^ 32 ks4 in the pair-swizzled tile.
+        // Sums of 128 products of codes stay below 2^21: exact in the int32 accumulator and in fp32.
+        constexpr int KS4 = D / 32;
+        u32x4 kq[KS4][2];
 #pragma unroll
-    for (int mt = 0; mt < 2; mt++)
-#pragma unroll
-      for (int e = 0; e < 16; e++) sacc[mt][e] = 0.f;
-    if constexpr (INT8) {
-      // 32-deep integer products (v_mfma_i32_32x32x32_i8: lane l holds row l % 32, contraction indices
-      // 16 (l / 32) + 0..15): the operand of (step ks4, key half mt) is 16 consecutive codes of key row
-      // 32 mt + l % 32 - one 16-byte read at (address of step 0) ^ 32 ks4 in the pair-swizzled tile.
-      // Sums of 128 products of codes stay below 2^21: exact in the int32 accumulator and in fp32.
-      constexpr int KS4 = D / 32;
-      const unsigned ka = lds_address(kbuf(buf) + SL8::offset(lane % 32, 16 * g));
-      u32x4 kq[KS4][2];
-#pragma unroll
-      for (int ks4 = 0; ks4 < KS4; ks4++) {
-        kq[ks4][0] = lds_read16_untracked<0>(ka ^ (32u * ks4));
-        kq[ks4][1] = lds_read16_untracked<32 * D>(ka ^ (32u * ks4));
-      }
-      if constexpr (kRequestsInsideScores) state_loads();
-      i32x16 iacc[2];
-#pragma unroll
-      for (int mt = 0; mt < 2; mt++)
-#pragma unroll
-        for (int e = 0; e < 16; e++) iacc[mt][e] = 0;
-#pragma unroll
-      for (int ks4 = 0; ks4 < KS4; ks4++)
-#pragma unroll
-        for (int mt = 0; mt < 2; mt++) {
-          wait_lgkmcnt(2 * (KS4 - 1 - ks4) + 1 - mt);
-          settle(kq[ks4][mt]);
-          const u32x4 kk = kq[ks4][mt];
-          const i32x4 a = {(int)kk[0], (int)kk[1], (int)kk[2], (int)kk[3]};
-          const i32x4 b = {(int)(unsigned)((unsigned long)qf8[2 * ks4]), (int)(unsigned)((unsigned long)qf8[2 * ks4] >> 32),
-                           (int)(unsigned)((unsigned long)qf8[2 * ks4 + 1]), (int)(unsigned)((unsigned long)qf8[2 * ks4 + 1] >> 32)};
-          iacc[mt] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, iacc[mt], 0, 0, 0);
+        for (int ks4 = 0; ks4 < KS4; ks4++) {
+          kq[ks4][0] = lds_read16_untracked<0>(ka ^ (32u * ks4));
+          kq[ks4][1] = lds_read16_untracked<32 * D>(ka ^ (32u * ks4));
         }
-      if constexpr (kRequestsInsideScores) next_tile();
-#pragma unroll
-      for (int mt = 0; mt < 2; mt++)
-#pragma unroll
-        for (int e = 0; e < 16; e++) sacc[mt][e] = (float)iacc[mt][e];
-    } else if constexpr (FP8) {
-      // 64-deep products: the operand of (step ks2, key half mt) is 32 consecutive codes of key row
-      // 32 mt + l % 32, two 16-byte reads.  The swizzle is an XOR on the pair bits of the address,
-      // so step ks2 sits at (address of step 0) ^ 64 ks2; all reads of a tile are issued up front.
-      static_assert(D % 64 == 0, "the FP8 product consumes the head dimension 64 at a time");
-      constexpr int KS2 = D / 64;
-      const unsigned ka = lds_address(kbuf(buf) + SL8::offset(lane % 32, 32 * g));
-      u32x4 klo[KS2][2], khi[KS2][2];
-#pragma unroll
-      for (int ks2 = 0; ks2 < KS2; ks2++) {
-        klo[ks2][0] = lds_read16_untracked<0>(ka ^ (64u * ks2));
-        khi[ks2][0] = lds_read16_untracked<16>(ka ^ (64u * ks2));
-        klo[ks2][1] = lds_read16_untracked<32 * D>(ka ^ (64u * ks2));
-        khi[ks2][1] = lds_read16_untracked<32 * D + 16>(ka ^ (64u * ks2));
-      }
-      if constexpr (kRequestsInsideScores) state_loads();
-#pragma unroll
-      for (int ks2 = 0; ks2 < KS2; ks2++)
-#pragma unroll
-        for (int mt = 0; mt < 2; mt++) {
-          wait_lgkmcnt(2 * (2 * (KS2 - 1 - ks2) + 1 - mt));
-          settle(klo[ks2][mt]);
-          settle(khi[ks2][mt]);
-          const u32x4 lo = klo[ks2][mt], hi = khi[ks2][mt];
-          const i32x8 a = {(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3], (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
-          i32x8 b;
-#pragma unroll
-          for (int x = 0; x < 4; x++) {
-            b[2 * x] = (int)(unsigned)((unsigned long)qf8[4 * ks2 + x]);
-            b[2 * x + 1] = (int)(unsigned)((unsigned long)qf8[4 * ks2 + x] >> 32);
-          }
-          sacc[mt] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, sacc[mt], 0, 0, 0, 0, 0, 0);   // e4m3 x e4m3, no scales
-        }
-      if constexpr (kRequestsInsideScores) next_tile();
-    } else {
-      const uint16_t* kt = reinterpret_cast<const uint16_t*>(kbuf(buf));
-#pragma unroll
-      for (int ks = 0; ks < KS; ks++)
+        i32x16 iacc[2];
 #pragma unroll
         for (int mt = 0; mt < 2; mt++)
-          sacc[mt] = mfma_bf16(row_fragment<SL>(kt, 32 * mt + lane % 32, 16 * ks + 8 * g), qf[ks], sacc[mt]);
+#pragma unroll
+          for (int e = 0; e < 16; e++) iacc[mt][e] = 0;
+#pragma unroll
+        for (int ks4 = 0; ks4 < KS4; ks4++)
+#pragma unroll
+          for (int mt = 0; mt < 2; mt++) {
+            wait_lgkmcnt(2 * (KS4 - 1 - ks4) + 1 - mt);
+            settle(kq[ks4][mt]);
+            const i32x4 a = __builtin_bit_cast(i32x4, kq[ks4][mt]);
+            const i32x4 b = {(int)(unsigned)((unsigned long)qf8[2 * ks4]), (int)(unsigned)((unsigned long)qf8[2 * ks4] >> 32),
+                             (int)(unsigned)((unsigned long)qf8[2 * ks4 + 1]), (int)(unsigned)((unsigned long)qf8[2 * ks4 + 1] >> 32)};
+            iacc[mt] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, iacc[mt], 0, 0, 0);
+          }
+#pragma unroll
+        for (int mt = 0; mt < 2; mt++)
+#pragma unroll
+          for (int e = 0; e < 16; e++) sacc[mt][e] = (float)iacc[mt][e];
+      } else if constexpr (FP8) {
+        // 64-deep products: the operand of (step ks2, key half mt) is 32 consecutive codes of key row
+        // 32 mt + l % 32, two 16-byte reads.  The swizzle is an XOR on the pair bits of the address,
+        // so step ks2 sits at (address of step 0) ^ 64 ks2; all reads of a tile are issued up front.
+        static_assert(D % 64 == 0, "the FP8 product consumes the head dimension 64 at a time");
+        constexpr int KS2 = D / 64;
+        u32x4 klo[KS2][2], khi[KS2][2];
+#pragma unroll
+        for (int ks2 = 0; ks2 < KS2; ks2++) {
+          klo[ks2][0] = lds_read16_untracked<0>(ka ^ (64u * ks2));
+          khi[ks2][0] = lds_read16_untracked<16>(ka ^ (64u * ks2));
+          klo[ks2][1] = lds_read16_untracked<32 * D>(ka ^ (64u * ks2));
+          khi[ks2][1] = lds_read16_untracked<32 * D + 16>(ka ^ (64u * ks2));
+        }
+#pragma unroll
+        for (int mt = 0; mt < 2; mt++)
+#pragma unroll
+          for (int e = 0; e < 16; e++) sacc[mt][e] = 0.f;
+#pragma unroll
+        for (int ks2 = 0; ks2 < KS2; ks2++)
+#pragma unroll
+          for (int mt = 0; mt < 2; mt++) {
+            wait_lgkmcnt(2 * (2 * (KS2 - 1 - ks2) + 1 - mt));
+            settle(klo[ks2][mt]);
+            settle(khi[ks2][mt]);
+            const u32x4 lo = klo[ks2][mt], hi = khi[ks2][mt];
+            const i32x8 a = {(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3], (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
+            i32x8 b;
+#pragma unroll
+            for (int x = 0; x < 4; x++) {
+              b[2 * x] = (int)(unsigned)((unsigned long)qf8[4 * ks2 + x]);
+              b[2 * x + 1] = (int)(unsigned)((unsigned long)qf8[4 * ks2 + x] >> 32);
+            }
+            sacc[mt] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, sacc[mt], 0, 0, 0, 0, 0, 0);   // e4m3 x e4m3, no scales
+          }
+      } else {
+        // the operand of (step ks, key half mt): 16 bytes of key row 32 mt + l % 32, step ks at (address of step 0) ^ 32 ks
+        constexpr int kItems = 2 * KS, kAhead = 3, kSlots = kAhead + 1;
+        u32x4 ring[kSlots];
+        auto issue = [&](int n) {
+          if (n % 2 == 0) ring[n % kSlots] = lds_read16_untracked<0>(ka ^ (32u * (n / 2)));
+          else ring[n % kSlots] = lds_read16_untracked<32 * D * 2>(ka ^ (32u * (n / 2)));
+        };
+#pragma unroll
+        for (int n = 0; n < kAhead; n++) issue(n);
+#pragma unroll
+        for (int mt = 0; mt < 2; mt++)
+#pragma unroll
+          for (int e = 0; e < 16; e++) sacc[mt][e] = 0.f;
+#pragma unroll
+        for (int n = 0; n < kItems; n++) {
+          if (n + kAhead < kItems) issue(n + kAhead);
+          wait_lgkmcnt(n + kAhead < kItems ? kAhead : kItems - 1 - n);
+          settle(ring[n % kSlots]);
+          sacc[n % 2] = mfma_bf16(__builtin_bit_cast(bf16x8, ring[n % kSlots]), qf[n / 2], sacc[n % 2]);
+        }
+      }
+    };
+    // Online softmax of this lane's query row over the 64 keys in sacc, in pieces.
+    float c1 = 1.f, mx = 0.f, m_new = 0.f, m_off = 0.f, corr = 1.f, rs = 0.f;
+    bool rescale = false;
+    bf16x8 pf[FP8V ? 1 : kSteps];                    // P^T fragments, token order
+    i32x8 pb, pb_new;                                // FP8V: the e4m3 codes of P^T, byte 16 mt + e of the lane's half
+    int codes = 0;
+    auto mask_tail = [&](int valid) {
+      if (valid < kTileTokens) {
+        const int g4 = 4 * (int)(lane_again() / 32);
+        asm volatile("" : "+s"(valid));              // none of the comparisons below is to be hoisted out of this rare branch
+#pragma unroll
+        for (int mt = 0; mt < 2; mt++)
+#pragma unroll
+          for (int e = 0; e < 16; e++) {
+            sacc[mt][e] = 32 * mt + 8 * (e / 4) + e % 4 < valid - g4 ? sacc[mt][e] : -INFINITY;
+            __builtin_amdgcn_sched_barrier(0);       // one comparison at a time: 32 at once take 64 scalar registers
+          }
+      }
+    };
+    // The reference of the exponentials.  With P rounded to a grid (low-bit modes) it is the running maximum,
+    // as Alg. 2 states it.  Otherwise any reference gives the same O / l, and the one in use is kept while the
+    // maximum of the row stays within 2^kLazy of it (the weights reach at most 2^kLazy, harmless in bf16 and fp32).
+    // O^T and l are rescaled when any row of the wave moves its reference.
+    constexpr float kLazy = FP8 ? 0.f : 8.f;
+    auto soft_max = [&](int mt) {
+      if (mt == 0) mx = -INFINITY;
+#pragma unroll
+      for (int e = 0; e < 16; e++) mx = fmaxf(mx, sacc[mt][e]);
+    };
+    auto soft_reference = [&]() {
+      mx = swap_halves_max(mx) * c1;
+      rescale = __builtin_amdgcn_ballot_w64(mx > m_run + kLazy) != 0;   // first tile: m_run = -inf
+      m_new = rescale ? fmaxf(m_run, mx) : m_run;    // finite: a tile holds at least one key
+      m_off = m_new - kPShift;
+      corr = fast_exp2(m_run - m_new);               // 0 on the first tile
+      rs = 0.f;
+    };
+    auto soft_pair = [&](int n) {                    // probabilities 2 n, 2 n + 1 of the lane
+      const int mt = n / 8, e = 2 * (n % 8);
+      const float p0 = fast_exp2(sacc[mt][e] * c1 - m_off);
+      const float p1 = fast_exp2(sacc[mt][e + 1] * c1 - m_off);
+      rs += p0 + p1;                                 // the denominator keeps the un-rounded P
+      settle(rs);                                    // (summed here: left for later, 32 addends stay in registers)
+      if constexpr (FP8V) {
+        const int q = 4 * mt + e / 4;                // two codes into the lower or upper half of dword q
+        if (e % 4 == 0) pb_new[q] = __builtin_amdgcn_cvt_pk_fp8_f32(p0, p1, 0, false);
+        else pb_new[q] = __builtin_amdgcn_cvt_pk_fp8_f32(p0, p1, pb_new[q], true);
+      } else if constexpr (FP8) {
+        // quant(P): e4m3 grid.  The instruction keeps the other half of its destination; feeding it the
+        // previous pair's register (dead by now) instead of a zero saves a register move per pair
+        codes = __builtin_amdgcn_cvt_pk_fp8_f32(p0, p1, codes, false);
+        typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+        const bf16x2 pq = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(codes, 1.0f, false);
+        pf[2 * mt + e / 8][e % 8] = pq[0];
+        pf[2 * mt + e / 8][e % 8 + 1] = pq[1];
+      } else {
+        pf[2 * mt + e / 8][e % 8] = (__bf16)p0;
+        pf[2 * mt + e / 8][e % 8 + 1] = (__bf16)p1;
+      }
+    };
+    // The weights are made where they stand: left to itself the compiler moves the conversions behind the products, to
+    // their first use in the next pass.
+    auto soft_keep = [&](int ks) {
+      if constexpr (FP8V) settle(pb_new);
+      else settle(pf[ks]);
+    };
+    auto soft_end = [&]() {
+      l_run = l_run * corr + swap_halves_sum(rs);
+      m_run = m_new;
+      if constexpr (FP8V) pb = pb_new;
+    };
+
+    int j1 = j_nxt;                                  // key block of tile s + 1
+    int j2 = ntiles > 0 ? tile_block(2) : 0;
+    float sk1 = 1.f;                                 // scale of tile s + 1
+    if constexpr (FP8) sk1 = k_scale[blk0 + j1];
+    // The last tile has a copy of the pass of its own, with Q^phi in the place of the softmax - in the low-bit modes; bf16
+    // operands, whose query fragments take 16 registers more, leave none for what the two copies would exchange.
+    auto pass = [&](int s, auto last_pass) {
+      constexpr bool LAST = decltype(last_pass)::value;
+      const int buf = s & 1;
+      const bool more = kPeel ? !LAST : s + 1 < ntiles;
+      if (s + 2 < ntiles) dma_k(j2, buf);
+      if (more) dma_v(j1, buf ^ 1);
+      if constexpr (LAST) dma_q(q_again(buf));
+      float zj[HS::kMtw];
+#pragma unroll
+      for (int a = 0; a < HS::kMtw; a++)
+        zj[a] = load_untracked_at(z_blocks + (blk0 + j_cur) * D + 32 * (mt0 + a), (lane16 >> 2) & 124u);
+      const int j3 = tile_block(s + 3);              // indices and scales are fetched a pass ahead of their use
+      float sk2 = 1.f, sv1 = 1.f;
+      if constexpr (FP8) sk2 = k_scale[blk0 + j2];
+      if constexpr (FP8V) sv1 = v_scale[blk0 + j1];
+      if constexpr (FP8V) {
+        // O^T is carried in units of the V scale of the tile being added
+        const float co = corr * (sv_prev / sv_cur);
+#pragma unroll
+        for (int et = 0; et < ET; et++)
+#pragma unroll
+          for (int e = 0; e < 16; e++) oacc[et][e] *= co;
+        sv_prev = sv_cur;
+        sv_cur = sv1;
+      } else if (rescale) {
+#pragma unroll
+        for (int et = 0; et < ET; et++)
+#pragma unroll
+          for (int e = 0; e < 16; e++) oacc[et][e] *= corr;
+      }
+      if (more) {
+        scores(buf ^ 1);
+        mask_tail(N - j1 * kTileTokens);
+      }
+      c1 = FP8 ? c0 * s_q * sk1 : c0;
+      // the K^phi fragments of this tile have landed
+      if constexpr (LAST) wait_vmcnt<kQOps + HS::kMtw>();
+      else if (!more) wait_vmcnt<HS::kMtw>();
+      else if (s + 2 < ntiles) wait_vmcnt<kKOps + kVOps + HS::kMtw>();
+      else wait_vmcnt<kVOps + HS::kMtw>();
+      // ---- O^T += V^T P^T and h += K^phi^T V of tile s; softmax of tile s + 1, or Q^phi ----
+      const unsigned va = vbuf(buf) + v_lane, pa = phi_lds + lane16;
+      constexpr int kFrags = kSteps * ET, kVAhead = 2;
+      // reads are counted as they are issued; everything here is a constant once the loops are unrolled
+      int issued = 0, v_at[kFrags], q_at = 0;
+      u32x2 vlo[kVAhead + 1], vhi[kVAhead + 1];
+      u32x4 ph[2][HS::kMtw];
+      auto read_v = [&](int f) {
+        vlo[f % (kVAhead + 1)] = lds_read_tr_untracked_at<16 * D>(va ^ (64u * (f % ET)), 2 * (f / ET));
+        vhi[f % (kVAhead + 1)] = lds_read_tr_untracked_at<16 * D>(va ^ (64u * (f % ET) ^ kHiXor), 2 * (f / ET) + 1);
+        v_at[f] = issued += 2;
+      };
+      auto read_phi = [&](int ks) {
+#pragma unroll
+        for (int a = 0; a < HS::kMtw; a++) ph[ks % 2][a] = lds_read16_untracked_at<1024>(pa + a * (kSteps * 1024), ks);
+        issued += HS::kMtw;
+      };
+      if constexpr (FP8V) {
+        // O^T += Vhat^T Ptilde^T as 64-deep FP8 products, one per 32-channel tile: the operand is the half
+        // row (l / 32) of channel row 32 et + l % 32 of the code tile, two 16-byte reads
+        typedef SwizzledLayoutVq<D> SLV;
+        const unsigned qa = vqbuf(buf) + SLV::offset(lane % 32, 2 * g);
+        u32x4 vq_lo[ET], vq_hi[ET];
+#pragma unroll
+        for (int et = 0; et < ET; et++) {
+          vq_lo[et] = lds_read16_untracked_at<32 * kTileTokens>(qa, et);
+          vq_hi[et] = lds_read16_untracked_at<32 * kTileTokens>(qa ^ 16u, et);
+        }
+#pragma unroll
+        for (int et = 0; et < ET; et++) {
+          wait_lgkmcnt(2 * (ET - 1 - et));
+          settle(vq_lo[et]);
+          settle(vq_hi[et]);
+          const u32x4 lo = vq_lo[et], hi = vq_hi[et];
+          const i32x8 a = {(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3], (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
+          oacc[et] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, pb, oacc[et], 0, 0, 0, 0, 0, 0);
+        }
+      }
+      constexpr int kQFrom = kFrags / 2;             // LAST: fragment from which on Q^phi is made of the query rows, back by then
+      u32x4 raw[KS];
+      read_phi(0);
+#pragma unroll
+      for (int f = 0; f < kVAhead; f++) read_v(f);
+      unrolled<kFrags>([&](auto frag) {
+        constexpr int f = decltype(frag)::value, ks = f / ET, et = f % ET;
+        if (LAST && f == kQFrom - 1) {
+          wait_vmcnt<HS::kMtw>();
+#pragma unroll
+          for (int x = 0; x < KS; x++) raw[x] = read_q(q_again(buf), g, 2 * x);
+          q_at = issued += KS;
+        }
+        // K^phi of the next step before the V fragment it meets first: the wait for that one covers both
+        static_assert(kVAhead == 2, "");
+        if (et == ET - 2 && ks + 1 < kSteps) read_phi(ks + 1);
+        if (f + kVAhead < kFrags) read_v(f + kVAhead);
+        wait_lgkmcnt(issued - v_at[f]);
+        settle(vlo[f % (kVAhead + 1)]);
+        settle(vhi[f % (kVAhead + 1)]);
+        if (et == 0) {
+#pragma unroll
+          for (int a = 0; a < HS::kMtw; a++) settle(ph[ks % 2][a]);
+          asm volatile("" ::: "memory");             // the fragments have left LDS: their successors may be requested
+          if constexpr (!LAST) {
+#pragma unroll
+            for (int a = 0; a < HS::kMtw; a++) dma_phi(j1, a, ks);   // (bf16, past the last tile: that one again, never read)
+          }
+        }
+        if (LAST && f == kQFrom) {
+          wait_lgkmcnt(issued - q_at);
+#pragma unroll
+          for (int x = 0; x < KS; x++) {
+            settle(raw[x]);
+            qf[x] = __builtin_bit_cast(bf16x8, raw[x]);
+          }
+        }
+        const u32x4 v4 = {vlo[f % (kVAhead + 1)][0], vlo[f % (kVAhead + 1)][1], vhi[f % (kVAhead + 1)][0], vhi[f % (kVAhead + 1)][1]};
+        const bf16x8 vf = __builtin_bit_cast(bf16x8, v4);
+        if constexpr (!FP8V) oacc[et] = mfma_bf16(vf, pf[ks], oacc[et]);
+#pragma unroll
+        for (int a = 0; a < HS::kMtw; a++) hacc[a][et] = mfma_bf16(__builtin_bit_cast(bf16x8, ph[ks % 2][a]), vf, hacc[a][et]);
+        if constexpr (LAST) {
+          if (f == kQFrom) q_max();
+          if (f > kQFrom) {
+#pragma unroll
+            for (int x = 2 * (f - kQFrom - 1); x < 2 * (f - kQFrom); x++)
+              if (x < KS) q_exp(x);
+          }
+        } else if (ks == 0) {
+          // softmax of the next tile: maximum and reference in step 0, then the probabilities of the step just done with
+          if (et == 0) soft_max(0);
+          if (et == (ET > 2 ? 1 : 0)) soft_max(1);
+          if (et == (ET > 2 ? 2 : 1)) soft_reference();
+        } else {
+#pragma unroll
+          for (int n = 4 / ET * et; n < 4 / ET * (et + 1); n++) soft_pair(4 * (ks - 1) + n);
+          if (et == ET - 1) soft_keep(ks - 1);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      if constexpr (LAST) {
+        wait_vmcnt<0>();                             // z_j
+      } else {
+#pragma unroll
+        for (int n = 0; n < 4; n++) soft_pair(4 * (kSteps - 1) + n);
+        soft_keep(kSteps - 1);
+        if (more) soft_end();
+        wait_vmcnt<kPhiOps>();                       // the next K and V tiles have landed (and z_j) ...
+      }
+#pragma unroll
+      for (int a = 0; a < HS::kMtw; a++) {
+        settle(zj[a]);
+        zsel[a] += zj[a];
+      }
+      phase_barrier();                               // ... for everyone, and this pass's tiles are free
+      j_cur = j1;
+      j1 = j2;
+      j2 = j3;
+      sk1 = sk2;
+    };
+    if (ntiles > 0) {
+      scores(0);
+      c1 = FP8 ? c0 * s_q * sk_cur : c0;             // dequantisation folded into the score scale
+      mask_tail(N - j_cur * kTileTokens);
+      soft_max(0);
+      soft_max(1);
+      soft_reference();
+#pragma unroll
+      for (int n = 0; n < 16; n++) soft_pair(n);
+      soft_end();
+      rescale = false;                               // O^T is zero
+      __builtin_amdgcn_s_waitcnt(kVmcnt0);           // V and K^phi of the first tile, K of the second have landed
+      phase_barrier();                               // everyone is done with the first K tile
+      for (int s = 0; s < ntiles - (kPeel ? 1 : 0); s++) pass(s, std::integral_constant<bool, false>());
+      if constexpr (kPeel) pass(ntiles - 1, std::integral_constant<bool, true>());
+      else __builtin_amdgcn_s_waitcnt(kVmcnt0);      // the last fragment requests: the epilogue reuses their place
     }
-    j_cur = j_nxt;
-    j_nxt = j_nn;
-    if constexpr (!DENSE) __builtin_amdgcn_s_setprio(0);   // softmax: the other wave's matrix products go first
-    // ---- online softmax of this lane's query row over the 64 keys ----
-    const float c1 = FP8 ? c0 * s_q * sk : c0;       // dequantisation folded into the score scale
-    if (valid < kTileTokens) {
+  } else {
+  for (int s = 0; s < ntiles; s++) {
+      const int buf = s & 1;
+      const int j = j_cur;
+      const int valid = min(kTileTokens, N - j * kTileTokens);
+      const float sk = sk_cur;
+      const int j_nn = tile_block(s + 2);                // consumed in the next iteration
+      if constexpr (FP8) sk_cur = k_scale[blk0 + j_nxt];
+      const float sv = sv_cur;
+      if constexpr (FP8V) sv_cur = v_scale[blk0 + j_nxt];
+      // K^phi fragments and z_j of this tile straight from global memory into registers (no other
+      // wave needs them); they are consumed after the softmax.  They are issued before the next
+      // tile's transfer and, since vmcnt retires in order, are complete once at most kDmaOps
+      // operations are outstanding.  The loads are opaque to the compiler on purpose: its own
+      // bookkeeping across the conditional transfer below falls back to vmcnt(0) at their first
+      // use, which stalls every iteration on the tile that was just requested.
+      bf16x8 kphi[DENSE ? 1 : HS::kMtw][kTileTokens / 16];
+      float zj[DENSE ? 1 : HS::kMtw];
+      auto state_loads = [&]() {
+        if constexpr (!DENSE) {
+#pragma unroll
+          for (int a = 0; a < HS::kMtw; a++) {
+#pragma unroll
+            for (int ks = 0; ks < kTileTokens / 16; ks++)
+              kphi[a][ks] = load_maybe_tracked<bf16x8, kManual>(k_phi + kphi_offset<D>(blk0 + j, mt0 + a, ks, lane));
+            zj[a] = load_maybe_tracked<float, kManual>(z_blocks + (blk0 + j) * D + 32 * (mt0 + a) + lane % 32);
+            if constexpr (!kManual) zsel[a] += zj[a];
+          }
+        }
+      };
+      auto next_tile = [&]() {
+        if (s + 1 < ntiles) dma(j_nxt, buf ^ 1);             // next tile -> other buffer
+      };
+      // With the reads under this kernel's own control (low-bit modes) the requests for the rest of the
+      // tile's data are placed inside the score product: the fragment loads behind its operand reads, the
+      // next tile's transfer behind its matrix instructions - some hundred instructions that otherwise
+      // stand in front of it, on a wave whose progress is bound by its own chain of dependent steps.
+      constexpr bool kRequestsInsideScores = kManual;
+      if constexpr (!kRequestsInsideScores) {
+        state_loads();
+        next_tile();
+      }
+      const uint16_t* vt = reinterpret_cast<const uint16_t*>(smem + SM::kVOff + buf * SM::kVBytes);
+      // Two waves share a SIMD.  The one that is issuing matrix products is given the higher issue priority, so
+      // that the matrix pipe is fed while the other wave's softmax fills the gaps (measured: 2 % on the
+      // sparse modes; the dense comparator, all of whose waves are in step, loses with it).
+      if constexpr (!DENSE) __builtin_amdgcn_s_setprio(2);
+      // ---- S^T = K Q^T (keys x query rows), two 32-key halves ----
+      f32x16 sacc[2];
 #pragma unroll
       for (int mt = 0; mt < 2; mt++)
 #pragma unroll
-        for (int e = 0; e < 16; e++)
-          if (32 * mt + 8 * (e / 4) + 4 * g + e % 4 >= valid) sacc[mt][e] = -INFINITY;
-    }
-    float mx = -INFINITY;
+        for (int e = 0; e < 16; e++) sacc[mt][e] = 0.f;
+      if constexpr (INT8) {
+        // 32-deep integer products (v_mfma_i32_32x32x32_i8: lane l holds row l % 32, contraction indices
+        // 16 (l / 32) + 0..15): the operand of (step ks4, key half mt) is 16 consecutive codes of key row
+        // 32 mt + l % 32 - one 16-byte read at (address of step 0) ^ 32 ks4 in the pair-swizzled tile.
+        // Sums of 128 products of codes stay below 2^21: exact in the int32 accumulator and in fp32.
+        constexpr int KS4 = D / 32;
+        const unsigned ka = kbuf(buf) + SL8::offset(lane % 32, 16 * g);
+        u32x4 kq[KS4][2];
 #pragma unroll
-    for (int mt = 0; mt < 2; mt++)
-#pragma unroll
-      for (int e = 0; e < 16; e++) mx = fmaxf(mx, sacc[mt][e]);
-    mx = half_max(mx) * c1;
-    // The reference of the exponentials.  With P rounded to a grid (low-bit modes) it is the running maximum,
-    // as Alg. 2 states it.  Otherwise any reference gives the same O / l, and the one in use is kept while the
-    // maximum of the row stays within 2^kLazy of it: O^T, l then need no rescaling in most tiles (the weights
-    // reach at most 2^kLazy, harmless in bf16 and fp32).  The decision is taken for the whole wave.
-    constexpr float kLazy = 8.f;
-    bool rescale = true;
-    if constexpr (!FP8) rescale = __builtin_amdgcn_ballot_w64(mx > m_run + kLazy) != 0;   // first tile: m_run = -inf
-    const float m_new = rescale ? fmaxf(m_run, mx) : m_run;   // finite: a tile holds at least one key
-    const float m_off = m_new - kPShift;
-    float rs = 0.f;
-    bf16x8 pf[FP8V ? 1 : 4];                         // P^T fragments, token order
-    i32x8 pb;                                        // FP8V: the e4m3 codes of P^T, byte 16 mt + e of the lane's half
-    int codes = 0;
-#pragma unroll
-    for (int mt = 0; mt < 2; mt++)
-#pragma unroll
-      for (int e = 0; e < 16; e += 2) {
-        const float p0 = fast_exp2(sacc[mt][e] * c1 - m_off);
-        const float p1 = fast_exp2(sacc[mt][e + 1] * c1 - m_off);
-        rs += p0 + p1;                               // the denominator keeps the un-rounded P
-        if constexpr (FP8V) {
-          const int q = 4 * mt + e / 4;              // two codes into the lower or upper half of dword q
-          if (e % 4 == 0) pb[q] = __builtin_amdgcn_cvt_pk_fp8_f32(p0, p1, 0, false);
-          else pb[q] = __builtin_amdgcn_cvt_pk_fp8_f32(p0, p1, pb[q], true);
-        } else if constexpr (FP8) {
-          // quant(P): e4m3 grid.  The instruction keeps the other half of its destination; feeding it the
-          // previous pair's register (dead by now) instead of a zero saves a register move per pair
-          codes = __builtin_amdgcn_cvt_pk_fp8_f32(p0, p1, codes, false);
-          typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
-          const bf16x2 pq = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(codes, 1.0f, false);
-          pf[2 * mt + e / 8][e % 8] = pq[0];
-          pf[2 * mt + e / 8][e % 8 + 1] = pq[1];
-        } else {
-          pf[2 * mt + e / 8][e % 8] = (__bf16)p0;
-          pf[2 * mt + e / 8][e % 8 + 1] = (__bf16)p1;
+        for (int ks4 = 0; ks4 < KS4; ks4++) {
+          kq[ks4][0] = lds_read16_untracked<0>(ka ^ (32u * ks4));
+          kq[ks4][1] = lds_read16_untracked<32 * D>(ka ^ (32u * ks4));
         }
-      }
-    rs = half_sum(rs);
-    if (rescale) {
-      const float corr = fast_exp2(m_run - m_new);   // 0 on the first tile
-      l_run *= corr;
-      m_run = m_new;
-      const float corr_o = FP8V ? corr * (sv_prev / sv) : corr;   // FP8V: also from the last tile's V scale to this one's
-      sv_prev = sv;
+        if constexpr (kRequestsInsideScores) state_loads();
+        i32x16 iacc[2];
 #pragma unroll
-      for (int et = 0; et < ET; et++)
+        for (int mt = 0; mt < 2; mt++)
 #pragma unroll
-        for (int e = 0; e < 16; e++) oacc[et][e] *= corr_o;
-    }
-    l_run += rs;
-
-    if constexpr (!DENSE) __builtin_amdgcn_s_setprio(2);   // matrix products again
-    if constexpr (!DENSE) {
-      if constexpr (kManual) {
-        // the register loads issued at the top have landed; the tile transfer may still be in flight
-        if (s + 1 < ntiles) wait_vmcnt<kDmaOps>();
-        else wait_vmcnt<0>();
+          for (int e = 0; e < 16; e++) iacc[mt][e] = 0;
 #pragma unroll
-        for (int a = 0; a < HS::kMtw; a++) {
+        for (int ks4 = 0; ks4 < KS4; ks4++)
 #pragma unroll
-          for (int ks = 0; ks < kTileTokens / 16; ks++) settle(kphi[a][ks]);
-          settle(zj[a]);
-        }
-#pragma unroll
-        for (int a = 0; a < HS::kMtw; a++) zsel[a] += zj[a];
-      }
-    }
-    if constexpr (FP8V) {
-      // O^T += Vhat^T Ptilde^T as 64-deep FP8 products, one per 32-channel tile: the operand is the half
-      // row (l / 32) of channel row 32 et + l % 32 of the code tile, two 16-byte reads
-      typedef SwizzledLayoutVq<D> SLV;
-      const unsigned qa = lds_address(vqbuf(buf) + SLV::offset(lane % 32, 2 * g));
-      u32x4 vq_lo[ET], vq_hi[ET];
-#pragma unroll
-      for (int et = 0; et < ET; et++) {
-        vq_lo[et] = lds_read16_untracked_at<32 * kTileTokens>(qa, et);
-        vq_hi[et] = lds_read16_untracked_at<32 * kTileTokens>(qa ^ 16u, et);
-      }
-#pragma unroll
-      for (int et = 0; et < ET; et++) {
-        wait_lgkmcnt(2 * (ET - 1 - et));
-        settle(vq_lo[et]);
-        settle(vq_hi[et]);
-        const u32x4 lo = vq_lo[et], hi = vq_hi[et];
-        const i32x8 a = {(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3], (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
-        oacc[et] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, pb, oacc[et], 0, 0, 0, 0, 0, 0);
-      }
-    }
-    // ---- O^T += V^T P^T, and the d x d state of this block: h += K^phi^T V ----
-    // address of this lane's first transposing read of fragment (ks = 0, et = 0), cf. read_tr4
-    const unsigned va = lds_address(vt + SL::offset(4 * g + (lane % 16) / 4, 16 * ((lane / 16) % 2) + 4 * (lane % 4)));
-    unsigned vaddr[ET];                              // one address per 32-channel tile; the token step is an immediate
-#pragma unroll
-    for (int et = 0; et < ET; et++) vaddr[et] = va ^ (64u * et);
-    u32x2 vlo[3], vhi[3];
-#pragma unroll
-    for (int ks = 0; ks < kTileTokens / 16; ks++) {
-      if constexpr (!kManual && (HS::kNtw == ET || DENSE)) {   // every V fragment feeds both products
-#pragma unroll
-        for (int et = 0; et < ET; et++) {
-          bf16x8 vf = v_fragment<SL>(vt, ks, 32 * et, lane);
-          if constexpr (!FP8V) oacc[et] = mfma_bf16(vf, pf[ks], oacc[et]);
-          if constexpr (!DENSE) {
-#pragma unroll
-            for (int a = 0; a < HS::kMtw; a++) hacc[a][et] = mfma_bf16(kphi[a][ks], vf, hacc[a][et]);
+          for (int mt = 0; mt < 2; mt++) {
+            wait_lgkmcnt(2 * (KS4 - 1 - ks4) + 1 - mt);
+            settle(kq[ks4][mt]);
+            const u32x4 kk = kq[ks4][mt];
+            const i32x4 a = {(int)kk[0], (int)kk[1], (int)kk[2], (int)kk[3]};
+            const i32x4 b = {(int)(unsigned)((unsigned long)qf8[2 * ks4]), (int)(unsigned)((unsigned long)qf8[2 * ks4] >> 32),
+                             (int)(unsigned)((unsigned long)qf8[2 * ks4 + 1]), (int)(unsigned)((unsigned long)qf8[2 * ks4 + 1] >> 32)};
+            iacc[mt] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, iacc[mt], 0, 0, 0);
           }
-        }
-      } else if constexpr (HS::kNtw == ET || DENSE) {       // the same with the reads kept in flight
-        // fragment f = ks ET + et: two transposing reads (tokens 16 ks + 4 g.. and + 8), kept kVAhead
-        // fragments ahead of the products.  Row swizzle and lane terms are the same for every
-        // fragment of a lane, so fragment (ks, et) sits at (va ^ 64 et) + 32 D ks.
-        constexpr int kVAhead = FP8 ? 2 : 1, kFrags = (kTileTokens / 16) * ET;
-        if (ks == 0) {
+        if constexpr (kRequestsInsideScores) next_tile();
 #pragma unroll
-          for (int f = 0; f < kVAhead; f++) {
-            vlo[f] = lds_read_tr_untracked_at<8 * D * 2>(vaddr[f % ET], 2 * (f / ET));
-            vhi[f] = lds_read_tr_untracked_at<8 * D * 2>(vaddr[f % ET], 2 * (f / ET) + 1);
-          }
-        }
+        for (int mt = 0; mt < 2; mt++)
 #pragma unroll
-        for (int et = 0; et < ET; et++) {
-          const int f = ks * ET + et;
-          if (f + kVAhead < kFrags) {
-            const int f2 = f + kVAhead;
-            vlo[f2 % (kVAhead + 1)] = lds_read_tr_untracked_at<8 * D * 2>(vaddr[f2 % ET], 2 * (f2 / ET));
-            vhi[f2 % (kVAhead + 1)] = lds_read_tr_untracked_at<8 * D * 2>(vaddr[f2 % ET], 2 * (f2 / ET) + 1);
-          }
-          const int left = kFrags - 1 - f;
-          wait_lgkmcnt(2 * (left < kVAhead ? left : kVAhead));
-          u32x2& lo = vlo[f % (kVAhead + 1)];
-          u32x2& hi = vhi[f % (kVAhead + 1)];
-          settle(lo);
-          settle(hi);
-          const u32x4 v4 = {lo[0], lo[1], hi[0], hi[1]};
-          const bf16x8 vf = __builtin_bit_cast(bf16x8, v4);
-          if constexpr (!FP8V) oacc[et] = mfma_bf16(vf, pf[ks], oacc[et]);
-          if constexpr (!DENSE) {
+          for (int e = 0; e < 16; e++) sacc[mt][e] = (float)iacc[mt][e];
+      } else if constexpr (FP8) {
+        // 64-deep products: the operand of (step ks2, key half mt) is 32 consecutive codes of key row
+        // 32 mt + l % 32, two 16-byte reads.  The swizzle is an XOR on the pair bits of the address,
+        // so step ks2 sits at (address of step 0) ^ 64 ks2; all reads of a tile are issued up front.
+        static_assert(D % 64 == 0, "the FP8 product consumes the head dimension 64 at a time");
+        constexpr int KS2 = D / 64;
+        const unsigned ka = kbuf(buf) + SL8::offset(lane % 32, 32 * g);
+        u32x4 klo[KS2][2], khi[KS2][2];
 #pragma unroll
-            for (int a = 0; a < HS::kMtw; a++) hacc[a][et] = mfma_bf16(kphi[a][ks], vf, hacc[a][et]);
-          }
+        for (int ks2 = 0; ks2 < KS2; ks2++) {
+          klo[ks2][0] = lds_read16_untracked<0>(ka ^ (64u * ks2));
+          khi[ks2][0] = lds_read16_untracked<16>(ka ^ (64u * ks2));
+          klo[ks2][1] = lds_read16_untracked<32 * D>(ka ^ (64u * ks2));
+          khi[ks2][1] = lds_read16_untracked<32 * D + 16>(ka ^ (64u * ks2));
         }
+        if constexpr (kRequestsInsideScores) state_loads();
+#pragma unroll
+        for (int ks2 = 0; ks2 < KS2; ks2++)
+#pragma unroll
+          for (int mt = 0; mt < 2; mt++) {
+            wait_lgkmcnt(2 * (2 * (KS2 - 1 - ks2) + 1 - mt));
+            settle(klo[ks2][mt]);
+            settle(khi[ks2][mt]);
+            const u32x4 lo = klo[ks2][mt], hi = khi[ks2][mt];
+            const i32x8 a = {(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3], (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
+            i32x8 b;
+#pragma unroll
+            for (int x = 0; x < 4; x++) {
+              b[2 * x] = (int)(unsigned)((unsigned long)qf8[4 * ks2 + x]);
+              b[2 * x + 1] = (int)(unsigned)((unsigned long)qf8[4 * ks2 + x] >> 32);
+            }
+            sacc[mt] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, sacc[mt], 0, 0, 0, 0, 0, 0);   // e4m3 x e4m3, no scales
+          }
+        if constexpr (kRequestsInsideScores) next_tile();
       } else {
+        const uint16_t* kt = reinterpret_cast<const uint16_t*>(smem + SM::kKOff + buf * SM::kKBytes);
 #pragma unroll
-        for (int et = 0; et < ET; et++) {
-          bf16x8 vf = v_fragment<SL>(vt, ks, 32 * et, lane);
-          if constexpr (!FP8V) oacc[et] = mfma_bf16(vf, pf[ks], oacc[et]);
+        for (int ks = 0; ks < KS; ks++)
+#pragma unroll
+          for (int mt = 0; mt < 2; mt++)
+            sacc[mt] = mfma_bf16(row_fragment<SL>(kt, 32 * mt + lane % 32, 16 * ks + 8 * g), qf[ks], sacc[mt]);
+      }
+      j_cur = j_nxt;
+      j_nxt = j_nn;
+      if constexpr (!DENSE) __builtin_amdgcn_s_setprio(0);   // softmax: the other wave's matrix products go first
+      // ---- online softmax of this lane's query row over the 64 keys ----
+      const float c1 = FP8 ? c0 * s_q * sk : c0;       // dequantisation folded into the score scale
+      if (valid < kTileTokens) {
+#pragma unroll
+        for (int mt = 0; mt < 2; mt++)
+#pragma unroll
+          for (int e = 0; e < 16; e++)
+            if (32 * mt + 8 * (e / 4) + 4 * g + e % 4 >= valid) sacc[mt][e] = -INFINITY;
+      }
+      float mx = -INFINITY;
+#pragma unroll
+      for (int mt = 0; mt < 2; mt++)
+#pragma unroll
+        for (int e = 0; e < 16; e++) mx = fmaxf(mx, sacc[mt][e]);
+      mx = half_max(mx) * c1;
+      // The reference of the exponentials.  With P rounded to a grid (low-bit modes) it is the running maximum,
+      // as Alg. 2 states it.  Otherwise any reference gives the same O / l, and the one in use is kept while the
+      // maximum of the row stays within 2^kLazy of it: O^T, l then need no rescaling in most tiles (the weights
+      // reach at most 2^kLazy, harmless in bf16 and fp32).  The decision is taken for the whole wave.
+      constexpr float kLazy = 8.f;
+      bool rescale = true;
+      if constexpr (!FP8) rescale = __builtin_amdgcn_ballot_w64(mx > m_run + kLazy) != 0;   // first tile: m_run = -inf
+      const float m_new = rescale ? fmaxf(m_run, mx) : m_run;   // finite: a tile holds at least one key
+      const float m_off = m_new - kPShift;
+      float rs = 0.f;
+      bf16x8 pf[FP8V ? 1 : 4];                         // P^T fragments, token order
+      i32x8 pb;                                        // FP8V: the e4m3 codes of P^T, byte 16 mt + e of the lane's half
+      int codes = 0;
+#pragma unroll
+      for (int mt = 0; mt < 2; mt++)
+#pragma unroll
+        for (int e = 0; e < 16; e += 2) {
+          const float p0 = fast_exp2(sacc[mt][e] * c1 - m_off);
+          const float p1 = fast_exp2(sacc[mt][e + 1] * c1 - m_off);
+          rs += p0 + p1;                               // the denominator keeps the un-rounded P
+          if constexpr (FP8V) {
+            const int q = 4 * mt + e / 4;              // two codes into the lower or upper half of dword q
+            if (e % 4 == 0) pb[q] = __builtin_amdgcn_cvt_pk_fp8_f32(p0, p1, 0, false);
+            else pb[q] = __builtin_amdgcn_cvt_pk_fp8_f32(p0, p1, pb[q], true);
+          } else if constexpr (FP8) {
+            // quant(P): e4m3 grid.  The instruction keeps the other half of its destination; feeding it the
+            // previous pair's register (dead by now) instead of a zero saves a register move per pair
+            codes = __builtin_amdgcn_cvt_pk_fp8_f32(p0, p1, codes, false);
+            typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+            const bf16x2 pq = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(codes, 1.0f, false);
+            pf[2 * mt + e / 8][e % 8] = pq[0];
+            pf[2 * mt + e / 8][e % 8 + 1] = pq[1];
+          } else {
+            pf[2 * mt + e / 8][e % 8] = (__bf16)p0;
+            pf[2 * mt + e / 8][e % 8 + 1] = (__bf16)p1;
+          }
         }
+      rs = half_sum(rs);
+      if (rescale) {
+        const float corr = fast_exp2(m_run - m_new);   // 0 on the first tile
+        l_run *= corr;
+        m_run = m_new;
+        const float corr_o = FP8V ? corr * (sv_prev / sv) : corr;   // FP8V: also from the last tile's V scale to this one's
+        sv_prev = sv;
 #pragma unroll
-        for (int b = 0; b < HS::kNtw; b++) {
-          bf16x8 vf = v_fragment<SL>(vt, ks, 32 * (nt0 + b), lane);
+        for (int et = 0; et < ET; et++)
 #pragma unroll
-          for (int a = 0; a < HS::kMtw; a++) hacc[a][b] = mfma_bf16(kphi[a][ks], vf, hacc[a][b]);
+          for (int e = 0; e < 16; e++) oacc[et][e] *= corr_o;
+      }
+      l_run += rs;
+
+      if constexpr (!DENSE) __builtin_amdgcn_s_setprio(2);   // matrix products again
+      if constexpr (!DENSE) {
+        if constexpr (kManual) {
+          // the register loads issued at the top have landed; the tile transfer may still be in flight
+          if (s + 1 < ntiles) wait_vmcnt<kDmaOps>();
+          else wait_vmcnt<0>();
+#pragma unroll
+          for (int a = 0; a < HS::kMtw; a++) {
+#pragma unroll
+            for (int ks = 0; ks < kTileTokens / 16; ks++) settle(kphi[a][ks]);
+            settle(zj[a]);
+          }
+#pragma unroll
+          for (int a = 0; a < HS::kMtw; a++) zsel[a] += zj[a];
         }
       }
+      if constexpr (FP8V) {
+        // O^T += Vhat^T Ptilde^T as 64-deep FP8 products, one per 32-channel tile: the operand is the half
+        // row (l / 32) of channel row 32 et + l % 32 of the code tile, two 16-byte reads
+        typedef SwizzledLayoutVq<D> SLV;
+        const unsigned qa = vqbuf(buf) + SLV::offset(lane % 32, 2 * g);
+        u32x4 vq_lo[ET], vq_hi[ET];
+#pragma unroll
+        for (int et = 0; et < ET; et++) {
+          vq_lo[et] = lds_read16_untracked_at<32 * kTileTokens>(qa, et);
+          vq_hi[et] = lds_read16_untracked_at<32 * kTileTokens>(qa ^ 16u, et);
+        }
+#pragma unroll
+        for (int et = 0; et < ET; et++) {
+          wait_lgkmcnt(2 * (ET - 1 - et));
+          settle(vq_lo[et]);
+          settle(vq_hi[et]);
+          const u32x4 lo = vq_lo[et], hi = vq_hi[et];
+          const i32x8 a = {(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3], (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
+          oacc[et] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, pb, oacc[et], 0, 0, 0, 0, 0, 0);
+        }
+      }
+      // ---- O^T += V^T P^T, and the d x d state of this block: h += K^phi^T V ----
+      // address of this lane's first transposing read of fragment (ks = 0, et = 0), cf. read_tr4
+      const unsigned va = lds_address(vt + SL::offset(4 * g + (lane % 16) / 4, 16 * ((lane / 16) % 2) + 4 * (lane % 4)));
+      unsigned vaddr[ET];                              // one address per 32-channel tile; the token step is an immediate
+#pragma unroll
+      for (int et = 0; et < ET; et++) vaddr[et] = va ^ (64u * et);
+      u32x2 vlo[3], vhi[3];
+#pragma unroll
+      for (int ks = 0; ks < kTileTokens / 16; ks++) {
+        if constexpr (!kManual && (HS::kNtw == ET || DENSE)) {   // every V fragment feeds both products
+#pragma unroll
+          for (int et = 0; et < ET; et++) {
+            bf16x8 vf = v_fragment<SL>(vt, ks, 32 * et, lane);
+            if constexpr (!FP8V) oacc[et] = mfma_bf16(vf, pf[ks], oacc[et]);
+            if constexpr (!DENSE) {
+#pragma unroll
+              for (int a = 0; a < HS::kMtw; a++) hacc[a][et] = mfma_bf16(kphi[a][ks], vf, hacc[a][et]);
+            }
+          }
+        } else if constexpr (HS::kNtw == ET || DENSE) {       // the same with the reads kept in flight
+          // fragment f = ks ET + et: two transposing reads (tokens 16 ks + 4 g.. and + 8), kept kVAhead
+          // fragments ahead of the products.  Row swizzle and lane terms are the same for every
+          // fragment of a lane, so fragment (ks, et) sits at (va ^ 64 et) + 32 D ks.
+          constexpr int kVAhead = FP8 ? 2 : 1, kFrags = (kTileTokens / 16) * ET;
+          if (ks == 0) {
+#pragma unroll
+            for (int f = 0; f < kVAhead; f++) {
+              vlo[f] = lds_read_tr_untracked_at<8 * D * 2>(vaddr[f % ET], 2 * (f / ET));
+              vhi[f] = lds_read_tr_untracked_at<8 * D * 2>(vaddr[f % ET], 2 * (f / ET) + 1);
+            }
+          }
+#pragma unroll
+          for (int et = 0; et < ET; et++) {
+            const int f = ks * ET + et;
+            if (f + kVAhead < kFrags) {
+              const int f2 = f + kVAhead;
+              vlo[f2 % (kVAhead + 1)] = lds_read_tr_untracked_at<8 * D * 2>(vaddr[f2 % ET], 2 * (f2 / ET));
+              vhi[f2 % (kVAhead + 1)] = lds_read_tr_untracked_at<8 * D * 2>(vaddr[f2 % ET], 2 * (f2 / ET) + 1);
+            }
+            const int left = kFrags - 1 - f;
+            wait_lgkmcnt(2 * (left < kVAhead ? left : kVAhead));
+            u32x2& lo = vlo[f % (kVAhead + 1)];
+            u32x2& hi = vhi[f % (kVAhead + 1)];
+            settle(lo);
+            settle(hi);
+            const u32x4 v4 = {lo[0], lo[1], hi[0], hi[1]};
+            const bf16x8 vf = __builtin_bit_cast(bf16x8, v4);
+            if constexpr (!FP8V) oacc[et] = mfma_bf16(vf, pf[ks], oacc[et]);
+            if constexpr (!DENSE) {
+#pragma unroll
+              for (int a = 0; a < HS::kMtw; a++) hacc[a][et] = mfma_bf16(kphi[a][ks], vf, hacc[a][et]);
+            }
+          }
+        } else {
+#pragma unroll
+          for (int et = 0; et < ET; et++) {
+            bf16x8 vf = v_fragment<SL>(vt, ks, 32 * et, lane);
+            if constexpr (!FP8V) oacc[et] = mfma_bf16(vf, pf[ks], oacc[et]);
+          }
+#pragma unroll
+          for (int b = 0; b < HS::kNtw; b++) {
+            bf16x8 vf = v_fragment<SL>(vt, ks, 32 * (nt0 + b), lane);
+#pragma unroll
+            for (int a = 0; a < HS::kMtw; a++) hacc[a][b] = mfma_bf16(kphi[a][ks], vf, hacc[a][b]);
+          }
+        }
+      }
+      __builtin_amdgcn_s_waitcnt(kVmcnt0);             // the next tile has landed in LDS ...
+      __syncthreads();                                 // ... for everyone, and this tile's buffer is free
     }
-    __builtin_amdgcn_s_waitcnt(kVmcnt0);             // the next tile has landed in LDS ...
-    __syncthreads();                                 // ... for everyone, and this tile's buffer is free
   }
 
   if constexpr (!DENSE) __builtin_amdgcn_s_setprio(0);
   // ================= epilogue =================
   const float inv_l = l_run > 0.f ? 1.f / l_run : 0.f;
   const int qrow = 32 * w + lane % 32;               // this lane's query row inside the block
-  if (lse != nullptr || lse_save != nullptr) {
-    // Alg. 2 defines L on the smoothed keys.  The bf16 products above use the raw K, whose scores
-    // are larger by q . colmean(K) / sqrt(d) in every column of a row (the softmax cancels it);
-    // the FP8 codes are those of the smoothed K already.
-    float qmu = 0.f;
-    if (!DENSE && !FP8) {
+  if (!DENSE && (!PIPE || !FP8 || ntiles == 0)) {
+    if constexpr (FP8) {
+      dma_q(q_again(0));
+      wait_vmcnt<0>();
+      u32x4 raw[KS];
 #pragma unroll
-      for (int ks = 0; ks < KS; ks++)
+      for (int ks = 0; ks < KS; ks++) raw[ks] = read_q(q_again(0), g, 2 * ks);
+      wait_lgkmcnt(0);
 #pragma unroll
-        for (int e = 0; e < 8; e++) qmu += (float)qf[ks][e] * (float)k_mean[(size_t)bh * D + 16 * ks + 8 * g + e];
-      qmu = half_sum(qmu);
+      for (int ks = 0; ks < KS; ks++) {
+        settle(raw[ks]);
+        qf[ks] = __builtin_bit_cast(bf16x8, raw[ks]);
+      }
     }
-    if (g == 0 && qrow < rows_valid) {
-      const float L =
-          l_run > 0.f ? (m_run - kPShift + __log2f(l_run)) * 0.6931471805599453f - qmu * rsqrtf((float)D) : -INFINITY;
-      if (lse != nullptr) lse[(size_t)bh * N + row0 + qrow] = L;
-      if (lse_save != nullptr) lse_save[(size_t)bh * N + row0 + qrow] = L;
-    }
-  }
-
-  if constexpr (FP8) {
-    // the bf16 Q fragments were dropped after quantisation to keep two waves per SIMD; the linear
-    // branch needs them once more
-    const int r = min(32 * w + lane % 32, rows_valid - 1);
-    const uint16_t* src = qh + (size_t)(row0 + r) * tok_stride + 8 * g;
+    q_max();
 #pragma unroll
-    for (int ks = 0; ks < KS; ks++) qf[ks] = *reinterpret_cast<const bf16x8*>(src + 16 * ks);
+    for (int ks = 0; ks < KS; ks++) q_exp(ks);
+    __syncthreads();                                 // the rows have left LDS
   }
   uint16_t* ht = reinterpret_cast<uint16_t*>(smem);  // H_i^T as bf16 [e][c], row stride LD
   uint16_t* os = ht + D * LD;                        // output tile [BQ][LD]
+  uint16_t* zs = reinterpret_cast<uint16_t*>(smem + SM::kZsOff);   // Z_i: three bf16 rows whose sum it is
   f32x16 lacc[ET];
   float inv_den = 0.f;
   if constexpr (!DENSE) {
@@ -853,50 +1325,39 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
         }
       }
       // zsel holds the same sum on both lane halves (each half added z_j of channel l % 32)
-      if (g == 0 && nt0 == 0) zs[32 * (mt0 + a) + lane] = -zsel[a];
-    }
-    // Q^phi = softmax_d(Q) of this lane's row, kept as fragments - without its normaliser, which cancels
-    // between Q^phi H_i and Q^phi Z_i
-    float qx[KS][8];
-    float qm = -INFINITY;
+      if (g == 0 && nt0 == 0) {
+        const int c = 32 * (mt0 + a) + lane;
+        float z = -zsel[a];
+        if (z_save != nullptr) z_save[((size_t)bh * Tm + i) * D + c] = z;
 #pragma unroll
-    for (int ks = 0; ks < KS; ks++)
-#pragma unroll
-      for (int e = 0; e < 8; e++) {
-        qx[ks][e] = (float)qf[ks][e];
-        qm = fmaxf(qm, qx[ks][e]);
+        for (int r = 0; r < 3; r++) {
+          const __bf16 part = (__bf16)z;
+          *reinterpret_cast<__bf16*>(zs + r * LD + c) = part;
+          z -= (float)part;
+        }
       }
-    qm = half_max(qm);
-#pragma unroll
-    for (int ks = 0; ks < KS; ks++)
-#pragma unroll
-      for (int e = 0; e < 8; e++) qx[ks][e] = fast_exp2((qx[ks][e] - qm) * kLog2e);
+    }
     __syncthreads();                                 // H_i^T and Z_i visible
-    float den = 0.f;
+    // O_l^T = H_i^T Q^phi^T, and Q^phi Z_i as one product more (rows 0, 1, 2 of its result; the other rows repeat row 2).
+    // The accumulators take turns, so that no product waits for the one before it.
+    f32x16 dacc;
 #pragma unroll
-    for (int ks = 0; ks < KS; ks++) {
-      const f32x4 z0 = *reinterpret_cast<const f32x4*>(zs + 16 * ks + 8 * g);
-      const f32x4 z1 = *reinterpret_cast<const f32x4*>(zs + 16 * ks + 8 * g + 4);
-#pragma unroll
-      for (int e = 0; e < 8; e++) {
-        den += qx[ks][e] * (e < 4 ? z0[e] : z1[e - 4]);
-        qf[ks][e] = (__bf16)qx[ks][e];
-      }
-    }
-    den = half_sum(den);
-    inv_den = ksel >= Tn ? 0.f : 1.f / den;          // every block selected: nothing left for the linear branch
-    // O_l^T = H_i^T Q^phi^T (the four accumulators take turns, so that no product waits for the one before it)
+    for (int e = 0; e < 16; e++) dacc[e] = 0.f;
 #pragma unroll
     for (int et = 0; et < ET; et++)
 #pragma unroll
       for (int e = 0; e < 16; e++) lacc[et][e] = 0.f;
+    const uint16_t* zrow = zs + min(lane % 32, 2) * LD + 8 * g;
+    const uint16_t* hrow = ht + (lane % 32) * LD + 8 * g;
 #pragma unroll
-    for (int ks = 0; ks < KS; ks++)
+    for (int ks = 0; ks < KS; ks++) {
+      dacc = mfma_bf16(*reinterpret_cast<const bf16x8*>(zrow + 16 * ks), qf[ks], dacc);
 #pragma unroll
-      for (int et = 0; et < ET; et++) {
-        bf16x8 a = *reinterpret_cast<const bf16x8*>(ht + (32 * et + lane % 32) * LD + 16 * ks + 8 * g);
-        lacc[et] = mfma_bf16(a, qf[ks], lacc[et]);
-      }
+      for (int et = 0; et < ET; et++)
+        lacc[et] = mfma_bf16(*reinterpret_cast<const bf16x8*>(hrow + 32 * et * LD + 16 * ks), qf[ks], lacc[et]);
+    }
+    const float den = low_half((dacc[0] + dacc[1]) + dacc[2]);
+    inv_den = ksel >= Tn ? 0.f : 1.f / den;          // every block selected: nothing left for the linear branch
   }
   // ---- mix (Eq. 13), transpose through LDS, coalesced store ----
   const float al = DENSE ? 1.f : alpha[alpha_per_block ? (size_t)h * Tm + i : (size_t)h];
@@ -914,10 +1375,11 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
       }
       *reinterpret_cast<bf16x4*>(os + qrow * LD + 32 * et + 8 * v4 + 4 * g) = pk;
     }
-  __syncthreads();
+  // (a wave stores the 32 rows that it wrote itself: no barrier)
   uint16_t* oh = out + head_offset(sout, bh, H) + (size_t)row0 * sout.n;
-  for (int idx = tid; idx < BQ * (D / 8); idx += NT) {
-    const int r = idx / (D / 8), ch = idx % (D / 8);
+#pragma unroll
+  for (int x = 0; x < D / 16; x++) {
+    const int r = 32 * w + (x * kWave + lane) / (D / 8), ch = lane % (D / 8);
     if (r < rows_valid) *reinterpret_cast<u32x4*>(oh + (size_t)r * sout.n + 8 * ch) = *reinterpret_cast<const u32x4*>(os + r * LD + 8 * ch);
   }
   if constexpr (!DENSE) {
@@ -928,14 +1390,12 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
         const int e = idx / (D / 8), ch = idx % (D / 8);
         *reinterpret_cast<u32x4*>(dst + e * D + 8 * ch) = *reinterpret_cast<const u32x4*>(ht + e * LD + 8 * ch);
       }
-      if (tid < D) z_save[((size_t)bh * Tm + i) * D + tid] = zs[tid];
     }
   }
   if (o_s_save != nullptr) {
     // O^s (and O^l, if asked for) on its own ([BH, N, d] contiguous), kept for the backward pass: same
     // route through the transposing tile as the mixed output
     for (int which = 0; which < (o_l_save != nullptr ? 2 : 1); which++) {
-      __syncthreads();                                 // the tile has been read out
 #pragma unroll
       for (int et = 0; et < ET; et++)
 #pragma unroll
@@ -951,12 +1411,34 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
           }
           *reinterpret_cast<bf16x4*>(os + qrow * LD + 32 * et + 8 * v4 + 4 * g) = pk;
         }
-      __syncthreads();
       uint16_t* dst = (which == 0 ? o_s_save : o_l_save) + ((size_t)bh * N + row0) * D;
-      for (int idx = tid; idx < BQ * (D / 8); idx += NT) {
-        const int r = idx / (D / 8), ch = idx % (D / 8);
+#pragma unroll
+      for (int x = 0; x < D / 16; x++) {
+        const int r = 32 * w + (x * kWave + lane) / (D / 8), ch = lane % (D / 8);
         if (r < rows_valid) *reinterpret_cast<u32x4*>(dst + (size_t)r * D + 8 * ch) = *reinterpret_cast<const u32x4*>(os + r * LD + 8 * ch);
       }
+    }
+  }
+  if (lse != nullptr || lse_save != nullptr) {
+    // Alg. 2 defines L on the smoothed keys.  The bf16 products use the raw K, whose scores are larger by
+    // q . colmean(K) / sqrt(d) in every column of a row (the softmax cancels it); the low-bit codes are those of
+    // the smoothed K already.  (The rows are read again: the fragments hold Q^phi by now.)
+    float qmu = 0.f;
+    if constexpr (!DENSE && !FP8) {
+      const uint16_t* src = qh + (size_t)(row0 + min(qrow, rows_valid - 1)) * tok_stride + 8 * g;
+#pragma unroll
+      for (int ks = 0; ks < KS; ks++) {
+        const bf16x8 x = *reinterpret_cast<const bf16x8*>(src + 16 * ks);
+#pragma unroll
+        for (int e = 0; e < 8; e++) qmu += (float)x[e] * (float)k_mean[(size_t)bh * D + 16 * ks + 8 * g + e];
+      }
+      qmu = swap_halves_sum(qmu);
+    }
+    if (g == 0 && qrow < rows_valid) {
+      const float L =
+          l_run > 0.f ? (m_run - kPShift + __log2f(l_run)) * 0.6931471805599453f - qmu * rsqrtf((float)D) : -INFINITY;
+      if (lse != nullptr) lse[(size_t)bh * N + row0 + qrow] = L;
+      if (lse_save != nullptr) lse_save[(size_t)bh * N + row0 + qrow] = L;
     }
   }
 }
@@ -969,7 +1451,7 @@ struct AttnArgs {
   const uint8_t* k_fp8;
   const float* k_scale;
   const uint8_t* v_codes;
-  const float *v_scale, *h_total, *z_total;
+  const float *v_scale, *h_frag, *z_total;
   const int32_t* block_idx;
   const float* alpha;
   uint16_t* out;
@@ -979,13 +1461,14 @@ struct AttnArgs {
 
 template <int D, int BQ, int MODE>
 static hipError_t launch_attn_t(const Shape& s, const AttnArgs& a, hipStream_t stream) {
-  constexpr int smem = AttnSmem<D, BQ, MODE == kSparseFp8 || MODE == kSparseInt8 || MODE == kSparseFp8V, MODE == kSparseFp8V>::kBytes;
+  constexpr int smem = AttnSmem<D, BQ, MODE == kSparseFp8 || MODE == kSparseInt8 || MODE == kSparseFp8V, MODE == kSparseFp8V,
+                                kPipelined<D, BQ, MODE>>::kBytes;
   static OncePerDevice once;
   if (hipError_t e = allow_dynamic_lds(once, (const void*)attn_mfma_kernel<D, BQ, MODE>, smem); e != hipSuccess) return e;
   const int Tm = (s.N + BQ - 1) / BQ;
   const int grid = ((Tm + kXcds - 1) / kXcds) * kXcds * s.BH;   // some workgroups of the last run of a head may have no block
   attn_mfma_kernel<D, BQ, MODE><<<dim3((unsigned)grid), BQ * 2, smem, stream>>>(
-      a.q, a.k, a.v, a.k_mean, a.k_phi, a.z_blocks, a.k_fp8, a.k_scale, a.v_codes, a.v_scale, a.h_total, a.z_total,
+      a.q, a.k, a.v, a.k_mean, a.k_phi, a.z_blocks, a.k_fp8, a.k_scale, a.v_codes, a.v_scale, a.h_frag, a.z_total,
       a.block_idx, a.alpha,
       a.out, a.lse, (uint16_t*)a.sv.o_s, (uint16_t*)a.sv.o_l, a.sv.lse, (uint16_t*)a.sv.h_i, a.sv.z_i, s.sin, s.sout, s.H, s.N, Tm, s.Tn, s.k,
       s.alpha_per_block ? 1 : 0);
@@ -995,10 +1478,10 @@ static hipError_t launch_attn_t(const Shape& s, const AttnArgs& a, hipStream_t s
 hipError_t launch_attn_bf16(const Shape& s, const uint16_t* q, const uint16_t* k, const uint16_t* v,
                             const double* k_mean, const uint16_t* k_phi, const float* z_blocks, const uint8_t* k_fp8,
                             const float* k_scale, const uint8_t* v_codes, const float* v_scale,
-                            const float* h_total, const float* z_total,
+                            const float* h_frag, const float* z_total,
                             const int32_t* block_idx, const float* alpha, uint16_t* out, float* lse,
                             const SavedForBackward& sv, hipStream_t stream) {
-  AttnArgs a{q, k, v, k_mean, k_phi, z_blocks, k_fp8, k_scale, v_codes, v_scale, h_total, z_total, block_idx, alpha, out, lse, sv};
+  AttnArgs a{q, k, v, k_mean, k_phi, z_blocks, k_fp8, k_scale, v_codes, v_scale, h_frag, z_total, block_idx, alpha, out, lse, sv};
 #define SLA2_ATTN(DD, QQ)                                                  \
   return s.quant == 3 ? launch_attn_t<DD, QQ, kSparseFp8V>(s, a, stream)   \
        : s.quant == 2 ? launch_attn_t<DD, QQ, kSparseInt8>(s, a, stream)   \
