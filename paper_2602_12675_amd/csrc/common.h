@@ -1,5 +1,7 @@
 // Shared declarations of the SLA2 HIP kernels (gfx950 only).
 #pragma once
+#include <type_traits>
+
 #include <hip/hip_runtime.h>
 #include <stddef.h>
 #include <stdint.h>
@@ -82,6 +84,39 @@ __device__ __forceinline__ float load_elem(const uint16_t* p, size_t i) { return
 __device__ __forceinline__ void store_elem(float* p, size_t i, float v) { p[i] = v; }
 __device__ __forceinline__ void store_elem(uint16_t* p, size_t i, float v) { p[i] = f32_to_bf16_bits(v); }
 
+// lanes l and l ^ 32 combine their values through v_permlane32_swap (a vector instruction: no LDS round trip,
+// whose latency a wave that has the vector unit to itself would sit out)
+__device__ __forceinline__ float swap_halves_max(float x) {
+  const unsigned u = __builtin_bit_cast(unsigned, x);
+  const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);   // r[0] = low half twice, r[1] = high half twice
+  return fmaxf(__builtin_bit_cast(float, (unsigned)r[0]), __builtin_bit_cast(float, (unsigned)r[1]));
+}
+__device__ __forceinline__ float swap_halves_sum(float x) {
+  const unsigned u = __builtin_bit_cast(unsigned, x);
+  const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  return __builtin_bit_cast(float, (unsigned)r[0]) + __builtin_bit_cast(float, (unsigned)r[1]);
+}
+// lanes 32..63 take the values of lanes 0..31
+__device__ __forceinline__ float low_half(float x) {
+  const unsigned u = __builtin_bit_cast(unsigned, x);
+  return __builtin_bit_cast(float, (unsigned)__builtin_amdgcn_permlane32_swap(u, u, false, false)[0]);
+}
+// Maximum over the wave, on every lane; vector instructions only.
+__device__ __forceinline__ float wave_max(float x) {
+  auto dpp = [&](auto ctrl) {
+    const int i = __builtin_bit_cast(int, x);
+    x = fmaxf(x, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(i, i, decltype(ctrl)::value, 0xf, 0xf, false)));
+  };
+  dpp(std::integral_constant<int, 0xB1>());          // quad_perm 1 0 3 2
+  dpp(std::integral_constant<int, 0x4E>());          // quad_perm 2 3 0 1
+  dpp(std::integral_constant<int, 0x141>());         // row_half_mirror
+  dpp(std::integral_constant<int, 0x140>());         // row_mirror
+  const unsigned u = __builtin_bit_cast(unsigned, x);
+  const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  x = fmaxf(__builtin_bit_cast(float, (unsigned)r[0]), __builtin_bit_cast(float, (unsigned)r[1]));
+  return swap_halves_max(x);
+}
+
 // Where sla2_forward keeps O^s, O^l ([BH, N, d], element type of out; o_l may be null on its own) and
 // L ([BH, N]) for the backward pass; all null when nothing is to be kept.  With them goes the state of the linear branch
 // per query block: Z_i [BH, T_m, d] and H_i, bf16 tensors: H_i^T as bf16 [BH, T_m, d(e), d(c)], fp32 tensors: H_i as fp32
@@ -124,11 +159,15 @@ hipError_t launch_bwd_q_f32(const Shape& s, const BwdArgs& a, hipStream_t stream
 hipError_t launch_bwd_kv_f32(const Shape& s, const BwdArgs& a, hipStream_t stream);
 
 // ---- launchers (one per kernel file); all enqueue on `stream` and return hipGetLastError() ----
+// k_frag [BH, T_n, d]: the block sums of K once more, as the operand fragments of the router's products: for each group of
+// 16 key blocks of a head (the last group of a head: of the n it has) [d / 8][4][16 (n)][2], entry (j, g, b, x) being channel
+// 8 j + 2 g + x of block b.  The router reads whole kilobytes; from the row-major sums each of the 16 lanes of a quarter
+// wave would touch a cache line of its own, which took 60 cycles a load.
 hipError_t launch_block_sums(const Shape& s, const void* q, const void* k, const float* router_w, double* q_sum,
-                             double* k_sum, double* router_m, hipStream_t stream);
-hipError_t launch_router_topk(const Shape& s, const double* q_sum, const double* k_sum, const double* router_m,
+                             double* k_sum, double* k_frag, double* router_m, hipStream_t stream);
+hipError_t launch_router_topk(const Shape& s, const double* q_sum, const double* k_sum, const double* k_frag, const double* router_m,
                               int32_t* block_idx, double* k_mean, hipStream_t stream);
-hipError_t launch_router_soft(const Shape& s, const double* q_sum, const double* k_sum, const double* router_m,
+hipError_t launch_router_soft(const Shape& s, const double* q_sum, const double* k_frag, const double* router_m,
                               float* mask, double tau, hipStream_t stream);
 hipError_t launch_kv_state_f32(const Shape& s, const float* k, const float* v, const double* k_mean, float* k_stats,
                                float* partial, hipStream_t stream);

@@ -22,38 +22,6 @@ constexpr int kVmcnt0 = 0x0F70;                    // s_waitcnt vmcnt(0), other 
 __device__ __forceinline__ float half_sum(float x) { return x + __shfl_xor(x, 32); }
 __device__ __forceinline__ float half_max(float x) { return fmaxf(x, __shfl_xor(x, 32)); }
 
-// lanes l and l ^ 32 combine their values through v_permlane32_swap (a vector instruction: no LDS round trip,
-// whose latency a wave that has the vector unit to itself would sit out)
-__device__ __forceinline__ float swap_halves_max(float x) {
-  const unsigned u = __builtin_bit_cast(unsigned, x);
-  const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);   // r[0] = low half twice, r[1] = high half twice
-  return fmaxf(__builtin_bit_cast(float, (unsigned)r[0]), __builtin_bit_cast(float, (unsigned)r[1]));
-}
-__device__ __forceinline__ float swap_halves_sum(float x) {
-  const unsigned u = __builtin_bit_cast(unsigned, x);
-  const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-  return __builtin_bit_cast(float, (unsigned)r[0]) + __builtin_bit_cast(float, (unsigned)r[1]);
-}
-// lanes 32..63 take the values of lanes 0..31
-__device__ __forceinline__ float low_half(float x) {
-  const unsigned u = __builtin_bit_cast(unsigned, x);
-  return __builtin_bit_cast(float, (unsigned)__builtin_amdgcn_permlane32_swap(u, u, false, false)[0]);
-}
-// Maximum over the wave, on every lane; vector instructions only.
-__device__ __forceinline__ float wave_max(float x) {
-  auto dpp = [&](auto ctrl) {
-    const int i = __builtin_bit_cast(int, x);
-    x = fmaxf(x, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(i, i, decltype(ctrl)::value, 0xf, 0xf, false)));
-  };
-  dpp(std::integral_constant<int, 0xB1>());          // quad_perm 1 0 3 2
-  dpp(std::integral_constant<int, 0x4E>());          // quad_perm 2 3 0 1
-  dpp(std::integral_constant<int, 0x141>());         // row_half_mirror
-  dpp(std::integral_constant<int, 0x140>());         // row_mirror
-  const unsigned u = __builtin_bit_cast(unsigned, x);
-  const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-  x = fmaxf(__builtin_bit_cast(float, (unsigned)r[0]), __builtin_bit_cast(float, (unsigned)r[1]));
-  return swap_halves_max(x);
-}
 // Between two phases of a workgroup.  LDS is written by the tile transfers only (waited for through vmcnt where a phase
 // needs them), and every operand read is waited for by the product that consumes it, so the barrier itself
 // waits for nothing: reads issued before it stay in flight across it.

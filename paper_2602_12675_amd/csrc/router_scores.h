@@ -61,7 +61,7 @@ __device__ __forceinline__ void project16(const double (*A)[D + 2], double (*C)[
 // -infinity).  All 16 waves of the workgroup call it; `lds` holds router_lds_bytes<D>().
 template <int D, int SLOTS>
 __device__ __forceinline__ void router_scores(double (&score)[SLOTS], const double* __restrict__ q_sum,
-                                              const double* __restrict__ k_sum, const double* __restrict__ M, double* lds,
+                                              const double* __restrict__ k_frag, const double* __restrict__ M, double* lds,
                                               int bh, int row0, int N, int bq, int bk, int Tm, int Tn) {
   // LDS: xa [16][D+2] pooled queries, later Qbar M | tile [16][264] one round of scores (the partial projections
   // before the first round)
@@ -74,30 +74,35 @@ __device__ __forceinline__ void router_scores(double (&score)[SLOTS], const doub
 
   // Operand B of a round: lane l feeds key block col0 + l % 16.  The contraction runs in an order of its own (the
   // same for both operands): product 2 j + x takes channels 8 j + 2 (l / 16) + x, so that one 16-byte load serves two
-  // products and the four lanes of a row cover 64 consecutive bytes.  The loads go straight to registers, kBatch of
-  // them ahead of the products (staging them through LDS for fully coalesced rows takes the same time and 70 KB more of
-  // LDS per workgroup).
+  // products; the pooled keys lie in that order (k_frag).  The loads go straight to registers, kBatch of them ahead of
+  // the products.
   constexpr int kLoads = D / 8, kBatch = SLOTS > 16 ? 4 : 8;
   f64x2 pre[2][kBatch];
-  const double* kb = k_sum + (size_t)bh * Tn * D + 2 * (lane / 16);
+  const double* kb = k_frag + (size_t)bh * Tn * D;
   auto fetch = [&](int r, int batch) {
-    const int col = min(r * kColsPerRound + wave * 16 + lane % 16, Tn - 1);    // past the end: the last key block again
-    const double* p = kb + (size_t)col * D + 8 * kBatch * batch;
+    const int first = min(r * kColsPerRound + wave * 16, (Tn - 1) / 16 * 16), n = min(16, Tn - first);   // past the end: the last group again
+    const double* p = kb + (size_t)first * D + 8 * n * kBatch * batch + 2 * (lane / 16 * n + min(lane % 16, n - 1));
 #pragma unroll
-    for (int i = 0; i < kBatch; i++) pre[batch & 1][i] = *reinterpret_cast<const f64x2*>(p + 8 * i);
+    for (int i = 0; i < kBatch; i++) pre[batch & 1][i] = *reinterpret_cast<const f64x2*>(p + 8 * n * i);
   };
 
-  double mb[ProjGeom<D>::kSteps];
-  project16_fetch<D>(mb, M, wave, lane);               // operands of the projection, in flight during the Qbar load
-  for (int e = threadIdx.x; e < kRouterRows * D; e += 1024) {
-    const int r = e / D, c = e % D;
-    const int row = min(row0 + r, Tm - 1);             // rows past the end repeat the last one; never stored
-    const int rows = min(bq, N - row * bq);
-    xa[r][c] = q_sum[((size_t)bh * Tm + row) * D + c] / (double)rows;     // mean pooling (Eq. 15)
+  // requested in the order of use: block sums of Q, operands of the projection, the first pooled keys
+  constexpr int kQLoads = kRouterRows * D / 1024;
+  double qv[kQLoads], mb[ProjGeom<D>::kSteps];
+#pragma unroll
+  for (int x = 0; x < kQLoads; x++) {
+    const int r = (threadIdx.x + 1024 * x) / D, c = threadIdx.x % D;
+    qv[x] = q_sum[((size_t)bh * Tm + min(row0 + r, Tm - 1)) * D + c];     // rows past the end repeat the last one; never stored
+  }
+  project16_fetch<D>(mb, M, wave, lane);
+  fetch(0, 0);
+#pragma unroll
+  for (int x = 0; x < kQLoads; x++) {
+    const int r = (threadIdx.x + 1024 * x) / D, c = threadIdx.x % D;
+    xa[r][c] = qv[x] / (double)min(bq, N - min(row0 + r, Tm - 1) * bq);   // mean pooling (Eq. 15)
   }
   __syncthreads();
   project16<D>(xa, xb, mb, wave, lane);                                   // Qbar (Wq Wk^T / sqrt(d)), in shares
-  fetch(0, 0);
   __syncthreads();
   for (int e = threadIdx.x; e < kRouterRows * D; e += 1024) {
     const int r = e / D, c = e % D;
@@ -110,7 +115,7 @@ __device__ __forceinline__ void router_scores(double (&score)[SLOTS], const doub
 
 #pragma unroll
   for (int s = 0; s < SLOTS; s++) score[s] = -INFINITY;
-  const double last_cnt = (double)(N - (Tn - 1) * bk);
+  const double last_cnt = (double)(N - (Tn - 1) * bk), inv_bk = 1.0 / bk;   // bk = 64: the product is the exact quotient
 #pragma unroll
   for (int r = 0; r < SLOTS / 4; r++) {
     if (r < rounds) {
@@ -136,7 +141,8 @@ __device__ __forceinline__ void router_scores(double (&score)[SLOTS], const doub
 #pragma unroll
       for (int x = 0; x < 4; x++) {
         const int col = r * kColsPerRound + x * kWave + lane;
-        const double sc = tile[wave][x * kWave + lane] / (col == Tn - 1 ? last_cnt : (double)bk);
+        double sc = tile[wave][x * kWave + lane] * inv_bk;
+        if (col == Tn - 1) sc = tile[wave][x * kWave + lane] / last_cnt;
         score[4 * r + x] = col < Tn ? sc : -INFINITY;
       }
       __syncthreads();

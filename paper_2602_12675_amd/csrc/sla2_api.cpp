@@ -117,7 +117,10 @@ void make_layout(const Shape& s, sla2_ws_layout* L) {
   L->k_scale = take(s.quant ? BH * (size_t)s.Tn * sizeof(float) : 0);
   L->v_fp8 = take(s.quant == 3 ? BH * (size_t)s.Tn * s.bk * d : 0);
   L->v_scale = take(s.quant == 3 ? BH * (size_t)s.Tn * sizeof(float) : 0);
-  L->partial = take(BH * ((size_t)s.chunks * (d * d + d) + (s.bf16 ? d * d : 0)) * sizeof(float));   // bf16: -h_total as fragments behind
+  // two lives: the pooled keys as fragments, for the router; then the partial sums (bf16: -h_total as fragments behind them)
+  const size_t partials = BH * ((size_t)s.chunks * (d * d + d) + (s.bf16 ? d * d : 0)) * sizeof(float);
+  const size_t pooled = BH * (size_t)s.Tn * d * sizeof(double);
+  L->partial = take(partials > pooled ? partials : pooled);
   const size_t esz = s.bf16 ? 2 : 4;
   L->o_s = take(s.save ? BH * (size_t)s.N * d * esz : 0);
   L->o_l = take(s.save && !s.bf16 ? BH * (size_t)s.N * d * esz : 0);   // bf16 tensors: rebuilt from H_i in the backward pass
@@ -199,11 +202,12 @@ static int run_router(const Shape& s, const sla2_ws_layout& L, const void* q, co
                       void* ws, hipStream_t st) {
   double* q_sum = at<double>(ws, L.q_sum);
   double* k_sum = at<double>(ws, L.k_sum);
+  double* k_frag = at<double>(ws, L.partial);
   double* router_m = at<double>(ws, L.router_m);
-  if (SLA2_STAGE(SLA2_STAGE_BLOCK_SUMS, launch_block_sums(s, q, k, router_w, q_sum, k_sum, router_m, st)) !=
+  if (SLA2_STAGE(SLA2_STAGE_BLOCK_SUMS, launch_block_sums(s, q, k, router_w, q_sum, k_sum, k_frag, router_m, st)) !=
       hipSuccess)
     return SLA2_EHIP;
-  if (SLA2_STAGE(SLA2_STAGE_TOPK, launch_router_topk(s, q_sum, k_sum, router_m, at<int32_t>(ws, L.block_idx),
+  if (SLA2_STAGE(SLA2_STAGE_TOPK, launch_router_topk(s, q_sum, k_sum, k_frag, router_m, at<int32_t>(ws, L.block_idx),
                                                      at<double>(ws, L.k_mean), st)) != hipSuccess)
     return SLA2_EHIP;
   return SLA2_OK;
@@ -270,10 +274,10 @@ int sla2_router_soft(const sla2_params* params, const void* q, const void* k, co
   hipStream_t st = (hipStream_t)hip_stream;
   count_call();
   if (SLA2_STAGE(SLA2_STAGE_BLOCK_SUMS, launch_block_sums(s, q, k, router_w, at<double>(workspace, L.q_sum),
-                                                          at<double>(workspace, L.k_sum),
+                                                          at<double>(workspace, L.k_sum), at<double>(workspace, L.partial),
                                                           at<double>(workspace, L.router_m), st)) != hipSuccess)
     return SLA2_EHIP;
-  if (SLA2_STAGE(SLA2_STAGE_TOPK, launch_router_soft(s, at<double>(workspace, L.q_sum), at<double>(workspace, L.k_sum),
+  if (SLA2_STAGE(SLA2_STAGE_TOPK, launch_router_soft(s, at<double>(workspace, L.q_sum), at<double>(workspace, L.partial),
                                                      at<double>(workspace, L.router_m), mask_out, (double)tau,
                                                      st)) != hipSuccess)
     return SLA2_EHIP;

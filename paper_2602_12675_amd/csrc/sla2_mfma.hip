@@ -261,9 +261,9 @@ __global__ __launch_bounds__(256) void kv_state_bf16_kernel(const uint16_t* __re
 #pragma unroll
     for (int b = 0; b < HS::kNtw; b++)
 #pragma unroll
-      for (int e = 0; e < 16; e++) {
-        const int c = 32 * (mt0 + a) + 8 * (e / 4) + 4 * g + e % 4;
-        ph[c * D + 32 * (nt0 + b) + lane % 32] = hacc[a][b][e];
+      for (int x = 0; x < 4; x++) {
+        const f32x4 part = {hacc[a][b][4 * x], hacc[a][b][4 * x + 1], hacc[a][b][4 * x + 2], hacc[a][b][4 * x + 3]};
+        *reinterpret_cast<f32x4*>(ph + (((mt0 + a) * (D / 32) + nt0 + b) * 4 + x) * 256 + 4 * lane) = part;   // as it lies (kv_total)
       }
     if (g == 0 && nt0 == 0) ph[D * D + 32 * (mt0 + a) + lane] = zacc[a];
   }

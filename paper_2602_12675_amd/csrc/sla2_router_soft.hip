@@ -43,7 +43,7 @@ __device__ __forceinline__ double reciprocal(double x) {
 
 template <int D, int SLOTS>
 __global__ __launch_bounds__(1024) void router_soft_kernel(const double* __restrict__ q_sum,
-                                                           const double* __restrict__ k_sum,
+                                                           const double* __restrict__ k_frag,
                                                            const double* __restrict__ router_m,
                                                            float* __restrict__ mask, int H, int N, int bq, int bk,
                                                            int Tm, int Tn, int k, double tau, int w_per_head) {
@@ -59,7 +59,7 @@ __global__ __launch_bounds__(1024) void router_soft_kernel(const double* __restr
     return;
   }
   double x[SLOTS];
-  router_scores<D, SLOTS>(x, q_sum, k_sum, router_m + (w_per_head ? (size_t)(bh % H) * D * D : 0), lds, bh, row0, N, bq, bk,
+  router_scores<D, SLOTS>(x, q_sum, k_frag, router_m + (w_per_head ? (size_t)(bh % H) * D * D : 0), lds, bh, row0, N, bq, bk,
                           Tm, Tn);
   if (row >= Tm) return;
   const int slots = (Tn + kColsPerRound - 1) / kColsPerRound * 4;
@@ -148,7 +148,7 @@ __global__ __launch_bounds__(1024) void router_soft_kernel(const double* __restr
       out[column(s)] = (float)(fast ? reciprocal(__builtin_fma(x[s], u, 1.0)) : sigmoid_f64(y - x[s]));
 }
 
-hipError_t launch_router_soft(const Shape& s, const double* q_sum, const double* k_sum, const double* router_m,
+hipError_t launch_router_soft(const Shape& s, const double* q_sum, const double* k_frag, const double* router_m,
                               float* mask, double tau, hipStream_t stream) {
   const dim3 grid((unsigned)(s.BH * ((s.Tm + kRouterRows - 1) / kRouterRows)));
   const int rounds = (s.Tn + kColsPerRound - 1) / kColsPerRound;     // <= 8 (kMaxKeyBlocks)
@@ -158,7 +158,7 @@ hipError_t launch_router_soft(const Shape& s, const double* q_sum, const double*
     if (hipError_t e = allow_dynamic_lds(once, (const void*)router_soft_kernel<DD, SS>, (int)router_lds_bytes<DD>()); \
         e != hipSuccess)                                                                                             \
       return e;                                                                                                      \
-    router_soft_kernel<DD, SS><<<grid, 1024, router_lds_bytes<DD>(), stream>>>(q_sum, k_sum, router_m, mask, s.H, s.N, \
+    router_soft_kernel<DD, SS><<<grid, 1024, router_lds_bytes<DD>(), stream>>>(q_sum, k_frag, router_m, mask, s.H, s.N, \
                                                                                s.bq, s.bk, s.Tm, s.Tn, s.k, tau,      \
                                                                                s.w_per_head ? 1 : 0);                 \
   }
