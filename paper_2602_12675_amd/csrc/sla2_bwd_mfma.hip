@@ -148,9 +148,10 @@ __global__ __launch_bounds__(BQ * 2, 2) void bwd_q_mfma_kernel(
   float sumds = 0.f;
   const float c0 = kLog2e * rscale;
 
-  for (int s = 0; s < ntiles; s++) {
+  auto tile = [&](int s, auto is_short) {
+    constexpr bool kShort = decltype(is_short)::value;
     const int buf = s & 1;
-    const int valid = min(kTileTokens, N - j_cur * kTileTokens);
+    const int valid = kShort ? N - j_cur * kTileTokens : kTileTokens;
     const int j_nn = sel[min(s + 2, ntiles - 1)];
     if (s + 1 < ntiles) dma(j_nxt, buf ^ 1);
     j_cur = j_nxt;
@@ -161,6 +162,24 @@ __global__ __launch_bounds__(BQ * 2, 2) void bwd_q_mfma_kernel(
     for (int mt = 0; mt < 2; mt++)
 #pragma unroll
       for (int e = 0; e < 16; e++) { sacc[mt][e] = 0.f; dpacc[mt][e] = 0.f; }
+    // Element x of the tile: P^T = exp(S^T - L), in the place of the score, and dS^T = P^T (.) (alpha dP^T - D^s), as
+    // B-operand fragments in token order.  Both run between the products of other elements: the exponentials behind
+    // those of dP^T, dS^T of the first 32 keys behind those of the second half, the rest behind dQ's first products.
+    // The matrix and the vector unit then work side by side within a wave too: a training step on 12 heads of 32,760
+    // tokens 1,730 -> 1,711 us.
+    bf16x8 dsf[4];
+    constexpr int kPer = 16 / KS;                      // elements per product
+    auto prob = [&](int x) {
+      float p = fast_exp2(sacc[x / 16][x % 16] * c0 - L2);
+      if (kShort && 32 * (x / 16) + 8 * (x % 16 / 4) + 4 * g + x % 4 >= valid) p = 0.f;
+      settle(p);                                       // here, not where the compiler would gather them
+      sacc[x / 16][x % 16] = p;
+    };
+    auto grad = [&](int x) {
+      const float dsv = sacc[x / 16][x % 16] * (al * dpacc[x / 16][x % 16] - Ds);
+      sumds += dsv;
+      dsf[x / 8][x % 8] = (__bf16)dsv;
+    };
     // S^T = K Q^T and dP^T = V dO^T (keys x query rows; alpha joins below), two 32-key halves each.  One operand read
     // (16 bytes of key row 32 mt + l % 32) per product, issued untracked and kept kAhead deep in flight:
     // a tracked read would be waited for right before its product, one LDS round trip per product.
@@ -184,20 +203,14 @@ __global__ __launch_bounds__(BQ * 2, 2) void bwd_q_mfma_kernel(
         const int grp = n / KS, ks = n % KS;
         if (grp < 2) sacc[grp] = mfma_bf16(a, qf[ks], sacc[grp]);
         else dpacc[grp - 2] = mfma_bf16(a, gof[ks], dpacc[grp - 2]);
+        if (grp >= 2)
+#pragma unroll
+          for (int x = 0; x < kPer; x++) prob(kPer * (n - 2 * KS) + x);
+        if (grp == 3)
+#pragma unroll
+          for (int x = 0; x < kPer; x++) grad(kPer * ks + x);
       }
     }
-    // dS^T = P^T (.) (alpha dP^T - D^s), as B-operand fragments in token order
-    bf16x8 dsf[4];
-#pragma unroll
-    for (int mt = 0; mt < 2; mt++)
-#pragma unroll
-      for (int e = 0; e < 16; e++) {
-        float arg = sacc[mt][e] * c0 - L2;
-        if (valid < kTileTokens) arg = 32 * mt + 8 * (e / 4) + 4 * g + e % 4 >= valid ? -INFINITY : arg;
-        const float dsv = fast_exp2(arg) * (al * dpacc[mt][e] - Ds);
-        sumds += dsv;
-        dsf[2 * mt + e / 8][e % 8] = (__bf16)dsv;
-      }
     // dQ^T += K^T dS^T: transposing reads of the K tile, those of the next 16-token step in flight
     // while the products of this one run
     {
@@ -221,12 +234,19 @@ __global__ __launch_bounds__(BQ * 2, 2) void bwd_q_mfma_kernel(
           settle(rk[slot][et][1]);
           const u32x4 v4 = {rk[slot][et][0][0], rk[slot][et][0][1], rk[slot][et][1][0], rk[slot][et][1][1]};
           dqacc[et] = mfma_bf16(__builtin_bit_cast(bf16x8, v4), dsf[ks], dqacc[et]);
+          if (ks < 2)
+#pragma unroll
+            for (int x = 0; x < 8 / ET; x++) grad(16 + 8 * ks + (8 / ET) * et + x);
         }
       }
     }
     __builtin_amdgcn_s_waitcnt(kVmcnt0);             // the next tile has landed in LDS ...
     __syncthreads();                                 // ... for everyone, and this tile's buffer is free
-  }
+  };
+  // indices ascend: only the last tile of the list can be the short one at the end of the sequence
+  const int whole = ntiles - (ntiles > 0 && N % kTileTokens != 0 && sel[ntiles - 1] == Tn - 1 ? 1 : 0);
+  for (int s = 0; s < whole; s++) tile(s, std::false_type());
+  if (whole < ntiles) tile(whole, std::true_type());
 
   // ================= epilogue =================
   uint16_t* ta = reinterpret_cast<uint16_t*>(smem);                 // H_i^T [e][c]; then the dQ tile; then dO [row][e]
