@@ -50,7 +50,9 @@ __global__ __launch_bounds__(BQ * 2, 2) void bwd_q_mfma_kernel(
     int ksel, int alpha_per_block) {
   constexpr int NW = BQ / 32, NT = NW * kWave;
   constexpr int LD = D + 8, KS = D / 16, ET = D / 32;
-  typedef SwizzledLayout<D> SL;
+  typedef typename std::conditional<D == 128 && BQ == 128, SwizzledLayoutB<128>, SwizzledLayout<D>>::type SL;
+  // (at d = 128 free of bank conflicts, which were half of the LDS cycles: 435 -> 427 us on 12 heads of 32,760 tokens; its
+  // rows repeat every 16, which the two waves of a 64-row block do not cover with one transfer)
   typedef PaddedLayout<D> PL;
   typedef BwdQSmem<D, BQ> SM;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
@@ -87,8 +89,8 @@ __global__ __launch_bounds__(BQ * 2, 2) void bwd_q_mfma_kernel(
 
   auto dma = [&](int j, int buf) {
     const int t0 = j * kTileTokens, valid = min(kTileTokens, N - t0);
-    dma_tile<D, NW>(kh + (size_t)t0 * tok_stride, tok_stride, valid, lds_address(kbuf(buf)), w, lane);
-    dma_tile<D, NW>(vh + (size_t)t0 * tok_stride, tok_stride, valid, lds_address(vbuf(buf)), w, lane);
+    dma_tile<D, NW, SL>(kh + (size_t)t0 * tok_stride, tok_stride, valid, lds_address(kbuf(buf)), w, lane);
+    dma_tile<D, NW, SL>(vh + (size_t)t0 * tok_stride, tok_stride, valid, lds_address(vbuf(buf)), w, lane);
   };
   int j_cur = ntiles > 0 ? sel[0] : 0, j_nxt = ntiles > 1 ? sel[1] : 0;
   if (ntiles > 0) dma(j_cur, 0);
@@ -134,12 +136,11 @@ __global__ __launch_bounds__(BQ * 2, 2) void bwd_q_mfma_kernel(
   }
 
   // LDS byte offsets of this lane's operand reads inside a K or V tile: row-wise reads (key row
-  // l % 32, channel step ks at (offset of step 0) ^ 32 ks) and transposing reads (cf. read_tr4)
+  // l % 32, channel step ks at (offset of step 0) ^ 32 ks) and transposing reads (cf. read_tr4): rows 4 g + (l % 16) / 4 (lo)
+  // and 8 further (hi), channel tile et at (offset of tile 0) ^ 64 et, 16-token step ks 32 D ks further
   const unsigned b_off = (unsigned)SL::offset(lane % 32, 8 * g) * 2;
-  unsigned a_off[ET];
-#pragma unroll
-  for (int et = 0; et < ET; et++)
-    a_off[et] = (unsigned)SL::offset(4 * g + (lane % 16) / 4, 32 * et + 16 * ((lane / 16) % 2) + 4 * (lane % 4)) * 2;
+  const int tr_row = 4 * g + (lane % 16) / 4, tr_col = 16 * ((lane / 16) % 2) + 4 * (lane % 4);
+  const unsigned a_off[2] = {(unsigned)SL::offset(tr_row, tr_col) * 2, (unsigned)SL::offset(tr_row + 8, tr_col) * 2};
   f32x16 dqacc[ET];
 #pragma unroll
   for (int et = 0; et < ET; et++)
@@ -220,7 +221,7 @@ __global__ __launch_bounds__(BQ * 2, 2) void bwd_q_mfma_kernel(
 #pragma unroll
         for (int et = 0; et < ET; et++)
 #pragma unroll
-          for (int hi = 0; hi < 2; hi++) rk[slot][et][hi] = lds_read_tr_untracked_at<16 * D>(ka + a_off[et], 2 * ks + hi);
+          for (int hi = 0; hi < 2; hi++) rk[slot][et][hi] = lds_read_tr_untracked_at<32 * D>((ka + a_off[hi]) ^ (64u * et), ks);
       };
       issue(0, 0);
 #pragma unroll
@@ -436,6 +437,20 @@ static hipError_t launch_bwd_q_mfma(const Shape& s, const BwdArgs& a, hipStream_
 }
 
 // ---------------------------------------------------------------------------------------------
+// 16 bytes of a step's row quantities: the 32-byte groups 8 rows apart, L at n = 0 .. 3 and D^s, 256 bytes on, at 8 .. 11
+__device__ __forceinline__ u32x4 stat_read(unsigned base, int n) {
+  switch (n) {
+    case 0: return lds_read16_untracked<0>(base);
+    case 1: return lds_read16_untracked<32>(base);
+    case 2: return lds_read16_untracked<64>(base);
+    case 3: return lds_read16_untracked<96>(base);
+    case 8: return lds_read16_untracked<256>(base);
+    case 9: return lds_read16_untracked<288>(base);
+    case 10: return lds_read16_untracked<320>(base);
+    default: return lds_read16_untracked<352>(base);
+  }
+}
+
 template <int D> struct BwdKvSmem {
   static constexpr int kLd = D + 8;
   static constexpr int kTile = SwizzledLayout<D>::kTileBytes;                  // one 64 x D bf16 tile
@@ -572,15 +587,32 @@ __global__ __launch_bounds__(256, 2) void bwd_kv_mfma_kernel(
     }
     i_nxt = block_of(t + 2);
     const unsigned qa = lds_address(qbuf(buf)), ga = lds_address(gbuf(buf));
-    const float* st_l = stat + buf * 128 + 32 * rh + 4 * g;
-    // S = Q K^T and dP = dO V^T: this wave's 32 rows x its 32 keys.  16 operand reads, each feeding one product.
+    const unsigned st = lds_address(stat + buf * 128 + 32 * rh + 4 * g);
+    // S = Q K^T and dP = dO V^T: this wave's 32 rows x its 32 keys; alpha P and dS = P (.) (alpha dP - D^s), as B-operand
+    // fragments over the 32 rows (token order).  One stream of LDS reads, kAhead of them in flight: the operand reads, each
+    // feeding one product, and among them the row quantities - L of four rows behind every KS / 4 products of dP, whose
+    // exponentials then run beside the products, and D^s at the end (12 heads of 32,760 tokens: 860 -> 852 us).  Keys past the end of a short key block need no
+    // mask: their columns mix with no others and are not stored.
     f32x16 sacc, dpacc;
+    bf16x8 pf[2], dsf[2];
 #pragma unroll
     for (int e = 0; e < 16; e++) { sacc[e] = 0.f; dpacc[e] = 0.f; }
     {
-      constexpr int kItems = 2 * KS, kAhead = 4, kSlots = kAhead + 1;
+      constexpr int kGroup = KS / 4 + 1, kItems = KS + 4 * kGroup + 4, kAhead = 4, kSlots = kAhead + 1;
       u32x4 ring[kSlots];
-      auto issue = [&](int n) { ring[n % kSlots] = lds_read16_untracked<0>(((n < KS ? qa : ga) + b_off) ^ (32u * (n % KS))); };
+      auto pin = [](bf16x8& f) {                       // converted here: eight registers less than the fp32 values
+        u32x4 u = __builtin_bit_cast(u32x4, f);
+        settle(u);
+        f = __builtin_bit_cast(bf16x8, u);
+      };
+      // items: KS of S; four groups of (KS / 4 of dP, L of rows 8 v4 + 4 g ..); D^s of the same rows, v4 = 0 .. 3
+      auto issue = [&](int n) {
+        const int m = n - KS, v4 = m / kGroup;
+        if (n < KS) ring[n % kSlots] = lds_read16_untracked<0>((qa + b_off) ^ (32u * n));
+        else if (m >= 4 * kGroup) ring[n % kSlots] = stat_read(st, 8 + m - 4 * kGroup);
+        else if (m % kGroup == kGroup - 1) ring[n % kSlots] = stat_read(st, v4);
+        else ring[n % kSlots] = lds_read16_untracked<0>((ga + b_off) ^ (32u * (v4 * (kGroup - 1) + m % kGroup)));
+      };
 #pragma unroll
       for (int n = 0; n < kAhead; n++) issue(n);
 #pragma unroll
@@ -588,27 +620,37 @@ __global__ __launch_bounds__(256, 2) void bwd_kv_mfma_kernel(
         if (n + kAhead < kItems) issue(n + kAhead);
         wait_lgkmcnt(n + kAhead < kItems ? kAhead : kItems - 1 - n);
         settle(ring[n % kSlots]);
-        const bf16x8 a = __builtin_bit_cast(bf16x8, ring[n % kSlots]);
-        if (n < KS) sacc = mfma_bf16(a, kfr[n], sacc);
-        else dpacc = mfma_bf16(a, vfr[n - KS], dpacc);
+        const int m = n - KS, v4 = m / kGroup;
+        if (n < KS) {
+          sacc = mfma_bf16(__builtin_bit_cast(bf16x8, ring[n % kSlots]), kfr[n], sacc);
+        } else if (m >= 4 * kGroup) {
+          const int q = m - 4 * kGroup;
+          const f32x4 d4 = __builtin_bit_cast(f32x4, ring[n % kSlots]);
+#pragma unroll
+          for (int r = 0; r < 4; r++) {
+            const int e = 4 * q + r;
+            pf[q / 2][e % 8] = (__bf16)(cur.al * sacc[e]);
+            dsf[q / 2][e % 8] = (__bf16)(sacc[e] * (cur.al * dpacc[e] - d4[r]));
+          }
+          if (q % 2 == 1) {
+            pin(pf[q / 2]);
+            pin(dsf[q / 2]);
+          }
+        } else if (m % kGroup == kGroup - 1) {
+          const f32x4 l4 = __builtin_bit_cast(f32x4, ring[n % kSlots]);
+#pragma unroll
+          for (int r = 0; r < 4; r++) {
+            const int e = 4 * v4 + r;
+            float p = fast_exp2(sacc[e] * c0 - l4[r]);
+            settle(p);                                 // here, not where the compiler would gather them
+            sacc[e] = p;
+          }
+        } else {
+          const int ks = v4 * (kGroup - 1) + m % kGroup;
+          dpacc = mfma_bf16(__builtin_bit_cast(bf16x8, ring[n % kSlots]), vfr[ks], dpacc);
+        }
       }
     }
-    // alpha P and dS = P (.) (alpha dP - D^s), as B-operand fragments over the 32 rows (token order).  Keys past the end
-    // of a short key block need no mask: their columns mix with no others and are not stored.
-    bf16x8 pf[2], dsf[2];
-#pragma unroll
-    for (int v4 = 0; v4 < 4; v4++) {
-      const f32x4 l4 = *reinterpret_cast<const f32x4*>(st_l + 8 * v4);
-      const f32x4 d4 = *reinterpret_cast<const f32x4*>(st_l + 64 + 8 * v4);
-#pragma unroll
-      for (int r = 0; r < 4; r++) {
-        const int e = 4 * v4 + r;
-        const float p = fast_exp2(sacc[e] * c0 - l4[r]);
-        pf[v4 / 2][4 * (v4 % 2) + r] = (__bf16)(cur.al * p);
-        dsf[v4 / 2][4 * (v4 % 2) + r] = (__bf16)(p * (cur.al * dpacc[e] - d4[r]));
-      }
-    }
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // nothing tracked is in flight when the counted reads below start
     // dV^T += dO^T (alpha P), dK'^T += Q^T dS: contraction over the 32 rows.  Fragment n: 16-row step, tensor, channel tile.
     {
       constexpr int kFrags = 4 * ET, kAhead = 3, kSlots = kAhead + 1;
