@@ -85,23 +85,59 @@ __global__ __launch_bounds__(256) void bwd_columns_kernel(const int32_t* __restr
 
 // ---------------------------------------------------------------------------------------------
 // The order in which bwd_kv takes the key blocks.  Its work on a key block is proportional to the length of the block's
-// list, which varies a lot (mean 7.5, longest 38 on 512 key blocks): a long list that starts last runs on alone.  So long
-// ones go first - but only among blocks that would share a cache anyway: neighbouring key blocks are selected by the same
-// query blocks, whose rows they gather.  Every head is cut into 8 runs of consecutive key blocks, one per XCD (workgroup p
-// runs on XCD p % 8), and the runs of a group of heads are each taken longest list first (a counting sort on the length,
-// cut off at 255).  The order decides when a block is worked on, never what is summed.
-__device__ void order_group(const int32_t* __restrict__ counts, int32_t* __restrict__ order, int h0, int h1, int Tn,
-                            int* hist /* LDS [8 x 256] */) {
-  const int tid = threadIdx.x, per_head = (Tn + kXcds - 1) / kXcds, n = (h1 - h0) * Tn;
-  int32_t* out = order + (size_t)h0 * kXcds * per_head;
+// list, which varies a lot (mean 7.5, a tenth above 15, longest 91 on 12 heads of 512 key blocks): a long list that starts
+// late runs on alone.  So the long ones go first, longest first over all heads.  The others follow
+// head by head, in groups of heads whose gathered rows fit the caches, again longest first: neighbouring key blocks are
+// selected by the same query blocks, whose rows they gather.  Every head is cut into 8 runs of consecutive key blocks, one
+// per XCD (workgroup p runs on XCD p % 8).  With the groups alone, the last group's long lists kept a fifth of the CUs
+// waiting (in a model of the 64 places of each XCD the last one ended at 1.54 times the mean, at twice the mean now at 1.09, at thrice at 1.12): training step on
+// those lists 1,747 -> 1,691 us, 20 heads of 75,600 tokens 11.86 -> 11.60 ms.
+// The order decides when a block is worked on, never what is summed.
+//
+// One call writes the places of one group: the long lists of all heads (h0 = 0, h1 = BH, LONG) or the others of heads
+// [h0, h1).  Place 8 r + x is the r-th of XCD x; a counting sort on the length, cut off at 255.
+constexpr int kNoLongList = 1 << 30;                  // every list is shorter
+template <bool LONG>
+__device__ void order_group(const int32_t* __restrict__ counts, int32_t* __restrict__ order, int BH, int h0, int h1, int Tn,
+                            int long_list, int* hist /* LDS [8 x 256] */, int* at /* LDS [16] */) {
+  const int tid = threadIdx.x, per_head = (Tn + kXcds - 1) / kXcds;
+  auto each = [&](int first, int end, auto f) {       // f(key block bh T_n + j, its count), eight loads in flight
+    for (int e0 = first + tid; e0 < end; e0 += 8 * 256) {
+      int c[8];
+#pragma unroll
+      for (int y = 0; y < 8; y++) c[y] = e0 + 256 * y < end ? counts[e0 + 256 * y] : 0;
+#pragma unroll
+      for (int y = 0; y < 8; y++)
+        if (e0 + 256 * y < end) f(e0 + 256 * y, c[y]);
+    }
+  };
   for (int x = tid; x < kXcds * 256; x += 256) hist[x] = 0;
-  for (int x = tid; x < (h1 - h0) * kXcds * per_head; x += 256) out[x] = -1;   // places a short last run leaves empty
+  if (tid < 2 * kXcds) at[tid] = 0;                   // long lists per XCD: of all heads, of those before h0
   __syncthreads();
-  auto bin = [&](int e) { return (e % Tn) / per_head * 256 + 255 - min(counts[(size_t)h0 * Tn + e], 255); };
-  for (int e = tid; e < n; e += 256) atomicAdd(&hist[bin(e)], 1);
+  if constexpr (LONG) {
+    // places that a short last run of every head leaves empty: behind all others of their XCD
+    for (int e = tid; e < BH * kXcds * per_head; e += 256) {
+      const int x = e % kXcds, run = max(0, min(per_head, Tn - x * per_head));
+      if (e / kXcds >= BH * run) order[e] = -1;
+    }
+  } else if (long_list != kNoLongList) {
+    each(0, BH * Tn, [&](int e, int c) {
+      if (c > long_list) {
+        const int x = (e % Tn) / per_head;
+        atomicAdd(&at[x], 1);
+        if (e < h0 * Tn) atomicAdd(&at[kXcds + x], 1);
+      }
+    });
+  }
+  auto mine = [&](int c) { return (c > long_list) == LONG; };
+  auto bin = [&](int e, int c) { return (e % Tn) / per_head * 256 + 255 - min(c, 255); };
+  if (LONG && long_list == kNoLongList) return;
+  each(h0 * Tn, h1 * Tn, [&](int e, int c) {
+    if (mine(c)) atomicAdd(&hist[bin(e, c)], 1);
+  });
   __syncthreads();
   for (int x = tid / kWave; x < kXcds; x += 4) {      // per XCD an exclusive scan of its 256 bins, 4 per lane
-    const int lane = tid % kWave;
+    const int lane = tid % kWave, run_len = max(0, min(per_head, Tn - x * per_head));
     int c[4], sum = 0;
 #pragma unroll
     for (int y = 0; y < 4; y++) { c[y] = hist[256 * x + 4 * lane + y]; sum += c[y]; }
@@ -112,14 +148,17 @@ __device__ void order_group(const int32_t* __restrict__ counts, int32_t* __restr
       if (lane >= o) run += y;
     }
     run -= sum;
+    if constexpr (!LONG) run += at[x] + h0 * run_len - at[kXcds + x];   // behind the long ones and the groups before
 #pragma unroll
     for (int y = 0; y < 4; y++) { hist[256 * x + 4 * lane + y] = run; run += c[y]; }
   }
   __syncthreads();
-  for (int e = tid; e < n; e += 256) {
-    const int b = bin(e);
-    out[kXcds * atomicAdd(&hist[b], 1) + b / 256] = (h0 + e / Tn) * kMaxKeyBlocks + e % Tn;
-  }
+  each(h0 * Tn, h1 * Tn, [&](int e, int c) {
+    if (mine(c)) {
+      const int b = bin(e, c);
+      order[kXcds * atomicAdd(&hist[b], 1) + b / 256] = e / Tn * kMaxKeyBlocks + e % Tn;
+    }
+  });
 }
 
 // dst[e] = sum over b < count of src[b][e] for the 256 entries from e0 on.  32 threads of 8 elements each, times 8
@@ -160,19 +199,22 @@ __device__ void sum_slots(const S* __restrict__ src, float* __restrict__ dst, in
   }
 }
 
-// workgroups: `groups` of order_group, then per head the 256-entry slices of dH_total and one for dZ_total
+// workgroups: one of order_group for the long lists and `groups` for the others, then per head the 256-entry slices of dH_total and one for dZ_total
 template <typename S>
 __global__ __launch_bounds__(256) void bwd_totals_kernel(const S* __restrict__ dh, const float* __restrict__ dz,
                                                          float* __restrict__ dh_total, float* __restrict__ dz_total,
                                                          const int32_t* __restrict__ counts, int32_t* __restrict__ order,
-                                                         int groups, int heads_per_group, int BH, int Tm, int Tn, int d) {
+                                                         int groups, int heads_per_group, int long_list, int BH, int Tm, int Tn, int d) {
   __shared__ float part[8][256];
-  if ((int)blockIdx.x < groups) {
-    const int h0 = blockIdx.x * heads_per_group, h1 = min(BH, h0 + heads_per_group);
-    order_group(counts, order, h0, h1, Tn, reinterpret_cast<int*>(&part[0][0]));
+  __shared__ int at[2 * kXcds];
+  if ((int)blockIdx.x <= groups) {
+    int* hist = reinterpret_cast<int*>(&part[0][0]);
+    const int h0 = ((int)blockIdx.x - 1) * heads_per_group, h1 = min(BH, h0 + heads_per_group);
+    if (blockIdx.x == 0) order_group<true>(counts, order, BH, 0, BH, Tn, long_list, hist, at);
+    else order_group<false>(counts, order, BH, h0, h1, Tn, long_list, hist, at);
     return;
   }
-  const int slices = d * d / 256 + 1, id = blockIdx.x - groups, bh = id / slices, x = id % slices;
+  const int slices = d * d / 256 + 1, id = blockIdx.x - groups - 1, bh = id / slices, x = id % slices;
   if (x + 1 < slices) sum_slots<S>(dh + (size_t)bh * Tm * d * d, dh_total + (size_t)bh * d * d, Tm, d * d, 256 * x, part);
   else sum_slots<float>(dz + (size_t)bh * Tm * d, dz_total + (size_t)bh * d, Tm, d, 0, part);
 }
@@ -268,13 +310,17 @@ hipError_t launch_bwd_totals(const Shape& s, const BwdArgs& a, hipStream_t strea
   const size_t fit = ((size_t)(s.bf16 ? 48 : 192) << 20) / head_bytes;
   const int heads = fit < 1 ? 1 : fit > (size_t)s.BH ? s.BH : (int)fit;
   const int groups = (s.BH + heads - 1) / heads;
-  const dim3 grid((unsigned)(groups + s.BH * (s.d * s.d / 256 + 1)));
+  // Length from which a list counts as long, see order_group: thrice the mean, and a sixth of what each of about 512
+  // workgroups at a time has to do in all.  One group is sorted as a whole: none.
+  const int64_t entries = (int64_t)s.Tm * s.k, share = entries * s.BH / (512 * 6);
+  const int long_list = groups == 1 ? kNoLongList : (int)(3 * entries / s.Tn > share ? 3 * entries / s.Tn : share);
+  const dim3 grid((unsigned)(1 + groups + s.BH * (s.d * s.d / 256 + 1)));
   if (s.bf16)
     bwd_totals_kernel<uint16_t><<<grid, 256, 0, stream>>>((const uint16_t*)a.dh, a.dz, a.dh_total, a.dz_total, a.col_cnt, a.order,
-                                                          groups, heads, s.BH, s.Tm, s.Tn, s.d);
+                                                          groups, heads, long_list, s.BH, s.Tm, s.Tn, s.d);
   else
     bwd_totals_kernel<float><<<grid, 256, 0, stream>>>((const float*)a.dh, a.dz, a.dh_total, a.dz_total, a.col_cnt, a.order, groups,
-                                                       heads, s.BH, s.Tm, s.Tn, s.d);
+                                                       heads, long_list, s.BH, s.Tm, s.Tn, s.d);
   return hipGetLastError();
 }
 

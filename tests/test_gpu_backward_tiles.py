@@ -20,6 +20,39 @@ CASES = [
 ]
 
 
+# key blocks in several groups of heads (over 48 MB of gathered rows each), lists far longer than the mean among them
+GROUPS = W.TINY.replace(name="bf16-d128-two-groups", B=1, H=3, grid=(21, 30, 52), d=128, block_q=128, dtype="bf16", topk_frac=0.03)
+
+
+def test_backward_over_groups_of_heads():
+    """Heads are independent: a call over several order groups gives bit for bit what calls over single heads give."""
+    import torch
+    from paper_2602_12675_amd import api
+    w, gen = GROUPS, torch.Generator(device="cuda").manual_seed(5)
+    q, k, v, go = (torch.randn((1, w.H, w.N, w.d), generator=gen, device="cuda") for _ in range(4))
+    k[:, :, : w.N // 10] *= 3.0                      # a few key blocks that most query blocks select
+    k[:, :, : w.N // 10] += q.mean(2, keepdim=True) * 40
+    q, k, v, go = (x.bfloat16() for x in (q, k, v, go))
+    rw = torch.randn((2, w.d, w.d), generator=gen, device="cuda") / w.d ** 0.5
+    al = torch.rand((w.H,), generator=gen, device="cuda")
+
+    def grads(h0, h1):
+        p = api.make_params(1, h1 - h0, w.N, w.d, w.block_q, w.block_kv, w.topk_frac, dtype=api.SLA2_BF16,
+                            flags=api.SLA2_FLAG_SAVE_FOR_BACKWARD)
+        a = [x[:, h0:h1].contiguous() for x in (q, k, v)]
+        out, ws, da = torch.empty_like(a[0]), api.alloc_workspace(p), torch.empty((h1 - h0,), device="cuda")
+        d = [torch.empty_like(x) for x in a]
+        api.sla2_forward(p, *a, rw, al[h0:h1].contiguous(), out, workspace=ws)
+        api.sla2_backward(p, *a, al[h0:h1].contiguous(), go[:, h0:h1].contiguous(), *d, da, ws)
+        torch.cuda.synchronize()
+        return d + [da]
+
+    whole = grads(0, w.H)
+    for h in range(w.H):
+        for name, x, y in zip(("dq", "dk", "dv", "dalpha"), whole, grads(h, h + 1)):
+            assert torch.equal(x[:, h : h + 1] if x.dim() == 4 else x[h : h + 1], y), (name, h)
+
+
 @pytest.mark.parametrize("w", CASES, ids=lambda w: w.name)
 def test_backward_at_tile_edges(w):
     check(w, True, True)
