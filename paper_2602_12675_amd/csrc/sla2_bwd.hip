@@ -86,12 +86,12 @@ __global__ __launch_bounds__(256) void bwd_columns_kernel(const int32_t* __restr
 // ---------------------------------------------------------------------------------------------
 // The order in which bwd_kv takes the key blocks.  Its work on a key block is proportional to the length of the block's
 // list, which varies a lot (mean 7.5, a tenth above 15, longest 91 on 12 heads of 512 key blocks): a long list that starts
-// late runs on alone.  So the long ones go first, longest first over all heads.  The others follow
-// head by head, in groups of heads whose gathered rows fit the caches, again longest first: neighbouring key blocks are
-// selected by the same query blocks, whose rows they gather.  Every head is cut into 8 runs of consecutive key blocks, one
-// per XCD (workgroup p runs on XCD p % 8).  With the groups alone, the last group's long lists kept a fifth of the CUs
-// waiting (in a model of the 64 places of each XCD the last one ended at 1.54 times the mean, at twice the mean now at 1.09, at thrice at 1.12): training step on
-// those lists 1,747 -> 1,691 us, 20 heads of 75,600 tokens 11.86 -> 11.60 ms.
+// late runs on alone.  So the long ones go first, longest first over all heads.  The others follow head by head, in groups
+// of heads whose gathered rows fit the caches, again longest first: neighbouring key blocks are selected by the same query
+// blocks, whose rows they gather.  Every head is cut into 8 runs of consecutive key blocks, one per XCD (workgroup p runs
+// on XCD p % 8).  With the groups alone the long lists of the last one kept a fifth of the CUs waiting (in a model of the
+// 64 places of each XCD the last one ended at 1.54 times the mean, with the long lists first at 1.12): training step on
+// such lists 1,747 -> 1,691 us, on 20 heads of 75,600 tokens 11.86 -> 11.60 ms.
 // The order decides when a block is worked on, never what is summed.
 //
 // One call writes the places of one group: the long lists of all heads (h0 = 0, h1 = BH, LONG) or the others of heads
