@@ -775,7 +775,14 @@ __global__ __launch_bounds__(256, 2) void bwd_kv_mfma_kernel(
     }
     float dzj = (tid < D && !all_selected) ? dz_total[(size_t)bh * D + tid] : 0.f;
     if (tid < D)
-      for (int l = l0; l < last; l++) dzj -= dz_in[((size_t)bh * Tm + ci[l]) * D + tid];
+      for (int l = l0; l < last; l += 4) {             // four at a time on their way: one by one each costs a round trip
+        float z[4];
+#pragma unroll
+        for (int x = 0; x < 4; x++) z[x] = dz_in[((size_t)bh * Tm + ci[min(l + x, last - 1)]) * D + tid];
+#pragma unroll
+        for (int x = 0; x < 4; x++)
+          if (l + x < last) dzj -= z[x];
+      }
     if (tid < D) dzs[tid] = dzj;
   }
   // K_j -> K^phi_j = exp(K - colmean(K) - lnZ) in the fragment registers (keys past the end: 0); one
