@@ -96,11 +96,6 @@ __device__ __forceinline__ float swap_halves_sum(float x) {
   const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
   return __builtin_bit_cast(float, (unsigned)r[0]) + __builtin_bit_cast(float, (unsigned)r[1]);
 }
-// lanes 32..63 take the values of lanes 0..31
-__device__ __forceinline__ float low_half(float x) {
-  const unsigned u = __builtin_bit_cast(unsigned, x);
-  return __builtin_bit_cast(float, (unsigned)__builtin_amdgcn_permlane32_swap(u, u, false, false)[0]);
-}
 // Maximum over the wave, on every lane; vector instructions only.
 __device__ __forceinline__ float wave_max(float x) {
   auto dpp = [&](auto ctrl) {

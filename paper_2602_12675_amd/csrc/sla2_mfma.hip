@@ -309,7 +309,7 @@ template <int D, int BQ, int MODE> constexpr bool kPipelined = MODE != kDenseBf1
 // (bf16); codes of the first V tile (when V is quantised for the second product); two K tiles (bf16, or 8-bit codes);
 // codes of the second V tile - all in the layouts the load unit fills directly.  Before the loop the query rows of
 // waves 0, 1 pass through the place of the second V tile and those of waves 2, 3 through that from the second K tile on.
-// Epilogue, over the same memory: H_i^T as bf16 [D][D+8], the output tile [BQ][D+8] and Z_i as three bf16 rows.  At
+// Epilogue, over the same memory: H_i^T as bf16 [D][D+8], the output tile [BQ][D+8] and Z_i as fp32.  At
 // d = 128 the loop takes at most 80 KB: two workgroups a CU.
 template <int D, int BQ, bool FP8, bool VQ, bool PIPE> struct AttnSmem {
   static constexpr int kLd = TileGeom<D>::kLd, NW = BQ / 32;
@@ -323,8 +323,8 @@ template <int D, int BQ, bool FP8, bool VQ, bool PIPE> struct AttnSmem {
   static constexpr int kVq1Off = kKOff + 2 * kKBytes;
   static constexpr int kTiles = kVq1Off + kVqBytes, kQEnd = kKOff + kKBytes + (NW - 2) * kQBytes;
   static constexpr int kLoopBytes = kTiles > kQEnd ? kTiles : kQEnd;
-  static constexpr int kZsOff = (D + BQ) * kLd * 2;                 // bf16 [3][D+8]: Z_i (epilogue)
-  static constexpr int kEpiBytes = kZsOff + 3 * kLd * 2;
+  static constexpr int kZsOff = (D + BQ) * kLd * 2;                 // fp32 [D]: Z_i (epilogue)
+  static constexpr int kEpiBytes = kZsOff + D * 4;
   static constexpr int kBytes = kLoopBytes > kEpiBytes ? kLoopBytes : kEpiBytes;
   __device__ static unsigned q_rows(int w) { return w < 2 ? kVOff + kVBytes + w * kQBytes : kKOff + kKBytes + (w - 2) * kQBytes; }
 };
@@ -581,9 +581,11 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
   constexpr float kPShift = FP8 ? 8.f : 0.f;
   const float c0 = kLog2e * rsqrtf((float)D);        // scores are used as S * log2(e) / sqrt(d)
 
-  // Q^phi = softmax_d(Q) of this lane's row, in the place of its fragments - without its normaliser, which cancels
-  // between Q^phi H_i and Q^phi Z_i.  In pieces: the pipelined loop has them between the products of its last tile.
+  // Q^phi = softmax_d(Q) of this lane's row, in the order of its fragments - without its normaliser, which cancels
+  // between Q^phi H_i and Q^phi Z_i.  In fp32: the numerator takes it rounded to bf16, the denominator as it is.
+  // In pieces: the pipelined loop has them between the products of its last tile.
   // (The low-bit modes dropped the bf16 rows after quantisation; they come back through LDS, q_again.)
+  f32x4 qx[DENSE ? 1 : KS][2];
   float qm = -INFINITY;
   auto q_max = [&]() {
 #pragma unroll
@@ -594,8 +596,11 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
   };
   auto q_exp = [&](int ks) {
 #pragma unroll
-    for (int e = 0; e < 8; e++) qf[ks][e] = (__bf16)fast_exp2((float)qf[ks][e] * kLog2e - qm);
-    settle(qf[ks]);
+    for (int x = 0; x < 2; x++) {
+#pragma unroll
+      for (int e = 0; e < 4; e++) qx[ks][x][e] = fast_exp2((float)qf[ks][4 * x + e] * kLog2e - qm);
+      settle(qx[ks][x]);
+    }
   };
   // where the query rows go at the last tile (V in vbuf(buf)): both K tiles and the other V tile are done with
   auto q_again = [&](int buf) { return w < 2 ? vbuf(buf ^ 1) + w * SM::kQBytes : kbuf(0) + (w - 2) * SM::kQBytes; };
@@ -1305,7 +1310,7 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
   }
   uint16_t* ht = reinterpret_cast<uint16_t*>(smem);  // H_i^T as bf16 [e][c], row stride LD
   uint16_t* os = ht + D * LD;                        // output tile [BQ][LD]
-  uint16_t* zs = reinterpret_cast<uint16_t*>(smem + SM::kZsOff);   // Z_i: three bf16 rows whose sum it is
+  float* zs = reinterpret_cast<float*>(smem + SM::kZsOff);   // Z_i
   f32x16 lacc[ET];
   float inv_den = 0.f;
   if constexpr (!DENSE) {
@@ -1327,36 +1332,41 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
       // zsel holds the same sum on both lane halves (each half added z_j of channel l % 32)
       if (g == 0 && nt0 == 0) {
         const int c = 32 * (mt0 + a) + lane;
-        float z = -zsel[a];
+        const float z = -zsel[a];
         if (z_save != nullptr) z_save[((size_t)bh * Tm + i) * D + c] = z;
-#pragma unroll
-        for (int r = 0; r < 3; r++) {
-          const __bf16 part = (__bf16)z;
-          *reinterpret_cast<__bf16*>(zs + r * LD + c) = part;
-          z -= (float)part;
-        }
+        zs[c] = z;
       }
     }
     __syncthreads();                                 // H_i^T and Z_i visible
-    // O_l^T = H_i^T Q^phi^T, and Q^phi Z_i as one product more (rows 0, 1, 2 of its result; the other rows repeat row 2).
-    // The accumulators take turns, so that no product waits for the one before it.
-    f32x16 dacc;
+    // Q^phi Z_i in fp32 from the un-rounded Q^phi, in four sums side by side, and O_l^T = H_i^T Q^phi^T.  The denominator
+    // is no matrix product (Z_i in three bf16 parts against the fragments of Q^phi): that rounds the weights, each by up
+    // to 2^-8 of itself, and where they round to one side the output is off by as much (1.2e-3 in the mean on rows of
+    // two weights).  It would save nothing either: 8 products of 33 cycles against 64 multiply-adds of 4, and the times
+    // of both are equal (12 heads of 32,760 tokens, FP8: 443.6 us with the product, 443.0 us so).
+    f32x4 den4 = {0.f, 0.f, 0.f, 0.f};
+    const float* zlane = zs + 8 * g;
 #pragma unroll
-    for (int e = 0; e < 16; e++) dacc[e] = 0.f;
+    for (int ks = 0; ks < KS; ks++)
+#pragma unroll
+      for (int x = 0; x < 2; x++) {
+        const f32x4 z4 = *reinterpret_cast<const f32x4*>(zlane + 16 * ks + 4 * x);
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+          den4[e] += qx[ks][x][e] * z4[e];
+          qf[ks][4 * x + e] = (__bf16)qx[ks][x][e];
+        }
+      }
+    const float den = swap_halves_sum((den4[0] + den4[1]) + (den4[2] + den4[3]));
 #pragma unroll
     for (int et = 0; et < ET; et++)
 #pragma unroll
       for (int e = 0; e < 16; e++) lacc[et][e] = 0.f;
-    const uint16_t* zrow = zs + min(lane % 32, 2) * LD + 8 * g;
     const uint16_t* hrow = ht + (lane % 32) * LD + 8 * g;
 #pragma unroll
-    for (int ks = 0; ks < KS; ks++) {
-      dacc = mfma_bf16(*reinterpret_cast<const bf16x8*>(zrow + 16 * ks), qf[ks], dacc);
+    for (int ks = 0; ks < KS; ks++)
 #pragma unroll
       for (int et = 0; et < ET; et++)
         lacc[et] = mfma_bf16(*reinterpret_cast<const bf16x8*>(hrow + 32 * et * LD + 16 * ks), qf[ks], lacc[et]);
-    }
-    const float den = low_half((dacc[0] + dacc[1]) + dacc[2]);
     inv_den = ksel >= Tn ? 0.f : 1.f / den;          // every block selected: nothing left for the linear branch
   }
   // ---- mix (Eq. 13), transpose through LDS, coalesced store ----
