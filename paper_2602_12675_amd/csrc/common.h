@@ -112,6 +112,14 @@ __device__ __forceinline__ float wave_max(float x) {
   return swap_halves_max(x);
 }
 
+// What the lanes of a wave wrote to LDS ahead of it the other lanes of that wave may read behind it, and the other way
+// round.  LDS serves the accesses of a wave in order, so this is no instruction: it tells the compiler to keep them so.
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Where sla2_forward keeps O^s, O^l ([BH, N, d], element type of out; o_l may be null on its own) and
 // L ([BH, N]) for the backward pass; all null when nothing is to be kept.  With them goes the state of the linear branch
 // per query block: Z_i [BH, T_m, d] and H_i, bf16 tensors: H_i^T as bf16 [BH, T_m, d(e), d(c)], fp32 tensors: H_i as fp32

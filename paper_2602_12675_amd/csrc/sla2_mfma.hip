@@ -1385,7 +1385,7 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
       }
       *reinterpret_cast<bf16x4*>(os + qrow * LD + 32 * et + 8 * v4 + 4 * g) = pk;
     }
-  // (a wave stores the 32 rows that it wrote itself: no barrier)
+  wave_lds_fence();                                  // (a wave stores the 32 rows that it wrote itself: no barrier)
   uint16_t* oh = out + head_offset(sout, bh, H) + (size_t)row0 * sout.n;
 #pragma unroll
   for (int x = 0; x < D / 16; x++) {
@@ -1406,6 +1406,7 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
     // O^s (and O^l, if asked for) on its own ([BH, N, d] contiguous), kept for the backward pass: same
     // route through the transposing tile as the mixed output
     for (int which = 0; which < (o_l_save != nullptr ? 2 : 1); which++) {
+      wave_lds_fence();                              // the tile has been read out
 #pragma unroll
       for (int et = 0; et < ET; et++)
 #pragma unroll
@@ -1421,6 +1422,7 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
           }
           *reinterpret_cast<bf16x4*>(os + qrow * LD + 32 * et + 8 * v4 + 4 * g) = pk;
         }
+      wave_lds_fence();
       uint16_t* dst = (which == 0 ? o_s_save : o_l_save) + ((size_t)bh * N + row0) * D;
 #pragma unroll
       for (int x = 0; x < D / 16; x++) {
