@@ -73,16 +73,6 @@ void make_layout(const Shape& s, sla2_ws_layout* L);
 __device__ __forceinline__ float bf16_bits_to_f32(uint16_t b) {
   return __builtin_bit_cast(float, (uint32_t)b << 16);
 }
-// round to nearest even; inputs are finite
-__device__ __forceinline__ uint16_t f32_to_bf16_bits(float f) {
-  uint32_t u = __builtin_bit_cast(uint32_t, f);
-  u += 0x7FFFu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
-}
-__device__ __forceinline__ float load_elem(const float* p, size_t i) { return p[i]; }
-__device__ __forceinline__ float load_elem(const uint16_t* p, size_t i) { return bf16_bits_to_f32(p[i]); }
-__device__ __forceinline__ void store_elem(float* p, size_t i, float v) { p[i] = v; }
-__device__ __forceinline__ void store_elem(uint16_t* p, size_t i, float v) { p[i] = f32_to_bf16_bits(v); }
 
 // lanes l and l ^ 32 combine their values through v_permlane32_swap (a vector instruction: no LDS round trip,
 // whose latency a wave that has the vector unit to itself would sit out)

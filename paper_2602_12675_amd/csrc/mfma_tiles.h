@@ -344,12 +344,6 @@ __device__ __forceinline__ void settle(T& x) { asm volatile("" : "+v"(x)); }
 // LDS counter retires in order, so "at most n outstanding" settles everything but the n youngest.
 // Another benefit: a tracked transposing read is treated as a possible alias of the tile transfer
 // in flight and is preceded by vmcnt(0).
-template <int OFF1>   // 8 bytes at addr and 8 bytes at addr + 512 OFF1
-__device__ __forceinline__ u32x4 lds_read2_untracked(unsigned addr) {
-  u32x4 r;
-  asm volatile("ds_read2st64_b64 %0, %1 offset1:%2" : "=v"(r) : "v"(addr), "n"(OFF1));
-  return r;
-}
 template <int OFF>    // 16 bytes at addr + OFF
 __device__ __forceinline__ u32x4 lds_read16_untracked(unsigned addr) {
   u32x4 r;

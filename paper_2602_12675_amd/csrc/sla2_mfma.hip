@@ -360,10 +360,8 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
   // the layout without bank conflicts where the tile transfers of a workgroup's waves allow it
   typedef typename std::conditional<PIPE && D == 128 && NW == 4, SwizzledLayoutB<128>, SwizzledLayout<D>>::type SL;
   typedef SwizzledLayout8<D> SL8;
-  // Loads and LDS reads of the main loop are issued untracked and waited for by count (see
-  // load_untracked).  The one exception is the shape with the highest register pressure, bf16
-  // operands at d = 128 with two workgroups per CU: holding reads in flight costs registers it
-  // does not have, and the compiler-tracked form is the faster one there.
+  // Loads and LDS reads are issued untracked and waited for by count (see load_untracked): in the pipelined loop always,
+  // in the plain one in the low-bit modes.  Its two bf16 forms leave them to the compiler.
   constexpr bool kManual = FP8;
   // global -> LDS transfers (1 KB each) a wave issues per tile: K in bf16 or 8-bit codes, V with its codes, K^phi fragments
   constexpr int kKOps = kTileTokens * D * (FP8 ? 1 : 2) / 1024 / NW;
@@ -605,6 +603,83 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
   // where the query rows go at the last tile (V in vbuf(buf)): both K tiles and the other V tile are done with
   auto q_again = [&](int buf) { return w < 2 ? vbuf(buf ^ 1) + w * SM::kQBytes : kbuf(0) + (w - 2) * SM::kQBytes; };
 
+  // S^T = K Q^T on the 8-bit codes, two 32-key halves; ka: this lane's first operand in the K tile.  The callbacks run
+  // behind the operand reads and behind the matrix instructions.
+  auto low_bit_scores = [&](unsigned ka, f32x16 (&sacc)[2], auto behind_reads, auto behind_products) {
+    if constexpr (INT8) {
+      // 32-deep integer products (v_mfma_i32_32x32x32_i8: lane l holds row l % 32, contraction indices
+      // 16 (l / 32) + 0..15): the operand of (step ks4, key half mt) is 16 consecutive codes of key row
+      // 32 mt + l % 32 - one 16-byte read at (address of step 0) ^ 32 ks4 in the pair-swizzled tile.
+      // Sums of 128 products of codes stay below 2^21: exact in the int32 accumulator and in fp32.
+      constexpr int KS4 = D / 32;
+      u32x4 kq[KS4][2];
+#pragma unroll
+      for (int ks4 = 0; ks4 < KS4; ks4++) {
+        kq[ks4][0] = lds_read16_untracked<0>(ka ^ (32u * ks4));
+        kq[ks4][1] = lds_read16_untracked<32 * D>(ka ^ (32u * ks4));
+      }
+      behind_reads();
+      i32x16 iacc[2];
+#pragma unroll
+      for (int mt = 0; mt < 2; mt++)
+#pragma unroll
+        for (int e = 0; e < 16; e++) iacc[mt][e] = 0;
+#pragma unroll
+      for (int ks4 = 0; ks4 < KS4; ks4++)
+#pragma unroll
+        for (int mt = 0; mt < 2; mt++) {
+          wait_lgkmcnt(2 * (KS4 - 1 - ks4) + 1 - mt);
+          settle(kq[ks4][mt]);
+          const i32x4 a = __builtin_bit_cast(i32x4, kq[ks4][mt]);
+          const i32x4 b = {(int)(unsigned)((unsigned long)qf8[2 * ks4]), (int)(unsigned)((unsigned long)qf8[2 * ks4] >> 32),
+                           (int)(unsigned)((unsigned long)qf8[2 * ks4 + 1]), (int)(unsigned)((unsigned long)qf8[2 * ks4 + 1] >> 32)};
+          iacc[mt] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, iacc[mt], 0, 0, 0);
+        }
+      behind_products();
+#pragma unroll
+      for (int mt = 0; mt < 2; mt++)
+#pragma unroll
+        for (int e = 0; e < 16; e++) sacc[mt][e] = (float)iacc[mt][e];
+    } else {
+      // 64-deep products: the operand of (step ks2, key half mt) is 32 consecutive codes of key row
+      // 32 mt + l % 32, two 16-byte reads.  The swizzle is an XOR on the pair bits of the address,
+      // so step ks2 sits at (address of step 0) ^ 64 ks2; all reads of a tile are issued up front.
+      static_assert(D % 64 == 0, "the FP8 product consumes the head dimension 64 at a time");
+      constexpr int KS2 = D / 64;
+      u32x4 klo[KS2][2], khi[KS2][2];
+#pragma unroll
+      for (int ks2 = 0; ks2 < KS2; ks2++) {
+        klo[ks2][0] = lds_read16_untracked<0>(ka ^ (64u * ks2));
+        khi[ks2][0] = lds_read16_untracked<16>(ka ^ (64u * ks2));
+        klo[ks2][1] = lds_read16_untracked<32 * D>(ka ^ (64u * ks2));
+        khi[ks2][1] = lds_read16_untracked<32 * D + 16>(ka ^ (64u * ks2));
+      }
+      behind_reads();
+#pragma unroll
+      for (int mt = 0; mt < 2; mt++)
+#pragma unroll
+        for (int e = 0; e < 16; e++) sacc[mt][e] = 0.f;
+#pragma unroll
+      for (int ks2 = 0; ks2 < KS2; ks2++)
+#pragma unroll
+        for (int mt = 0; mt < 2; mt++) {
+          wait_lgkmcnt(2 * (2 * (KS2 - 1 - ks2) + 1 - mt));
+          settle(klo[ks2][mt]);
+          settle(khi[ks2][mt]);
+          const u32x4 lo = klo[ks2][mt], hi = khi[ks2][mt];
+          const i32x8 a = {(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3], (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
+          i32x8 b;
+#pragma unroll
+          for (int x = 0; x < 4; x++) {
+            b[2 * x] = (int)(unsigned)((unsigned long)qf8[4 * ks2 + x]);
+            b[2 * x + 1] = (int)(unsigned)((unsigned long)qf8[4 * ks2 + x] >> 32);
+          }
+          sacc[mt] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, sacc[mt], 0, 0, 0, 0, 0, 0);   // e4m3 x e4m3, no scales
+        }
+      behind_products();
+    }
+  };
+
   if constexpr (PIPE) {
     // The pipelined loop.  Pass s forms S of tile s + 1, then runs the products of tile s, P V and K^phi^T V, with the
     // softmax of tile s + 1 in between them: a matrix product holds the issue port of its SIMD for about a third of its
@@ -632,73 +707,8 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
     // S^T = K Q^T of the tile in kbuf(buf), two 32-key halves
     auto scores = [&](int buf) {
       const unsigned ka = kbuf(buf) + k_lane;
-      if constexpr (INT8) {
-        // 32-deep integer products (v_mfma_i32_32x32x32_i8: lane l holds row l % 32, contraction indices
-        // 16 (l / 32) + 0..15): the operand of (step ks4, key half mt) is 16 consecutive codes of key row
-        // 32 mt + l % 32 - one 16-byte read at (address of step 0) ^ 32 ks4 in the pair-swizzled tile.
-        // Sums of 128 products of codes stay below 2^21: exact in the int32 accumulator and in fp32.
-        constexpr int KS4 = D / 32;
-        u32x4 kq[KS4][2];
-#pragma unroll
-        for (int ks4 = 0; ks4 < KS4; ks4++) {
-          kq[ks4][0] = lds_read16_untracked<0>(ka ^ (32u * ks4));
-          kq[ks4][1] = lds_read16_untracked<32 * D>(ka ^ (32u * ks4));
-        }
-        i32x16 iacc[2];
-#pragma unroll
-        for (int mt = 0; mt < 2; mt++)
-#pragma unroll
-          for (int e = 0; e < 16; e++) iacc[mt][e] = 0;
-#pragma unroll
-        for (int ks4 = 0; ks4 < KS4; ks4++)
-#pragma unroll
-          for (int mt = 0; mt < 2; mt++) {
-            wait_lgkmcnt(2 * (KS4 - 1 - ks4) + 1 - mt);
-            settle(kq[ks4][mt]);
-            const i32x4 a = __builtin_bit_cast(i32x4, kq[ks4][mt]);
-            const i32x4 b = {(int)(unsigned)((unsigned long)qf8[2 * ks4]), (int)(unsigned)((unsigned long)qf8[2 * ks4] >> 32),
-                             (int)(unsigned)((unsigned long)qf8[2 * ks4 + 1]), (int)(unsigned)((unsigned long)qf8[2 * ks4 + 1] >> 32)};
-            iacc[mt] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, iacc[mt], 0, 0, 0);
-          }
-#pragma unroll
-        for (int mt = 0; mt < 2; mt++)
-#pragma unroll
-          for (int e = 0; e < 16; e++) sacc[mt][e] = (float)iacc[mt][e];
-      } else if constexpr (FP8) {
-        // 64-deep products: the operand of (step ks2, key half mt) is 32 consecutive codes of key row
-        // 32 mt + l % 32, two 16-byte reads.  The swizzle is an XOR on the pair bits of the address,
-        // so step ks2 sits at (address of step 0) ^ 64 ks2; all reads of a tile are issued up front.
-        static_assert(D % 64 == 0, "the FP8 product consumes the head dimension 64 at a time");
-        constexpr int KS2 = D / 64;
-        u32x4 klo[KS2][2], khi[KS2][2];
-#pragma unroll
-        for (int ks2 = 0; ks2 < KS2; ks2++) {
-          klo[ks2][0] = lds_read16_untracked<0>(ka ^ (64u * ks2));
-          khi[ks2][0] = lds_read16_untracked<16>(ka ^ (64u * ks2));
-          klo[ks2][1] = lds_read16_untracked<32 * D>(ka ^ (64u * ks2));
-          khi[ks2][1] = lds_read16_untracked<32 * D + 16>(ka ^ (64u * ks2));
-        }
-#pragma unroll
-        for (int mt = 0; mt < 2; mt++)
-#pragma unroll
-          for (int e = 0; e < 16; e++) sacc[mt][e] = 0.f;
-#pragma unroll
-        for (int ks2 = 0; ks2 < KS2; ks2++)
-#pragma unroll
-          for (int mt = 0; mt < 2; mt++) {
-            wait_lgkmcnt(2 * (2 * (KS2 - 1 - ks2) + 1 - mt));
-            settle(klo[ks2][mt]);
-            settle(khi[ks2][mt]);
-            const u32x4 lo = klo[ks2][mt], hi = khi[ks2][mt];
-            const i32x8 a = {(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3], (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
-            i32x8 b;
-#pragma unroll
-            for (int x = 0; x < 4; x++) {
-              b[2 * x] = (int)(unsigned)((unsigned long)qf8[4 * ks2 + x]);
-              b[2 * x + 1] = (int)(unsigned)((unsigned long)qf8[4 * ks2 + x] >> 32);
-            }
-            sacc[mt] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, sacc[mt], 0, 0, 0, 0, 0, 0);   // e4m3 x e4m3, no scales
-          }
+      if constexpr (FP8) {
+        low_bit_scores(ka, sacc, [] {}, [] {});
       } else {
         // the operand of (step ks, key half mt): 16 bytes of key row 32 mt + l % 32, step ks at (address of step 0) ^ 32 ks
         constexpr int kItems = 2 * KS, kAhead = 3, kSlots = kAhead + 1;
@@ -1013,8 +1023,7 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
       // tile's data are placed inside the score product: the fragment loads behind its operand reads, the
       // next tile's transfer behind its matrix instructions - some hundred instructions that otherwise
       // stand in front of it, on a wave whose progress is bound by its own chain of dependent steps.
-      constexpr bool kRequestsInsideScores = kManual;
-      if constexpr (!kRequestsInsideScores) {
+      if constexpr (!kManual) {
         state_loads();
         next_tile();
       }
@@ -1025,82 +1034,14 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
       if constexpr (!DENSE) __builtin_amdgcn_s_setprio(2);
       // ---- S^T = K Q^T (keys x query rows), two 32-key halves ----
       f32x16 sacc[2];
-#pragma unroll
-      for (int mt = 0; mt < 2; mt++)
-#pragma unroll
-        for (int e = 0; e < 16; e++) sacc[mt][e] = 0.f;
-      if constexpr (INT8) {
-        // 32-deep integer products (v_mfma_i32_32x32x32_i8: lane l holds row l % 32, contraction indices
-        // 16 (l / 32) + 0..15): the operand of (step ks4, key half mt) is 16 consecutive codes of key row
-        // 32 mt + l % 32 - one 16-byte read at (address of step 0) ^ 32 ks4 in the pair-swizzled tile.
-        // Sums of 128 products of codes stay below 2^21: exact in the int32 accumulator and in fp32.
-        constexpr int KS4 = D / 32;
-        const unsigned ka = kbuf(buf) + SL8::offset(lane % 32, 16 * g);
-        u32x4 kq[KS4][2];
-#pragma unroll
-        for (int ks4 = 0; ks4 < KS4; ks4++) {
-          kq[ks4][0] = lds_read16_untracked<0>(ka ^ (32u * ks4));
-          kq[ks4][1] = lds_read16_untracked<32 * D>(ka ^ (32u * ks4));
-        }
-        if constexpr (kRequestsInsideScores) state_loads();
-        i32x16 iacc[2];
-#pragma unroll
-        for (int mt = 0; mt < 2; mt++)
-#pragma unroll
-          for (int e = 0; e < 16; e++) iacc[mt][e] = 0;
-#pragma unroll
-        for (int ks4 = 0; ks4 < KS4; ks4++)
-#pragma unroll
-          for (int mt = 0; mt < 2; mt++) {
-            wait_lgkmcnt(2 * (KS4 - 1 - ks4) + 1 - mt);
-            settle(kq[ks4][mt]);
-            const u32x4 kk = kq[ks4][mt];
-            const i32x4 a = {(int)kk[0], (int)kk[1], (int)kk[2], (int)kk[3]};
-            const i32x4 b = {(int)(unsigned)((unsigned long)qf8[2 * ks4]), (int)(unsigned)((unsigned long)qf8[2 * ks4] >> 32),
-                             (int)(unsigned)((unsigned long)qf8[2 * ks4 + 1]), (int)(unsigned)((unsigned long)qf8[2 * ks4 + 1] >> 32)};
-            iacc[mt] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, iacc[mt], 0, 0, 0);
-          }
-        if constexpr (kRequestsInsideScores) next_tile();
-#pragma unroll
-        for (int mt = 0; mt < 2; mt++)
-#pragma unroll
-          for (int e = 0; e < 16; e++) sacc[mt][e] = (float)iacc[mt][e];
-      } else if constexpr (FP8) {
-        // 64-deep products: the operand of (step ks2, key half mt) is 32 consecutive codes of key row
-        // 32 mt + l % 32, two 16-byte reads.  The swizzle is an XOR on the pair bits of the address,
-        // so step ks2 sits at (address of step 0) ^ 64 ks2; all reads of a tile are issued up front.
-        static_assert(D % 64 == 0, "the FP8 product consumes the head dimension 64 at a time");
-        constexpr int KS2 = D / 64;
-        const unsigned ka = kbuf(buf) + SL8::offset(lane % 32, 32 * g);
-        u32x4 klo[KS2][2], khi[KS2][2];
-#pragma unroll
-        for (int ks2 = 0; ks2 < KS2; ks2++) {
-          klo[ks2][0] = lds_read16_untracked<0>(ka ^ (64u * ks2));
-          khi[ks2][0] = lds_read16_untracked<16>(ka ^ (64u * ks2));
-          klo[ks2][1] = lds_read16_untracked<32 * D>(ka ^ (64u * ks2));
-          khi[ks2][1] = lds_read16_untracked<32 * D + 16>(ka ^ (64u * ks2));
-        }
-        if constexpr (kRequestsInsideScores) state_loads();
-#pragma unroll
-        for (int ks2 = 0; ks2 < KS2; ks2++)
-#pragma unroll
-          for (int mt = 0; mt < 2; mt++) {
-            wait_lgkmcnt(2 * (2 * (KS2 - 1 - ks2) + 1 - mt));
-            settle(klo[ks2][mt]);
-            settle(khi[ks2][mt]);
-            const u32x4 lo = klo[ks2][mt], hi = khi[ks2][mt];
-            const i32x8 a = {(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3], (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
-            i32x8 b;
-#pragma unroll
-            for (int x = 0; x < 4; x++) {
-              b[2 * x] = (int)(unsigned)((unsigned long)qf8[4 * ks2 + x]);
-              b[2 * x + 1] = (int)(unsigned)((unsigned long)qf8[4 * ks2 + x] >> 32);
-            }
-            sacc[mt] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, sacc[mt], 0, 0, 0, 0, 0, 0);   // e4m3 x e4m3, no scales
-          }
-        if constexpr (kRequestsInsideScores) next_tile();
+      if constexpr (FP8) {
+        low_bit_scores(kbuf(buf) + SL8::offset(lane % 32, (INT8 ? 16 : 32) * g), sacc, state_loads, next_tile);
       } else {
         const uint16_t* kt = reinterpret_cast<const uint16_t*>(smem + SM::kKOff + buf * SM::kKBytes);
+#pragma unroll
+        for (int mt = 0; mt < 2; mt++)
+#pragma unroll
+          for (int e = 0; e < 16; e++) sacc[mt][e] = 0.f;
 #pragma unroll
         for (int ks = 0; ks < KS; ks++)
 #pragma unroll
@@ -1214,64 +1155,14 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
         }
       }
       // ---- O^T += V^T P^T, and the d x d state of this block: h += K^phi^T V ----
-      // address of this lane's first transposing read of fragment (ks = 0, et = 0), cf. read_tr4
-      const unsigned va = lds_address(vt + SL::offset(4 * g + (lane % 16) / 4, 16 * ((lane / 16) % 2) + 4 * (lane % 4)));
-      unsigned vaddr[ET];                              // one address per 32-channel tile; the token step is an immediate
-#pragma unroll
-      for (int et = 0; et < ET; et++) vaddr[et] = va ^ (64u * et);
-      u32x2 vlo[3], vhi[3];
 #pragma unroll
       for (int ks = 0; ks < kTileTokens / 16; ks++) {
-        if constexpr (!kManual && (HS::kNtw == ET || DENSE)) {   // every V fragment feeds both products
 #pragma unroll
-          for (int et = 0; et < ET; et++) {
-            bf16x8 vf = v_fragment<SL>(vt, ks, 32 * et, lane);
-            if constexpr (!FP8V) oacc[et] = mfma_bf16(vf, pf[ks], oacc[et]);
-            if constexpr (!DENSE) {
-#pragma unroll
-              for (int a = 0; a < HS::kMtw; a++) hacc[a][et] = mfma_bf16(kphi[a][ks], vf, hacc[a][et]);
-            }
-          }
-        } else if constexpr (HS::kNtw == ET || DENSE) {       // the same with the reads kept in flight
-          // fragment f = ks ET + et: two transposing reads (tokens 16 ks + 4 g.. and + 8), kept kVAhead
-          // fragments ahead of the products.  Row swizzle and lane terms are the same for every
-          // fragment of a lane, so fragment (ks, et) sits at (va ^ 64 et) + 32 D ks.
-          constexpr int kVAhead = FP8 ? 2 : 1, kFrags = (kTileTokens / 16) * ET;
-          if (ks == 0) {
-#pragma unroll
-            for (int f = 0; f < kVAhead; f++) {
-              vlo[f] = lds_read_tr_untracked_at<8 * D * 2>(vaddr[f % ET], 2 * (f / ET));
-              vhi[f] = lds_read_tr_untracked_at<8 * D * 2>(vaddr[f % ET], 2 * (f / ET) + 1);
-            }
-          }
-#pragma unroll
-          for (int et = 0; et < ET; et++) {
-            const int f = ks * ET + et;
-            if (f + kVAhead < kFrags) {
-              const int f2 = f + kVAhead;
-              vlo[f2 % (kVAhead + 1)] = lds_read_tr_untracked_at<8 * D * 2>(vaddr[f2 % ET], 2 * (f2 / ET));
-              vhi[f2 % (kVAhead + 1)] = lds_read_tr_untracked_at<8 * D * 2>(vaddr[f2 % ET], 2 * (f2 / ET) + 1);
-            }
-            const int left = kFrags - 1 - f;
-            wait_lgkmcnt(2 * (left < kVAhead ? left : kVAhead));
-            u32x2& lo = vlo[f % (kVAhead + 1)];
-            u32x2& hi = vhi[f % (kVAhead + 1)];
-            settle(lo);
-            settle(hi);
-            const u32x4 v4 = {lo[0], lo[1], hi[0], hi[1]};
-            const bf16x8 vf = __builtin_bit_cast(bf16x8, v4);
-            if constexpr (!FP8V) oacc[et] = mfma_bf16(vf, pf[ks], oacc[et]);
-            if constexpr (!DENSE) {
-#pragma unroll
-              for (int a = 0; a < HS::kMtw; a++) hacc[a][et] = mfma_bf16(kphi[a][ks], vf, hacc[a][et]);
-            }
-          }
-        } else {
-#pragma unroll
-          for (int et = 0; et < ET; et++) {
-            bf16x8 vf = v_fragment<SL>(vt, ks, 32 * et, lane);
-            if constexpr (!FP8V) oacc[et] = mfma_bf16(vf, pf[ks], oacc[et]);
-          }
+        for (int et = 0; et < ET; et++) {
+          bf16x8 vf = v_fragment<SL>(vt, ks, 32 * et, lane);
+          if constexpr (!FP8V) oacc[et] = mfma_bf16(vf, pf[ks], oacc[et]);
+        }
+        if constexpr (!DENSE) {
 #pragma unroll
           for (int b = 0; b < HS::kNtw; b++) {
             bf16x8 vf = v_fragment<SL>(vt, ks, 32 * (nt0 + b), lane);
