@@ -155,10 +155,15 @@ hipError_t launch_bwd_kv_f32(const Shape& s, const BwdArgs& a, hipStream_t strea
 // k_frag [BH, T_n, d]: the block sums of K once more, as the operand fragments of the router's products: for each group of
 // 16 key blocks of a head (the last group of a head: of the n it has) [d / 8][4][16 (n)][2], entry (j, g, b, x) being channel
 // 8 j + 2 g + x of block b.  The router reads whole kilobytes; from the row-major sums each of the 16 lanes of a quarter
-// wave would touch a cache line of its own, which took 60 cycles a load.
+// wave would touch a cache line of its own, which took 60 cycles a load.  k_sum may be null: only callers of the library
+// read it (sla2_ws_layout.k_sum).
+__host__ __device__ __forceinline__ size_t k_frag_offset(int bh, int j, int c, int Tn, int d) {
+  const int first = j - j % 16, n = Tn - first < 16 ? Tn - first : 16;
+  return ((size_t)bh * Tn + first) * d + (c / 2 * n + j % 16) * 2 + c % 2;
+}
 hipError_t launch_block_sums(const Shape& s, const void* q, const void* k, const float* router_w, double* q_sum,
                              double* k_sum, double* k_frag, double* router_m, hipStream_t stream);
-hipError_t launch_router_topk(const Shape& s, const double* q_sum, const double* k_sum, const double* k_frag, const double* router_m,
+hipError_t launch_router_topk(const Shape& s, const double* q_sum, const double* k_frag, const double* router_m,
                               int32_t* block_idx, double* k_mean, hipStream_t stream);
 hipError_t launch_router_soft(const Shape& s, const double* q_sum, const double* k_frag, const double* router_m,
                               float* mask, double tau, hipStream_t stream);

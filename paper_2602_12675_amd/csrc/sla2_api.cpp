@@ -207,7 +207,7 @@ static int run_router(const Shape& s, const sla2_ws_layout& L, const void* q, co
   if (SLA2_STAGE(SLA2_STAGE_BLOCK_SUMS, launch_block_sums(s, q, k, router_w, q_sum, k_sum, k_frag, router_m, st)) !=
       hipSuccess)
     return SLA2_EHIP;
-  if (SLA2_STAGE(SLA2_STAGE_TOPK, launch_router_topk(s, q_sum, k_sum, k_frag, router_m, at<int32_t>(ws, L.block_idx),
+  if (SLA2_STAGE(SLA2_STAGE_TOPK, launch_router_topk(s, q_sum, k_frag, router_m, at<int32_t>(ws, L.block_idx),
                                                      at<double>(ws, L.k_mean), st)) != hipSuccess)
     return SLA2_EHIP;
   return SLA2_OK;

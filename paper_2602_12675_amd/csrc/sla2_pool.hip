@@ -93,7 +93,6 @@ __global__ __launch_bounds__(256) void block_sums_kernel(const T* __restrict__ q
   if (bh >= bh_count || t >= (is_k ? Tn : Tm)) return;
   const int b = is_k ? bk : bq;
   const T* x = (is_k ? k : q) + head_offset(sin, bh, H);
-  double* out = (is_k ? k_sum + ((size_t)bh * Tn + t) * d : q_sum + ((size_t)bh * Tm + t) * d);
 
   const int tpr = d / EPL;                   // threads per row
   const int rpp = 256 / tpr;                 // rows per pass
@@ -144,10 +143,11 @@ __global__ __launch_bounds__(256) void block_sums_kernel(const T* __restrict__ q
   if (threadIdx.x < d) {
     double s = 0.0;
     for (int gi = 0; gi < rpp; gi++) s += red[gi * d + threadIdx.x];
-    out[threadIdx.x] = s;
     if (is_k) {
-      const int first = t - t % 16, n = min(16, Tn - first);
-      k_frag[((size_t)bh * Tn + first) * d + (threadIdx.x / 2 * n + t % 16) * 2 + threadIdx.x % 2] = s;
+      if (k_sum != nullptr) k_sum[((size_t)bh * Tn + t) * d + threadIdx.x] = s;
+      k_frag[k_frag_offset(bh, t, threadIdx.x, Tn, d)] = s;
+    } else {
+      q_sum[((size_t)bh * Tm + t) * d + threadIdx.x] = s;
     }
   }
 }

@@ -25,7 +25,6 @@ __device__ __forceinline__ int wave_count(bool pred) { return __builtin_popcount
 
 template <int D, int SLOTS>
 __global__ __launch_bounds__(1024) void router_topk_kernel(const double* __restrict__ q_sum,
-                                                           const double* __restrict__ k_sum,
                                                            const double* __restrict__ k_frag,
                                                            const double* __restrict__ router_m,
                                                            int32_t* __restrict__ block_idx,
@@ -42,7 +41,7 @@ __global__ __launch_bounds__(1024) void router_topk_kernel(const double* __restr
     const int g = threadIdx.x / 16;
     double s = 0.0;
     if (smooth)
-      for (int j = g; j < Tn; j += 64) s += k_sum[((size_t)bh * Tn + j) * D + c];
+      for (int j = g; j < Tn; j += 64) s += k_frag[k_frag_offset(bh, j, c, Tn, D)];
     red[threadIdx.x] = s;
     __syncthreads();
     if (threadIdx.x < 16) {
@@ -188,7 +187,7 @@ __global__ __launch_bounds__(1024) void router_topk_kernel(const double* __restr
   }
 }
 
-hipError_t launch_router_topk(const Shape& s, const double* q_sum, const double* k_sum, const double* k_frag, const double* router_m,
+hipError_t launch_router_topk(const Shape& s, const double* q_sum, const double* k_frag, const double* router_m,
                               int32_t* block_idx, double* k_mean, hipStream_t stream) {
   const int row_tiles = (s.Tm + kRouterRows - 1) / kRouterRows;
   const int topk_blocks = s.k > 0 ? s.BH * row_tiles : 0;        // k = 0: only the colmean workgroups run
@@ -201,7 +200,7 @@ hipError_t launch_router_topk(const Shape& s, const double* q_sum, const double*
         e != hipSuccess)                                                                                         \
       return e;                                                                                                  \
     router_topk_kernel<DD, SS><<<grid, 1024, router_lds_bytes<DD>(), stream>>>(                                  \
-        q_sum, k_sum, k_frag, router_m, block_idx, k_mean, s.H, s.N, s.bq, s.bk, s.Tm, s.Tn, s.k, s.w_per_head ? 1 : 0,   \
+        q_sum, k_frag, router_m, block_idx, k_mean, s.H, s.N, s.bq, s.bk, s.Tm, s.Tn, s.k, s.w_per_head ? 1 : 0,   \
         topk_blocks, s.smooth ? 1 : 0);                                                                          \
   }
   if (s.d == 128) {

@@ -1,7 +1,8 @@
 // sla2_router_static: the router entry point for callers that cannot allocate device memory and have
 // no workspace to hand over (code under graph capture, tight serving loops).  Same kernels as
 // sla2_router; their intermediate arrays - fp64 block sums of Q and K, colmean(K), the folded router
-// matrix - live in a file-scope device array instead of a caller's workspace.
+// matrix - live in a file-scope device array instead of a caller's workspace.  The sums of K are kept once, as the operand
+// fragments the router reads; nobody looks at them in this array.
 #include <atomic>
 
 #include "common.h"
@@ -10,7 +11,7 @@ namespace sla2 {
 namespace {
 
 static_assert(SLA2_STATIC_SCRATCH_BYTES % 256 == 0, "scratch size must keep the carve-up aligned");
-static __device__ __align__(256) unsigned char scratch[2 * (size_t)SLA2_STATIC_SCRATCH_BYTES];   // the workspace arrays | k_frag
+static __device__ __align__(256) unsigned char scratch[SLA2_STATIC_SCRATCH_BYTES];
 
 // Each GPU holds its own copy of the array at its own address: the address is looked up once per
 // device, with that device current, and only this pointer is ever handed to a kernel (the array's name
@@ -53,13 +54,12 @@ extern "C" int sla2_router_static(const sla2_params* params, const void* q, cons
   unsigned char* base = nullptr;
   if (scratch_of_current_device(&base) != hipSuccess) return SLA2_EHIP;
   double* q_sum = (double*)(base + L.q_sum);
-  double* k_sum = (double*)(base + L.k_sum);
+  double* k_frag = (double*)(base + L.k_sum);          // as many bytes
   double* k_mean = (double*)(base + L.k_mean);
   double* router_m = (double*)(base + L.router_m);
-  double* k_frag = (double*)(base + SLA2_STATIC_SCRATCH_BYTES);   // as many bytes as k_sum
   hipStream_t st = (hipStream_t)hip_stream;
   // every array is written in full before it is read: nothing has to start at zero
-  if (launch_block_sums(s, q, k, router_w, q_sum, k_sum, k_frag, router_m, st) != hipSuccess) return SLA2_EHIP;
-  if (launch_router_topk(s, q_sum, k_sum, k_frag, router_m, block_idx, k_mean, st) != hipSuccess) return SLA2_EHIP;
+  if (launch_block_sums(s, q, k, router_w, q_sum, nullptr, k_frag, router_m, st) != hipSuccess) return SLA2_EHIP;
+  if (launch_router_topk(s, q_sum, k_frag, router_m, block_idx, k_mean, st) != hipSuccess) return SLA2_EHIP;
   return SLA2_OK;
 }
