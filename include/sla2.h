@@ -120,7 +120,9 @@ typedef struct sla2_ws_layout {
                        byte 32 g + b of a row holds token 32 (b / 16) + 8 ((b % 16) / 4) + 4 g + b % 4
                        (g = 0, 1; b = 0..31).  SLA2_QUANT_FP8_V only; tokens >= N are 0 */
   size_t v_scale;   /* float  [BH, T_n]      dequantisation scale of each V block (SLA2_QUANT_FP8_V only) */
-  size_t partial;   /* scratch for per-chunk partial sums of h and z */
+  size_t partial;   /* scratch, two lives: double [BH, T_n, d], k_sum once more as the operand fragments of the router
+                       (written by the pooling step, dead after the router); then the per-chunk partial sums of h and z and,
+                       behind them, -h_total as accumulator fragments (bf16 path only) */
   /* with SLA2_FLAG_SAVE_FOR_BACKWARD only (0 bytes otherwise): */
   size_t o_s;       /* dtype  [BH, N, d]     sparse-branch output O^s, before the mix of Eq. 13   (input of Alg. 3) */
   size_t o_l;       /* dtype  [BH, N, d]     linear-branch output O^l (fp32 tensors only; 0 bytes for bf16 tensors, whose
@@ -210,7 +212,10 @@ int sla2_forward(const sla2_params* params, const void* q, const void* k, const 
  *                    each other or any input (they may be the slices of one packed [B, N, x, H, d]
  *                    buffer: interleaved, sharing no element)
  *   dalpha           DEVICE float [H] or [H, T_m] (alpha_per_block), written
- * Deterministic: fixed summation orders; the only atomic is an order-independent OR on LDS words.  Errors as sla2_forward; SLA2_EINVAL without the flag. */
+ * Deterministic: every sum has a fixed order, so two calls on the same data give the same bits.  The atomics are
+ * integer ones on LDS: an order-independent OR, and counters that give key blocks of equally long lists their places
+ * in the order of work - which may differ between two calls and decides when a block is worked on, never what is added.
+ * Errors as sla2_forward; SLA2_EINVAL without the flag. */
 int sla2_backward(const sla2_params* params, const void* q, const void* k, const void* v, const float* alpha,
                   const void* dout, void* dq, void* dk, void* dv, float* dalpha,
                   void* workspace, size_t workspace_bytes, void* hip_stream);

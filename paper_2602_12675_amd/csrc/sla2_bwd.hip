@@ -3,7 +3,7 @@
 // High precision throughout, from the original Q, K, V (Sec. 5: the backward pass is never quantised).
 //
 // This file holds the launch sequence and the small kernels every tensor type shares (deterministic: no float atomics,
-// fixed summation orders); the two heavy steps are in sla2_bwd_mfma.hip (bf16 tensors) and sla2_bwd_f32.hip.
+// fixed summation orders; only the order of work on key blocks of equally long lists is open); the two heavy steps are in sla2_bwd_mfma.hip (bf16 tensors) and sla2_bwd_f32.hip.
 //
 //   bwd_columns    for every key block j the ascending list of query blocks i with M_c[i, j] = 1
 //   (bwd_q)        per query block: D^s, D^l, d alpha parts, dQ, dH_i, dZ_i

@@ -44,8 +44,9 @@ template <int D, int NW> struct HSplit {
 
 // K^phi of one key block is stored as the A-operand fragments of the product K^phi^T V:
 // [block][mt = channel tile][ks = 16-token step][lane][8 bf16], lane l holding channel 32 mt + l % 32
-// and the 8 tokens of (ks, l / 32) in token order - 1 KB per fragment, read back with one
-// coalesced 16-byte load per lane and no LDS traffic.
+// and the 8 tokens of (ks, l / 32) in token order - 1 KB per fragment, 16 consecutive
+// bytes a lane: the attention kernel's pipelined loop brings it into the wave's own part of LDS, its plain loop into
+// registers.
 template <int D>
 __device__ __forceinline__ size_t kphi_offset(size_t block, int mt, int ks, int lane) {
   return (((block * (D / 32) + mt) * (kTileTokens / 16) + ks) * kWave + lane) * 8;

@@ -192,7 +192,13 @@ hipError_t launch_router_topk(const Shape& s, const double* q_sum, const double*
   const int row_tiles = (s.Tm + kRouterRows - 1) / kRouterRows;
   const int topk_blocks = s.k > 0 ? s.BH * row_tiles : 0;        // k = 0: only the colmean workgroups run
   dim3 grid((unsigned)(topk_blocks + s.BH * (s.d / 16)));
-  const int rounds = (s.Tn + kColsPerRound - 1) / kColsPerRound;     // <= 8 (kMaxKeyBlocks)
+  // Three register classes by rounds of 256 key blocks: up to 2 (8 slots a lane), up to 5 (20), up to 8 (32; kMaxKeyBlocks).
+  // Up to 8 slots the operands are read 8 at a time, else 4 (router_scores.h): the slots take the registers.  The middle
+  // class ends at 5 rounds for the 1,025 to 1,280 key blocks that 20 slots serve better than 32: 12 heads, d = 128, 128-row
+  // blocks: 1,182 key blocks 112 -> 86 us; 16 heads, d = 64, 64-row blocks: 200 -> 140 us.  The price is paid by 513 to 1,024
+  // key blocks, which 16 slots with reads 8 at a time serve in 3 to 6 % less (d = 128: 640 key blocks 34.2 against 35.4 us,
+  // 1,024 75.0 against 78.0; 40 heads 198 against 207) to 10 % less (d = 64: 57.4 against 63.7, 96.2 against 105.5).
+  const int rounds = (s.Tn + kColsPerRound - 1) / kColsPerRound;
 #define SLA2_TOPK(DD, SS)                                                                                        \
   {                                                                                                              \
     static OncePerDevice once;                                                                                   \

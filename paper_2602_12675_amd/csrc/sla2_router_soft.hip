@@ -151,7 +151,10 @@ __global__ __launch_bounds__(1024) void router_soft_kernel(const double* __restr
 hipError_t launch_router_soft(const Shape& s, const double* q_sum, const double* k_frag, const double* router_m,
                               float* mask, double tau, hipStream_t stream) {
   const dim3 grid((unsigned)(s.BH * ((s.Tm + kRouterRows - 1) / kRouterRows)));
-  const int rounds = (s.Tn + kColsPerRound - 1) / kColsPerRound;     // <= 8 (kMaxKeyBlocks)
+  // The register classes of the hard selection (sla2_router.hip).  Measured on the same shapes, 20 slots against 32 at 1,182
+  // key blocks: 117 against 131 us (d = 128), 216 against 245 (d = 64); against 16 with reads 8 at a time at 640 and 1,024:
+  // 40.6 against 41.1 and 98.9 against 100.2 us (d = 128), 84.9 against 81.0 and 149.8 against 142.0 (d = 64).
+  const int rounds = (s.Tn + kColsPerRound - 1) / kColsPerRound;
 #define SLA2_SOFT(DD, SS)                                                                                            \
   {                                                                                                                  \
     static OncePerDevice once;                                                                                       \
