@@ -302,9 +302,20 @@ __device__ __forceinline__ unsigned lane_again() {
 enum AttnMode { kSparseBf16 = 0, kSparseFp8 = 1, kDenseBf16 = 2, kSparseInt8 = 3, kSparseFp8V = 4 };
 
 
-// Whether the main loop is the pipelined one (see there); the others keep the plain loop: the dense comparator, and
+// Shapes whose main loop can be the pipelined one (see there).  The others keep the plain loop: the dense comparator, and
 // d = 64 with 128-row blocks, whose waves own single tiles of the d x d state.
 template <int D, int BQ, int MODE> constexpr bool kPipelined = MODE != kDenseBf16 && HSplit<D, BQ / 32>::kNtw == D / 32;
+// Shapes that take the plain loop for long lists over many key blocks all the same, and the line: k T_n above 2,500.  A tile
+// is short there (d = 64, 64-row blocks, FP8 scores) and the loop bound by its transfers, so it lives on what the workgroups
+// of a head find in the L2 of their XCD; that takes workgroups in step with each other, and the pipelined loop holds them
+// there less well: 12 heads of 32,760 tokens, k = 61, L2 hits 45 % against 72 % (FP8), 42 % against 66 % (FP8 with V), bytes
+// through the fabric 4.4 against 2.2 GB and 5.5 against 3.2.  Attention kernel, pipelined / plain, us at k T_n:
+//            480 (6,144 tokens)  1,920 (12,288)  3,328 (16,384)  4,416 (12,288)  5,120 (32,760)  31,232 (32,760)
+//   FP8      51.0 / 52.7         76.3 / 77.1     115.8 / 112.8   143.7 / 143.9   137.2 / 130.9   693 / 634
+//   with V   55.5 / 57.6         85.5 / 87.5     126.3 / 125.4   153.8 / 149.0   156.4 / 147.8   789 / 619
+// The other shapes do not lose with it: INT8 stays within 4 % either way, bf16 gains up to 10 %, d = 128 gains throughout.
+template <int D, int BQ, int MODE> constexpr bool kPlainToo = D == 64 && BQ == 64 && (MODE == kSparseFp8 || MODE == kSparseFp8V);
+constexpr int kPipelinedTiles = 2500;
 
 // LDS carve-up.  Loop, in this order: K^phi fragments of one tile, each wave's own (pipelined loop only); two V tiles
 // (bf16); codes of the first V tile (when V is quantised for the second product); two K tiles (bf16, or 8-bit codes);
@@ -335,7 +346,7 @@ template <int D, int BQ, bool FP8, bool VQ, bool PIPE> struct AttnSmem {
 // two waves hold half of the d x d state each; 3 for d = 64 with 128-row blocks, where the accumulators are small
 // enough for 168 registers (measured on a 32,760-token d = 64 input: 6 % faster in FP8 mode, 10 % in bf16 mode;
 // with 64-row blocks three waves gain nothing).
-template <int D, int BQ, int MODE>
+template <int D, int BQ, int MODE, bool PIPE>
 __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ == 128) ? 3 : 2) void attn_mfma_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const double* __restrict__ k_mean, const uint16_t* __restrict__ k_phi, const float* __restrict__ z_blocks,
@@ -356,7 +367,6 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
   constexpr int KS = D / 16;            // contraction steps over the head dimension
   constexpr int ET = D / 32;            // 32-wide tiles over the head dimension
   typedef HSplit<D, NW> HS;
-  constexpr bool PIPE = kPipelined<D, BQ, MODE>;
   typedef AttnSmem<D, BQ, FP8, FP8V, PIPE> SM;
   // the layout without bank conflicts where the tile transfers of a workgroup's waves allow it
   typedef typename std::conditional<PIPE && D == 128 && NW == 4, SwizzledLayoutB<128>, SwizzledLayout<D>>::type SL;
@@ -1156,19 +1166,47 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
         }
       }
       // ---- O^T += V^T P^T, and the d x d state of this block: h += K^phi^T V ----
+      if constexpr (!DENSE && HS::kNtw == ET) {        // every V fragment feeds both products
+        // fragment f = ks ET + et: two transposing reads (tokens 16 ks + 4 g.. and + 8), kept kVAhead fragments ahead of the
+        // products; (ks, et) sits at (address of the first) ^ 64 et, + 32 D ks.
+        constexpr int kVAhead = 2, kFrags = (kTileTokens / 16) * ET;
+        const unsigned va = lds_address(vt + SL::offset(4 * g + (lane % 16) / 4, 16 * ((lane / 16) % 2) + 4 * (lane % 4)));
+        u32x2 vlo[kVAhead + 1], vhi[kVAhead + 1];
+        auto read_v = [&](int f) {
+          vlo[f % (kVAhead + 1)] = lds_read_tr_untracked_at<16 * D>(va ^ (64u * (f % ET)), 2 * (f / ET));
+          vhi[f % (kVAhead + 1)] = lds_read_tr_untracked_at<16 * D>(va ^ (64u * (f % ET)), 2 * (f / ET) + 1);
+        };
 #pragma unroll
-      for (int ks = 0; ks < kTileTokens / 16; ks++) {
+        for (int f = 0; f < kVAhead; f++) read_v(f);
 #pragma unroll
-        for (int et = 0; et < ET; et++) {
-          bf16x8 vf = v_fragment<SL>(vt, ks, 32 * et, lane);
+        for (int f = 0; f < kFrags; f++) {
+          if (f + kVAhead < kFrags) read_v(f + kVAhead);
+          const int ks = f / ET, et = f % ET, left = kFrags - 1 - f;
+          wait_lgkmcnt(2 * (left < kVAhead ? left : kVAhead));
+          u32x2 &lo = vlo[f % (kVAhead + 1)], &hi = vhi[f % (kVAhead + 1)];
+          settle(lo);
+          settle(hi);
+          const u32x4 v4 = {lo[0], lo[1], hi[0], hi[1]};
+          const bf16x8 vf = __builtin_bit_cast(bf16x8, v4);
           if constexpr (!FP8V) oacc[et] = mfma_bf16(vf, pf[ks], oacc[et]);
+#pragma unroll
+          for (int a = 0; a < HS::kMtw; a++) hacc[a][et] = mfma_bf16(kphi[a][ks], vf, hacc[a][et]);
         }
-        if constexpr (!DENSE) {
+      } else {
 #pragma unroll
-          for (int b = 0; b < HS::kNtw; b++) {
-            bf16x8 vf = v_fragment<SL>(vt, ks, 32 * (nt0 + b), lane);
+        for (int ks = 0; ks < kTileTokens / 16; ks++) {
 #pragma unroll
-            for (int a = 0; a < HS::kMtw; a++) hacc[a][b] = mfma_bf16(kphi[a][ks], vf, hacc[a][b]);
+          for (int et = 0; et < ET; et++) {
+            bf16x8 vf = v_fragment<SL>(vt, ks, 32 * et, lane);
+            if constexpr (!FP8V) oacc[et] = mfma_bf16(vf, pf[ks], oacc[et]);
+          }
+          if constexpr (!DENSE) {
+#pragma unroll
+            for (int b = 0; b < HS::kNtw; b++) {
+              bf16x8 vf = v_fragment<SL>(vt, ks, 32 * (nt0 + b), lane);
+#pragma unroll
+              for (int a = 0; a < HS::kMtw; a++) hacc[a][b] = mfma_bf16(kphi[a][ks], vf, hacc[a][b]);
+            }
           }
         }
       }
@@ -1363,20 +1401,26 @@ struct AttnArgs {
   SavedForBackward sv;
 };
 
-template <int D, int BQ, int MODE>
-static hipError_t launch_attn_t(const Shape& s, const AttnArgs& a, hipStream_t stream) {
-  constexpr int smem = AttnSmem<D, BQ, MODE == kSparseFp8 || MODE == kSparseInt8 || MODE == kSparseFp8V, MODE == kSparseFp8V,
-                                kPipelined<D, BQ, MODE>>::kBytes;
+template <int D, int BQ, int MODE, bool PIPE>
+static hipError_t launch_attn_loop(const Shape& s, const AttnArgs& a, hipStream_t stream) {
+  constexpr int smem = AttnSmem<D, BQ, MODE == kSparseFp8 || MODE == kSparseInt8 || MODE == kSparseFp8V, MODE == kSparseFp8V, PIPE>::kBytes;
   static OncePerDevice once;
-  if (hipError_t e = allow_dynamic_lds(once, (const void*)attn_mfma_kernel<D, BQ, MODE>, smem); e != hipSuccess) return e;
+  if (hipError_t e = allow_dynamic_lds(once, (const void*)attn_mfma_kernel<D, BQ, MODE, PIPE>, smem); e != hipSuccess) return e;
   const int Tm = (s.N + BQ - 1) / BQ;
   const int grid = ((Tm + kXcds - 1) / kXcds) * kXcds * s.BH;   // some workgroups of the last run of a head may have no block
-  attn_mfma_kernel<D, BQ, MODE><<<dim3((unsigned)grid), BQ * 2, smem, stream>>>(
+  attn_mfma_kernel<D, BQ, MODE, PIPE><<<dim3((unsigned)grid), BQ * 2, smem, stream>>>(
       a.q, a.k, a.v, a.k_mean, a.k_phi, a.z_blocks, a.k_fp8, a.k_scale, a.v_codes, a.v_scale, a.h_frag, a.z_total,
       a.block_idx, a.alpha,
       a.out, a.lse, (uint16_t*)a.sv.o_s, (uint16_t*)a.sv.o_l, a.sv.lse, (uint16_t*)a.sv.h_i, a.sv.z_i, s.sin, s.sout, s.H, s.N, Tm, s.Tn, s.k,
       s.alpha_per_block ? 1 : 0);
   return hipGetLastError();
+}
+
+template <int D, int BQ, int MODE>
+static hipError_t launch_attn_t(const Shape& s, const AttnArgs& a, hipStream_t stream) {
+  if constexpr (kPlainToo<D, BQ, MODE>)
+    if (s.k * s.Tn > kPipelinedTiles) return launch_attn_loop<D, BQ, MODE, false>(s, a, stream);   // below 2^22
+  return launch_attn_loop<D, BQ, MODE, kPipelined<D, BQ, MODE>>(s, a, stream);
 }
 
 hipError_t launch_attn_bf16(const Shape& s, const uint16_t* q, const uint16_t* k, const uint16_t* v,
