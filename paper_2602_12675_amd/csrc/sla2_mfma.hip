@@ -697,8 +697,10 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
     // time, and what fits into the rest - a wave's own vector instructions included - costs nothing (micro-benchmark: one
     // product alone 33 cycles, with four multiply-adds behind it 34).  P replaces its predecessor 16 tokens at a time,
     // right after the products that read it, so it takes no second set of registers.
-    // At d = 128 with 128-row blocks the kernel draws the card down to 1.6 GHz: what counts is work, not latency.  Measured
-    // on 12 heads of 32,760 tokens: bf16, 26 tiles a block 520 -> 480 us; FP8, 15 tiles 287 -> 276 us.
+    // Measured on 12 heads of 32,760 tokens, d = 128, 128-row blocks: bf16, 26 tiles a block 520 -> 480 us; FP8, 15 tiles
+    // 287 -> 276 us.  The clock falls as the loop gets denser and the launch longer: 2.1 GHz over that FP8 launch, 1.8 over
+    // the bf16 one, 1.65 over 4.7 ms on 40 heads of 75,600 tokens (GRBM_GUI_ACTIVE over the launch): there work counts, not
+    // latency.
     // Transfers, all global -> LDS: K of tile s + 2 and V of tile s + 1 are requested at the top of pass s, into places
     // read for the last time before the barrier above, and have a whole pass to land; the K^phi fragments of tile s + 1
     // are requested one by one as those of tile s leave the wave's part of LDS.  Counts: requests at the top are older
