@@ -407,7 +407,8 @@ def main():
         note = "peak = dense bf16 MFMA"
     roofline = {"kernel": "attn_mfma (sparse + linear branch + mix)", "bound": "mfma", "achieved": round(achieved, 2),
                 "peak": round(peak, 1), "unit": "TFLOP/s", "frac": round(achieved / peak, 4),
-                "traffic": measured_traffic(w.name, w.quant), "traffic_source": traffic_source(), "ms": round(attn_ms, 4),
+                "traffic": measured_traffic(w.name, w.quant) if args.topk is None and args.block_q is None else None,
+                "traffic_source": traffic_source(), "ms": round(attn_ms, 4),
                 "launches_timed": prof["attn"][1],
                 "algorithmic_flops": attn_flops, "note": note}
     if "attn" in stages:
