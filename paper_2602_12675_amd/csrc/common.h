@@ -134,9 +134,13 @@ struct BwdArgs {
   const void* h_i;                           // as SavedForBackward
   const float* z_i;
   // scratch.  dh: one d x d slot per query block, element type of the tensors; lraw: L log2(e) per row (bf16: on the raw keys)
-  float *ds, *lraw, *dz, *dh_total, *dz_total, *colsum, *dk_mean, *dalpha_part;
+  float *ds, *lraw, *dz, *dh_total /* fp32 tensors */, *dz_total, *colsum, *dk_mean, *dalpha_part;
   void* dh;
   int32_t *col_ptr, *col_idx, *col_cnt;      // per key block the query blocks that selected it: offsets, lists, lengths
+  // bf16 tensors: the query blocks that did not, as a bit matrix (masked_sums.h), and dH_j, the sum of their dH_i, one d x d
+  // slot per key block in the element order of dh
+  uint32_t* col_bits;
+  void* dh_sum;
   int32_t* order;                            // [bwd_kv_grid] the key block (bh kMaxKeyBlocks + j, or -1) of every bwd_kv workgroup
 };
 inline size_t bwd_kv_grid(const Shape& s) { return (size_t)s.BH * kXcds * ((s.Tn + kXcds - 1) / kXcds); }

@@ -7,14 +7,15 @@
 //
 //   bwd_columns    for every key block j the ascending list of query blocks i with M_c[i, j] = 1
 //   (bwd_q)        per query block: D^s, D^l, d alpha parts, dQ, dH_i, dZ_i
-//   bwd_totals     dH_total = sum_i dH_i, dZ_total = sum_i dZ_i; the order in which bwd_kv takes the key blocks
+//   bwd_totals     dZ_total = sum_i dZ_i; bf16 tensors: per key block the sum of dH_i over the query blocks that did not select
+//                  it, fp32: dH_total = sum_i dH_i; the order in which bwd_kv takes the key blocks
 //   (bwd_kv)       per key block: dK', dV, column sums of dK'
 //   bwd_finish     colmean(dK'); d alpha summed over its parts
 //   bwd_unsmooth   dK = dK' - colmean(dK') (gradient of the smoothing)
 //
 // A launch costs 4.6 us however little it does, so what does not depend on each other shares one: this took eleven
 // launches before, 45 us of the 210 us of the pass on 32 heads of 4,096 tokens (d = 64).
-#include "common.h"
+#include "masked_sums.h"
 
 namespace sla2 {
 
@@ -22,10 +23,11 @@ namespace sla2 {
 // For every key block j of head bh: the ascending list of query blocks i with M_c[i, j] = 1, as offsets
 // col_ptr[bh][0..T_n] into col_idx[bh][.], and its length.  One workgroup per 64 columns of a head reads all index lists
 // of the head: entries of its own columns become bits (column x, bit i), those of earlier columns are counted - the
-// offset of its first list.  Then every thread writes out the bits of a few 32-row words at their places.
+// offset of its first list.  Then every thread writes out the bits of a few 32-row words at their places, and the complement
+// of the words (bits from T_m on: 0) as rows of the bit matrix, if there is one.
 __global__ __launch_bounds__(256) void bwd_columns_kernel(const int32_t* __restrict__ block_idx, int32_t* __restrict__ col_ptr,
-                                                          int32_t* __restrict__ col_idx, int32_t* __restrict__ counts, int Tm,
-                                                          int Tn, int ksel) {
+                                                          int32_t* __restrict__ col_idx, int32_t* __restrict__ counts,
+                                                          uint32_t* __restrict__ bits, int Tm, int Tn, int ksel) {
   extern __shared__ uint32_t words[];                 // [64][LW] bits, LW = W | 1 (odd: no bank conflicts down a column)
   const int W = (Tm + 31) / 32, LW = W | 1;           // W <= 64
   uint16_t* place = reinterpret_cast<uint16_t*>(words + 64 * LW);   // [64][LW] set bits of the column before the word
@@ -79,6 +81,14 @@ __global__ __launch_bounds__(256) void bwd_columns_kernel(const int32_t* __restr
     while (word) {
       out[at++] = 32 * y + __ffs(word) - 1;
       word &= word - 1u;
+    }
+  }
+  if (bits != nullptr) {
+    const int pitch = masked_pitch(Tn), rows = masked_words(Tm);
+    for (int x = tid; x < 64 * rows; x += 256) {
+      const int c = x % 64, y = x / 64, left = Tm - 32 * y;
+      const uint32_t open = left >= 32 ? ~0u : left > 0 ? (1u << left) - 1u : 0u;
+      bits[((size_t)bh * rows + y) * pitch + j0 + c] = y < W ? ~words[c * LW + y] & open : 0u;
     }
   }
 }
@@ -163,29 +173,19 @@ __device__ void order_group(const int32_t* __restrict__ counts, int32_t* __restr
 
 // dst[e] = sum over b < count of src[b][e] for the 256 entries from e0 on.  32 threads of 8 elements each, times 8
 // interleaved subsets of b that are combined in a fixed order.
-template <typename S>
-__device__ void sum_slots(const S* __restrict__ src, float* __restrict__ dst, int count, int len, int first, float (*part)[256]) {
+__device__ void sum_slots(const float* __restrict__ src, float* __restrict__ dst, int count, int len, int first, float (*part)[256]) {
   const int tid = threadIdx.x, col = tid % 32, sub = tid / 32;
   const int e0 = first + 8 * col;
   float acc[8];
 #pragma unroll
   for (int x = 0; x < 8; x++) acc[x] = 0.f;
   if (e0 < len) {
-    const S* p = src + e0;
+    const float* p = src + e0;
 #pragma unroll 8
     for (int b = sub; b < count; b += 8) {
-      float v[8];
-      if constexpr (sizeof(S) == 2) {
-        const bf16x8 x = *reinterpret_cast<const bf16x8*>(p + (size_t)b * len);
+      const f32x4 x0 = *reinterpret_cast<const f32x4*>(p + (size_t)b * len), x1 = *reinterpret_cast<const f32x4*>(p + (size_t)b * len + 4);
 #pragma unroll
-        for (int y = 0; y < 8; y++) v[y] = (float)x[y];
-      } else {
-        const f32x4 x0 = *reinterpret_cast<const f32x4*>(p + (size_t)b * len), x1 = *reinterpret_cast<const f32x4*>(p + (size_t)b * len + 4);
-#pragma unroll
-        for (int y = 0; y < 4; y++) { v[y] = x0[y]; v[4 + y] = x1[y]; }
-      }
-#pragma unroll
-      for (int y = 0; y < 8; y++) acc[y] += v[y];
+      for (int y = 0; y < 4; y++) { acc[y] += x0[y]; acc[4 + y] += x1[y]; }
     }
   }
 #pragma unroll
@@ -199,24 +199,49 @@ __device__ void sum_slots(const S* __restrict__ src, float* __restrict__ dst, in
   }
 }
 
-// workgroups: one of order_group for the long lists and `groups` for the others, then per head the 256-entry slices of dH_total and one for dZ_total
-template <typename S>
-__global__ __launch_bounds__(256) void bwd_totals_kernel(const S* __restrict__ dh, const float* __restrict__ dz,
-                                                         float* __restrict__ dh_total, float* __restrict__ dz_total,
-                                                         const int32_t* __restrict__ counts, int32_t* __restrict__ order,
-                                                         int groups, int heads_per_group, int long_list, int BH, int Tm, int Tn, int d) {
-  __shared__ float part[8][256];
+// workgroups: one of order_group for the long lists and `groups` for the others, then per head one for dZ_total, then the
+// sums of dH_i: fp32 tensors: per head the 256-entry slices of dH_total; bf16 tensors: the tiles of dH_j (masked_sums.h).
+// The tiles of one set of columns, which read the same dH_i, run next to each other on one XCD.
+struct TotalsArgs {
+  const void* dh;
+  const float* dz;
+  const uint32_t* bits;
+  void* dh_sum;                              // dH_total as fp32 or dH_j as bf16
+  float* dz_total;
+  const int32_t* counts;
+  int32_t* order;
+  int groups, heads_per_group, long_list, BH, Tm, Tn, d;
+};
+template <bool BF16>
+__global__ __launch_bounds__(256, 2) void bwd_totals_kernel(const TotalsArgs a) {
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   __shared__ int at[2 * kXcds];
-  if ((int)blockIdx.x <= groups) {
-    int* hist = reinterpret_cast<int*>(&part[0][0]);
-    const int h0 = ((int)blockIdx.x - 1) * heads_per_group, h1 = min(BH, h0 + heads_per_group);
-    if (blockIdx.x == 0) order_group<true>(counts, order, BH, 0, BH, Tn, long_list, hist, at);
-    else order_group<false>(counts, order, BH, h0, h1, Tn, long_list, hist, at);
+  float (*part)[256] = reinterpret_cast<float (*)[256]>(smem);
+  int id = blockIdx.x;
+  if (id <= a.groups) {
+    int* hist = reinterpret_cast<int*>(smem);
+    const int h0 = (id - 1) * a.heads_per_group, h1 = min(a.BH, h0 + a.heads_per_group);
+    if (id == 0) order_group<true>(a.counts, a.order, a.BH, 0, a.BH, a.Tn, a.long_list, hist, at);
+    else order_group<false>(a.counts, a.order, a.BH, h0, h1, a.Tn, a.long_list, hist, at);
     return;
   }
-  const int slices = d * d / 256 + 1, id = blockIdx.x - groups - 1, bh = id / slices, x = id % slices;
-  if (x + 1 < slices) sum_slots<S>(dh + (size_t)bh * Tm * d * d, dh_total + (size_t)bh * d * d, Tm, d * d, 256 * x, part);
-  else sum_slots<float>(dz + (size_t)bh * Tm * d, dz_total + (size_t)bh * d, Tm, d, 0, part);
+  id -= a.groups + 1;
+  if (id < a.BH) {
+    sum_slots(a.dz + (size_t)id * a.Tm * a.d, a.dz_total + (size_t)id * a.d, a.Tm, a.d, 0, part);
+    return;
+  }
+  id -= a.BH;
+  const int len = a.d * a.d;
+  if constexpr (BF16) {
+    const int x = blockIdx.x % kXcds, tiles = (a.Tn + kMaskedRows - 1) / kMaskedRows, sets = len / kMaskedCols;
+    const int y = id / kXcds, set = y / tiles * kXcds + x, bh = set / sets;
+    masked_sums_tile((const uint16_t*)a.dh + (size_t)bh * a.Tm * len, a.bits + (size_t)bh * masked_words(a.Tm) * masked_pitch(a.Tn),
+                     (uint16_t*)a.dh_sum + (size_t)bh * a.Tn * len, a.Tm, a.Tn, len, y % tiles * kMaskedRows,
+                     set % sets * kMaskedCols, smem);
+  } else {
+    const int slices = len / 256, bh = id / slices;
+    sum_slots((const float*)a.dh + (size_t)bh * a.Tm * len, (float*)a.dh_sum + (size_t)bh * len, a.Tm, len, 256 * (id % slices), part);
+  }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -292,7 +317,8 @@ hipError_t launch_bwd_lists(const Shape& s, const BwdArgs& a, hipStream_t stream
   // k = 0: every column is empty
   const size_t smem = (size_t)64 * (((s.Tm + 31) / 32) | 1) * (sizeof(uint32_t) + sizeof(uint16_t));   // at most 25 KB (T_m <= 2048)
   bwd_columns_kernel<<<dim3((unsigned)((s.Tn + 63) / 64), (unsigned)s.BH), 256, smem, stream>>>(a.block_idx, a.col_ptr, a.col_idx,
-                                                                                               a.col_cnt, s.Tm, s.Tn, s.k);
+                                                                                               a.col_cnt, s.bf16 ? a.col_bits : nullptr, s.Tm, s.Tn,
+                                                                                               s.k);
   return hipGetLastError();
 }
 
@@ -314,13 +340,17 @@ hipError_t launch_bwd_totals(const Shape& s, const BwdArgs& a, hipStream_t strea
   // workgroups at a time has to do in all.  One group is sorted as a whole: none.
   const int64_t entries = (int64_t)s.Tm * s.k, share = entries * s.BH / (512 * 6);
   const int long_list = groups == 1 ? kNoLongList : (int)(3 * entries / s.Tn > share ? 3 * entries / s.Tn : share);
-  const dim3 grid((unsigned)(1 + groups + s.BH * (s.d * s.d / 256 + 1)));
-  if (s.bf16)
-    bwd_totals_kernel<uint16_t><<<grid, 256, 0, stream>>>((const uint16_t*)a.dh, a.dz, a.dh_total, a.dz_total, a.col_cnt, a.order,
-                                                          groups, heads, long_list, s.BH, s.Tm, s.Tn, s.d);
-  else
-    bwd_totals_kernel<float><<<grid, 256, 0, stream>>>((const float*)a.dh, a.dz, a.dh_total, a.dz_total, a.col_cnt, a.order, groups,
-                                                       heads, long_list, s.BH, s.Tm, s.Tn, s.d);
+  const TotalsArgs t{a.dh, a.dz, a.col_bits, s.bf16 ? a.dh_sum : (void*)a.dh_total, a.dz_total, a.col_cnt, a.order,
+                     groups, heads, long_list, s.BH, s.Tm, s.Tn, s.d};
+  const int first = 1 + groups + s.BH, len = s.d * s.d;
+  if (s.bf16) {
+    static OncePerDevice once;
+    if (hipError_t e = allow_dynamic_lds(once, (const void*)bwd_totals_kernel<true>, kMaskedLds); e != hipSuccess) return e;
+    const int tiles = (s.Tn + kMaskedRows - 1) / kMaskedRows;           // sets of columns: a multiple of 8
+    bwd_totals_kernel<true><<<dim3((unsigned)(first + s.BH * (len / kMaskedCols) * tiles)), 256, kMaskedLds, stream>>>(t);
+  } else {
+    bwd_totals_kernel<false><<<dim3((unsigned)(first + s.BH * (len / 256))), 256, 8 * 256 * sizeof(float), stream>>>(t);
+  }
   return hipGetLastError();
 }
 

@@ -15,8 +15,8 @@
 //   bwd_kv_mfma  one workgroup per key block j, over the query blocks that selected it, 64 rows a
 //                step: here S = Q K^T (rows x keys), so that P and dS are already laid out as the
 //                B operands of dV^T += dO^T (alpha P), dK'^T += Q^T dS.  Then the linear branch:
-//                dH = dH_total - sum over those query blocks of dH_i (Alg. 3's M_c[i, j] = 0 sum, by
-//                complement), dK^phi^T = dH V^T + dZ 1^T, dV^T += dH^T K^phi^T,
+//                dH = the sum of dH_i over the other query blocks (Alg. 3's M_c[i, j] = 0 sum, a matrix product
+//                in bwd_totals), dK^phi^T = dH V^T + dZ 1^T, dV^T += dH^T K^phi^T,
 //                dK' += softmax-backward(dK^phi).
 #include <type_traits>
 
@@ -479,7 +479,7 @@ __global__ __launch_bounds__(256, 2) void bwd_kv_mfma_kernel(
     const uint16_t* __restrict__ dout, const float* __restrict__ lraw2, const float* __restrict__ ds_in,
     const double* __restrict__ k_mean, const float* __restrict__ k_stats, const int32_t* __restrict__ col_ptr, const int32_t* __restrict__ col_idx,
     const int32_t* __restrict__ order, const uint16_t* __restrict__ dh_in, const float* __restrict__ dz_in,
-    const float* __restrict__ dh_total, const float* __restrict__ dz_total, const float* __restrict__ alpha,
+    const float* __restrict__ dz_total, const float* __restrict__ alpha,
     uint16_t* __restrict__ dk, uint16_t* __restrict__ dv, float* __restrict__ colsum, Strides sin, Strides sout, int H,
     int N, int Tm, int Tn, int ksel, int alpha_per_block) {
   constexpr int NW = 4, NT = 256;
@@ -715,64 +715,24 @@ __global__ __launch_bounds__(256, 2) void bwd_kv_mfma_kernel(
   uint16_t* kpt = dht + D * LD;                                          // K^phi_j [key][c], row stride LD
   const bool all_selected = ksel >= Tn;
   {
-    // dH = dH_total - sum over the query blocks that selected j of dH_i (Alg. 3's M_c[i, j] = 0 sum), both in the order
-    // in which the query-side kernel leaves dH_i
-    // A thread takes PART 16-byte chunks of a slot at a time and two slots of the list per round: as many loads in
-    // flight as with all chunks of one slot, at half the accumulators (with all of them at once 54 registers of dK, dV
-    // and the operand fragments went to scratch memory here and came back).  With dH_i in whole kilobytes on both sides:
-    // 1,759 -> 1,679 us for a forward and backward pass on 12 heads of 32,760 tokens.
-    constexpr int NCH = D * D / 8 / NT, PART = NCH > 4 ? 4 : NCH;
-    static_assert(NCH % PART == 0, "whole parts");
-    const int last = all_selected ? l0 : l1;
-#pragma unroll 1
-    for (int n0 = 0; n0 < NCH; n0 += PART) {
-      const size_t at = (size_t)(tid + NT * n0) * 8;
-      float acc[PART][8];
+    // dH (Alg. 3's M_c[i, j] = 0 sum, from bwd_totals) in the order in which the query-side kernel leaves dH_i
+    constexpr int NCH = D * D / 8 / NT;
+    const uint16_t* src = dh_in + ((size_t)bh * Tn + j) * D * D + (size_t)tid * 8;
+    bf16x8 x[NCH];
 #pragma unroll
-      for (int n = 0; n < PART; n++) {
-        const float* tot = dh_total + (size_t)bh * D * D + at + NT * n * 8;
-        const f32x4 a = *reinterpret_cast<const f32x4*>(tot), b = *reinterpret_cast<const f32x4*>(tot + 4);
+    for (int n = 0; n < NCH; n++) x[n] = *reinterpret_cast<const bf16x8*>(src + NT * n * 8);
 #pragma unroll
-        for (int e = 0; e < 4; e++) { acc[n][e] = all_selected ? 0.f : a[e]; acc[n][4 + e] = all_selected ? 0.f : b[e]; }
-      }
-      auto take = [&](const bf16x8 (&x)[PART]) {
+    for (int n = 0; n < NCH; n++) {
+      const int idx = tid + NT * n, l = idx % kWave, half = idx / kWave % 2, t = idx / (2 * kWave);
+      uint16_t* dst = dht + (32 * (t / ET) + l % 32) * LD + 32 * (t % ET) + 16 * half + 4 * (l / 32);
 #pragma unroll
-        for (int n = 0; n < PART; n++)
-#pragma unroll
-          for (int e = 0; e < 8; e++) acc[n][e] -= (float)x[n][e];
-      };
-      int l = l0;
-      for (; l + 1 < last; l += 2) {
-        const uint16_t* src0 = dh_in + ((size_t)bh * Tm + ci[l]) * D * D + at;
-        const uint16_t* src1 = dh_in + ((size_t)bh * Tm + ci[l + 1]) * D * D + at;
-        bf16x8 x0[PART], x1[PART];
-#pragma unroll
-        for (int n = 0; n < PART; n++) x0[n] = *reinterpret_cast<const bf16x8*>(src0 + NT * n * 8);
-#pragma unroll
-        for (int n = 0; n < PART; n++) x1[n] = *reinterpret_cast<const bf16x8*>(src1 + NT * n * 8);
-        take(x0);
-        take(x1);
-      }
-      if (l < last) {
-        const uint16_t* src = dh_in + ((size_t)bh * Tm + ci[l]) * D * D + at;
-        bf16x8 x[PART];
-#pragma unroll
-        for (int n = 0; n < PART; n++) x[n] = *reinterpret_cast<const bf16x8*>(src + NT * n * 8);
-        take(x);
-      }
-#pragma unroll
-      for (int n = 0; n < PART; n++) {
-        const int idx = tid + NT * (n0 + n), l = idx % kWave, half = idx / kWave % 2, t = idx / (2 * kWave);
-        uint16_t* dst = dht + (32 * (t / ET) + l % 32) * LD + 32 * (t % ET) + 16 * half + 4 * (l / 32);
-#pragma unroll
-        for (int x = 0; x < 2; x++) {
-          bf16x4 y;
-#pragma unroll
-          for (int e = 0; e < 4; e++) y[e] = (__bf16)acc[n][4 * x + e];
-          *reinterpret_cast<bf16x4*>(dst + 8 * x) = y;
-        }
+      for (int y = 0; y < 2; y++) {
+        bf16x4 four = {x[n][4 * y], x[n][4 * y + 1], x[n][4 * y + 2], x[n][4 * y + 3]};
+        if (all_selected) four = bf16x4{};           // no gradient, whatever dO holds
+        *reinterpret_cast<bf16x4*>(dst + 8 * y) = four;
       }
     }
+    const int last = all_selected ? l0 : l1;
     float dzj = (tid < D && !all_selected) ? dz_total[(size_t)bh * D + tid] : 0.f;
     if (tid < D)
       for (int l = l0; l < last; l += 4) {             // four at a time on their way: one by one each costs a round trip
@@ -887,7 +847,7 @@ static hipError_t launch_bwd_kv_mfma(const Shape& s, const BwdArgs& a, hipStream
   if (hipError_t e = allow_dynamic_lds(once, (const void*)bwd_kv_mfma_kernel<D, BQ>, smem); e != hipSuccess) return e;
   bwd_kv_mfma_kernel<D, BQ><<<dim3((unsigned)bwd_kv_grid(s)), 256, smem, stream>>>(
       (const uint16_t*)a.q, (const uint16_t*)a.k, (const uint16_t*)a.v, (const uint16_t*)a.dout, a.lraw, a.ds, a.k_mean,
-      a.k_stats, a.col_ptr, a.col_idx, a.order, (const uint16_t*)a.dh, a.dz, a.dh_total, a.dz_total, a.alpha, (uint16_t*)a.dk,
+      a.k_stats, a.col_ptr, a.col_idx, a.order, (const uint16_t*)a.dh_sum, a.dz, a.dz_total, a.alpha, (uint16_t*)a.dk,
       (uint16_t*)a.dv, a.colsum, s.sin, s.sout, s.H, s.N, s.Tm, s.Tn, s.k, s.alpha_per_block ? 1 : 0);
   return hipGetLastError();
 }
