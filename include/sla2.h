@@ -121,8 +121,9 @@ typedef struct sla2_ws_layout {
                        (g = 0, 1; b = 0..31).  SLA2_QUANT_FP8_V only; tokens >= N are 0 */
   size_t v_scale;   /* float  [BH, T_n]      dequantisation scale of each V block (SLA2_QUANT_FP8_V only) */
   size_t partial;   /* scratch, two lives: double [BH, T_n, d], k_sum once more as the operand fragments of the router
-                       (written by the pooling step, dead after the router); then the per-chunk partial sums of h and z and,
-                       behind them, -h_total as accumulator fragments (bf16 path only) */
+                       (written by the pooling step, dead after the router); then, bf16 path: the per-chunk partial sums of h
+                       and z and, behind them, -h_total as accumulator fragments; fp32 path: h_j, z_j of every key block and,
+                       without SLA2_FLAG_SAVE_FOR_BACKWARD, H_i, Z_i of every query block behind them */
   /* with SLA2_FLAG_SAVE_FOR_BACKWARD only (0 bytes otherwise): */
   size_t o_s;       /* dtype  [BH, N, d]     sparse-branch output O^s, before the mix of Eq. 13   (input of Alg. 3) */
   size_t o_l;       /* dtype  [BH, N, d]     linear-branch output O^l (fp32 tensors only; 0 bytes for bf16 tensors, whose

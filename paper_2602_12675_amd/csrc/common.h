@@ -171,11 +171,15 @@ hipError_t launch_router_topk(const Shape& s, const double* q_sum, const double*
                               int32_t* block_idx, double* k_mean, hipStream_t stream);
 hipError_t launch_router_soft(const Shape& s, const double* q_sum, const double* k_frag, const double* router_m,
                               float* mask, double tau, hipStream_t stream);
+// states [BH, T_n, d * d + d]: h_j, z_j of every key block; h_i [BH, T_m, d, d], z_i [BH, T_m, d]: their sums over the
+// key blocks that a query block did not select
 hipError_t launch_kv_state_f32(const Shape& s, const float* k, const float* v, const double* k_mean, float* k_stats,
-                               float* partial, hipStream_t stream);
-hipError_t launch_attn_f32(const Shape& s, const float* q, const float* k, const float* v, const double* k_mean,
-                           const float* k_stats, const float* h_total, const float* z_total, const int32_t* block_idx,
-                           const float* alpha, float* out, float* lse, const SavedForBackward& sv, hipStream_t stream);
+                               float* states, hipStream_t stream);
+hipError_t launch_block_states_f32(const Shape& s, const float* states, const int32_t* block_idx, float* h_total, float* z_total,
+                                   float* h_i, float* z_i, hipStream_t stream);
+hipError_t launch_attn_f32(const Shape& s, const float* q, const float* k, const float* v, const double* k_mean, const float* h_i,
+                           const float* z_i, const int32_t* block_idx, const float* alpha, float* out, float* lse,
+                           const SavedForBackward& sv, hipStream_t stream);
 
 hipError_t launch_kv_total(const Shape& s, const float* partial, float* h_total, float* z_total, float* h_frag, hipStream_t stream);
 hipError_t launch_kv_state_bf16(const Shape& s, const uint16_t* k, const uint16_t* v, const double* k_mean,

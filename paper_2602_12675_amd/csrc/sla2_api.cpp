@@ -103,6 +103,9 @@ static BwdLayout make_bwd_layout(const Shape& s) {
 }
 static size_t bwd_scratch_bytes(const Shape& s) { return make_bwd_layout(s).total; }
 
+// fp32 tensors: entries of the key blocks' states (a whole number of 256-byte units)
+static size_t f32_states(const Shape& s) { return ((size_t)s.BH * s.Tn * (s.d * s.d + s.d) + 63) & ~(size_t)63; }
+
 void make_layout(const Shape& s, sla2_ws_layout* L) {
   size_t off = 0, BH = (size_t)s.BH, d = (size_t)s.d;
   auto take = [&](size_t bytes) { size_t o = off; off = align256(off + bytes); return o; };
@@ -120,8 +123,10 @@ void make_layout(const Shape& s, sla2_ws_layout* L) {
   L->k_scale = take(s.quant ? BH * (size_t)s.Tn * sizeof(float) : 0);
   L->v_fp8 = take(s.quant == 3 ? BH * (size_t)s.Tn * s.bk * d : 0);
   L->v_scale = take(s.quant == 3 ? BH * (size_t)s.Tn * sizeof(float) : 0);
-  // two lives: the pooled keys as fragments, for the router; then the partial sums (bf16: -h_total as fragments behind them)
-  const size_t partials = BH * ((size_t)s.chunks * (d * d + d) + (s.bf16 ? d * d : 0)) * sizeof(float);
+  // two lives: the pooled keys as fragments, for the router; then bf16: the partial sums, -h_total as fragments behind them;
+  // fp32: the states of all key blocks and, unless `bwd` keeps them, H_i, Z_i of the query blocks
+  const size_t state = d * d + d, partials = (s.bf16 ? BH * ((size_t)s.chunks * state + d * d)
+                                                     : f32_states(s) + (s.save ? 0 : BH * s.Tm * state)) * sizeof(float);
   const size_t pooled = BH * (size_t)s.Tn * d * sizeof(double);
   L->partial = take(partials > pooled ? partials : pooled);
   const size_t esz = s.bf16 ? 2 : 4;
@@ -323,14 +328,16 @@ int sla2_forward(const sla2_params* params, const void* q, const void* k, const 
   float* z_total = at<float>(workspace, L.z_total);
   float* partial = at<float>(workspace, L.partial);
   if (!s.bf16) {
+    float* h_i = s.save ? (float*)sv.h_i : partial + f32_states(s);
+    float* z_i = s.save ? sv.z_i : h_i + (size_t)s.BH * s.Tm * s.d * s.d;
     if (SLA2_STAGE(SLA2_STAGE_KV_STATE, launch_kv_state_f32(s, (const float*)k, (const float*)v, k_mean, k_stats,
                                                             partial, st)) != hipSuccess)
       return SLA2_EHIP;
-    if (SLA2_STAGE(SLA2_STAGE_KV_TOTAL, launch_kv_total(s, partial, h_total, z_total, nullptr, st)) != hipSuccess)
+    if (SLA2_STAGE(SLA2_STAGE_KV_TOTAL, launch_block_states_f32(s, partial, idx, h_total, z_total, h_i, z_i, st)) != hipSuccess)
       return SLA2_EHIP;
     if (SLA2_STAGE(SLA2_STAGE_ATTN,
-                   launch_attn_f32(s, (const float*)q, (const float*)k, (const float*)v, k_mean, k_stats, h_total,
-                                   z_total, idx, alpha, (float*)out, lse_or_null, sv, st)) != hipSuccess)
+                   launch_attn_f32(s, (const float*)q, (const float*)k, (const float*)v, k_mean, h_i, z_i, idx, alpha,
+                                   (float*)out, lse_or_null, sv, st)) != hipSuccess)
       return SLA2_EHIP;
     return SLA2_OK;
   }

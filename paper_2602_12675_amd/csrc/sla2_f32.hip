@@ -1,82 +1,73 @@
-// fp32 path of the SLA2 forward pass (Alg. 2 of the paper), used when q, k, v are stored in fp32.  The data flow is the
-// one of the bf16 / FP8 path - per-head totals of h_j, z_j first, then one pass per query block that runs the sparse
-// branch over the selected key/value blocks, rebuilds the h_j, z_j of exactly those blocks, subtracts them from the
-// totals, and mixes the two branches - in fp32 throughout: products on the fp32 matrix instruction (f32_tiles.h).
+// fp32 path of the SLA2 forward pass (Alg. 2 of the paper), used when q, k, v are stored in fp32.  h_j, z_j of every key
+// block are formed once and kept; their sums over the blocks that a query block did not select, H_i and Z_i, come out of a
+// product of the selection's complement with all of them; one pass per query block then runs the sparse branch over the
+// selected key/value blocks, applies H_i, Z_i and mixes the two branches.  fp32 throughout: products on the fp32 matrix
+// instruction (f32_tiles.h).
 #include "f32_tiles.h"
 
 namespace sla2 {
 
+// A block's state: h_j [d (c)][d (e)], then z_j [d].
+__host__ __device__ constexpr int f32_state(int d) { return d * d + d; }
+
 // ---------------------------------------------------------------------------------------------
-// kv_state_f32: for a chunk of key blocks of one head
+// kv_state_f32: one workgroup per key block
 //   k' = k - colmean(K);  stats[token] = lnZ = log sum_c exp(k'_c);
-//   K^phi = softmax_d(k');  partial h += (K^phi_j)^T V_j,  partial z += colsum(K^phi_j)
+//   K^phi = softmax_d(k');  h_j = (K^phi_j)^T V_j,  z_j = colsum(K^phi_j)
 // (Alg. 2: K^phi, h, z).  Tokens past N contribute nothing.  A token's channels sit on neighbouring lanes, 4 each, so
-// the softmax is taken in registers on the way into LDS.
+// the softmax is taken in registers on the way into LDS.  h_j is as large as the block's K and V together at d = 128:
+// writing it is what bounds the kernel there.
 // ---------------------------------------------------------------------------------------------
 template <int D>
-__global__ __launch_bounds__(256) void kv_state_f32_kernel(const float* __restrict__ k, const float* __restrict__ v,
-                                                           const double* __restrict__ k_mean,
-                                                           float* __restrict__ k_stats, float* __restrict__ partial,
-                                                           Strides sin, int H, int N, int Tn, int chunks,
-                                                           int blocks_per_chunk) {
+__global__ __launch_bounds__(256, 2) void kv_state_f32_kernel(const float* __restrict__ k, const float* __restrict__ v,
+                                                              const double* __restrict__ k_mean, float* __restrict__ k_stats,
+                                                              float* __restrict__ states, Strides sin, int H, int N, int Tn) {
   constexpr int LD = kF32Ld<D>;
   typedef ChunkMap<D, 256, kF32Tokens> CM;
   typedef StateSplit<D, 4> SS;
   extern __shared__ __attribute__((aligned(16))) float smem[];
   float* kp = smem;                       // [64][LD]  K^phi tile
   float* vs = smem + kF32Tokens * LD;     // [64][LD]  V tile
-  const int bh = blockIdx.x / chunks, chunk = blockIdx.x % chunks;
+  const int bh = blockIdx.x / Tn, j = blockIdx.x % Tn;
   const int tid = threadIdx.x, lane = tid % kWave, g = lane / 32, w = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int ch = tid % CM::kChunks, trow = tid / CM::kChunks;
-  const float* kh = k + head_offset(sin, bh, H);
-  const float* vh = v + head_offset(sin, bh, H);
-  const int j0 = chunk * blocks_per_chunk, j1 = min(Tn, j0 + blocks_per_chunk);
-  f32x4 mu;
+  const int t0 = j * kF32Tokens, valid = min(kF32Tokens, N - t0);
+  f32x4 kr[CM::kLoads], vr[CM::kLoads], mu;
+  CM::load(kr, k + head_offset(sin, bh, H) + (size_t)t0 * sin.n, sin.n, valid, tid);
+  CM::load(vr, v + head_offset(sin, bh, H) + (size_t)t0 * sin.n, sin.n, valid, tid);
 #pragma unroll
   for (int x = 0; x < 4; x++) mu[x] = (float)k_mean[(size_t)bh * D + 4 * ch + x];
 
+  f32x4 zacc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int i = 0; i < CM::kLoads; i++) {
+    const int t = trow + i * CM::kRows;
+    const bool ok = t < valid;
+    const f32x4 x = kr[i] - mu;
+    const float m = CM::row_max(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])));
+    f32x4 e;
+#pragma unroll
+    for (int c = 0; c < 4; c++) e[c] = exp2_f32((x[c] - m) * kLog2e);
+    const float sum = CM::row_sum((e[0] + e[1]) + (e[2] + e[3]));
+    const float inv = ok ? 1.f / sum : 0.f;
+    e *= inv;
+    zacc += e;
+    *reinterpret_cast<f32x4*>(kp + t * LD + 4 * ch) = e;
+    *reinterpret_cast<f32x4*>(vs + t * LD + 4 * ch) = vr[i];
+    if (ok && ch == 0) k_stats[(size_t)bh * N + t0 + t] = m + __log2f(sum) * kLn2;
+  }
+  __syncthreads();
   f32x16 hacc[SS::kTiles];
 #pragma unroll
   for (int x = 0; x < SS::kTiles; x++) hacc[x] = zero16();
-  f32x4 zacc = {0.f, 0.f, 0.f, 0.f};
-  f32x4 kr[CM::kLoads], vr[CM::kLoads];
-  auto fetch = [&](int j) {
-    const int t0 = j * kF32Tokens, valid = min(kF32Tokens, N - t0);
-    CM::load(kr, kh + (size_t)t0 * sin.n, sin.n, valid, tid);
-    CM::load(vr, vh + (size_t)t0 * sin.n, sin.n, valid, tid);
-  };
-  if (j0 < j1) fetch(j0);
-  for (int j = j0; j < j1; j++) {
-    const int t0 = j * kF32Tokens, valid = min(kF32Tokens, N - t0);
-    __syncthreads();                      // previous tile fully consumed
-#pragma unroll
-    for (int i = 0; i < CM::kLoads; i++) {
-      const int t = trow + i * CM::kRows;
-      const bool ok = t < valid;
-      f32x4 x = kr[i] - mu;
-      const float m = CM::row_max(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])));
-      f32x4 e;
-#pragma unroll
-      for (int c = 0; c < 4; c++) e[c] = exp2_f32((x[c] - m) * kLog2e);
-      const float sum = CM::row_sum((e[0] + e[1]) + (e[2] + e[3]));
-      const float inv = ok ? 1.f / sum : 0.f;
-      e *= inv;
-      zacc += e;
-      *reinterpret_cast<f32x4*>(kp + t * LD + 4 * ch) = e;
-      *reinterpret_cast<f32x4*>(vs + t * LD + 4 * ch) = vr[i];
-      if (ok && ch == 0) k_stats[(size_t)bh * N + t0 + t] = m + __log2f(sum) * kLn2;
-    }
-    if (j + 1 < j1) fetch(j + 1);
-    __syncthreads();
-    state_product<D, 4>(hacc, kp, vs, kF32Tokens, w, lane);
-  }
-  float* ph = partial + (size_t)blockIdx.x * (D * D + D);
+  state_product<D, 4>(hacc, kp, vs, kF32Tokens, w, lane);
+  float* ph = states + (size_t)blockIdx.x * f32_state(D);
 #pragma unroll
   for (int x = 0; x < SS::kTiles; x++)
 #pragma unroll
     for (int e = 0; e < 16; e++)
       ph[(32 * SS::mt(w) + 8 * (e / 4) + 4 * g + e % 4) * D + 32 * (SS::nt(w) + x) + lane % 32] = hacc[x][e];
-  __syncthreads();                        // the last tile fully consumed: its place takes the column sums
+  __syncthreads();                        // the tile fully consumed: its place takes the column sums
   *reinterpret_cast<f32x4*>(kp + trow * D + 4 * ch) = zacc;
   __syncthreads();
   if (tid < D) {
@@ -87,181 +78,276 @@ __global__ __launch_bounds__(256) void kv_state_f32_kernel(const float* __restri
   }
 }
 
-// Totals over the chunks of a head (Alg. 2's sums of h_j and z_j over all key blocks).  A thread owns 4 consecutive entries
-// of the partial sums; the 8 waves of a workgroup walk the chunks 8 apart and meet in LDS, always in the same
-// order, so the totals are the same bits on every run.  Bound by the start of the launch and one pass over the partial sums
-// (33 MB for 12 heads of 32k tokens).
-// FRAG: the h part of the partial sums lies as accumulator fragments (kv_state_bf16): [d/32 (c)][d/32 (e)][4][64 lanes][4],
-// lane l of part x holding rows c = 8 x + 4 (l / 32) + 0..3 of column e = l % 32; h_frag takes -h_total in the same order, which
-// is what the accumulators of the attention kernel start from.
-constexpr int kTotalWaves = 8;
-template <bool FRAG>
-__global__ __launch_bounds__(64 * kTotalWaves) void kv_total_kernel(const float* __restrict__ partial, float* __restrict__ h_total,
-                                                                    float* __restrict__ z_total, float* __restrict__ h_frag,
-                                                                    int d, int chunks) {
-  __shared__ f32x4 red[64 * kTotalWaves];
-  const int per_head = d * d + d;
-  const int bh = blockIdx.y, l = threadIdx.x % 64, cg = threadIdx.x / 64;
-  const int e = (blockIdx.x * 64 + l) * 4;
-  f32x4 s = {0.f, 0.f, 0.f, 0.f};
-  if (e < per_head) {
-    const float* p = partial + (size_t)bh * chunks * per_head + e;
-#pragma unroll 4
-    for (int c = cg; c < chunks; c += kTotalWaves) s += *reinterpret_cast<const f32x4*>(p + (size_t)c * per_head);
-  }
-  red[threadIdx.x] = s;
-  __syncthreads();
-  if (cg == 0 && e < per_head) {
-    for (int x = 1; x < kTotalWaves; x++) s += red[64 * x + l];
-    if (e >= d * d) {
-      *reinterpret_cast<f32x4*>(z_total + (size_t)bh * d + (e - d * d)) = s;
-    } else if (!FRAG) {
-      *reinterpret_cast<f32x4*>(h_total + (size_t)bh * d * d + e) = s;
-    } else {
-      *reinterpret_cast<f32x4*>(h_frag + (size_t)bh * d * d + e) = -s;
-      const int tile = e / 1024, x = e / 256 % 4, lane = e / 4 % 64;
-      const int row = 32 * (tile / (d / 32)) + 8 * x + 4 * (lane / 32), col = 32 * (tile % (d / 32)) + lane % 32;
-      for (int r = 0; r < 4; r++) h_total[((size_t)bh * d + row + r) * d + col] = s[r];
-    }
-  }
-}
-
-hipError_t launch_kv_total(const Shape& s, const float* partial, float* h_total, float* z_total, float* h_frag, hipStream_t stream) {
-  const dim3 grid((unsigned)((s.d * s.d + s.d + 255) / 256), (unsigned)s.BH);
-  if (s.bf16) kv_total_kernel<true><<<grid, 64 * kTotalWaves, 0, stream>>>(partial, h_total, z_total, h_frag, s.d, s.chunks);
-  else kv_total_kernel<false><<<grid, 64 * kTotalWaves, 0, stream>>>(partial, h_total, z_total, nullptr, s.d, s.chunks);
-  return hipGetLastError();
-}
-
 template <int D>
 static hipError_t launch_kv_state_f32_t(const Shape& s, const float* k, const float* v, const double* k_mean, float* k_stats,
-                                        float* partial, hipStream_t stream) {
+                                        float* states, hipStream_t stream) {
   constexpr int smem = 2 * kF32Tokens * kF32Ld<D> * (int)sizeof(float);
   static OncePerDevice once;
   if (hipError_t e = allow_dynamic_lds(once, (const void*)kv_state_f32_kernel<D>, smem); e != hipSuccess) return e;
-  kv_state_f32_kernel<D><<<dim3((unsigned)(s.BH * s.chunks)), 256, smem, stream>>>(k, v, k_mean, k_stats, partial, s.sin, s.H, s.N,
-                                                                                s.Tn, s.chunks, s.blocks_per_chunk);
+  kv_state_f32_kernel<D><<<dim3((unsigned)(s.BH * s.Tn)), 256, smem, stream>>>(k, v, k_mean, k_stats, states, s.sin, s.H, s.N, s.Tn);
   return hipGetLastError();
 }
 hipError_t launch_kv_state_f32(const Shape& s, const float* k, const float* v, const double* k_mean, float* k_stats,
-                               float* partial, hipStream_t stream) {
-  return s.d == 128 ? launch_kv_state_f32_t<128>(s, k, v, k_mean, k_stats, partial, stream)
-                    : launch_kv_state_f32_t<64>(s, k, v, k_mean, k_stats, partial, stream);
+                               float* states, hipStream_t stream) {
+  return s.d == 128 ? launch_kv_state_f32_t<128>(s, k, v, k_mean, k_stats, states, stream)
+                    : launch_kv_state_f32_t<64>(s, k, v, k_mean, k_stats, states, stream);
 }
 
 // ---------------------------------------------------------------------------------------------
-// attn_f32: one workgroup per query block i, BQ / 16 waves.
-//   sparse branch  : for j in sel(i), ascending: S^T = K'_j Q_i^T / sqrt(d), online softmax, O^T += V_j^T P^T
-//   linear branch  : H_i = H_total - sum_{j in sel(i)} h_j (h_j rebuilt from the staged tiles and the
-//                    per-token log-partition lnZ), Z_i likewise; O_l^T = H_i^T Q^phi^T
-//   mix            : out = alpha O_s / l + (1 - alpha) O_l                                   (Eq. 13)
-// Wave (rg, kh) owns query rows 32 rg.. and, in the sparse branch, keys 32 kh.. of every tile: the two waves of a row
-// group keep running maxima of their own and meet once, after the loop, like two halves of a split softmax.  A lane owns
-// one query row, so its probabilities feed O^T += V^T P^T from registers.  The bound is the fp32 matrix rate: on 12 heads
-// of 4,096 tokens (d = 128, 10 % kept) 12 GFLOP.
+// block_states_f32: H_i, Z_i of 32 query blocks and 128 of the d^2 + d entries of a state per wave: the 32 x T_n matrix of
+// 0 (selected) and 1 times the states of the head, and the sums over all key blocks, h_total and z_total.  A lane has four
+// consecutive entries, so a state is read 512 bytes at a time and stored the same way; the mask operand of 32 key blocks is
+// one word per lane, put together in LDS from the lists.
+// Bound by the states, read once per 32 query blocks, and H_i written: 18 us on 12 heads of 64 key and 32 query blocks
+// (d = 128; 50 MB read, 25 MB written).  The query blocks used to rebuild the h_j of their lists, a third of the products
+// of the attention kernel, and to form K^phi of every tile again.
 // ---------------------------------------------------------------------------------------------
-template <int D, int BQ> struct AttnF32Smem {
-  static constexpr int NW = BQ / 16, NT = NW * kWave;
-  static constexpr int kTile = kF32Tokens * kF32Ld<D>;                     // floats
-  static constexpr int kState = D * kF32Ld<D>;                             // H_i, over the K' and K^phi tiles
-  static_assert(kState <= 2 * kTile, "H_i takes the place of the K' and K^phi tiles");
-  static constexpr int kSwap = NW * (D / 64) * 16 * kWave;                 // half of every wave's O^T tiles
-  static constexpr int kSwapOff = 2 * kTile;                               // over the V tile and behind it
-  static constexpr int kZred = NT * 4;                                     // column sums of K^phi, before the swap
-  static constexpr int kBig = kTile > kSwap ? (kTile > kZred ? kTile : kZred) : (kSwap > kZred ? kSwap : kZred);
-  static constexpr int kMlOff = kSwapOff + kBig;                           // [NW][2][32] m and l
-  static constexpr int kZsOff = kMlOff + NW * 64;                          // [D] Z_i
-  static constexpr int kBytes = (kZsOff + D) * (int)sizeof(float);
+constexpr int kStateCols = 128;           // entries of a state per wave
+template <int D, bool TOTALS_ONLY>
+__global__ __launch_bounds__(256, 2) void block_states_f32_kernel(const float* __restrict__ states, const int32_t* __restrict__ block_idx,
+                                                                  float* __restrict__ h_total, float* __restrict__ z_total,
+                                                                  float* __restrict__ h_i, float* __restrict__ z_i, int BH, int Tm,
+                                                                  int Tn, int ksel, int row_tiles) {
+  constexpr int P = f32_state(D), kSets = (P + 4 * kStateCols - 1) / (4 * kStateCols);   // of four waves
+  extern __shared__ uint32_t bits[];      // [W][32] bit j % 32 of word j / 32 of a row: key block j is selected
+  const int W = (Tn + 31) / 32;
+  // the workgroups that read the same entries run next to each other on one XCD
+  const int y = blockIdx.x / kXcds, set = y / row_tiles * kXcds + blockIdx.x % kXcds, tile = y % row_tiles;
+  if (set >= BH * kSets) return;
+  const int bh = set / kSets, row0 = 32 * tile;
+  const int tid = threadIdx.x, lane = tid % kWave, g = lane / 32, w = tid / kWave;
+  if constexpr (!TOTALS_ONLY) {
+    for (int x = tid; x < 32 * W; x += 256) bits[x] = 0u;
+    __syncthreads();
+    const int rows = min(32, Tm - row0);
+    const int32_t* idx = block_idx + ((size_t)bh * Tm + row0) * ksel;
+    for (int e = tid; e < rows * ksel; e += 256) {
+      const int j = idx[e];
+      atomicOr(&bits[j / 32 * 32 + e / ksel], 1u << (j % 32));   // OR: the result does not depend on the order
+    }
+    __syncthreads();
+  }
+  const int col = (set % kSets * 4 + w) * kStateCols + 4 * (lane % 32);
+  const float* src = states + (size_t)bh * Tn * P + min(col, P - 4);
+  f32x16 acc[4];
+#pragma unroll
+  for (int x = 0; x < 4; x++) acc[x] = zero16();
+  f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+  for (int jw = 0; jw < W; jw++) {
+    const uint32_t word = TOTALS_ONLY ? 0u : bits[32 * jw + lane % 32];
+    f32x4 b[16];                          // key blocks 32 jw + 2 s + g; past the end the last one, with weight 0
+#pragma unroll
+    for (int s = 0; s < 16; s++) b[s] = *reinterpret_cast<const f32x4*>(src + (size_t)min(32 * jw + 2 * s + g, Tn - 1) * P);
+#pragma unroll
+    for (int s = 0; s < 16; s++) {
+      const bool exists = 32 * jw + 2 * s + g < Tn;
+      if (tile == 0) sum += exists ? b[s] : f32x4{0.f, 0.f, 0.f, 0.f};
+      if constexpr (!TOTALS_ONLY) {
+        const float a = exists && (word >> (2 * s + g) & 1u) == 0u ? 1.f : 0.f;
+#pragma unroll
+        for (int x = 0; x < 4; x++) acc[x] = mfma_f32(a, b[s][x], acc[x]);
+      }
+    }
+  }
+  if (col >= P) return;
+  if (tile == 0) {
+#pragma unroll
+    for (int x = 0; x < 4; x++) sum[x] = both_halves_sum(sum[x]);
+    if (g == 0) *reinterpret_cast<f32x4*>(col < D * D ? h_total + (size_t)bh * D * D + col : z_total + (size_t)bh * D + (col - D * D)) = sum;
+  }
+  if constexpr (!TOTALS_ONLY) {
+#pragma unroll
+    for (int v = 0; v < 16; v++) {
+      const int i = row0 + 8 * (v / 4) + 4 * g + v % 4;
+      const size_t slot = (size_t)bh * Tm + i;
+      if (i < Tm)
+        *reinterpret_cast<f32x4*>(col < D * D ? h_i + slot * D * D + col : z_i + slot * D + (col - D * D)) =
+            f32x4{acc[0][v], acc[1][v], acc[2][v], acc[3][v]};
+    }
+  }
+}
+
+// H_i, Z_i as the totals less the states of the selected blocks: 1,024 entries of a query block per workgroup.
+template <int D>
+__global__ __launch_bounds__(256) void block_states_gather_f32_kernel(const float* __restrict__ states, const int32_t* __restrict__ block_idx,
+                                                                      const float* __restrict__ h_total, const float* __restrict__ z_total,
+                                                                      float* __restrict__ h_i, float* __restrict__ z_i, int Tm, int Tn,
+                                                                      int ksel) {
+  constexpr int P = f32_state(D), kParts = (P + 1023) / 1024;
+  const int part = blockIdx.x % kParts, slot = blockIdx.x / kParts, bh = slot / Tm;
+  const int col = 1024 * part + 4 * (int)threadIdx.x;
+  if (col >= P) return;
+  const int32_t* sel = block_idx + (size_t)slot * ksel;
+  const float* src = states + (size_t)bh * Tn * P + col;
+  f32x4 a = *reinterpret_cast<const f32x4*>(col < D * D ? h_total + (size_t)bh * D * D + col : z_total + (size_t)bh * D + (col - D * D));
+#pragma unroll 8
+  for (int s = 0; s < ksel; s++) a -= *reinterpret_cast<const f32x4*>(src + (size_t)sel[s] * P);
+  *reinterpret_cast<f32x4*>(col < D * D ? h_i + (size_t)slot * D * D + col : z_i + (size_t)slot * D + (col - D * D)) = a;
+}
+
+// The product costs T_n per query block whatever is selected, the gather k, and a launch of its own behind the totals: it
+// pays where the lists are a small part of many blocks.  d = 128, 128-row blocks, product / totals + gather, us:
+//   12 heads, T_n = 128    k = 1 51 / 34    k = 3 49 / 45      k = 6 50 / 59
+//   12 heads, T_n = 512    k = 4 500 / 203  k = 13 492 / 406   k = 26 497 / 726
+//    2 heads, T_n = 1,182  k = 9 491 / 160  k = 31 488 / 388   k = 59 507 / 679
+constexpr int kGatherBlocks = 64, kGatherRatio = 30;
+template <int D>
+static hipError_t launch_block_states_f32_t(const Shape& s, const float* states, const int32_t* block_idx, float* h_total,
+                                            float* z_total, float* h_i, float* z_i, hipStream_t stream) {
+  constexpr int P = f32_state(D), kSets = (P + 4 * kStateCols - 1) / (4 * kStateCols);
+  const int sets = (s.BH * kSets + kXcds - 1) / kXcds * kXcds;
+  if (s.Tn <= kGatherBlocks || s.Tn <= kGatherRatio * s.k) {
+    const int tiles = (s.Tm + 31) / 32, smem = (s.Tn + 31) / 32 * 32 * (int)sizeof(uint32_t);   // at most 8 KB
+    block_states_f32_kernel<D, false><<<dim3((unsigned)(sets * tiles)), 256, smem, stream>>>(states, block_idx, h_total, z_total, h_i, z_i,
+                                                                                         s.BH, s.Tm, s.Tn, s.k, tiles);
+    return hipGetLastError();
+  }
+  block_states_f32_kernel<D, true><<<dim3((unsigned)sets), 256, 0, stream>>>(states, block_idx, h_total, z_total, h_i, z_i, s.BH, s.Tm,
+                                                                             s.Tn, s.k, 1);
+  if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+  block_states_gather_f32_kernel<D><<<dim3((unsigned)((size_t)s.BH * s.Tm * ((P + 1023) / 1024))), 256, 0, stream>>>(
+      states, block_idx, h_total, z_total, h_i, z_i, s.Tm, s.Tn, s.k);
+  return hipGetLastError();
+}
+hipError_t launch_block_states_f32(const Shape& s, const float* states, const int32_t* block_idx, float* h_total, float* z_total,
+                                   float* h_i, float* z_i, hipStream_t stream) {
+  return s.d == 128 ? launch_block_states_f32_t<128>(s, states, block_idx, h_total, z_total, h_i, z_i, stream)
+                    : launch_block_states_f32_t<64>(s, states, block_idx, h_total, z_total, h_i, z_i, stream);
+}
+
+// ---------------------------------------------------------------------------------------------
+// attn_f32: one workgroup of four waves per 32 query rows of a query block i
+//   sparse branch  : for j in sel(i): S^T = K'_j Q^T / sqrt(d), online softmax, O^T += V_j^T P^T
+//   linear branch  : O_l^T = H_i^T Q^phi^T / (Q^phi Z_i)
+//   mix            : out = alpha O_s / l + (1 - alpha) O_l                                   (Eq. 13)
+// Wave w takes every fourth half (32 keys) of the selected blocks, with a running maximum and sum of its own; the four
+// meet once, after the loop, like the parts of a split softmax.  A wave's K rows and V rows are its own, so they come
+// straight from global memory into operand registers: no tile in LDS, no barrier in the loop, and four times as many
+// workgroups as with 128 rows each.  K of the next 32 keys is requested before the products with V of the present ones, V
+// before the scores.
+// Which channel a row of an O^T tile stands for is free: tile x has channels ET r + x, so that a lane reads ET consecutive
+// channels of a V row at a time.  Wave w finishes the entries v / 4 = w of all tiles, channels 32 w.. (16 w.. at d = 64).
+// Bound by the fp32 matrix rate in the loop (a wave needs 64 products, 4,096 cycles, for every 16 loads of 1 KB; 82 % of the
+// time of a longer list) and by HBM outside: 12 heads of 4,096 tokens, d = 128, keeping O^s and O^l, 6 blocks a list 139 us, none
+// 55 us; 128-row workgroups with K', K^phi and V tiles in LDS, which rebuilt H_i, took 245 us.  2 heads of 1,024, d = 64: 20.5 ->
+// 9.8 us.
+// ---------------------------------------------------------------------------------------------
+template <int D> struct AttnF32Smem {
+  static constexpr int LD = kF32Ld<D>, ET = D / 32, NW = 4;
+  static constexpr int kQOff = 0;                                          // [32][LD] query rows
+  static constexpr int kMuOff = kQOff + 32 * LD;                           // [D] colmean(K)
+  static constexpr int kZsOff = kMuOff + D;                                // [D] Z_i
+  static constexpr int kMlOff = kZsOff + D;                                // [NW][2][32] m and l
+  static constexpr int kSwapOff = kMlOff + NW * 64;                        // [owner][NW - 1][4 ET][64] parts of O^T
+  static constexpr int kLSwapOff = kSwapOff + NW * (NW - 1) * 4 * ET * kWave;   // d = 64: [NW][8][64] parts of O_l^T
+  static constexpr int kBytes = (kLSwapOff + (D == 64 ? NW * 8 * kWave : 0)) * (int)sizeof(float);
+  static_assert(kBytes <= 80 * 1024, "two workgroups a CU");
 };
 
-template <int D, int BQ>
-__global__ __launch_bounds__(BQ * 4, BQ / 64) void attn_f32_kernel(
+template <int D>
+__global__ __launch_bounds__(256, 2) void attn_f32_kernel(
     const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v, const double* __restrict__ k_mean,
-    const float* __restrict__ k_stats, const float* __restrict__ h_total, const float* __restrict__ z_total,
-    const int32_t* __restrict__ block_idx, const float* __restrict__ alpha, float* __restrict__ out, float* __restrict__ lse,
-    float* __restrict__ o_s_save, float* __restrict__ o_l_save, float* __restrict__ lse_save, float* __restrict__ h_save,
-    float* __restrict__ z_save, Strides sin, Strides sout, int H, int N, int Tm, int Tn, int ksel, int alpha_per_block) {
-  typedef AttnF32Smem<D, BQ> SM;
-  constexpr int NW = SM::NW, NT = SM::NT, LD = kF32Ld<D>, ET = D / 32, J = D / 8;
-  typedef ChunkMap<D, NT, kF32Tokens> CM;
-  typedef StateSplit<D, NW> SS;
+    const float* __restrict__ h_i, const float* __restrict__ z_i, const int32_t* __restrict__ block_idx,
+    const float* __restrict__ alpha, float* __restrict__ out, float* __restrict__ lse, float* __restrict__ o_s_save,
+    float* __restrict__ o_l_save, float* __restrict__ lse_save, Strides sin, Strides sout, int BH, int H, int N, int Tm, int Tn, int bq,
+    int ksel, int alpha_per_block) {
+  typedef AttnF32Smem<D> SM;
+  constexpr int LD = SM::LD, ET = SM::ET, J = D / 8, NW = SM::NW;
+  typedef __attribute__((ext_vector_type(ET))) float f32xe;
   extern __shared__ __attribute__((aligned(16))) float smem[];
-  float* ks = smem;                       // [64][LD]  K' tile
-  float* kp = smem + SM::kTile;           // [64][LD]  K^phi tile
-  float* vs = smem + 2 * SM::kTile;       // [64][LD]  V tile
-  float* hs = smem;                       // [D][LD]   H_i
-  float* swap = smem + SM::kSwapOff;
-  float* ml = smem + SM::kMlOff;
+  float* qs = smem + SM::kQOff;
+  float* mus = smem + SM::kMuOff;
   float* zs = smem + SM::kZsOff;
+  float* ml = smem + SM::kMlOff;
+  float* swap = smem + SM::kSwapOff;
 
-  const int i = blockIdx.x % Tm, bh = blockIdx.x / Tm, h = bh % H;
-  const int tid = threadIdx.x, lane = tid % kWave, g = lane / 32, w = __builtin_amdgcn_readfirstlane(tid / kWave);
-  const int rg = w >> 1, kh = w & 1;
-  const int ch = tid % CM::kChunks, trow = tid / CM::kChunks;
-  const int row0 = i * BQ, rows_valid = min(BQ, N - row0);
-  const int qrow = 32 * rg + lane % 32;
-  const bool row_ok = qrow < rows_valid;
-  const float* kh_ = k + head_offset(sin, bh, H);
-  const float* vh = v + head_offset(sin, bh, H);
-  const int32_t* sel = block_idx + ((size_t)bh * Tm + i) * ksel;
+  // All row groups in runs of consecutive ones, one run per XCD: what runs there at a time gathers from a head or two
+  const int groups = (N + 31) / 32, all = BH * groups, run = (all + kXcds - 1) / kXcds;
+  const int at = blockIdx.x % kXcds * run + blockIdx.x / kXcds;
+  if (at >= all) return;
+  const int bh = at / groups, grp = at % groups, h = bh % H;
+  const int row0 = 32 * grp, rows_valid = min(32, N - row0), i = row0 / bq;
+  const int tid = threadIdx.x, lane = tid % kWave, g = lane / 32, r = lane % 32;
+  const int w = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const bool row_ok = r < rows_valid;
+  const size_t slot = (size_t)bh * Tm + i;
+  const float* kh = k + head_offset(sin, bh, H) + 4 * g;
+  const float* vh = v + head_offset(sin, bh, H) + ET * r;
+  const int32_t* sel = block_idx + slot * ksel;
 
-  f32x4 kr[CM::kLoads], vr[CM::kLoads];
-  float zr[CM::kLoads];
-  auto fetch = [&](int j) {
-    const int t0 = j * kF32Tokens, valid = min(kF32Tokens, N - t0);
-    CM::load(kr, kh_ + (size_t)t0 * sin.n, sin.n, valid, tid);
-    CM::load(vr, vh + (size_t)t0 * sin.n, sin.n, valid, tid);
+  const int items = 2 * ksel;             // halves of the selected blocks; an odd one of the last block may hold no key
+  auto first_key = [&](int t) { return __builtin_amdgcn_readfirstlane(sel[t / 2]) * kF32Tokens + 32 * (t % 2); };
+  f32x4 kf[J];                            // a key row, channels 8 j + 4 g ..
+  auto k_row = [&](int first) { return kh + (size_t)min(first + r, N - 1) * sin.n; };
+  typedef ChunkMap<D, 256, 32> QM;
+  f32x4 qr[QM::kLoads];
+  QM::load(qr, q + head_offset(sin, bh, H) + (size_t)row0 * sin.n, sin.n, rows_valid, tid);
+  const double mu = tid < D ? k_mean[(size_t)bh * D + tid] : 0.0;
+  const float zi = tid < D ? z_i[slot * D + tid] : 0.f;
+  __builtin_amdgcn_sched_barrier(0);
+  int t = w, key0 = 0;
+  if (t < items) {
+    key0 = first_key(t);
+    const float* src = k_row(key0);
 #pragma unroll
-    for (int x = 0; x < CM::kLoads; x++) zr[x] = k_stats[(size_t)bh * N + t0 + min(trow + x * CM::kRows, valid - 1)];
-  };
-  if (ksel > 0) fetch(sel[0]);
-  f32x4 qf[J];                            // this lane's query row, channels 8 j + 4 g ..
-  {
-    const float* src = q + head_offset(sin, bh, H) + (size_t)(row0 + min(qrow, rows_valid - 1)) * sin.n + 4 * g;
-#pragma unroll
-    for (int j = 0; j < J; j++) qf[j] = *reinterpret_cast<const f32x4*>(src + 8 * j);
+    for (int j = 0; j < J; j++) kf[j] = *reinterpret_cast<const f32x4*>(src + 8 * j);
   }
-  f32x4 mu;
+  __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-  for (int x = 0; x < 4; x++) mu[x] = (float)k_mean[(size_t)bh * D + 4 * ch + x];
-
-  f32x16 oacc[ET], hacc[SS::kTiles];
+  for (int y = 0; y < QM::kLoads; y++)
+    *reinterpret_cast<f32x4*>(qs + (tid / QM::kChunks + y * QM::kRows) * LD + 4 * (tid % QM::kChunks)) = qr[y];
+  if (tid < D) {
+    mus[tid] = (float)mu;
+    zs[tid] = zi;
+  }
+  f32x16 oacc[ET];
 #pragma unroll
   for (int e = 0; e < ET; e++) oacc[e] = zero16();
-#pragma unroll
-  for (int x = 0; x < SS::kTiles; x++) hacc[x] = zero16();
-  f32x4 zacc = {0.f, 0.f, 0.f, 0.f};
   float m_run = -INFINITY, l_run = 0.f;   // this lane's row over this wave's keys, log2 domain
   const float c0 = kLog2e * rsqrtf((float)D);
+  const float *qrow = qs + r * LD + 4 * g, *mrow = mus + 4 * g;
+  // H_i: O_l^T of 32 channels, tile nt; the waves of a tile share the contraction.  Row r of the product is the channel that
+  // the entry it lands on has in O^T.
+  constexpr int KS = NW / ET, JW = J / KS;
+  const int nt = w / KS, j0 = w % KS * JW;
+  const int ch_row = D == 128 ? 16 * (r >> 2 & 1) + 4 * (r >> 3) + (r & 3) : 16 * (r >> 4) + 8 * (r >> 2 & 1) + 4 * (r >> 3 & 1) + (r & 3);
+  const float* hsrc = h_i + slot * D * D + (size_t)(8 * j0 + 4 * g) * D + 32 * nt + ch_row;
+  float hf[JW][4];
+  __syncthreads();
 
-  for (int s = 0; s < ksel; s++) {
-    const int valid = min(kF32Tokens, N - sel[s] * kF32Tokens);
-    __syncthreads();                      // previous tile fully consumed
+  int key_next = t + NW < items ? first_key(t + NW) : 0;
+  // Requests are made one by one between the products: sixteen K requests in a row (32 cache lines each) hold the issue of
+  // a wave, and of the others of its CU, for as long as the products they feed take.  The last pass has a copy of its own:
+  // where a request may or may not have been made, the wait for the V rows in front of it is a wait for that request.
+  auto pass = [&](auto more) {
+    constexpr bool MORE = decltype(more)::value;
+    const int valid = N - key0;           // keys of this half that exist: below 32 only at the end of the sequence
+    f32xe vf[16];                         // V rows 8 (e / 4) + 4 g + e % 4, channels ET r ..
+    f32x16 sacc = zero16();
+    f32x4 qb = *reinterpret_cast<const f32x4*>(qrow), mb = *reinterpret_cast<const f32x4*>(mrow);
 #pragma unroll
-    for (int x = 0; x < CM::kLoads; x++) {
-      const int t = trow + x * CM::kRows;
-      const bool ok = t < valid;
-      f32x4 a = kr[x] - mu, e;
+    for (int j = 0; j < J; j++) {
 #pragma unroll
-      for (int c = 0; c < 4; c++) e[c] = ok ? exp2_f32((a[c] - zr[x]) * kLog2e) : 0.f;
-      zacc += e;
-      *reinterpret_cast<f32x4*>(ks + t * LD + 4 * ch) = a;
-      *reinterpret_cast<f32x4*>(kp + t * LD + 4 * ch) = e;
-      *reinterpret_cast<f32x4*>(vs + t * LD + 4 * ch) = vr[x];   // rows past the end: finite, weighted with 0
+      for (int e = 16 / J * j; e < 16 / J * (j + 1); e++)
+        vf[e] = *reinterpret_cast<const f32xe*>(vh + (size_t)min(key0 + 8 * (e / 4) + 4 * g + e % 4, N - 1) * sin.n);
+      const f32x4 a = kf[j] - mb, b = qb;
+      if (j + 1 < J) {
+        qb = *reinterpret_cast<const f32x4*>(qrow + 8 * (j + 1));
+        mb = *reinterpret_cast<const f32x4*>(mrow + 8 * (j + 1));
+      }
+#pragma unroll
+      for (int x = 0; x < 4; x++) sacc = mfma_f32(a[x], b[x], sacc);
+      __builtin_amdgcn_sched_barrier(0);
     }
-    if (s + 1 < ksel) fetch(sel[s + 1]);
-    __syncthreads();
-    f32x16 sacc = channel_product<D>(ks + (32 * kh + lane % 32) * LD, qf, zero16(), g);
     float mx = -INFINITY;
 #pragma unroll
     for (int e = 0; e < 16; e++) {
-      const bool ok = 32 * kh + 8 * (e / 4) + 4 * g + e % 4 < valid;
-      sacc[e] = ok ? sacc[e] * c0 : -INFINITY;
+      sacc[e] = 8 * (e / 4) + 4 * g + e % 4 < valid ? sacc[e] * c0 : -INFINITY;
       mx = fmaxf(mx, sacc[e]);
     }
-    mx = both_halves_max(mx);
+    mx = swap_halves_max(mx);
     const float m_new = fmaxf(m_run, mx);
-    const float m_ref = m_new == -INFINITY ? 0.f : m_new;        // no key of this half seen yet (short last block)
+    const float m_ref = m_new == -INFINITY ? 0.f : m_new;        // no key seen yet
     const float corr = exp2_f32(m_run - m_ref);
     float rs = 0.f;
 #pragma unroll
@@ -269,159 +355,171 @@ __global__ __launch_bounds__(BQ * 4, BQ / 64) void attn_f32_kernel(
       sacc[e] = exp2_f32(sacc[e] - m_ref);
       rs += sacc[e];
     }
-    l_run = l_run * corr + both_halves_sum(rs);
+    l_run = l_run * corr + swap_halves_sum(rs);
     m_run = m_new;
 #pragma unroll
-    for (int et = 0; et < ET; et++) oacc[et] *= corr;
-    const float* va = vs + (32 * kh + 4 * g) * LD + lane % 32;
+    for (int x = 0; x < ET; x++) oacc[x] *= corr;
+    const float* ksrc = nullptr;
+    if constexpr (MORE) {
+      key0 = key_next;
+      ksrc = k_row(key0);
+      if (t + 2 * NW < items) key_next = first_key(t + 2 * NW);
+    }
 #pragma unroll
-    for (int e = 0; e < 16; e++)
+    for (int e = 0; e < 16; e++) {
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (MORE) {
+        if (e < J) kf[e] = *reinterpret_cast<const f32x4*>(ksrc + 8 * e);
+      } else if (e < JW) {
 #pragma unroll
-      for (int et = 0; et < ET; et++) oacc[et] = mfma_f32(va[(8 * (e / 4) + e % 4) * LD + 32 * et], sacc[e], oacc[et]);
-    if (SS::active(w)) state_product<D, NW>(hacc, kp, vs, kF32Tokens, w, lane);
-  }
-  __syncthreads();
-
-  // ---- H_i = H_total - sum, Z_i likewise; the two key halves exchange m and l ----
-  if (SS::active(w)) {
-    const float* ht = h_total + (size_t)bh * D * D;
-    float* hsv = h_save != nullptr ? h_save + ((size_t)bh * Tm + i) * D * D : nullptr;
-#pragma unroll
-    for (int x = 0; x < SS::kTiles; x++)
-#pragma unroll
-      for (int e = 0; e < 16; e++) {
-        const int c = 32 * SS::mt(w) + 8 * (e / 4) + 4 * g + e % 4, col = 32 * (SS::nt(w) + x) + lane % 32;
-        const float y = ht[c * D + col] - hacc[x][e];
-        hs[c * LD + col] = y;
-        if (hsv != nullptr) hsv[c * D + col] = y;
+        for (int x = 0; x < 4; x++) hf[e][x] = hsrc[(8 * e + x) * D];
       }
-  }
-  *reinterpret_cast<f32x4*>(swap + trow * D + 4 * ch) = zacc;
-  if (g == 0) {
-    ml[w * 64 + lane] = m_run;
-    ml[w * 64 + 32 + lane] = l_run;
-  }
-  __syncthreads();
-  if (tid < D) {
-    float z = 0.f;
 #pragma unroll
-    for (int r = 0; r < CM::kRows; r++) z += swap[r * D + tid];
-    z = z_total[(size_t)bh * D + tid] - z;
-    zs[tid] = z;
-    if (z_save != nullptr) z_save[((size_t)bh * Tm + i) * D + tid] = z;
-  }
-  const float m_o = ml[(w ^ 1) * 64 + lane % 32], l_o = ml[(w ^ 1) * 64 + 32 + lane % 32];
-  const float m_all = fmaxf(m_run, m_o), m_ref = m_all == -INFINITY ? 0.f : m_all;
-  const float mine = exp2_f32(m_run - m_ref), l = l_run * mine + l_o * exp2_f32(m_o - m_ref);
+      for (int x = 0; x < ET; x++) oacc[x] = mfma_f32(vf[e][x], sacc[e], oacc[x]);
+    }
+  };
+  if (t < items) {
+    for (; t + NW < items; t += NW) pass(std::integral_constant<bool, true>());
+    pass(std::integral_constant<bool, false>());
+  } else {
 #pragma unroll
-  for (int et = 0; et < ET; et++) oacc[et] *= mine;
-  // Q^phi = softmax_d(Q) of this lane's row
+    for (int j = 0; j < JW; j++)
+#pragma unroll
+      for (int x = 0; x < 4; x++) hf[j][x] = hsrc[(8 * j + x) * D];
+  }
+
+  // ---- linear branch ----
+  // Q^phi = softmax_d(Q) of this lane's row, and Q^phi Z_i
+  f32x4 qf[J];
   float qm = -INFINITY;
 #pragma unroll
-  for (int j = 0; j < J; j++)
+  for (int j = 0; j < J; j++) {
+    qf[j] = *reinterpret_cast<const f32x4*>(qrow + 8 * j);
 #pragma unroll
     for (int x = 0; x < 4; x++) qm = fmaxf(qm, qf[j][x]);
-  qm = both_halves_max(qm);
-  float qs = 0.f;
-#pragma unroll
-  for (int j = 0; j < J; j++)
-#pragma unroll
-    for (int x = 0; x < 4; x++) {
-      qf[j][x] = exp2_f32((qf[j][x] - qm) * kLog2e);
-      qs += qf[j][x];
-    }
-  const float qinv = 1.f / both_halves_sum(qs);
-#pragma unroll
-  for (int j = 0; j < J; j++) qf[j] *= qinv;
-  __syncthreads();                        // Z_i visible, the column sums have been read
-  float den = 0.f;
+  }
+  qm = swap_halves_max(qm);
+  float qsum = 0.f, den = 0.f;
 #pragma unroll
   for (int j = 0; j < J; j++) {
     const f32x4 z = *reinterpret_cast<const f32x4*>(zs + 8 * j + 4 * g);
 #pragma unroll
-    for (int x = 0; x < 4; x++) den += qf[j][x] * z[x];
+    for (int x = 0; x < 4; x++) {
+      qf[j][x] = exp2_f32((qf[j][x] - qm) * kLog2e);
+      qsum += qf[j][x];
+      den += qf[j][x] * z[x];
+    }
   }
-  den = both_halves_sum(den);
+  const float qinv = 1.f / swap_halves_sum(qsum);
+  den = swap_halves_sum(den) * qinv;
   const bool all_selected = ksel >= Tn;   // nothing left for the linear branch: O_l = 0
-  const float inv_l = l > 0.f ? 1.f / l : 0.f, inv_den = all_selected ? 0.f : 1.f / den;
-  const float al = alpha[alpha_per_block ? (size_t)h * Tm + i : (size_t)h];
-
-  // Each of the two waves of a row group finishes half of the channel tiles: it hands the other half of its O^T over.
-  float* mine_out = swap + (size_t)w * (ET / 2) * 16 * kWave + lane;
-  const float* other = swap + (size_t)(w ^ 1) * (ET / 2) * 16 * kWave + lane;
-  auto finish = [&](auto half) {
-    constexpr int E0 = decltype(half)::value * (ET / 2), F0 = ET / 2 - E0;      // own tiles, tiles handed over
+  const float inv_den = all_selected ? 0.f : 1.f / den;
+  f32x16 lacc = zero16();
+  auto apply = [&](auto from) {
 #pragma unroll
-    for (int x = 0; x < ET / 2; x++)
+    for (int j = 0; j < JW; j++) {
+      const f32x4 b = qf[decltype(from)::value + j] * qinv;
 #pragma unroll
-      for (int e = 0; e < 16; e++) mine_out[(x * 16 + e) * kWave] = oacc[F0 + x][e];
-    __syncthreads();
-#pragma unroll
-    for (int x = 0; x < ET / 2; x++) {
-      constexpr int et0 = E0;
-      const int et = et0 + x;
-#pragma unroll
-      for (int e = 0; e < 16; e++) oacc[et][e] += other[(x * 16 + e) * kWave];
-      f32x16 lacc = zero16();
-      const float* ha = hs + 4 * g * LD + 32 * et + lane % 32;
-#pragma unroll
-      for (int j = 0; j < J; j++)
-#pragma unroll
-        for (int y = 0; y < 4; y++) lacc = mfma_f32(ha[(8 * j + y) * LD], qf[j][y], lacc);
-      if (row_ok) {
-        float* o = out + head_offset(sout, bh, H) + (size_t)(row0 + qrow) * sout.n + 32 * et + 4 * g;
-        const size_t at = ((size_t)bh * N + row0 + qrow) * D + 32 * et + 4 * g;
-#pragma unroll
-        for (int v4 = 0; v4 < 4; v4++) {
-          f32x4 os, ol;
-#pragma unroll
-          for (int r = 0; r < 4; r++) {
-            os[r] = oacc[et][4 * v4 + r] * inv_l;
-            ol[r] = lacc[4 * v4 + r] * inv_den;
-          }
-          *reinterpret_cast<f32x4*>(o + 8 * v4) = al * os + (1.f - al) * ol;
-          if (o_s_save != nullptr) {      // the two branches, kept for the backward pass
-            *reinterpret_cast<f32x4*>(o_s_save + at + 8 * v4) = os;
-            *reinterpret_cast<f32x4*>(o_l_save + at + 8 * v4) = ol;
-          }
-        }
-      }
+      for (int x = 0; x < 4; x++) lacc = mfma_f32(hf[j][x], b[x], lacc);
     }
   };
-  if (kh == 0) finish(std::integral_constant<int, 0>());
-  else finish(std::integral_constant<int, 1>());
-  if (kh == 0 && g == 0 && row_ok) {
-    const float L = l > 0.f ? (m_all + __log2f(l)) * kLn2 : -INFINITY;
-    if (lse != nullptr) lse[(size_t)bh * N + row0 + qrow] = L;
-    if (lse_save != nullptr) lse_save[(size_t)bh * N + row0 + qrow] = L;
+  if (j0 == 0) apply(std::integral_constant<int, 0>());
+  else apply(std::integral_constant<int, J - JW>());
+
+  // ---- the four parts of the softmax meet ----
+  if (g == 0) {
+    ml[w * 64 + r] = m_run;
+    ml[w * 64 + 32 + r] = l_run;
+  }
+  __syncthreads();
+  float m_all = -INFINITY, l = 0.f;
+#pragma unroll
+  for (int x = 0; x < NW; x++) m_all = fmaxf(m_all, ml[x * 64 + r]);
+  const float m_ref = m_all == -INFINITY ? 0.f : m_all, mine = exp2_f32(m_run - m_ref);
+#pragma unroll
+  for (int x = 0; x < NW; x++) l += ml[x * 64 + 32 + r] * exp2_f32(ml[x * 64 + r] - m_ref);
+  float os[4 * ET], ol[4 * ET];           // entry ET (v % 4) + x: channel ET (8 w + 4 g + v % 4) + x
+  auto part = [&](int owner, int from) { return swap + ((owner * (NW - 1) + (from - (from > owner))) * 4 * ET) * kWave + lane; };
+#pragma unroll
+  for (int o = 0; o < NW; o++)
+#pragma unroll
+    for (int y = 0; y < 4; y++)
+#pragma unroll
+      for (int x = 0; x < ET; x++) {
+        const float p = oacc[x][4 * o + y] * mine;
+        if (o == w) os[ET * y + x] = p;
+        else part(o, w)[(ET * y + x) * kWave] = p;
+      }
+  if constexpr (D == 64) {                // the other half of the contraction: half of the tile's entries each
+    float* ls = smem + SM::kLSwapOff;
+    auto exchange = [&](auto half) {
+      constexpr int E0 = 8 * decltype(half)::value;
+#pragma unroll
+      for (int e = 0; e < 8; e++) ls[((w ^ 1) * 8 + e) * kWave + lane] = lacc[8 - E0 + e];
+      __syncthreads();
+#pragma unroll
+      for (int e = 0; e < 8; e++) ol[e] = lacc[E0 + e] + ls[(w * 8 + e) * kWave + lane];
+    };
+    if (w % 2 == 0) exchange(std::integral_constant<int, 0>());
+    else exchange(std::integral_constant<int, 1>());
+  } else {
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < 16; e++) ol[e] = lacc[e];
+  }
+#pragma unroll
+  for (int f = 0; f < NW; f++)
+    if (f != w) {
+#pragma unroll
+      for (int e = 0; e < 4 * ET; e++) os[e] += part(w, f)[e * kWave];
+    }
+  const float inv_l = l > 0.f ? 1.f / l : 0.f;
+  const float al = alpha[alpha_per_block ? (size_t)h * Tm + i : (size_t)h];
+  if (row_ok) {
+    const int c = ET * (8 * w + 4 * g);
+    float* o = out + head_offset(sout, bh, H) + (size_t)(row0 + r) * sout.n + c;
+    const size_t kept = ((size_t)bh * N + row0 + r) * D + c;
+#pragma unroll
+    for (int e = 0; e < ET; e++) {
+      f32x4 s4, l4;
+#pragma unroll
+      for (int x = 0; x < 4; x++) {
+        s4[x] = os[4 * e + x] * inv_l;
+        l4[x] = ol[4 * e + x] * inv_den;
+      }
+      *reinterpret_cast<f32x4*>(o + 4 * e) = al * s4 + (1.f - al) * l4;
+      if (o_s_save != nullptr) {          // the two branches, kept for the backward pass
+        *reinterpret_cast<f32x4*>(o_s_save + kept + 4 * e) = s4;
+        *reinterpret_cast<f32x4*>(o_l_save + kept + 4 * e) = l4;
+      }
+    }
+    if (w == 0 && g == 0) {
+      const float L = l > 0.f ? (m_all + __log2f(l)) * kLn2 : -INFINITY;
+      if (lse != nullptr) lse[(size_t)bh * N + row0 + r] = L;
+      if (lse_save != nullptr) lse_save[(size_t)bh * N + row0 + r] = L;
+    }
   }
 }
 
-template <int D, int BQ>
-static hipError_t launch_attn_f32_t(const Shape& s, const float* q, const float* k, const float* v,
-                                    const double* k_mean, const float* k_stats, const float* h_total,
-                                    const float* z_total, const int32_t* block_idx, const float* alpha, float* out,
+template <int D>
+static hipError_t launch_attn_f32_t(const Shape& s, const float* q, const float* k, const float* v, const double* k_mean,
+                                    const float* h_i, const float* z_i, const int32_t* block_idx, const float* alpha, float* out,
                                     float* lse, const SavedForBackward& sv, hipStream_t stream) {
-  constexpr int smem = AttnF32Smem<D, BQ>::kBytes;
+  constexpr int smem = AttnF32Smem<D>::kBytes;
   static OncePerDevice once;
-  if (hipError_t e = allow_dynamic_lds(once, (const void*)attn_f32_kernel<D, BQ>, smem); e != hipSuccess) return e;
-  attn_f32_kernel<D, BQ><<<dim3((unsigned)(s.BH * s.Tm)), BQ * 4, smem, stream>>>(
-      q, k, v, k_mean, k_stats, h_total, z_total, block_idx, alpha, out, lse, (float*)sv.o_s, (float*)sv.o_l, sv.lse,
-      (float*)sv.h_i, sv.z_i, s.sin, s.sout, s.H, s.N, s.Tm, s.Tn, s.k, s.alpha_per_block ? 1 : 0);
+  if (hipError_t e = allow_dynamic_lds(once, (const void*)attn_f32_kernel<D>, smem); e != hipSuccess) return e;
+  const int run = (s.BH * ((s.N + 31) / 32) + kXcds - 1) / kXcds;
+  attn_f32_kernel<D><<<dim3((unsigned)(run * kXcds)), 256, smem, stream>>>(
+      q, k, v, k_mean, h_i, z_i, block_idx, alpha, out, lse, (float*)sv.o_s, (float*)sv.o_l, sv.lse, s.sin, s.sout, s.BH, s.H, s.N, s.Tm,
+      s.Tn, s.bq, s.k, s.alpha_per_block ? 1 : 0);
   return hipGetLastError();
 }
 
-hipError_t launch_attn_f32(const Shape& s, const float* q, const float* k, const float* v, const double* k_mean,
-                           const float* k_stats, const float* h_total, const float* z_total, const int32_t* block_idx,
-                           const float* alpha, float* out, float* lse, const SavedForBackward& sv,
-                           hipStream_t stream) {
-#define SLA2_F32(DD, QQ) \
-  return launch_attn_f32_t<DD, QQ>(s, q, k, v, k_mean, k_stats, h_total, z_total, block_idx, alpha, out, lse, sv, stream)
-  if (s.d == 128 && s.bq == 128) SLA2_F32(128, 128);
-  if (s.d == 128) SLA2_F32(128, 64);
-  if (s.bq == 128) SLA2_F32(64, 128);
-  SLA2_F32(64, 64);
-#undef SLA2_F32
+hipError_t launch_attn_f32(const Shape& s, const float* q, const float* k, const float* v, const double* k_mean, const float* h_i,
+                           const float* z_i, const int32_t* block_idx, const float* alpha, float* out, float* lse,
+                           const SavedForBackward& sv, hipStream_t stream) {
+  return s.d == 128 ? launch_attn_f32_t<128>(s, q, k, v, k_mean, h_i, z_i, block_idx, alpha, out, lse, sv, stream)
+                    : launch_attn_f32_t<64>(s, q, k, v, k_mean, h_i, z_i, block_idx, alpha, out, lse, sv, stream);
 }
 
 }  // namespace sla2

@@ -290,6 +290,48 @@ hipError_t launch_kv_state_bf16(const Shape& s, const uint16_t* k, const uint16_
   return hipGetLastError();
 }
 
+// Totals over the chunks of a head (Alg. 2's sums of h_j and z_j over all key blocks).  A thread owns 4 consecutive entries
+// of the partial sums; the 8 waves of a workgroup walk the chunks 8 apart and meet in LDS, always in the same
+// order, so the totals are the same bits on every run.  Bound by the start of the launch and one pass over the partial sums
+// (33 MB for 12 heads of 32k tokens).
+// The h part of the partial sums lies as accumulator fragments (kv_state_bf16): [d/32 (c)][d/32 (e)][4][64 lanes][4],
+// lane l of part x holding rows c = 8 x + 4 (l / 32) + 0..3 of column e = l % 32; h_frag takes -h_total in the same order, which
+// is what the accumulators of the attention kernel start from.
+constexpr int kTotalWaves = 8;
+__global__ __launch_bounds__(64 * kTotalWaves) void kv_total_kernel(const float* __restrict__ partial, float* __restrict__ h_total,
+                                                                    float* __restrict__ z_total, float* __restrict__ h_frag,
+                                                                    int d, int chunks) {
+  __shared__ f32x4 red[64 * kTotalWaves];
+  const int per_head = d * d + d;
+  const int bh = blockIdx.y, l = threadIdx.x % 64, cg = threadIdx.x / 64;
+  const int e = (blockIdx.x * 64 + l) * 4;
+  f32x4 s = {0.f, 0.f, 0.f, 0.f};
+  if (e < per_head) {
+    const float* p = partial + (size_t)bh * chunks * per_head + e;
+#pragma unroll 4
+    for (int c = cg; c < chunks; c += kTotalWaves) s += *reinterpret_cast<const f32x4*>(p + (size_t)c * per_head);
+  }
+  red[threadIdx.x] = s;
+  __syncthreads();
+  if (cg == 0 && e < per_head) {
+    for (int x = 1; x < kTotalWaves; x++) s += red[64 * x + l];
+    if (e >= d * d) {
+      *reinterpret_cast<f32x4*>(z_total + (size_t)bh * d + (e - d * d)) = s;
+    } else {
+      *reinterpret_cast<f32x4*>(h_frag + (size_t)bh * d * d + e) = -s;
+      const int tile = e / 1024, x = e / 256 % 4, lane = e / 4 % 64;
+      const int row = 32 * (tile / (d / 32)) + 8 * x + 4 * (lane / 32), col = 32 * (tile % (d / 32)) + lane % 32;
+      for (int r = 0; r < 4; r++) h_total[((size_t)bh * d + row + r) * d + col] = s[r];
+    }
+  }
+}
+
+hipError_t launch_kv_total(const Shape& s, const float* partial, float* h_total, float* z_total, float* h_frag, hipStream_t stream) {
+  const dim3 grid((unsigned)((s.d * s.d + s.d + 255) / 256), (unsigned)s.BH);
+  kv_total_kernel<<<grid, 64 * kTotalWaves, 0, stream>>>(partial, h_total, z_total, h_frag, s.d, s.chunks);
+  return hipGetLastError();
+}
+
 // =============================================================================================
 // attn_mfma
 // =============================================================================================
