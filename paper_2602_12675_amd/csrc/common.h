@@ -133,17 +133,21 @@ struct BwdArgs {
   float* dalpha;
   const void* h_i;                           // as SavedForBackward
   const float* z_i;
-  // scratch.  dh: one d x d slot per query block, element type of the tensors; lraw: L log2(e) per row (bf16: on the raw keys)
-  float *ds, *lraw, *dz, *dh_total /* fp32 tensors */, *dz_total, *colsum, *dk_mean, *dalpha_part;
+  // scratch.  dh: one d x d slot per query block (fp32 tensors: dZ_i behind each); lraw: L log2(e) per row (bf16: on the raw keys)
+  float *ds, *lraw, *dz /* bf16 tensors */, *dz_total, *colsum, *dk_mean, *dalpha_part;
   void* dh;
   int32_t *col_ptr, *col_idx, *col_cnt;      // per key block the query blocks that selected it: offsets, lists, lengths
-  // bf16 tensors: the query blocks that did not, as a bit matrix (masked_sums.h), and dH_j, the sum of their dH_i, one d x d
-  // slot per key block in the element order of dh
+  // bf16 tensors: the query blocks that did not, as a bit matrix (masked_sums.h)
   uint32_t* col_bits;
-  void* dh_sum;
+  void* dh_sum;                              // dH_j, the sum of their dH_i, one d x d slot per key block in the element order of dh
+  float *dz_sum, *dh_total;                  // fp32 tensors: dZ_j per key block; the sum of all dH_i
+  float *inv_den, *dl;                       // fp32 tensors, per row: 1 / (Q^phi Z_i) and D^l
   int32_t* order;                            // [bwd_kv_grid] the key block (bh kMaxKeyBlocks + j, or -1) of every bwd_kv workgroup
 };
 inline size_t bwd_kv_grid(const Shape& s) { return (size_t)s.BH * kXcds * ((s.Tn + kXcds - 1) / kXcds); }
+// parts of d alpha per query block, column sums of dK' per head: fp32 kernels work on 32 rows and 32 keys at a time
+inline int bwd_alpha_parts(const Shape& s) { return s.bf16 ? 1 : s.bq / 32; }
+inline int bwd_colsums(const Shape& s) { return s.bf16 ? s.Tn : 2 * s.Tn; }
 // the backward pass in the order it runs: lists, query side, totals, key side, finish
 hipError_t launch_bwd_lists(const Shape& s, const BwdArgs& a, hipStream_t stream);
 hipError_t launch_bwd_q(const Shape& s, const BwdArgs& a, hipStream_t stream);
@@ -152,6 +156,7 @@ hipError_t launch_bwd_kv(const Shape& s, const BwdArgs& a, hipStream_t stream);
 hipError_t launch_bwd_finish(const Shape& s, const BwdArgs& a, hipStream_t stream);
 hipError_t launch_bwd_q_bf16(const Shape& s, const BwdArgs& a, hipStream_t stream);   // matrix-core kernels, bf16 tensors
 hipError_t launch_bwd_kv_bf16(const Shape& s, const BwdArgs& a, hipStream_t stream);
+hipError_t launch_bwd_totals_f32(const Shape& s, const BwdArgs& a, hipStream_t stream);
 hipError_t launch_bwd_q_f32(const Shape& s, const BwdArgs& a, hipStream_t stream);
 hipError_t launch_bwd_kv_f32(const Shape& s, const BwdArgs& a, hipStream_t stream);
 
@@ -177,6 +182,8 @@ hipError_t launch_kv_state_f32(const Shape& s, const float* k, const float* v, c
                                float* states, hipStream_t stream);
 hipError_t launch_block_states_f32(const Shape& s, const float* states, const int32_t* block_idx, float* h_total, float* z_total,
                                    float* h_i, float* z_i, hipStream_t stream);
+// the same on the key side of the backward pass: dH_j, dZ_j from dH_i, dZ_i of the query blocks that did not select j
+hipError_t launch_key_states_f32(const Shape& s, const BwdArgs& a, hipStream_t stream);
 hipError_t launch_attn_f32(const Shape& s, const float* q, const float* k, const float* v, const double* k_mean, const float* h_i,
                            const float* z_i, const int32_t* block_idx, const float* alpha, float* out, float* lse,
                            const SavedForBackward& sv, hipStream_t stream);

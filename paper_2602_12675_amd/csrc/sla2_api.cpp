@@ -74,7 +74,7 @@ int make_shape(const sla2_params* p, Shape* s) {
 
 // scratch of the backward pass, carved out of the `bwd` region of the workspace
 struct BwdLayout {
-  size_t ds, dh, dz, dh_total, dz_total, colsum, dk_mean, dalpha_part, col_ptr, col_idx, col_cnt, col_bits, dh_sum, order, h_i, z_i, lraw, total;
+  size_t ds, dh, dz, dh_total, dz_total, colsum, dk_mean, dalpha_part, col_ptr, col_idx, col_cnt, col_bits, dh_sum, dz_sum, inv_den, dl, order, h_i, z_i, lraw, total;
 };
 static BwdLayout make_bwd_layout(const Shape& s) {
   BwdLayout B;
@@ -82,18 +82,21 @@ static BwdLayout make_bwd_layout(const Shape& s) {
   auto take = [&](size_t bytes) { size_t o = off; off = align256(off + bytes); return o; };
   const size_t slots = BH * s.Tm, esz = s.bf16 ? 2 : 4;   // dH_i, dZ_i, H_i, Z_i, d alpha parts: one slot per query block
   B.ds = take(slots * s.bq * sizeof(float));           // ds, lraw: whole query blocks
-  B.dh = take(slots * d * d * esz);
-  B.dz = take(slots * d * sizeof(float));
+  B.dh = take(slots * (s.bf16 ? d * d * 2 : (d * d + d) * 4));
+  B.dz = take(s.bf16 ? slots * d * sizeof(float) : 0);
   B.dh_total = take(s.bf16 ? 0 : BH * d * d * sizeof(float));
   B.dz_total = take(BH * d * sizeof(float));
-  B.colsum = take(BH * (size_t)s.Tn * d * sizeof(float));
+  B.colsum = take(BH * (size_t)bwd_colsums(s) * d * sizeof(float));
   B.dk_mean = take(BH * d * sizeof(float));
-  B.dalpha_part = take(slots * sizeof(float));
+  B.dalpha_part = take(slots * bwd_alpha_parts(s) * sizeof(float));
   B.col_ptr = take(BH * (size_t)(s.Tn + 1) * sizeof(int32_t));
   B.col_idx = take(BH * s.Tm * (size_t)(s.k > 0 ? s.k : 1) * sizeof(int32_t));
   B.col_cnt = take(BH * (size_t)s.Tn * sizeof(int32_t));
   B.col_bits = take(s.bf16 ? BH * masked_words(s.Tm) * masked_pitch(s.Tn) * sizeof(uint32_t) : 0);
-  B.dh_sum = take(s.bf16 ? BH * (size_t)s.Tn * d * d * 2 : 0);
+  B.dh_sum = take(BH * (size_t)s.Tn * d * d * esz);
+  B.dz_sum = take(s.bf16 ? 0 : BH * (size_t)s.Tn * d * sizeof(float));
+  B.inv_den = take(s.bf16 ? 0 : slots * s.bq * sizeof(float));
+  B.dl = take(s.bf16 ? 0 : slots * s.bq * sizeof(float));
   B.order = take(bwd_kv_grid(s) * sizeof(int32_t));
   B.h_i = take(slots * d * d * esz);                 // left here by the forward kernel
   B.z_i = take(slots * d * sizeof(float));
@@ -402,6 +405,7 @@ int sla2_backward(const sla2_params* params, const void* q, const void* k, const
   a.dalpha_part = (float*)(bw + B.dalpha_part);
   a.col_ptr = (int32_t*)(bw + B.col_ptr); a.col_idx = (int32_t*)(bw + B.col_idx);
   a.col_bits = (uint32_t*)(bw + B.col_bits); a.dh_sum = (void*)(bw + B.dh_sum);
+  a.dz_sum = (float*)(bw + B.dz_sum); a.inv_den = (float*)(bw + B.inv_den); a.dl = (float*)(bw + B.dl);
   a.col_cnt = (int32_t*)(bw + B.col_cnt); a.order = (int32_t*)(bw + B.order);
   hipStream_t st = (hipStream_t)hip_stream;
   count_call();

@@ -1,352 +1,398 @@
-// The two heavy steps of the backward pass for fp32 tensors (Alg. 3 of the paper's appendix with the steps it leaves to
+// The heavy steps of the backward pass for fp32 tensors (Alg. 3 of the paper's appendix with the steps it leaves to
 // automatic differentiation written out): products on the fp32 matrix instruction, everything fp32 (f32_tiles.h).
 //
-//   bwd_q_f32   one workgroup per query block i:  D^s, D^l, d alpha;  over the selected key blocks, scores transposed as
-//               in the forward kernel (a lane owns a query row):  P^T = exp(S^T - L), dP^T = V dO^T,
-//               dS^T = P^T (.) (alpha dP^T - D^s), dQ^T += K'^T dS^T;  then from the H_i, Z_i the forward pass kept
-//               dQ^phi^T = ((1 - alpha) H_i dO^T - Z_i D^l^T) / (Q^phi Z_i), dQ += softmax-backward(dQ^phi),
-//               dH_i = (1 - alpha) (Q^phi / (Q^phi Z_i))^T dO, dZ_i.
-//   bwd_kv_f32  one workgroup per key block j, over the query blocks that selected it, 64 rows a step:  S = Q K'^T (a lane
-//               owns a key), dV^T += dO^T (alpha P), dK'^T += Q^T dS;  then dH = dH_total - sum of those blocks' dH_i
-//               (the M_c[i, j] = 0 sum of Alg. 3, by complement), dK^phi^T = dH V^T + dZ 1^T, dV^T += dH^T K^phi^T,
-//               dK' += softmax-backward(dK^phi).
+//   bwd_q_f32     one workgroup per 32 rows of a query block i:  D^s, D^l, d alpha;  over the selected key blocks, scores
+//                 transposed as in the forward kernel (a lane owns a query row):  P^T = exp(S^T - L), dP^T = V dO^T,
+//                 dS^T = P^T (.) (alpha dP^T - D^s), dQ^T += K'^T dS^T;  then from the H_i, Z_i the forward pass kept
+//                 dQ^phi^T = ((1 - alpha) H_i dO^T - Z_i D^l^T) / (Q^phi Z_i), dQ += softmax-backward(dQ^phi).
+//   bwd_state_f32 one workgroup per query block:  dH_i = (1 - alpha) (Q^phi / (Q^phi Z_i))^T dO, dZ_i;  and the order of work
+//                 of bwd_kv_f32 (work_order.h).  Then dH_j, dZ_j, their sums over the query blocks that did not select key
+//                 block j (the M_c[i, j] = 0 sum of Alg. 3): masked_states_f32 in sla2_f32.hip.
+//   bwd_kv_f32    one workgroup per 32 keys of a key block j, over the query blocks that selected it:  S = Q K'^T (a lane
+//                 owns a key), dV^T += dO^T (alpha P), dK'^T += Q^T dS;  then dK^phi^T = dH_j V^T + dZ_j 1^T,
+//                 dV^T += dH_j^T K^phi^T, dK' += softmax-backward(dK^phi).
 //
-// The waves of a workgroup share the work as in the forward kernel: two waves own the same 32 query rows (keys) and one
-// half of the contraction each - keys of a tile, query rows of a step - and add their results once, after the loop.
+// The four waves of a workgroup of bwd_q and bwd_kv share 32 rows (keys) and take every fourth 32-token piece of the list, as
+// in the forward kernel: no tile in LDS and no barrier in the loop; what a lane streams, 16-byte pieces of its row or the same
+// channels of 16 rows, is requested kStream elements ahead.  The parts meet once, after the loop (meet4).
+// 12 heads of 4,096 tokens, d = 128, 128-row blocks, 6 of 64 blocks a list, against 128-row (64-key) workgroups with the tiles
+// in LDS between two barriers, two waves to each 32 rows: bwd_q 235 -> 164 us
+// and bwd_state 36, bwd_kv 290 -> 222 us and the sums of states 21 (the gathers of dH_i and lists of unequal length took their
+// time at the end of few workgroups).  A longer list costs bwd_q 18.3 us a block and bwd_kv 22.0, where the products alone take
+// 16.0 and 21.4; without a list they take 51 and 71 us, which is HBM and the meeting of the parts.
 #include "f32_tiles.h"
+#include "work_order.h"
 
 namespace sla2 {
 
-template <int D, int BQ> struct BwdQF32Smem {
-  static constexpr int NW = BQ / 16, NT = NW * kWave, LD = kF32Ld<D>;
-  static constexpr int kTile = kF32Tokens * LD;                            // floats
-  // K' and V tiles; after the loop the swapped halves of dQ^T, then H_i, then w = Q^phi / (Q^phi Z_i)
-  static constexpr int kSwap = NW * (D / 64) * 16 * kWave;
-  static constexpr int kA0 = 2 * kTile > kSwap ? 2 * kTile : kSwap;
-  static constexpr int kA1 = kA0 > D * LD ? kA0 : D * LD;
-  static constexpr int kBig = kA1 > BQ * LD ? kA1 : BQ * LD;
-  static constexpr int kDoOff = kBig;                                      // [BQ][LD] dO
-  static constexpr int kRowOff = kDoOff + BQ * LD;                         // [2][BQ] dO . O^s and dO . O^l per row
-  static constexpr int kDotOff = kRowOff + 2 * BQ;                         // [NW][32] halves of row sums
-  static constexpr int kZsOff = kDotOff + NW * 32;                         // [D] Z_i
-  static constexpr int kRedOff = kZsOff + D;                               // [NT]
-  static constexpr int kBytes = (kRedOff + NT) * (int)sizeof(float);
-  static_assert(kBytes <= 160 * 1024, "LDS of a CU");
+template <int D> struct BwdQF32Smem {
+  static constexpr int LD = kF32Ld<D>;
+  // query rows and dO rows; after the loop, when both are consumed, the parts of dQ^T
+  static constexpr int kRounds = D / 64;                                   // of meet4
+  static constexpr int kDoOff = 32 * LD;
+  static constexpr int kRowsEnd = 2 * 32 * LD;
+  static constexpr int kA = kRowsEnd > kMeetFloats<D, kRounds> ? kRowsEnd : kMeetFloats<D, kRounds>;
+  static constexpr int kLSwapOff = kA;
+  static constexpr int kMuOff = kLSwapOff + StatePart<D>::kLds;            // [D] colmean(K)
+  static constexpr int kZsOff = kMuOff + D;                                // [D] Z_i
+  static constexpr int kRowOff = kZsOff + D;                               // [3][32] dO . O^s, dO . O^l, their difference
+  static constexpr int kDotOff = kRowOff + 96;                             // [4][32] parts of row sums
+  static constexpr int kBytes = (kDotOff + 128) * (int)sizeof(float);
+  static_assert(kBytes <= 80 * 1024, "two workgroups a CU");
 };
 
-template <int D, int BQ>
-__global__ __launch_bounds__(BQ * 4, BQ / 64) void bwd_q_f32_kernel(
+template <int D>
+__global__ __launch_bounds__(256, 2) void bwd_q_f32_kernel(
     const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v, const float* __restrict__ dout,
     const float* __restrict__ o_s, const float* __restrict__ o_l, const float* __restrict__ lse,
     const double* __restrict__ k_mean, const float* __restrict__ h_i, const float* __restrict__ z_i,
     const int32_t* __restrict__ block_idx, const float* __restrict__ alpha, float* __restrict__ dq, float* __restrict__ ds_out,
-    float* __restrict__ l2_out, float* __restrict__ dh_out, float* __restrict__ dz_out, float* __restrict__ dalpha_part,
-    Strides sin, Strides sout, int H, int N, int Tm, int Tn, int ksel, int alpha_per_block) {
-  typedef BwdQF32Smem<D, BQ> SM;
-  constexpr int NW = SM::NW, NT = SM::NT, LD = SM::LD, ET = D / 32, J = D / 8;
-  typedef ChunkMap<D, NT, kF32Tokens> CM;
-  typedef ChunkMap<D, NT, BQ> RM;
-  typedef StateSplit<D, NW> SS;
+    float* __restrict__ l2_out, float* __restrict__ inv_den_out, float* __restrict__ dl_out, float* __restrict__ dalpha_part,
+    Strides sin, Strides sout, int BH, int H, int N, int Tm, int Tn, int bq, int ksel, int alpha_per_block) {
+  typedef BwdQF32Smem<D> SM;
+  typedef StatePart<D> SP;
+  constexpr int LD = SM::LD, ET = D / 32, J = D / 8, NW = 4;
   extern __shared__ __attribute__((aligned(16))) float smem[];
-  float* ks = smem;                       // [64][LD] K' tile
-  float* vs = smem + SM::kTile;           // [64][LD] V tile
-  float* hs = smem;                       // [D][LD]  H_i
-  float* wt = smem;                       // [BQ][LD] w
-  float* swap = smem;
+  float* qs = smem;
   float* dos = smem + SM::kDoOff;
+  float* mus = smem + SM::kMuOff;
+  float* zs = smem + SM::kZsOff;
   float* rows = smem + SM::kRowOff;
   float* dots = smem + SM::kDotOff;
-  float* zs = smem + SM::kZsOff;
-  float* red = smem + SM::kRedOff;
 
-  const int i = blockIdx.x % Tm, bh = blockIdx.x / Tm, h = bh % H;
+  const int groups = (N + 31) / 32, all = BH * groups, run = (all + kXcds - 1) / kXcds;   // as in the forward kernel
+  const int at = blockIdx.x % kXcds * run + blockIdx.x / kXcds;
+  if (at >= all) return;
+  const int bh = at / groups, grp = at % groups, h = bh % H;
+  const int row0 = 32 * grp, rows_valid = min(32, N - row0), i = row0 / bq;
   const size_t slot = (size_t)bh * Tm + i;
-  const int tid = threadIdx.x, lane = tid % kWave, g = lane / 32, w = __builtin_amdgcn_readfirstlane(tid / kWave);
-  const int rg = w >> 1, kh = w & 1;
-  const int ch = tid % CM::kChunks, trow = tid / CM::kChunks;
-  const int row0 = i * BQ, rows_valid = min(BQ, N - row0);
-  const int qrow = 32 * rg + lane % 32;
-  const bool row_ok = qrow < rows_valid;
-  const float* kh_ = k + head_offset(sin, bh, H);
+  const int tid = threadIdx.x, lane = tid % kWave, g = lane / 32, r = lane % 32;
+  const int w = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const bool row_ok = r < rows_valid;
+  const float* kh = k + head_offset(sin, bh, H);
   const float* vh = v + head_offset(sin, bh, H);
   const int32_t* sel = block_idx + slot * ksel;
   const float al = alpha[alpha_per_block ? (size_t)h * Tm + i : (size_t)h];
   const float rscale = rsqrtf((float)D);
 
-  f32x4 kr[CM::kLoads], vr[CM::kLoads];
-  auto fetch = [&](int j) {
-    const int t0 = j * kF32Tokens, valid = min(kF32Tokens, N - t0);
-    CM::load(kr, kh_ + (size_t)t0 * sin.n, sin.n, valid, tid);
-    CM::load(vr, vh + (size_t)t0 * sin.n, sin.n, valid, tid);
-  };
-  if (ksel > 0) fetch(sel[0]);
-  f32x4 mu;
+  typedef ChunkMap<D, 256, 32> QM;
+  {  // Q and dO into LDS (dO: zero rows past the end), dO . O^s and dO . O^l per row
+    const int ch = tid % QM::kChunks, trow = tid / QM::kChunks;
+    f32x4 qr[QM::kLoads], gr[QM::kLoads], sr[QM::kLoads], lr[QM::kLoads];
+    QM::load(qr, q + head_offset(sin, bh, H) + (size_t)row0 * sin.n, sin.n, rows_valid, tid);
+    QM::load(gr, dout + head_offset(sout, bh, H) + (size_t)row0 * sout.n, sout.n, rows_valid, tid);
+    QM::load(sr, o_s + ((size_t)bh * N + row0) * D, D, rows_valid, tid);
+    QM::load(lr, o_l + ((size_t)bh * N + row0) * D, D, rows_valid, tid);
+    if (tid < D) {
+      mus[tid] = (float)k_mean[(size_t)bh * D + tid];
+      zs[tid] = z_i[slot * D + tid];
+    }
 #pragma unroll
-  for (int x = 0; x < 4; x++) mu[x] = (float)k_mean[(size_t)bh * D + 4 * ch + x];
-  f32x4 qf[J];                            // this lane's query row, channels 8 j + 4 g ..
-  {
-    const float* src = q + head_offset(sin, bh, H) + (size_t)(row0 + min(qrow, rows_valid - 1)) * sin.n + 4 * g;
-#pragma unroll
-    for (int j = 0; j < J; j++) qf[j] = *reinterpret_cast<const f32x4*>(src + 8 * j);
-  }
-  {  // dO into LDS (zero rows past the end), dO . O^s and dO . O^l per row
-    const float* doh = dout + head_offset(sout, bh, H) + (size_t)row0 * sout.n;
-    const float* osh = o_s + ((size_t)bh * N + row0) * D;
-    const float* olh = o_l + ((size_t)bh * N + row0) * D;
-    float mix = 0.f;
-#pragma unroll
-    for (int x = 0; x < RM::kLoads; x++) {
-      const int r = trow + x * RM::kRows, rc = min(r, rows_valid - 1);
-      const float keep = r < rows_valid ? 1.f : 0.f;
-      f32x4 go = *reinterpret_cast<const f32x4*>(doh + (size_t)rc * sout.n + 4 * ch);
-      const f32x4 os = *reinterpret_cast<const f32x4*>(osh + (size_t)rc * D + 4 * ch);
-      const f32x4 ol = *reinterpret_cast<const f32x4*>(olh + (size_t)rc * D + 4 * ch);
-      go *= keep;
-      *reinterpret_cast<f32x4*>(dos + r * LD + 4 * ch) = go;
-      float s_s = 0.f, s_l = 0.f;
+    for (int y = 0; y < QM::kLoads; y++) {
+      const int row = trow + y * QM::kRows;
+      const float keep = row < rows_valid ? 1.f : 0.f;
+      gr[y] *= keep;
+      *reinterpret_cast<f32x4*>(qs + row * LD + 4 * ch) = qr[y];
+      *reinterpret_cast<f32x4*>(dos + row * LD + 4 * ch) = gr[y];
+      float s_s = 0.f, s_l = 0.f, mix = 0.f;
 #pragma unroll
       for (int c = 0; c < 4; c++) {
-        s_s += go[c] * os[c];
-        s_l += go[c] * ol[c];
-        mix += go[c] * (os[c] - ol[c]);
+        s_s += gr[y][c] * sr[y][c];
+        s_l += gr[y][c] * lr[y][c];
+        mix += gr[y][c] * (sr[y][c] - lr[y][c]);
       }
-      s_s = RM::row_sum(s_s);
-      s_l = RM::row_sum(s_l);
+      s_s = QM::row_sum(s_s);
+      s_l = QM::row_sum(s_l);
+      mix = QM::row_sum(mix);
       if (ch == 0) {
-        rows[r] = s_s;
-        rows[BQ + r] = s_l;
+        rows[row] = s_s;
+        rows[32 + row] = s_l;
+        rows[64 + row] = mix;
       }
     }
-    red[tid] = mix;
   }
-  __syncthreads();
-  if (tid < kWave) {                      // d alpha: the sum over the block's tokens of dO . (O^s - O^l)
-    float t = 0.f;
+  const int items = 2 * ksel;             // halves of the selected blocks; an odd one of the last block may hold no key
+  auto first_key = [&](int t) { return __builtin_amdgcn_readfirstlane(sel[t / 2]) * kF32Tokens + 32 * (t % 2); };
+  auto rows_of = [&](const float* head, int first) { return RowPieces(head, first, N - 1, sin.n); };
+  int t = w, key0 = 0;
+  f32x4 st[kStream];                      // per piece of 32 keys: J elements of K by lane, J of V, J of the columns of K
+  if (t < items) {
+    key0 = first_key(t);
+    const RowPieces kp = rows_of(kh, key0);
+    const unsigned own = kp.own(r, g);
 #pragma unroll
-    for (int x = 0; x < NW; x++) t += red[tid + x * kWave];
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) t += __shfl_xor(t, o);
-    if (tid == 0) dalpha_part[slot] = t;
+    for (int n = 0; n < kStream; n++) st[n] = kp.piece(own, n);
   }
-  const float Ds = al * rows[qrow], Dl = (1.f - al) * rows[BQ + qrow];
-  const float L2 = lse[(size_t)bh * N + row0 + min(qrow, rows_valid - 1)] * kLog2e;
-  if (kh == 0 && g == 0) {                // as the key-side kernel uses them: rows past the end get exp2(-inf) = 0 there
-    ds_out[slot * BQ + qrow] = row_ok ? Ds : 0.f;
-    l2_out[slot * BQ + qrow] = row_ok ? L2 : INFINITY;
-  }
-
+  const float L2 = lse[(size_t)bh * N + row0 + min(r, rows_valid - 1)] * kLog2e;
   f32x16 dqacc[ET];
 #pragma unroll
   for (int e = 0; e < ET; e++) dqacc[e] = zero16();
   const float c0 = kLog2e * rscale;
-  for (int s = 0; s < ksel; s++) {
-    const int valid = min(kF32Tokens, N - sel[s] * kF32Tokens);
-    __syncthreads();                      // previous tile fully consumed
+  const float *qrow = qs + r * LD + 4 * g, *grow = dos + r * LD + 4 * g, *mrow = mus + 4 * g;
+  const int j0 = SP::first(w);            // H_i: channels c of dQ^phi by rows, contracted over e
+  const float* hsrc = h_i + slot * D * D + (size_t)(32 * SP::tile(w) + SP::row(r)) * D + 8 * j0 + 4 * g;
+  __syncthreads();
+  const float Ds = al * rows[r], Dl = (1.f - al) * rows[32 + r];
+  if (w == 0) {                           // d alpha: the sum over the tokens of dO . (O^s - O^l)
+    float x = g == 0 ? rows[64 + r] : 0.f;
 #pragma unroll
-    for (int x = 0; x < CM::kLoads; x++) {
-      const int t = trow + x * CM::kRows;
-      *reinterpret_cast<f32x4*>(ks + t * LD + 4 * ch) = kr[x] - mu;
-      *reinterpret_cast<f32x4*>(vs + t * LD + 4 * ch) = vr[x];
+    for (int o = 1; o < kWave; o <<= 1) x += __shfl_xor(x, o);
+    const int parts = bq / 32, part = grp % parts;
+    if (lane == 0) dalpha_part[slot * parts + part] = x;
+    if (grp == groups - 1 && lane > part && lane < parts) dalpha_part[slot * parts + lane] = 0.f;   // groups past the end
+  }
+  if (w == 0 && g == 0) {                 // as the key-side kernel uses them: rows past the end get exp2(-inf) = 0 there
+    ds_out[slot * bq + row0 % bq + r] = row_ok ? Ds : 0.f;
+    l2_out[slot * bq + row0 % bq + r] = row_ok ? L2 : INFINITY;
+    dl_out[slot * bq + row0 % bq + r] = row_ok ? Dl : 0.f;
+  }
+  f32x4 mc;                               // colmean(K) as it meets an element of the columns
+#pragma unroll
+  for (int x = 0; x < 4; x++) mc[x] = mus[ET * r + x % ET];
+
+  int key_next = t + NW < items ? first_key(t + NW) : 0;
+  auto pass = [&](auto more) {
+    constexpr bool MORE = decltype(more)::value;
+    const int valid = N - key0;
+    const RowPieces kp = rows_of(kh, key0), vp = rows_of(vh, key0), np = rows_of(kh, MORE ? key_next : key0);
+    const unsigned own_k = kp.own(r, g), own_v = vp.own(r, g), own_n = np.own(r, g);
+    auto request = [&](int n) {           // element n of the piece, behind the last one of the next
+      const int j = n % J;
+      if (n < J) st[n % kStream] = kp.piece(own_k, j);
+      else if (n < 2 * J) st[n % kStream] = vp.piece(own_v, j);
+      else if (n < 3 * J) st[n % kStream] = kp.cols<D>(j, r, g);
+      else if (MORE) st[n % kStream] = np.piece(own_n, j);
+    };
+    f32x16 ds = zero16(), dp = zero16();
+    f32x4 bb = *reinterpret_cast<const f32x4*>(qrow), mb = *reinterpret_cast<const f32x4*>(mrow);
+#pragma unroll
+    for (int j = 0; j < J; j++) {         // S^T = K' Q^T
+      const f32x4 a = st[j % kStream] - mb, b = bb;
+      bb = *reinterpret_cast<const f32x4*>(j + 1 < J ? qrow + 8 * (j + 1) : grow);
+      if (j + 1 < J) mb = *reinterpret_cast<const f32x4*>(mrow + 8 * (j + 1));
+#pragma unroll
+      for (int x = 0; x < 4; x++) ds = mfma_f32(a[x], b[x], ds);
+      __builtin_amdgcn_sched_barrier(0);
+      request(j + kStream);
     }
-    if (s + 1 < ksel) fetch(sel[s + 1]);
-    __syncthreads();
-    f32x16 ds = channel_product<D>(ks + (32 * kh + lane % 32) * LD, qf, zero16(), g);
-    const f32x16 dp = channel_product<D>(vs + (32 * kh + lane % 32) * LD, dos + qrow * LD, zero16(), g);
+#pragma unroll
+    for (int j = 0; j < J; j++) {         // dP^T = V dO^T
+      const f32x4 a = st[(J + j) % kStream], b = bb;
+      if (j + 1 < J) bb = *reinterpret_cast<const f32x4*>(grow + 8 * (j + 1));
+#pragma unroll
+      for (int x = 0; x < 4; x++) dp = mfma_f32(a[x], b[x], dp);
+      __builtin_amdgcn_sched_barrier(0);
+      request(J + j + kStream);
+    }
 #pragma unroll
     for (int e = 0; e < 16; e++) {
-      const bool ok = row_ok && 32 * kh + 8 * (e / 4) + 4 * g + e % 4 < valid;
+      const bool ok = row_ok && 8 * (e / 4) + 4 * g + e % 4 < valid;
       const float p = ok ? exp2_f32(ds[e] * c0 - L2) : 0.f;
       ds[e] = p * (al * dp[e] - Ds);
     }
-    const float* ka = ks + (32 * kh + 4 * g) * LD + lane % 32;
 #pragma unroll
-    for (int e = 0; e < 16; e++)
+    for (int j = 0; j < J; j++) {         // dQ^T += K'^T dS^T
+      col_products<D>(dqacc, st[(2 * J + j) % kStream] - mc, ds, j);
+      __builtin_amdgcn_sched_barrier(0);
+      request(2 * J + j + kStream);
+    }
+    if constexpr (MORE) {
+      key0 = key_next;
+      if (t + 2 * NW < items) key_next = first_key(t + 2 * NW);
+    }
+  };
+  for (; t + NW < items; t += NW) pass(std::integral_constant<bool, true>());
+  if (t < items) pass(std::integral_constant<bool, false>());
 #pragma unroll
-      for (int et = 0; et < ET; et++) dqacc[et] = mfma_f32(ka[(8 * (e / 4) + e % 4) * LD + 32 * et], ds[e], dqacc[et]);
-  }
+  for (int j = 0; j < kStream; j++)
+    if (j < SP::kSteps) st[j] = *reinterpret_cast<const f32x4*>(hsrc + 8 * j);
 
   // ---- linear branch ----
-  // Q^phi = softmax_d(Q) of this lane's row
+  // Q^phi = softmax_d(Q) of this lane's row: its normaliser, Q^phi Z_i, and the channels this wave owns
   float qm = -INFINITY;
 #pragma unroll
-  for (int j = 0; j < J; j++)
+  for (int j = 0; j < J; j++) {
+    const f32x4 x = *reinterpret_cast<const f32x4*>(qrow + 8 * j);
 #pragma unroll
-    for (int x = 0; x < 4; x++) qm = fmaxf(qm, qf[j][x]);
-  qm = both_halves_max(qm);
-  float qs = 0.f;
-#pragma unroll
-  for (int j = 0; j < J; j++)
-#pragma unroll
-    for (int x = 0; x < 4; x++) {
-      qf[j][x] = exp2_f32((qf[j][x] - qm) * kLog2e);
-      qs += qf[j][x];
-    }
-  const float qinv = 1.f / both_halves_sum(qs);
-#pragma unroll
-  for (int j = 0; j < J; j++) qf[j] *= qinv;
-  float* mine_out = swap + (size_t)w * (ET / 2) * 16 * kWave + lane;
-  const float* other = swap + (size_t)(w ^ 1) * (ET / 2) * 16 * kWave + lane;
-  f32x16 dqo[ET / 2];                     // dQ^T of the channel tiles this wave finishes
-  auto exchange = [&](auto half) {
-    constexpr int E0 = decltype(half)::value * (ET / 2), F0 = ET / 2 - E0;
-    __syncthreads();                      // the tiles are free
-#pragma unroll
-    for (int x = 0; x < ET / 2; x++)
-#pragma unroll
-      for (int e = 0; e < 16; e++) mine_out[(x * 16 + e) * kWave] = dqacc[F0 + x][e];
-    __syncthreads();
-#pragma unroll
-    for (int x = 0; x < ET / 2; x++)
-#pragma unroll
-      for (int e = 0; e < 16; e++) dqo[x][e] = dqacc[E0 + x][e] + other[(x * 16 + e) * kWave];
-  };
-  if (kh == 0) exchange(std::integral_constant<int, 0>());
-  else exchange(std::integral_constant<int, 1>());
-  __syncthreads();                        // the swapped halves have been read
-  for (int idx = tid; idx < D * (D / 4); idx += NT)
-    *reinterpret_cast<f32x4*>(hs + (idx / (D / 4)) * LD + 4 * (idx % (D / 4))) =
-        *reinterpret_cast<const f32x4*>(h_i + slot * D * D + 4 * (size_t)idx);
-  if (tid < D) zs[tid] = z_i[slot * D + tid];
-  __syncthreads();
-  float den = 0.f;
+    for (int y = 0; y < 4; y++) qm = fmaxf(qm, x[y]);
+  }
+  qm = swap_halves_max(qm);
+  float qsum = 0.f, den = 0.f;
 #pragma unroll
   for (int j = 0; j < J; j++) {
-    const f32x4 z = *reinterpret_cast<const f32x4*>(zs + 8 * j + 4 * g);
+    const f32x4 x = *reinterpret_cast<const f32x4*>(qrow + 8 * j), z = *reinterpret_cast<const f32x4*>(zs + 8 * j + 4 * g);
 #pragma unroll
-    for (int x = 0; x < 4; x++) den += qf[j][x] * z[x];
+    for (int y = 0; y < 4; y++) {
+      const float e = exp2_f32((x[y] - qm) * kLog2e);
+      qsum += e;
+      den += e * z[y];
+    }
   }
-  den = both_halves_sum(den);
+  const float qinv = 1.f / swap_halves_sum(qsum);
+  den = swap_halves_sum(den) * qinv;
   // every block selected: the linear branch receives and passes no gradient
   const float inv_den = (ksel >= Tn || !row_ok) ? 0.f : 1.f / den;
-  f32x16 dqp[ET / 2];
+  if (w == 0 && g == 0) inv_den_out[slot * bq + row0 % bq + r] = inv_den;
+  const int c_own = own_channel(D, w, g);
+  f32x4 qp[ET];
+#pragma unroll
+  for (int y = 0; y < ET; y++) {
+    qp[y] = *reinterpret_cast<const f32x4*>(qs + r * LD + c_own + 4 * y);
+#pragma unroll
+    for (int x = 0; x < 4; x++) qp[y][x] = exp2_f32((qp[y][x] - qm) * kLog2e) * qinv;
+  }
+  f32x16 hacc = zero16();
+#pragma unroll
+  for (int j = 0; j < SP::kSteps; j++) {
+    const f32x4 a = st[j % kStream], b = *reinterpret_cast<const f32x4*>(grow + 8 * (j0 + j));
+#pragma unroll
+    for (int x = 0; x < 4; x++) hacc = mfma_f32(a[x], b[x], hacc);
+    if (j + kStream < SP::kSteps) st[j % kStream] = *reinterpret_cast<const f32x4*>(hsrc + 8 * (j + kStream));
+  }
+  float dqp[D / 8], dqo[D / 8];
+  SP::own(dqp, hacc, smem + SM::kLSwapOff, w, lane);
   float dot = 0.f;
-  auto state_grad = [&](auto half) {
-    constexpr int E0 = decltype(half)::value * (ET / 2);
 #pragma unroll
-    for (int x = 0; x < ET / 2; x++) {
-      dqp[x] = channel_product<D>(hs + (32 * (E0 + x) + lane % 32) * LD, dos + qrow * LD, zero16(), g);
-#pragma unroll
-      for (int e = 0; e < 16; e++) {
-        const int c = 32 * (E0 + x) + 8 * (e / 4) + 4 * g + e % 4;
-        dqp[x][e] = ((1.f - al) * dqp[x][e] - Dl * zs[c]) * inv_den;
-        dot += dqp[x][e] * qf[4 * (E0 + x) + e / 4][e % 4];
-      }
-    }
-  };
-  if (kh == 0) state_grad(std::integral_constant<int, 0>());
-  else state_grad(std::integral_constant<int, 1>());
-  dot = both_halves_sum(dot);
-  if (g == 0) dots[w * 32 + lane] = dot;
-  __syncthreads();                        // the row sums are visible; H_i has been read
-  dot += dots[(w ^ 1) * 32 + lane % 32];
-  auto store = [&](auto half) {
-    constexpr int E0 = decltype(half)::value * (ET / 2);
-    float* dst = dq + head_offset(sin, bh, H) + (size_t)(row0 + qrow) * sin.n + 4 * g;
-#pragma unroll
-    for (int x = 0; x < ET / 2; x++)
-#pragma unroll
-      for (int v4 = 0; v4 < 4; v4++) {
-        const f32x4 qp = qf[4 * (E0 + x) + v4];
-        f32x4 y;
-#pragma unroll
-        for (int r = 0; r < 4; r++) y[r] = dqo[x][4 * v4 + r] * rscale + qp[r] * (dqp[x][4 * v4 + r] - dot);
-        if (row_ok) *reinterpret_cast<f32x4*>(dst + 32 * (E0 + x) + 8 * v4) = y;
-        *reinterpret_cast<f32x4*>(wt + qrow * LD + 32 * (E0 + x) + 8 * v4 + 4 * g) = qp * inv_den;
-      }
-  };
-  if (kh == 0) store(std::integral_constant<int, 0>());
-  else store(std::integral_constant<int, 1>());
-  __syncthreads();                        // w complete
-  if (SS::active(w)) {
-    f32x16 dh[SS::kTiles];
-#pragma unroll
-    for (int x = 0; x < SS::kTiles; x++) dh[x] = zero16();
-    state_product<D, NW>(dh, wt, dos, BQ, w, lane);
-#pragma unroll
-    for (int x = 0; x < SS::kTiles; x++)
-#pragma unroll
-      for (int e = 0; e < 16; e++)
-        dh_out[slot * D * D + (32 * SS::mt(w) + 8 * (e / 4) + 4 * g + e % 4) * D + 32 * (SS::nt(w) + x) + lane % 32] =
-            (1.f - al) * dh[x][e];
+  for (int e = 0; e < D / 8; e++) {
+    dqp[e] = ((1.f - al) * dqp[e] - Dl * zs[c_own + e]) * inv_den;
+    dot += dqp[e] * qp[e / 4][e % 4];
   }
-  {  // dZ_i[c] = -sum_r w[r][c] D^l_r, a share of the rows per thread
-    constexpr int kParts = NT / D;
-    const int c = tid % D, part = tid / D;
-    float dz = 0.f;
-#pragma unroll 4
-    for (int r = part * (BQ / kParts); r < (part + 1) * (BQ / kParts); r++) dz -= wt[r * LD + c] * rows[BQ + r];
-    red[tid] = dz;
+  dot = swap_halves_sum(dot);
+  if (g == 0) dots[w * 32 + r] = dot;
+  __syncthreads();                        // everyone is done with the Q and dO rows
+  meet4<D, SM::kRounds>(dqo, dqacc, 1.f, smem, w, lane);
+  dot = (dots[r] + dots[32 + r]) + (dots[64 + r] + dots[96 + r]);
+  __syncthreads();                        // the parts have been read: their place takes dQ, to leave in whole rows
+#pragma unroll
+  for (int y = 0; y < ET; y++) {
+    f32x4 o;
+#pragma unroll
+    for (int x = 0; x < 4; x++) o[x] = dqo[4 * y + x] * rscale + qp[y][x] * (dqp[4 * y + x] - dot);
+    *reinterpret_cast<f32x4*>(smem + r * LD + c_own + 4 * y) = o;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int y = 0; y < QM::kLoads; y++) {
+    const int row = tid / QM::kChunks + y * QM::kRows, c = 4 * (tid % QM::kChunks);
+    if (row < rows_valid)
+      *reinterpret_cast<f32x4*>(dq + head_offset(sin, bh, H) + (size_t)(row0 + row) * sin.n + c) =
+          *reinterpret_cast<const f32x4*>(smem + row * LD + c);
+  }
+}
+
+// ---------------------------------------------------------------------------------------------
+template <int D>
+__global__ __launch_bounds__(256, 2) void bwd_state_f32_kernel(const WorkOrder order, const float* __restrict__ q,
+                                                               const float* __restrict__ dout, const float* __restrict__ inv_den,
+                                                               const float* __restrict__ dl, const float* __restrict__ alpha,
+                                                               float* __restrict__ dh, Strides sin, Strides sout, int H, int N,
+                                                               int Tm, int bq, int alpha_per_block) {
+  constexpr int LD = kF32Ld<D>;
+  typedef ChunkMap<D, 256, 64> CM;
+  typedef StateSplit<D, 4> SS;
+  extern __shared__ __attribute__((aligned(16))) float smem[];
+  __shared__ int places[2 * kXcds];
+  if ((int)blockIdx.x <= order.groups) return order_job(order, blockIdx.x, reinterpret_cast<int*>(smem), places);
+  float* wt = smem;                       // [64][LD] w = Q^phi / (Q^phi Z_i)
+  const int slot = blockIdx.x - order.groups - 1, bh = slot / Tm, i = slot % Tm, h = bh % H;
+  const int tid = threadIdx.x, lane = tid % kWave, w = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int ch = tid % CM::kChunks, trow = tid / CM::kChunks;
+  const float al = alpha[alpha_per_block ? (size_t)h * Tm + i : (size_t)h];
+  f32x16 hacc[SS::kTiles];
+#pragma unroll
+  for (int x = 0; x < SS::kTiles; x++) hacc[x] = zero16();
+  f32x4 zacc = {0.f, 0.f, 0.f, 0.f};
+  const int end = min((i + 1) * bq, N);
+  f32x4 qr[CM::kLoads];
+  StateProduct<D> sp;                     // dO
+  auto fetch = [&](int t0) {
+    CM::load(qr, q + head_offset(sin, bh, H) + (size_t)t0 * sin.n, sin.n, min(64, end - t0), tid);
+  };
+  fetch(i * bq);
+#pragma unroll 1
+  for (int t0 = i * bq; t0 < end; t0 += 64) {
+    const int valid = min(64, end - t0);
+    const size_t row = (size_t)slot * bq + t0 % bq;
+    sp.begin(dout + head_offset(sout, bh, H) + (size_t)t0 * sout.n, sout.n, valid, w, lane);
+    __syncthreads();                      // previous rows fully consumed
+#pragma unroll
+    for (int y = 0; y < CM::kLoads; y++) {
+      const int t = trow + y * CM::kRows;
+      const bool ok = t < valid;
+      const f32x4 x = qr[y];
+      const float m = CM::row_max(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])));
+      f32x4 e;
+#pragma unroll
+      for (int c = 0; c < 4; c++) e[c] = exp2_f32((x[c] - m) * kLog2e);
+      const float sum = CM::row_sum((e[0] + e[1]) + (e[2] + e[3]));
+      const float scale = ok ? inv_den[row + t] / sum : 0.f, l = ok ? dl[row + t] : 0.f;
+      e *= scale;
+      zacc -= e * l;                      // dZ_i = -sum_r w[r] D^l_r
+      *reinterpret_cast<f32x4*>(wt + t * LD + 4 * ch) = e;
+    }
+    if (t0 + 64 < end) fetch(t0 + 64);
     __syncthreads();
-    if (tid < D) {
-      float t = 0.f;
-#pragma unroll
-      for (int x = 0; x < kParts; x++) t += red[x * D + tid];
-      dz_out[slot * D + tid] = (1.f - al) * t;
-    }
+    sp.add(hacc, wt, w, lane);
   }
-}
-
-template <int D, int BQ>
-static hipError_t launch_q(const Shape& s, const BwdArgs& a, hipStream_t stream) {
-  constexpr int smem = BwdQF32Smem<D, BQ>::kBytes;
-  static OncePerDevice once;
-  if (hipError_t e = allow_dynamic_lds(once, (const void*)bwd_q_f32_kernel<D, BQ>, smem); e != hipSuccess) return e;
-  bwd_q_f32_kernel<D, BQ><<<dim3((unsigned)(s.BH * s.Tm)), BQ * 4, smem, stream>>>(
-      (const float*)a.q, (const float*)a.k, (const float*)a.v, (const float*)a.dout, (const float*)a.o_s, (const float*)a.o_l,
-      a.lse, a.k_mean, (const float*)a.h_i, a.z_i, a.block_idx, a.alpha, (float*)a.dq, a.ds, a.lraw, (float*)a.dh, a.dz,
-      a.dalpha_part, s.sin, s.sout, s.H, s.N, s.Tm, s.Tn, s.k, s.alpha_per_block ? 1 : 0);
-  return hipGetLastError();
-}
-
-hipError_t launch_bwd_q_f32(const Shape& s, const BwdArgs& a, hipStream_t stream) {
-  if (s.d == 128) return s.bq == 128 ? launch_q<128, 128>(s, a, stream) : launch_q<128, 64>(s, a, stream);
-  return s.bq == 128 ? launch_q<64, 128>(s, a, stream) : launch_q<64, 64>(s, a, stream);
+  float* out = dh + (size_t)slot * (D * D + D);
+  StateProduct<D>::store(hacc, 1.f - al, out, w, lane);
+  __syncthreads();                        // the last rows fully consumed: their place takes the column sums
+  *reinterpret_cast<f32x4*>(wt + trow * D + 4 * ch) = zacc;
+  __syncthreads();
+  if (tid < D) {
+    float z = 0.f;
+#pragma unroll
+    for (int y = 0; y < CM::kRows; y++) z += wt[y * D + tid];
+    out[D * D + tid] = z;
+  }
 }
 
 // ---------------------------------------------------------------------------------------------
 template <int D> struct BwdKvF32Smem {
   static constexpr int LD = kF32Ld<D>;
-  static constexpr int kTile = 64 * LD;                                    // floats
-  // Q and dO rows of a step; after the loop the swapped halves of dV^T and dK^T, then dH, then the outputs
-  static constexpr int kSwap = 4 * 2 * (D / 64) * 16 * kWave;
-  static constexpr int kA0 = 2 * kTile > kSwap ? 2 * kTile : kSwap;
-  static constexpr int kBig = kA0 > D * LD ? kA0 : D * LD;
-  static constexpr int kRowOff = kBig;                                     // [2][64] L log2(e) and D^s of a step's rows
-  static constexpr int kDzOff = kRowOff + 128;                             // [D]
-  static constexpr int kDotOff = kDzOff + D;                               // [4][32]
+  // K' (later K^phi) and V rows; the parts of dV^T and of dK^T, then dK'
+  static constexpr int kRounds = D / 64;                                   // of meet4: two workgroups a CU
+  static constexpr int kVOff = 32 * LD, kSwapOff = 2 * 32 * LD;
+  static constexpr int kA = kSwapOff + kMeetFloats<D, kRounds>;
+  static constexpr int kLSwapOff = kA;
+  static constexpr int kStatOff = kLSwapOff + StatePart<D>::kLds;          // [4 waves][2][32] L log2(e) and D^s of a piece's rows
+  static constexpr int kDzOff = kStatOff + 256;                            // [D] dZ_j
+  static constexpr int kDotOff = kDzOff + D;                               // [4][32] parts of row sums
   static constexpr int kBytes = (kDotOff + 128) * (int)sizeof(float);
+  static_assert(kBytes <= 80 * 1024, "two workgroups a CU");
+  static_assert(32 * LD <= kMeetFloats<D, kRounds>, "dK' takes the place of the parts");
 };
 
-template <int D, int BQ>
-__global__ __launch_bounds__(256, 1) void bwd_kv_f32_kernel(
+template <int D>
+__global__ __launch_bounds__(256, 2) void bwd_kv_f32_kernel(
     const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v, const float* __restrict__ dout,
     const float* __restrict__ l2_in, const float* __restrict__ ds_in, const double* __restrict__ k_mean,
-    const float* __restrict__ k_stats, const int32_t* __restrict__ col_ptr, const int32_t* __restrict__ col_idx, const int32_t* __restrict__ order,
-    const float* __restrict__ dh_in, const float* __restrict__ dz_in, const float* __restrict__ dh_total,
-    const float* __restrict__ dz_total, const float* __restrict__ alpha, float* __restrict__ dk, float* __restrict__ dv,
-    float* __restrict__ colsum, Strides sin, Strides sout, int H, int N, int Tm, int Tn, int ksel, int alpha_per_block) {
+    const float* __restrict__ k_stats, const int32_t* __restrict__ col_ptr, const int32_t* __restrict__ col_idx,
+    const int32_t* __restrict__ order, const float* __restrict__ dh_sum, const float* __restrict__ dz_sum,
+    const float* __restrict__ alpha, float* __restrict__ dk, float* __restrict__ dv, float* __restrict__ colsum, Strides sin,
+    Strides sout, int H, int N, int Tm, int Tn, int bq, int ksel, int alpha_per_block) {
   typedef BwdKvF32Smem<D> SM;
-  constexpr int NT = 256, LD = SM::LD, ET = D / 32, J = D / 8, HP = BQ / 64;
-  typedef ChunkMap<D, NT, 64> CM;
+  typedef StatePart<D> SP;
+  constexpr int LD = SM::LD, ET = D / 32, J = D / 8, NW = 4;
   extern __shared__ __attribute__((aligned(16))) float smem[];
-  float* qs = smem;                       // [64][LD] Q rows of the step
-  float* dos = smem + SM::kTile;          // [64][LD] dO rows of the step
-  float* dhs = smem;                      // [D][LD]  dH
-  float* okt = smem;                      // [64][LD] dK', then dV behind it
-  float* ovt = smem + SM::kTile;
-  float* rows = smem + SM::kRowOff;
+  float* ks = smem;
+  float* vs = smem + SM::kVOff;
   float* dzs = smem + SM::kDzOff;
   float* dots = smem + SM::kDotOff;
 
-  const int entry = __builtin_amdgcn_readfirstlane(order[blockIdx.x]);
+  // the two halves of a key block next to each other on the block's XCD
+  const int y2 = blockIdx.x / kXcds, entry = __builtin_amdgcn_readfirstlane(order[y2 / 2 * kXcds + blockIdx.x % kXcds]);
   if (entry < 0) return;
-  const int j = entry & (kMaxKeyBlocks - 1), bh = entry / kMaxKeyBlocks, h = bh % H;
-  const int tid = threadIdx.x, lane = tid % kWave, g = lane / 32, w = __builtin_amdgcn_readfirstlane(tid / kWave);
-  const int kh = w >> 1, rh = w & 1;      // 32 keys of the block, 32 rows of a step
-  const int ch = tid % CM::kChunks, trow = tid / CM::kChunks;
-  const int t0 = j * kF32Tokens, valid = min(kF32Tokens, N - t0);
-  const int mykey = 32 * kh + lane % 32;
-  const bool key_ok = mykey < valid;
+  const int j = entry & (kMaxKeyBlocks - 1), bh = entry / kMaxKeyBlocks, h = bh % H, half = y2 % 2;
+  const int tid = threadIdx.x, lane = tid % kWave, g = lane / 32, r = lane % 32;
+  const int w = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const size_t sums = (((size_t)bh * Tn + j) * 2 + half) * D;
+  const int t0 = j * kF32Tokens + 32 * half, valid = min(32, N - t0);
+  if (valid <= 0) {                       // no key in this half of the last block
+    if (tid < D) colsum[sums + tid] = 0.f;
+    return;
+  }
+  float* stat = smem + SM::kStatOff + 64 * w;
   const float* qh = q + head_offset(sin, bh, H);
   const float* doh = dout + head_offset(sout, bh, H);
   const float rscale = rsqrtf((float)D), c0 = kLog2e * rscale;
@@ -354,217 +400,263 @@ __global__ __launch_bounds__(256, 1) void bwd_kv_f32_kernel(
   const int32_t* cp = col_ptr + (size_t)bh * (Tn + 1);
   const int l0 = __builtin_amdgcn_readfirstlane(cp[j]), listed = __builtin_amdgcn_readfirstlane(cp[j + 1]) - l0;
   const int32_t* ci = col_idx + (size_t)bh * Tm * ksel + l0;   // the query blocks that selected this key block
-  const int nsteps = listed * HP;
-  // Step t: rows [64 (t % HP), +64) of query block ci[t / HP].  Rows past the end repeat an existing one; their L is
-  // +inf, so their probabilities are 0.
-  f32x4 qr[CM::kLoads], gr[CM::kLoads];
-  float lr = 0.f, dr = 0.f;
-    auto fetch = [&](int t) {
-    const int i = ci[t / HP], r0 = i * BQ + 64 * (t % HP), src = r0 < N ? r0 : i * BQ, n = max(1, min(64, N - r0));
-    CM::load(qr, qh + (size_t)src * sin.n, sin.n, n, tid);
-    CM::load(gr, doh + (size_t)src * sout.n, sout.n, n, tid);
-    if (tid < 64) {
-      const size_t at = (size_t)bh * Tm * BQ + r0 + tid;
-      lr = l2_in[at];
-      dr = ds_in[at];
-    }
-  };
-  if (nsteps > 0) fetch(0);
-
-  f32x4 kf[J], vf[J];                     // K' and V of this lane's key, channels 8 j + 4 g ..
+  const int per = bq / 32;
+  // Piece t: rows [32 (t % per), +32) of query block ci[t / per].  Rows past the end repeat the last one; their L is +inf,
+  // so their probabilities are 0.  A piece with no row at all (only in the last query block) has the last row throughout.
+  const int items = listed * per;
+  typedef ChunkMap<D, 256, 32> KM;
+  const int ch = tid % KM::kChunks, trow = tid / KM::kChunks;
   {
-    const size_t at = head_offset(sin, bh, H) + (size_t)(t0 + min(mykey, valid - 1)) * sin.n + 4 * g;
-    const double* mu = k_mean + (size_t)bh * D + 4 * g;
+    f32x4 kr[KM::kLoads], vr[KM::kLoads], mu;
+    KM::load(kr, k + head_offset(sin, bh, H) + (size_t)t0 * sin.n, sin.n, valid, tid);
+    KM::load(vr, v + head_offset(sin, bh, H) + (size_t)t0 * sin.n, sin.n, valid, tid);
 #pragma unroll
-    for (int x = 0; x < J; x++) {
-      kf[x] = *reinterpret_cast<const f32x4*>(k + at + 8 * x);
-      vf[x] = *reinterpret_cast<const f32x4*>(v + at + 8 * x);
+    for (int x = 0; x < 4; x++) mu[x] = (float)k_mean[(size_t)bh * D + 4 * ch + x];
+    if (tid < D) dzs[tid] = ksel >= Tn ? 0.f : dz_sum[((size_t)bh * Tn + j) * D + tid];
 #pragma unroll
-      for (int y = 0; y < 4; y++) kf[x][y] -= (float)mu[8 * x + y];
+    for (int y = 0; y < KM::kLoads; y++) {
+      *reinterpret_cast<f32x4*>(ks + (trow + y * KM::kRows) * LD + 4 * ch) = kr[y] - mu;
+      *reinterpret_cast<f32x4*>(vs + (trow + y * KM::kRows) * LD + 4 * ch) = vr[y];
     }
   }
   f32x16 dvacc[ET], dkacc[ET];
 #pragma unroll
   for (int e = 0; e < ET; e++) { dvacc[e] = zero16(); dkacc[e] = zero16(); }
-
-  for (int t = 0; t < nsteps; t++) {
-    const int i = ci[t / HP];
-    const float al = alpha[alpha_per_block ? (size_t)h * Tm + i : (size_t)h];
-    __syncthreads();                      // previous step fully consumed
+  const float *krow = ks + r * LD + 4 * g, *vrow = vs + r * LD + 4 * g;
+  f32x4 st[kStream];                      // per piece: J elements of Q by lane, J of dO, J of the columns of dO, J of those of Q
+  int t = w, i = 0, i_next = 0;
+  auto block_of = [&](int x) { return __builtin_amdgcn_readfirstlane(ci[x / per]); };
+  auto first_row = [&](int x, int block) { return block * bq + 32 * (x % per); };
+  auto row_stat = [&](int r0) {           // L log2(e) (g = 0) or D^s (g = 1) of a row of the piece
+    const size_t row = (size_t)bh * Tm * bq + min(r0 + r, N - 1);
+    const float x = g == 0 ? l2_in[row] : ds_in[row];
+    return r0 + r < N ? x : g == 0 ? INFINITY : 0.f;
+  };
+  float stat_next = 0.f;
+  if (t < items) {
+    i = block_of(t);
+    const RowPieces qp(qh, first_row(t, i), N - 1, sin.n);
+    const unsigned own = qp.own(r, g);
 #pragma unroll
-    for (int x = 0; x < CM::kLoads; x++) {
-      *reinterpret_cast<f32x4*>(qs + (trow + x * CM::kRows) * LD + 4 * ch) = qr[x];
-      *reinterpret_cast<f32x4*>(dos + (trow + x * CM::kRows) * LD + 4 * ch) = gr[x];
+    for (int n = 0; n < kStream; n++) st[n] = qp.piece(own, n);
+    stat_next = row_stat(first_row(t, i));
+    if (t + NW < items) i_next = block_of(t + NW);
+  }
+  __syncthreads();
+
+  auto pass = [&](auto more) {
+    constexpr bool MORE = decltype(more)::value;
+    const int r0 = first_row(t, i), r0_next = MORE ? first_row(t + NW, i_next) : r0;
+    const float al = alpha[alpha_per_block ? (size_t)h * Tm + i : (size_t)h];
+    stat[32 * g + r] = stat_next;
+    if constexpr (MORE) stat_next = row_stat(r0_next);
+    const RowPieces qp(qh, r0, N - 1, sin.n), gp(doh, r0, N - 1, sout.n), np(qh, r0_next, N - 1, sin.n);
+    const unsigned own_q = qp.own(r, g), own_g = gp.own(r, g), own_n = np.own(r, g);
+    auto request = [&](int n) {           // element n of the piece, behind the last one of the next
+      const int x = n % J;
+      if (n < J) st[n % kStream] = qp.piece(own_q, x);
+      else if (n < 2 * J) st[n % kStream] = gp.piece(own_g, x);
+      else if (n < 3 * J) st[n % kStream] = gp.cols<D>(x, r, g);
+      else if (n < 4 * J) st[n % kStream] = qp.cols<D>(x, r, g);
+      else if (MORE) st[n % kStream] = np.piece(own_n, x);
+    };
+    f32x16 p = zero16(), ds = zero16();
+    f32x4 bb = *reinterpret_cast<const f32x4*>(krow);
+#pragma unroll
+    for (int x = 0; x < J; x++) {         // S = Q K'^T
+      const f32x4 a = st[x % kStream], b = bb;
+      bb = *reinterpret_cast<const f32x4*>(x + 1 < J ? krow + 8 * (x + 1) : vrow);
+#pragma unroll
+      for (int y = 0; y < 4; y++) p = mfma_f32(a[y], b[y], p);
+      __builtin_amdgcn_sched_barrier(0);
+      request(x + kStream);
     }
-    if (tid < 64) {
-      rows[tid] = lr;
-      rows[64 + tid] = dr;
-    }
-    if (t + 1 < nsteps) fetch(t + 1);
-    __syncthreads();
-    f32x16 p = channel_product<D>(qs + (32 * rh + lane % 32) * LD, kf, zero16(), g);
-    f32x16 ds = channel_product<D>(dos + (32 * rh + lane % 32) * LD, vf, zero16(), g);
+    wave_lds_fence();
 #pragma unroll
     for (int v4 = 0; v4 < 4; v4++) {
-      const int r = 32 * rh + 8 * v4 + 4 * g;
-      const f32x4 l4 = *reinterpret_cast<const f32x4*>(rows + r);
-      const f32x4 d4 = *reinterpret_cast<const f32x4*>(rows + 64 + r);
+      const f32x4 l4 = *reinterpret_cast<const f32x4*>(stat + 8 * v4 + 4 * g);
+#pragma unroll
+      for (int y = 0; y < 4; y++) p[4 * v4 + y] = exp2_f32(p[4 * v4 + y] * c0 - l4[y]);   // keys past the end: columns of their own, not stored
+    }
+#pragma unroll
+    for (int x = 0; x < J; x++) {         // dP = dO V^T
+      const f32x4 a = st[(J + x) % kStream], b = bb;
+      if (x + 1 < J) bb = *reinterpret_cast<const f32x4*>(vrow + 8 * (x + 1));
+#pragma unroll
+      for (int y = 0; y < 4; y++) ds = mfma_f32(a[y], b[y], ds);
+      __builtin_amdgcn_sched_barrier(0);
+      request(J + x + kStream);
+    }
+#pragma unroll
+    for (int v4 = 0; v4 < 4; v4++) {
+      const f32x4 d4 = *reinterpret_cast<const f32x4*>(stat + 32 + 8 * v4 + 4 * g);
 #pragma unroll
       for (int y = 0; y < 4; y++) {
         const int e = 4 * v4 + y;
-        const float pv = exp2_f32(p[e] * c0 - l4[y]);   // keys past the end: columns of their own, not stored
-        ds[e] = pv * (al * ds[e] - d4[y]);
-        p[e] = al * pv;
+        ds[e] = p[e] * (al * ds[e] - d4[y]);
+        p[e] *= al;
       }
     }
-    const float* ga = dos + (32 * rh + 4 * g) * LD + lane % 32;
-    const float* qa = qs + (32 * rh + 4 * g) * LD + lane % 32;
+    wave_lds_fence();                     // read before the next piece's take their place
 #pragma unroll
-    for (int e = 0; e < 16; e++)
-#pragma unroll
-      for (int et = 0; et < ET; et++) {
-        dvacc[et] = mfma_f32(ga[(8 * (e / 4) + e % 4) * LD + 32 * et], p[e], dvacc[et]);
-        dkacc[et] = mfma_f32(qa[(8 * (e / 4) + e % 4) * LD + 32 * et], ds[e], dkacc[et]);
-      }
-  }
-
-  // the two row halves add up: each wave finishes half of the channel tiles
-  f32x16 dvo[ET / 2], dko[ET / 2];
-  {
-    float* mine_out = smem + (size_t)w * ET * 16 * kWave + lane;
-    const float* other = smem + (size_t)(w ^ 1) * ET * 16 * kWave + lane;
-    auto exchange = [&](auto half) {
-      constexpr int E0 = decltype(half)::value * (ET / 2), F0 = ET / 2 - E0;
-      __syncthreads();                    // the last step fully consumed
-#pragma unroll
-      for (int x = 0; x < ET / 2; x++)
-#pragma unroll
-        for (int e = 0; e < 16; e++) {
-          mine_out[(x * 16 + e) * kWave] = dvacc[F0 + x][e];
-          mine_out[((ET / 2 + x) * 16 + e) * kWave] = dkacc[F0 + x][e];
-        }
-      __syncthreads();
-#pragma unroll
-      for (int x = 0; x < ET / 2; x++)
-#pragma unroll
-        for (int e = 0; e < 16; e++) {
-          dvo[x][e] = dvacc[E0 + x][e] + other[(x * 16 + e) * kWave];
-          dko[x][e] = dkacc[E0 + x][e] + other[((ET / 2 + x) * 16 + e) * kWave];
-        }
-    };
-    if (rh == 0) exchange(std::integral_constant<int, 0>());
-    else exchange(std::integral_constant<int, 1>());
-  }
-
-  // ---- linear branch: dH = dH_total - sum over the query blocks that selected j of dH_i ----
-  const bool all_selected = ksel >= Tn;
-  {
-    constexpr int NC = D * D / 4 / NT;    // 16-byte chunks per thread
-    f32x4 acc[NC];
-    const float* tot = dh_total + (size_t)bh * D * D + 4 * tid;
-#pragma unroll
-    for (int x = 0; x < NC; x++) acc[x] = *reinterpret_cast<const f32x4*>(tot + 4 * NT * x);
-    float dz = tid < D ? dz_total[(size_t)bh * D + tid] : 0.f;
-    for (int l = 0; l < listed; l++) {
-      const size_t slot = (size_t)bh * Tm + ci[l];
-      const float* src = dh_in + slot * D * D + 4 * tid;
-#pragma unroll
-      for (int x = 0; x < NC; x++) acc[x] -= *reinterpret_cast<const f32x4*>(src + 4 * NT * x);
-      if (tid < D) dz -= dz_in[slot * D + tid];
+    for (int x = 0; x < J; x++) {         // dV^T += dO^T (alpha P)
+      col_products<D>(dvacc, st[(2 * J + x) % kStream], p, x);
+      __builtin_amdgcn_sched_barrier(0);
+      request(2 * J + x + kStream);
     }
-    __syncthreads();                      // the swapped halves have been read
 #pragma unroll
-    for (int x = 0; x < NC; x++) {
-      const int idx = tid + NT * x;
-      *reinterpret_cast<f32x4*>(dhs + (idx / (D / 4)) * LD + 4 * (idx % (D / 4))) = all_selected ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[x];
+    for (int x = 0; x < J; x++) {         // dK'^T += Q^T dS
+      col_products<D>(dkacc, st[(3 * J + x) % kStream], ds, x);
+      __builtin_amdgcn_sched_barrier(0);
+      request(3 * J + x + kStream);
     }
-    if (tid < D) dzs[tid] = all_selected ? 0.f : dz;
-  }
-  {  // K' -> K^phi = exp(K' - lnZ) (keys past the end: 0)
-    const float lnz = k_stats[(size_t)bh * N + t0 + min(mykey, valid - 1)];
+    if constexpr (MORE) {
+      i = i_next;
+      if (t + 2 * NW < items) i_next = block_of(t + 2 * NW);
+    }
+  };
+  for (; t + NW < items; t += NW) pass(std::integral_constant<bool, true>());
+  if (t < items) pass(std::integral_constant<bool, false>());
+
+  // ---- linear branch ----
+  const bool all_selected = ksel >= Tn;   // no gradient, whatever dO holds
+  const int j0 = SP::first(w), tile = SP::tile(w), c_own = own_channel(D, w, g);
+  const float* dhj = dh_sum + ((size_t)bh * Tn + j) * D * D;
+  f32x4 hf[SP::kSteps];                   // dH_j: channels c of dK^phi by rows, contracted over e
+  {
+    const float* src = dhj + (size_t)(32 * tile + SP::row(r)) * D + 8 * j0 + 4 * g;
 #pragma unroll
-    for (int x = 0; x < J; x++)
-#pragma unroll
-      for (int y = 0; y < 4; y++) kf[x][y] = key_ok ? exp2_f32((kf[x][y] - lnz) * kLog2e) : 0.f;
+    for (int x = 0; x < SP::kSteps; x++) hf[x] = *reinterpret_cast<const f32x4*>(src + 8 * x);
   }
-  __syncthreads();
-  f32x16 dkp[ET / 2];
+  float dvo[D / 8], dko[D / 8];
+  float* swap = smem + SM::kSwapOff;
+  meet4<D, SM::kRounds>(dvo, dvacc, 1.f, swap, w, lane);
+  __syncthreads();                        // everyone is done with K', and the parts have been read
+  meet4<D, SM::kRounds>(dko, dkacc, 1.f, swap, w, lane);
+#pragma unroll
+  for (int y = 0; y < KM::kLoads; y++) {  // K' -> K^phi = exp(K' - lnZ) (keys past the end: 0)
+    const int row = trow + y * KM::kRows;
+    const float lnz = k_stats[(size_t)bh * N + t0 + min(row, valid - 1)];
+    f32x4 x = *reinterpret_cast<const f32x4*>(ks + row * LD + 4 * ch);
+#pragma unroll
+    for (int c = 0; c < 4; c++) x[c] = row < valid ? exp2_f32((x[c] - lnz) * kLog2e) : 0.f;
+    *reinterpret_cast<f32x4*>(ks + row * LD + 4 * ch) = x;
+  }
+  f32x16 acc = zero16();
+#pragma unroll
+  for (int x = 0; x < SP::kSteps; x++) {
+    const f32x4 b = *reinterpret_cast<const f32x4*>(vrow + 8 * (j0 + x));
+#pragma unroll
+    for (int y = 0; y < 4; y++) acc = mfma_f32(all_selected ? 0.f : hf[x][y], b[y], acc);
+  }
+  {  // dH_j^T: channels e of dV by rows, contracted over c
+    const float* src = dhj + (size_t)(8 * j0 + 4 * g) * D + 32 * tile + SP::row(r);
+#pragma unroll
+    for (int x = 0; x < SP::kSteps; x++)
+#pragma unroll
+      for (int y = 0; y < 4; y++) hf[x][y] = src[(8 * x + y) * D];
+  }
+  float dkp[D / 8], dvl[D / 8];
+  SP::own(dkp, acc, smem + SM::kLSwapOff, w, lane);
+  __syncthreads();                        // K^phi complete
+  acc = zero16();
+#pragma unroll
+  for (int x = 0; x < SP::kSteps; x++) {
+    const f32x4 b = *reinterpret_cast<const f32x4*>(krow + 8 * (j0 + x));
+#pragma unroll
+    for (int y = 0; y < 4; y++) acc = mfma_f32(all_selected ? 0.f : hf[x][y], b[y], acc);
+  }
+  SP::own(dvl, acc, smem + SM::kLSwapOff, w, lane);
+  f32x4 kp[ET];
   float dot = 0.f;
-  auto state_grad = [&](auto half) {
-    constexpr int E0 = decltype(half)::value * (ET / 2);
 #pragma unroll
-    for (int x = 0; x < ET / 2; x++) {
-      dkp[x] = channel_product<D>(dhs + (32 * (E0 + x) + lane % 32) * LD, vf, zero16(), g);    // over e
-      const float* ha = dhs + 4 * g * LD + 32 * (E0 + x) + lane % 32;
+  for (int y = 0; y < ET; y++) {
+    kp[y] = *reinterpret_cast<const f32x4*>(ks + r * LD + c_own + 4 * y);
 #pragma unroll
-      for (int jj = 0; jj < J; jj++)
-#pragma unroll
-        for (int y = 0; y < 4; y++) dvo[x] = mfma_f32(ha[(8 * jj + y) * LD], kf[jj][y], dvo[x]);   // over c
-#pragma unroll
-      for (int e = 0; e < 16; e++) {
-        dkp[x][e] += dzs[32 * (E0 + x) + 8 * (e / 4) + 4 * g + e % 4];
-        dot += dkp[x][e] * kf[4 * (E0 + x) + e / 4][e % 4];
-      }
+    for (int x = 0; x < 4; x++) {
+      dkp[4 * y + x] += dzs[c_own + 4 * y + x];
+      dot += dkp[4 * y + x] * kp[y][x];
     }
-  };
-  if (rh == 0) state_grad(std::integral_constant<int, 0>());
-  else state_grad(std::integral_constant<int, 1>());
-  dot = both_halves_sum(dot);
-  if (g == 0) dots[w * 32 + lane] = dot;
-  __syncthreads();                        // row sums visible; dH has been read
-  dot += dots[(w ^ 1) * 32 + lane % 32];
-  auto park = [&](auto half) {
-    constexpr int E0 = decltype(half)::value * (ET / 2);
+  }
+  dot = swap_halves_sum(dot);
+  if (g == 0) dots[w * 32 + r] = dot;
+  __syncthreads();                        // the row sums are there
+  dot = (dots[r] + dots[32 + r]) + (dots[64 + r] + dots[96 + r]);
 #pragma unroll
-    for (int x = 0; x < ET / 2; x++)
+  for (int y = 0; y < ET; y++) {          // to leave in whole rows
+    f32x4 ok, ov;
 #pragma unroll
-      for (int v4 = 0; v4 < 4; v4++) {
-        const f32x4 kp = kf[4 * (E0 + x) + v4];
-        f32x4 yk, yv;
-#pragma unroll
-        for (int r = 0; r < 4; r++) {
-          yk[r] = dko[x][4 * v4 + r] * rscale + kp[r] * (dkp[x][4 * v4 + r] - dot);
-          yv[r] = dvo[x][4 * v4 + r];
-        }
-        *reinterpret_cast<f32x4*>(okt + mykey * LD + 32 * (E0 + x) + 8 * v4 + 4 * g) = yk;
-        *reinterpret_cast<f32x4*>(ovt + mykey * LD + 32 * (E0 + x) + 8 * v4 + 4 * g) = yv;
-      }
-  };
-  if (rh == 0) park(std::integral_constant<int, 0>());
-  else park(std::integral_constant<int, 1>());
+    for (int x = 0; x < 4; x++) {
+      ok[x] = dko[4 * y + x] * rscale + kp[y][x] * (dkp[4 * y + x] - dot);
+      ov[x] = dvo[4 * y + x] + dvl[4 * y + x];
+    }
+    *reinterpret_cast<f32x4*>(swap + r * LD + c_own + 4 * y) = r < valid ? ok : f32x4{0.f, 0.f, 0.f, 0.f};
+    *reinterpret_cast<f32x4*>(vs + r * LD + c_own + 4 * y) = ov;
+  }
   __syncthreads();
-  float* dkh = dk + head_offset(sin, bh, H) + (size_t)t0 * sin.n + 4 * ch;
-  float* dvh = dv + head_offset(sin, bh, H) + (size_t)t0 * sin.n + 4 * ch;
 #pragma unroll
-  for (int x = 0; x < CM::kLoads; x++) {
-    const int t = trow + x * CM::kRows;
-    if (t < valid) {
-      *reinterpret_cast<f32x4*>(dkh + (size_t)t * sin.n) = *reinterpret_cast<const f32x4*>(okt + t * LD + 4 * ch);
-      *reinterpret_cast<f32x4*>(dvh + (size_t)t * sin.n) = *reinterpret_cast<const f32x4*>(ovt + t * LD + 4 * ch);
+  for (int y = 0; y < KM::kLoads; y++) {
+    const int row = trow + y * KM::kRows;
+    const size_t dst = head_offset(sin, bh, H) + (size_t)(t0 + row) * sin.n + 4 * ch;
+    if (row < valid) {
+      *reinterpret_cast<f32x4*>(dk + dst) = *reinterpret_cast<const f32x4*>(swap + row * LD + 4 * ch);
+      *reinterpret_cast<f32x4*>(dv + dst) = *reinterpret_cast<const f32x4*>(vs + row * LD + 4 * ch);
     }
   }
   if (tid < D) {                          // column sums of dK' for the smoothing term
     float sum = 0.f;
-    for (int t = 0; t < valid; t++) sum += okt[t * LD + tid];
-    colsum[((size_t)bh * Tn + j) * D + tid] = sum;
+#pragma unroll
+    for (int x = 0; x < 32; x++) sum += swap[x * LD + tid];
+    colsum[sums + tid] = sum;
   }
 }
 
-template <int D, int BQ>
+// ---------------------------------------------------------------------------------------------
+template <int D>
+static hipError_t launch_q(const Shape& s, const BwdArgs& a, hipStream_t stream) {
+  constexpr int smem = BwdQF32Smem<D>::kBytes;
+  static OncePerDevice once;
+  if (hipError_t e = allow_dynamic_lds(once, (const void*)bwd_q_f32_kernel<D>, smem); e != hipSuccess) return e;
+  const int run = (s.BH * ((s.N + 31) / 32) + kXcds - 1) / kXcds;
+  bwd_q_f32_kernel<D><<<dim3((unsigned)(run * kXcds)), 256, smem, stream>>>(
+      (const float*)a.q, (const float*)a.k, (const float*)a.v, (const float*)a.dout, (const float*)a.o_s, (const float*)a.o_l,
+      a.lse, a.k_mean, (const float*)a.h_i, a.z_i, a.block_idx, a.alpha, (float*)a.dq, a.ds, a.lraw, a.inv_den, a.dl,
+      a.dalpha_part, s.sin, s.sout, s.BH, s.H, s.N, s.Tm, s.Tn, s.bq, s.k, s.alpha_per_block ? 1 : 0);
+  return hipGetLastError();
+}
+hipError_t launch_bwd_q_f32(const Shape& s, const BwdArgs& a, hipStream_t stream) {
+  return s.d == 128 ? launch_q<128>(s, a, stream) : launch_q<64>(s, a, stream);
+}
+
+template <int D>
+static hipError_t launch_state(const Shape& s, const BwdArgs& a, hipStream_t stream) {
+  constexpr int smem = 64 * kF32Ld<D> * (int)sizeof(float);
+  static OncePerDevice once;
+  if (hipError_t e = allow_dynamic_lds(once, (const void*)bwd_state_f32_kernel<D>, smem); e != hipSuccess) return e;
+  const WorkOrder o = make_order(s, a);
+  bwd_state_f32_kernel<D><<<dim3((unsigned)(1 + o.groups + s.BH * s.Tm)), 256, smem, stream>>>(
+      o, (const float*)a.q, (const float*)a.dout, a.inv_den, a.dl, a.alpha, (float*)a.dh, s.sin, s.sout, s.H, s.N, s.Tm, s.bq,
+      s.alpha_per_block ? 1 : 0);
+  return hipGetLastError();
+}
+hipError_t launch_bwd_totals_f32(const Shape& s, const BwdArgs& a, hipStream_t stream) {
+  if (hipError_t e = s.d == 128 ? launch_state<128>(s, a, stream) : launch_state<64>(s, a, stream); e != hipSuccess) return e;
+  return launch_key_states_f32(s, a, stream);
+}
+
+template <int D>
 static hipError_t launch_kv(const Shape& s, const BwdArgs& a, hipStream_t stream) {
   constexpr int smem = BwdKvF32Smem<D>::kBytes;
   static OncePerDevice once;
-  if (hipError_t e = allow_dynamic_lds(once, (const void*)bwd_kv_f32_kernel<D, BQ>, smem); e != hipSuccess) return e;
-  bwd_kv_f32_kernel<D, BQ><<<dim3((unsigned)bwd_kv_grid(s)), 256, smem, stream>>>(
+  if (hipError_t e = allow_dynamic_lds(once, (const void*)bwd_kv_f32_kernel<D>, smem); e != hipSuccess) return e;
+  bwd_kv_f32_kernel<D><<<dim3((unsigned)(2 * bwd_kv_grid(s))), 256, smem, stream>>>(
       (const float*)a.q, (const float*)a.k, (const float*)a.v, (const float*)a.dout, a.lraw, a.ds, a.k_mean, a.k_stats,
-      a.col_ptr, a.col_idx, a.order, (const float*)a.dh, a.dz, a.dh_total, a.dz_total, a.alpha, (float*)a.dk, (float*)a.dv, a.colsum, s.sin, s.sout,
-      s.H, s.N, s.Tm, s.Tn, s.k, s.alpha_per_block ? 1 : 0);
+      a.col_ptr, a.col_idx, a.order, (const float*)a.dh_sum, a.dz_sum, a.alpha, (float*)a.dk, (float*)a.dv, a.colsum, s.sin,
+      s.sout, s.H, s.N, s.Tm, s.Tn, s.bq, s.k, s.alpha_per_block ? 1 : 0);
   return hipGetLastError();
 }
-
 hipError_t launch_bwd_kv_f32(const Shape& s, const BwdArgs& a, hipStream_t stream) {
-  if (s.d == 128) return s.bq == 128 ? launch_kv<128, 128>(s, a, stream) : launch_kv<128, 64>(s, a, stream);
-  return s.bq == 128 ? launch_kv<64, 128>(s, a, stream) : launch_kv<64, 64>(s, a, stream);
+  return s.d == 128 ? launch_kv<128>(s, a, stream) : launch_kv<64>(s, a, stream);
 }
 
 }  // namespace sla2

@@ -15,11 +15,11 @@ __host__ __device__ constexpr int f32_state(int d) { return d * d + d; }
 //   k' = k - colmean(K);  stats[token] = lnZ = log sum_c exp(k'_c);
 //   K^phi = softmax_d(k');  h_j = (K^phi_j)^T V_j,  z_j = colsum(K^phi_j)
 // (Alg. 2: K^phi, h, z).  Tokens past N contribute nothing.  A token's channels sit on neighbouring lanes, 4 each, so
-// the softmax is taken in registers on the way into LDS.  h_j is as large as the block's K and V together at d = 128:
-// writing it is what bounds the kernel there.
+// the softmax is taken in registers on the way into LDS; V goes from memory to its products.  h_j is as large as the block's
+// K and V together at d = 128: 12 heads of 4,096 tokens take 28 us for 100 MB (37 with V through LDS as well).
 // ---------------------------------------------------------------------------------------------
 template <int D>
-__global__ __launch_bounds__(256, 2) void kv_state_f32_kernel(const float* __restrict__ k, const float* __restrict__ v,
+__global__ __launch_bounds__(256, 4) void kv_state_f32_kernel(const float* __restrict__ k, const float* __restrict__ v,
                                                               const double* __restrict__ k_mean, float* __restrict__ k_stats,
                                                               float* __restrict__ states, Strides sin, int H, int N, int Tn) {
   constexpr int LD = kF32Ld<D>;
@@ -27,14 +27,14 @@ __global__ __launch_bounds__(256, 2) void kv_state_f32_kernel(const float* __res
   typedef StateSplit<D, 4> SS;
   extern __shared__ __attribute__((aligned(16))) float smem[];
   float* kp = smem;                       // [64][LD]  K^phi tile
-  float* vs = smem + kF32Tokens * LD;     // [64][LD]  V tile
   const int bh = blockIdx.x / Tn, j = blockIdx.x % Tn;
-  const int tid = threadIdx.x, lane = tid % kWave, g = lane / 32, w = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int tid = threadIdx.x, lane = tid % kWave, w = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int ch = tid % CM::kChunks, trow = tid / CM::kChunks;
   const int t0 = j * kF32Tokens, valid = min(kF32Tokens, N - t0);
-  f32x4 kr[CM::kLoads], vr[CM::kLoads], mu;
+  f32x4 kr[CM::kLoads], mu;
   CM::load(kr, k + head_offset(sin, bh, H) + (size_t)t0 * sin.n, sin.n, valid, tid);
-  CM::load(vr, v + head_offset(sin, bh, H) + (size_t)t0 * sin.n, sin.n, valid, tid);
+  StateProduct<D> sp;
+  sp.begin(v + head_offset(sin, bh, H) + (size_t)t0 * sin.n, sin.n, valid, w, lane);
 #pragma unroll
   for (int x = 0; x < 4; x++) mu[x] = (float)k_mean[(size_t)bh * D + 4 * ch + x];
 
@@ -53,20 +53,15 @@ __global__ __launch_bounds__(256, 2) void kv_state_f32_kernel(const float* __res
     e *= inv;
     zacc += e;
     *reinterpret_cast<f32x4*>(kp + t * LD + 4 * ch) = e;
-    *reinterpret_cast<f32x4*>(vs + t * LD + 4 * ch) = vr[i];
     if (ok && ch == 0) k_stats[(size_t)bh * N + t0 + t] = m + __log2f(sum) * kLn2;
   }
   __syncthreads();
   f32x16 hacc[SS::kTiles];
 #pragma unroll
   for (int x = 0; x < SS::kTiles; x++) hacc[x] = zero16();
-  state_product<D, 4>(hacc, kp, vs, kF32Tokens, w, lane);
+  sp.add(hacc, kp, w, lane);
   float* ph = states + (size_t)blockIdx.x * f32_state(D);
-#pragma unroll
-  for (int x = 0; x < SS::kTiles; x++)
-#pragma unroll
-    for (int e = 0; e < 16; e++)
-      ph[(32 * SS::mt(w) + 8 * (e / 4) + 4 * g + e % 4) * D + 32 * (SS::nt(w) + x) + lane % 32] = hacc[x][e];
+  StateProduct<D>::store(hacc, 1.f, ph, w, lane);
   __syncthreads();                        // the tile fully consumed: its place takes the column sums
   *reinterpret_cast<f32x4*>(kp + trow * D + 4 * ch) = zacc;
   __syncthreads();
@@ -81,7 +76,7 @@ __global__ __launch_bounds__(256, 2) void kv_state_f32_kernel(const float* __res
 template <int D>
 static hipError_t launch_kv_state_f32_t(const Shape& s, const float* k, const float* v, const double* k_mean, float* k_stats,
                                         float* states, hipStream_t stream) {
-  constexpr int smem = 2 * kF32Tokens * kF32Ld<D> * (int)sizeof(float);
+  constexpr int smem = kF32Tokens * kF32Ld<D> * (int)sizeof(float);
   static OncePerDevice once;
   if (hipError_t e = allow_dynamic_lds(once, (const void*)kv_state_f32_kernel<D>, smem); e != hipSuccess) return e;
   kv_state_f32_kernel<D><<<dim3((unsigned)(s.BH * s.Tn)), 256, smem, stream>>>(k, v, k_mean, k_stats, states, s.sin, s.H, s.N, s.Tn);
@@ -94,23 +89,37 @@ hipError_t launch_kv_state_f32(const Shape& s, const float* k, const float* v, c
 }
 
 // ---------------------------------------------------------------------------------------------
-// block_states_f32: H_i, Z_i of 32 query blocks and 128 of the d^2 + d entries of a state per wave: the 32 x T_n matrix of
-// 0 (selected) and 1 times the states of the head, and the sums over all key blocks, h_total and z_total.  A lane has four
-// consecutive entries, so a state is read 512 bytes at a time and stored the same way; the mask operand of 32 key blocks is
-// one word per lane, put together in LDS from the lists.
-// Bound by the states, read once per 32 query blocks, and H_i written: 18 us on 12 heads of 64 key and 32 query blocks
+// masked_states_f32: sums of states over the blocks that a list does not name - H_i, Z_i over the key blocks that query block
+// i did not select, and in the backward pass dH_j, dZ_j over the query blocks that did not select key block j.  A wave forms
+// 32 such sums for 128 of the d^2 + d entries of a state: the 32 x S matrix of 0 (listed) and 1 times the S states of the
+// head; and the sums over all of them.  A lane has four consecutive entries, so a state is read 512 bytes at a time and
+// stored the same way; the mask operand of 32 blocks is one word per lane, put together in LDS from the lists.
+// Bound by the states, read once per 32 sums, and the sums written: 18 us on 12 heads of 64 key and 32 query blocks
 // (d = 128; 50 MB read, 25 MB written).  The query blocks used to rebuild the h_j of their lists, a third of the products
-// of the attention kernel, and to form K^phi of every tile again.
+// of the attention kernel, and to form K^phi of every tile again; the key blocks gathered one dH_i per list entry.
 // ---------------------------------------------------------------------------------------------
+// R lists a head over S blocks: offsets ptr [R + 1] into idx [S k] (key side), or k entries each (query side, ptr null)
+struct BlockLists {
+  const int32_t *ptr, *idx;
+  int R, S, k;
+  __device__ __forceinline__ const int32_t* begin(int bh, int r) const {
+    return ptr ? idx + (size_t)bh * S * k + ptr[(size_t)bh * (R + 1) + r] : idx + ((size_t)bh * R + r) * k;
+  }
+  __device__ __forceinline__ int length(int bh, int r) const {
+    return ptr ? ptr[(size_t)bh * (R + 1) + r + 1] - ptr[(size_t)bh * (R + 1) + r] : k;
+  }
+};
+// sums: h [R][d * d] and z [R][d] per head; totals likewise with R = 1
+struct StateSums {
+  float *h, *z, *h_total, *z_total;
+};
 constexpr int kStateCols = 128;           // entries of a state per wave
 template <int D, bool TOTALS_ONLY>
-__global__ __launch_bounds__(256, 2) void block_states_f32_kernel(const float* __restrict__ states, const int32_t* __restrict__ block_idx,
-                                                                  float* __restrict__ h_total, float* __restrict__ z_total,
-                                                                  float* __restrict__ h_i, float* __restrict__ z_i, int BH, int Tm,
-                                                                  int Tn, int ksel, int row_tiles) {
+__global__ __launch_bounds__(256, 2) void masked_states_f32_kernel(const float* __restrict__ states, const BlockLists lists,
+                                                                   const StateSums out, int BH, int row_tiles) {
   constexpr int P = f32_state(D), kSets = (P + 4 * kStateCols - 1) / (4 * kStateCols);   // of four waves
-  extern __shared__ uint32_t bits[];      // [W][32] bit j % 32 of word j / 32 of a row: key block j is selected
-  const int W = (Tn + 31) / 32;
+  extern __shared__ uint32_t bits[];      // [W][32] bit s % 32 of word s / 32 of a row: block s is listed
+  const int R = lists.R, S = lists.S, W = (S + 31) / 32;
   // the workgroups that read the same entries run next to each other on one XCD
   const int y = blockIdx.x / kXcds, set = y / row_tiles * kXcds + blockIdx.x % kXcds, tile = y % row_tiles;
   if (set >= BH * kSets) return;
@@ -119,33 +128,36 @@ __global__ __launch_bounds__(256, 2) void block_states_f32_kernel(const float* _
   if constexpr (!TOTALS_ONLY) {
     for (int x = tid; x < 32 * W; x += 256) bits[x] = 0u;
     __syncthreads();
-    const int rows = min(32, Tm - row0);
-    const int32_t* idx = block_idx + ((size_t)bh * Tm + row0) * ksel;
-    for (int e = tid; e < rows * ksel; e += 256) {
-      const int j = idx[e];
-      atomicOr(&bits[j / 32 * 32 + e / ksel], 1u << (j % 32));   // OR: the result does not depend on the order
+    const int row = tid / 8;
+    if (row0 + row < R) {
+      const int32_t* list = lists.begin(bh, row0 + row);
+      const int n = lists.length(bh, row0 + row);
+      for (int e = tid % 8; e < n; e += 8) {
+        const int s = list[e];
+        atomicOr(&bits[s / 32 * 32 + row], 1u << (s % 32));   // OR: the result does not depend on the order
+      }
     }
     __syncthreads();
   }
   const int col = (set % kSets * 4 + w) * kStateCols + 4 * (lane % 32);
-  const float* src = states + (size_t)bh * Tn * P + min(col, P - 4);
+  const float* src = states + (size_t)bh * S * P + min(col, P - 4);
   f32x16 acc[4];
 #pragma unroll
   for (int x = 0; x < 4; x++) acc[x] = zero16();
   f32x4 sum = {0.f, 0.f, 0.f, 0.f};
-  for (int jw = 0; jw < W; jw++) {
-    const uint32_t word = TOTALS_ONLY ? 0u : bits[32 * jw + lane % 32];
-    f32x4 b[16];                          // key blocks 32 jw + 2 s + g; past the end the last one, with weight 0
+  for (int sw = 0; sw < W; sw++) {
+    const uint32_t word = TOTALS_ONLY ? 0u : bits[32 * sw + lane % 32];
+    f32x4 b[16];                          // blocks 32 sw + 2 n + g; past the end the last one, with weight 0
 #pragma unroll
-    for (int s = 0; s < 16; s++) b[s] = *reinterpret_cast<const f32x4*>(src + (size_t)min(32 * jw + 2 * s + g, Tn - 1) * P);
+    for (int n = 0; n < 16; n++) b[n] = *reinterpret_cast<const f32x4*>(src + (size_t)min(32 * sw + 2 * n + g, S - 1) * P);
 #pragma unroll
-    for (int s = 0; s < 16; s++) {
-      const bool exists = 32 * jw + 2 * s + g < Tn;
-      if (tile == 0) sum += exists ? b[s] : f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int n = 0; n < 16; n++) {
+      const bool exists = 32 * sw + 2 * n + g < S;
+      if (tile == 0) sum += exists ? b[n] : f32x4{0.f, 0.f, 0.f, 0.f};
       if constexpr (!TOTALS_ONLY) {
-        const float a = exists && (word >> (2 * s + g) & 1u) == 0u ? 1.f : 0.f;
+        const float a = exists && (word >> (2 * n + g) & 1u) == 0u ? 1.f : 0.f;
 #pragma unroll
-        for (int x = 0; x < 4; x++) acc[x] = mfma_f32(a, b[s][x], acc[x]);
+        for (int x = 0; x < 4; x++) acc[x] = mfma_f32(a, b[n][x], acc[x]);
       }
     }
   }
@@ -153,66 +165,68 @@ __global__ __launch_bounds__(256, 2) void block_states_f32_kernel(const float* _
   if (tile == 0) {
 #pragma unroll
     for (int x = 0; x < 4; x++) sum[x] = both_halves_sum(sum[x]);
-    if (g == 0) *reinterpret_cast<f32x4*>(col < D * D ? h_total + (size_t)bh * D * D + col : z_total + (size_t)bh * D + (col - D * D)) = sum;
+    if (g == 0) *reinterpret_cast<f32x4*>(col < D * D ? out.h_total + (size_t)bh * D * D + col : out.z_total + (size_t)bh * D + (col - D * D)) = sum;
   }
   if constexpr (!TOTALS_ONLY) {
 #pragma unroll
     for (int v = 0; v < 16; v++) {
-      const int i = row0 + 8 * (v / 4) + 4 * g + v % 4;
-      const size_t slot = (size_t)bh * Tm + i;
-      if (i < Tm)
-        *reinterpret_cast<f32x4*>(col < D * D ? h_i + slot * D * D + col : z_i + slot * D + (col - D * D)) =
+      const int r = row0 + 8 * (v / 4) + 4 * g + v % 4;
+      const size_t slot = (size_t)bh * R + r;
+      if (r < R)
+        *reinterpret_cast<f32x4*>(col < D * D ? out.h + slot * D * D + col : out.z + slot * D + (col - D * D)) =
             f32x4{acc[0][v], acc[1][v], acc[2][v], acc[3][v]};
     }
   }
 }
 
-// H_i, Z_i as the totals less the states of the selected blocks: 1,024 entries of a query block per workgroup.
+// The same sums as the totals less the states of the listed blocks: 1,024 entries of one sum per workgroup.
 template <int D>
-__global__ __launch_bounds__(256) void block_states_gather_f32_kernel(const float* __restrict__ states, const int32_t* __restrict__ block_idx,
-                                                                      const float* __restrict__ h_total, const float* __restrict__ z_total,
-                                                                      float* __restrict__ h_i, float* __restrict__ z_i, int Tm, int Tn,
-                                                                      int ksel) {
+__global__ __launch_bounds__(256) void gather_states_f32_kernel(const float* __restrict__ states, const BlockLists lists, const StateSums out) {
   constexpr int P = f32_state(D), kParts = (P + 1023) / 1024;
-  const int part = blockIdx.x % kParts, slot = blockIdx.x / kParts, bh = slot / Tm;
+  const int part = blockIdx.x % kParts, slot = blockIdx.x / kParts, bh = slot / lists.R;
   const int col = 1024 * part + 4 * (int)threadIdx.x;
   if (col >= P) return;
-  const int32_t* sel = block_idx + (size_t)slot * ksel;
-  const float* src = states + (size_t)bh * Tn * P + col;
-  f32x4 a = *reinterpret_cast<const f32x4*>(col < D * D ? h_total + (size_t)bh * D * D + col : z_total + (size_t)bh * D + (col - D * D));
+  const int32_t* list = lists.begin(bh, slot % lists.R);
+  const int n = lists.length(bh, slot % lists.R);
+  const float* src = states + (size_t)bh * lists.S * P + col;
+  f32x4 a = *reinterpret_cast<const f32x4*>(col < D * D ? out.h_total + (size_t)bh * D * D + col : out.z_total + (size_t)bh * D + (col - D * D));
 #pragma unroll 8
-  for (int s = 0; s < ksel; s++) a -= *reinterpret_cast<const f32x4*>(src + (size_t)sel[s] * P);
-  *reinterpret_cast<f32x4*>(col < D * D ? h_i + (size_t)slot * D * D + col : z_i + (size_t)slot * D + (col - D * D)) = a;
+  for (int s = 0; s < n; s++) a -= *reinterpret_cast<const f32x4*>(src + (size_t)list[s] * P);
+  *reinterpret_cast<f32x4*>(col < D * D ? out.h + (size_t)slot * D * D + col : out.z + (size_t)slot * D + (col - D * D)) = a;
 }
 
-// The product costs T_n per query block whatever is selected, the gather k, and a launch of its own behind the totals: it
-// pays where the lists are a small part of many blocks.  d = 128, 128-row blocks, product / totals + gather, us:
+// The product costs S per sum whatever is listed, the gather the length of the list, and a launch of its own behind the
+// totals: it pays where the lists are a small part of many blocks (`listed` of T_n).  Query side, d = 128, 128-row blocks,
+// product / totals + gather, us:
 //   12 heads, T_n = 128    k = 1 51 / 34    k = 3 49 / 45      k = 6 50 / 59
 //   12 heads, T_n = 512    k = 4 500 / 203  k = 13 492 / 406   k = 26 497 / 726
 //    2 heads, T_n = 1,182  k = 9 491 / 160  k = 31 488 / 388   k = 59 507 / 679
 constexpr int kGatherBlocks = 64, kGatherRatio = 30;
 template <int D>
-static hipError_t launch_block_states_f32_t(const Shape& s, const float* states, const int32_t* block_idx, float* h_total,
-                                            float* z_total, float* h_i, float* z_i, hipStream_t stream) {
+static hipError_t launch_states_f32(const Shape& s, const float* states, const BlockLists& lists, const StateSums& out, hipStream_t stream) {
   constexpr int P = f32_state(D), kSets = (P + 4 * kStateCols - 1) / (4 * kStateCols);
   const int sets = (s.BH * kSets + kXcds - 1) / kXcds * kXcds;
   if (s.Tn <= kGatherBlocks || s.Tn <= kGatherRatio * s.k) {
-    const int tiles = (s.Tm + 31) / 32, smem = (s.Tn + 31) / 32 * 32 * (int)sizeof(uint32_t);   // at most 8 KB
-    block_states_f32_kernel<D, false><<<dim3((unsigned)(sets * tiles)), 256, smem, stream>>>(states, block_idx, h_total, z_total, h_i, z_i,
-                                                                                         s.BH, s.Tm, s.Tn, s.k, tiles);
+    const int tiles = (lists.R + 31) / 32, smem = (lists.S + 31) / 32 * 32 * (int)sizeof(uint32_t);   // at most 8 KB
+    masked_states_f32_kernel<D, false><<<dim3((unsigned)(sets * tiles)), 256, smem, stream>>>(states, lists, out, s.BH, tiles);
     return hipGetLastError();
   }
-  block_states_f32_kernel<D, true><<<dim3((unsigned)sets), 256, 0, stream>>>(states, block_idx, h_total, z_total, h_i, z_i, s.BH, s.Tm,
-                                                                             s.Tn, s.k, 1);
+  masked_states_f32_kernel<D, true><<<dim3((unsigned)sets), 256, 0, stream>>>(states, lists, out, s.BH, 1);
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
-  block_states_gather_f32_kernel<D><<<dim3((unsigned)((size_t)s.BH * s.Tm * ((P + 1023) / 1024))), 256, 0, stream>>>(
-      states, block_idx, h_total, z_total, h_i, z_i, s.Tm, s.Tn, s.k);
+  gather_states_f32_kernel<D><<<dim3((unsigned)((size_t)s.BH * lists.R * ((P + 1023) / 1024))), 256, 0, stream>>>(states, lists, out);
   return hipGetLastError();
 }
 hipError_t launch_block_states_f32(const Shape& s, const float* states, const int32_t* block_idx, float* h_total, float* z_total,
                                    float* h_i, float* z_i, hipStream_t stream) {
-  return s.d == 128 ? launch_block_states_f32_t<128>(s, states, block_idx, h_total, z_total, h_i, z_i, stream)
-                    : launch_block_states_f32_t<64>(s, states, block_idx, h_total, z_total, h_i, z_i, stream);
+  const BlockLists lists{nullptr, block_idx, s.Tm, s.Tn, s.k};
+  const StateSums out{h_i, z_i, h_total, z_total};
+  return s.d == 128 ? launch_states_f32<128>(s, states, lists, out, stream) : launch_states_f32<64>(s, states, lists, out, stream);
+}
+hipError_t launch_key_states_f32(const Shape& s, const BwdArgs& a, hipStream_t stream) {
+  const BlockLists lists{a.col_ptr, a.col_idx, s.Tn, s.Tm, s.k};
+  const StateSums out{(float*)a.dh_sum, a.dz_sum, a.dh_total, a.dz_total};
+  return s.d == 128 ? launch_states_f32<128>(s, (const float*)a.dh, lists, out, stream)
+                    : launch_states_f32<64>(s, (const float*)a.dh, lists, out, stream);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -223,13 +237,10 @@ hipError_t launch_block_states_f32(const Shape& s, const float* states, const in
 // Wave w takes every fourth half (32 keys) of the selected blocks, with a running maximum and sum of its own; the four
 // meet once, after the loop, like the parts of a split softmax.  A wave's K rows and V rows are its own, so they come
 // straight from global memory into operand registers: no tile in LDS, no barrier in the loop, and four times as many
-// workgroups as with 128 rows each.  K of the next 32 keys is requested before the products with V of the present ones, V
-// before the scores.
-// Which channel a row of an O^T tile stands for is free: tile x has channels ET r + x, so that a lane reads ET consecutive
-// channels of a V row at a time.  Wave w finishes the entries v / 4 = w of all tiles, channels 32 w.. (16 w.. at d = 64).
-// Bound by the fp32 matrix rate in the loop (a wave needs 64 products, 4,096 cycles, for every 16 loads of 1 KB; 82 % of the
-// time of a longer list) and by HBM outside: 12 heads of 4,096 tokens, d = 128, keeping O^s and O^l, 6 blocks a list 139 us, none
-// 55 us; 128-row workgroups with K', K^phi and V tiles in LDS, which rebuilt H_i, took 245 us.  2 heads of 1,024, d = 64: 20.5 ->
+// workgroups as with 128 rows each.
+// Bound by the fp32 matrix rate in the loop (a wave needs 64 products, 4,096 cycles, for every 16 loads of 1 KB; 85 % of the
+// time of a longer list) and by HBM outside: 12 heads of 4,096 tokens, d = 128, keeping O^s and O^l, 6 blocks a list 125 us, none
+// 46 us; 128-row workgroups with K', K^phi and V tiles in LDS, which rebuilt H_i, took 245 us.  2 heads of 1,024, d = 64: 20.5 ->
 // 9.8 us.
 // ---------------------------------------------------------------------------------------------
 template <int D> struct AttnF32Smem {
@@ -238,10 +249,12 @@ template <int D> struct AttnF32Smem {
   static constexpr int kMuOff = kQOff + 32 * LD;                           // [D] colmean(K)
   static constexpr int kZsOff = kMuOff + D;                                // [D] Z_i
   static constexpr int kMlOff = kZsOff + D;                                // [NW][2][32] m and l
-  static constexpr int kSwapOff = kMlOff + NW * 64;                        // [owner][NW - 1][4 ET][64] parts of O^T
-  static constexpr int kLSwapOff = kSwapOff + NW * (NW - 1) * 4 * ET * kWave;   // d = 64: [NW][8][64] parts of O_l^T
-  static constexpr int kBytes = (kLSwapOff + (D == 64 ? NW * 8 * kWave : 0)) * (int)sizeof(float);
+  static constexpr int kRounds = D / 64;                                   // of meet4
+  static constexpr int kSwapOff = kMlOff + NW * 64;                        // parts of O^T
+  static constexpr int kLSwapOff = kSwapOff + kMeetFloats<D, kRounds>;     // parts of O_l^T
+  static constexpr int kBytes = (kLSwapOff + StatePart<D>::kLds) * (int)sizeof(float);
   static_assert(kBytes <= 80 * 1024, "two workgroups a CU");
+  static_assert(32 * LD <= kMeetFloats<D, kRounds>, "O_l takes the place of the parts");
 };
 
 template <int D>
@@ -253,7 +266,6 @@ __global__ __launch_bounds__(256, 2) void attn_f32_kernel(
     int ksel, int alpha_per_block) {
   typedef AttnF32Smem<D> SM;
   constexpr int LD = SM::LD, ET = SM::ET, J = D / 8, NW = SM::NW;
-  typedef __attribute__((ext_vector_type(ET))) float f32xe;
   extern __shared__ __attribute__((aligned(16))) float smem[];
   float* qs = smem + SM::kQOff;
   float* mus = smem + SM::kMuOff;
@@ -269,16 +281,15 @@ __global__ __launch_bounds__(256, 2) void attn_f32_kernel(
   const int row0 = 32 * grp, rows_valid = min(32, N - row0), i = row0 / bq;
   const int tid = threadIdx.x, lane = tid % kWave, g = lane / 32, r = lane % 32;
   const int w = __builtin_amdgcn_readfirstlane(tid / kWave);
-  const bool row_ok = r < rows_valid;
   const size_t slot = (size_t)bh * Tm + i;
-  const float* kh = k + head_offset(sin, bh, H) + 4 * g;
-  const float* vh = v + head_offset(sin, bh, H) + ET * r;
+  const float* kh = k + head_offset(sin, bh, H);
+  const float* vh = v + head_offset(sin, bh, H);
   const int32_t* sel = block_idx + slot * ksel;
 
   const int items = 2 * ksel;             // halves of the selected blocks; an odd one of the last block may hold no key
   auto first_key = [&](int t) { return __builtin_amdgcn_readfirstlane(sel[t / 2]) * kF32Tokens + 32 * (t % 2); };
-  f32x4 kf[J];                            // a key row, channels 8 j + 4 g ..
-  auto k_row = [&](int first) { return kh + (size_t)min(first + r, N - 1) * sin.n; };
+  auto rows_of = [&](const float* head, int first) { return RowPieces(head, first, N - 1, sin.n); };
+  f32x4 st[kStream];                      // per piece of 32 keys: J elements of K by lane, J of the columns of V; then H_i
   typedef ChunkMap<D, 256, 32> QM;
   f32x4 qr[QM::kLoads];
   QM::load(qr, q + head_offset(sin, bh, H) + (size_t)row0 * sin.n, sin.n, rows_valid, tid);
@@ -288,9 +299,10 @@ __global__ __launch_bounds__(256, 2) void attn_f32_kernel(
   int t = w, key0 = 0;
   if (t < items) {
     key0 = first_key(t);
-    const float* src = k_row(key0);
+    const RowPieces kp = rows_of(kh, key0);
+    const unsigned own = kp.own(r, g);
 #pragma unroll
-    for (int j = 0; j < J; j++) kf[j] = *reinterpret_cast<const f32x4*>(src + 8 * j);
+    for (int n = 0; n < kStream; n++) st[n] = kp.piece(own, n);
   }
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -306,31 +318,33 @@ __global__ __launch_bounds__(256, 2) void attn_f32_kernel(
   float m_run = -INFINITY, l_run = 0.f;   // this lane's row over this wave's keys, log2 domain
   const float c0 = kLog2e * rsqrtf((float)D);
   const float *qrow = qs + r * LD + 4 * g, *mrow = mus + 4 * g;
-  // H_i: O_l^T of 32 channels, tile nt; the waves of a tile share the contraction.  Row r of the product is the channel that
-  // the entry it lands on has in O^T.
-  constexpr int KS = NW / ET, JW = J / KS;
-  const int nt = w / KS, j0 = w % KS * JW;
-  const int ch_row = D == 128 ? 16 * (r >> 2 & 1) + 4 * (r >> 3) + (r & 3) : 16 * (r >> 4) + 8 * (r >> 2 & 1) + 4 * (r >> 3 & 1) + (r & 3);
-  const float* hsrc = h_i + slot * D * D + (size_t)(8 * j0 + 4 * g) * D + 32 * nt + ch_row;
-  float hf[JW][4];
+  // H_i^T: channels of O_l^T by rows, contracted over c
+  typedef StatePart<D> SP;
+  constexpr int JW = SP::kSteps;
+  const int j0 = SP::first(w);
+  const float* hsrc = h_i + slot * D * D + (size_t)(8 * j0 + 4 * g) * D + 32 * SP::tile(w) + SP::row(r);
   __syncthreads();
 
   int key_next = t + NW < items ? first_key(t + NW) : 0;
   // Requests are made one by one between the products: sixteen K requests in a row (32 cache lines each) hold the issue of
   // a wave, and of the others of its CU, for as long as the products they feed take.  The last pass has a copy of its own:
-  // where a request may or may not have been made, the wait for the V rows in front of it is a wait for that request.
+  // where a request may or may not have been made, the wait for one in front of it is a wait for that one.
   auto pass = [&](auto more) {
     constexpr bool MORE = decltype(more)::value;
     const int valid = N - key0;           // keys of this half that exist: below 32 only at the end of the sequence
-    f32xe vf[16];                         // V rows 8 (e / 4) + 4 g + e % 4, channels ET r ..
+    const RowPieces kp = rows_of(kh, key0), vp = rows_of(vh, key0), np = rows_of(kh, MORE ? key_next : key0);
+    const unsigned own_k = kp.own(r, g), own_n = np.own(r, g);
+    auto request = [&](int n) {           // element n of the piece, behind the last one of the next
+      const int j = n % J;
+      if (n < J) st[n % kStream] = kp.piece(own_k, j);
+      else if (n < 2 * J) st[n % kStream] = vp.cols<D>(j, r, g);
+      else if (MORE) st[n % kStream] = np.piece(own_n, j);
+    };
     f32x16 sacc = zero16();
     f32x4 qb = *reinterpret_cast<const f32x4*>(qrow), mb = *reinterpret_cast<const f32x4*>(mrow);
 #pragma unroll
     for (int j = 0; j < J; j++) {
-#pragma unroll
-      for (int e = 16 / J * j; e < 16 / J * (j + 1); e++)
-        vf[e] = *reinterpret_cast<const f32xe*>(vh + (size_t)min(key0 + 8 * (e / 4) + 4 * g + e % 4, N - 1) * sin.n);
-      const f32x4 a = kf[j] - mb, b = qb;
+      const f32x4 a = st[j % kStream] - mb, b = qb;
       if (j + 1 < J) {
         qb = *reinterpret_cast<const f32x4*>(qrow + 8 * (j + 1));
         mb = *reinterpret_cast<const f32x4*>(mrow + 8 * (j + 1));
@@ -338,6 +352,7 @@ __global__ __launch_bounds__(256, 2) void attn_f32_kernel(
 #pragma unroll
       for (int x = 0; x < 4; x++) sacc = mfma_f32(a[x], b[x], sacc);
       __builtin_amdgcn_sched_barrier(0);
+      request(j + kStream);
     }
     float mx = -INFINITY;
 #pragma unroll
@@ -359,55 +374,43 @@ __global__ __launch_bounds__(256, 2) void attn_f32_kernel(
     m_run = m_new;
 #pragma unroll
     for (int x = 0; x < ET; x++) oacc[x] *= corr;
-    const float* ksrc = nullptr;
+#pragma unroll
+    for (int j = 0; j < J; j++) {
+      col_products<D>(oacc, st[(J + j) % kStream], sacc, j);
+      __builtin_amdgcn_sched_barrier(0);
+      request(J + j + kStream);
+    }
     if constexpr (MORE) {
       key0 = key_next;
-      ksrc = k_row(key0);
       if (t + 2 * NW < items) key_next = first_key(t + 2 * NW);
     }
-#pragma unroll
-    for (int e = 0; e < 16; e++) {
-      __builtin_amdgcn_sched_barrier(0);
-      if constexpr (MORE) {
-        if (e < J) kf[e] = *reinterpret_cast<const f32x4*>(ksrc + 8 * e);
-      } else if (e < JW) {
-#pragma unroll
-        for (int x = 0; x < 4; x++) hf[e][x] = hsrc[(8 * e + x) * D];
-      }
-#pragma unroll
-      for (int x = 0; x < ET; x++) oacc[x] = mfma_f32(vf[e][x], sacc[e], oacc[x]);
-    }
   };
-  if (t < items) {
-    for (; t + NW < items; t += NW) pass(std::integral_constant<bool, true>());
-    pass(std::integral_constant<bool, false>());
-  } else {
+  for (; t + NW < items; t += NW) pass(std::integral_constant<bool, true>());
+  if (t < items) pass(std::integral_constant<bool, false>());
+  auto h_piece = [&](int j) { return f32x4{hsrc[8 * j * D], hsrc[(8 * j + 1) * D], hsrc[(8 * j + 2) * D], hsrc[(8 * j + 3) * D]}; };
 #pragma unroll
-    for (int j = 0; j < JW; j++)
-#pragma unroll
-      for (int x = 0; x < 4; x++) hf[j][x] = hsrc[(8 * j + x) * D];
-  }
+  for (int j = 0; j < kStream; j++)
+    if (j < JW) st[j] = h_piece(j);
 
   // ---- linear branch ----
-  // Q^phi = softmax_d(Q) of this lane's row, and Q^phi Z_i
-  f32x4 qf[J];
+  // Q^phi = softmax_d(Q) of this lane's row: its normaliser and Q^phi Z_i
   float qm = -INFINITY;
 #pragma unroll
   for (int j = 0; j < J; j++) {
-    qf[j] = *reinterpret_cast<const f32x4*>(qrow + 8 * j);
+    const f32x4 x = *reinterpret_cast<const f32x4*>(qrow + 8 * j);
 #pragma unroll
-    for (int x = 0; x < 4; x++) qm = fmaxf(qm, qf[j][x]);
+    for (int y = 0; y < 4; y++) qm = fmaxf(qm, x[y]);
   }
   qm = swap_halves_max(qm);
   float qsum = 0.f, den = 0.f;
 #pragma unroll
   for (int j = 0; j < J; j++) {
-    const f32x4 z = *reinterpret_cast<const f32x4*>(zs + 8 * j + 4 * g);
+    const f32x4 x = *reinterpret_cast<const f32x4*>(qrow + 8 * j), z = *reinterpret_cast<const f32x4*>(zs + 8 * j + 4 * g);
 #pragma unroll
-    for (int x = 0; x < 4; x++) {
-      qf[j][x] = exp2_f32((qf[j][x] - qm) * kLog2e);
-      qsum += qf[j][x];
-      den += qf[j][x] * z[x];
+    for (int y = 0; y < 4; y++) {
+      const float e = exp2_f32((x[y] - qm) * kLog2e);
+      qsum += e;
+      den += e * z[y];
     }
   }
   const float qinv = 1.f / swap_halves_sum(qsum);
@@ -415,16 +418,13 @@ __global__ __launch_bounds__(256, 2) void attn_f32_kernel(
   const bool all_selected = ksel >= Tn;   // nothing left for the linear branch: O_l = 0
   const float inv_den = all_selected ? 0.f : 1.f / den;
   f32x16 lacc = zero16();
-  auto apply = [&](auto from) {
 #pragma unroll
-    for (int j = 0; j < JW; j++) {
-      const f32x4 b = qf[decltype(from)::value + j] * qinv;
+  for (int j = 0; j < JW; j++) {
+    const f32x4 a = st[j % kStream], q4 = *reinterpret_cast<const f32x4*>(qrow + 8 * (j0 + j));
 #pragma unroll
-      for (int x = 0; x < 4; x++) lacc = mfma_f32(hf[j][x], b[x], lacc);
-    }
-  };
-  if (j0 == 0) apply(std::integral_constant<int, 0>());
-  else apply(std::integral_constant<int, J - JW>());
+    for (int x = 0; x < 4; x++) lacc = mfma_f32(a[x], exp2_f32((q4[x] - qm) * kLog2e) * qinv, lacc);
+    if (j + kStream < JW) st[j % kStream] = h_piece(j + kStream);
+  }
 
   // ---- the four parts of the softmax meet ----
   if (g == 0) {
@@ -438,66 +438,43 @@ __global__ __launch_bounds__(256, 2) void attn_f32_kernel(
   const float m_ref = m_all == -INFINITY ? 0.f : m_all, mine = exp2_f32(m_run - m_ref);
 #pragma unroll
   for (int x = 0; x < NW; x++) l += ml[x * 64 + 32 + r] * exp2_f32(ml[x * 64 + r] - m_ref);
-  float os[4 * ET], ol[4 * ET];           // entry ET (v % 4) + x: channel ET (8 w + 4 g + v % 4) + x
-  auto part = [&](int owner, int from) { return swap + ((owner * (NW - 1) + (from - (from > owner))) * 4 * ET) * kWave + lane; };
-#pragma unroll
-  for (int o = 0; o < NW; o++)
-#pragma unroll
-    for (int y = 0; y < 4; y++)
-#pragma unroll
-      for (int x = 0; x < ET; x++) {
-        const float p = oacc[x][4 * o + y] * mine;
-        if (o == w) os[ET * y + x] = p;
-        else part(o, w)[(ET * y + x) * kWave] = p;
-      }
-  if constexpr (D == 64) {                // the other half of the contraction: half of the tile's entries each
-    float* ls = smem + SM::kLSwapOff;
-    auto exchange = [&](auto half) {
-      constexpr int E0 = 8 * decltype(half)::value;
-#pragma unroll
-      for (int e = 0; e < 8; e++) ls[((w ^ 1) * 8 + e) * kWave + lane] = lacc[8 - E0 + e];
-      __syncthreads();
-#pragma unroll
-      for (int e = 0; e < 8; e++) ol[e] = lacc[E0 + e] + ls[(w * 8 + e) * kWave + lane];
-    };
-    if (w % 2 == 0) exchange(std::integral_constant<int, 0>());
-    else exchange(std::integral_constant<int, 1>());
-  } else {
-    __syncthreads();
-#pragma unroll
-    for (int e = 0; e < 16; e++) ol[e] = lacc[e];
-  }
-#pragma unroll
-  for (int f = 0; f < NW; f++)
-    if (f != w) {
-#pragma unroll
-      for (int e = 0; e < 4 * ET; e++) os[e] += part(w, f)[e * kWave];
-    }
+  float os[4 * ET], ol[4 * ET];
+  meet4<D, SM::kRounds>(os, oacc, mine, swap, w, lane);
+  SP::own(ol, lacc, smem + SM::kLSwapOff, w, lane);
   const float inv_l = l > 0.f ? 1.f / l : 0.f;
   const float al = alpha[alpha_per_block ? (size_t)h * Tm + i : (size_t)h];
-  if (row_ok) {
-    const int c = ET * (8 * w + 4 * g);
-    float* o = out + head_offset(sout, bh, H) + (size_t)(row0 + r) * sout.n + c;
-    const size_t kept = ((size_t)bh * N + row0 + r) * D + c;
+  // through LDS: a lane's 16 bytes of a row each are a request of their own, whole rows are not
+  const int c_own = own_channel(D, w, g);
+  __syncthreads();                        // the parts have been read, and the query rows
 #pragma unroll
-    for (int e = 0; e < ET; e++) {
-      f32x4 s4, l4;
+  for (int y = 0; y < ET; y++) {
+    f32x4 s4, l4;
 #pragma unroll
-      for (int x = 0; x < 4; x++) {
-        s4[x] = os[4 * e + x] * inv_l;
-        l4[x] = ol[4 * e + x] * inv_den;
-      }
-      *reinterpret_cast<f32x4*>(o + 4 * e) = al * s4 + (1.f - al) * l4;
+    for (int x = 0; x < 4; x++) {
+      s4[x] = os[4 * y + x] * inv_l;
+      l4[x] = ol[4 * y + x] * inv_den;
+    }
+    *reinterpret_cast<f32x4*>(qs + r * LD + c_own + 4 * y) = s4;
+    *reinterpret_cast<f32x4*>(swap + r * LD + c_own + 4 * y) = l4;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int y = 0; y < QM::kLoads; y++) {
+    const int row = tid / QM::kChunks + y * QM::kRows, c = 4 * (tid % QM::kChunks);
+    if (row < rows_valid) {
+      const f32x4 s4 = *reinterpret_cast<const f32x4*>(qs + row * LD + c), l4 = *reinterpret_cast<const f32x4*>(swap + row * LD + c);
+      *reinterpret_cast<f32x4*>(out + head_offset(sout, bh, H) + (size_t)(row0 + row) * sout.n + c) = al * s4 + (1.f - al) * l4;
       if (o_s_save != nullptr) {          // the two branches, kept for the backward pass
-        *reinterpret_cast<f32x4*>(o_s_save + kept + 4 * e) = s4;
-        *reinterpret_cast<f32x4*>(o_l_save + kept + 4 * e) = l4;
+        const size_t kept = ((size_t)bh * N + row0 + row) * D + c;
+        *reinterpret_cast<f32x4*>(o_s_save + kept) = s4;
+        *reinterpret_cast<f32x4*>(o_l_save + kept) = l4;
       }
     }
-    if (w == 0 && g == 0) {
-      const float L = l > 0.f ? (m_all + __log2f(l)) * kLn2 : -INFINITY;
-      if (lse != nullptr) lse[(size_t)bh * N + row0 + r] = L;
-      if (lse_save != nullptr) lse_save[(size_t)bh * N + row0 + r] = L;
-    }
+  }
+  if (w == 0 && g == 0 && r < rows_valid) {
+    const float L = l > 0.f ? (m_all + __log2f(l)) * kLn2 : -INFINITY;
+    if (lse != nullptr) lse[(size_t)bh * N + row0 + r] = L;
+    if (lse_save != nullptr) lse_save[(size_t)bh * N + row0 + r] = L;
   }
 }
 
