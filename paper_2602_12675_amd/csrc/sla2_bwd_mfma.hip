@@ -25,16 +25,16 @@
 namespace sla2 {
 
 // ---------------------------------------------------------------------------------------------
+// Two buffers of (K, V) tiles.  Before the loop: the query rows and then the dO rows of every wave pass through the first one,
+// which then takes w = Q^phi / (Q^phi Z_i); H_i^T arrives in the second, dO takes its place.  After it, dQ.  Rows of D
+// elements throughout, in the layout of the tiles.
 template <int D, int BQ> struct BwdQSmem {
-  static constexpr int kLd = D + 8;
   static constexpr int kTile = SwizzledLayout<D>::kTileBytes;                  // one 64 x D bf16 tile
-  static constexpr int kLoopBytes = 4 * kTile;                                 // two buffers of (K, V)
-  static constexpr int kEpiA = (D > BQ ? D : BQ) * kLd * 2;                    // H_i^T [D][kLd], the dQ tile, dO [BQ][kLd]
-  static constexpr int kEpiB = BQ * kLd * 2;                                   // w [BQ][kLd]
-  static constexpr int kTiles = kLoopBytes > kEpiA + kEpiB ? kLoopBytes : kEpiA + kEpiB;
+  static constexpr int kTiles = 4 * kTile;
+  static_assert(D * D * 2 <= 2 * kTile && BQ * D * 2 <= 2 * kTile, "a buffer holds H_i^T, and the rows of a query block");
   static constexpr int kZsOff = kTiles;                                        // float [D]   Z_i
   static constexpr int kMuOff = kZsOff + D * 4;                                // float [D]   colmean(K)
-  static constexpr int kDlOff = kMuOff + D * 4;                                // float [BQ]  D^l per row
+  static constexpr int kDlOff = kMuOff + D * 4;                                // float [BQ]  dO . O^s, later D^l, per row
   static constexpr int kRedOff = kDlOff + BQ * 4;                              // float [8]
   static constexpr int kBytes = kRedOff + 32;
 };
@@ -48,12 +48,11 @@ __global__ __launch_bounds__(BQ * 2, 2) void bwd_q_mfma_kernel(
     uint16_t* __restrict__ dq, float* __restrict__ ds_out, float* __restrict__ lraw_out, uint16_t* __restrict__ dh_out,
     float* __restrict__ dz_out, float* __restrict__ dalpha_part, Strides sin, Strides sout, int H, int N, int Tm, int Tn,
     int ksel, int alpha_per_block) {
-  constexpr int NW = BQ / 32, NT = NW * kWave;
-  constexpr int LD = D + 8, KS = D / 16, ET = D / 32;
+  constexpr int NW = BQ / 32;
+  constexpr int KS = D / 16, ET = D / 32;
   typedef typename std::conditional<D == 128 && BQ == 128, SwizzledLayoutB<128>, SwizzledLayout<D>>::type SL;
   // (at d = 128 free of bank conflicts, which were half of the LDS cycles: 435 -> 427 us on 12 heads of 32,760 tokens; its
   // rows repeat every 16, which the two waves of a 64-row block do not cover with one transfer)
-  typedef PaddedLayout<D> PL;
   typedef BwdQSmem<D, BQ> SM;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   float* zs = reinterpret_cast<float*>(smem + SM::kZsOff);
@@ -92,30 +91,59 @@ __global__ __launch_bounds__(BQ * 2, 2) void bwd_q_mfma_kernel(
     dma_tile<D, NW, SL>(kh + (size_t)t0 * tok_stride, tok_stride, valid, lds_address(kbuf(buf)), w, lane);
     dma_tile<D, NW, SL>(vh + (size_t)t0 * tok_stride, tok_stride, valid, lds_address(vbuf(buf)), w, lane);
   };
+#pragma unroll
+  for (int x = 0; x < D / 64; x++)                   // H_i^T [e][c]
+    dma_tile<D, NW, SL>(h_i + slot * D * D + x * 64 * D, D, 64, lds_address(kbuf(1)) + x * SM::kTile, w, lane);
   int j_cur = ntiles > 0 ? sel[0] : 0, j_nxt = ntiles > 1 ? sel[1] : 0;
-  if (ntiles > 0) dma(j_cur, 0);
-  if (tid < D) mus[tid] = (float)k_mean[(size_t)bh * D + tid];
 
   // ---- prologue: Q and dO as B-operand fragments (alpha is applied to the products); dO . O^s per row ----
+  // A wave loads its rows whole, 1 KB of consecutive bytes a request, and turns them through LDS: with every lane loading
+  // pieces of its own row, a request is 32 cache lines and takes four times as long.
   bf16x8 qf[KS], gof[KS];
   float dot_s = 0.f;                                 // dO . O^s of this lane's row;  D^s = alpha dot_s
   {
-    const uint16_t* qsrc = qh + (size_t)(row0 + r_ld) * tok_stride + 8 * g;
-    const uint16_t* gsrc = doh + (size_t)(row0 + r_ld) * sout.n + 8 * g;
-    const uint16_t* ossrc = o_s + ((size_t)bh * N + row0 + r_ld) * D + 8 * g;
+    constexpr int kChunks = D / 8, kLoads = 32 * kChunks / kWave, kRows = kWave / kChunks;
+    const int ch = lane % kChunks, first = 32 * w + lane / kChunks;
+    u32x4 qr[kLoads], gr[kLoads], sr[kLoads];
 #pragma unroll
-    for (int ks = 0; ks < KS; ks++) {
-      qf[ks] = *reinterpret_cast<const bf16x8*>(qsrc + 16 * ks);
-      gof[ks] = *reinterpret_cast<const bf16x8*>(gsrc + 16 * ks);
-      const bf16x8 os = *reinterpret_cast<const bf16x8*>(ossrc + 16 * ks);
-#pragma unroll
-      for (int e = 0; e < 8; e++) dot_s += (float)gof[ks][e] * (float)os[e];
+    for (int x = 0; x < kLoads; x++) {
+      const int row = row0 + min(first + kRows * x, rows_valid - 1);
+      qr[x] = *reinterpret_cast<const u32x4*>(qh + (size_t)row * tok_stride + 8 * ch);
+      gr[x] = *reinterpret_cast<const u32x4*>(doh + (size_t)row * sout.n + 8 * ch);
+      sr[x] = *reinterpret_cast<const u32x4*>(o_s + ((size_t)bh * N + row) * D + 8 * ch);
     }
+    if (tid < D) {
+      mus[tid] = (float)k_mean[(size_t)bh * D + tid];
+      zs[tid] = z_i[slot * D + tid];
+    }
+    uint16_t* turn = kbuf(0);
+    auto turned = [&](const u32x4 (&from)[kLoads], bf16x8 (&to)[KS]) {
+#pragma unroll
+      for (int x = 0; x < kLoads; x++) *reinterpret_cast<u32x4*>(turn + SL::offset(first + kRows * x, 8 * ch)) = from[x];
+      wave_lds_fence();
+#pragma unroll
+      for (int ks = 0; ks < KS; ks++) to[ks] = row_fragment<SL>(turn, qrow, 16 * ks + 8 * g);
+      wave_lds_fence();
+    };
+    turned(qr, qf);
+    turned(gr, gof);
+#pragma unroll
+    for (int x = 0; x < kLoads; x++) {
+      const bf16x8 go = __builtin_bit_cast(bf16x8, gr[x]), os = __builtin_bit_cast(bf16x8, sr[x]);
+      float part = 0.f;
+#pragma unroll
+      for (int e = 0; e < 8; e++) part += (float)go[e] * (float)os[e];
+#pragma unroll
+      for (int o = 1; o < kChunks; o <<= 1) part += __shfl_xor(part, o);
+      if (ch == 0) dls[first + kRows * x] = part;
+    }
+    wave_lds_fence();
+    dot_s = dls[qrow];
+    wave_lds_fence();
   }
-  dot_s = half_sum(dot_s);
   const float Ds = al * dot_s;
   const float L = lse[(size_t)bh * N + row0 + r_ld];
-  __builtin_amdgcn_s_waitcnt(kVmcnt0);               // tile 0 and everything above have landed
+  __builtin_amdgcn_s_waitcnt(kVmcnt0);               // H_i^T and everything above have landed
   __syncthreads();                                   // ... for everyone; mus is visible
   // The forward pass defines L on the smoothed keys; the products below use the raw K, whose scores are
   // larger by q . colmean(K) / sqrt(d) in every column of a row.
@@ -135,17 +163,180 @@ __global__ __launch_bounds__(BQ * 2, 2) void bwd_q_mfma_kernel(
     lraw_out[slot * BQ + qrow] = row_ok ? L2 : INFINITY;
   }
 
+  // ================= linear branch =================
+  // First, while the accumulators and scores of the loop take no registers: behind the loop it spilled fifty, each to be waited
+  // for at a time, and took 100 of 435 us.
+  uint16_t* ta = kbuf(1);                                           // H_i^T [e][c]; then dO [row][e]
+  uint16_t* tb = kbuf(0);                                           // w = Q^phi / (Q^phi Z_i) as [row][c]
+  // Byte offsets of this lane's row: 16 bytes of channels 16 ks + 8 g .. at (full) ^ 32 ks, 8 of 8 c + 4 g .. at (quarter) ^ 16 c
+  // (made opaque before every loop over them: sixteen addresses are not to be kept)
+  unsigned full = 2u * (unsigned)SL::offset(qrow, 8 * g), quarter = 2u * (unsigned)SL::offset(qrow, 4 * g);
+  unsigned char *pa = reinterpret_cast<unsigned char*>(ta), *pb = reinterpret_cast<unsigned char*>(tb);
+  // Q^phi = softmax_d(Q) of this lane's row from the Q fragments (channels 16 ks + 8 g + 0..7); as
+  // exp(q - max), the normalisation is applied where they are used
+  bf16x8 ef[KS];
+  float qm = -INFINITY;
+#pragma unroll
+  for (int ks = 0; ks < KS; ks++) {
+#pragma unroll
+    for (int e = 0; e < 8; e++) qm = fmaxf(qm, (float)qf[ks][e]);
+  }
+  qm = half_max(qm);
+  float qs = 0.f;
+#pragma unroll
+  for (int ks = 0; ks < KS; ks++) {
+#pragma unroll
+    for (int e = 0; e < 8; e++) {
+      const float x = fast_exp2(((float)qf[ks][e] - qm) * kLog2e);
+      qs += x;
+      ef[ks][e] = (__bf16)x;
+    }
+    settle(ef[ks]);
+  }
+  qs = half_sum(qs);
+  const float qinv = 1.f / qs;
+  float den = 0.f;
+#pragma unroll
+  for (int ks = 0; ks < KS; ks++) {
+    const f32x4 z0 = *reinterpret_cast<const f32x4*>(zs + 16 * ks + 8 * g);
+    const f32x4 z1 = *reinterpret_cast<const f32x4*>(zs + 16 * ks + 8 * g + 4);
+#pragma unroll
+    for (int e = 0; e < 8; e++) den += (float)ef[ks][e] * (e < 4 ? z0[e] : z1[e - 4]);
+  }
+  den = half_sum(den) * qinv;
+  // every block selected: the linear branch receives and passes no gradient
+  const float inv_den = (ksel >= Tn || !row_ok) ? 0.f : 1.f / den;
+  // w as a [row][c] tile (zero rows past the end); the softmax-backward step reads Q^phi = w den back
+  // from it in the layout of the accumulators
+  {
+    const float wscale = qinv * inv_den;
+#pragma unroll
+    for (int ks = 0; ks < KS; ks++) {
+      bf16x8 wv;
+#pragma unroll
+      for (int e = 0; e < 8; e++) wv[e] = (__bf16)((float)ef[ks][e] * wscale);
+      *reinterpret_cast<bf16x8*>(pb + (full ^ (32u * ks))) = wv;
+    }
+  }
+  // dQ^phi^T = (1 - alpha) H_i dO^T: A = H_i read transposed out of the H_i^T tile, B = the dO fragments
+  // (in the accumulators of dQ: what they end up with before the loop is added to by it)
+  f32x16 dqacc[ET];
+#pragma unroll
+  for (int ct = 0; ct < ET; ct++)
+#pragma unroll
+    for (int e = 0; e < 16; e++) dqacc[ct][e] = 0.f;
+#pragma unroll
+  for (int ks = 0; ks < KS; ks++) {
+#pragma unroll
+    for (int ct = 0; ct < ET; ct++) dqacc[ct] = mfma_bf16(nat_fragment<SL>(ta, ks, 32 * ct, lane), gof[ks], dqacc[ct]);
+  }
+  wave_lds_fence();                                  // (w rows: the wave's own)
+  settle(quarter);
+  // O^l is not kept by the forward pass: dO . O^l of a row equals sum_c w[r][c] (H_i dO^T)[c][r], both at
+  // hand.  D^l = (1 - alpha) dO . O^l; the row's part of d alpha is dO . (O^s - O^l).
+  float dot_l = 0.f;
+#pragma unroll
+  for (int ct = 0; ct < ET; ct++)
+#pragma unroll
+    for (int v4 = 0; v4 < 4; v4++) {
+      const bf16x4 wq = *reinterpret_cast<const bf16x4*>(pb + (quarter ^ (16u * (4 * ct + v4))));
+#pragma unroll
+      for (int r = 0; r < 4; r++) dot_l += (float)wq[r] * dqacc[ct][4 * v4 + r];
+    }
+  wave_lds_fence();                                  // w is read again below rather than kept in registers
+  settle(quarter);
+  dot_l = half_sum(dot_l);
+  const float Dl = (1.f - al) * dot_l;
+  if (g == 0) dls[qrow] = Dl;
+  {
+    float mix = (row_ok && g == 0) ? dot_s - dot_l : 0.f;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) mix += __shfl_xor(mix, o);
+    if (lane == 0) red[w] = mix;
+  }
+  float dot = 0.f;
+#pragma unroll
+  for (int ct = 0; ct < ET; ct++)
+#pragma unroll
+    for (int v4 = 0; v4 < 4; v4++) {
+      const f32x4 z = *reinterpret_cast<const f32x4*>(zs + 32 * ct + 8 * v4 + 4 * g);
+      const bf16x4 wq = *reinterpret_cast<const bf16x4*>(pb + (quarter ^ (16u * (4 * ct + v4))));
+#pragma unroll
+      for (int r = 0; r < 4; r++) {
+        dqacc[ct][4 * v4 + r] = ((1.f - al) * dqacc[ct][4 * v4 + r] - Dl * z[r]) * inv_den;
+        dot += dqacc[ct][4 * v4 + r] * ((float)wq[r] * den);
+      }
+    }
+  dot = half_sum(dot);
+  settle(quarter);
+  const float unscale = sqrtf((float)D);             // the loop's sums are scaled by 1 / sqrt(d) at the end
+#pragma unroll
+  for (int ct = 0; ct < ET; ct++)
+#pragma unroll
+    for (int v4 = 0; v4 < 4; v4++) {                 // softmax-backward(dQ^phi)
+      const bf16x4 wq = *reinterpret_cast<const bf16x4*>(pb + (quarter ^ (16u * (4 * ct + v4))));
+#pragma unroll
+      for (int r = 0; r < 4; r++)
+        dqacc[ct][4 * v4 + r] = (float)wq[r] * den * (dqacc[ct][4 * v4 + r] - dot) * unscale;
+    }
+  __syncthreads();                                   // nobody reads H_i^T any more
+#pragma unroll
+  for (int ks = 0; ks < KS; ks++) *reinterpret_cast<bf16x8*>(pa + (full ^ (32u * ks))) = gof[ks];   // dO as [row][e]
+  __syncthreads();                                   // dO and w complete; the waves' d alpha parts are visible
+  if (tid == 0) {
+    float t = 0.f;
+#pragma unroll
+    for (int x = 0; x < NW; x++) t += red[x];
+    dalpha_part[slot] = t;
+  }
+  // dH_i[c][e] = (1 - alpha) sum_r w[r][c] dO[r][e]: both operands read transposed, contraction over the rows.  Formed as
+  // dH_i^T tiles and stored as they lie in the accumulators, 16 bytes a lane and a whole kilobyte per store: lane l holds
+  // channel c = 32 ct + l % 32 and, in half x of tile (ct, et), e = 32 et + 16 x + 4 (l / 32) + {0..3, 8..11}.
+  // dZ_i[c] = -sum_r w[r][c] D^l_r from the same operands of w.
+  constexpr int kTilesPerWave = ET * ET / NW, kEts = kTilesPerWave < ET ? kTilesPerWave : ET, kCts = kTilesPerWave / kEts;
+  static_assert(kTilesPerWave >= 1, "unsupported split");
+  uint16_t* dh_slot = dh_out + slot * D * D;
+#pragma unroll 1
+  for (int x = 0; x < kCts; x++) {
+    const int t0 = w * kTilesPerWave + x * kEts, ct = t0 / ET, et0 = t0 % ET;
+    f32x16 acc[kEts];
+#pragma unroll
+    for (int y = 0; y < kEts; y++)
+#pragma unroll
+      for (int e = 0; e < 16; e++) acc[y][e] = 0.f;
+    float dz = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < BQ / 16; ks++) {
+      const bf16x8 wf = v_fragment<SL>(tb, ks, 32 * ct, lane);
+#pragma unroll
+      for (int y = 0; y < kEts; y++) acc[y] = mfma_bf16(v_fragment<SL>(ta, ks, 32 * (et0 + y), lane), wf, acc[y]);
+      const f32x4 d0 = *reinterpret_cast<const f32x4*>(dls + 16 * ks + 4 * g), d1 = *reinterpret_cast<const f32x4*>(dls + 16 * ks + 8 + 4 * g);
+#pragma unroll
+      for (int e = 0; e < 8; e++) dz -= (float)wf[e] * (e < 4 ? d0[e] : d1[e - 4]);
+    }
+#pragma unroll
+    for (int y = 0; y < kEts; y++)
+#pragma unroll
+      for (int half = 0; half < 2; half++) {
+        bf16x8 o;
+#pragma unroll
+        for (int e = 0; e < 8; e++) o[e] = (__bf16)((1.f - al) * acc[y][8 * half + e]);
+        *reinterpret_cast<bf16x8*>(dh_slot + (((t0 + y) * 2 + half) * kWave + lane) * 8) = o;
+      }
+    dz = half_sum(dz);
+    if (et0 == 0 && g == 0) dz_out[slot * D + 32 * ct + lane] = dz;
+  }
+  __syncthreads();                                   // w and dO consumed
+  if (ntiles > 0) dma(j_cur, 0);
+
   // LDS byte offsets of this lane's operand reads inside a K or V tile: row-wise reads (key row
   // l % 32, channel step ks at (offset of step 0) ^ 32 ks) and transposing reads (cf. read_tr4): rows 4 g + (l % 16) / 4 (lo)
   // and 8 further (hi), channel tile et at (offset of tile 0) ^ 64 et, 16-token step ks 32 D ks further
   const unsigned b_off = (unsigned)SL::offset(lane % 32, 8 * g) * 2;
   const int tr_row = 4 * g + (lane % 16) / 4, tr_col = 16 * ((lane / 16) % 2) + 4 * (lane % 4);
   const unsigned a_off[2] = {(unsigned)SL::offset(tr_row, tr_col) * 2, (unsigned)SL::offset(tr_row + 8, tr_col) * 2};
-  f32x16 dqacc[ET];
-#pragma unroll
-  for (int et = 0; et < ET; et++)
-#pragma unroll
-    for (int e = 0; e < 16; e++) dqacc[et][e] = 0.f;
+  __builtin_amdgcn_s_waitcnt(kVmcnt0);               // tile 0 has landed ...
+  __syncthreads();                                   // ... for everyone
   float sumds = 0.f;
   const float c0 = kLog2e * rscale;
 
@@ -250,176 +441,30 @@ __global__ __launch_bounds__(BQ * 2, 2) void bwd_q_mfma_kernel(
   if (whole < ntiles) tile(whole, std::true_type());
 
   // ================= epilogue =================
-  uint16_t* ta = reinterpret_cast<uint16_t*>(smem);                 // H_i^T [e][c]; then the dQ tile; then dO [row][e]
-  uint16_t* tb = reinterpret_cast<uint16_t*>(smem + SM::kEpiA);     // w = Q^phi / (Q^phi Z_i) as [row][c]
-  // dS K' = dS K - rowsum(dS) colmean(K)^T
+  // dS K' = dS K - rowsum(dS) colmean(K)^T; transposed through LDS for a coalesced store of the wave's own rows
   sumds = half_sum(sumds);
+  int ln = lane;
+  settle(ln);                                        // addresses are made here, not kept from the start of the kernel
+  const unsigned row_at = 2u * (unsigned)SL::offset(32 * w + ln % 32, 4 * (ln / 32));
 #pragma unroll
   for (int et = 0; et < ET; et++)
 #pragma unroll
     for (int v4 = 0; v4 < 4; v4++) {
-      const f32x4 m = *reinterpret_cast<const f32x4*>(mus + 32 * et + 8 * v4 + 4 * g);
-#pragma unroll
-      for (int r = 0; r < 4; r++) dqacc[et][4 * v4 + r] = (dqacc[et][4 * v4 + r] - sumds * m[r]) * rscale;
-    }
-  {
-    const uint16_t* hsrc = h_i + slot * D * D;
-    for (int idx = tid; idx < D * (D / 8); idx += NT) {
-      const int e = idx / (D / 8), ch = idx % (D / 8);
-      *reinterpret_cast<u32x4*>(ta + e * LD + 8 * ch) = *reinterpret_cast<const u32x4*>(hsrc + e * D + 8 * ch);
-    }
-    if (tid < D) zs[tid] = z_i[slot * D + tid];
-  }
-  // Q^phi = softmax_d(Q) of this lane's row from the Q fragments (channels 16 ks + 8 g + 0..7); the
-  // fragments are overwritten with exp(q - max), the normalisation is applied where they are used
-  // (the fragments are made opaque first: the widened copies that the prologue made of them would
-  // otherwise be kept alive across the whole main loop for reuse here)
-#pragma unroll
-  for (int ks = 0; ks < KS; ks++) settle(qf[ks]);
-  float qm = -INFINITY;
-#pragma unroll
-  for (int ks = 0; ks < KS; ks++)
-#pragma unroll
-    for (int e = 0; e < 8; e++) qm = fmaxf(qm, (float)qf[ks][e]);
-  qm = half_max(qm);
-  float qs = 0.f;
-#pragma unroll
-  for (int ks = 0; ks < KS; ks++)
-#pragma unroll
-    for (int e = 0; e < 8; e++) {
-      const float x = fast_exp2(((float)qf[ks][e] - qm) * kLog2e);
-      qs += x;
-      qf[ks][e] = (__bf16)x;
-    }
-  qs = half_sum(qs);
-  const float qinv = 1.f / qs;
-  __syncthreads();                                   // H_i^T and Z_i visible
-  float den = 0.f;
-#pragma unroll
-  for (int ks = 0; ks < KS; ks++) {
-    const f32x4 z0 = *reinterpret_cast<const f32x4*>(zs + 16 * ks + 8 * g);
-    const f32x4 z1 = *reinterpret_cast<const f32x4*>(zs + 16 * ks + 8 * g + 4);
-#pragma unroll
-    for (int e = 0; e < 8; e++) den += (float)qf[ks][e] * (e < 4 ? z0[e] : z1[e - 4]);
-  }
-  den = half_sum(den) * qinv;
-  // every block selected: the linear branch receives and passes no gradient
-  const float inv_den = (ksel >= Tn || !row_ok) ? 0.f : 1.f / den;
-  // w as a [row][c] tile (zero rows past the end); the softmax-backward step reads Q^phi = w den back
-  // from it in the layout of the accumulators
-  {
-    const float wscale = qinv * inv_den;
-#pragma unroll
-    for (int ks = 0; ks < KS; ks++) {
-      bf16x8 wv;
-#pragma unroll
-      for (int e = 0; e < 8; e++) wv[e] = (__bf16)((float)qf[ks][e] * wscale);
-      *reinterpret_cast<bf16x8*>(tb + qrow * LD + 16 * ks + 8 * g) = wv;
-    }
-  }
-  // dQ^phi^T = (1 - alpha) H_i dO^T: A = H_i read transposed out of the H_i^T tile, B = the dO fragments
-  f32x16 dqp[ET];
-#pragma unroll
-  for (int ct = 0; ct < ET; ct++)
-#pragma unroll
-    for (int e = 0; e < 16; e++) dqp[ct][e] = 0.f;
-#pragma unroll
-  for (int ks = 0; ks < KS; ks++)
-#pragma unroll
-    for (int ct = 0; ct < ET; ct++) dqp[ct] = mfma_bf16(nat_fragment<PL>(ta, ks, 32 * ct, lane), gof[ks], dqp[ct]);
-  __syncthreads();                                   // w complete; nobody reads H_i^T any more
-  // O^l is not kept by the forward pass: dO . O^l of a row equals sum_c w[r][c] (H_i dO^T)[c][r], both at
-  // hand.  D^l = (1 - alpha) dO . O^l; the row's part of d alpha is dO . (O^s - O^l).
-  float dot_l = 0.f;
-#pragma unroll
-  for (int ct = 0; ct < ET; ct++)
-#pragma unroll
-    for (int v4 = 0; v4 < 4; v4++) {
-      const bf16x4 wq = *reinterpret_cast<const bf16x4*>(tb + qrow * LD + 32 * ct + 8 * v4 + 4 * g);
-#pragma unroll
-      for (int r = 0; r < 4; r++) dot_l += (float)wq[r] * dqp[ct][4 * v4 + r];
-    }
-  dot_l = half_sum(dot_l);
-  const float Dl = (1.f - al) * dot_l;
-  if (g == 0) dls[qrow] = Dl;
-  {
-    float mix = (row_ok && g == 0) ? dot_s - dot_l : 0.f;
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) mix += __shfl_xor(mix, o);
-    if (lane == 0) red[w] = mix;
-  }
-  float dot = 0.f;
-#pragma unroll
-  for (int ct = 0; ct < ET; ct++)
-#pragma unroll
-    for (int v4 = 0; v4 < 4; v4++) {
-      const f32x4 z = *reinterpret_cast<const f32x4*>(zs + 32 * ct + 8 * v4 + 4 * g);
-      const bf16x4 wq = *reinterpret_cast<const bf16x4*>(tb + qrow * LD + 32 * ct + 8 * v4 + 4 * g);
-#pragma unroll
-      for (int r = 0; r < 4; r++) {
-        dqp[ct][4 * v4 + r] = ((1.f - al) * dqp[ct][4 * v4 + r] - Dl * z[r]) * inv_den;
-        dot += dqp[ct][4 * v4 + r] * ((float)wq[r] * den);
-      }
-    }
-  dot = half_sum(dot);
-  // dQ = sparse part + softmax-backward(dQ^phi); transposed through LDS for a coalesced store
-#pragma unroll
-  for (int et = 0; et < ET; et++)
-#pragma unroll
-    for (int v4 = 0; v4 < 4; v4++) {
-      const bf16x4 wq = *reinterpret_cast<const bf16x4*>(tb + qrow * LD + 32 * et + 8 * v4 + 4 * g);
+      const f32x4 m = *reinterpret_cast<const f32x4*>(mus + 32 * et + 8 * v4 + 4 * (ln / 32));
       bf16x4 pk;
 #pragma unroll
-      for (int r = 0; r < 4; r++)
-        pk[r] = (__bf16)(dqacc[et][4 * v4 + r] + (float)wq[r] * den * (dqp[et][4 * v4 + r] - dot));
-      *reinterpret_cast<bf16x4*>(ta + qrow * LD + 32 * et + 8 * v4 + 4 * g) = pk;
+      for (int r = 0; r < 4; r++) pk[r] = (__bf16)((dqacc[et][4 * v4 + r] - sumds * m[r]) * rscale);
+      *reinterpret_cast<bf16x4*>(smem + (row_at ^ (16u * (4 * et + v4)))) = pk;
     }
-  __syncthreads();                                   // dQ tile complete; the waves' d alpha parts are visible
-  if (tid == 0) {
-    float t = 0.f;
-#pragma unroll
-    for (int x = 0; x < NW; x++) t += red[x];
-    dalpha_part[slot] = t;
-  }
+  wave_lds_fence();
   {
     uint16_t* dst = dq + head_offset(sin, bh, H) + (size_t)row0 * tok_stride;
-    for (int idx = tid; idx < BQ * (D / 8); idx += NT) {
-      const int r = idx / (D / 8), ch = idx % (D / 8);
+#pragma unroll
+    for (int x = 0; x < D / 16; x++) {
+      const int r = 32 * w + (x * kWave + ln) / (D / 8), ch = ln % (D / 8);
       if (r < rows_valid)
-        *reinterpret_cast<u32x4*>(dst + (size_t)r * tok_stride + 8 * ch) = *reinterpret_cast<const u32x4*>(ta + r * LD + 8 * ch);
+        *reinterpret_cast<u32x4*>(dst + (size_t)r * tok_stride + 8 * ch) = *reinterpret_cast<const u32x4*>(kbuf(0) + SL::offset(r, 8 * ch));
     }
-  }
-  __syncthreads();                                   // the dQ tile has been read out
-#pragma unroll
-  for (int ks = 0; ks < KS; ks++) *reinterpret_cast<bf16x8*>(ta + qrow * LD + 16 * ks + 8 * g) = gof[ks];   // dO as [row][e]
-  __syncthreads();
-  // dH_i[c][e] = (1 - alpha) sum_r w[r][c] dO[r][e]: both operands read transposed, contraction over the rows.  Formed as
-  // dH_i^T tiles and stored as they lie in the accumulators, 16 bytes a lane and a whole kilobyte per store: lane l holds
-  // channel c = 32 ct + l % 32 and, in half x of tile (ct, et), e = 32 et + 16 x + 4 (l / 32) + {0..3, 8..11}.
-  constexpr int kTilesPerWave = ET * ET / NW;
-  static_assert(kTilesPerWave >= 1, "unsupported split");
-  uint16_t* dh_slot = dh_out + slot * D * D;
-#pragma unroll 1
-  for (int x = 0; x < kTilesPerWave; x++) {
-    const int t = w * kTilesPerWave + x, ct = t / ET, et = t % ET;
-    f32x16 acc;
-#pragma unroll
-    for (int e = 0; e < 16; e++) acc[e] = 0.f;
-#pragma unroll
-    for (int ks = 0; ks < BQ / 16; ks++)
-      acc = mfma_bf16(v_fragment<PL>(ta, ks, 32 * et, lane), v_fragment<PL>(tb, ks, 32 * ct, lane), acc);
-#pragma unroll
-    for (int half = 0; half < 2; half++) {
-      bf16x8 y;
-#pragma unroll
-      for (int e = 0; e < 8; e++) y[e] = (__bf16)((1.f - al) * acc[8 * half + e]);
-      *reinterpret_cast<bf16x8*>(dh_slot + ((t * 2 + half) * kWave + lane) * 8) = y;
-    }
-  }
-  if (tid < D) {                                     // dZ_i[c] = -sum_r w[r][c] D^l_r
-    float dz = 0.f;
-    for (int r = 0; r < BQ; r++) dz -= bf16_bits_to_f32(tb[r * LD + tid]) * dls[r];
-    dz_out[slot * D + tid] = dz;
   }
 }
 
