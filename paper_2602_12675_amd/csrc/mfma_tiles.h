@@ -31,6 +31,12 @@ __device__ __forceinline__ void phase_barrier() {
   asm volatile("" ::: "memory");
 }
 
+// The lane index again, from the hardware: what a long loop derives from it does not stay in registers meanwhile.
+__device__ __forceinline__ unsigned lane_again() {
+  unsigned l;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+  return l;
+}
 // f(0), .., f(N - 1) with the index as a constant expression: for bodies that are too long for the unroller
 template <int N, class F> __device__ __forceinline__ void unrolled(F f) {
   if constexpr (N > 0) {

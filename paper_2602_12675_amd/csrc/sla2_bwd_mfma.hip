@@ -164,8 +164,9 @@ __global__ __launch_bounds__(BQ * 2, 2) void bwd_q_mfma_kernel(
   }
 
   // ================= linear branch =================
-  // First, while the accumulators and scores of the loop take no registers: behind the loop it spilled fifty, each to be waited
-  // for at a time, and took 100 of 435 us.
+  // First, while the scores of the loop take no registers: behind the loop it spilled up to a hundred, each waited for by itself.
+  // 12 heads of 32,760 tokens: 438 -> 385 us with 15 tiles a block, 250 -> 177 without any (0.6 GB at 3.4 TB/s); 32 heads of
+  // 4,096, d = 64, 64-row blocks: 56 -> 51 us.
   uint16_t* ta = kbuf(1);                                           // H_i^T [e][c]; then dO [row][e]
   uint16_t* tb = kbuf(0);                                           // w = Q^phi / (Q^phi Z_i) as [row][c]
   // Byte offsets of this lane's row: 16 bytes of channels 16 ks + 8 g .. at (full) ^ 32 ks, 8 of 8 c + 4 g .. at (quarter) ^ 16 c
@@ -443,8 +444,7 @@ __global__ __launch_bounds__(BQ * 2, 2) void bwd_q_mfma_kernel(
   // ================= epilogue =================
   // dS K' = dS K - rowsum(dS) colmean(K)^T; transposed through LDS for a coalesced store of the wave's own rows
   sumds = half_sum(sumds);
-  int ln = lane;
-  settle(ln);                                        // addresses are made here, not kept from the start of the kernel
+  const int ln = (int)lane_again();                  // addresses are made here, not kept from the start of the kernel
   const unsigned row_at = 2u * (unsigned)SL::offset(32 * w + ln % 32, 4 * (ln / 32));
 #pragma unroll
   for (int et = 0; et < ET; et++)
@@ -499,14 +499,15 @@ __device__ __forceinline__ u32x4 stat_read(unsigned base, int n) {
 template <int D> struct BwdKvSmem {
   static constexpr int kLd = D + 8;
   static constexpr int kTile = SwizzledLayout<D>::kTileBytes;                  // one 64 x D bf16 tile
-  static constexpr int kStepBytes = 4 * kTile;                                 // two buffers of (Q rows, dO rows);
-                                                                               // after the loop: dH and K^phi, then the outputs
+  static constexpr int kStepBytes = 4 * kTile;                                 // two buffers of (Q rows, dO rows); before the loop
+                                                                               // K_j, V_j and dH_j, after it the outputs
   static constexpr int kStatOff = kStepBytes;                                  // float [2][2][64]: L log2(e) and D^s of a step's rows
+                                                                               // (before the loop parts of dZ_j, after it of sums)
   static constexpr int kMuOff = kStatOff + 2 * 2 * 64 * 4;                     // float [D]  colmean(K)
-  static constexpr int kDzOff = kMuOff + D * 4;                                // float [D]  dZ of this key block
-  static constexpr int kDotOff = kDzOff + D * 4;                               // float [D / 32][64]
-  static constexpr int kBytes = kDotOff + (D / 32) * 64 * 4;
-  static_assert((D + 64) * kLd * 2 <= kStepBytes && 2 * 64 * kLd * 2 <= kStepBytes, "epilogue tiles reuse the step buffers");
+  static constexpr int kDotOff = kMuOff + D * 4;                               // float [D / 32][64]
+  static constexpr int kBytes = kDotOff + 256 * 4;
+  static_assert(D * D * 2 <= 2 * kTile && 2 * 64 * kLd * 2 <= kStepBytes, "dH_j and the outputs in the place of the steps");
+  static_assert(kStatOff + 512 * 4 <= kBytes, "parts of the column sums");
 };
 
 // Scores are computed as S = Q K^T (query rows x keys) here: a lane of the result then owns one key
@@ -519,7 +520,7 @@ template <int D> struct BwdKvSmem {
 // of 32: LDS feeds 128 bytes a cycle, one operand per product and SIMD.)  The price is registers: 128 accumulators
 // next to the 64 of the K_j, V_j fragments, so the operand reads run only a few ahead.
 template <int D, int BQ>
-__global__ __launch_bounds__(256, 2) void bwd_kv_mfma_kernel(
+__global__ __launch_bounds__(256, D == 64 ? 3 : 2) void bwd_kv_mfma_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const uint16_t* __restrict__ dout, const float* __restrict__ lraw2, const float* __restrict__ ds_in,
     const double* __restrict__ k_mean, const float* __restrict__ k_stats, const int32_t* __restrict__ col_ptr, const int32_t* __restrict__ col_idx,
@@ -532,14 +533,12 @@ __global__ __launch_bounds__(256, 2) void bwd_kv_mfma_kernel(
   constexpr int HP = BQ / 64;                        // 64-row steps per query block
   constexpr int CT = ET / 2;                         // 32-channel tiles a wave finishes after the loop
   typedef typename std::conditional<D == 128, SwizzledLayoutB<128>, SwizzledLayout<64>>::type SL;   // no bank conflicts
-  typedef PaddedLayout<D> PL;
   typedef BwdKvSmem<D> SM;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   auto qbuf = [&](int buf) { return reinterpret_cast<uint16_t*>(smem + buf * 2 * SM::kTile); };
   auto gbuf = [&](int buf) { return reinterpret_cast<uint16_t*>(smem + buf * 2 * SM::kTile + SM::kTile); };
   float* stat = reinterpret_cast<float*>(smem + SM::kStatOff);
   float* mus = reinterpret_cast<float*>(smem + SM::kMuOff);
-  float* dzs = reinterpret_cast<float*>(smem + SM::kDzOff);
   float* dred = reinterpret_cast<float*>(smem + SM::kDotOff);
 
   const int entry = __builtin_amdgcn_readfirstlane(order[blockIdx.x]);
@@ -559,18 +558,9 @@ __global__ __launch_bounds__(256, 2) void bwd_kv_mfma_kernel(
   const float rscale = rsqrtf((float)D);
   const float c0 = kLog2e * rscale;
 
-  // K_j and V_j rows of this lane's key as operand fragments (rows past the end repeat the last one)
-  bf16x8 kfr[KS], vfr[KS];
-  {
-    const size_t row = (size_t)(t0 + min(mykey, valid - 1)) * tok_stride + 8 * g;
-#pragma unroll
-    for (int ks = 0; ks < KS; ks++) {
-      kfr[ks] = *reinterpret_cast<const bf16x8*>(kh_ + row + 16 * ks);
-      vfr[ks] = *reinterpret_cast<const bf16x8*>(vh + row + 16 * ks);
-    }
-  }
-  if (tid < D) mus[tid] = (float)k_mean[(size_t)bh * D + tid];
-
+  // K_j and V_j (rows past the end repeat the last one)
+  dma_tile<D, NW, SL>(kh_ + (size_t)t0 * tok_stride, tok_stride, valid, lds_address(qbuf(0)), w, lane);
+  dma_tile<D, NW, SL>(vh + (size_t)t0 * tok_stride, tok_stride, valid, lds_address(gbuf(0)), w, lane);
   const int32_t* cp = col_ptr + (size_t)bh * (Tn + 1);
   const int32_t* ci = col_idx + (size_t)bh * Tm * ksel;
   const int l0 = __builtin_amdgcn_readfirstlane(cp[j]), l1 = __builtin_amdgcn_readfirstlane(cp[j + 1]);
@@ -586,8 +576,7 @@ __global__ __launch_bounds__(256, 2) void bwd_kv_mfma_kernel(
     return Step{i, i * BQ + 64 * (t % HP), alpha[alpha_per_block ? (size_t)h * Tm + i : (size_t)h]};
   };
   auto request = [&](const Step& st, int buf) {
-    int ln = lane;
-    asm volatile("" : "+v"(ln));                      // lane addresses are made here each time, not kept through the loop
+    const int ln = (int)lane_again();                 // lane addresses are made here each time, not kept through the loop
     const int src = st.row0 < N ? st.row0 : st.i * BQ, rows = max(1, min(64, N - st.row0));
     dma_tile<D, NW, SL>(qh + (size_t)src * tok_stride, tok_stride, rows, lds_address(qbuf(buf)), w, ln);
     dma_tile<D, NW, SL>(doh + (size_t)src * sout.n, sout.n, rows, lds_address(gbuf(buf)), w, ln);
@@ -604,6 +593,122 @@ __global__ __launch_bounds__(256, 2) void bwd_kv_mfma_kernel(
 #pragma unroll
     for (int e = 0; e < 16; e++) { dvall[x][e] = 0.f; dkall[x][e] = 0.f; }
 
+  // ================= linear branch =================
+  // First: behind the loop every one of its steps (the lists' dZ_i, dH_j, its place in LDS, products, row sums) waits for the
+  // one before with nothing else to do, and takes registers from the accumulators.  What it gives is what they start from,
+  // each wave's half of the channel tiles.  12 heads of 32,760 tokens: 597 -> 566 us, 207 -> 188 without any list entry.
+  bf16x8 kfr[KS], vfr[KS];                           // K_j and V_j rows of this lane's key as operand fragments
+  {
+    const bool all_selected = ksel >= Tn;            // no gradient, whatever dO holds
+    uint16_t* dht = qbuf(1);                         // dH [c][e]
+    // dH (Alg. 3's M_c[i, j] = 0 sum, from bwd_totals) in the order in which the query-side kernel leaves dH_i
+    constexpr int NCH = D * D / 8 / NT;
+    const uint16_t* src = dh_in + ((size_t)bh * Tn + j) * D * D + (size_t)tid * 8;
+    bf16x8 x[NCH];
+#pragma unroll
+    for (int n = 0; n < NCH; n++) x[n] = *reinterpret_cast<const bf16x8*>(src + NT * n * 8);
+    const float lnz2 = k_stats[(size_t)bh * N + t0 + min(mykey, valid - 1)] * kLog2e;
+    if (tid < D) mus[tid] = (float)k_mean[(size_t)bh * D + tid];
+    // dZ_j = dZ_total less the dZ_i of the list, NT / D parts side by side and four entries each at a time on their way
+    constexpr int kParts = NT / D;
+    {
+      const int c = tid % D, part = tid / D, last = all_selected ? l0 : l1;
+      float dzj = (part == 0 && !all_selected) ? dz_total[(size_t)bh * D + c] : 0.f;
+      for (int l = l0 + 4 * part; l < last; l += 4 * kParts) {
+        float z[4];
+#pragma unroll
+        for (int y = 0; y < 4; y++) z[y] = dz_in[((size_t)bh * Tm + ci[min(l + y, last - 1)]) * D + c];
+#pragma unroll
+        for (int y = 0; y < 4; y++)
+          if (l + y < last) dzj -= z[y];
+      }
+      stat[tid] = dzj;
+    }
+#pragma unroll
+    for (int n = 0; n < NCH; n++) {
+      const int idx = tid + NT * n, l = idx % kWave, half = idx / kWave % 2, t = idx / (2 * kWave);
+      const int row = 32 * (t / ET) + l % 32, col = 32 * (t % ET) + 16 * half + 4 * (l / 32);
+#pragma unroll
+      for (int y = 0; y < 2; y++) {
+        bf16x4 four = {x[n][4 * y], x[n][4 * y + 1], x[n][4 * y + 2], x[n][4 * y + 3]};
+        if (all_selected) four = bf16x4{};
+        *reinterpret_cast<bf16x4*>(dht + SL::offset(row, col + 8 * y)) = four;
+      }
+    }
+    wait_vmcnt<0>();
+    __syncthreads();                                 // K_j, V_j, dH, parts of dZ_j and mus are in LDS for everyone
+    // K^phi_j = exp(K - colmean(K) - lnZ) (keys past the end: 0)
+    bf16x8 pfr[KS];
+#pragma unroll
+    for (int ks = 0; ks < KS; ks++) {
+      kfr[ks] = row_fragment<SL>(qbuf(0), mykey, 16 * ks + 8 * g);
+      vfr[ks] = row_fragment<SL>(gbuf(0), mykey, 16 * ks + 8 * g);
+      const f32x4 m0 = *reinterpret_cast<const f32x4*>(mus + 16 * ks + 8 * g);
+      const f32x4 m1 = *reinterpret_cast<const f32x4*>(mus + 16 * ks + 8 * g + 4);
+#pragma unroll
+      for (int e = 0; e < 8; e++)
+        pfr[ks][e] = (__bf16)(key_ok ? fast_exp2(((float)kfr[ks][e] - (e < 4 ? m0[e] : m1[e - 4])) * kLog2e - lnz2) : 0.f);
+      settle(pfr[ks]);                               // one fragment at a time: the registers
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    // dK^phi^T = dH V^T (+ dZ 1^T below) and dV^T += dH^T K^phi^T, both channels x keys
+    f32x16 dkp[CT], dvl[CT];
+#pragma unroll
+    for (int y = 0; y < CT; y++)
+#pragma unroll
+      for (int e = 0; e < 16; e++) { dkp[y][e] = 0.f; dvl[y][e] = 0.f; }
+#pragma unroll
+    for (int ks = 0; ks < KS; ks++) {
+#pragma unroll
+      for (int y = 0; y < CT; y++) {
+        const int ct = CT * rh + y;
+        dkp[y] = mfma_bf16(row_fragment<SL>(dht, 32 * ct + lane % 32, 16 * ks + 8 * g), vfr[ks], dkp[y]);   // over e
+        dvl[y] = mfma_bf16(nat_fragment<SL>(dht, ks, 32 * ct, lane), pfr[ks], dvl[y]);                     // over c
+      }
+      if (D == 64) __builtin_amdgcn_sched_barrier(0);
+    }
+    // back through phi: dK' += K^phi (.) (dK^phi - rowsum(dK^phi (.) K^phi)); the row sum spans all channels
+    float kp[CT][16];
+#pragma unroll
+    for (int y = 0; y < CT; y++) {
+      const int ct = CT * rh + y;
+      float part = 0.f;
+#pragma unroll
+      for (int v4 = 0; v4 < 4; v4++) {
+        const int c = 32 * ct + 8 * v4 + 4 * g;
+        const bf16x4 kk = *reinterpret_cast<const bf16x4*>(qbuf(0) + SL::offset(mykey, c));
+        const f32x4 m = *reinterpret_cast<const f32x4*>(mus + c);
+        f32x4 dz = *reinterpret_cast<const f32x4*>(stat + c);
+#pragma unroll
+        for (int n = 1; n < kParts; n++) dz += *reinterpret_cast<const f32x4*>(stat + n * D + c);
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+          kp[y][4 * v4 + r] = (float)(__bf16)(key_ok ? fast_exp2(((float)kk[r] - m[r]) * kLog2e - lnz2) : 0.f);
+          dkp[y][4 * v4 + r] += dz[r];
+          part += dkp[y][4 * v4 + r] * kp[y][4 * v4 + r];
+        }
+      }
+      part = half_sum(part);
+      if (g == 0) dred[ct * 64 + mykey] = part;
+    }
+    __syncthreads();                                 // row sums complete; the tiles have been read
+    float dot = 0.f;
+#pragma unroll
+    for (int c2 = 0; c2 < ET; c2++) dot += dred[c2 * 64 + mykey];
+    const float unscale = sqrtf((float)D);           // the loop's sums are scaled by 1 / sqrt(d) at the end
+    auto start_from = [&](auto half) {
+      constexpr int E0 = decltype(half)::value * CT;
+#pragma unroll
+      for (int y = 0; y < CT; y++) {
+        dvall[E0 + y] = dvl[y];
+#pragma unroll
+        for (int e = 0; e < 16; e++) dkall[E0 + y][e] = kp[y][e] * (dkp[y][e] - dot) * unscale;
+      }
+    };
+    if (rh == 0) start_from(std::integral_constant<int, 0>());
+    else start_from(std::integral_constant<int, 1>());
+  }
+
   Step cur{0, 0, 0.f};
   int i_nxt = 0;
   if (nsteps > 0) {
@@ -614,7 +719,7 @@ __global__ __launch_bounds__(256, 2) void bwd_kv_mfma_kernel(
   wait_vmcnt<0>();
 #pragma unroll
   for (int ks = 0; ks < KS; ks++) { settle(kfr[ks]); settle(vfr[ks]); }
-  __syncthreads();                                   // step 0 and mus are in LDS for everyone
+  __syncthreads();                                   // step 0 is in LDS for everyone
 
   // LDS byte offsets of this lane's operand reads inside a Q or dO tile.  Row-wise reads: row 32 rh + l % 32, channel
   // step ks at (offset of step 0) ^ 32 ks.  Transposing reads (cf. read_tr4): rows 32 rh + 4 g + (l % 16) / 4 (lo) and
@@ -727,10 +832,11 @@ __global__ __launch_bounds__(256, 2) void bwd_kv_mfma_kernel(
   }
 
   // the two row halves add up: each wave finishes half of the channel tiles and hands the other half over
+  const int ln = (int)lane_again(), thread = w * kWave + ln;   // (not kept through the loop)
   f32x16 dvacc[CT], dkacc[CT];
   {
-    float* mine = reinterpret_cast<float*>(smem) + (size_t)w * (2 * CT * 16 * kWave) + lane;
-    const float* other = reinterpret_cast<float*>(smem) + (size_t)(w ^ 1) * (2 * CT * 16 * kWave) + lane;
+    float* mine = reinterpret_cast<float*>(smem) + (size_t)w * (2 * CT * 16 * kWave) + ln;
+    const float* other = reinterpret_cast<float*>(smem) + (size_t)(w ^ 1) * (2 * CT * 16 * kWave) + ln;
     auto exchange = [&](auto half) {
       constexpr int E0 = decltype(half)::value * CT, F0 = CT - E0;
       __syncthreads();                               // the last step fully consumed
@@ -755,101 +861,9 @@ __global__ __launch_bounds__(256, 2) void bwd_kv_mfma_kernel(
   }
   __syncthreads();                                   // the halves have been read
 
-  // ================= linear branch =================
-  uint16_t* dht = reinterpret_cast<uint16_t*>(smem);                     // dH [c][e] as bf16, row stride LD
-  uint16_t* kpt = dht + D * LD;                                          // K^phi_j [key][c], row stride LD
-  const bool all_selected = ksel >= Tn;
+  uint16_t* okt = reinterpret_cast<uint16_t*>(smem);                     // dK' [key][c], then dV [key][e] behind it, row stride LD
+  uint16_t* ovt = okt + 64 * LD;
   {
-    // dH (Alg. 3's M_c[i, j] = 0 sum, from bwd_totals) in the order in which the query-side kernel leaves dH_i
-    constexpr int NCH = D * D / 8 / NT;
-    const uint16_t* src = dh_in + ((size_t)bh * Tn + j) * D * D + (size_t)tid * 8;
-    bf16x8 x[NCH];
-#pragma unroll
-    for (int n = 0; n < NCH; n++) x[n] = *reinterpret_cast<const bf16x8*>(src + NT * n * 8);
-#pragma unroll
-    for (int n = 0; n < NCH; n++) {
-      const int idx = tid + NT * n, l = idx % kWave, half = idx / kWave % 2, t = idx / (2 * kWave);
-      uint16_t* dst = dht + (32 * (t / ET) + l % 32) * LD + 32 * (t % ET) + 16 * half + 4 * (l / 32);
-#pragma unroll
-      for (int y = 0; y < 2; y++) {
-        bf16x4 four = {x[n][4 * y], x[n][4 * y + 1], x[n][4 * y + 2], x[n][4 * y + 3]};
-        if (all_selected) four = bf16x4{};           // no gradient, whatever dO holds
-        *reinterpret_cast<bf16x4*>(dst + 8 * y) = four;
-      }
-    }
-    const int last = all_selected ? l0 : l1;
-    float dzj = (tid < D && !all_selected) ? dz_total[(size_t)bh * D + tid] : 0.f;
-    if (tid < D)
-      for (int l = l0; l < last; l += 4) {             // four at a time on their way: one by one each costs a round trip
-        float z[4];
-#pragma unroll
-        for (int x = 0; x < 4; x++) z[x] = dz_in[((size_t)bh * Tm + ci[min(l + x, last - 1)]) * D + tid];
-#pragma unroll
-        for (int x = 0; x < 4; x++)
-          if (l + x < last) dzj -= z[x];
-      }
-    if (tid < D) dzs[tid] = dzj;
-  }
-  // K_j -> K^phi_j = exp(K - colmean(K) - lnZ) in the fragment registers (keys past the end: 0); one
-  // wave of each key half also leaves it in LDS for the softmax-backward step
-  {
-    const float lnz2 = k_stats[(size_t)bh * N + t0 + min(mykey, valid - 1)] * kLog2e;
-#pragma unroll
-    for (int ks = 0; ks < KS; ks++) {
-      const f32x4 m0 = *reinterpret_cast<const f32x4*>(mus + 16 * ks + 8 * g);
-      const f32x4 m1 = *reinterpret_cast<const f32x4*>(mus + 16 * ks + 8 * g + 4);
-#pragma unroll
-      for (int e = 0; e < 8; e++) {
-        const float kp = key_ok ? fast_exp2(((float)kfr[ks][e] - (e < 4 ? m0[e] : m1[e - 4])) * kLog2e - lnz2) : 0.f;
-        kfr[ks][e] = (__bf16)kp;
-      }
-      if (rh == 0) *reinterpret_cast<bf16x8*>(kpt + mykey * LD + 16 * ks + 8 * g) = kfr[ks];
-    }
-  }
-  __syncthreads();
-  // dK^phi^T = dH V^T (+ dZ 1^T below) and dV^T += dH^T K^phi^T, both channels x keys; V_j and K^phi_j
-  // are the B operands, from registers
-  f32x16 dkp[CT];
-#pragma unroll
-  for (int x = 0; x < CT; x++)
-#pragma unroll
-    for (int e = 0; e < 16; e++) dkp[x][e] = 0.f;
-#pragma unroll
-  for (int ks = 0; ks < KS; ks++) {
-#pragma unroll
-    for (int x = 0; x < CT; x++) {
-      const int ct = CT * rh + x;
-      dkp[x] = mfma_bf16(row_fragment<PL>(dht, 32 * ct + lane % 32, 16 * ks + 8 * g), vfr[ks], dkp[x]);   // over e
-      dvacc[x] = mfma_bf16(nat_fragment<PL>(dht, ks, 32 * ct, lane), kfr[ks], dvacc[x]);                 // over c
-    }
-  }
-  // back through phi: dK' += K^phi (.) (dK^phi - rowsum(dK^phi (.) K^phi)); the row sum spans all channels
-  float kp[CT][16];
-#pragma unroll
-  for (int x = 0; x < CT; x++) {
-    const int ct = CT * rh + x;
-    float part = 0.f;
-#pragma unroll
-    for (int v4 = 0; v4 < 4; v4++) {
-      const bf16x4 kk = *reinterpret_cast<const bf16x4*>(kpt + mykey * LD + 32 * ct + 8 * v4 + 4 * g);
-      const f32x4 dz = *reinterpret_cast<const f32x4*>(dzs + 32 * ct + 8 * v4 + 4 * g);
-#pragma unroll
-      for (int r = 0; r < 4; r++) {
-        kp[x][4 * v4 + r] = (float)kk[r];
-        dkp[x][4 * v4 + r] += dz[r];
-        part += dkp[x][4 * v4 + r] * kp[x][4 * v4 + r];
-      }
-    }
-    part = half_sum(part);
-    if (g == 0) dred[ct * 64 + mykey] = part;
-  }
-  __syncthreads();                                   // row sums complete; every wave is done with the dH and K^phi tiles
-  uint16_t* okt = dht;                               // dK' [key][c], then dV [key][e] behind it
-  uint16_t* ovt = dht + 64 * LD;
-  {
-    float dot = 0.f;
-#pragma unroll
-    for (int c2 = 0; c2 < ET; c2++) dot += dred[c2 * 64 + mykey];
 #pragma unroll
     for (int x = 0; x < CT; x++) {
       const int ct = CT * rh + x;
@@ -858,11 +872,11 @@ __global__ __launch_bounds__(256, 2) void bwd_kv_mfma_kernel(
         bf16x4 pk, pv;
 #pragma unroll
         for (int r = 0; r < 4; r++) {
-          pk[r] = (__bf16)(dkacc[x][4 * v4 + r] * rscale + kp[x][4 * v4 + r] * (dkp[x][4 * v4 + r] - dot));
+          pk[r] = (__bf16)(dkacc[x][4 * v4 + r] * rscale);
           pv[r] = (__bf16)dvacc[x][4 * v4 + r];
         }
-        *reinterpret_cast<bf16x4*>(okt + mykey * LD + 32 * ct + 8 * v4 + 4 * g) = pk;
-        *reinterpret_cast<bf16x4*>(ovt + mykey * LD + 32 * ct + 8 * v4 + 4 * g) = pv;
+        *reinterpret_cast<bf16x4*>(okt + (32 * kh + ln % 32) * LD + 32 * ct + 8 * v4 + 4 * (ln / 32)) = pk;
+        *reinterpret_cast<bf16x4*>(ovt + (32 * kh + ln % 32) * LD + 32 * ct + 8 * v4 + 4 * (ln / 32)) = pv;
       }
     }
   }
@@ -870,17 +884,31 @@ __global__ __launch_bounds__(256, 2) void bwd_kv_mfma_kernel(
   {
     uint16_t* dkh = dk + head_offset(sin, bh, H) + (size_t)t0 * tok_stride;
     uint16_t* dvh = dv + head_offset(sin, bh, H) + (size_t)t0 * tok_stride;
-    for (int idx = tid; idx < kTileTokens * (D / 8); idx += NT) {
+    for (int idx = thread; idx < kTileTokens * (D / 8); idx += NT) {
       const int t = idx / (D / 8), ch = idx % (D / 8);
       if (t < valid) {
         *reinterpret_cast<u32x4*>(dkh + (size_t)t * tok_stride + 8 * ch) = *reinterpret_cast<const u32x4*>(okt + t * LD + 8 * ch);
         *reinterpret_cast<u32x4*>(dvh + (size_t)t * tok_stride + 8 * ch) = *reinterpret_cast<const u32x4*>(ovt + t * LD + 8 * ch);
       }
     }
-    if (tid < D) {                                   // column sums of dK' (as stored) for the smoothing term
+    // column sums of dK' (as stored) for the smoothing term: two channels and 64 / kParts rows per thread
+    constexpr int kParts = 2 * NT / D, kRows = 64 / kParts;
+    const int c2 = thread % (D / 2), part = thread / (D / 2);
+    float s0 = 0.f, s1 = 0.f;
+#pragma unroll
+    for (int y = 0; y < kRows; y++) {
+      const int t = part * kRows + y;
+      const unsigned two = *reinterpret_cast<const unsigned*>(okt + t * LD + 2 * c2);
+      s0 += t < valid ? bf16_bits_to_f32((uint16_t)two) : 0.f;
+      s1 += t < valid ? bf16_bits_to_f32((uint16_t)(two >> 16)) : 0.f;
+    }
+    *reinterpret_cast<float2*>(stat + part * D + 2 * c2) = float2{s0, s1};
+    __syncthreads();
+    if (thread < D) {
       float sum = 0.f;
-      for (int t = 0; t < valid; t++) sum += bf16_bits_to_f32(okt[t * LD + tid]);
-      colsum[((size_t)bh * Tn + j) * D + tid] = sum;
+#pragma unroll
+      for (int y = 0; y < kParts; y++) sum += stat[y * D + thread];
+      colsum[((size_t)bh * Tn + j) * D + thread] = sum;
     }
   }
 }

@@ -335,12 +335,6 @@ hipError_t launch_kv_total(const Shape& s, const float* partial, float* h_total,
 // =============================================================================================
 // attn_mfma
 // =============================================================================================
-// The lane index again, from the hardware: what a long loop derives from it does not stay in registers meanwhile.
-__device__ __forceinline__ unsigned lane_again() {
-  unsigned l;
-  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
-  return l;
-}
 enum AttnMode { kSparseBf16 = 0, kSparseFp8 = 1, kDenseBf16 = 2, kSparseInt8 = 3, kSparseFp8V = 4 };
 
 
