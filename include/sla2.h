@@ -110,7 +110,9 @@ typedef struct sla2_ws_layout {
   size_t k_stats;   /* float  [BH, N]        per key token: lnZ = log sum_c exp(k'_c), k' = k - colmean(K); K^phi = exp(k' - lnZ) */
   size_t k_phi;     /* bf16   [BH, T_n, d/32, 4, 64, 8]  K^phi = softmax_d(K - colmean K) of each key block as matrix-core
                                                         operand fragments (bf16 path only): lane l of fragment (mt, ks)
-                                                        holds channel 32 mt + l%32, tokens 16 ks + 8 (i/4) + 4 (l/32) + i%4, i = 0..7 */
+                                                        holds channel 32 mt + l%32, tokens 16 ks + 8 (i/4) + 4 (l/32) + i%4, i = 0..7.
+                                                        d = 128 with 128-row blocks and long lists: H_i of the query blocks and
+                                                        scratch instead (the lists that the library takes for long are its own) */
   size_t z_blocks;  /* float  [BH, T_n, d]   z_j = colsum(K^phi_j) per key block (bf16 path only)        (Alg. 2: z) */
   size_t k_fp8;     /* uint8  [BH, T_n*block_kv, d]  e4m3 (FP8 mode) or two's-complement int8 (INT8 mode) codes of the
                        smoothed K; low-bit modes only; rows >= N are 0 */

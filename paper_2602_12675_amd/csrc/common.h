@@ -64,6 +64,8 @@ struct Shape {
   int quant;                                 // sla2_quant: 0 none, 1 FP8 e4m3, 2 INT8 codes of Q and K, 3 FP8 with V in e4m3 too
   // kv precompute: each workgroup reduces `blocks_per_chunk` key blocks; `chunks` per head
   int blocks_per_chunk, chunks;
+  // bf16 tensors, long lists: H_i formed before the attention kernel, the states of this many heads at a time (0: rebuilt there)
+  int state_heads;
 };
 
 // sla2_api.cpp: parameter validation (SLA2_OK or a negative sla2_status) and the workspace carve-up
@@ -192,6 +194,16 @@ hipError_t launch_kv_total(const Shape& s, const float* partial, float* h_total,
 hipError_t launch_kv_state_bf16(const Shape& s, const uint16_t* k, const uint16_t* v, const double* k_mean,
                                 float* k_stats, float* partial, uint16_t* k_phi, float* z_blocks, uint8_t* k_codes,
                                 float* k_scale, uint8_t* v_codes, float* v_scale, hipStream_t stream);
+// bf16 tensors with Shape::state_heads: kv_state with the states of the key blocks, and H_i from them
+struct GivenStates {
+  uint16_t* states;                          // [state_heads][T_n][2][d * d]: h_j as two bf16 parts, scratch
+  uint16_t* h_i;                             // [BH][T_m][d * d], in the order in which kv_state leaves the parts
+  uint32_t* bits;                            // scratch
+};
+hipError_t launch_kv_states_bf16(const Shape& s, const uint16_t* k, const uint16_t* v, const double* k_mean, float* k_stats,
+                                 float* partial, float* z_blocks, uint8_t* k_codes, float* k_scale, uint8_t* v_codes, float* v_scale,
+                                 const int32_t* block_idx, const GivenStates& gs, hipStream_t stream);
+// k_phi: with Shape::state_heads H_i in its place
 hipError_t launch_attn_bf16(const Shape& s, const uint16_t* q, const uint16_t* k, const uint16_t* v,
                             const double* k_mean, const uint16_t* k_phi, const float* z_blocks, const uint8_t* k_codes,
                             const float* k_scale, const uint8_t* v_codes, const float* v_scale,

@@ -7,6 +7,7 @@
 // gathers took 135 us of the key-side kernel and the sum of all dH_i 18 us, this product takes 84 us: 0.1 GB read, 0.2 GB
 // written, 52 GFLOP.  A gather grows with the kept fraction, this does not.  At d = 64 (32 heads of 64 by 64, 6 blocks a list):
 // 7 us of the key-side kernel against 6 us here.
+// Query side of the forward pass with long lists: launch_kv_states_bf16.
 #pragma once
 #include "mfma_tiles.h"
 

@@ -14,6 +14,21 @@ namespace sla2 {
 
 static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
+// bf16 tensors, d = 128, 128-row blocks: from which k on H_i is formed before the attention kernel (launch_kv_states_bf16: per key
+// block its states written and read, per pair of blocks 64 K products) rather than rebuilt in it (a third of its products per
+// selected pair, and 16 of 48 KB of its tiles).  Calls, us, rebuilt / formed before:
+//   8 heads of 75,600 tokens (T_n = 1,182)  bf16  k = 50 1,606 / 1,725   70 2,109 / 2,094   110 3,110 / 2,864
+//                                           FP8   k = 70 1,936 / 1,990   90 2,390 / 2,323   140 3,527 / 3,198
+//  12 heads of 32,760 (512)                 bf16  k = 30 660 / 725       50 979 / 960       90 1,601 / 1,439
+//                                           FP8   k = 50 913 / 941       70 1,189 / 1,152   90 1,466 / 1,342
+//  24 heads of 16,384 (256)                 bf16  k = 30 662 / 697       45 898 / 881       FP8  45 845 / 825
+//  48 heads of 4,096 (64)                   bf16  k = 36 384 / 401       60 567 / 532       FP8  44 426 / 425
+//  48 heads of 1,536 (24)                   bf16  k = 20 141 / 158
+// 80 heads of 75,601 tokens, bf16, k = 177: 51.5 -> 42.3 ms.
+constexpr float kStatesFrom = 40.f, kStatesPerBf16 = 0.025f, kStatesPerLowBit = 0.034f;
+// What the states of the heads that are worked on at a time may take: 8 heads of 1,182 key blocks, at the least one head.
+constexpr size_t kStateBytes = (size_t)640 << 20;
+
 // Validate everything that does not need pointers and derive the block counts.
 int make_shape(const sla2_params* p, Shape* s) {
   if (!p) return SLA2_EINVAL;
@@ -63,7 +78,13 @@ int make_shape(const sla2_params* p, Shape* s) {
   // would wait for a free slot and double the kernel's time, so the head's blocks are cut into the
   // largest number of chunks that still fits in one resident set.
   const int kResident = 512;
-  int chunks_max = kResident / s->BH;
+  s->state_heads = 0;
+  if (s->bf16 && s->d == 128 && s->bq == 128 && s->k > kStatesFrom + (s->quant ? kStatesPerLowBit : kStatesPerBf16) * s->Tn) {
+    const size_t head = (size_t)s->Tn * 2 * s->d * s->d * 2;
+    const size_t fit = kStateBytes / head;
+    s->state_heads = fit < 1 ? 1 : fit > (size_t)s->BH ? s->BH : (int)fit;
+  }
+  int chunks_max = kResident / (s->state_heads ? s->state_heads : s->BH);
   if (chunks_max < 1) chunks_max = 1;
   int bpc = (s->Tn + chunks_max - 1) / chunks_max;
   if (bpc < 1) bpc = 1;
@@ -109,6 +130,13 @@ static size_t bwd_scratch_bytes(const Shape& s) { return make_bwd_layout(s).tota
 // fp32 tensors: entries of the key blocks' states (a whole number of 256-byte units)
 static size_t f32_states(const Shape& s) { return ((size_t)s.BH * s.Tn * (s.d * s.d + s.d) + 63) & ~(size_t)63; }
 
+// with state_heads, in the place of K^phi: H_i, then the states of a group of heads, then the bits
+static size_t given_h(const Shape& s) { return align256((size_t)s.BH * s.Tm * s.d * s.d * 2); }
+static size_t given_states(const Shape& s) { return align256((size_t)s.state_heads * s.Tn * 2 * s.d * s.d * 2); }
+static size_t given_bytes(const Shape& s) {
+  return given_h(s) + given_states(s) + (size_t)s.BH * masked_words(2 * s.Tn) * masked_pitch(s.Tm) * sizeof(uint32_t);
+}
+
 void make_layout(const Shape& s, sla2_ws_layout* L) {
   size_t off = 0, BH = (size_t)s.BH, d = (size_t)s.d;
   auto take = [&](size_t bytes) { size_t o = off; off = align256(off + bytes); return o; };
@@ -120,7 +148,7 @@ void make_layout(const Shape& s, sla2_ws_layout* L) {
   L->h_total = take(BH * d * d * sizeof(float));
   L->z_total = take(BH * d * sizeof(float));
   L->k_stats = take(BH * (size_t)s.N * sizeof(float));
-  L->k_phi = take(s.bf16 ? BH * (size_t)s.Tn * s.bk * d * 2 : 0);
+  L->k_phi = take(s.bf16 ? (s.state_heads ? given_bytes(s) : BH * (size_t)s.Tn * s.bk * d * 2) : 0);
   L->z_blocks = take(s.bf16 ? BH * (size_t)s.Tn * d * sizeof(float) : 0);
   L->k_fp8 = take(s.quant ? BH * (size_t)s.Tn * s.bk * d : 0);
   L->k_scale = take(s.quant ? BH * (size_t)s.Tn * sizeof(float) : 0);
@@ -351,7 +379,13 @@ int sla2_forward(const sla2_params* params, const void* q, const void* k, const 
   float* k_scale = at<float>(workspace, L.k_scale);
   uint8_t* v_fp8 = at<uint8_t>(workspace, L.v_fp8);
   float* v_scale = at<float>(workspace, L.v_scale);
-  if (SLA2_STAGE(SLA2_STAGE_KV_STATE,
+  GivenStates gs{(uint16_t*)((char*)k_phi + given_h(s)), k_phi, (uint32_t*)((char*)k_phi + given_h(s) + given_states(s))};
+  if (s.state_heads) {
+    if (SLA2_STAGE(SLA2_STAGE_KV_STATE,
+                   launch_kv_states_bf16(s, (const uint16_t*)k, (const uint16_t*)v, k_mean, k_stats, partial, z_blocks, k_fp8, k_scale,
+                                         v_fp8, v_scale, idx, gs, st)) != hipSuccess)
+      return SLA2_EHIP;
+  } else if (SLA2_STAGE(SLA2_STAGE_KV_STATE,
                  launch_kv_state_bf16(s, (const uint16_t*)k, (const uint16_t*)v, k_mean, k_stats, partial, k_phi,
                                       z_blocks, k_fp8, k_scale, v_fp8, v_scale, st)) != hipSuccess)
     return SLA2_EHIP;

@@ -10,7 +10,8 @@
 //                     the d x d state of exactly those blocks, sum_sel (K^phi_j)^T V_j, from the stored
 //                     K^phi fragments and the V tile that is already staged for P V;
 //                     H_i = H_total - that sum, Z_i = Z_total - sum_sel z_j  (complement of the
-//                     M_c[i,j] = 0 sum of Alg. 2);  O_l = Q^phi H_i / (Q^phi Z_i);
+//                     M_c[i,j] = 0 sum of Alg. 2; for long lists H_i is formed beforehand, by
+//                     block_states_bf16);  O_l = Q^phi H_i / (Q^phi Z_i);
 //                     out = alpha O_s + (1 - alpha) O_l                                     (Eq. 13)
 //                   The same kernel with the block list replaced by 0..T_n-1 and the linear branch
 //                   compiled out is the dense attention comparator.
@@ -20,7 +21,7 @@
 // with V quantised as well, P V is a 64-deep FP8 product too.  Scores are kept transposed (S^T = K Q^T) so that one lane owns one query row:
 // row maxima and sums are in-lane reductions plus one exchange between the two lane halves, and
 // the probabilities go back into the next product as its B operand without leaving registers.
-#include "mfma_tiles.h"
+#include "masked_sums.h"
 
 namespace sla2 {
 
@@ -55,16 +56,20 @@ __device__ __forceinline__ size_t kphi_offset(size_t block, int mt, int ks, int 
 // =============================================================================================
 // kv_state_bf16
 // =============================================================================================
-template <int D, int QUANT>   // QUANT: 0 none, 1 FP8 e4m3 codes of K - colmean K, 2 INT8 codes, 3 as 1 plus e4m3 codes of V
-__global__ __launch_bounds__(256) void kv_state_bf16_kernel(const uint16_t* __restrict__ k,
+// QUANT: 0 none, 1 FP8 e4m3 codes of K - colmean K, 2 INT8 codes, 3 as 1 plus e4m3 codes of V.
+// STATES: h_j of every key block is written too, as the sum of two bf16 parts (2^-17 of an entry is left out), in the place of
+// K^phi: rows 2 j and 2 j + 1 of `states`, each as the accumulators lie - [tile (mt, nt)][2][64 lanes][8], lane l of half y
+// holding column e = 32 nt + l % 32, rows c = 32 mt + 16 y + 4 (l / 32) + {0..3, 8..11}.  The heads are those from bh0 on.
+template <int D, int QUANT, bool STATES>
+__global__ __launch_bounds__(256, STATES ? 2 : 1) void kv_state_bf16_kernel(const uint16_t* __restrict__ k,
                                                             const uint16_t* __restrict__ v,
                                                             const double* __restrict__ k_mean,
                                                             float* __restrict__ k_stats, float* __restrict__ partial,
                                                             uint16_t* __restrict__ k_phi, float* __restrict__ z_blocks,
                                                             uint8_t* __restrict__ k_codes, float* __restrict__ k_scale,
                                                             uint8_t* __restrict__ v_codes, float* __restrict__ v_scale,
-                                                            Strides sin, int H, int N, int Tn, int chunks,
-                                                            int blocks_per_chunk) {
+                                                            uint16_t* __restrict__ states, Strides sin, int bh0, int H, int N,
+                                                            int Tn, int chunks, int blocks_per_chunk) {
   constexpr int LD = TileGeom<D>::kLd;
   typedef HSplit<D, 4> HS;
   __shared__ __attribute__((aligned(16))) uint16_t ktile[kTileTokens * LD];
@@ -73,7 +78,7 @@ __global__ __launch_bounds__(256) void kv_state_bf16_kernel(const uint16_t* __re
   __shared__ float mu_s[D];
   __shared__ float red[4];
   __shared__ float red_v[4];
-  const int bh = blockIdx.x / chunks, chunk = blockIdx.x % chunks;
+  const int bh = bh0 + blockIdx.x / chunks, chunk = blockIdx.x % chunks;
   const int tid = threadIdx.x, lane = tid % kWave, w = tid / kWave, g = lane / 32;
   const uint16_t* kh = k + head_offset(sin, bh, H);
   const uint16_t* vh = v + head_offset(sin, bh, H);
@@ -233,20 +238,51 @@ __global__ __launch_bounds__(256) void kv_state_bf16_kernel(const uint16_t* __re
     float zsum[HS::kMtw];
 #pragma unroll
     for (int a = 0; a < HS::kMtw; a++) zsum[a] = 0.f;
+    if constexpr (STATES) {
+      static_assert(HS::kMtw == 1, "one row of tiles a wave");
+      bf16x8 kf[kTileTokens / 16];
 #pragma unroll
-    for (int ks = 0; ks < kTileTokens / 16; ks++) {
-      bf16x8 kf[HS::kMtw];
-#pragma unroll
-      for (int a = 0; a < HS::kMtw; a++) {
-        kf[a] = kphi_fragment<PaddedLayout<D>>(ktile, lnz2, mu2[a], ks, 32 * (mt0 + a), lane, zsum[a]);
-        if (nt0 == 0)
-          *reinterpret_cast<bf16x8*>(k_phi + kphi_offset<D>((size_t)bh * Tn + j, mt0 + a, ks, lane)) = kf[a];
-      }
+      for (int ks = 0; ks < kTileTokens / 16; ks++)
+        kf[ks] = kphi_fragment<PaddedLayout<D>>(ktile, lnz2, mu2[0], ks, 32 * mt0, lane, zsum[0]);
+      uint16_t* hi = states + ((size_t)(bh - bh0) * Tn + j) * (2 * D * D) + ((mt0 * (D / 32) + nt0) * 2 * kWave + lane) * 8;
 #pragma unroll
       for (int b = 0; b < HS::kNtw; b++) {
-        bf16x8 vf = v_fragment<PaddedLayout<D>>(vtile, ks, 32 * (nt0 + b), lane);
+        f32x16 h;
 #pragma unroll
-        for (int a = 0; a < HS::kMtw; a++) hacc[a][b] = mfma_bf16(kf[a], vf, hacc[a][b]);
+        for (int e = 0; e < 16; e++) h[e] = 0.f;
+#pragma unroll
+        for (int ks = 0; ks < kTileTokens / 16; ks++)
+          h = mfma_bf16(kf[ks], v_fragment<PaddedLayout<D>>(vtile, ks, 32 * (nt0 + b), lane), h);
+#pragma unroll
+        for (int y = 0; y < 2; y++) {
+          bf16x8 large, small;
+#pragma unroll
+          for (int e = 0; e < 8; e++) {
+            large[e] = (__bf16)h[8 * y + e];
+            small[e] = (__bf16)(h[8 * y + e] - (float)large[e]);
+          }
+          *reinterpret_cast<bf16x8*>(hi + (2 * b + y) * kWave * 8) = large;
+          *reinterpret_cast<bf16x8*>(hi + D * D + (2 * b + y) * kWave * 8) = small;
+        }
+        hacc[0][b] += h;
+        __builtin_amdgcn_sched_barrier(0);             // one tile at a time: the registers
+      }
+    } else {
+#pragma unroll
+      for (int ks = 0; ks < kTileTokens / 16; ks++) {
+        bf16x8 kf[HS::kMtw];
+#pragma unroll
+        for (int a = 0; a < HS::kMtw; a++) {
+          kf[a] = kphi_fragment<PaddedLayout<D>>(ktile, lnz2, mu2[a], ks, 32 * (mt0 + a), lane, zsum[a]);
+          if (nt0 == 0)
+            *reinterpret_cast<bf16x8*>(k_phi + kphi_offset<D>((size_t)bh * Tn + j, mt0 + a, ks, lane)) = kf[a];
+        }
+#pragma unroll
+        for (int b = 0; b < HS::kNtw; b++) {
+          bf16x8 vf = v_fragment<PaddedLayout<D>>(vtile, ks, 32 * (nt0 + b), lane);
+#pragma unroll
+          for (int a = 0; a < HS::kMtw; a++) hacc[a][b] = mfma_bf16(kf[a], vf, hacc[a][b]);
+        }
       }
     }
 #pragma unroll
@@ -256,7 +292,7 @@ __global__ __launch_bounds__(256) void kv_state_bf16_kernel(const uint16_t* __re
       if (g == 0 && nt0 == 0) z_blocks[((size_t)bh * Tn + j) * D + 32 * (mt0 + a) + lane] = z;
     }
   }
-  float* ph = partial + (size_t)blockIdx.x * (D * D + D);
+  float* ph = partial + ((size_t)bh * chunks + chunk) * (D * D + D);
 #pragma unroll
   for (int a = 0; a < HS::kMtw; a++) {
 #pragma unroll
@@ -275,9 +311,9 @@ hipError_t launch_kv_state_bf16(const Shape& s, const uint16_t* k, const uint16_
                                 float* k_scale, uint8_t* v_codes, float* v_scale, hipStream_t stream) {
   dim3 grid((unsigned)(s.BH * s.chunks));
 #define SLA2_KV(DD, QQ)                                                                                          \
-  kv_state_bf16_kernel<DD, QQ><<<grid, 256, 0, stream>>>(k, v, k_mean, k_stats, partial, k_phi, z_blocks, k_codes, \
-                                                         k_scale, v_codes, v_scale, s.sin, s.H, s.N, s.Tn, s.chunks, \
-                                                         s.blocks_per_chunk)
+  kv_state_bf16_kernel<DD, QQ, false><<<grid, 256, 0, stream>>>(k, v, k_mean, k_stats, partial, k_phi, z_blocks, k_codes, \
+                                                                k_scale, v_codes, v_scale, nullptr, s.sin, 0, s.H, s.N, s.Tn, \
+                                                                s.chunks, s.blocks_per_chunk)
 #define SLA2_KV_D(DD)                                                                                  \
   do {                                                                                                 \
     if (s.quant == 3) SLA2_KV(DD, 3); else if (s.quant == 2) SLA2_KV(DD, 2);                           \
@@ -288,6 +324,72 @@ hipError_t launch_kv_state_bf16(const Shape& s, const uint16_t* k, const uint16_
 #undef SLA2_KV_D
 #undef SLA2_KV
   return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------------------------
+// H_i of all query blocks of a call as a product of the selection's complement with all h_j (masked_sums.h), for long lists:
+// an h_j in two bf16 parts (the error of the linear branch alone against fp64 is what it was, 1.8e-3 to 2.6e-3 for 64 to 200 key
+// blocks, within 2e-4 of itself), the sum in fp32, H_i as bf16 (as the attention kernel applies it) in the order of kv_state.
+// On 8 heads of 75,601 tokens: kv_state 173 us (0.6 GB written, K^phi left out), the product 360 us (366 GFLOP, 1.0 PFLOP/s); the
+// attention kernel without the rebuilt states takes 35.4 instead of 48.4 ms on 80 of them at 85 % sparsity.
+//
+// block_bits: the complement as bits, 2 j and 2 j + 1 of a row for key block j; one workgroup per 64 rows of a head.
+__global__ __launch_bounds__(256) void block_bits_kernel(const int32_t* __restrict__ block_idx, uint32_t* __restrict__ bits, int Tm, int Tn,
+                                                         int ksel) {
+  extern __shared__ uint32_t listed[];                // [words][64]
+  const int words = masked_words(2 * Tn), pitch = masked_pitch(Tm), r0 = blockIdx.x * 64, bh = blockIdx.y, rows = min(64, Tm - r0);
+  for (int x = threadIdx.x; x < 64 * words; x += 256) listed[x] = 0u;
+  __syncthreads();
+  const int32_t* idx = block_idx + ((size_t)bh * Tm + r0) * ksel;
+  for (int e = threadIdx.x; e < rows * ksel; e += 256) {
+    const int j = idx[e];
+    atomicOr(&listed[j / 16 * 64 + e / ksel], 3u << (2 * (j % 16)));   // OR: the result does not depend on the order
+  }
+  __syncthreads();
+  for (int x = threadIdx.x; x < 64 * words; x += 256) {
+    const int y = x / 64, left = 2 * Tn - 32 * y;
+    const uint32_t open = left >= 32 ? ~0u : left > 0 ? (1u << left) - 1u : 0u;
+    bits[((size_t)bh * words + y) * pitch + r0 + x % 64] = ~listed[x] & open;
+  }
+}
+
+// The tiles of one set of columns, which read the same states, run next to each other on one XCD.
+__global__ __launch_bounds__(256, 2) void block_states_bf16_kernel(const uint16_t* __restrict__ states, const uint32_t* __restrict__ bits,
+                                                                   uint16_t* __restrict__ h_i, int Tm, int Tn, int len) {
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+  const int tiles = (Tm + kMaskedRows - 1) / kMaskedRows, sets = len / kMaskedCols;
+  const int y = blockIdx.x / kXcds, set = y / tiles * kXcds + blockIdx.x % kXcds, head = set / sets;   // sets: a multiple of 8
+  masked_sums_tile(states + (size_t)head * 2 * Tn * len, bits + (size_t)head * masked_words(2 * Tn) * masked_pitch(Tm),
+                   h_i + (size_t)head * Tm * len, 2 * Tn, Tm, len, y % tiles * kMaskedRows, set % sets * kMaskedCols, smem);
+}
+
+// As many heads at a time as their states fill kStateBytes: with kv_state of a group, its product.
+hipError_t launch_kv_states_bf16(const Shape& s, const uint16_t* k, const uint16_t* v, const double* k_mean, float* k_stats,
+                                 float* partial, float* z_blocks, uint8_t* k_codes, float* k_scale, uint8_t* v_codes, float* v_scale,
+                                 const int32_t* block_idx, const GivenStates& gs, hipStream_t stream) {
+  const int words = masked_words(2 * s.Tn), len = s.d * s.d, tiles = (s.Tm + kMaskedRows - 1) / kMaskedRows;
+  block_bits_kernel<<<dim3((unsigned)((s.Tm + 63) / 64), (unsigned)s.BH), 256, 64 * words * sizeof(uint32_t), stream>>>(   // at most 32 KB
+      block_idx, gs.bits, s.Tm, s.Tn, s.k);
+  if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+  static OncePerDevice once;
+  if (hipError_t e = allow_dynamic_lds(once, (const void*)block_states_bf16_kernel, kMaskedLds); e != hipSuccess) return e;
+  for (int bh0 = 0; bh0 < s.BH; bh0 += s.state_heads) {
+    const int heads = s.BH - bh0 < s.state_heads ? s.BH - bh0 : s.state_heads;
+#define SLA2_KV(QQ)                                                                                                        \
+  kv_state_bf16_kernel<128, QQ, true><<<dim3((unsigned)(heads * s.chunks)), 256, 0, stream>>>(                             \
+      k, v, k_mean, k_stats, partial, nullptr, z_blocks, k_codes, k_scale, v_codes, v_scale, gs.states, s.sin, bh0, s.H, s.N, \
+      s.Tn, s.chunks, s.blocks_per_chunk)
+    if (s.quant == 3) SLA2_KV(3);
+    else if (s.quant == 2) SLA2_KV(2);
+    else if (s.quant == 1) SLA2_KV(1);
+    else SLA2_KV(0);
+#undef SLA2_KV
+    if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+    block_states_bf16_kernel<<<dim3((unsigned)(heads * (len / kMaskedCols) * tiles)), 256, kMaskedLds, stream>>>(
+        gs.states, gs.bits + (size_t)bh0 * words * masked_pitch(s.Tm), gs.h_i + (size_t)bh0 * s.Tm * len, s.Tm, s.Tn, len);
+    if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 // Totals over the chunks of a head (Alg. 2's sums of h_j and z_j over all key blocks).  A thread owns 4 consecutive entries
@@ -359,13 +461,13 @@ constexpr int kPipelinedTiles = 2500;
 // waves 0, 1 pass through the place of the second V tile and those of waves 2, 3 through that from the second K tile on.
 // Epilogue, over the same memory: H_i^T as bf16 [D][D+8], the output tile [BQ][D+8] and Z_i as fp32.  At
 // d = 128 the loop takes at most 80 KB: two workgroups a CU.
-template <int D, int BQ, bool FP8, bool VQ, bool PIPE> struct AttnSmem {
+template <int D, int BQ, bool FP8, bool VQ, bool PIPE, bool GIVEN> struct AttnSmem {
   static constexpr int kLd = TileGeom<D>::kLd, NW = BQ / 32;
   static constexpr int kVBytes = SwizzledLayout<D>::kTileBytes;
   static constexpr int kKBytes = FP8 ? SwizzledLayout8<D>::kTileBytes : kVBytes;
   static constexpr int kVqBytes = VQ ? SwizzledLayoutVq<D>::kTileBytes : 0;   // e4m3 codes of V, when P V is an FP8 product
   static constexpr int kQBytes = 32 * D * 2;                        // query rows of one wave
-  static constexpr int kVOff = PIPE ? kTileTokens * D * 2 : 0;      // behind the K^phi fragments
+  static constexpr int kVOff = PIPE && !GIVEN ? kTileTokens * D * 2 : 0;      // behind the K^phi fragments
   static constexpr int kVq0Off = kVOff + 2 * kVBytes;
   static constexpr int kKOff = kVq0Off + kVqBytes;
   static constexpr int kVq1Off = kKOff + 2 * kKBytes;
@@ -382,7 +484,8 @@ template <int D, int BQ, bool FP8, bool VQ, bool PIPE> struct AttnSmem {
 // two waves hold half of the d x d state each; 3 for d = 64 with 128-row blocks, where the accumulators are small
 // enough for 168 registers (measured on a 32,760-token d = 64 input: 6 % faster in FP8 mode, 10 % in bf16 mode;
 // with 64-row blocks three waves gain nothing).
-template <int D, int BQ, int MODE, bool PIPE>
+// GIVEN (pipelined loop): H_i was formed before (launch_kv_states_bf16) and is not rebuilt from K^phi; `k_phi` points to it.
+template <int D, int BQ, int MODE, bool PIPE, bool GIVEN>
 __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ == 128) ? 3 : 2) void attn_mfma_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const double* __restrict__ k_mean, const uint16_t* __restrict__ k_phi, const float* __restrict__ z_blocks,
@@ -403,7 +506,7 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
   constexpr int KS = D / 16;            // contraction steps over the head dimension
   constexpr int ET = D / 32;            // 32-wide tiles over the head dimension
   typedef HSplit<D, NW> HS;
-  typedef AttnSmem<D, BQ, FP8, FP8V, PIPE> SM;
+  typedef AttnSmem<D, BQ, FP8, FP8V, PIPE, GIVEN> SM;
   // the layout without bank conflicts where the tile transfers of a workgroup's waves allow it
   typedef typename std::conditional<PIPE && D == 128 && NW == 4, SwizzledLayoutB<128>, SwizzledLayout<D>>::type SL;
   typedef SwizzledLayout8<D> SL8;
@@ -414,7 +517,7 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
   constexpr int kKOps = kTileTokens * D * (FP8 ? 1 : 2) / 1024 / NW;
   constexpr int kVOps = kTileTokens * D * 2 / 1024 / NW + (FP8V ? kTileTokens * D / 1024 / NW : 0);
   constexpr int kDmaOps = kKOps + kVOps;
-  constexpr int kSteps = kTileTokens / 16, kPhiOps = PIPE ? HS::kMtw * kSteps : 0;
+  constexpr int kSteps = kTileTokens / 16, kPhiOps = PIPE && !GIVEN ? HS::kMtw * kSteps : 0;
   constexpr int kQOps = SM::kQBytes / 1024;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   const unsigned lds0 = lds_address(smem);
@@ -456,7 +559,7 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
   // key block j: global memory -> LDS buffer `buf`, no registers involved (completion: vmcnt)
   const uint8_t* k_codes_h = FP8 ? k_codes + blk0 * (kTileTokens * D) : nullptr;
   const uint8_t* v_codes_h = FP8V ? v_codes + blk0 * (kTileTokens * D) : nullptr;
-  const uint16_t* k_phi_h = DENSE ? nullptr : k_phi + kphi_offset<D>(blk0, mt0, 0, 0);
+  const uint16_t* k_phi_h = DENSE || GIVEN ? nullptr : k_phi + kphi_offset<D>(blk0, mt0, 0, 0);
   const unsigned tile_stride = (unsigned)tok_stride * (kTileTokens * 2);   // bytes; below 2^31
   auto rows_at = [&](const uint16_t* head, int j) { return (const uint16_t*)((const char*)head + (size_t)(unsigned)j * tile_stride); };
   // what a lane adds to the base of its transfers; the pipelined loop keeps these in registers
@@ -512,9 +615,16 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
   // The state accumulators start at -H_total (and -Z_total): the loop adds the h_j and z_j of the selected
   // blocks, which leaves -(H_total - sum) = -H_i.  The total lies there negated and as accumulator fragments
   // (kv_total): four 16-byte loads a tile.
-  f32x4 hq[HS::kMtw][HS::kNtw][4];
+  // GIVEN: H_i itself, 16 bytes of the slot per thread and kilobyte; it waits in registers for the epilogue.
+  constexpr int kGivenLoads = GIVEN ? D * D / 8 / NT : 1;
+  f32x4 hq[HS::kMtw][HS::kNtw][4], hgiven[kGivenLoads];
   float zsel[HS::kMtw];
   if constexpr (!DENSE) {
+    if constexpr (GIVEN) {
+      const float* slot = reinterpret_cast<const float*>(k_phi + ((size_t)bh * Tm + i) * D * D) + w * (D * D / 2 / NW);
+#pragma unroll
+      for (int x = 0; x < kGivenLoads; x++) hgiven[x] = load16_untracked_at(slot + 1024 * (x / 4), lane16, x % 4);
+    } else {
 #pragma unroll
     for (int a = 0; a < HS::kMtw; a++)
 #pragma unroll
@@ -522,13 +632,14 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
 #pragma unroll
         for (int x = 0; x < 4; x++)
           hq[a][b][x] = load16_untracked_at(h_frag + (size_t)bh * D * D + ((mt0 + a) * ET + nt0 + b) * 1024, lane16, x);
+    }
 #pragma unroll
     for (int a = 0; a < HS::kMtw; a++)
       zsel[a] = load_untracked_at(z_total + (size_t)bh * D + 32 * (mt0 + a), 4u * (unsigned)(lane % 32));
   }
   if (ntiles > 0) {
     dma(j_cur, 0);
-    if constexpr (PIPE) {
+    if constexpr (PIPE && !GIVEN) {
 #pragma unroll
       for (int a = 0; a < HS::kMtw; a++)
 #pragma unroll
@@ -547,7 +658,7 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
     }
 #pragma unroll
     for (int b = 0; b < HS::kNtw; b++)
-      if constexpr (!DENSE) {
+      if constexpr (!DENSE && !GIVEN) {
 #pragma unroll
         for (int x = 0; x < 4; x++) {
           settle(hq[a][b][x]);
@@ -556,6 +667,10 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
         }
         settle(hacc[a][b]);                          // one value from here on, not four
       }
+  }
+  if constexpr (GIVEN) {
+#pragma unroll
+    for (int x = 0; x < kGivenLoads; x++) settle(hgiven[x]);
   }
   // bf16 product: fragment ks = columns 16 ks + 8 g + 0..7.  FP8 product (64 deep): the lane's
   // operand of step ks2 is columns 64 ks2 + 32 g + 0..31, held as fragments 4 ks2 + 0..3.
@@ -912,6 +1027,7 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
         v_at[f] = issued += 2;
       };
       auto read_phi = [&](int ks) {
+        if constexpr (GIVEN) return;
 #pragma unroll
         for (int a = 0; a < HS::kMtw; a++) ph[ks % 2][a] = lds_read16_untracked_at<1024>(pa + a * (kSteps * 1024), ks);
         issued += HS::kMtw;
@@ -957,7 +1073,7 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
         wait_lgkmcnt(issued - v_at[f]);
         settle(vlo[f % (kVAhead + 1)]);
         settle(vhi[f % (kVAhead + 1)]);
-        if (et == 0) {
+        if (!GIVEN && et == 0) {
 #pragma unroll
           for (int a = 0; a < HS::kMtw; a++) settle(ph[ks % 2][a]);
           asm volatile("" ::: "memory");             // the fragments have left LDS: their successors may be requested
@@ -977,8 +1093,10 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
         const u32x4 v4 = {vlo[f % (kVAhead + 1)][0], vlo[f % (kVAhead + 1)][1], vhi[f % (kVAhead + 1)][0], vhi[f % (kVAhead + 1)][1]};
         const bf16x8 vf = __builtin_bit_cast(bf16x8, v4);
         if constexpr (!FP8V) oacc[et] = mfma_bf16(vf, pf[ks], oacc[et]);
+        if constexpr (!GIVEN) {
 #pragma unroll
-        for (int a = 0; a < HS::kMtw; a++) hacc[a][et] = mfma_bf16(__builtin_bit_cast(bf16x8, ph[ks % 2][a]), vf, hacc[a][et]);
+          for (int a = 0; a < HS::kMtw; a++) hacc[a][et] = mfma_bf16(__builtin_bit_cast(bf16x8, ph[ks % 2][a]), vf, hacc[a][et]);
+        }
         if constexpr (LAST) {
           if (f == kQFrom) q_max();
           if (f > kQFrom) {
@@ -1286,7 +1404,7 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
 #pragma unroll
     for (int a = 0; a < HS::kMtw; a++) {
 #pragma unroll
-      for (int b = 0; b < HS::kNtw; b++) {
+      for (int b = 0; b < (GIVEN ? 0 : HS::kNtw); b++) {
         const int e_col = 32 * (nt0 + b) + lane % 32;
 #pragma unroll
         for (int v4 = 0; v4 < 4; v4++) {
@@ -1303,6 +1421,16 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
         const float z = -zsel[a];
         if (z_save != nullptr) z_save[((size_t)bh * Tm + i) * D + c] = z;
         zs[c] = z;
+      }
+    }
+    if constexpr (GIVEN) {
+#pragma unroll
+      for (int x = 0; x < kGivenLoads; x++) {
+        const int n = w * kGivenLoads + x, t = n / 2;  // kilobyte of the slot, tile of h
+        const bf16x8 y = __builtin_bit_cast(bf16x8, hgiven[x]);
+        uint16_t* dst = ht + (32 * (t % ET) + lane % 32) * LD + 32 * (t / ET) + 16 * (n % 2) + 4 * g;
+        *reinterpret_cast<bf16x4*>(dst) = bf16x4{y[0], y[1], y[2], y[3]};
+        *reinterpret_cast<bf16x4*>(dst + 8) = bf16x4{y[4], y[5], y[6], y[7]};
       }
     }
     __syncthreads();                                 // H_i^T and Z_i visible
@@ -1439,14 +1567,14 @@ struct AttnArgs {
   SavedForBackward sv;
 };
 
-template <int D, int BQ, int MODE, bool PIPE>
+template <int D, int BQ, int MODE, bool PIPE, bool GIVEN = false>
 static hipError_t launch_attn_loop(const Shape& s, const AttnArgs& a, hipStream_t stream) {
-  constexpr int smem = AttnSmem<D, BQ, MODE == kSparseFp8 || MODE == kSparseInt8 || MODE == kSparseFp8V, MODE == kSparseFp8V, PIPE>::kBytes;
+  constexpr int smem = AttnSmem<D, BQ, MODE == kSparseFp8 || MODE == kSparseInt8 || MODE == kSparseFp8V, MODE == kSparseFp8V, PIPE, GIVEN>::kBytes;
   static OncePerDevice once;
-  if (hipError_t e = allow_dynamic_lds(once, (const void*)attn_mfma_kernel<D, BQ, MODE, PIPE>, smem); e != hipSuccess) return e;
+  if (hipError_t e = allow_dynamic_lds(once, (const void*)attn_mfma_kernel<D, BQ, MODE, PIPE, GIVEN>, smem); e != hipSuccess) return e;
   const int Tm = (s.N + BQ - 1) / BQ;
   const int grid = ((Tm + kXcds - 1) / kXcds) * kXcds * s.BH;   // some workgroups of the last run of a head may have no block
-  attn_mfma_kernel<D, BQ, MODE, PIPE><<<dim3((unsigned)grid), BQ * 2, smem, stream>>>(
+  attn_mfma_kernel<D, BQ, MODE, PIPE, GIVEN><<<dim3((unsigned)grid), BQ * 2, smem, stream>>>(
       a.q, a.k, a.v, a.k_mean, a.k_phi, a.z_blocks, a.k_fp8, a.k_scale, a.v_codes, a.v_scale, a.h_frag, a.z_total,
       a.block_idx, a.alpha,
       a.out, a.lse, (uint16_t*)a.sv.o_s, (uint16_t*)a.sv.o_l, a.sv.lse, (uint16_t*)a.sv.h_i, a.sv.z_i, s.sin, s.sout, s.H, s.N, Tm, s.Tn, s.k,
@@ -1456,6 +1584,8 @@ static hipError_t launch_attn_loop(const Shape& s, const AttnArgs& a, hipStream_
 
 template <int D, int BQ, int MODE>
 static hipError_t launch_attn_t(const Shape& s, const AttnArgs& a, hipStream_t stream) {
+  if constexpr (D == 128 && BQ == 128 && MODE != kDenseBf16)
+    if (s.state_heads > 0) return launch_attn_loop<D, BQ, MODE, true, true>(s, a, stream);
   if constexpr (kPlainToo<D, BQ, MODE>)
     if (s.k * s.Tn > kPipelinedTiles) return launch_attn_loop<D, BQ, MODE, false>(s, a, stream);   // below 2^22
   return launch_attn_loop<D, BQ, MODE, kPipelined<D, BQ, MODE>>(s, a, stream);
