@@ -122,10 +122,10 @@ typedef struct sla2_ws_layout {
                        byte 32 g + b of a row holds token 32 (b / 16) + 8 ((b % 16) / 4) + 4 g + b % 4
                        (g = 0, 1; b = 0..31).  SLA2_QUANT_FP8_V only; tokens >= N are 0 */
   size_t v_scale;   /* float  [BH, T_n]      dequantisation scale of each V block (SLA2_QUANT_FP8_V only) */
-  size_t partial;   /* scratch, two lives: double [BH, T_n, d], k_sum once more as the operand fragments of the router
-                       (written by the pooling step, dead after the router); then, bf16 path: the per-chunk partial sums of h
-                       and z and, behind them, -h_total as accumulator fragments; fp32 path: h_j, z_j of every key block and,
-                       without SLA2_FLAG_SAVE_FOR_BACKWARD, H_i, Z_i of every query block behind them */
+  size_t partial;   /* scratch.  double [BH, T_n, d], k_sum once more as the operand fragments of the router (written by the
+                       pooling step, dead after the router).  bf16 path, in their place afterwards: the per-chunk partial sums of h
+                       and z and, behind them, -h_total as accumulator fragments; fp32 path, behind them: h_j, z_j of every key block
+                       and, without SLA2_FLAG_SAVE_FOR_BACKWARD, H_i, Z_i of every query block */
   /* with SLA2_FLAG_SAVE_FOR_BACKWARD only (0 bytes otherwise): */
   size_t o_s;       /* dtype  [BH, N, d]     sparse-branch output O^s, before the mix of Eq. 13   (input of Alg. 3) */
   size_t o_l;       /* dtype  [BH, N, d]     linear-branch output O^l (fp32 tensors only; 0 bytes for bf16 tensors, whose
@@ -243,7 +243,8 @@ int sla2_dense_forward(const sla2_params* params, const void* q, const void* k, 
 typedef enum {
   SLA2_STAGE_BLOCK_SUMS = 0,  /* pooling sums of Q and K blocks; router weights folded   (Eq. 15-16) */
   SLA2_STAGE_TOPK = 1,        /* projection, scores, row-wise top-k; colmean(K)   (Eq. 16; Alg. 2, smoothing) */
-  SLA2_STAGE_KV_STATE = 2,    /* K^phi, partial h and z, low-bit codes of K (Alg. 2: K^phi, h, z) */
+  SLA2_STAGE_KV_STATE = 2,    /* K^phi, partial h and z, low-bit codes of K (Alg. 2: K^phi, h, z); small fp32
+                                 calls: the launch of SLA2_STAGE_TOPK, which forms them too */
   SLA2_STAGE_KV_TOTAL = 3,    /* per-head totals of h and z */
   SLA2_STAGE_ATTN = 4,        /* sparse + linear branch + mix              (Alg. 2 block loop, Eq. 13) */
   SLA2_STAGE_DENSE = 5,       /* dense attention comparator */

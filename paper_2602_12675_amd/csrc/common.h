@@ -176,12 +176,17 @@ hipError_t launch_block_sums(const Shape& s, const void* q, const void* k, const
                              double* k_sum, double* k_frag, double* router_m, hipStream_t stream);
 hipError_t launch_router_topk(const Shape& s, const double* q_sum, const double* k_frag, const double* router_m,
                               int32_t* block_idx, double* k_mean, hipStream_t stream);
+// fp32 tensors, where every workgroup finds a CU of its own (router_has_room): with it states [BH, T_n, d * d + d], h_j and z_j of every key block, and lnZ of every token; `states` may not
+// be where k_frag is
+bool router_has_room(const Shape& s);
+hipError_t launch_router_topk_f32(const Shape& s, const double* q_sum, const double* k_frag, const double* router_m,
+                                  int32_t* block_idx, double* k_mean, const float* k, const float* v, float* k_stats, float* states,
+                                  hipStream_t stream);
 hipError_t launch_router_soft(const Shape& s, const double* q_sum, const double* k_frag, const double* router_m,
                               float* mask, double tau, hipStream_t stream);
-// states [BH, T_n, d * d + d]: h_j, z_j of every key block; h_i [BH, T_m, d, d], z_i [BH, T_m, d]: their sums over the
-// key blocks that a query block did not select
 hipError_t launch_kv_state_f32(const Shape& s, const float* k, const float* v, const double* k_mean, float* k_stats,
                                float* states, hipStream_t stream);
+// h_i [BH, T_m, d, d], z_i [BH, T_m, d]: the sums of the states over the key blocks that a query block did not select
 hipError_t launch_block_states_f32(const Shape& s, const float* states, const int32_t* block_idx, float* h_total, float* z_total,
                                    float* h_i, float* z_i, hipStream_t stream);
 // the same on the key side of the backward pass: dH_j, dZ_j from dH_i, dZ_i of the query blocks that did not select j

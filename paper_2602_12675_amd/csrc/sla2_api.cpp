@@ -127,6 +127,7 @@ static BwdLayout make_bwd_layout(const Shape& s) {
 }
 static size_t bwd_scratch_bytes(const Shape& s) { return make_bwd_layout(s).total; }
 
+static size_t pooled_bytes(const Shape& s) { return align256((size_t)s.BH * s.Tn * s.d * sizeof(double)); }
 // fp32 tensors: entries of the key blocks' states (a whole number of 256-byte units)
 static size_t f32_states(const Shape& s) { return ((size_t)s.BH * s.Tn * (s.d * s.d + s.d) + 63) & ~(size_t)63; }
 
@@ -154,12 +155,11 @@ void make_layout(const Shape& s, sla2_ws_layout* L) {
   L->k_scale = take(s.quant ? BH * (size_t)s.Tn * sizeof(float) : 0);
   L->v_fp8 = take(s.quant == 3 ? BH * (size_t)s.Tn * s.bk * d : 0);
   L->v_scale = take(s.quant == 3 ? BH * (size_t)s.Tn * sizeof(float) : 0);
-  // two lives: the pooled keys as fragments, for the router; then bf16: the partial sums, -h_total as fragments behind them;
-  // fp32: the states of all key blocks and, unless `bwd` keeps them, H_i, Z_i of the query blocks
-  const size_t state = d * d + d, partials = (s.bf16 ? BH * ((size_t)s.chunks * state + d * d)
-                                                     : f32_states(s) + (s.save ? 0 : BH * s.Tm * state)) * sizeof(float);
-  const size_t pooled = BH * (size_t)s.Tn * d * sizeof(double);
-  L->partial = take(partials > pooled ? partials : pooled);
+  // bf16, two lives: the pooled keys as fragments, for the router; then the partial sums, -h_total as fragments behind them.
+  // fp32: the pooled keys, the states of all key blocks and, unless `bwd` keeps them, H_i, Z_i of the query blocks
+  const size_t state = d * d + d, pooled = pooled_bytes(s), partials = BH * ((size_t)s.chunks * state + d * d) * sizeof(float);
+  if (s.bf16) L->partial = take(partials > pooled ? partials : pooled);
+  else L->partial = take(pooled + (f32_states(s) + (s.save ? 0 : BH * s.Tm * state)) * sizeof(float));
   const size_t esz = s.bf16 ? 2 : 4;
   L->o_s = take(s.save ? BH * (size_t)s.N * d * esz : 0);
   L->o_l = take(s.save && !s.bf16 ? BH * (size_t)s.N * d * esz : 0);   // bf16 tensors: rebuilt from H_i in the backward pass
@@ -236,9 +236,15 @@ struct StageTimer {
 #define SLA2_STAGE(stage, call) ([&]() { StageTimer t_(stage, st); return (call); }())
 static void count_call() { if (g_prof.active.load(std::memory_order_acquire)) g_prof.calls++; }
 
-// pool -> colmean -> project -> scores + top-k.  Leaves the index lists in the workspace.
+// fp32 tensors: where the states lie
+static float* f32_states_at(const Shape& s, const sla2_ws_layout& L, void* ws) {
+  return (float*)((char*)ws + L.partial + pooled_bytes(s));
+}
+
+// pool -> colmean -> project -> scores + top-k.  Leaves the index lists in the workspace; with v, where there is room, also
+// the states of the key blocks, whose stage the same launch is.
 static int run_router(const Shape& s, const sla2_ws_layout& L, const void* q, const void* k, const float* router_w,
-                      void* ws, hipStream_t st) {
+                      void* ws, hipStream_t st, const void* v = nullptr) {
   double* q_sum = at<double>(ws, L.q_sum);
   double* k_sum = at<double>(ws, L.k_sum);
   double* k_frag = at<double>(ws, L.partial);
@@ -246,8 +252,17 @@ static int run_router(const Shape& s, const sla2_ws_layout& L, const void* q, co
   if (SLA2_STAGE(SLA2_STAGE_BLOCK_SUMS, launch_block_sums(s, q, k, router_w, q_sum, k_sum, k_frag, router_m, st)) !=
       hipSuccess)
     return SLA2_EHIP;
-  if (SLA2_STAGE(SLA2_STAGE_TOPK, launch_router_topk(s, q_sum, k_frag, router_m, at<int32_t>(ws, L.block_idx),
-                                                     at<double>(ws, L.k_mean), st)) != hipSuccess)
+  int32_t* idx = at<int32_t>(ws, L.block_idx);
+  double* k_mean = at<double>(ws, L.k_mean);
+  if (v && router_has_room(s)) {
+    auto launch = [&]() {
+      return launch_router_topk_f32(s, q_sum, k_frag, router_m, idx, k_mean, (const float*)k, (const float*)v,
+                                    at<float>(ws, L.k_stats), f32_states_at(s, L, ws), st);
+    };
+    if (SLA2_STAGE(SLA2_STAGE_KV_STATE, SLA2_STAGE(SLA2_STAGE_TOPK, launch())) != hipSuccess) return SLA2_EHIP;
+    return SLA2_OK;
+  }
+  if (SLA2_STAGE(SLA2_STAGE_TOPK, launch_router_topk(s, q_sum, k_frag, router_m, idx, k_mean, st)) != hipSuccess)
     return SLA2_EHIP;
   return SLA2_OK;
 }
@@ -339,7 +354,7 @@ int sla2_forward(const sla2_params* params, const void* q, const void* k, const 
   if ((rc = check_workspace(L, workspace, workspace_bytes)) != SLA2_OK) return rc;
   hipStream_t st = (hipStream_t)hip_stream;
   count_call();
-  if ((rc = run_router(s, L, q, k, router_w, workspace, st)) != SLA2_OK) return rc;
+  if ((rc = run_router(s, L, q, k, router_w, workspace, st, v)) != SLA2_OK) return rc;
   int32_t* idx = at<int32_t>(workspace, L.block_idx);
   if (block_idx_or_null && s.k > 0) {
     size_t bytes = (size_t)s.BH * s.Tm * s.k * sizeof(int32_t);
@@ -354,17 +369,18 @@ int sla2_forward(const sla2_params* params, const void* q, const void* k, const 
     sv.h_i = (void*)(at<char>(workspace, L.bwd) + B.h_i);
     sv.z_i = (float*)(at<char>(workspace, L.bwd) + B.z_i);
   }
-  float* k_stats = at<float>(workspace, L.k_stats);
   float* h_total = at<float>(workspace, L.h_total);
   float* z_total = at<float>(workspace, L.z_total);
   float* partial = at<float>(workspace, L.partial);
   if (!s.bf16) {
-    float* h_i = s.save ? (float*)sv.h_i : partial + f32_states(s);
+    float* states = f32_states_at(s, L, workspace);
+    float* h_i = s.save ? (float*)sv.h_i : states + f32_states(s);
     float* z_i = s.save ? sv.z_i : h_i + (size_t)s.BH * s.Tm * s.d * s.d;
-    if (SLA2_STAGE(SLA2_STAGE_KV_STATE, launch_kv_state_f32(s, (const float*)k, (const float*)v, k_mean, k_stats,
-                                                            partial, st)) != hipSuccess)
+    if (!router_has_room(s) &&
+        SLA2_STAGE(SLA2_STAGE_KV_STATE, launch_kv_state_f32(s, (const float*)k, (const float*)v, k_mean, at<float>(workspace, L.k_stats),
+                                                            states, st)) != hipSuccess)
       return SLA2_EHIP;
-    if (SLA2_STAGE(SLA2_STAGE_KV_TOTAL, launch_block_states_f32(s, partial, idx, h_total, z_total, h_i, z_i, st)) != hipSuccess)
+    if (SLA2_STAGE(SLA2_STAGE_KV_TOTAL, launch_block_states_f32(s, states, idx, h_total, z_total, h_i, z_i, st)) != hipSuccess)
       return SLA2_EHIP;
     if (SLA2_STAGE(SLA2_STAGE_ATTN,
                    launch_attn_f32(s, (const float*)q, (const float*)k, (const float*)v, k_mean, h_i, z_i, idx, alpha,
@@ -372,6 +388,7 @@ int sla2_forward(const sla2_params* params, const void* q, const void* k, const 
       return SLA2_EHIP;
     return SLA2_OK;
   }
+  float* k_stats = at<float>(workspace, L.k_stats);
   float* h_frag = partial + (size_t)s.BH * s.chunks * (s.d * s.d + s.d);
   uint16_t* k_phi = at<uint16_t>(workspace, L.k_phi);
   float* z_blocks = at<float>(workspace, L.z_blocks);

@@ -3,89 +3,29 @@
 // product of the selection's complement with all of them; one pass per query block then runs the sparse branch over the
 // selected key/value blocks, applies H_i, Z_i and mixes the two branches.  fp32 throughout: products on the fp32 matrix
 // instruction (f32_tiles.h).
-#include "f32_tiles.h"
+#include "kv_state_f32.h"
 
 namespace sla2 {
 
-// A block's state: h_j [d (c)][d (e)], then z_j [d].
-__host__ __device__ constexpr int f32_state(int d) { return d * d + d; }
-
 // ---------------------------------------------------------------------------------------------
-// kv_state_f32: one workgroup per key block
-//   k' = k - colmean(K);  stats[token] = lnZ = log sum_c exp(k'_c);
-//   K^phi = softmax_d(k');  h_j = (K^phi_j)^T V_j,  z_j = colsum(K^phi_j)
-// (Alg. 2: K^phi, h, z).  Tokens past N contribute nothing.  A token's channels sit on neighbouring lanes, 4 each, so
-// the softmax is taken in registers on the way into LDS; V goes from memory to its products.  h_j is as large as the block's
-// K and V together at d = 128: 12 heads of 4,096 tokens take 28 us for 100 MB (37 with V through LDS as well).
-// ---------------------------------------------------------------------------------------------
+// kv_state_f32: one workgroup per key block, where the block selection's launch has no room for them
 template <int D>
-__global__ __launch_bounds__(256, 4) void kv_state_f32_kernel(const float* __restrict__ k, const float* __restrict__ v,
-                                                              const double* __restrict__ k_mean, float* __restrict__ k_stats,
-                                                              float* __restrict__ states, Strides sin, int H, int N, int Tn) {
-  constexpr int LD = kF32Ld<D>;
-  typedef ChunkMap<D, 256, kF32Tokens> CM;
-  typedef StateSplit<D, 4> SS;
+__global__ __launch_bounds__(256, 4) void kv_state_f32_kernel(const KvStateArgs a, const double* __restrict__ k_mean, int H, int N, int Tn) {
   extern __shared__ __attribute__((aligned(16))) float smem[];
-  float* kp = smem;                       // [64][LD]  K^phi tile
-  const int bh = blockIdx.x / Tn, j = blockIdx.x % Tn;
-  const int tid = threadIdx.x, lane = tid % kWave, w = __builtin_amdgcn_readfirstlane(tid / kWave);
-  const int ch = tid % CM::kChunks, trow = tid / CM::kChunks;
-  const int t0 = j * kF32Tokens, valid = min(kF32Tokens, N - t0);
-  f32x4 kr[CM::kLoads], mu;
-  CM::load(kr, k + head_offset(sin, bh, H) + (size_t)t0 * sin.n, sin.n, valid, tid);
-  StateProduct<D> sp;
-  sp.begin(v + head_offset(sin, bh, H) + (size_t)t0 * sin.n, sin.n, valid, w, lane);
-#pragma unroll
-  for (int x = 0; x < 4; x++) mu[x] = (float)k_mean[(size_t)bh * D + 4 * ch + x];
-
-  f32x4 zacc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int i = 0; i < CM::kLoads; i++) {
-    const int t = trow + i * CM::kRows;
-    const bool ok = t < valid;
-    const f32x4 x = kr[i] - mu;
-    const float m = CM::row_max(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])));
-    f32x4 e;
-#pragma unroll
-    for (int c = 0; c < 4; c++) e[c] = exp2_f32((x[c] - m) * kLog2e);
-    const float sum = CM::row_sum((e[0] + e[1]) + (e[2] + e[3]));
-    const float inv = ok ? 1.f / sum : 0.f;
-    e *= inv;
-    zacc += e;
-    *reinterpret_cast<f32x4*>(kp + t * LD + 4 * ch) = e;
-    if (ok && ch == 0) k_stats[(size_t)bh * N + t0 + t] = m + __log2f(sum) * kLn2;
-  }
-  __syncthreads();
-  f32x16 hacc[SS::kTiles];
-#pragma unroll
-  for (int x = 0; x < SS::kTiles; x++) hacc[x] = zero16();
-  sp.add(hacc, kp, w, lane);
-  float* ph = states + (size_t)blockIdx.x * f32_state(D);
-  StateProduct<D>::store(hacc, 1.f, ph, w, lane);
-  __syncthreads();                        // the tile fully consumed: its place takes the column sums
-  *reinterpret_cast<f32x4*>(kp + trow * D + 4 * ch) = zacc;
-  __syncthreads();
-  if (tid < D) {
-    float z = 0.f;
-#pragma unroll
-    for (int r = 0; r < CM::kRows; r++) z += kp[r * D + tid];
-    ph[D * D + tid] = z;
-  }
+  kv_state_f32_job<D, false>(a, k_mean, smem, blockIdx.x, threadIdx.x, H, N, Tn, 1);
 }
-
 template <int D>
-static hipError_t launch_kv_state_f32_t(const Shape& s, const float* k, const float* v, const double* k_mean, float* k_stats,
-                                        float* states, hipStream_t stream) {
-  constexpr int smem = kF32Tokens * kF32Ld<D> * (int)sizeof(float);
+static hipError_t launch_kv_state_f32_t(const Shape& s, const KvStateArgs& a, const double* k_mean, hipStream_t stream) {
+  constexpr int smem = kKvStateFloats<D> * (int)sizeof(float);
   static OncePerDevice once;
   if (hipError_t e = allow_dynamic_lds(once, (const void*)kv_state_f32_kernel<D>, smem); e != hipSuccess) return e;
-  kv_state_f32_kernel<D><<<dim3((unsigned)(s.BH * s.Tn)), 256, smem, stream>>>(k, v, k_mean, k_stats, states, s.sin, s.H, s.N, s.Tn);
+  kv_state_f32_kernel<D><<<dim3((unsigned)(s.BH * s.Tn)), 256, smem, stream>>>(a, k_mean, s.H, s.N, s.Tn);
   return hipGetLastError();
 }
 hipError_t launch_kv_state_f32(const Shape& s, const float* k, const float* v, const double* k_mean, float* k_stats,
                                float* states, hipStream_t stream) {
-  return s.d == 128 ? launch_kv_state_f32_t<128>(s, k, v, k_mean, k_stats, states, stream)
-                    : launch_kv_state_f32_t<64>(s, k, v, k_mean, k_stats, states, stream);
+  const KvStateArgs a{k, v, k_stats, states, s.sin};
+  return s.d == 128 ? launch_kv_state_f32_t<128>(s, a, k_mean, stream) : launch_kv_state_f32_t<64>(s, a, k_mean, stream);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -125,6 +65,12 @@ __global__ __launch_bounds__(256, 2) void masked_states_f32_kernel(const float* 
   if (set >= BH * kSets) return;
   const int bh = set / kSets, row0 = 32 * tile;
   const int tid = threadIdx.x, lane = tid % kWave, g = lane / 32, w = tid / kWave;
+  const int col = (set % kSets * 4 + w) * kStateCols + 4 * (lane % 32);
+  const float* src = states + (size_t)bh * S * P + min(col, P - 4);
+  f32x4 b[16];                            // blocks 32 sw + 2 n + g; past the end the last one, with weight 0
+  auto request = [&](int sw, int n) { b[n] = *reinterpret_cast<const f32x4*>(src + (size_t)min(32 * sw + 2 * n + g, S - 1) * P); };
+#pragma unroll
+  for (int n = 0; n < 16; n++) request(0, n);
   if constexpr (!TOTALS_ONLY) {
     for (int x = tid; x < 32 * W; x += 256) bits[x] = 0u;
     __syncthreads();
@@ -139,25 +85,29 @@ __global__ __launch_bounds__(256, 2) void masked_states_f32_kernel(const float* 
     }
     __syncthreads();
   }
-  const int col = (set % kSets * 4 + w) * kStateCols + 4 * (lane % 32);
-  const float* src = states + (size_t)bh * S * P + min(col, P - 4);
   f32x16 acc[4];
 #pragma unroll
   for (int x = 0; x < 4; x++) acc[x] = zero16();
   f32x4 sum = {0.f, 0.f, 0.f, 0.f};
   for (int sw = 0; sw < W; sw++) {
     const uint32_t word = TOTALS_ONLY ? 0u : bits[32 * sw + lane % 32];
-    f32x4 b[16];                          // blocks 32 sw + 2 n + g; past the end the last one, with weight 0
+    if (sw > 0) {
 #pragma unroll
-    for (int n = 0; n < 16; n++) b[n] = *reinterpret_cast<const f32x4*>(src + (size_t)min(32 * sw + 2 * n + g, S - 1) * P);
+      for (int n = 0; n < 16; n++) request(sw, n);
+    }
 #pragma unroll
-    for (int n = 0; n < 16; n++) {
-      const bool exists = 32 * sw + 2 * n + g < S;
-      if (tile == 0) sum += exists ? b[n] : f32x4{0.f, 0.f, 0.f, 0.f};
-      if constexpr (!TOTALS_ONLY) {
-        const float a = exists && (word >> (2 * n + g) & 1u) == 0u ? 1.f : 0.f;
+    for (int half = 0; half < 2; half++) {
+      if (32 * sw + 16 * half < S) {
 #pragma unroll
-        for (int x = 0; x < 4; x++) acc[x] = mfma_f32(a, b[n][x], acc[x]);
+        for (int n = 8 * half; n < 8 * half + 8; n++) {
+          const bool exists = 32 * sw + 2 * n + g < S;
+          if (tile == 0) sum += exists ? b[n] : f32x4{0.f, 0.f, 0.f, 0.f};
+          if constexpr (!TOTALS_ONLY) {
+            const float a = exists && (word >> (2 * n + g) & 1u) == 0u ? 1.f : 0.f;
+#pragma unroll
+            for (int x = 0; x < 4; x++) acc[x] = mfma_f32(a, b[n][x], acc[x]);
+          }
+        }
       }
     }
   }

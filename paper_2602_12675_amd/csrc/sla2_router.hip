@@ -11,6 +11,7 @@
 // Measured on 12 heads of 256 x 512 blocks 28.7 -> 26 us, on 40 heads of 591 x 1182 361 -> 315 us, with the pooled keys
 // read as operand fragments and the search on 32-bit images.  A workgroup of the latter spends 57k cycles on scores
 // (41k of them the fp64 products alone), 13k on the selection and 11k on the projection of its rows.
+#include "kv_state_f32.h"
 #include "router_scores.h"
 
 namespace sla2 {
@@ -23,15 +24,24 @@ __device__ __forceinline__ uint64_t order_key(double x) {
 
 __device__ __forceinline__ int wave_count(bool pred) { return __builtin_popcountll(__ballot(pred)); }
 
-template <int D, int SLOTS>
+// KV: the states of the key blocks too, one by each workgroup from topk_blocks + mean_blocks on (kv_state_f32.h)
+template <int D, int SLOTS, bool KV>
 __global__ __launch_bounds__(1024) void router_topk_kernel(const double* __restrict__ q_sum,
                                                            const double* __restrict__ k_frag,
                                                            const double* __restrict__ router_m,
                                                            int32_t* __restrict__ block_idx,
                                                            double* __restrict__ k_mean, int H, int N, int bq, int bk,
                                                            int Tm, int Tn, int k, int w_per_head, int topk_blocks,
-                                                           int smooth) {
+                                                           int mean_blocks, int smooth, const KvStateArgs kv) {
   extern __shared__ __attribute__((aligned(16))) double lds[];
+  if constexpr (KV) {
+    if ((int)blockIdx.x >= topk_blocks + mean_blocks) {
+      if (threadIdx.x >= 256) return;                    // (a barrier counts the waves that are left)
+      kv_state_f32_job<D, true>(kv, k_frag, reinterpret_cast<float*>(lds), (int)blockIdx.x - topk_blocks - mean_blocks, threadIdx.x, H, N, Tn,
+                                smooth);
+      return;
+    }
+  }
   if ((int)blockIdx.x >= topk_blocks) {
     // Spare workgroups of this launch form colmean(K) (K-smoothing step of Alg. 2) from the block sums
     // for the kernels that follow; the router itself does not need it.  16 channels per workgroup,
@@ -187,11 +197,23 @@ __global__ __launch_bounds__(1024) void router_topk_kernel(const double* __restr
   }
 }
 
-hipError_t launch_router_topk(const Shape& s, const double* q_sum, const double* k_frag, const double* router_m,
-                              int32_t* block_idx, double* k_mean, hipStream_t stream) {
+template <int D, int SLOTS, bool KV>
+static hipError_t launch_topk(const Shape& s, const double* q_sum, const double* k_frag, const double* router_m, int32_t* block_idx,
+                              double* k_mean, const KvStateArgs& kv, hipStream_t stream) {
+  constexpr size_t job = KV ? kKvStateFloats<D> * sizeof(float) : 0, lds = job > router_lds_bytes<D>() ? job : router_lds_bytes<D>();
+  static OncePerDevice once;
+  if (hipError_t e = allow_dynamic_lds(once, (const void*)router_topk_kernel<D, SLOTS, KV>, (int)lds); e != hipSuccess) return e;
   const int row_tiles = (s.Tm + kRouterRows - 1) / kRouterRows;
   const int topk_blocks = s.k > 0 ? s.BH * row_tiles : 0;        // k = 0: only the colmean workgroups run
-  dim3 grid((unsigned)(topk_blocks + s.BH * (s.d / 16)));
+  const int mean_blocks = s.BH * (D / 16), kv_blocks = KV ? s.BH * s.Tn : 0;
+  router_topk_kernel<D, SLOTS, KV><<<dim3((unsigned)(topk_blocks + mean_blocks + kv_blocks)), 1024, lds, stream>>>(
+      q_sum, k_frag, router_m, block_idx, k_mean, s.H, s.N, s.bq, s.bk, s.Tm, s.Tn, s.k, s.w_per_head ? 1 : 0, topk_blocks, mean_blocks,
+      s.smooth ? 1 : 0, kv);
+  return hipGetLastError();
+}
+template <bool KV>
+static hipError_t launch_topk_class(const Shape& s, const double* q_sum, const double* k_frag, const double* router_m, int32_t* block_idx,
+                                    double* k_mean, const KvStateArgs& kv, hipStream_t stream) {
   // Three register classes by rounds of 256 key blocks: up to 2 (8 slots a lane), up to 5 (20), up to 8 (32; kMaxKeyBlocks).
   // Up to 8 slots the operands are read 8 at a time, else 4 (router_scores.h): the slots take the registers.  The middle
   // class ends at 5 rounds for the 1,025 to 1,280 key blocks that 20 slots serve better than 32: 12 heads, d = 128, 128-row
@@ -199,23 +221,28 @@ hipError_t launch_router_topk(const Shape& s, const double* q_sum, const double*
   // key blocks, which 16 slots with reads 8 at a time serve in 3 to 6 % less (d = 128: 640 key blocks 34.2 against 35.4 us,
   // 1,024 75.0 against 78.0; 40 heads 198 against 207) to 10 % less (d = 64: 57.4 against 63.7, 96.2 against 105.5).
   const int rounds = (s.Tn + kColsPerRound - 1) / kColsPerRound;
-#define SLA2_TOPK(DD, SS)                                                                                        \
-  {                                                                                                              \
-    static OncePerDevice once;                                                                                   \
-    if (hipError_t e = allow_dynamic_lds(once, (const void*)router_topk_kernel<DD, SS>, (int)router_lds_bytes<DD>()); \
-        e != hipSuccess)                                                                                         \
-      return e;                                                                                                  \
-    router_topk_kernel<DD, SS><<<grid, 1024, router_lds_bytes<DD>(), stream>>>(                                  \
-        q_sum, k_frag, router_m, block_idx, k_mean, s.H, s.N, s.bq, s.bk, s.Tm, s.Tn, s.k, s.w_per_head ? 1 : 0,   \
-        topk_blocks, s.smooth ? 1 : 0);                                                                          \
-  }
+#define SLA2_TOPK(DD, SS) return launch_topk<DD, SS, KV>(s, q_sum, k_frag, router_m, block_idx, k_mean, kv, stream)
   if (s.d == 128) {
-    if (rounds <= 2) SLA2_TOPK(128, 8) else if (rounds <= 5) SLA2_TOPK(128, 20) else SLA2_TOPK(128, 32)
-  } else {
-    if (rounds <= 2) SLA2_TOPK(64, 8) else if (rounds <= 5) SLA2_TOPK(64, 20) else SLA2_TOPK(64, 32)
+    if (rounds <= 2) SLA2_TOPK(128, 8);
+    if (rounds <= 5) SLA2_TOPK(128, 20);
+    SLA2_TOPK(128, 32);
   }
+  if (rounds <= 2) SLA2_TOPK(64, 8);
+  if (rounds <= 5) SLA2_TOPK(64, 20);
+  SLA2_TOPK(64, 32);
 #undef SLA2_TOPK
-  return hipGetLastError();
+}
+hipError_t launch_router_topk(const Shape& s, const double* q_sum, const double* k_frag, const double* router_m,
+                              int32_t* block_idx, double* k_mean, hipStream_t stream) {
+  return launch_topk_class<false>(s, q_sum, k_frag, router_m, block_idx, k_mean, KvStateArgs{}, stream);
+}
+bool router_has_room(const Shape& s) {
+  return !s.bf16 && (size_t)s.BH * ((s.Tm + kRouterRows - 1) / kRouterRows + s.d / 16 + s.Tn) <= 256;
+}
+hipError_t launch_router_topk_f32(const Shape& s, const double* q_sum, const double* k_frag, const double* router_m,
+                                  int32_t* block_idx, double* k_mean, const float* k, const float* v, float* k_stats, float* states,
+                                  hipStream_t stream) {
+  return launch_topk_class<true>(s, q_sum, k_frag, router_m, block_idx, k_mean, KvStateArgs{k, v, k_stats, states, s.sin}, stream);
 }
 
 }  // namespace sla2

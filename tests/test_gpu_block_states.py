@@ -1,5 +1,6 @@
 """fp32 tensors: H_i, Z_i from the states of all key blocks, as a product of the selection's complement (short heads, long
-lists) or the totals less a gather, on both sides of the lines between the two and one block more or less than whole tiles."""
+lists) or the totals less a gather, on both sides of the lines between the two and one block more or less than whole tiles; and
+the states formed in the selection's launch or in one of their own, on both sides of that line."""
 import pytest
 
 from paper_2602_12675_amd import workloads as W
@@ -17,6 +18,8 @@ CASES = [
     BASE.replace(name="d64-91-of-3", grid=(15, 16, 24), extra_tokens=33, topk_frac=0.0334, H=2),
     BASE.replace(name="d128-65-of-1", grid=(16, 16, 16), extra_tokens=31, topk_frac=0.016, d=128, block_q=128),
     BASE.replace(name="d128-31-of-4", grid=(8, 15, 16), extra_tokens=32, topk_frac=0.13, d=128),         # T_m = 31
+    BASE.replace(name="d64-237-of-12-one-launch", grid=(16, 12, 79), topk_frac=0.05),                    # 15 + 4 + 237 workgroups
+    BASE.replace(name="d64-238-of-12", grid=(16, 12, 79), extra_tokens=1, topk_frac=0.05),
     BASE.replace(name="d128-33-of-5", grid=(8, 16, 16), extra_tokens=33, topk_frac=0.15, d=128, H=3),    # T_m = 33
 ]
 
@@ -26,6 +29,6 @@ def test_forward(w):
     check_forward(w)
 
 
-@pytest.mark.parametrize("w", [CASES[2], CASES[5], CASES[7]], ids=lambda w: w.name)
+@pytest.mark.parametrize("w", [CASES[2], CASES[5], CASES[9]], ids=lambda w: w.name)
 def test_backward(w):
     check_backward(w, True, True)
