@@ -13,7 +13,15 @@
 // A workgroup has 16 waves.  Scores are formed (v_mfma_f64_16x16x4) 256 key blocks at a time: wave w multiplies the
 // projected 16 x d tile with key blocks [256 r + 16 w, +16), parks its 16 x 16 result in LDS, and wave i then picks up
 // row i, so that after the last round every wave holds one complete score row in registers (4 values per lane and
-// round).  Scores never touch HBM.
+// round).  Scores never touch HBM.  Two LDS tiles take the rounds in turn: one barrier a round, and a wave that has its row
+// starts on the next products while others still collect (a workgroup has its CU to itself by its registers, so the second
+// tile costs no place).
+//
+// What bounds it: the chain of a workgroup, half of it the fp64 products themselves (64 cycles each), the rest the phases
+// between barriers.  The second tile, the divisions left to ragged blocks (they ran for every score before) and the order
+// of the workgroups below: soft router on 12 heads of 256 x 512 blocks 73.4 -> 71.1 us with its pooling, selection on 40
+// heads of 591 x 1,182 315 -> 309 us, on 4 heads of 16 x 16 (d = 64) the whole forward call 25.2 -> 24.9 us; at 12 heads of 256 x 512
+// the hard selection, one workgroup on three quarters of the CUs, is where it was.
 #pragma once
 #include "common.h"
 
@@ -24,7 +32,14 @@ constexpr int kColsPerRound = 256;                    // key blocks scored per r
 typedef __attribute__((ext_vector_type(2))) double f64x2;
 
 template <int D> constexpr size_t router_lds_bytes() {
-  return sizeof(double) * (kRouterRows * (D + 2) + kRouterRows * (kColsPerRound + 8));
+  return sizeof(double) * (kRouterRows * (D + 2) + 2 * kRouterRows * (kColsPerRound + 8));
+}
+
+// The (head, row tile) of a selection workgroup: all of them, head by head, in kXcds runs, one per XCD, so that the workgroups
+// that an XCD runs at a time read the pooled keys of a head or two (1.2 MB a head of 1,182 key blocks) from its L2.
+__device__ __forceinline__ int router_tile(int block, int blocks) {
+  const int x = block % kXcds;
+  return x * (blocks / kXcds) + min(x, blocks % kXcds) + block / kXcds;
 }
 
 // C[16][D] = A[16][D] M on the matrix cores, M fp64 [D][D] row-major in global memory.  All 16 waves
@@ -63,12 +78,13 @@ template <int D, int SLOTS>
 __device__ __forceinline__ void router_scores(double (&score)[SLOTS], const double* __restrict__ q_sum,
                                               const double* __restrict__ k_frag, const double* __restrict__ M, double* lds,
                                               int bh, int row0, int N, int bq, int bk, int Tm, int Tn) {
-  // LDS: xa [16][D+2] pooled queries, later Qbar M | tile [16][264] one round of scores (the partial projections
+  // LDS: xa [16][D+2] pooled queries, later Qbar M | tile [2][16][264] the scores of a round (the partial projections
   // before the first round)
   double (*xa)[D + 2] = reinterpret_cast<double (*)[D + 2]>(lds);
-  double (*tile)[kColsPerRound + 8] = reinterpret_cast<double (*)[kColsPerRound + 8]>(lds + kRouterRows * (D + 2));
+  typedef double Tile[kRouterRows][kColsPerRound + 8];
+  Tile* tiles = reinterpret_cast<Tile*>(lds + kRouterRows * (D + 2));
   static_assert(ProjGeom<D>::kShares * (D + 2) <= kColsPerRound + 8, "projection shares must fit the score tile");
-  double (*xb)[D + 2] = reinterpret_cast<double (*)[D + 2]>(&tile[0][0]);   // partial Qbar M; dead before the first round
+  double (*xb)[D + 2] = reinterpret_cast<double (*)[D + 2]>(&tiles[0][0][0]);   // partial Qbar M; dead before the first round
   const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
   const int rounds = (Tn + kColsPerRound - 1) / kColsPerRound;
 
@@ -96,10 +112,16 @@ __device__ __forceinline__ void router_scores(double (&score)[SLOTS], const doub
   }
   project16_fetch<D>(mb, M, wave, lane);
   fetch(0, 0);
+  // Mean pooling (Eq. 15).  Blocks are powers of two: for full ones the product with 1 / b_q is the exact quotient; only the
+  // tile that holds a ragged last block divides.
+  const double inv_bq = 1.0 / bq;
+  const bool ragged_q = row0 + kRouterRows >= Tm && Tm * bq != N;
 #pragma unroll
   for (int x = 0; x < kQLoads; x++) {
     const int r = (threadIdx.x + 1024 * x) / D, c = threadIdx.x % D;
-    xa[r][c] = qv[x] / (double)min(bq, N - min(row0 + r, Tm - 1) * bq);   // mean pooling (Eq. 15)
+    if (ragged_q) qv[x] /= (double)min(bq, N - min(row0 + r, Tm - 1) * bq);
+    else qv[x] *= inv_bq;
+    xa[r][c] = qv[x];
   }
   __syncthreads();
   project16<D>(xa, xb, mb, wave, lane);                                   // Qbar (Wq Wk^T / sqrt(d)), in shares
@@ -115,7 +137,8 @@ __device__ __forceinline__ void router_scores(double (&score)[SLOTS], const doub
 
 #pragma unroll
   for (int s = 0; s < SLOTS; s++) score[s] = -INFINITY;
-  const double last_cnt = (double)(N - (Tn - 1) * bk), inv_bk = 1.0 / bk;   // bk = 64: the product is the exact quotient
+  const double inv_bk = 1.0 / bk;                      // bk = 64: the product is the exact quotient
+  const bool ragged_k = Tn * bk != N;
 #pragma unroll
   for (int r = 0; r < SLOTS / 4; r++) {
     if (r < rounds) {
@@ -133,6 +156,7 @@ __device__ __forceinline__ void router_scores(double (&score)[SLOTS], const doub
         }
       }
       if (r + 1 < rounds) fetch(r + 1, 0);
+      Tile& tile = tiles[r & 1];
       // result layout: lane l, register v holds C[l/16 + 4 v][l%16]
 #pragma unroll
       for (int v = 0; v < 4; v++) tile[lane / 16 + 4 * v][wave * 16 + lane % 16] = acc[v];
@@ -141,11 +165,12 @@ __device__ __forceinline__ void router_scores(double (&score)[SLOTS], const doub
 #pragma unroll
       for (int x = 0; x < 4; x++) {
         const int col = r * kColsPerRound + x * kWave + lane;
-        double sc = tile[wave][x * kWave + lane] * inv_bk;
-        if (col == Tn - 1) sc = tile[wave][x * kWave + lane] / last_cnt;
+        const double sum = tile[wave][x * kWave + lane];
+        double sc = sum * inv_bk;
+        if (ragged_k && col / kWave == (Tn - 1) / kWave)                  // one slot of the row: the others spend no division
+          if (col == Tn - 1) sc = sum / (double)(N - (Tn - 1) * bk);
         score[4 * r + x] = col < Tn ? sc : -INFINITY;
       }
-      __syncthreads();
     }
   }
 }

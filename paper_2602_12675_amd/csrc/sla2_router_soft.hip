@@ -9,9 +9,9 @@
 // bracket is replaced by its midpoint), 5 to 7 evaluations of the row where a bisection to the last bit takes 55.  An
 // evaluation costs a reciprocal per entry instead of an exponential and a division:
 //      sigmoid(x + lambda) = 1 / (1 + exp(xmax - x) exp(-(lambda + xmax))),
-// with exp(xmax - x) formed once per entry.  Measured on 12 heads of 256 x 512 blocks: 37 us, against 252 us
+// with exp(xmax - x) formed once per entry.  Measured on 12 heads of 256 x 512 blocks: 33 us, against 252 us
 // for one workgroup per row that read all pooled keys itself and bisected through LDS reductions; what is left is the
-// scoring (28 us, bound by the chain of fp64 products of a workgroup) and 9 us of exponentials and root search.
+// scoring (24 us, bound by the chain of fp64 products of a workgroup) and 9 us of exponentials and root search.
 #include "router_scores.h"
 
 namespace sla2 {
@@ -49,7 +49,7 @@ __global__ __launch_bounds__(1024) void router_soft_kernel(const double* __restr
                                                            int Tm, int Tn, int k, double tau, int w_per_head) {
   extern __shared__ __attribute__((aligned(16))) double lds[];
   const int row_tiles = (Tm + kRouterRows - 1) / kRouterRows;
-  const int bh = blockIdx.x / row_tiles, row0 = (blockIdx.x % row_tiles) * kRouterRows;
+  const int job = router_tile(blockIdx.x, gridDim.x), bh = job / row_tiles, row0 = job % row_tiles * kRouterRows;
   const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
   const int row = row0 + wave;
   float* out = mask + ((size_t)bh * Tm + row) * Tn;
