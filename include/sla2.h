@@ -248,7 +248,8 @@ typedef enum {
   SLA2_STAGE_KV_TOTAL = 3,    /* per-head totals of h and z */
   SLA2_STAGE_ATTN = 4,        /* sparse + linear branch + mix              (Alg. 2 block loop, Eq. 13) */
   SLA2_STAGE_DENSE = 5,       /* dense attention comparator */
-  SLA2_STAGE_BWD_LISTS = 6,   /* sla2_backward: the block mask as bits, per key block the list of its query blocks */
+  SLA2_STAGE_BWD_LISTS = 6,   /* sla2_backward: the block mask as bits, per key block the list of its query blocks:
+                                 the launch of SLA2_STAGE_BWD_Q, which makes them too */
   SLA2_STAGE_BWD_Q = 7,       /* query-side kernel: D^s, D^l, dQ, dH_i, dZ_i, d alpha parts          (Alg. 3) */
   SLA2_STAGE_BWD_KV = 8,      /* key-side kernel: dK', dV                                             (Alg. 3) */
   SLA2_STAGE_BWD_REST = 9,    /* totals of dH_i, dZ_i; dK = dK' - colmean(dK'); d alpha               */

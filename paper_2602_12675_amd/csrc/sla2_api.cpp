@@ -460,8 +460,7 @@ int sla2_backward(const sla2_params* params, const void* q, const void* k, const
   a.col_cnt = (int32_t*)(bw + B.col_cnt); a.order = (int32_t*)(bw + B.order);
   hipStream_t st = (hipStream_t)hip_stream;
   count_call();
-  if (SLA2_STAGE(SLA2_STAGE_BWD_LISTS, launch_bwd_lists(s, a, st)) != hipSuccess) return SLA2_EHIP;
-  if (SLA2_STAGE(SLA2_STAGE_BWD_Q, launch_bwd_q(s, a, st)) != hipSuccess) return SLA2_EHIP;
+  if (SLA2_STAGE(SLA2_STAGE_BWD_LISTS, SLA2_STAGE(SLA2_STAGE_BWD_Q, launch_bwd_q(s, a, st))) != hipSuccess) return SLA2_EHIP;
   if (SLA2_STAGE(SLA2_STAGE_BWD_REST, launch_bwd_totals(s, a, st)) != hipSuccess) return SLA2_EHIP;
   if (SLA2_STAGE(SLA2_STAGE_BWD_KV, launch_bwd_kv(s, a, st)) != hipSuccess) return SLA2_EHIP;
   if (SLA2_STAGE(SLA2_STAGE_BWD_REST, launch_bwd_finish(s, a, st)) != hipSuccess) return SLA2_EHIP;

@@ -5,8 +5,8 @@
 // This file holds the launch sequence and the small kernels every tensor type shares (deterministic: no float atomics,
 // fixed summation orders; only the order of work on key blocks of equally long lists is open); the two heavy steps are in sla2_bwd_mfma.hip (bf16 tensors) and sla2_bwd_f32.hip.
 //
-//   bwd_columns    for every key block j the ascending list of query blocks i with M_c[i, j] = 1
-//   (bwd_q)        per query block: D^s, D^l, d alpha parts, dQ, dH_i, dZ_i
+//   (bwd_q)        per query block: D^s, D^l, d alpha parts, dQ, dH_i, dZ_i; its first workgroups make, for every key block j,
+//                  the ascending list of query blocks i with M_c[i, j] = 1 (bwd_columns.h)
 //   bwd_totals     per key block the sum of dH_i over the query blocks that did not select it, dZ_total = sum_i dZ_i; the order
 //                  in which bwd_kv takes the key blocks (fp32 tensors: kernels of their own in sla2_bwd_f32.hip)
 //   (bwd_kv)       per key block: dK', dV, column sums of dK'
@@ -21,79 +21,6 @@
 namespace sla2 {
 
 // ---------------------------------------------------------------------------------------------
-// For every key block j of head bh: the ascending list of query blocks i with M_c[i, j] = 1, as offsets
-// col_ptr[bh][0..T_n] into col_idx[bh][.], and its length.  One workgroup per 64 columns of a head reads all index lists
-// of the head: entries of its own columns become bits (column x, bit i), those of earlier columns are counted - the
-// offset of its first list.  Then every thread writes out the bits of a few 32-row words at their places, and the complement
-// of the words (bits from T_m on: 0) as rows of the bit matrix, if there is one.
-__global__ __launch_bounds__(256) void bwd_columns_kernel(const int32_t* __restrict__ block_idx, int32_t* __restrict__ col_ptr,
-                                                          int32_t* __restrict__ col_idx, int32_t* __restrict__ counts,
-                                                          uint32_t* __restrict__ bits, int Tm, int Tn, int ksel) {
-  extern __shared__ uint32_t words[];                 // [64][LW] bits, LW = W | 1 (odd: no bank conflicts down a column)
-  const int W = (Tm + 31) / 32, LW = W | 1;           // W <= 64
-  uint16_t* place = reinterpret_cast<uint16_t*>(words + 64 * LW);   // [64][LW] set bits of the column before the word
-  __shared__ int before[4], first[64];
-  const int j0 = blockIdx.x * 64, bh = blockIdx.y, tid = threadIdx.x, cols = min(64, Tn - j0);
-  const int lane = tid % kWave, wave = tid / kWave;
-  for (int x = tid; x < 64 * LW; x += 256) words[x] = 0u;
-  __syncthreads();
-  const int32_t* idx = block_idx + (size_t)bh * Tm * ksel;
-  const unsigned entries = (unsigned)Tm * (unsigned)ksel;
-  int earlier = 0;
-#pragma unroll 8
-  for (unsigned e = tid; e < entries; e += 256) {
-    const int j = idx[e] - j0;
-    earlier += j < 0;
-    if (j >= 0 && j < 64) {
-      const unsigned i = e / (unsigned)ksel;
-      atomicOr(&words[j * LW + (i >> 5)], 1u << (i & 31));   // OR: the result does not depend on the order
-    }
-  }
-#pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) earlier += __shfl_xor(earlier, o);
-  if (lane == 0) before[wave] = earlier;
-  __syncthreads();
-  if (wave == 0) {                                    // one lane per column: places of its words, list length and offset
-    int n = 0;
-    for (int x = 0; x < W; x++) {
-      place[lane * LW + x] = (uint16_t)n;
-      n += __popc(words[lane * LW + x]);
-    }
-    int at = n;
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-      const int y = __shfl_up(at, o);
-      if (lane >= o) at += y;
-    }
-    at += before[0] + before[1] + before[2] + before[3];
-    first[lane] = at - n;
-    if (lane < cols) {
-      counts[(size_t)bh * Tn + j0 + lane] = n;
-      col_ptr[(size_t)bh * (Tn + 1) + j0 + lane + 1] = at;
-    }
-    if (j0 == 0 && lane == 0) col_ptr[(size_t)bh * (Tn + 1)] = 0;
-  }
-  __syncthreads();
-  int32_t* out = col_idx + (size_t)bh * Tm * ksel;
-  for (int x = tid; x < 64 * W; x += 256) {
-    const int c = x % 64, y = x / 64;
-    uint32_t word = words[c * LW + y];
-    int at = first[c] + place[c * LW + y];
-    while (word) {
-      out[at++] = 32 * y + __ffs(word) - 1;
-      word &= word - 1u;
-    }
-  }
-  if (bits != nullptr) {
-    const int pitch = masked_pitch(Tn), rows = masked_words(Tm);
-    for (int x = tid; x < 64 * rows; x += 256) {
-      const int c = x % 64, y = x / 64, left = Tm - 32 * y;
-      const uint32_t open = left >= 32 ? ~0u : left > 0 ? (1u << left) - 1u : 0u;
-      bits[((size_t)bh * rows + y) * pitch + j0 + c] = y < W ? ~words[c * LW + y] & open : 0u;
-    }
-  }
-}
-
 // dst[e] = sum over b < count of src[b][e] for the 256 entries from e0 on.  32 threads of 8 elements each, times 8
 // interleaved subsets of b that are combined in a fixed order.
 __device__ void sum_slots(const float* __restrict__ src, float* __restrict__ dst, int count, int len, int first, float (*part)[256]) {
@@ -221,15 +148,6 @@ __global__ __launch_bounds__(256) void bwd_unsmooth_kernel(T* __restrict__ dk, c
 }
 
 // ---------------------------------------------------------------------------------------------
-hipError_t launch_bwd_lists(const Shape& s, const BwdArgs& a, hipStream_t stream) {
-  // k = 0: every column is empty
-  const size_t smem = (size_t)64 * (((s.Tm + 31) / 32) | 1) * (sizeof(uint32_t) + sizeof(uint16_t));   // at most 25 KB (T_m <= 2048)
-  bwd_columns_kernel<<<dim3((unsigned)((s.Tn + 63) / 64), (unsigned)s.BH), 256, smem, stream>>>(a.block_idx, a.col_ptr, a.col_idx,
-                                                                                               a.col_cnt, s.bf16 ? a.col_bits : nullptr, s.Tm, s.Tn,
-                                                                                               s.k);
-  return hipGetLastError();
-}
-
 hipError_t launch_bwd_q(const Shape& s, const BwdArgs& a, hipStream_t stream) {
   return s.bf16 ? launch_bwd_q_bf16(s, a, stream) : launch_bwd_q_f32(s, a, stream);
 }

@@ -20,6 +20,7 @@
 // and bwd_state 36, bwd_kv 290 -> 222 us and the sums of states 21 (the gathers of dH_i and lists of unequal length took their
 // time at the end of few workgroups).  A longer list costs bwd_q 18.3 us a block and bwd_kv 22.0, where the products alone take
 // 16.0 and 21.4; without a list they take 51 and 71 us, which is HBM and the meeting of the parts.
+#include "bwd_columns.h"
 #include "f32_tiles.h"
 #include "work_order.h"
 
@@ -39,6 +40,7 @@ template <int D> struct BwdQF32Smem {
   static constexpr int kDotOff = kRowOff + 96;                             // [4][32] parts of row sums
   static constexpr int kBytes = (kDotOff + 128) * (int)sizeof(float);
   static_assert(kBytes <= 80 * 1024, "two workgroups a CU");
+  static_assert(kBwdColumnsLds <= kBytes, "the lists are made by workgroups of the same launch");
 };
 
 template <int D>
@@ -48,11 +50,14 @@ __global__ __launch_bounds__(256, 2) void bwd_q_f32_kernel(
     const double* __restrict__ k_mean, const float* __restrict__ h_i, const float* __restrict__ z_i,
     const int32_t* __restrict__ block_idx, const float* __restrict__ alpha, float* __restrict__ dq, float* __restrict__ ds_out,
     float* __restrict__ l2_out, float* __restrict__ inv_den_out, float* __restrict__ dl_out, float* __restrict__ dalpha_part,
-    Strides sin, Strides sout, int BH, int H, int N, int Tm, int Tn, int bq, int ksel, int alpha_per_block) {
+    Strides sin, Strides sout, int BH, int H, int N, int Tm, int Tn, int bq, int ksel, int alpha_per_block,
+    BwdColumns columns) {
   typedef BwdQF32Smem<D> SM;
   typedef StatePart<D> SP;
   constexpr int LD = SM::LD, ET = D / 32, J = D / 8, NW = 4;
   extern __shared__ __attribute__((aligned(16))) float smem[];
+  if ((int)blockIdx.x < columns.blocks) return bwd_columns_job<256>(columns, blockIdx.x, reinterpret_cast<unsigned char*>(smem));
+  const int block = blockIdx.x - columns.blocks;
   float* qs = smem;
   float* dos = smem + SM::kDoOff;
   float* mus = smem + SM::kMuOff;
@@ -61,7 +66,7 @@ __global__ __launch_bounds__(256, 2) void bwd_q_f32_kernel(
   float* dots = smem + SM::kDotOff;
 
   const int groups = (N + 31) / 32, all = BH * groups, run = (all + kXcds - 1) / kXcds;   // as in the forward kernel
-  const int at = blockIdx.x % kXcds * run + blockIdx.x / kXcds;
+  const int at = block % kXcds * run + block / kXcds;
   if (at >= all) return;
   const int bh = at / groups, grp = at % groups, h = bh % H;
   const int row0 = 32 * grp, rows_valid = min(32, N - row0), i = row0 / bq;
@@ -618,10 +623,11 @@ static hipError_t launch_q(const Shape& s, const BwdArgs& a, hipStream_t stream)
   static OncePerDevice once;
   if (hipError_t e = allow_dynamic_lds(once, (const void*)bwd_q_f32_kernel<D>, smem); e != hipSuccess) return e;
   const int run = (s.BH * ((s.N + 31) / 32) + kXcds - 1) / kXcds;
-  bwd_q_f32_kernel<D><<<dim3((unsigned)(run * kXcds)), 256, smem, stream>>>(
+  const BwdColumns columns = bwd_columns(s, a);
+  bwd_q_f32_kernel<D><<<dim3((unsigned)(columns.blocks + run * kXcds)), 256, smem, stream>>>(
       (const float*)a.q, (const float*)a.k, (const float*)a.v, (const float*)a.dout, (const float*)a.o_s, (const float*)a.o_l,
       a.lse, a.k_mean, (const float*)a.h_i, a.z_i, a.block_idx, a.alpha, (float*)a.dq, a.ds, a.lraw, a.inv_den, a.dl,
-      a.dalpha_part, s.sin, s.sout, s.BH, s.H, s.N, s.Tm, s.Tn, s.bq, s.k, s.alpha_per_block ? 1 : 0);
+      a.dalpha_part, s.sin, s.sout, s.BH, s.H, s.N, s.Tm, s.Tn, s.bq, s.k, s.alpha_per_block ? 1 : 0, columns);
   return hipGetLastError();
 }
 hipError_t launch_bwd_q_f32(const Shape& s, const BwdArgs& a, hipStream_t stream) {

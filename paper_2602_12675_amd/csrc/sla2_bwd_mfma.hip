@@ -20,6 +20,7 @@
 //                dK' += softmax-backward(dK^phi).
 #include <type_traits>
 
+#include "bwd_columns.h"
 #include "mfma_tiles.h"
 
 namespace sla2 {
@@ -37,6 +38,7 @@ template <int D, int BQ> struct BwdQSmem {
   static constexpr int kDlOff = kMuOff + D * 4;                                // float [BQ]  dO . O^s, later D^l, per row
   static constexpr int kRedOff = kDlOff + BQ * 4;                              // float [8]
   static constexpr int kBytes = kRedOff + 32;
+  static_assert(kBwdColumnsLds <= kBytes, "the lists are made by workgroups of the same launch");
 };
 
 template <int D, int BQ>
@@ -47,7 +49,7 @@ __global__ __launch_bounds__(BQ * 2, 2) void bwd_q_mfma_kernel(
     const float* __restrict__ z_i, const int32_t* __restrict__ block_idx, const float* __restrict__ alpha,
     uint16_t* __restrict__ dq, float* __restrict__ ds_out, float* __restrict__ lraw_out, uint16_t* __restrict__ dh_out,
     float* __restrict__ dz_out, float* __restrict__ dalpha_part, Strides sin, Strides sout, int H, int N, int Tm, int Tn,
-    int ksel, int alpha_per_block) {
+    int ksel, int alpha_per_block, BwdColumns columns) {
   constexpr int NW = BQ / 32;
   constexpr int KS = D / 16, ET = D / 32;
   typedef typename std::conditional<D == 128 && BQ == 128, SwizzledLayoutB<128>, SwizzledLayout<D>>::type SL;
@@ -55,6 +57,8 @@ __global__ __launch_bounds__(BQ * 2, 2) void bwd_q_mfma_kernel(
   // rows repeat every 16, which the two waves of a 64-row block do not cover with one transfer)
   typedef BwdQSmem<D, BQ> SM;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+  if ((int)blockIdx.x < columns.blocks) return bwd_columns_job<BQ * 2>(columns, blockIdx.x, smem);
+  const int block = blockIdx.x - columns.blocks;
   float* zs = reinterpret_cast<float*>(smem + SM::kZsOff);
   float* mus = reinterpret_cast<float*>(smem + SM::kMuOff);
   float* dls = reinterpret_cast<float*>(smem + SM::kDlOff);
@@ -65,7 +69,7 @@ __global__ __launch_bounds__(BQ * 2, 2) void bwd_q_mfma_kernel(
   // consecutive query blocks of a head share key/value tiles: every head is cut into 8 runs of
   // consecutive blocks, one per XCD (own L2), and all XCDs work through the heads in the same order
   const int per_head = (Tm + kXcds - 1) / kXcds;
-  const int bh = (blockIdx.x / kXcds) / per_head, i = (blockIdx.x % kXcds) * per_head + (blockIdx.x / kXcds) % per_head;
+  const int bh = (block / kXcds) / per_head, i = (block % kXcds) * per_head + (block / kXcds) % per_head;
   if (i >= Tm) return;
   const int h = bh % H;
   const int tid = threadIdx.x, lane = tid % kWave, g = lane / 32;
@@ -474,10 +478,11 @@ static hipError_t launch_bwd_q_mfma(const Shape& s, const BwdArgs& a, hipStream_
   static OncePerDevice once;
   if (hipError_t e = allow_dynamic_lds(once, (const void*)bwd_q_mfma_kernel<D, BQ>, smem); e != hipSuccess) return e;
   const int grid = ((s.Tm + kXcds - 1) / kXcds) * kXcds * s.BH;
-  bwd_q_mfma_kernel<D, BQ><<<dim3((unsigned)grid), BQ * 2, smem, stream>>>(
+  const BwdColumns columns = bwd_columns(s, a);
+  bwd_q_mfma_kernel<D, BQ><<<dim3((unsigned)(columns.blocks + grid)), BQ * 2, smem, stream>>>(
       (const uint16_t*)a.q, (const uint16_t*)a.k, (const uint16_t*)a.v, (const uint16_t*)a.dout, (const uint16_t*)a.o_s,
       a.lse, a.k_mean, (const uint16_t*)a.h_i, a.z_i, a.block_idx, a.alpha, (uint16_t*)a.dq, a.ds, a.lraw,
-      (uint16_t*)a.dh, a.dz, a.dalpha_part, s.sin, s.sout, s.H, s.N, s.Tm, s.Tn, s.k, s.alpha_per_block ? 1 : 0);
+      (uint16_t*)a.dh, a.dz, a.dalpha_part, s.sin, s.sout, s.H, s.N, s.Tm, s.Tn, s.k, s.alpha_per_block ? 1 : 0, columns);
   return hipGetLastError();
 }
 
