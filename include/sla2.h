@@ -245,7 +245,8 @@ typedef enum {
   SLA2_STAGE_TOPK = 1,        /* projection, scores, row-wise top-k; colmean(K)   (Eq. 16; Alg. 2, smoothing) */
   SLA2_STAGE_KV_STATE = 2,    /* K^phi, partial h and z, low-bit codes of K (Alg. 2: K^phi, h, z); small fp32
                                  calls: the launch of SLA2_STAGE_TOPK, which forms them too */
-  SLA2_STAGE_KV_TOTAL = 3,    /* per-head totals of h and z */
+  SLA2_STAGE_KV_TOTAL = 3,    /* per-head totals of h and z; fp32 tensors: also H_i, Z_i of the query blocks (small
+                                 calls: in the launch of SLA2_STAGE_ATTN) */
   SLA2_STAGE_ATTN = 4,        /* sparse + linear branch + mix              (Alg. 2 block loop, Eq. 13) */
   SLA2_STAGE_DENSE = 5,       /* dense attention comparator */
   SLA2_STAGE_BWD_LISTS = 6,   /* sla2_backward: the block mask as bits, per key block the list of its query blocks:

@@ -190,9 +190,11 @@ hipError_t launch_block_states_f32(const Shape& s, const float* states, const in
                                    float* h_i, float* z_i, hipStream_t stream);
 // the same on the key side of the backward pass: dH_j, dZ_j from dH_i, dZ_i of the query blocks that did not select j
 hipError_t launch_key_states_f32(const Shape& s, const BwdArgs& a, hipStream_t stream);
-hipError_t launch_attn_f32(const Shape& s, const float* q, const float* k, const float* v, const double* k_mean, const float* h_i,
-                           const float* z_i, const int32_t* block_idx, const float* alpha, float* out, float* lse,
-                           const SavedForBackward& sv, hipStream_t stream);
+// small calls: the attention kernel forms them (and the totals) itself, from the states
+bool attn_forms_states(const Shape& s);
+hipError_t launch_attn_f32(const Shape& s, const float* q, const float* k, const float* v, const double* k_mean, const float* states,
+                           float* h_i, float* z_i, float* h_total, float* z_total, const int32_t* block_idx, const float* alpha,
+                           float* out, float* lse, const SavedForBackward& sv, hipStream_t stream);
 
 hipError_t launch_kv_total(const Shape& s, const float* partial, float* h_total, float* z_total, float* h_frag, hipStream_t stream);
 hipError_t launch_kv_state_bf16(const Shape& s, const uint16_t* k, const uint16_t* v, const double* k_mean,

@@ -20,7 +20,7 @@
 // What bounds it: the chain of a workgroup, half of it the fp64 products themselves (64 cycles each), the rest the phases
 // between barriers.  The second tile, the divisions left to ragged blocks (they ran for every score before) and the order
 // of the workgroups below: soft router on 12 heads of 256 x 512 blocks 73.4 -> 71.1 us with its pooling, selection on 40
-// heads of 591 x 1,182 315 -> 309 us, on 4 heads of 16 x 16 (d = 64) the whole forward call 25.2 -> 24.9 us; at 12 heads of 256 x 512
+// heads of 591 x 1,182 315 -> 309 us, on 2 heads of 16 x 16 (d = 64) the whole forward call 25.2 -> 24.9 us; at 12 heads of 256 x 512
 // the hard selection, one workgroup on three quarters of the CUs, is where it was.
 #pragma once
 #include "common.h"

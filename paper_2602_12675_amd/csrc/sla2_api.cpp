@@ -380,13 +380,15 @@ int sla2_forward(const sla2_params* params, const void* q, const void* k, const 
         SLA2_STAGE(SLA2_STAGE_KV_STATE, launch_kv_state_f32(s, (const float*)k, (const float*)v, k_mean, at<float>(workspace, L.k_stats),
                                                             states, st)) != hipSuccess)
       return SLA2_EHIP;
+    auto attn = [&]() {
+      return launch_attn_f32(s, (const float*)q, (const float*)k, (const float*)v, k_mean, states, h_i, z_i, h_total, z_total, idx,
+                             alpha, (float*)out, lse_or_null, sv, st);
+    };
+    if (attn_forms_states(s))
+      return SLA2_STAGE(SLA2_STAGE_KV_TOTAL, SLA2_STAGE(SLA2_STAGE_ATTN, attn())) != hipSuccess ? SLA2_EHIP : SLA2_OK;
     if (SLA2_STAGE(SLA2_STAGE_KV_TOTAL, launch_block_states_f32(s, states, idx, h_total, z_total, h_i, z_i, st)) != hipSuccess)
       return SLA2_EHIP;
-    if (SLA2_STAGE(SLA2_STAGE_ATTN,
-                   launch_attn_f32(s, (const float*)q, (const float*)k, (const float*)v, k_mean, h_i, z_i, idx, alpha,
-                                   (float*)out, lse_or_null, sv, st)) != hipSuccess)
-      return SLA2_EHIP;
-    return SLA2_OK;
+    return SLA2_STAGE(SLA2_STAGE_ATTN, attn()) != hipSuccess ? SLA2_EHIP : SLA2_OK;
   }
   float* k_stats = at<float>(workspace, L.k_stats);
   float* h_frag = partial + (size_t)s.BH * s.chunks * (s.d * s.d + s.d);

@@ -191,7 +191,7 @@ hipError_t launch_key_states_f32(const Shape& s, const BwdArgs& a, hipStream_t s
 // Bound by the fp32 matrix rate in the loop (a wave needs 64 products, 4,096 cycles, for every 16 loads of 1 KB; 85 % of the
 // time of a longer list) and by HBM outside: 12 heads of 4,096 tokens, d = 128, keeping O^s and O^l, 6 blocks a list 125 us, none
 // 46 us; 128-row workgroups with K', K^phi and V tiles in LDS, which rebuilt H_i, took 245 us.  2 heads of 1,024, d = 64: 20.5 ->
-// 9.8 us.
+// 9.8 us (with the states' sums in it 12.8).
 // ---------------------------------------------------------------------------------------------
 template <int D> struct AttnF32Smem {
   static constexpr int LD = kF32Ld<D>, ET = D / 32, NW = 4;
@@ -207,13 +207,66 @@ template <int D> struct AttnF32Smem {
   static_assert(32 * LD <= kMeetFloats<D, kRounds>, "O_l takes the place of the parts");
 };
 
-template <int D>
+// OWN (small calls at d = 64): H_i, Z_i of the workgroup's query block formed here, from the states of the head's key blocks,
+// into LDS: 16 KB a state, four states requested at a time.  Kept for the backward pass by one workgroup of the query block,
+// the totals written by one of the head.
+struct OwnStates {
+  const float* states;
+  float *h_i, *z_i, *h_total, *z_total;   // h_i, z_i: null unless kept
+};
+constexpr int kOwnBlocks = 16;            // attn_forms_states
+constexpr int kOwnLd = 64 + 8;            // rows 4 apart meet the other half of the banks
+__device__ __forceinline__ void own_states(const OwnStates& o, float* hs, float* zs, const int32_t* sel, int ksel, int Tn, int bh,
+                                           size_t slot, bool keep, bool total) {
+  constexpr int D = 64, P = f32_state(D), S = 4, U = 4;                     // U pieces of 1,024 entries: h; then z
+  const int tid = threadIdx.x, zcol = min(4 * tid, D - 4);
+  uint32_t listed = 0u;
+  for (int e = 0; e < ksel; e++) listed |= 1u << __builtin_amdgcn_readfirstlane(sel[e]);
+  const float* src = o.states + (size_t)bh * Tn * P;
+  f32x4 sum[U + 1], all[U + 1];
+#pragma unroll
+  for (int u = 0; u <= U; u++) sum[u] = all[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int s0 = 0; s0 < Tn; s0 += S) {
+    f32x4 x[S][U + 1];
+#pragma unroll
+    for (int n = 0; n < S; n++) {
+      const float* p = src + (size_t)min(s0 + n, Tn - 1) * P;
+#pragma unroll
+      for (int u = 0; u < U; u++) x[n][u] = *reinterpret_cast<const f32x4*>(p + 1024 * u + 4 * tid);
+      x[n][U] = *reinterpret_cast<const f32x4*>(p + D * D + zcol);
+    }
+#pragma unroll
+    for (int n = 0; n < S; n++)
+      if (s0 + n < Tn) {
+        if ((listed >> (s0 + n) & 1u) == 0u)
+#pragma unroll
+          for (int u = 0; u <= U; u++) sum[u] += x[n][u];
+        if (total)
+#pragma unroll
+          for (int u = 0; u <= U; u++) all[u] += x[n][u];
+      }
+  }
+#pragma unroll
+  for (int u = 0; u < U; u++) {
+    const int e = 1024 * u + 4 * tid;
+    *reinterpret_cast<f32x4*>(hs + e / D * kOwnLd + e % D) = sum[u];
+    if (keep) *reinterpret_cast<f32x4*>(o.h_i + slot * D * D + e) = sum[u];
+    if (total) *reinterpret_cast<f32x4*>(o.h_total + (size_t)bh * D * D + e) = all[u];
+  }
+  if (4 * tid < D) {
+    *reinterpret_cast<f32x4*>(zs + zcol) = sum[U];
+    if (keep) *reinterpret_cast<f32x4*>(o.z_i + slot * D + zcol) = sum[U];
+    if (total) *reinterpret_cast<f32x4*>(o.z_total + (size_t)bh * D + zcol) = all[U];
+  }
+}
+
+template <int D, bool OWN>
 __global__ __launch_bounds__(256, 2) void attn_f32_kernel(
     const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v, const double* __restrict__ k_mean,
     const float* __restrict__ h_i, const float* __restrict__ z_i, const int32_t* __restrict__ block_idx,
     const float* __restrict__ alpha, float* __restrict__ out, float* __restrict__ lse, float* __restrict__ o_s_save,
     float* __restrict__ o_l_save, float* __restrict__ lse_save, Strides sin, Strides sout, int BH, int H, int N, int Tm, int Tn, int bq,
-    int ksel, int alpha_per_block) {
+    int ksel, int alpha_per_block, const OwnStates own) {
   typedef AttnF32Smem<D> SM;
   constexpr int LD = SM::LD, ET = SM::ET, J = D / 8, NW = SM::NW;
   extern __shared__ __attribute__((aligned(16))) float smem[];
@@ -244,7 +297,7 @@ __global__ __launch_bounds__(256, 2) void attn_f32_kernel(
   f32x4 qr[QM::kLoads];
   QM::load(qr, q + head_offset(sin, bh, H) + (size_t)row0 * sin.n, sin.n, rows_valid, tid);
   const double mu = tid < D ? k_mean[(size_t)bh * D + tid] : 0.0;
-  const float zi = tid < D ? z_i[slot * D + tid] : 0.f;
+  const float zi = !OWN && tid < D ? z_i[slot * D + tid] : 0.f;
   __builtin_amdgcn_sched_barrier(0);
   int t = w, key0 = 0;
   if (t < items) {
@@ -260,8 +313,10 @@ __global__ __launch_bounds__(256, 2) void attn_f32_kernel(
     *reinterpret_cast<f32x4*>(qs + (tid / QM::kChunks + y * QM::kRows) * LD + 4 * (tid % QM::kChunks)) = qr[y];
   if (tid < D) {
     mus[tid] = (float)mu;
-    zs[tid] = zi;
+    if (!OWN) zs[tid] = zi;
   }
+  float* hs = smem + SM::kBytes / sizeof(float);
+  if constexpr (OWN) own_states(own, hs, zs, sel, ksel, Tn, bh, slot, own.h_i != nullptr && row0 % bq == 0, grp == 0);
   f32x16 oacc[ET];
 #pragma unroll
   for (int e = 0; e < ET; e++) oacc[e] = zero16();
@@ -272,7 +327,8 @@ __global__ __launch_bounds__(256, 2) void attn_f32_kernel(
   typedef StatePart<D> SP;
   constexpr int JW = SP::kSteps;
   const int j0 = SP::first(w);
-  const float* hsrc = h_i + slot * D * D + (size_t)(8 * j0 + 4 * g) * D + 32 * SP::tile(w) + SP::row(r);
+  constexpr int LH = OWN ? kOwnLd : D;
+  const float* hsrc = (OWN ? hs : h_i + slot * D * D) + (size_t)(8 * j0 + 4 * g) * LH + 32 * SP::tile(w) + SP::row(r);
   __syncthreads();
 
   int key_next = t + NW < items ? first_key(t + NW) : 0;
@@ -337,7 +393,7 @@ __global__ __launch_bounds__(256, 2) void attn_f32_kernel(
   };
   for (; t + NW < items; t += NW) pass(std::integral_constant<bool, true>());
   if (t < items) pass(std::integral_constant<bool, false>());
-  auto h_piece = [&](int j) { return f32x4{hsrc[8 * j * D], hsrc[(8 * j + 1) * D], hsrc[(8 * j + 2) * D], hsrc[(8 * j + 3) * D]}; };
+  auto h_piece = [&](int j) { return f32x4{hsrc[8 * j * LH], hsrc[(8 * j + 1) * LH], hsrc[(8 * j + 2) * LH], hsrc[(8 * j + 3) * LH]}; };
 #pragma unroll
   for (int j = 0; j < kStream; j++)
     if (j < JW) st[j] = h_piece(j);
@@ -428,25 +484,36 @@ __global__ __launch_bounds__(256, 2) void attn_f32_kernel(
   }
 }
 
-template <int D>
+// Small calls form H_i in the attention kernel: a launch fewer, for T_n x 16 KB that every workgroup reads from L2 where the masked
+// product reads them once per 32 query blocks.  The call with own states / with the product, us, d = 64, a tenth of the blocks kept:
+//   T_n = 4, 4 heads 16.6 / 19.8      T_n = 8, 2 heads 20.7 / 23.0, 12 heads 21.6 / 24.4
+//   T_n = 16, 2 heads 23.6 / 25.0, 4 heads 24.0 / 25.5, 10 heads 30.3 / 31.3 (128-row blocks 29.4 / 29.5)
+//   T_n = 24, 2 heads 25.3 / 26.4, 6 heads 32.4 / 32.0      T_n = 32, 2 heads 29.6 / 29.8, 5 heads 40.2 / 38.1
+// and at d = 128, where a state is 64 KB, 31.4 / 31.5 at T_n = 4, 47.5 / 40.8 at 16 (4 heads each).
+bool attn_forms_states(const Shape& s) { return s.d == 64 && s.Tn <= kOwnBlocks && router_has_room(s); }
+
+template <int D, bool OWN>
 static hipError_t launch_attn_f32_t(const Shape& s, const float* q, const float* k, const float* v, const double* k_mean,
                                     const float* h_i, const float* z_i, const int32_t* block_idx, const float* alpha, float* out,
-                                    float* lse, const SavedForBackward& sv, hipStream_t stream) {
-  constexpr int smem = AttnF32Smem<D>::kBytes;
+                                    float* lse, const SavedForBackward& sv, const OwnStates& own, hipStream_t stream) {
+  constexpr int smem = AttnF32Smem<D>::kBytes + (OWN ? D * kOwnLd * (int)sizeof(float) : 0);
   static OncePerDevice once;
-  if (hipError_t e = allow_dynamic_lds(once, (const void*)attn_f32_kernel<D>, smem); e != hipSuccess) return e;
+  if (hipError_t e = allow_dynamic_lds(once, (const void*)attn_f32_kernel<D, OWN>, smem); e != hipSuccess) return e;
   const int run = (s.BH * ((s.N + 31) / 32) + kXcds - 1) / kXcds;
-  attn_f32_kernel<D><<<dim3((unsigned)(run * kXcds)), 256, smem, stream>>>(
+  attn_f32_kernel<D, OWN><<<dim3((unsigned)(run * kXcds)), 256, smem, stream>>>(
       q, k, v, k_mean, h_i, z_i, block_idx, alpha, out, lse, (float*)sv.o_s, (float*)sv.o_l, sv.lse, s.sin, s.sout, s.BH, s.H, s.N, s.Tm,
-      s.Tn, s.bq, s.k, s.alpha_per_block ? 1 : 0);
+      s.Tn, s.bq, s.k, s.alpha_per_block ? 1 : 0, own);
   return hipGetLastError();
 }
 
-hipError_t launch_attn_f32(const Shape& s, const float* q, const float* k, const float* v, const double* k_mean, const float* h_i,
-                           const float* z_i, const int32_t* block_idx, const float* alpha, float* out, float* lse,
-                           const SavedForBackward& sv, hipStream_t stream) {
-  return s.d == 128 ? launch_attn_f32_t<128>(s, q, k, v, k_mean, h_i, z_i, block_idx, alpha, out, lse, sv, stream)
-                    : launch_attn_f32_t<64>(s, q, k, v, k_mean, h_i, z_i, block_idx, alpha, out, lse, sv, stream);
+hipError_t launch_attn_f32(const Shape& s, const float* q, const float* k, const float* v, const double* k_mean, const float* states,
+                           float* h_i, float* z_i, float* h_total, float* z_total, const int32_t* block_idx, const float* alpha,
+                           float* out, float* lse, const SavedForBackward& sv, hipStream_t stream) {
+  const OwnStates own{states, s.save ? h_i : nullptr, s.save ? z_i : nullptr, h_total, z_total};
+#define SLA2_ATTN(DD, OO) launch_attn_f32_t<DD, OO>(s, q, k, v, k_mean, h_i, z_i, block_idx, alpha, out, lse, sv, own, stream)
+  if (attn_forms_states(s)) return SLA2_ATTN(64, true);
+  return s.d == 128 ? SLA2_ATTN(128, false) : SLA2_ATTN(64, false);
+#undef SLA2_ATTN
 }
 
 }  // namespace sla2
