@@ -150,7 +150,7 @@ inline size_t bwd_kv_grid(const Shape& s) { return (size_t)s.BH * kXcds * ((s.Tn
 // parts of d alpha per query block, column sums of dK' per head: fp32 kernels work on 32 rows and 32 keys at a time
 inline int bwd_alpha_parts(const Shape& s) { return s.bf16 ? 1 : s.bq / 32; }
 inline int bwd_colsums(const Shape& s) { return s.bf16 ? s.Tn : 2 * s.Tn; }
-// the backward pass in the order it runs: lists, query side, totals, key side, finish
+// the backward pass in the order it runs: query side (with the lists), totals, key side, finish
 hipError_t launch_bwd_q(const Shape& s, const BwdArgs& a, hipStream_t stream);
 hipError_t launch_bwd_totals(const Shape& s, const BwdArgs& a, hipStream_t stream);
 hipError_t launch_bwd_kv(const Shape& s, const BwdArgs& a, hipStream_t stream);
