@@ -201,8 +201,9 @@ hipError_t launch_kv_state_bf16(const Shape& s, const uint16_t* k, const uint16_
                                 float* k_stats, float* partial, uint16_t* k_phi, float* z_blocks, uint8_t* k_codes,
                                 float* k_scale, uint8_t* v_codes, float* v_scale, hipStream_t stream);
 // bf16 tensors with Shape::state_heads: kv_state with the states of the key blocks, and H_i from them
+constexpr int kStateParts = 3;               // bf16 numbers that hold an fp32 entry of h_j exactly
 struct GivenStates {
-  uint16_t* states;                          // [state_heads][T_n][2][d * d]: h_j as two bf16 parts, scratch
+  uint16_t* states;                          // [state_heads][T_n][kStateParts][d * d]: h_j in bf16 parts, scratch
   uint16_t* h_i;                             // [BH][T_m][d * d], in the order in which kv_state leaves the parts
   uint32_t* bits;                            // scratch
 };

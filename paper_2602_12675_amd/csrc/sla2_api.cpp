@@ -24,10 +24,13 @@ static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 //  24 heads of 16,384 (256)                 bf16  k = 30 662 / 697       45 898 / 881       FP8  45 845 / 825
 //  48 heads of 4,096 (64)                   bf16  k = 36 384 / 401       60 567 / 532       FP8  44 426 / 425
 //  48 heads of 1,536 (24)                   bf16  k = 20 141 / 158
-// 80 heads of 75,601 tokens, bf16, k = 177: 51.5 -> 42.3 ms.
+// 80 heads of 75,601 tokens, bf16, k = 177: 50.1 -> 43.9 ms.
 constexpr float kStatesFrom = 40.f, kStatesPerBf16 = 0.025f, kStatesPerLowBit = 0.034f;
-// What the states of the heads that are worked on at a time may take: 8 heads of 1,182 key blocks, at the least one head.
-constexpr size_t kStateBytes = (size_t)640 << 20;
+// What the states of the heads that are worked on at a time may take: 8 heads of 1,182 key blocks (five whole rounds of the
+// product's workgroups), at the least one head.
+constexpr size_t kStateBytes = (size_t)960 << 20;
+
+static size_t state_bytes(const Shape& s) { return (size_t)s.Tn * kStateParts * s.d * s.d * 2; }   // bf16 parts of a head's h_j
 
 // Validate everything that does not need pointers and derive the block counts.
 int make_shape(const sla2_params* p, Shape* s) {
@@ -80,8 +83,7 @@ int make_shape(const sla2_params* p, Shape* s) {
   const int kResident = 512;
   s->state_heads = 0;
   if (s->bf16 && s->d == 128 && s->bq == 128 && s->k > kStatesFrom + (s->quant ? kStatesPerLowBit : kStatesPerBf16) * s->Tn) {
-    const size_t head = (size_t)s->Tn * 2 * s->d * s->d * 2;
-    const size_t fit = kStateBytes / head;
+    const size_t fit = kStateBytes / state_bytes(*s);
     s->state_heads = fit < 1 ? 1 : fit > (size_t)s->BH ? s->BH : (int)fit;
   }
   int chunks_max = kResident / (s->state_heads ? s->state_heads : s->BH);
@@ -133,9 +135,9 @@ static size_t f32_states(const Shape& s) { return ((size_t)s.BH * s.Tn * (s.d * 
 
 // with state_heads, in the place of K^phi: H_i, then the states of a group of heads, then the bits
 static size_t given_h(const Shape& s) { return align256((size_t)s.BH * s.Tm * s.d * s.d * 2); }
-static size_t given_states(const Shape& s) { return align256((size_t)s.state_heads * s.Tn * 2 * s.d * s.d * 2); }
+static size_t given_states(const Shape& s) { return align256(s.state_heads * state_bytes(s)); }
 static size_t given_bytes(const Shape& s) {
-  return given_h(s) + given_states(s) + (size_t)s.BH * masked_words(2 * s.Tn) * masked_pitch(s.Tm) * sizeof(uint32_t);
+  return given_h(s) + given_states(s) + (size_t)s.BH * masked_words(kStateParts * s.Tn) * masked_pitch(s.Tm) * sizeof(uint32_t);
 }
 
 void make_layout(const Shape& s, sla2_ws_layout* L) {

@@ -57,8 +57,8 @@ __device__ __forceinline__ size_t kphi_offset(size_t block, int mt, int ks, int 
 // kv_state_bf16
 // =============================================================================================
 // QUANT: 0 none, 1 FP8 e4m3 codes of K - colmean K, 2 INT8 codes, 3 as 1 plus e4m3 codes of V.
-// STATES: h_j of every key block is written too, as the sum of two bf16 parts (2^-17 of an entry is left out), in the place of
-// K^phi: rows 2 j and 2 j + 1 of `states`, each as the accumulators lie - [tile (mt, nt)][2][64 lanes][8], lane l of half y
+// STATES: h_j of every key block is written too, in the place of K^phi, as the sum of three bf16 parts (8 + 8 + 8 bits: nothing
+// of an fp32 entry is left out): rows 3 j to 3 j + 2 of `states`, each as the accumulators lie - [tile (mt, nt)][2][64 lanes][8], lane l of half y
 // holding column e = 32 nt + l % 32, rows c = 32 mt + 16 y + 4 (l / 32) + {0..3, 8..11}.  The heads are those from bh0 on.
 template <int D, int QUANT, bool STATES>
 __global__ __launch_bounds__(256, STATES ? 2 : 1) void kv_state_bf16_kernel(const uint16_t* __restrict__ k,
@@ -244,7 +244,7 @@ __global__ __launch_bounds__(256, STATES ? 2 : 1) void kv_state_bf16_kernel(cons
 #pragma unroll
       for (int ks = 0; ks < kTileTokens / 16; ks++)
         kf[ks] = kphi_fragment<PaddedLayout<D>>(ktile, lnz2, mu2[0], ks, 32 * mt0, lane, zsum[0]);
-      uint16_t* hi = states + ((size_t)(bh - bh0) * Tn + j) * (2 * D * D) + ((mt0 * (D / 32) + nt0) * 2 * kWave + lane) * 8;
+      uint16_t* to = states + ((size_t)(bh - bh0) * Tn + j) * (kStateParts * D * D) + ((mt0 * (D / 32) + nt0) * 2 * kWave + lane) * 8;
 #pragma unroll
       for (int b = 0; b < HS::kNtw; b++) {
         f32x16 h;
@@ -255,14 +255,19 @@ __global__ __launch_bounds__(256, STATES ? 2 : 1) void kv_state_bf16_kernel(cons
           h = mfma_bf16(kf[ks], v_fragment<PaddedLayout<D>>(vtile, ks, 32 * (nt0 + b), lane), h);
 #pragma unroll
         for (int y = 0; y < 2; y++) {
-          bf16x8 large, small;
+          float left[8];
 #pragma unroll
-          for (int e = 0; e < 8; e++) {
-            large[e] = (__bf16)h[8 * y + e];
-            small[e] = (__bf16)(h[8 * y + e] - (float)large[e]);
+          for (int e = 0; e < 8; e++) left[e] = h[8 * y + e];
+#pragma unroll
+          for (int p = 0; p < kStateParts; p++) {
+            bf16x8 part;
+#pragma unroll
+            for (int e = 0; e < 8; e++) {
+              part[e] = (__bf16)left[e];
+              left[e] -= (float)part[e];
+            }
+            *reinterpret_cast<bf16x8*>(to + p * (D * D) + (2 * b + y) * kWave * 8) = part;
           }
-          *reinterpret_cast<bf16x8*>(hi + (2 * b + y) * kWave * 8) = large;
-          *reinterpret_cast<bf16x8*>(hi + D * D + (2 * b + y) * kWave * 8) = small;
         }
         hacc[0][b] += h;
         __builtin_amdgcn_sched_barrier(0);             // one tile at a time: the registers
@@ -328,26 +333,28 @@ hipError_t launch_kv_state_bf16(const Shape& s, const uint16_t* k, const uint16_
 
 // ---------------------------------------------------------------------------------------------
 // H_i of all query blocks of a call as a product of the selection's complement with all h_j (masked_sums.h), for long lists:
-// an h_j in two bf16 parts (the error of the linear branch alone against fp64 is what it was, 1.8e-3 to 2.6e-3 for 64 to 200 key
-// blocks, within 2e-4 of itself), the sum in fp32, H_i as bf16 (as the attention kernel applies it) in the order of kv_state.
-// On 8 heads of 75,601 tokens: kv_state 173 us (0.6 GB written, K^phi left out), the product 360 us (366 GFLOP, 1.0 PFLOP/s); the
-// attention kernel without the rebuilt states takes 35.4 instead of 48.4 ms on 80 of them at 85 % sparsity.
+// an h_j in three bf16 parts, which hold its fp32 entries whole, the sum in fp32, H_i as bf16 (as the attention kernel applies it)
+// in the order of kv_state.  Two parts leave out 2^-18 of an entry: where 257 states cancel to 2^-9 of one, the output was off by
+// 5e-2 with them, by the rounding of its operands with three (and with states rebuilt from bf16 operands).
+// On 8 heads of 75,601 tokens: kv_state 244 us (0.9 GB written, K^phi left out), the product 534 us (549 GFLOP, 1.0 PFLOP/s, bound
+// by the matrix cores); with two parts 173 and 349 us.  The attention kernel without the rebuilt states takes 35.4 instead of
+// 48.4 ms on 80 of them at 85 % sparsity, the call 43.9 instead of 50.1 (two parts 41.6).
 //
-// block_bits: the complement as bits, 2 j and 2 j + 1 of a row for key block j; one workgroup per 64 rows of a head.
+// block_bits: the complement as bits, 3 j to 3 j + 2 of a row for key block j; one workgroup per 64 rows of a head.
 __global__ __launch_bounds__(256) void block_bits_kernel(const int32_t* __restrict__ block_idx, uint32_t* __restrict__ bits, int Tm, int Tn,
                                                          int ksel) {
   extern __shared__ uint32_t listed[];                // [words][64]
-  const int words = masked_words(2 * Tn), pitch = masked_pitch(Tm), r0 = blockIdx.x * 64, bh = blockIdx.y, rows = min(64, Tm - r0);
+  const int words = masked_words(kStateParts * Tn), pitch = masked_pitch(Tm), r0 = blockIdx.x * 64, bh = blockIdx.y, rows = min(64, Tm - r0);
   for (int x = threadIdx.x; x < 64 * words; x += 256) listed[x] = 0u;
   __syncthreads();
   const int32_t* idx = block_idx + ((size_t)bh * Tm + r0) * ksel;
   for (int e = threadIdx.x; e < rows * ksel; e += 256) {
-    const int j = idx[e];
-    atomicOr(&listed[j / 16 * 64 + e / ksel], 3u << (2 * (j % 16)));   // OR: the result does not depend on the order
+    for (int s = kStateParts * idx[e], end = s + kStateParts; s < end; s++)
+      atomicOr(&listed[s / 32 * 64 + e / ksel], 1u << (s % 32));       // OR: the result does not depend on the order
   }
   __syncthreads();
   for (int x = threadIdx.x; x < 64 * words; x += 256) {
-    const int y = x / 64, left = 2 * Tn - 32 * y;
+    const int y = x / 64, left = kStateParts * Tn - 32 * y;
     const uint32_t open = left >= 32 ? ~0u : left > 0 ? (1u << left) - 1u : 0u;
     bits[((size_t)bh * words + y) * pitch + r0 + x % 64] = ~listed[x] & open;
   }
@@ -359,16 +366,17 @@ __global__ __launch_bounds__(256, 2) void block_states_bf16_kernel(const uint16_
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   const int tiles = (Tm + kMaskedRows - 1) / kMaskedRows, sets = len / kMaskedCols;
   const int y = blockIdx.x / kXcds, set = y / tiles * kXcds + blockIdx.x % kXcds, head = set / sets;   // sets: a multiple of 8
-  masked_sums_tile(states + (size_t)head * 2 * Tn * len, bits + (size_t)head * masked_words(2 * Tn) * masked_pitch(Tm),
-                   h_i + (size_t)head * Tm * len, 2 * Tn, Tm, len, y % tiles * kMaskedRows, set % sets * kMaskedCols, smem);
+  const int S = kStateParts * Tn;
+  masked_sums_tile(states + (size_t)head * S * len, bits + (size_t)head * masked_words(S) * masked_pitch(Tm),
+                   h_i + (size_t)head * Tm * len, S, Tm, len, y % tiles * kMaskedRows, set % sets * kMaskedCols, smem);
 }
 
 // As many heads at a time as their states fill kStateBytes: with kv_state of a group, its product.
 hipError_t launch_kv_states_bf16(const Shape& s, const uint16_t* k, const uint16_t* v, const double* k_mean, float* k_stats,
                                  float* partial, float* z_blocks, uint8_t* k_codes, float* k_scale, uint8_t* v_codes, float* v_scale,
                                  const int32_t* block_idx, const GivenStates& gs, hipStream_t stream) {
-  const int words = masked_words(2 * s.Tn), len = s.d * s.d, tiles = (s.Tm + kMaskedRows - 1) / kMaskedRows;
-  block_bits_kernel<<<dim3((unsigned)((s.Tm + 63) / 64), (unsigned)s.BH), 256, 64 * words * sizeof(uint32_t), stream>>>(   // at most 32 KB
+  const int words = masked_words(kStateParts * s.Tn), len = s.d * s.d, tiles = (s.Tm + kMaskedRows - 1) / kMaskedRows;
+  block_bits_kernel<<<dim3((unsigned)((s.Tm + 63) / 64), (unsigned)s.BH), 256, 64 * words * sizeof(uint32_t), stream>>>(   // at most 48 KB
       block_idx, gs.bits, s.Tm, s.Tn, s.k);
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
   static OncePerDevice once;

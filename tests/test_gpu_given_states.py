@@ -1,5 +1,5 @@
 """Long lists at d = 128 with 128-row blocks: H_i formed before the attention kernel, as a product of the selection's complement
-with the states of all key blocks in two bf16 parts - every mode, ragged ends, around whole tiles of 128 query blocks and 32 key
+with the states of all key blocks in three bf16 parts - every mode, ragged ends, around whole tiles of 128 query blocks and 32 key
 blocks, every block but one and every block selected, the training call, and more heads than one group holds."""
 import numpy as np
 import pytest
@@ -38,7 +38,7 @@ def test_backward(quant):
 
 
 def test_groups_of_heads():
-    """160 heads of 64 key blocks: 4.2 MB of states each, 152 at a time.  The call against two of 80 heads: only the order of the
+    """160 heads of 64 key blocks: 6.3 MB of states each.  The call against two of 80 heads: only the order of the
     sums of Z_total differs (1e-7), which moves an output across a bf16 boundary now and then."""
     import torch
     from paper_2602_12675_amd import api

@@ -1,0 +1,54 @@
+"""States of the linear branch at the ends of what they hold: sums that cancel to a small part of their
+terms - for long bf16 lists (H_i as a masked product of bf16 operands)."""
+import numpy as np
+import pytest
+
+import sla2_oracle as O
+from helpers import rel_l2
+
+pytestmark = pytest.mark.gpu
+
+
+def call(q, k, v, frac, alpha, block_q=128, dout=None, flags=0):
+    """q, k, v [1, H, N, d] on the GPU -> out, block lists (and dv for dout), the router being the identity.  H_i of bf16 tensors is a
+    masked product where the lists are long and the heads many enough to fill the GPU, so some tests repeat one head."""
+    import torch
+    from paper_2602_12675_amd import api
+    _, H, N, d = q.shape
+    p = api.make_params(1, H, N, d, block_q, 64, frac, dtype=api.SLA2_BF16 if q.dtype == torch.bfloat16 else api.SLA2_F32,
+                        flags=flags | (api.SLA2_FLAG_SAVE_FOR_BACKWARD if dout is not None else 0))
+    rw = torch.eye(d, device="cuda").repeat(2, 1, 1)
+    al = torch.full((H,), alpha, device="cuda")
+    ws, out = api.alloc_workspace(p), torch.empty_like(q)
+    idx = torch.empty((1, H, -(-N // block_q), api.sla2_num_selected(p)), dtype=torch.int32, device="cuda")
+    api.sla2_forward(p, q, k, v, rw, al, out, block_idx=idx, workspace=ws)
+    if dout is None:
+        return out, idx.cpu().numpy()
+    dq, dk, dv = (torch.empty_like(q) for _ in range(3))
+    api.sla2_backward(p, q, k, v, al, dout, dq, dk, dv, torch.empty_like(al), ws)
+    return out, idx.cpu().numpy(), dv
+
+
+def test_cancelling_states():
+    """H_i = (128 x 129/128 - 129 + 2^-9) h with the terms in turn: 2^-9 of h is left of 257 terms of its size.  A state held to
+    2^-18 of itself would leave 128 x 2^-19 x 2^9 = 0.1 of that (its errors are the same in all terms of a sign); fp32 states
+    and sums leave 2^-24 of about two terms now and then, 1e-3.  K^phi, Q^phi, H_i and the output are rounded to bf16: 2e-3 each."""
+    import torch
+    d, H, sel, rest = 128, 10, 90, 258
+    blocks, N = sel + rest, 64 * (sel + rest)
+    gen = torch.Generator().manual_seed(3)
+    k0, u = torch.randn((64, d), generator=gen), torch.randint(0, 2, (64, d), generator=gen) * 2.0 - 1.0
+    toward = torch.randn((d,), generator=gen)
+    scale = torch.tensor([0.0] * sel + [129 / 128, -1.0] * 128 + [-1.0, 2.0 ** -9])
+    k = k0 + (torch.arange(blocks) < sel)[:, None, None] * toward
+    v = scale[:, None, None] * u
+    q = torch.randn((N, d), generator=gen) + toward
+    q, k, v = (x.reshape(1, 1, N, d).to(torch.bfloat16) for x in (q, k, v))
+    out, idx = call(*(x.cuda().repeat(1, H, 1, 1) for x in (q, k, v)), sel / blocks, 0.0)
+    assert (idx == np.arange(sel)).all()
+    q, k, v = (x[0, 0].double().numpy() for x in (q, k, v))
+    some = [0, 77, idx.shape[2] - 1]
+    ref, _, _ = O.linear_branch(q, O.smooth_k(k), v, idx[0, 0], 128, 64, q_blocks=some)
+    rows = np.concatenate([np.arange(128 * i, min(N, 128 * i + 128)) for i in some])
+    for h in (0, H - 1):
+        assert rel_l2(out[0, h].float().cpu().numpy()[rows], ref[rows]) < 1e-2
