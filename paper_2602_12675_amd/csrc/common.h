@@ -135,7 +135,7 @@ struct BwdArgs {
   float* dalpha;
   const void* h_i;                           // as SavedForBackward
   const float* z_i;
-  // scratch.  dh: one d x d slot per query block (fp32 tensors: dZ_i behind each); lraw: L log2(e) per row (bf16: on the raw keys)
+  // scratch.  dh: one d x d slot per query block (bf16 tensors: dH_i / 2; fp32 tensors: dZ_i behind each); lraw: L log2(e) per row (bf16: on the raw keys)
   float *ds, *lraw, *dz /* bf16 tensors */, *dz_total, *colsum, *dk_mean, *dalpha_part;
   void* dh;
   int32_t *col_ptr, *col_idx, *col_cnt;      // per key block the query blocks that selected it: offsets, lists, lengths
@@ -203,7 +203,7 @@ hipError_t launch_kv_state_bf16(const Shape& s, const uint16_t* k, const uint16_
 // bf16 tensors with Shape::state_heads: kv_state with the states of the key blocks, and H_i from them
 constexpr int kStateParts = 3;               // bf16 numbers that hold an fp32 entry of h_j exactly
 struct GivenStates {
-  uint16_t* states;                          // [state_heads][T_n][kStateParts][d * d]: h_j in bf16 parts, scratch
+  uint16_t* states;                          // [state_heads][T_n][kStateParts][d * d]: h_j / 2 in bf16 parts, scratch
   uint16_t* h_i;                             // [BH][T_m][d * d], in the order in which kv_state leaves the parts
   uint32_t* bits;                            // scratch
 };

@@ -25,12 +25,12 @@ constexpr int kMaskedLds = 2 * kMaskedTile;           // two buffers: two workgr
 // permuted by the row bits in which the four rows of a transposing read differ (below), which then meet different banks.
 __device__ __forceinline__ unsigned masked_unit(unsigned row) { return (row & 1) | (row >> 3 & 2); }
 
-// The 128 x 256 tile of C from (row0, col0).  b: [S][cols] bf16, c: [R][cols] bf16, bits: words of this head.
+// The 128 x 256 tile of C from (row0, col0).  b: [S][cols] bf16, halves of what is summed, c: [R][cols] bf16, bits: words of this head.
 //
 // One step is 64 rows of B.  Operand order: contraction index k = 2 q + x (+ 8 g for the upper half of the wave) of
 // 16-row product ks is row 32 g + 16 x + 4 ks + q of the step, so that the two bits of a register of the mask operand
-// are 16 apart in the row's word and all of them come out of it with a shift and an AND: 0x4000 is 2.0 in bf16, and C is
-// halved at the end.
+// are 16 apart in the row's word and all of them come out of it with a shift and an AND: 0x4000 is 2.0 in bf16, so B holds
+// halves (halving C at the end instead would lose what the sums hold above half of the largest number).
 // Bound by the matrix cores: 8 products (256 cycles) a wave and ks against 128 cycles for the mask operands, 2 KB of LDS
 // reads; B arrives one step ahead.
 __device__ __forceinline__ void masked_sums_tile(const uint16_t* __restrict__ b, const uint32_t* __restrict__ bits,
@@ -142,7 +142,7 @@ __device__ __forceinline__ void masked_sums_tile(const uint16_t* __restrict__ b,
         for (int v = 0; v < 16; v += 2) {
           typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
           const f32x16& x = acc[part * (RT / 2) + t][u];
-          const bf16x2 two = {(__bf16)(0.5f * x[v]), (__bf16)(0.5f * x[v + 1])};
+          const bf16x2 two = {(__bf16)x[v], (__bf16)x[v + 1]};
           const unsigned own = __builtin_bit_cast(unsigned, two);
           const unsigned other = (unsigned)__builtin_amdgcn_update_dpp((int)own, (int)own, 0xB1, 0xf, 0xf, false);   // lane ^ 1
           const unsigned row = 32 * t + 8 * (v / 4) + 4 * g + v % 4 + odd;

@@ -301,6 +301,7 @@ __global__ __launch_bounds__(BQ * 2, 2) void bwd_q_mfma_kernel(
   constexpr int kTilesPerWave = ET * ET / NW, kEts = kTilesPerWave < ET ? kTilesPerWave : ET, kCts = kTilesPerWave / kEts;
   static_assert(kTilesPerWave >= 1, "unsupported split");
   uint16_t* dh_slot = dh_out + slot * D * D;
+  const float dh_scale = 0.5f * (1.f - al);          // a half of it, for masked_sums.h
 #pragma unroll 1
   for (int x = 0; x < kCts; x++) {
     const int t0 = w * kTilesPerWave + x * kEts, ct = t0 / ET, et0 = t0 % ET;
@@ -325,7 +326,7 @@ __global__ __launch_bounds__(BQ * 2, 2) void bwd_q_mfma_kernel(
       for (int half = 0; half < 2; half++) {
         bf16x8 o;
 #pragma unroll
-        for (int e = 0; e < 8; e++) o[e] = (__bf16)((1.f - al) * acc[y][8 * half + e]);
+        for (int e = 0; e < 8; e++) o[e] = (__bf16)(dh_scale * acc[y][8 * half + e]);
         *reinterpret_cast<bf16x8*>(dh_slot + (((t0 + y) * 2 + half) * kWave + lane) * 8) = o;
       }
     dz = half_sum(dz);

@@ -57,8 +57,8 @@ __device__ __forceinline__ size_t kphi_offset(size_t block, int mt, int ks, int 
 // kv_state_bf16
 // =============================================================================================
 // QUANT: 0 none, 1 FP8 e4m3 codes of K - colmean K, 2 INT8 codes, 3 as 1 plus e4m3 codes of V.
-// STATES: h_j of every key block is written too, in the place of K^phi, as the sum of three bf16 parts (8 + 8 + 8 bits: nothing
-// of an fp32 entry is left out): rows 3 j to 3 j + 2 of `states`, each as the accumulators lie - [tile (mt, nt)][2][64 lanes][8], lane l of half y
+// STATES: half of h_j of every key block is written too (masked_sums.h), in the place of K^phi, as the sum of three bf16 parts
+// (8 + 8 + 8 bits: nothing of an fp32 entry is left out): rows 3 j to 3 j + 2 of `states`, each as the accumulators lie - [tile (mt, nt)][2][64 lanes][8], lane l of half y
 // holding column e = 32 nt + l % 32, rows c = 32 mt + 16 y + 4 (l / 32) + {0..3, 8..11}.  The heads are those from bh0 on.
 template <int D, int QUANT, bool STATES>
 __global__ __launch_bounds__(256, STATES ? 2 : 1) void kv_state_bf16_kernel(const uint16_t* __restrict__ k,
@@ -257,7 +257,7 @@ __global__ __launch_bounds__(256, STATES ? 2 : 1) void kv_state_bf16_kernel(cons
         for (int y = 0; y < 2; y++) {
           float left[8];
 #pragma unroll
-          for (int e = 0; e < 8; e++) left[e] = h[8 * y + e];
+          for (int e = 0; e < 8; e++) left[e] = 0.5f * h[8 * y + e];
 #pragma unroll
           for (int p = 0; p < kStateParts; p++) {
             bf16x8 part;

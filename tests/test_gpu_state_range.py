@@ -1,5 +1,5 @@
 """States of the linear branch at the ends of what they hold: sums that cancel to a small part of their
-terms - for long bf16 lists (H_i as a masked product of bf16 operands)."""
+terms, sums near the largest fp32 value - for long bf16 lists (H_i as a masked product of bf16 operands), dH_j and fp32 tensors."""
 import numpy as np
 import pytest
 
@@ -52,3 +52,46 @@ def test_cancelling_states():
     rows = np.concatenate([np.arange(128 * i, min(N, 128 * i + 128)) for i in some])
     for h in (0, H - 1):
         assert rel_l2(out[0, h].float().cpu().numpy()[rows], ref[rows]) < 1e-2
+
+
+# A channel that takes nearly all of Q^phi and K^phi: H_i and dH_j are then about the number of tokens times one value.
+def one_channel(N, d, gen):
+    import torch
+    x = 0.1 * torch.randn((N, d), generator=gen)
+    x[:, 0] += 20.0
+    return x
+
+
+def test_large_states():
+    """H_i of 1.9e38, where fp32 ends at 3.4e38."""
+    import torch
+    from paper_2602_12675_amd import api
+    N, H, d, frac, v0 = 10240, 20, 128, 68 / 160, 3.2e34
+    gen = torch.Generator().manual_seed(5)
+    q, k = one_channel(N, d, gen), one_channel(N, d, gen)
+    v = v0 * (1.0 + 0.1 * torch.randn((N, d), generator=gen))
+    q, k, v = (x.reshape(1, 1, N, d).to(torch.bfloat16) for x in (q, k, v))
+    out, idx = call(*(x.cuda().repeat(1, H, 1, 1) for x in (q, k, v)), frac, 0.25, flags=api.SLA2_FLAG_NO_SMOOTH_K)
+    Q, K, V = (x[0, 0].double().numpy() for x in (q, k, v))
+    some = [0, 40, 79]
+    ref = O.forward_head(Q, K, V / v0, np.eye(d), np.eye(d), 0.25, frac, 128, 64, smooth=False, sel=idx[0, 0], q_blocks=some)
+    rows = np.concatenate([np.arange(128 * i, 128 * i + 128) for i in some])
+    for h in (0, H - 1):
+        assert rel_l2(out[0, h].double().cpu().numpy()[rows] / v0, ref["O"][rows]) < 1e-2
+
+
+@pytest.mark.parametrize("d,block_q,dtype", [(128, 128, "bfloat16"), (64, 64, "bfloat16"), (128, 128, "float32")])
+def test_large_gradient_states(d, block_q, dtype):
+    import torch
+    from paper_2602_12675_amd import api
+    N, frac, g0 = 2048, 0.2, 2.0e38
+    gen = torch.Generator().manual_seed(6)
+    q, k = one_channel(N, d, gen), one_channel(N, d, gen)
+    dout = torch.zeros((N, d))
+    dout[:, 5] = g0
+    q, k, dout = (x.reshape(1, 1, N, d).to(getattr(torch, dtype)) for x in (q, k, dout))
+    _, idx, dv = call(q.cuda(), k.cuda(), torch.zeros_like(q).cuda(), frac, 0.0, block_q, dout.cuda(), api.SLA2_FLAG_NO_SMOOTH_K)
+    g = O.backward_head(q[0, 0].double().numpy(), k[0, 0].double().numpy(), np.zeros((N, d)), idx[0, 0], 0.0,
+                        dout[0, 0].double().numpy() / g0, block_q, 64, smooth=False)
+    assert g["dV"].max() > 0.86                        # x g0: more than half of what fp32 holds
+    assert rel_l2(dv[0, 0].double().cpu().numpy() / g0, g["dV"]) < 1e-2
