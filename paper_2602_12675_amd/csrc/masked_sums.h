@@ -44,7 +44,7 @@ __device__ __forceinline__ void masked_sums_tile(const uint16_t* __restrict__ b,
   // transfer n of wave w: rows 16 w + 2 n, + 1 of the step
   auto request = [&](int step, int buf) {
     const char* base = reinterpret_cast<const char*>(b) + (size_t)step * 64 * cols * 2 + (size_t)col0 * 2;
-    const unsigned rows = min(64, S - 64 * step);      // rows past the end repeat the last one; their bits are 0
+    const unsigned rows = min(64, S - 64 * step);      // rows past the end repeat the last one (cleared below)
 #pragma unroll
     for (int n = 0; n < 8; n++) {
       const unsigned row = 16 * w + 2 * n + lane / 32;
@@ -61,8 +61,12 @@ __device__ __forceinline__ void masked_sums_tile(const uint16_t* __restrict__ b,
       to[t] = __builtin_bit_cast(unsigned, load_untracked_at(reinterpret_cast<const float*>(base), 4 * (g * (unsigned)pitch + r)));
     }
   };
-  auto landed = [&](unsigned (&x)[RT]) {
+  auto landed = [&](unsigned (&x)[RT], int step) {
     wait_vmcnt<0>();
+    // rows past the end: their bits are 0, but 0 times an infinite entry is NaN.  Of this wave's rows 16 w to 16 w + 15
+    for (int row = max(S - 64 * step, 16 * w); row < 16 * w + 16; row++)
+      *reinterpret_cast<u32x2*>(smem + (step & 1) * kMaskedTile + row * 512 + 8 * lane) = u32x2{0u, 0u};
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
     for (int t = 0; t < RT; t++) settle(x[t]);
   };
@@ -82,7 +86,7 @@ __device__ __forceinline__ void masked_sums_tile(const uint16_t* __restrict__ b,
 #pragma unroll
   for (int u = 0; u < CT; u++)
     at[u] = lds0 + tr_row * 512 + 64 * ((unsigned)(CT * w + u) ^ masked_unit(tr_row)) + 32 * (lane / 16 % 2) + 8 * (lane % 4);
-  landed(word);
+  landed(word, 0);
   phase_barrier();
   for (int step = 0; step < steps; step++) {
     const unsigned buf = (step & 1) * kMaskedTile;
@@ -120,7 +124,7 @@ __device__ __forceinline__ void masked_sums_tile(const uint16_t* __restrict__ b,
           acc[t][u] = mfma_bf16(__builtin_bit_cast(bf16x8, a[t]), __builtin_bit_cast(bf16x8, v4), acc[t][u]);
       }
     }
-    landed(next);                                      // the next step is there ...
+    landed(next, more ? step + 1 : step);              // the next step is there ...
 #pragma unroll
     for (int t = 0; t < RT; t++) word[t] = next[t];
     phase_barrier();                                   // ... for everyone, and this one's tile is free

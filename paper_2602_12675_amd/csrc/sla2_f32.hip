@@ -67,7 +67,7 @@ __global__ __launch_bounds__(256, 2) void masked_states_f32_kernel(const float* 
   const int tid = threadIdx.x, lane = tid % kWave, g = lane / 32, w = tid / kWave;
   const int col = (set % kSets * 4 + w) * kStateCols + 4 * (lane % 32);
   const float* src = states + (size_t)bh * S * P + min(col, P - 4);
-  f32x4 b[16];                            // blocks 32 sw + 2 n + g; past the end the last one, with weight 0
+  f32x4 b[16];                            // blocks 32 sw + 2 n + g; past the end the last one, taken as 0
   auto request = [&](int sw, int n) { b[n] = *reinterpret_cast<const f32x4*>(src + (size_t)min(32 * sw + 2 * n + g, S - 1) * P); };
 #pragma unroll
   for (int n = 0; n < 16; n++) request(0, n);
@@ -101,9 +101,10 @@ __global__ __launch_bounds__(256, 2) void masked_states_f32_kernel(const float* 
 #pragma unroll
         for (int n = 8 * half; n < 8 * half + 8; n++) {
           const bool exists = 32 * sw + 2 * n + g < S;
-          if (tile == 0) sum += exists ? b[n] : f32x4{0.f, 0.f, 0.f, 0.f};
+          if (!exists) b[n] = f32x4{0.f, 0.f, 0.f, 0.f};   // (0 times an infinite entry is NaN)
+          if (tile == 0) sum += b[n];
           if constexpr (!TOTALS_ONLY) {
-            const float a = exists && (word >> (2 * n + g) & 1u) == 0u ? 1.f : 0.f;
+            const float a = (word >> (2 * n + g) & 1u) == 0u ? 1.f : 0.f;
 #pragma unroll
             for (int x = 0; x < 4; x++) acc[x] = mfma_f32(a, b[n][x], acc[x]);
           }

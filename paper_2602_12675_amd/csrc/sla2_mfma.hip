@@ -264,7 +264,8 @@ __global__ __launch_bounds__(256, STATES ? 2 : 1) void kv_state_bf16_kernel(cons
 #pragma unroll
             for (int e = 0; e < 8; e++) {
               part[e] = (__bf16)left[e];
-              left[e] -= (float)part[e];
+              const float rest = left[e] - (float)part[e];
+              left[e] = p > 0 || __builtin_isfinite(left[e]) ? rest : 0.f;   // the first part has all of an infinite entry
             }
             *reinterpret_cast<bf16x8*>(to + p * (D * D) + (2 * b + y) * kWave * 8) = part;
           }

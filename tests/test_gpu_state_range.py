@@ -1,5 +1,5 @@
-"""States of the linear branch at the ends of what they hold: sums that cancel to a small part of their
-terms, sums near the largest fp32 value - for long bf16 lists (H_i as a masked product of bf16 operands), dH_j and fp32 tensors."""
+"""States of the linear branch at the ends of what they hold: sums that cancel to a small part of their terms, sums near the largest
+fp32 value, infinite entries - for long bf16 lists (H_i and dH_j as masked products of bf16 operands) and for fp32 tensors."""
 import numpy as np
 import pytest
 
@@ -95,3 +95,53 @@ def test_large_gradient_states(d, block_q, dtype):
                         dout[0, 0].double().numpy() / g0, block_q, 64, smooth=False)
     assert g["dV"].max() > 0.86                        # x g0: more than half of what fp32 holds
     assert rel_l2(dv[0, 0].double().cpu().numpy() / g0, g["dV"]) < 1e-2
+
+
+INFINITE = [   # H, T_n, d, block_q, type, kept fraction: both forms of the bf16 forward pass, the three of the fp32 one
+    (32, 97, 128, 128, "bfloat16", 0.68), (1, 97, 128, 128, "bfloat16", 0.2), (1, 45, 128, 128, "float32", 0.2),
+    (1, 97, 64, 64, "float32", 0.011), (1, 13, 64, 128, "float32", 0.3),
+]
+
+
+@pytest.mark.parametrize("which", ["last", "middle"])
+@pytest.mark.parametrize("H,T_n,d,block_q,dtype,frac", INFINITE)
+def test_infinite_value(H, T_n, d, block_q, dtype, frac, which):
+    """One infinite entry of V: query blocks that did not select its key block have +inf in that channel, and what they had in
+    the others; those that did have something infinite or NaN there, and what they had in the others."""
+    import torch
+    N, e = 64 * T_n - 7, 3
+    gen = torch.Generator(device="cuda").manual_seed(8)
+    q, k, v = (torch.randn((1, 1, N, d), generator=gen, device="cuda").to(getattr(torch, dtype)).repeat(1, H, 1, 1) for _ in range(3))
+    plain, idx = call(q, k, v, frac, 0.5, block_q)
+    j = T_n - 1 if which == "last" else idx[0, 0, 0, idx.shape[3] // 2]
+    v[0, :, 64 * j, e] = float("inf")
+    out, again = call(q, k, v, frac, 0.5, block_q)
+    assert (idx == again).all()
+    listed = np.repeat((idx[0, 0] == j).any(axis=1), block_q)[:N]
+    assert not listed.all()
+    others = np.arange(d) != e
+    for h in (0, H - 1):
+        got, want = out[0, h].double().cpu().numpy(), plain[0, h].double().cpu().numpy()
+        assert np.array_equal(got[:, others], want[:, others])
+        assert np.isposinf(got[~listed, e]).all() and not np.isfinite(got[listed, e]).any()
+
+
+@pytest.mark.parametrize("d,block_q,dtype", [(128, 128, "bfloat16"), (64, 64, "bfloat16"), (128, 128, "float32"), (64, 64, "float32")])
+@pytest.mark.parametrize("which", ["last", "middle"])
+def test_infinite_gradient(d, block_q, dtype, which):
+    """One infinite entry of dO in a query block: dV of the keys that it did not select is infinite in that channel alone."""
+    import torch
+    N, e = 2048 - 7, 3
+    gen = torch.Generator(device="cuda").manual_seed(9)
+    q, k, v, dout = (torch.randn((1, 1, N, d), generator=gen, device="cuda").to(getattr(torch, dtype)) for _ in range(4))
+    _, idx, plain = call(q, k, v, 0.2, 0.5, block_q, dout)
+    T_m = idx.shape[2]
+    i = T_m - 1 if which == "last" else T_m // 2
+    dout[0, 0, block_q * i, e] = float("inf")
+    _, again, dv = call(q, k, v, 0.2, 0.5, block_q, dout)
+    assert (idx == again).all()
+    listed = np.repeat(np.isin(np.arange(-(-N // 64)), idx[0, 0, i]), 64)[:N]
+    got, want = dv[0, 0].double().cpu().numpy(), plain[0, 0].double().cpu().numpy()
+    others = np.arange(d) != e
+    assert np.array_equal(got[~listed][:, others], want[~listed][:, others])
+    assert np.isposinf(got[~listed, e]).all()
