@@ -111,8 +111,8 @@ typedef struct sla2_ws_layout {
   size_t k_phi;     /* bf16   [BH, T_n, d/32, 4, 64, 8]  K^phi = softmax_d(K - colmean K) of each key block as matrix-core
                                                         operand fragments (bf16 path only): lane l of fragment (mt, ks)
                                                         holds channel 32 mt + l%32, tokens 16 ks + 8 (i/4) + 4 (l/32) + i%4, i = 0..7.
-                                                        d = 128 with 128-row blocks and long lists: H_i of the query blocks and
-                                                        scratch instead (the lists that the library takes for long are its own) */
+                                                        0 bytes (z_blocks at the same offset) where a call does without: d = 128
+                                                        with 128-row blocks and long lists (H_i formed ahead, in `partial`) */
   size_t z_blocks;  /* float  [BH, T_n, d]   z_j = colsum(K^phi_j) per key block (bf16 path only)        (Alg. 2: z) */
   size_t k_fp8;     /* uint8  [BH, T_n*block_kv, d]  e4m3 (FP8 mode) or two's-complement int8 (INT8 mode) codes of the
                        smoothed K; low-bit modes only; rows >= N are 0 */
@@ -124,7 +124,8 @@ typedef struct sla2_ws_layout {
   size_t v_scale;   /* float  [BH, T_n]      dequantisation scale of each V block (SLA2_QUANT_FP8_V only) */
   size_t partial;   /* scratch.  double [BH, T_n, d], k_sum once more as the operand fragments of the router (written by the
                        pooling step, dead after the router).  bf16 path, in their place afterwards: the per-chunk partial sums of h
-                       and z and, behind them, -h_total as accumulator fragments; fp32 path, behind them: h_j, z_j of every key block
+                       and z and, behind them, -h_total as accumulator fragments (where k_phi has 0 bytes: then H_i and what it
+                       is formed of); fp32 path, behind them: h_j, z_j of every key block
                        and, without SLA2_FLAG_SAVE_FOR_BACKWARD, H_i, Z_i of every query block */
   /* with SLA2_FLAG_SAVE_FOR_BACKWARD only (0 bytes otherwise): */
   size_t o_s;       /* dtype  [BH, N, d]     sparse-branch output O^s, before the mix of Eq. 13   (input of Alg. 3) */

@@ -133,11 +133,16 @@ static size_t pooled_bytes(const Shape& s) { return align256((size_t)s.BH * s.Tn
 // fp32 tensors: entries of the key blocks' states (a whole number of 256-byte units)
 static size_t f32_states(const Shape& s) { return ((size_t)s.BH * s.Tn * (s.d * s.d + s.d) + 63) & ~(size_t)63; }
 
-// with state_heads, in the place of K^phi: H_i, then the states of a group of heads, then the bits
+// bf16 tensors: per chunk of key blocks the partial sums of h and z, then -h_total as fragments
+static size_t partial_bytes(const Shape& s) {
+  const size_t state = (size_t)s.d * s.d + s.d;
+  return align256((size_t)s.BH * ((size_t)s.chunks * state + (size_t)s.d * s.d) * sizeof(float));
+}
+// with state_heads, behind the partial sums: H_i, then the states of a group of heads, then the bits
 static size_t given_h(const Shape& s) { return align256((size_t)s.BH * s.Tm * s.d * s.d * 2); }
 static size_t given_states(const Shape& s) { return align256(s.state_heads * state_bytes(s)); }
 static size_t given_bytes(const Shape& s) {
-  return given_h(s) + given_states(s) + (size_t)s.BH * masked_words(kStateParts * s.Tn) * masked_pitch(s.Tm) * sizeof(uint32_t);
+  return s.state_heads == 0 ? 0 : given_h(s) + given_states(s) + (size_t)s.BH * masked_words(kStateParts * s.Tn) * masked_pitch(s.Tm) * sizeof(uint32_t);
 }
 
 void make_layout(const Shape& s, sla2_ws_layout* L) {
@@ -151,16 +156,17 @@ void make_layout(const Shape& s, sla2_ws_layout* L) {
   L->h_total = take(BH * d * d * sizeof(float));
   L->z_total = take(BH * d * sizeof(float));
   L->k_stats = take(BH * (size_t)s.N * sizeof(float));
-  L->k_phi = take(s.bf16 ? (s.state_heads ? given_bytes(s) : BH * (size_t)s.Tn * s.bk * d * 2) : 0);
+  L->k_phi = take(s.bf16 && s.state_heads == 0 ? BH * (size_t)s.Tn * s.bk * d * 2 : 0);
   L->z_blocks = take(s.bf16 ? BH * (size_t)s.Tn * d * sizeof(float) : 0);
   L->k_fp8 = take(s.quant ? BH * (size_t)s.Tn * s.bk * d : 0);
   L->k_scale = take(s.quant ? BH * (size_t)s.Tn * sizeof(float) : 0);
   L->v_fp8 = take(s.quant == 3 ? BH * (size_t)s.Tn * s.bk * d : 0);
   L->v_scale = take(s.quant == 3 ? BH * (size_t)s.Tn * sizeof(float) : 0);
-  // bf16, two lives: the pooled keys as fragments, for the router; then the partial sums, -h_total as fragments behind them.
+  // bf16, two lives: the pooled keys as fragments, for the router; then the partial sums, -h_total as fragments behind them
+  // and, with state_heads, H_i and what it is formed of.
   // fp32: the pooled keys, the states of all key blocks and, unless `bwd` keeps them, H_i, Z_i of the query blocks
-  const size_t state = d * d + d, pooled = pooled_bytes(s), partials = BH * ((size_t)s.chunks * state + d * d) * sizeof(float);
-  if (s.bf16) L->partial = take(partials > pooled ? partials : pooled);
+  const size_t state = d * d + d, pooled = pooled_bytes(s), sums = partial_bytes(s) + given_bytes(s);
+  if (s.bf16) L->partial = take(sums > pooled ? sums : pooled);
   else L->partial = take(pooled + (f32_states(s) + (s.save ? 0 : BH * s.Tm * state)) * sizeof(float));
   const size_t esz = s.bf16 ? 2 : 4;
   L->o_s = take(s.save ? BH * (size_t)s.N * d * esz : 0);
@@ -400,8 +406,10 @@ int sla2_forward(const sla2_params* params, const void* q, const void* k, const 
   float* k_scale = at<float>(workspace, L.k_scale);
   uint8_t* v_fp8 = at<uint8_t>(workspace, L.v_fp8);
   float* v_scale = at<float>(workspace, L.v_scale);
-  GivenStates gs{(uint16_t*)((char*)k_phi + given_h(s)), k_phi, (uint32_t*)((char*)k_phi + given_h(s) + given_states(s))};
   if (s.state_heads) {
+    char* given = (char*)partial + partial_bytes(s);
+    const GivenStates gs{(uint16_t*)(given + given_h(s)), (uint16_t*)given, (uint32_t*)(given + given_h(s) + given_states(s))};
+    k_phi = gs.h_i;
     if (SLA2_STAGE(SLA2_STAGE_KV_STATE,
                    launch_kv_states_bf16(s, (const uint16_t*)k, (const uint16_t*)v, k_mean, k_stats, partial, z_blocks, k_fp8, k_scale,
                                          v_fp8, v_scale, idx, gs, st)) != hipSuccess)

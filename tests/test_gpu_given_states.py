@@ -57,3 +57,23 @@ def test_groups_of_heads():
     whole, parts = call(0, H), np.concatenate([call(0, H // 2), call(H // 2, H)], axis=1)
     for h in range(H):
         assert rel_l2(whole[0, h], parts[0, h]) < 2e-4, h
+
+
+@pytest.mark.parametrize("H,frac", [(48, 1.0), (2, 0.1)])
+def test_kphi_in_the_workspace(H, frac):
+    """sla2_ws_layout.k_phi holds K^phi as fragments or has no bytes, whatever the lists' length (here the longest and a short one)."""
+    import torch
+    from paper_2602_12675_amd import api
+    N, d, T_n = 4096, 128, 64
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    q, k, v = (torch.randn((1, H, N, d), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(3))
+    p = api.make_params(1, H, N, d, 128, 64, frac, dtype=api.SLA2_BF16)
+    ws, L = api.alloc_workspace(p), api.sla2_workspace_layout(p)
+    api.sla2_forward(p, q, k, v, torch.eye(d, device="cuda").repeat(2, 1, 1), torch.ones((H,), device="cuda"), torch.empty_like(q), workspace=ws)
+    if L.z_blocks == L.k_phi:
+        return
+    got = api.workspace_view(ws, L.k_phi, torch.bfloat16, (H, T_n, d // 32, 4, 2, 32, 2, 4)).float().cpu().numpy()   # mt, ks, l / 32, l % 32, i / 4, i % 4
+    got = got.transpose(0, 1, 3, 6, 4, 7, 2, 5).reshape(H, N, d)                # tokens 16 ks + 8 (i / 4) + 4 (l / 32) + i % 4
+    kd = k[0].double()
+    want = torch.softmax(kd - kd.mean(dim=1, keepdim=True), dim=-1).cpu().numpy()
+    assert rel_l2(got, want) < 4e-3                                              # rounded to bf16: at most 2^-9 each
