@@ -210,7 +210,7 @@ struct GivenStates {
 hipError_t launch_kv_states_bf16(const Shape& s, const uint16_t* k, const uint16_t* v, const double* k_mean, float* k_stats,
                                  float* partial, float* z_blocks, uint8_t* k_codes, float* k_scale, uint8_t* v_codes, float* v_scale,
                                  const int32_t* block_idx, const GivenStates& gs, hipStream_t stream);
-// k_phi: with Shape::state_heads H_i in its place
+// k_phi: with Shape::state_heads H_i in its place (read from sv.h_i where that is not null)
 hipError_t launch_attn_bf16(const Shape& s, const uint16_t* q, const uint16_t* k, const uint16_t* v,
                             const double* k_mean, const uint16_t* k_phi, const float* z_blocks, const uint8_t* k_codes,
                             const float* k_scale, const uint8_t* v_codes, const float* v_scale,

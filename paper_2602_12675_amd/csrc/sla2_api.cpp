@@ -138,8 +138,8 @@ static size_t partial_bytes(const Shape& s) {
   const size_t state = (size_t)s.d * s.d + s.d;
   return align256((size_t)s.BH * ((size_t)s.chunks * state + (size_t)s.d * s.d) * sizeof(float));
 }
-// with state_heads, behind the partial sums: H_i, then the states of a group of heads, then the bits
-static size_t given_h(const Shape& s) { return align256((size_t)s.BH * s.Tm * s.d * s.d * 2); }
+// with state_heads, behind the partial sums: H_i (unless `bwd` keeps it), then the states of a group of heads, then the bits
+static size_t given_h(const Shape& s) { return s.save ? 0 : align256((size_t)s.BH * s.Tm * s.d * s.d * 2); }
 static size_t given_states(const Shape& s) { return align256(s.state_heads * state_bytes(s)); }
 static size_t given_bytes(const Shape& s) {
   return s.state_heads == 0 ? 0 : given_h(s) + given_states(s) + (size_t)s.BH * masked_words(kStateParts * s.Tn) * masked_pitch(s.Tm) * sizeof(uint32_t);
@@ -408,7 +408,7 @@ int sla2_forward(const sla2_params* params, const void* q, const void* k, const 
   float* v_scale = at<float>(workspace, L.v_scale);
   if (s.state_heads) {
     char* given = (char*)partial + partial_bytes(s);
-    const GivenStates gs{(uint16_t*)(given + given_h(s)), (uint16_t*)given, (uint32_t*)(given + given_h(s) + given_states(s))};
+    const GivenStates gs{(uint16_t*)(given + given_h(s)), (uint16_t*)(s.save ? sv.h_i : given), (uint32_t*)(given + given_h(s) + given_states(s))};
     k_phi = gs.h_i;
     if (SLA2_STAGE(SLA2_STAGE_KV_STATE,
                    launch_kv_states_bf16(s, (const uint16_t*)k, (const uint16_t*)v, k_mean, k_stats, partial, z_blocks, k_fp8, k_scale,

@@ -493,7 +493,8 @@ template <int D, int BQ, bool FP8, bool VQ, bool PIPE, bool GIVEN> struct AttnSm
 // two waves hold half of the d x d state each; 3 for d = 64 with 128-row blocks, where the accumulators are small
 // enough for 168 registers (measured on a 32,760-token d = 64 input: 6 % faster in FP8 mode, 10 % in bf16 mode;
 // with 64-row blocks three waves gain nothing).
-// GIVEN (pipelined loop): H_i was formed before (launch_kv_states_bf16) and is not rebuilt from K^phi; `k_phi` points to it.
+// GIVEN (pipelined loop): H_i was formed before (launch_kv_states_bf16) and is not rebuilt from K^phi: in the slots of `h_save`,
+// which the workgroup of the block turns into H_i^T at its end, or without it where `k_phi` points to.
 template <int D, int BQ, int MODE, bool PIPE, bool GIVEN>
 __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ == 128) ? 3 : 2) void attn_mfma_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
@@ -630,7 +631,7 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
   float zsel[HS::kMtw];
   if constexpr (!DENSE) {
     if constexpr (GIVEN) {
-      const float* slot = reinterpret_cast<const float*>(k_phi + ((size_t)bh * Tm + i) * D * D) + w * (D * D / 2 / NW);
+      const float* slot = reinterpret_cast<const float*>((h_save ? h_save : k_phi) + ((size_t)bh * Tm + i) * D * D) + w * (D * D / 2 / NW);
 #pragma unroll
       for (int x = 0; x < kGivenLoads; x++) hgiven[x] = load16_untracked_at(slot + 1024 * (x / 4), lane16, x % 4);
     } else {

@@ -1,0 +1,13 @@
+"""What the workspace may take: the scratch of the states of the linear branch is bounded, whatever the number of heads."""
+from paper_2602_12675_amd import api
+
+MB = 1 << 20
+
+
+def test_training_with_long_lists_keeps_H_i_once():
+    """40 heads of 75,601 tokens, 177 of 1,182 key blocks: H_i of all query blocks (739 MB) is in `bwd`; `partial` holds the states of
+    some heads, their bits, partial sums - or, in the backward pass, dH_j (1,478 MB)."""
+    p = api.make_params(1, 40, 75601, 128, 128, 64, 0.15, dtype=api.SLA2_BF16, flags=api.SLA2_FLAG_SAVE_FOR_BACKWARD)
+    L = api.sla2_workspace_layout(p)
+    assert L.z_blocks == L.k_phi
+    assert L.o_s - L.partial <= max(1200 * MB, 40 * 1182 * 128 * 128 * 2)
