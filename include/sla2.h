@@ -247,7 +247,8 @@ typedef enum {
   SLA2_STAGE_KV_STATE = 2,    /* K^phi, partial h and z, low-bit codes of K (Alg. 2: K^phi, h, z); small fp32
                                  calls: the launch of SLA2_STAGE_TOPK, which forms them too */
   SLA2_STAGE_KV_TOTAL = 3,    /* per-head totals of h and z; fp32 tensors: also H_i, Z_i of the query blocks (small
-                                 calls: in the launch of SLA2_STAGE_ATTN) */
+                                 calls: in the launch of SLA2_STAGE_ATTN); where k_phi has 0 bytes no launch of its own:
+                                 SLA2_STAGE_KV_STATE has them, and H_i, a group of heads at a time */
   SLA2_STAGE_ATTN = 4,        /* sparse + linear branch + mix              (Alg. 2 block loop, Eq. 13) */
   SLA2_STAGE_DENSE = 5,       /* dense attention comparator */
   SLA2_STAGE_BWD_LISTS = 6,   /* sla2_backward: the block mask as bits, per key block the list of its query blocks:

@@ -196,11 +196,11 @@ hipError_t launch_attn_f32(const Shape& s, const float* q, const float* k, const
                            float* h_i, float* z_i, float* h_total, float* z_total, const int32_t* block_idx, const float* alpha,
                            float* out, float* lse, const SavedForBackward& sv, hipStream_t stream);
 
-hipError_t launch_kv_total(const Shape& s, const float* partial, float* h_total, float* z_total, float* h_frag, hipStream_t stream);
+hipError_t launch_kv_total(const Shape& s, int heads, const float* partial, float* h_total, float* z_total, float* h_frag, hipStream_t stream);
 hipError_t launch_kv_state_bf16(const Shape& s, const uint16_t* k, const uint16_t* v, const double* k_mean,
                                 float* k_stats, float* partial, uint16_t* k_phi, float* z_blocks, uint8_t* k_codes,
                                 float* k_scale, uint8_t* v_codes, float* v_scale, hipStream_t stream);
-// bf16 tensors with Shape::state_heads: kv_state with the states of the key blocks, and H_i from them
+// bf16 tensors with Shape::state_heads: kv_state with the states of the key blocks, the totals, and H_i from the states
 constexpr int kStateParts = 3;               // bf16 numbers that hold an fp32 entry of h_j exactly
 struct GivenStates {
   uint16_t* states;                          // [state_heads][T_n][kStateParts][d * d]: h_j / 2 in bf16 parts, scratch
@@ -208,8 +208,8 @@ struct GivenStates {
   uint32_t* bits;                            // scratch
 };
 hipError_t launch_kv_states_bf16(const Shape& s, const uint16_t* k, const uint16_t* v, const double* k_mean, float* k_stats,
-                                 float* partial, float* z_blocks, uint8_t* k_codes, float* k_scale, uint8_t* v_codes, float* v_scale,
-                                 const int32_t* block_idx, const GivenStates& gs, hipStream_t stream);
+                                 float* partial, float* h_total, float* z_total, float* z_blocks, uint8_t* k_codes, float* k_scale,
+                                 uint8_t* v_codes, float* v_scale, const int32_t* block_idx, const GivenStates& gs, hipStream_t stream);
 // k_phi: with Shape::state_heads H_i in its place (read from sv.h_i where that is not null)
 hipError_t launch_attn_bf16(const Shape& s, const uint16_t* q, const uint16_t* k, const uint16_t* v,
                             const double* k_mean, const uint16_t* k_phi, const float* z_blocks, const uint8_t* k_codes,

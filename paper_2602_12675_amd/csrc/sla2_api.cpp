@@ -133,10 +133,11 @@ static size_t pooled_bytes(const Shape& s) { return align256((size_t)s.BH * s.Tn
 // fp32 tensors: entries of the key blocks' states (a whole number of 256-byte units)
 static size_t f32_states(const Shape& s) { return ((size_t)s.BH * s.Tn * (s.d * s.d + s.d) + 63) & ~(size_t)63; }
 
-// bf16 tensors: per chunk of key blocks the partial sums of h and z, then -h_total as fragments
+// bf16 tensors: per chunk of key blocks the partial sums of h and z, then -h_total as fragments; with state_heads the
+// partial sums of those heads alone
 static size_t partial_bytes(const Shape& s) {
   const size_t state = (size_t)s.d * s.d + s.d;
-  return align256((size_t)s.BH * ((size_t)s.chunks * state + (size_t)s.d * s.d) * sizeof(float));
+  return align256((s.state_heads ? s.state_heads * s.chunks * state : (size_t)s.BH * (s.chunks * state + (size_t)s.d * s.d)) * sizeof(float));
 }
 // with state_heads, behind the partial sums: H_i (unless `bwd` keeps it), then the states of a group of heads, then the bits
 static size_t given_h(const Shape& s) { return s.save ? 0 : align256((size_t)s.BH * s.Tm * s.d * s.d * 2); }
@@ -399,7 +400,7 @@ int sla2_forward(const sla2_params* params, const void* q, const void* k, const 
     return SLA2_STAGE(SLA2_STAGE_ATTN, attn()) != hipSuccess ? SLA2_EHIP : SLA2_OK;
   }
   float* k_stats = at<float>(workspace, L.k_stats);
-  float* h_frag = partial + (size_t)s.BH * s.chunks * (s.d * s.d + s.d);
+  float* h_frag = s.state_heads ? nullptr : partial + (size_t)s.BH * s.chunks * (s.d * s.d + s.d);
   uint16_t* k_phi = at<uint16_t>(workspace, L.k_phi);
   float* z_blocks = at<float>(workspace, L.z_blocks);
   uint8_t* k_fp8 = at<uint8_t>(workspace, L.k_fp8);
@@ -411,15 +412,17 @@ int sla2_forward(const sla2_params* params, const void* q, const void* k, const 
     const GivenStates gs{(uint16_t*)(given + given_h(s)), (uint16_t*)(s.save ? sv.h_i : given), (uint32_t*)(given + given_h(s) + given_states(s))};
     k_phi = gs.h_i;
     if (SLA2_STAGE(SLA2_STAGE_KV_STATE,
-                   launch_kv_states_bf16(s, (const uint16_t*)k, (const uint16_t*)v, k_mean, k_stats, partial, z_blocks, k_fp8, k_scale,
-                                         v_fp8, v_scale, idx, gs, st)) != hipSuccess)
+                   launch_kv_states_bf16(s, (const uint16_t*)k, (const uint16_t*)v, k_mean, k_stats, partial, h_total, z_total, z_blocks,
+                                         k_fp8, k_scale, v_fp8, v_scale, idx, gs, st)) != hipSuccess)
       return SLA2_EHIP;
-  } else if (SLA2_STAGE(SLA2_STAGE_KV_STATE,
-                 launch_kv_state_bf16(s, (const uint16_t*)k, (const uint16_t*)v, k_mean, k_stats, partial, k_phi,
-                                      z_blocks, k_fp8, k_scale, v_fp8, v_scale, st)) != hipSuccess)
-    return SLA2_EHIP;
-  if (SLA2_STAGE(SLA2_STAGE_KV_TOTAL, launch_kv_total(s, partial, h_total, z_total, h_frag, st)) != hipSuccess)
-    return SLA2_EHIP;
+  } else {
+    if (SLA2_STAGE(SLA2_STAGE_KV_STATE,
+                   launch_kv_state_bf16(s, (const uint16_t*)k, (const uint16_t*)v, k_mean, k_stats, partial, k_phi,
+                                        z_blocks, k_fp8, k_scale, v_fp8, v_scale, st)) != hipSuccess)
+      return SLA2_EHIP;
+    if (SLA2_STAGE(SLA2_STAGE_KV_TOTAL, launch_kv_total(s, s.BH, partial, h_total, z_total, h_frag, st)) != hipSuccess)
+      return SLA2_EHIP;
+  }
   if (SLA2_STAGE(SLA2_STAGE_ATTN,
                  launch_attn_bf16(s, (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, k_mean, k_phi,
                                   z_blocks, k_fp8, k_scale, v_fp8, v_scale, h_frag, z_total, idx, alpha, (uint16_t*)out,

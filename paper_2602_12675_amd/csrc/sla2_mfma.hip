@@ -59,7 +59,8 @@ __device__ __forceinline__ size_t kphi_offset(size_t block, int mt, int ks, int 
 // QUANT: 0 none, 1 FP8 e4m3 codes of K - colmean K, 2 INT8 codes, 3 as 1 plus e4m3 codes of V.
 // STATES: half of h_j of every key block is written too (masked_sums.h), in the place of K^phi, as the sum of three bf16 parts
 // (8 + 8 + 8 bits: nothing of an fp32 entry is left out): rows 3 j to 3 j + 2 of `states`, each as the accumulators lie - [tile (mt, nt)][2][64 lanes][8], lane l of half y
-// holding column e = 32 nt + l % 32, rows c = 32 mt + 16 y + 4 (l / 32) + {0..3, 8..11}.  The heads are those from bh0 on.
+// holding column e = 32 nt + l % 32, rows c = 32 mt + 16 y + 4 (l / 32) + {0..3, 8..11}.  The heads are those from bh0 on;
+// `partial` and `states` hold theirs alone.
 template <int D, int QUANT, bool STATES>
 __global__ __launch_bounds__(256, STATES ? 2 : 1) void kv_state_bf16_kernel(const uint16_t* __restrict__ k,
                                                             const uint16_t* __restrict__ v,
@@ -298,7 +299,7 @@ __global__ __launch_bounds__(256, STATES ? 2 : 1) void kv_state_bf16_kernel(cons
       if (g == 0 && nt0 == 0) z_blocks[((size_t)bh * Tn + j) * D + 32 * (mt0 + a) + lane] = z;
     }
   }
-  float* ph = partial + ((size_t)bh * chunks + chunk) * (D * D + D);
+  float* ph = partial + (size_t)blockIdx.x * (D * D + D);   // head of the launch, chunk
 #pragma unroll
   for (int a = 0; a < HS::kMtw; a++) {
 #pragma unroll
@@ -372,10 +373,10 @@ __global__ __launch_bounds__(256, 2) void block_states_bf16_kernel(const uint16_
                    h_i + (size_t)head * Tm * len, S, Tm, len, y % tiles * kMaskedRows, set % sets * kMaskedCols, smem);
 }
 
-// As many heads at a time as their states fill kStateBytes: with kv_state of a group, its product.
+// As many heads at a time as their states fill kStateBytes: with kv_state of a group, its totals and its product.
 hipError_t launch_kv_states_bf16(const Shape& s, const uint16_t* k, const uint16_t* v, const double* k_mean, float* k_stats,
-                                 float* partial, float* z_blocks, uint8_t* k_codes, float* k_scale, uint8_t* v_codes, float* v_scale,
-                                 const int32_t* block_idx, const GivenStates& gs, hipStream_t stream) {
+                                 float* partial, float* h_total, float* z_total, float* z_blocks, uint8_t* k_codes, float* k_scale,
+                                 uint8_t* v_codes, float* v_scale, const int32_t* block_idx, const GivenStates& gs, hipStream_t stream) {
   const int words = masked_words(kStateParts * s.Tn), len = s.d * s.d, tiles = (s.Tm + kMaskedRows - 1) / kMaskedRows;
   block_bits_kernel<<<dim3((unsigned)((s.Tm + 63) / 64), (unsigned)s.BH), 256, 64 * words * sizeof(uint32_t), stream>>>(   // at most 48 KB
       block_idx, gs.bits, s.Tm, s.Tn, s.k);
@@ -394,6 +395,7 @@ hipError_t launch_kv_states_bf16(const Shape& s, const uint16_t* k, const uint16
     else SLA2_KV(0);
 #undef SLA2_KV
     if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+    if (hipError_t e = launch_kv_total(s, heads, partial, h_total + (size_t)bh0 * len, z_total + (size_t)bh0 * s.d, nullptr, stream); e != hipSuccess) return e;
     block_states_bf16_kernel<<<dim3((unsigned)(heads * (len / kMaskedCols) * tiles)), 256, kMaskedLds, stream>>>(
         gs.states, gs.bits + (size_t)bh0 * words * masked_pitch(s.Tm), gs.h_i + (size_t)bh0 * s.Tm * len, s.Tm, s.Tn, len);
     if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
@@ -407,7 +409,7 @@ hipError_t launch_kv_states_bf16(const Shape& s, const uint16_t* k, const uint16
 // (33 MB for 12 heads of 32k tokens).
 // The h part of the partial sums lies as accumulator fragments (kv_state_bf16): [d/32 (c)][d/32 (e)][4][64 lanes][4],
 // lane l of part x holding rows c = 8 x + 4 (l / 32) + 0..3 of column e = l % 32; h_frag takes -h_total in the same order, which
-// is what the accumulators of the attention kernel start from.
+// is what the accumulators of the attention kernel start from (null where H_i is given to it).
 constexpr int kTotalWaves = 8;
 __global__ __launch_bounds__(64 * kTotalWaves) void kv_total_kernel(const float* __restrict__ partial, float* __restrict__ h_total,
                                                                     float* __restrict__ z_total, float* __restrict__ h_frag,
@@ -429,7 +431,7 @@ __global__ __launch_bounds__(64 * kTotalWaves) void kv_total_kernel(const float*
     if (e >= d * d) {
       *reinterpret_cast<f32x4*>(z_total + (size_t)bh * d + (e - d * d)) = s;
     } else {
-      *reinterpret_cast<f32x4*>(h_frag + (size_t)bh * d * d + e) = -s;
+      if (h_frag != nullptr) *reinterpret_cast<f32x4*>(h_frag + (size_t)bh * d * d + e) = -s;
       const int tile = e / 1024, x = e / 256 % 4, lane = e / 4 % 64;
       const int row = 32 * (tile / (d / 32)) + 8 * x + 4 * (lane / 32), col = 32 * (tile % (d / 32)) + lane % 32;
       for (int r = 0; r < 4; r++) h_total[((size_t)bh * d + row + r) * d + col] = s[r];
@@ -437,8 +439,9 @@ __global__ __launch_bounds__(64 * kTotalWaves) void kv_total_kernel(const float*
   }
 }
 
-hipError_t launch_kv_total(const Shape& s, const float* partial, float* h_total, float* z_total, float* h_frag, hipStream_t stream) {
-  const dim3 grid((unsigned)((s.d * s.d + s.d + 255) / 256), (unsigned)s.BH);
+hipError_t launch_kv_total(const Shape& s, int heads, const float* partial, float* h_total, float* z_total, float* h_frag,
+                           hipStream_t stream) {
+  const dim3 grid((unsigned)((s.d * s.d + s.d + 255) / 256), (unsigned)heads);
   kv_total_kernel<<<grid, 64 * kTotalWaves, 0, stream>>>(partial, h_total, z_total, h_frag, s.d, s.chunks);
   return hipGetLastError();
 }

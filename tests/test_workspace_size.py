@@ -11,3 +11,10 @@ def test_training_with_long_lists_keeps_H_i_once():
     L = api.sla2_workspace_layout(p)
     assert L.z_blocks == L.k_phi
     assert L.o_s - L.partial <= max(1200 * MB, 40 * 1182 * 128 * 128 * 2)
+
+
+def test_long_lists_keep_the_scratch_of_a_group_of_heads():
+    """80 heads of the same: H_i of all query blocks (1,478 MB), states of as many heads as fit 960 MB, their partial sums; the bits."""
+    p = api.make_params(2, 40, 75601, 128, 128, 64, 0.15, dtype=api.SLA2_BF16)
+    L = api.sla2_workspace_layout(p)
+    assert L.o_s - L.partial <= 80 * 591 * 128 * 128 * 2 + (960 + 60) * MB
