@@ -15,17 +15,33 @@ namespace sla2 {
 static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // bf16 tensors, d = 128, 128-row blocks: from which k on H_i is formed before the attention kernel (launch_kv_states_bf16: per key
-// block its states written and read, per pair of blocks 64 K products) rather than rebuilt in it (a third of its products per
-// selected pair, and 16 of 48 KB of its tiles).  Calls, us, rebuilt / formed before:
-//   8 heads of 75,600 tokens (T_n = 1,182)  bf16  k = 50 1,606 / 1,725   70 2,109 / 2,094   110 3,110 / 2,864
-//                                           FP8   k = 70 1,936 / 1,990   90 2,390 / 2,323   140 3,527 / 3,198
-//  12 heads of 32,760 (512)                 bf16  k = 30 660 / 725       50 979 / 960       90 1,601 / 1,439
-//                                           FP8   k = 50 913 / 941       70 1,189 / 1,152   90 1,466 / 1,342
-//  24 heads of 16,384 (256)                 bf16  k = 30 662 / 697       45 898 / 881       FP8  45 845 / 825
-//  48 heads of 4,096 (64)                   bf16  k = 36 384 / 401       60 567 / 532       FP8  44 426 / 425
-//  48 heads of 1,536 (24)                   bf16  k = 20 141 / 158
+// block its states written and read, per pair of blocks 96 K products) rather than rebuilt in it (a third of its products per
+// selected pair, and 16 of 48 KB of its tiles).  Between the two lies a k that grows with the work of the product per query
+// block: T_n, times what its workgroups of 128 query blocks by 256 entries do for nothing, in the last rows of a head and in
+// the last round of 512 (product_load).  The gain also takes an attention kernel that is short of matrix cores, three rounds of
+// workgroups; the 256 or 512 of a head or two wait for their tiles either way.  Calls, us, rebuilt / formed before:
+//   8 heads of 75,600 tokens (T_n = 1,182)  bf16  k = 80 2,392 / 2,535   100 2,907 / 2,937   120 3,414 / 3,331   150 4,208 / 3,924
+//     load 1.08, line at 116 (FP8 131)      FP8   k = 80 2,182 / 2,383   100 2,626 / 2,733   120 3,086 / 3,067   150 3,778 / 3,586
+//   4 heads, load 1.30, line at 129 (147)   bf16  k = 90 1,349 / 1,409   110 1,629 / 1,613   130 1,880 / 1,811
+//                                           FP8   k = 90 1,241 / 1,320   110 1,469 / 1,489   130 1,712 / 1,674   150 1,931 / 1,842
+//   4 heads of 128,000 (2,000), load 1.02   bf16  k = 120 2,972 / 3,081  150 3,632 / 3,584   FP8  150 3,250 / 3,301  180 3,826 / 3,795
+//  12 heads of 32,760 (512), load 1.00      bf16  k = 60 1,150 / 1,181   80 1,459 / 1,414    FP8  60 1,064 / 1,114   80 1,329 / 1,320
+//  12 heads of 19,200 (300), load 1.71      bf16  k = 60 718 / 748       75 869 / 881        90 1,021 / 976    FP8  75 798 / 857   90 931 / 930
+//  24 heads of 16,384 (256), load 1.00      bf16  k = 50 991 / 1,021     65 1,229 / 1,202    FP8  50 925 / 961       65 1,132 / 1,114
+//  48 heads of 8,192 (128), load 2.00       bf16  k = 55 1,067 / 1,080   65 1,225 / 1,206    FP8  55 999 / 1,014     65 1,134 / 1,111
+//  48 heads of 4,096 (64), load 4.00        bf16  k = 50 497 / 525       60 569 / 580        FP8  50 469 / 500       60 533 / 549
+// and too few workgroups:
+//   1 head of 75,600    bf16  k = 100 464 / 500  140 613 / 625  180 760 / 748     1 head of 32,760   bf16  k = 70 157 / 183  130 242 / 264
+//   2 heads of 32,760   bf16  k = 70 251 / 256   100 329 / 320   FP8 301 / 301    4 heads of 32,760  FP8   k = 90 507 / 525  110 602 / 601
+//   8 heads of 8,192    FP8   k = 65 215 / 219   100 294 / 282                   12 heads of 4,096   bf16  k = 45 154 / 162  60 186 / 186
 // 80 heads of 75,601 tokens, bf16, k = 177: 50.1 -> 43.9 ms.
-constexpr float kStatesFrom = 40.f, kStatesPerBf16 = 0.025f, kStatesPerLowBit = 0.034f;
+// Other head sizes and 64-row blocks rebuild it throughout: the path is built for the shape of the long workloads only.
+constexpr float kStatesFromBf16 = 52.f, kStatesPerBf16 = 0.05f, kStatesFromLowBit = 52.f, kStatesPerLowBit = 0.062f;
+constexpr int kRound = 512;               // workgroups that run at a time: two a CU
+static float product_load(const Shape& s, int heads) {
+  const int per_head = s.d * s.d / kMaskedCols * ((s.Tm + kMaskedRows - 1) / kMaskedRows), rounds = (heads * per_head + kRound - 1) / kRound;
+  return (float)rounds * kRound * kMaskedRows * kMaskedCols / ((float)heads * s.Tm * s.d * s.d);
+}
 // What the states of the heads that are worked on at a time may take: 8 heads of 1,182 key blocks (five whole rounds of the
 // product's workgroups), at the least one head.
 constexpr size_t kStateBytes = (size_t)960 << 20;
@@ -82,9 +98,11 @@ int make_shape(const sla2_params* p, Shape* s) {
   // largest number of chunks that still fits in one resident set.
   const int kResident = 512;
   s->state_heads = 0;
-  if (s->bf16 && s->d == 128 && s->bq == 128 && s->k > kStatesFrom + (s->quant ? kStatesPerLowBit : kStatesPerBf16) * s->Tn) {
+  if (s->bf16 && s->d == 128 && s->bq == 128 && (long long)s->BH * s->Tm >= 3 * kRound) {
     const size_t fit = kStateBytes / state_bytes(*s);
-    s->state_heads = fit < 1 ? 1 : fit > (size_t)s->BH ? s->BH : (int)fit;
+    const int heads = fit < 1 ? 1 : fit > (size_t)s->BH ? s->BH : (int)fit;
+    const float work = product_load(*s, heads) * s->Tn;
+    if (s->k > (s->quant ? kStatesFromLowBit + kStatesPerLowBit * work : kStatesFromBf16 + kStatesPerBf16 * work)) s->state_heads = heads;
   }
   int chunks_max = kResident / (s->state_heads ? s->state_heads : s->BH);
   if (chunks_max < 1) chunks_max = 1;
