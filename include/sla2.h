@@ -24,7 +24,8 @@
  *     return value is SLA2_OK (0) or a negative sla2_status; on an error no
  *     kernel has been launched (except SLA2_EHIP, which reports a failed
  *     launch).  No exceptions, no errno, no logging.
- *   - `workspace` must hold at least sla2_workspace_bytes(params) bytes and be
+ *   - `workspace` must hold at least sla2_workspace_bytes(params) bytes (for sla2_router and sla2_router_soft
+ *     those up to the doubles of sla2_ws_layout.partial are enough) and be
  *     256-byte aligned; its contents after a call are described by
  *     sla2_workspace_layout() and may be read by the caller (tests do).
  *     Calls that share a workspace must not overlap in time.
@@ -43,7 +44,8 @@ typedef enum {
   SLA2_OK = 0,
   SLA2_EINVAL = -1,       /* null pointer, non-positive size, topk_frac outside [0,1], bad enum */
   SLA2_EUNSUPPORTED = -2, /* a shape / mode combination the kernels do not cover (see sla2_params) */
-  SLA2_EWORKSPACE = -3,   /* workspace null, misaligned or smaller than sla2_workspace_bytes() */
+  SLA2_EWORKSPACE = -3,   /* workspace null, misaligned or smaller than sla2_workspace_bytes() (sla2_router, sla2_router_soft: than
+                             the part that they use) */
   SLA2_EALIAS = -4,       /* an output overlaps an input (or another output) */
   SLA2_EHIP = -5          /* a kernel launch failed */
 } sla2_status;

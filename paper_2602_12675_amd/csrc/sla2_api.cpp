@@ -222,10 +222,12 @@ static bool interleaved_disjoint(const Shape& s, const Strides& st, const void* 
   return r >= extent && r <= period - extent;
 }
 
-static int check_workspace(const sla2_ws_layout& L, const void* ws, size_t bytes) {
-  if (!ws || ((uintptr_t)ws & 255) || bytes < L.total) return SLA2_EWORKSPACE;
+static int check_workspace(size_t need, const void* ws, size_t bytes) {
+  if (!ws || ((uintptr_t)ws & 255) || bytes < need) return SLA2_EWORKSPACE;
   return SLA2_OK;
 }
+// What the router touches: all in front of `partial`, and there the pooled keys.
+static size_t router_bytes(const Shape& s, const sla2_ws_layout& L) { return L.partial + pooled_bytes(s); }
 
 template <class T>
 static T* at(void* ws, size_t off) { return (T*)((char*)ws + off); }
@@ -331,7 +333,7 @@ int sla2_router(const sla2_params* params, const void* q, const void* k, const f
   if (!q || !k || !router_w || (!block_idx && s.k > 0)) return SLA2_EINVAL;
   if (misaligned16(q) || misaligned16(k)) return SLA2_EINVAL;
   make_layout(s, &L);
-  if ((rc = check_workspace(L, workspace, workspace_bytes)) != SLA2_OK) return rc;
+  if ((rc = check_workspace(router_bytes(s, L), workspace, workspace_bytes)) != SLA2_OK) return rc;
   hipStream_t st = (hipStream_t)hip_stream;
   count_call();
   if ((rc = run_router(s, L, q, k, router_w, workspace, st)) != SLA2_OK) return rc;
@@ -351,7 +353,7 @@ int sla2_router_soft(const sla2_params* params, const void* q, const void* k, co
   if (!q || !k || !router_w || !mask_out || !(tau > 0.f)) return SLA2_EINVAL;
   if (misaligned16(q) || misaligned16(k)) return SLA2_EINVAL;
   make_layout(s, &L);
-  if ((rc = check_workspace(L, workspace, workspace_bytes)) != SLA2_OK) return rc;
+  if ((rc = check_workspace(router_bytes(s, L), workspace, workspace_bytes)) != SLA2_OK) return rc;
   hipStream_t st = (hipStream_t)hip_stream;
   count_call();
   if (SLA2_STAGE(SLA2_STAGE_BLOCK_SUMS, launch_block_sums(s, q, k, router_w, at<double>(workspace, L.q_sum),
@@ -378,7 +380,7 @@ int sla2_forward(const sla2_params* params, const void* q, const void* k, const 
       overlaps(out, out_bytes, v, in_bytes))
     return SLA2_EALIAS;
   make_layout(s, &L);
-  if ((rc = check_workspace(L, workspace, workspace_bytes)) != SLA2_OK) return rc;
+  if ((rc = check_workspace(L.total, workspace, workspace_bytes)) != SLA2_OK) return rc;
   hipStream_t st = (hipStream_t)hip_stream;
   count_call();
   if ((rc = run_router(s, L, q, k, router_w, workspace, st, v)) != SLA2_OK) return rc;
@@ -470,7 +472,7 @@ int sla2_backward(const sla2_params* params, const void* q, const void* k, const
   for (auto& pr : pairs)
     if (overlaps(pr[0], in_bytes, pr[1], in_bytes) && !interleaved_disjoint(s, s.sin, pr[0], pr[1])) return SLA2_EALIAS;
   make_layout(s, &L);
-  if ((rc = check_workspace(L, workspace, workspace_bytes)) != SLA2_OK) return rc;
+  if ((rc = check_workspace(L.total, workspace, workspace_bytes)) != SLA2_OK) return rc;
   const BwdLayout B = make_bwd_layout(s);
   char* bw = at<char>(workspace, L.bwd);
   BwdArgs a;

@@ -56,3 +56,27 @@ def test_router_equal_scores_at_the_edge(copies):
     rw = torch.eye(d, device="cuda").repeat(2, 1, 1)
     idx, kk = _route(q.round(), k, rw, d, 0.1)
     assert np.array_equal(idx, _expected(q.round(), k, rw, d, kk))
+
+
+@pytest.mark.parametrize("dtype", ["float32", "bfloat16"])
+def test_router_takes_the_part_of_the_workspace_that_it_uses(dtype):
+    """Up to the pooled keys in `partial`; what the forward pass puts behind them (fp32: the states of all key blocks) is not asked for."""
+    import torch
+    from paper_2602_12675_amd import api
+    B, H, N, d = 1, 3, 2048, 128
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    q, k = (torch.randn((B, H, N, d), generator=gen, device="cuda").to(getattr(torch, dtype)) for _ in range(2))
+    rw = torch.randn((2, d, d), generator=gen, device="cuda")
+    p = api.make_params(B, H, N, d, 128, 64, 0.25, dtype=api.SLA2_F32 if dtype == "float32" else api.SLA2_BF16)
+    whole = api.alloc_workspace(p)
+    need = api.sla2_workspace_layout(p).partial + B * H * (N // 64) * d * 8
+    idx, mask = [], []
+    for ws in (whole, whole[:need].clone()):
+        idx.append(torch.full((B, H, N // 128, 8), -1, dtype=torch.int32, device="cuda"))
+        mask.append(torch.zeros((B, H, N // 128, N // 64), device="cuda"))
+        api.sla2_router(p, q, k, rw, idx[-1], ws)
+        api.sla2_router_soft(p, q, k, rw, 0.1, mask[-1], ws)
+    assert torch.equal(idx[0], idx[1]) and torch.equal(mask[0], mask[1]) and int(idx[0].min()) >= 0
+    short = whole[:need - 1]
+    assert api.sla2_router(p, q, k, rw, idx[0], short, check=False) == api.SLA2_EWORKSPACE
+    assert api.sla2_router_soft(p, q, k, rw, 0.1, mask[0], short, check=False) == api.SLA2_EWORKSPACE
