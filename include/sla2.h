@@ -127,8 +127,9 @@ typedef struct sla2_ws_layout {
   size_t partial;   /* scratch.  double [BH, T_n, d], k_sum once more as the operand fragments of the router (written by the
                        pooling step, dead after the router).  bf16 path, in their place afterwards: the per-chunk partial sums of h
                        and z and, behind them, -h_total as accumulator fragments (where k_phi has 0 bytes: then H_i and what it
-                       is formed of); fp32 path, behind them: h_j, z_j of every key block
-                       and, without SLA2_FLAG_SAVE_FOR_BACKWARD, H_i, Z_i of every query block */
+                       is formed of); fp32 path, behind them: h_j, z_j of the key
+                       blocks and, without SLA2_FLAG_SAVE_FOR_BACKWARD, H_i, Z_i of the query blocks - of as many heads at a time
+                       as 256 MB hold.  sla2_backward: dH_j (and dZ_j) of every key block */
   /* with SLA2_FLAG_SAVE_FOR_BACKWARD only (0 bytes otherwise): */
   size_t o_s;       /* dtype  [BH, N, d]     sparse-branch output O^s, before the mix of Eq. 13   (input of Alg. 3) */
   size_t o_l;       /* dtype  [BH, N, d]     linear-branch output O^l (fp32 tensors only; 0 bytes for bf16 tensors, whose
@@ -251,7 +252,8 @@ typedef enum {
   SLA2_STAGE_KV_TOTAL = 3,    /* per-head totals of h and z; fp32 tensors: also H_i, Z_i of the query blocks (small
                                  calls: in the launch of SLA2_STAGE_ATTN); where k_phi has 0 bytes no launch of its own:
                                  SLA2_STAGE_KV_STATE has them, and H_i, a group of heads at a time */
-  SLA2_STAGE_ATTN = 4,        /* sparse + linear branch + mix              (Alg. 2 block loop, Eq. 13) */
+  SLA2_STAGE_ATTN = 4,        /* sparse + linear branch + mix              (Alg. 2 block loop, Eq. 13); fp32 tensors whose heads
+                                 are worked on in groups: with the two stages before it, which have no launches then */
   SLA2_STAGE_DENSE = 5,       /* dense attention comparator */
   SLA2_STAGE_BWD_LISTS = 6,   /* sla2_backward: the block mask as bits, per key block the list of its query blocks:
                                  the launch of SLA2_STAGE_BWD_Q, which makes them too */

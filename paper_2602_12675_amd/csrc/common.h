@@ -64,7 +64,8 @@ struct Shape {
   int quant;                                 // sla2_quant: 0 none, 1 FP8 e4m3, 2 INT8 codes of Q and K, 3 FP8 with V in e4m3 too
   // kv precompute: each workgroup reduces `blocks_per_chunk` key blocks; `chunks` per head
   int blocks_per_chunk, chunks;
-  // bf16 tensors, long lists: H_i formed before the attention kernel, the states of this many heads at a time (0: rebuilt there)
+  // the states of this many heads at a time.  bf16 tensors: long lists, H_i formed before the attention kernel (0: rebuilt there);
+  // fp32 tensors: always, the attention kernel with them
   int state_heads;
 };
 
@@ -175,26 +176,31 @@ hipError_t launch_block_sums(const Shape& s, const void* q, const void* k, const
                              double* k_sum, double* k_frag, double* router_m, hipStream_t stream);
 hipError_t launch_router_topk(const Shape& s, const double* q_sum, const double* k_frag, const double* router_m,
                               int32_t* block_idx, double* k_mean, hipStream_t stream);
-// fp32 tensors, where every workgroup finds a CU of its own (router_has_room): with it states [BH, T_n, d * d + d], h_j and z_j of every key block, and lnZ of every token; `states` may not
-// be where k_frag is
+// fp32 tensors, where every workgroup finds a CU of its own (router_has_room): with it states [BH, T_n, d * d + d], h_j and z_j of every
+// key block, and lnZ of every token; `states` may not be where k_frag is
 bool router_has_room(const Shape& s);
 hipError_t launch_router_topk_f32(const Shape& s, const double* q_sum, const double* k_frag, const double* router_m,
                                   int32_t* block_idx, double* k_mean, const float* k, const float* v, float* k_stats, float* states,
                                   hipStream_t stream);
 hipError_t launch_router_soft(const Shape& s, const double* q_sum, const double* k_frag, const double* router_m,
                               float* mask, double tau, hipStream_t stream);
-hipError_t launch_kv_state_f32(const Shape& s, const float* k, const float* v, const double* k_mean, float* k_stats,
-                               float* states, hipStream_t stream);
-// h_i [BH, T_m, d, d], z_i [BH, T_m, d]: the sums of the states over the key blocks that a query block did not select
-hipError_t launch_block_states_f32(const Shape& s, const float* states, const int32_t* block_idx, float* h_total, float* z_total,
-                                   float* h_i, float* z_i, hipStream_t stream);
+// The three steps of the fp32 forward pass behind the selection work on `heads` heads from bh0 on; states, h_i and z_i are of those
+// heads alone, everything else of all.
+struct HeadGroup {
+  int bh0, heads;
+};
+hipError_t launch_kv_state_f32(const Shape& s, const HeadGroup& hg, const float* k, const float* v, const double* k_mean,
+                               float* k_stats, float* states, hipStream_t stream);
+// h_i [heads, T_m, d, d], z_i [heads, T_m, d]: the sums of the states over the key blocks that a query block did not select
+hipError_t launch_block_states_f32(const Shape& s, const HeadGroup& hg, const float* states, const int32_t* block_idx, float* h_total,
+                                   float* z_total, float* h_i, float* z_i, hipStream_t stream);
 // the same on the key side of the backward pass: dH_j, dZ_j from dH_i, dZ_i of the query blocks that did not select j
 hipError_t launch_key_states_f32(const Shape& s, const BwdArgs& a, hipStream_t stream);
-// small calls: the attention kernel forms them (and the totals) itself, from the states
+// small calls: the attention kernel forms them (and the totals) itself, from the states; all heads are one group then
 bool attn_forms_states(const Shape& s);
-hipError_t launch_attn_f32(const Shape& s, const float* q, const float* k, const float* v, const double* k_mean, const float* states,
-                           float* h_i, float* z_i, float* h_total, float* z_total, const int32_t* block_idx, const float* alpha,
-                           float* out, float* lse, const SavedForBackward& sv, hipStream_t stream);
+hipError_t launch_attn_f32(const Shape& s, const HeadGroup& hg, const float* q, const float* k, const float* v, const double* k_mean,
+                           const float* states, float* h_i, float* z_i, float* h_total, float* z_total, const int32_t* block_idx,
+                           const float* alpha, float* out, float* lse, const SavedForBackward& sv, hipStream_t stream);
 
 hipError_t launch_kv_total(const Shape& s, int heads, const float* partial, float* h_total, float* z_total, float* h_frag, hipStream_t stream);
 hipError_t launch_kv_state_bf16(const Shape& s, const uint16_t* k, const uint16_t* v, const double* k_mean,

@@ -17,6 +17,7 @@ struct KvStateArgs {
   const float *k, *v;
   float *k_stats, *states;
   Strides sin;
+  int first;                              // block whose state is the first of `states`
 };
 template <int D> constexpr int kKvStateFloats = kF32Tokens * kF32Ld<D> + D;   // LDS
 
@@ -95,7 +96,7 @@ __device__ __forceinline__ void kv_state_f32_job(const KvStateArgs& a, const dou
 #pragma unroll
   for (int x = 0; x < SS::kTiles; x++) hacc[x] = zero16();
   sp.add(hacc, kp, w, lane);
-  float* ph = a.states + (size_t)block * f32_state(D);
+  float* ph = a.states + (size_t)(block - a.first) * f32_state(D);
   SP::store(hacc, 1.f, ph, w, lane);
   __syncthreads();                        // the tile fully consumed: its place takes the column sums
   *reinterpret_cast<f32x4*>(kp + trow * D + 4 * ch) = zacc;

@@ -42,11 +42,21 @@ static float product_load(const Shape& s, int heads) {
   const int per_head = s.d * s.d / kMaskedCols * ((s.Tm + kMaskedRows - 1) / kMaskedRows), rounds = (heads * per_head + kRound - 1) / kRound;
   return (float)rounds * kRound * kMaskedRows * kMaskedCols / ((float)heads * s.Tm * s.d * s.d);
 }
-// What the states of the heads that are worked on at a time may take: 8 heads of 1,182 key blocks (five whole rounds of the
-// product's workgroups), at the least one head.
+// What the states of the heads that are worked on at a time may take, at the least one head.  bf16 tensors: 8 heads of 1,182 key
+// blocks (five whole rounds of the product's workgroups).  fp32 tensors, with H_i: what the memory-side cache holds; all heads of
+// image-sized calls.  Forward, us, in groups of 128 MB / 256 MB / 512 MB / all heads at a time: 12 heads of 32,760 tokens 2,668 /
+// 2,588 / 2,577 / 2,542, 12 of 16,384 1,170 / 1,145 / 1,115 / 1,111, 10 of 75,600 10,873 / 10,278 / 10,137 / 10,602.
 constexpr size_t kStateBytes = (size_t)960 << 20;
+constexpr size_t kF32StateBytes = (size_t)256 << 20;
 
 static size_t state_bytes(const Shape& s) { return (size_t)s.Tn * kStateParts * s.d * s.d * 2; }   // bf16 parts of a head's h_j
+
+// fp32 tensors: entries of the key blocks' states of `heads` heads (a whole number of 256-byte units), and with them, unless `bwd`
+// keeps those, H_i, Z_i of their query blocks
+static size_t f32_states(const Shape& s, int heads) { return ((size_t)heads * s.Tn * (s.d * s.d + s.d) + 63) & ~(size_t)63; }
+static size_t f32_state_bytes(const Shape& s, int heads) {
+  return (f32_states(s, heads) + (s.save ? 0 : (size_t)heads * s.Tm * (s.d * s.d + s.d))) * sizeof(float);
+}
 
 // Validate everything that does not need pointers and derive the block counts.
 int make_shape(const sla2_params* p, Shape* s) {
@@ -104,6 +114,10 @@ int make_shape(const sla2_params* p, Shape* s) {
     const float work = product_load(*s, heads) * s->Tn;
     if (s->k > (s->quant ? kStatesFromLowBit + kStatesPerLowBit * work : kStatesFromBf16 + kStatesPerBf16 * work)) s->state_heads = heads;
   }
+  if (!s->bf16) {
+    const size_t fit = kF32StateBytes / f32_state_bytes(*s, 1);
+    s->state_heads = fit < 1 ? 1 : fit > (size_t)s->BH ? s->BH : (int)fit;
+  }
   int chunks_max = kResident / (s->state_heads ? s->state_heads : s->BH);
   if (chunks_max < 1) chunks_max = 1;
   int bpc = (s->Tn + chunks_max - 1) / chunks_max;
@@ -115,7 +129,7 @@ int make_shape(const sla2_params* p, Shape* s) {
 
 // scratch of the backward pass, carved out of the `bwd` region of the workspace
 struct BwdLayout {
-  size_t ds, dh, dz, dh_total, dz_total, colsum, dk_mean, dalpha_part, col_ptr, col_idx, col_cnt, col_bits, dh_sum, dz_sum, inv_den, dl, order, h_i, z_i, lraw, total;
+  size_t ds, dh, dz, dh_total, dz_total, colsum, dk_mean, dalpha_part, col_ptr, col_idx, col_cnt, col_bits, inv_den, dl, order, h_i, z_i, lraw, total;
 };
 static BwdLayout make_bwd_layout(const Shape& s) {
   BwdLayout B;
@@ -134,8 +148,6 @@ static BwdLayout make_bwd_layout(const Shape& s) {
   B.col_idx = take(BH * s.Tm * (size_t)(s.k > 0 ? s.k : 1) * sizeof(int32_t));
   B.col_cnt = take(BH * (size_t)s.Tn * sizeof(int32_t));
   B.col_bits = take(s.bf16 ? BH * masked_words(s.Tm) * masked_pitch(s.Tn) * sizeof(uint32_t) : 0);
-  B.dh_sum = take(BH * (size_t)s.Tn * d * d * esz);
-  B.dz_sum = take(s.bf16 ? 0 : BH * (size_t)s.Tn * d * sizeof(float));
   B.inv_den = take(s.bf16 ? 0 : slots * s.bq * sizeof(float));
   B.dl = take(s.bf16 ? 0 : slots * s.bq * sizeof(float));
   B.order = take(bwd_kv_grid(s) * sizeof(int32_t));
@@ -148,9 +160,6 @@ static BwdLayout make_bwd_layout(const Shape& s) {
 static size_t bwd_scratch_bytes(const Shape& s) { return make_bwd_layout(s).total; }
 
 static size_t pooled_bytes(const Shape& s) { return align256((size_t)s.BH * s.Tn * s.d * sizeof(double)); }
-// fp32 tensors: entries of the key blocks' states (a whole number of 256-byte units)
-static size_t f32_states(const Shape& s) { return ((size_t)s.BH * s.Tn * (s.d * s.d + s.d) + 63) & ~(size_t)63; }
-
 // bf16 tensors: per chunk of key blocks the partial sums of h and z, then -h_total as fragments; with state_heads the
 // partial sums of those heads alone
 static size_t partial_bytes(const Shape& s) {
@@ -163,6 +172,9 @@ static size_t given_states(const Shape& s) { return align256(s.state_heads * sta
 static size_t given_bytes(const Shape& s) {
   return s.state_heads == 0 ? 0 : given_h(s) + given_states(s) + (size_t)s.BH * masked_words(kStateParts * s.Tn) * masked_pitch(s.Tm) * sizeof(uint32_t);
 }
+
+// entries of dH_j of all key blocks and, fp32 tensors, dZ_j behind them
+static size_t key_states(const Shape& s) { return (size_t)s.BH * s.Tn * s.d * (s.bf16 ? s.d : s.d + 1); }
 
 void make_layout(const Shape& s, sla2_ws_layout* L) {
   size_t off = 0, BH = (size_t)s.BH, d = (size_t)s.d;
@@ -183,11 +195,13 @@ void make_layout(const Shape& s, sla2_ws_layout* L) {
   L->v_scale = take(s.quant == 3 ? BH * (size_t)s.Tn * sizeof(float) : 0);
   // bf16, two lives: the pooled keys as fragments, for the router; then the partial sums, -h_total as fragments behind them
   // and, with state_heads, H_i and what it is formed of.
-  // fp32: the pooled keys, the states of all key blocks and, unless `bwd` keeps them, H_i, Z_i of the query blocks
-  const size_t state = d * d + d, pooled = pooled_bytes(s), sums = partial_bytes(s) + given_bytes(s);
-  if (s.bf16) L->partial = take(sums > pooled ? sums : pooled);
-  else L->partial = take(pooled + (f32_states(s) + (s.save ? 0 : BH * s.Tm * state)) * sizeof(float));
-  const size_t esz = s.bf16 ? 2 : 4;
+  // fp32: the pooled keys, the states of the key blocks and, unless `bwd` keeps them, H_i, Z_i of the query blocks.
+  // Backward pass: dH_j of all key blocks, fp32 with dZ_j behind them
+  const size_t esz = s.bf16 ? 2 : 4, pooled = pooled_bytes(s);
+  size_t scratch = s.bf16 ? partial_bytes(s) + given_bytes(s) : pooled + f32_state_bytes(s, s.state_heads);
+  for (size_t other : {pooled, s.save ? key_states(s) * esz : 0})
+    if (other > scratch) scratch = other;
+  L->partial = take(scratch);
   L->o_s = take(s.save ? BH * (size_t)s.N * d * esz : 0);
   L->o_l = take(s.save && !s.bf16 ? BH * (size_t)s.N * d * esz : 0);   // bf16 tensors: rebuilt from H_i in the backward pass
   L->lse = take(s.save ? BH * (size_t)s.N * sizeof(float) : 0);
@@ -403,21 +417,38 @@ int sla2_forward(const sla2_params* params, const void* q, const void* k, const 
   float* partial = at<float>(workspace, L.partial);
   if (!s.bf16) {
     float* states = f32_states_at(s, L, workspace);
-    float* h_i = s.save ? (float*)sv.h_i : states + f32_states(s);
-    float* z_i = s.save ? sv.z_i : h_i + (size_t)s.BH * s.Tm * s.d * s.d;
-    if (!router_has_room(s) &&
-        SLA2_STAGE(SLA2_STAGE_KV_STATE, launch_kv_state_f32(s, (const float*)k, (const float*)v, k_mean, at<float>(workspace, L.k_stats),
-                                                            states, st)) != hipSuccess)
-      return SLA2_EHIP;
-    auto attn = [&]() {
-      return launch_attn_f32(s, (const float*)q, (const float*)k, (const float*)v, k_mean, states, h_i, z_i, h_total, z_total, idx,
-                             alpha, (float*)out, lse_or_null, sv, st);
+    const size_t state = (size_t)s.d * s.d;
+    // H_i, Z_i of the heads from bh0 on
+    auto h_i = [&](int bh0) { return s.save ? (float*)sv.h_i + bh0 * s.Tm * state : states + f32_states(s, s.state_heads); };
+    auto z_i = [&](int bh0) { return s.save ? sv.z_i + (size_t)bh0 * s.Tm * s.d : h_i(0) + s.state_heads * s.Tm * state; };
+    auto kv_state = [&](const HeadGroup& hg) {
+      return launch_kv_state_f32(s, hg, (const float*)k, (const float*)v, k_mean, at<float>(workspace, L.k_stats), states, st);
     };
+    auto sums = [&](const HeadGroup& hg) {
+      return launch_block_states_f32(s, hg, states, idx, h_total, z_total, h_i(hg.bh0), z_i(hg.bh0), st);
+    };
+    auto attn = [&](const HeadGroup& hg) {
+      return launch_attn_f32(s, hg, (const float*)q, (const float*)k, (const float*)v, k_mean, states, h_i(hg.bh0), z_i(hg.bh0), h_total,
+                             z_total, idx, alpha, (float*)out, lse_or_null, sv, st);
+    };
+    if (s.state_heads < s.BH) {
+      auto groups = [&]() {
+        for (int bh0 = 0; bh0 < s.BH; bh0 += s.state_heads) {
+          const HeadGroup hg{bh0, s.BH - bh0 < s.state_heads ? s.BH - bh0 : s.state_heads};
+          if (hipError_t e = kv_state(hg); e != hipSuccess) return e;
+          if (hipError_t e = sums(hg); e != hipSuccess) return e;
+          if (hipError_t e = attn(hg); e != hipSuccess) return e;
+        }
+        return hipSuccess;
+      };
+      return SLA2_STAGE(SLA2_STAGE_ATTN, groups()) != hipSuccess ? SLA2_EHIP : SLA2_OK;
+    }
+    const HeadGroup all{0, s.BH};
+    if (!router_has_room(s) && SLA2_STAGE(SLA2_STAGE_KV_STATE, kv_state(all)) != hipSuccess) return SLA2_EHIP;
     if (attn_forms_states(s))
-      return SLA2_STAGE(SLA2_STAGE_KV_TOTAL, SLA2_STAGE(SLA2_STAGE_ATTN, attn())) != hipSuccess ? SLA2_EHIP : SLA2_OK;
-    if (SLA2_STAGE(SLA2_STAGE_KV_TOTAL, launch_block_states_f32(s, states, idx, h_total, z_total, h_i, z_i, st)) != hipSuccess)
-      return SLA2_EHIP;
-    return SLA2_STAGE(SLA2_STAGE_ATTN, attn()) != hipSuccess ? SLA2_EHIP : SLA2_OK;
+      return SLA2_STAGE(SLA2_STAGE_KV_TOTAL, SLA2_STAGE(SLA2_STAGE_ATTN, attn(all))) != hipSuccess ? SLA2_EHIP : SLA2_OK;
+    if (SLA2_STAGE(SLA2_STAGE_KV_TOTAL, sums(all)) != hipSuccess) return SLA2_EHIP;
+    return SLA2_STAGE(SLA2_STAGE_ATTN, attn(all)) != hipSuccess ? SLA2_EHIP : SLA2_OK;
   }
   float* k_stats = at<float>(workspace, L.k_stats);
   float* h_frag = s.state_heads ? nullptr : partial + (size_t)s.BH * s.chunks * (s.d * s.d + s.d);
@@ -490,8 +521,10 @@ int sla2_backward(const sla2_params* params, const void* q, const void* k, const
   a.colsum = (float*)(bw + B.colsum); a.dk_mean = (float*)(bw + B.dk_mean);
   a.dalpha_part = (float*)(bw + B.dalpha_part);
   a.col_ptr = (int32_t*)(bw + B.col_ptr); a.col_idx = (int32_t*)(bw + B.col_idx);
-  a.col_bits = (uint32_t*)(bw + B.col_bits); a.dh_sum = (void*)(bw + B.dh_sum);
-  a.dz_sum = (float*)(bw + B.dz_sum); a.inv_den = (float*)(bw + B.inv_den); a.dl = (float*)(bw + B.dl);
+  a.col_bits = (uint32_t*)(bw + B.col_bits);
+  a.dh_sum = at<void>(workspace, L.partial);
+  a.dz_sum = s.bf16 ? nullptr : (float*)a.dh_sum + (size_t)s.BH * s.Tn * s.d * s.d;
+  a.inv_den = (float*)(bw + B.inv_den); a.dl = (float*)(bw + B.dl);
   a.col_cnt = (int32_t*)(bw + B.col_cnt); a.order = (int32_t*)(bw + B.order);
   hipStream_t st = (hipStream_t)hip_stream;
   count_call();

@@ -12,20 +12,20 @@ namespace sla2 {
 template <int D>
 __global__ __launch_bounds__(256, 4) void kv_state_f32_kernel(const KvStateArgs a, const double* __restrict__ k_mean, int H, int N, int Tn) {
   extern __shared__ __attribute__((aligned(16))) float smem[];
-  kv_state_f32_job<D, false>(a, k_mean, smem, blockIdx.x, threadIdx.x, H, N, Tn, 1);
+  kv_state_f32_job<D, false>(a, k_mean, smem, a.first + (int)blockIdx.x, threadIdx.x, H, N, Tn, 1);
 }
 template <int D>
-static hipError_t launch_kv_state_f32_t(const Shape& s, const KvStateArgs& a, const double* k_mean, hipStream_t stream) {
+static hipError_t launch_kv_state_f32_t(const Shape& s, int heads, const KvStateArgs& a, const double* k_mean, hipStream_t stream) {
   constexpr int smem = kKvStateFloats<D> * (int)sizeof(float);
   static OncePerDevice once;
   if (hipError_t e = allow_dynamic_lds(once, (const void*)kv_state_f32_kernel<D>, smem); e != hipSuccess) return e;
-  kv_state_f32_kernel<D><<<dim3((unsigned)(s.BH * s.Tn)), 256, smem, stream>>>(a, k_mean, s.H, s.N, s.Tn);
+  kv_state_f32_kernel<D><<<dim3((unsigned)(heads * s.Tn)), 256, smem, stream>>>(a, k_mean, s.H, s.N, s.Tn);
   return hipGetLastError();
 }
-hipError_t launch_kv_state_f32(const Shape& s, const float* k, const float* v, const double* k_mean, float* k_stats,
-                               float* states, hipStream_t stream) {
-  const KvStateArgs a{k, v, k_stats, states, s.sin};
-  return s.d == 128 ? launch_kv_state_f32_t<128>(s, a, k_mean, stream) : launch_kv_state_f32_t<64>(s, a, k_mean, stream);
+hipError_t launch_kv_state_f32(const Shape& s, const HeadGroup& hg, const float* k, const float* v, const double* k_mean,
+                               float* k_stats, float* states, hipStream_t stream) {
+  const KvStateArgs a{k, v, k_stats, states, s.sin, hg.bh0 * s.Tn};
+  return s.d == 128 ? launch_kv_state_f32_t<128>(s, hg.heads, a, k_mean, stream) : launch_kv_state_f32_t<64>(s, hg.heads, a, k_mean, stream);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -154,30 +154,32 @@ __global__ __launch_bounds__(256) void gather_states_f32_kernel(const float* __r
 //    2 heads, T_n = 1,182  k = 9 491 / 160  k = 31 488 / 388   k = 59 507 / 679
 constexpr int kGatherBlocks = 64, kGatherRatio = 30;
 template <int D>
-static hipError_t launch_states_f32(const Shape& s, const float* states, const BlockLists& lists, const StateSums& out, hipStream_t stream) {
+static hipError_t launch_states_f32(const Shape& s, int heads, const float* states, const BlockLists& lists, const StateSums& out, hipStream_t stream) {
   constexpr int P = f32_state(D), kSets = (P + 4 * kStateCols - 1) / (4 * kStateCols);
-  const int sets = (s.BH * kSets + kXcds - 1) / kXcds * kXcds;
+  const int sets = (heads * kSets + kXcds - 1) / kXcds * kXcds;
   if (s.Tn <= kGatherBlocks || s.Tn <= kGatherRatio * s.k) {
     const int tiles = (lists.R + 31) / 32, smem = (lists.S + 31) / 32 * 32 * (int)sizeof(uint32_t);   // at most 8 KB
-    masked_states_f32_kernel<D, false><<<dim3((unsigned)(sets * tiles)), 256, smem, stream>>>(states, lists, out, s.BH, tiles);
+    masked_states_f32_kernel<D, false><<<dim3((unsigned)(sets * tiles)), 256, smem, stream>>>(states, lists, out, heads, tiles);
     return hipGetLastError();
   }
-  masked_states_f32_kernel<D, true><<<dim3((unsigned)sets), 256, 0, stream>>>(states, lists, out, s.BH, 1);
+  masked_states_f32_kernel<D, true><<<dim3((unsigned)sets), 256, 0, stream>>>(states, lists, out, heads, 1);
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
-  gather_states_f32_kernel<D><<<dim3((unsigned)((size_t)s.BH * lists.R * ((P + 1023) / 1024))), 256, 0, stream>>>(states, lists, out);
+  gather_states_f32_kernel<D><<<dim3((unsigned)((size_t)heads * lists.R * ((P + 1023) / 1024))), 256, 0, stream>>>(states, lists, out);
   return hipGetLastError();
 }
-hipError_t launch_block_states_f32(const Shape& s, const float* states, const int32_t* block_idx, float* h_total, float* z_total,
-                                   float* h_i, float* z_i, hipStream_t stream) {
-  const BlockLists lists{nullptr, block_idx, s.Tm, s.Tn, s.k};
-  const StateSums out{h_i, z_i, h_total, z_total};
-  return s.d == 128 ? launch_states_f32<128>(s, states, lists, out, stream) : launch_states_f32<64>(s, states, lists, out, stream);
+hipError_t launch_block_states_f32(const Shape& s, const HeadGroup& hg, const float* states, const int32_t* block_idx, float* h_total,
+                                   float* z_total, float* h_i, float* z_i, hipStream_t stream) {
+  const size_t b = hg.bh0;
+  const BlockLists lists{nullptr, block_idx + b * s.Tm * s.k, s.Tm, s.Tn, s.k};
+  const StateSums out{h_i, z_i, h_total + b * s.d * s.d, z_total + b * s.d};
+  return s.d == 128 ? launch_states_f32<128>(s, hg.heads, states, lists, out, stream)
+                    : launch_states_f32<64>(s, hg.heads, states, lists, out, stream);
 }
 hipError_t launch_key_states_f32(const Shape& s, const BwdArgs& a, hipStream_t stream) {
   const BlockLists lists{a.col_ptr, a.col_idx, s.Tn, s.Tm, s.k};
   const StateSums out{(float*)a.dh_sum, a.dz_sum, a.dh_total, a.dz_total};
-  return s.d == 128 ? launch_states_f32<128>(s, (const float*)a.dh, lists, out, stream)
-                    : launch_states_f32<64>(s, (const float*)a.dh, lists, out, stream);
+  return s.d == 128 ? launch_states_f32<128>(s, s.BH, (const float*)a.dh, lists, out, stream)
+                    : launch_states_f32<64>(s, s.BH, (const float*)a.dh, lists, out, stream);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -266,7 +268,7 @@ __global__ __launch_bounds__(256, 2) void attn_f32_kernel(
     const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v, const double* __restrict__ k_mean,
     const float* __restrict__ h_i, const float* __restrict__ z_i, const int32_t* __restrict__ block_idx,
     const float* __restrict__ alpha, float* __restrict__ out, float* __restrict__ lse, float* __restrict__ o_s_save,
-    float* __restrict__ o_l_save, float* __restrict__ lse_save, Strides sin, Strides sout, int BH, int H, int N, int Tm, int Tn, int bq,
+    float* __restrict__ o_l_save, float* __restrict__ lse_save, Strides sin, Strides sout, HeadGroup hg, int H, int N, int Tm, int Tn, int bq,
     int ksel, int alpha_per_block, const OwnStates own) {
   typedef AttnF32Smem<D> SM;
   constexpr int LD = SM::LD, ET = SM::ET, J = D / 8, NW = SM::NW;
@@ -278,17 +280,17 @@ __global__ __launch_bounds__(256, 2) void attn_f32_kernel(
   float* swap = smem + SM::kSwapOff;
 
   // All row groups in runs of consecutive ones, one run per XCD: what runs there at a time gathers from a head or two
-  const int groups = (N + 31) / 32, all = BH * groups, run = (all + kXcds - 1) / kXcds;
+  const int groups = (N + 31) / 32, all = hg.heads * groups, run = (all + kXcds - 1) / kXcds;
   const int at = blockIdx.x % kXcds * run + blockIdx.x / kXcds;
   if (at >= all) return;
-  const int bh = at / groups, grp = at % groups, h = bh % H;
+  const int bh = hg.bh0 + at / groups, grp = at % groups, h = bh % H;
   const int row0 = 32 * grp, rows_valid = min(32, N - row0), i = row0 / bq;
   const int tid = threadIdx.x, lane = tid % kWave, g = lane / 32, r = lane % 32;
   const int w = __builtin_amdgcn_readfirstlane(tid / kWave);
-  const size_t slot = (size_t)bh * Tm + i;
+  const size_t slot = (size_t)(at / groups) * Tm + i;    // of H_i, Z_i
   const float* kh = k + head_offset(sin, bh, H);
   const float* vh = v + head_offset(sin, bh, H);
-  const int32_t* sel = block_idx + slot * ksel;
+  const int32_t* sel = block_idx + ((size_t)bh * Tm + i) * ksel;
 
   const int items = 2 * ksel;             // halves of the selected blocks; an odd one of the last block may hold no key
   auto first_key = [&](int t) { return __builtin_amdgcn_readfirstlane(sel[t / 2]) * kF32Tokens + 32 * (t % 2); };
@@ -494,24 +496,24 @@ __global__ __launch_bounds__(256, 2) void attn_f32_kernel(
 bool attn_forms_states(const Shape& s) { return s.d == 64 && s.Tn <= kOwnBlocks && router_has_room(s); }
 
 template <int D, bool OWN>
-static hipError_t launch_attn_f32_t(const Shape& s, const float* q, const float* k, const float* v, const double* k_mean,
+static hipError_t launch_attn_f32_t(const Shape& s, const HeadGroup& hg, const float* q, const float* k, const float* v, const double* k_mean,
                                     const float* h_i, const float* z_i, const int32_t* block_idx, const float* alpha, float* out,
                                     float* lse, const SavedForBackward& sv, const OwnStates& own, hipStream_t stream) {
   constexpr int smem = AttnF32Smem<D>::kBytes + (OWN ? D * kOwnLd * (int)sizeof(float) : 0);
   static OncePerDevice once;
   if (hipError_t e = allow_dynamic_lds(once, (const void*)attn_f32_kernel<D, OWN>, smem); e != hipSuccess) return e;
-  const int run = (s.BH * ((s.N + 31) / 32) + kXcds - 1) / kXcds;
+  const int run = (hg.heads * ((s.N + 31) / 32) + kXcds - 1) / kXcds;
   attn_f32_kernel<D, OWN><<<dim3((unsigned)(run * kXcds)), 256, smem, stream>>>(
-      q, k, v, k_mean, h_i, z_i, block_idx, alpha, out, lse, (float*)sv.o_s, (float*)sv.o_l, sv.lse, s.sin, s.sout, s.BH, s.H, s.N, s.Tm,
+      q, k, v, k_mean, h_i, z_i, block_idx, alpha, out, lse, (float*)sv.o_s, (float*)sv.o_l, sv.lse, s.sin, s.sout, hg, s.H, s.N, s.Tm,
       s.Tn, s.bq, s.k, s.alpha_per_block ? 1 : 0, own);
   return hipGetLastError();
 }
 
-hipError_t launch_attn_f32(const Shape& s, const float* q, const float* k, const float* v, const double* k_mean, const float* states,
-                           float* h_i, float* z_i, float* h_total, float* z_total, const int32_t* block_idx, const float* alpha,
-                           float* out, float* lse, const SavedForBackward& sv, hipStream_t stream) {
+hipError_t launch_attn_f32(const Shape& s, const HeadGroup& hg, const float* q, const float* k, const float* v, const double* k_mean,
+                           const float* states, float* h_i, float* z_i, float* h_total, float* z_total, const int32_t* block_idx,
+                           const float* alpha, float* out, float* lse, const SavedForBackward& sv, hipStream_t stream) {
   const OwnStates own{states, s.save ? h_i : nullptr, s.save ? z_i : nullptr, h_total, z_total};
-#define SLA2_ATTN(DD, OO) launch_attn_f32_t<DD, OO>(s, q, k, v, k_mean, h_i, z_i, block_idx, alpha, out, lse, sv, own, stream)
+#define SLA2_ATTN(DD, OO) launch_attn_f32_t<DD, OO>(s, hg, q, k, v, k_mean, h_i, z_i, block_idx, alpha, out, lse, sv, own, stream)
   if (attn_forms_states(s)) return SLA2_ATTN(64, true);
   return s.d == 128 ? SLA2_ATTN(128, false) : SLA2_ATTN(64, false);
 #undef SLA2_ATTN

@@ -242,7 +242,7 @@ bool router_has_room(const Shape& s) {
 hipError_t launch_router_topk_f32(const Shape& s, const double* q_sum, const double* k_frag, const double* router_m,
                                   int32_t* block_idx, double* k_mean, const float* k, const float* v, float* k_stats, float* states,
                                   hipStream_t stream) {
-  return launch_topk_class<true>(s, q_sum, k_frag, router_m, block_idx, k_mean, KvStateArgs{k, v, k_stats, states, s.sin}, stream);
+  return launch_topk_class<true>(s, q_sum, k_frag, router_m, block_idx, k_mean, KvStateArgs{k, v, k_stats, states, s.sin, 0}, stream);
 }
 
 }  // namespace sla2

@@ -25,3 +25,17 @@ def test_heads_that_do_not_fill_the_gpu_rebuild_the_states():
     for H, ahead in ((1, False), (12, True)):
         L = api.sla2_workspace_layout(api.make_params(1, H, 32760, 128, 128, 64, (70 if H == 1 else 80) / 512, dtype=api.SLA2_BF16))
         assert (L.z_blocks == L.k_phi) == ahead
+
+
+def test_fp32_states_of_a_group_of_heads():
+    """fp32 tensors: h_j and H_i of as many heads as fit 256 MB; the rest of a forward call's workspace is less than a byte an
+    element of K (42 MB on 12 heads of 32,760 tokens, 133 on 40 of 75,600).  Training adds dH_j of all key blocks, 64 KB each at d = 128."""
+    for H, N in ((12, 32760), (40, 75600)):
+        T_n, T_m = -(-N // 64), -(-N // 128)
+        forward = api.sla2_workspace_bytes(api.make_params(1, H, N, 128, 128, 64, 0.03, dtype=api.SLA2_F32))
+        assert forward <= 256 * MB + H * N * 128
+        p = api.make_params(1, H, N, 128, 128, 64, 0.03, dtype=api.SLA2_F32, flags=api.SLA2_FLAG_SAVE_FOR_BACKWARD)
+        L = api.sla2_workspace_layout(p)
+        state = 4 * (128 * 128 + 128)
+        assert L.o_s - L.partial <= max(256 * MB, H * T_n * state) + 8 * H * T_n * 128
+        assert L.total - L.bwd <= H * T_m * (2 * state + 128 * 32) + H * T_n * 4096    # dH_i, H_i; rows, lists and sums
