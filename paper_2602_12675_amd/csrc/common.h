@@ -129,7 +129,7 @@ struct BwdArgs {
   const void *q, *k, *v, *dout, *o_s, *o_l;
   const float* lse;
   const double* k_mean;
-  const float *k_stats, *h_total, *z_total;
+  const float* k_stats;
   const int32_t* block_idx;
   const float* alpha;
   void *dq, *dk, *dv;

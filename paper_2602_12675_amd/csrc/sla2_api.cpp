@@ -511,7 +511,6 @@ int sla2_backward(const sla2_params* params, const void* q, const void* k, const
   a.o_s = at<void>(workspace, L.o_s); a.o_l = at<void>(workspace, L.o_l); a.lse = at<float>(workspace, L.lse);
   a.k_mean = at<double>(workspace, L.k_mean);
   a.k_stats = at<float>(workspace, L.k_stats);
-  a.h_total = at<float>(workspace, L.h_total); a.z_total = at<float>(workspace, L.z_total);
   a.block_idx = at<int32_t>(workspace, L.block_idx);
   a.alpha = alpha;
   a.dq = dq; a.dk = dk; a.dv = dv; a.dalpha = dalpha;

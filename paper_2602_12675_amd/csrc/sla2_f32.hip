@@ -49,7 +49,7 @@ struct BlockLists {
     return ptr ? ptr[(size_t)bh * (R + 1) + r + 1] - ptr[(size_t)bh * (R + 1) + r] : k;
   }
 };
-// sums: h [R][d * d] and z [R][d] per head; totals likewise with R = 1
+// sums: h [R][d * d] and z [R][d] per head; totals likewise with R = 1 (null: not wanted)
 struct StateSums {
   float *h, *z, *h_total, *z_total;
 };
@@ -89,6 +89,7 @@ __global__ __launch_bounds__(256, 2) void masked_states_f32_kernel(const float* 
 #pragma unroll
   for (int x = 0; x < 4; x++) acc[x] = zero16();
   f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+  const bool total = tile == 0 && out.h_total != nullptr;
   for (int sw = 0; sw < W; sw++) {
     const uint32_t word = TOTALS_ONLY ? 0u : bits[32 * sw + lane % 32];
     if (sw > 0) {
@@ -102,7 +103,7 @@ __global__ __launch_bounds__(256, 2) void masked_states_f32_kernel(const float* 
         for (int n = 8 * half; n < 8 * half + 8; n++) {
           const bool exists = 32 * sw + 2 * n + g < S;
           if (!exists) b[n] = f32x4{0.f, 0.f, 0.f, 0.f};   // (0 times an infinite entry is NaN)
-          if (tile == 0) sum += b[n];
+          if (total) sum += b[n];
           if constexpr (!TOTALS_ONLY) {
             const float a = (word >> (2 * n + g) & 1u) == 0u ? 1.f : 0.f;
 #pragma unroll
@@ -113,7 +114,7 @@ __global__ __launch_bounds__(256, 2) void masked_states_f32_kernel(const float* 
     }
   }
   if (col >= P) return;
-  if (tile == 0) {
+  if (total) {
 #pragma unroll
     for (int x = 0; x < 4; x++) sum[x] = both_halves_sum(sum[x]);
     if (g == 0) *reinterpret_cast<f32x4*>(col < D * D ? out.h_total + (size_t)bh * D * D + col : out.z_total + (size_t)bh * D + (col - D * D)) = sum;
@@ -154,10 +155,12 @@ __global__ __launch_bounds__(256) void gather_states_f32_kernel(const float* __r
 //    2 heads, T_n = 1,182  k = 9 491 / 160  k = 31 488 / 388   k = 59 507 / 679
 constexpr int kGatherBlocks = 64, kGatherRatio = 30;
 template <int D>
-static hipError_t launch_states_f32(const Shape& s, int heads, const float* states, const BlockLists& lists, const StateSums& out, hipStream_t stream) {
+static hipError_t launch_states_f32(const Shape& s, int heads, const float* states, const BlockLists& lists, StateSums out, bool totals,
+                                    hipStream_t stream) {
   constexpr int P = f32_state(D), kSets = (P + 4 * kStateCols - 1) / (4 * kStateCols);
   const int sets = (heads * kSets + kXcds - 1) / kXcds * kXcds;
   if (s.Tn <= kGatherBlocks || s.Tn <= kGatherRatio * s.k) {
+    if (!totals) out.h_total = out.z_total = nullptr;
     const int tiles = (lists.R + 31) / 32, smem = (lists.S + 31) / 32 * 32 * (int)sizeof(uint32_t);   // at most 8 KB
     masked_states_f32_kernel<D, false><<<dim3((unsigned)(sets * tiles)), 256, smem, stream>>>(states, lists, out, heads, tiles);
     return hipGetLastError();
@@ -172,14 +175,14 @@ hipError_t launch_block_states_f32(const Shape& s, const HeadGroup& hg, const fl
   const size_t b = hg.bh0;
   const BlockLists lists{nullptr, block_idx + b * s.Tm * s.k, s.Tm, s.Tn, s.k};
   const StateSums out{h_i, z_i, h_total + b * s.d * s.d, z_total + b * s.d};
-  return s.d == 128 ? launch_states_f32<128>(s, hg.heads, states, lists, out, stream)
-                    : launch_states_f32<64>(s, hg.heads, states, lists, out, stream);
+  return s.d == 128 ? launch_states_f32<128>(s, hg.heads, states, lists, out, true, stream)
+                    : launch_states_f32<64>(s, hg.heads, states, lists, out, true, stream);
 }
 hipError_t launch_key_states_f32(const Shape& s, const BwdArgs& a, hipStream_t stream) {
   const BlockLists lists{a.col_ptr, a.col_idx, s.Tn, s.Tm, s.k};
   const StateSums out{(float*)a.dh_sum, a.dz_sum, a.dh_total, a.dz_total};
-  return s.d == 128 ? launch_states_f32<128>(s, s.BH, (const float*)a.dh, lists, out, stream)
-                    : launch_states_f32<64>(s, s.BH, (const float*)a.dh, lists, out, stream);
+  return s.d == 128 ? launch_states_f32<128>(s, s.BH, (const float*)a.dh, lists, out, false, stream)
+                    : launch_states_f32<64>(s, s.BH, (const float*)a.dh, lists, out, false, stream);
 }
 
 // ---------------------------------------------------------------------------------------------
