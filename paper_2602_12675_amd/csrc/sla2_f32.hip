@@ -148,18 +148,29 @@ __global__ __launch_bounds__(256) void gather_states_f32_kernel(const float* __r
 }
 
 // The product costs S per sum whatever is listed, the gather the length of the list, and a launch of its own behind the
-// totals: it pays where the lists are a small part of many blocks (`listed` of T_n).  Query side, d = 128, 128-row blocks,
-// product / totals + gather, us:
-//   12 heads, T_n = 128    k = 1 51 / 34    k = 3 49 / 45      k = 6 50 / 59
-//   12 heads, T_n = 512    k = 4 500 / 203  k = 13 492 / 406   k = 26 497 / 726
-//    2 heads, T_n = 1,182  k = 9 491 / 160  k = 31 488 / 388   k = 59 507 / 679
-constexpr int kGatherBlocks = 64, kGatherRatio = 30;
+// totals: it pays where the lists are a small part of many blocks.  In k / T_n the line lies in the same place on both sides (a
+// key block's list is k T_m / T_n of T_m blocks on average) and for few and many heads; states of 64 KB and of 16 KB have lines
+// of their own.  Calls, us, product / totals + gather:
+//   query side (forward)                       d = 128                                   d = 64
+//     12 heads, T_n = 64                       k = 1 129 / 130    k = 4 155 / 165        k = 1 66 / 64      k = 4 83 / 85
+//     12 heads, T_n = 128, 64-row blocks       k = 4 341 / 335    k = 8 437 / 456        k = 4 146 / 142    k = 8 198 / 199
+//     12 heads, T_n = 256                      k = 8 869 / 845    k = 16 1,272 / 1,335   k = 8 403 / 367    k = 16 618 / 598
+//      8 heads, T_n = 512                      k = 16 1,855 / 1,791   k = 32 2,943 / 3,158   k = 16 904 / 810   k = 32 1,475 / 1,461
+//      1 head, T_n = 512, 64-row blocks        k = 16 334 / 300   k = 32 470 / 503       k = 16 175 / 142   k = 32 248 / 225
+//      2 heads, T_n = 1,182                    k = 36 2,223 / 2,141   k = 72 3,722 / 3,987   k = 36 1,217 / 1,039   k = 72 1,979 / 1,984
+//   key side (training step, product on the query side)
+//     12 heads, T_n = 128, 64-row blocks       k = 2 874 / 857    k = 4 1,090 / 1,094    k = 2 415 / 409    k = 4 500 / 500
+//     12 heads, T_n = 256                      k = 8 2,911 / 2,893   k = 16 4,646 / 4,685   k = 8 1,472 / 1,446   k = 16 2,360 / 2,367
+//      8 heads, T_n = 512                      k = 16 6,628 / 6,551  k = 32 11,422 / 11,666   k = 16 3,336 / 3,278   k = 32 5,809 / 5,811
+//      2 heads, T_n = 1,182                    k = 36 8,103 / 8,018  k = 72 14,565 / 14,964   k = 36 4,312 / 4,140   k = 72 7,640 / 7,629
+constexpr int kGatherBlocks = 64;
+template <int D> constexpr int kGatherRatio = D == 128 ? 25 : 16;
 template <int D>
 static hipError_t launch_states_f32(const Shape& s, int heads, const float* states, const BlockLists& lists, StateSums out, bool totals,
                                     hipStream_t stream) {
   constexpr int P = f32_state(D), kSets = (P + 4 * kStateCols - 1) / (4 * kStateCols);
   const int sets = (heads * kSets + kXcds - 1) / kXcds * kXcds;
-  if (s.Tn <= kGatherBlocks || s.Tn <= kGatherRatio * s.k) {
+  if (s.Tn <= kGatherBlocks || s.Tn <= kGatherRatio<D> * s.k) {
     if (!totals) out.h_total = out.z_total = nullptr;
     const int tiles = (lists.R + 31) / 32, smem = (lists.S + 31) / 32 * 32 * (int)sizeof(uint32_t);   // at most 8 KB
     masked_states_f32_kernel<D, false><<<dim3((unsigned)(sets * tiles)), 256, smem, stream>>>(states, lists, out, heads, tiles);

@@ -17,12 +17,16 @@ CASES = [
     BASE.replace(name="d64-64-of-1", grid=(16, 16, 16), topk_frac=0.016),                                # T_n = 64, k = 1
     BASE.replace(name="d64-65-of-0", grid=(16, 16, 16), extra_tokens=1, topk_frac=0.0),                  # totals alone
     BASE.replace(name="d64-65-of-1", grid=(16, 16, 16), extra_tokens=1, topk_frac=0.016, block_q=128),   # gather; T_m = 33
-    BASE.replace(name="d64-90-of-3", grid=(15, 16, 24), topk_frac=0.0334),                               # T_n = 30 k
+    BASE.replace(name="d64-90-of-3", grid=(15, 16, 24), topk_frac=0.0334),                               # gather
     BASE.replace(name="d64-91-of-3", grid=(15, 16, 24), extra_tokens=33, topk_frac=0.0334, H=2),
     BASE.replace(name="d128-65-of-1", grid=(16, 16, 16), extra_tokens=31, topk_frac=0.016, d=128, block_q=128),
     BASE.replace(name="d128-31-of-4", grid=(8, 15, 16), extra_tokens=32, topk_frac=0.13, d=128),         # T_m = 31
     BASE.replace(name="d64-237-of-12-one-launch", grid=(16, 12, 79), topk_frac=0.05),                    # 15 + 4 + 237 workgroups
     BASE.replace(name="d64-238-of-12", grid=(16, 12, 79), extra_tokens=1, topk_frac=0.05),
+    BASE.replace(name="d64-80-of-5", grid=(20, 16, 16), topk_frac=0.0625),                               # T_n = 16 k: the product
+    BASE.replace(name="d64-81-of-5", grid=(20, 16, 16), extra_tokens=9, topk_frac=0.0617),               # gather
+    BASE.replace(name="d128-75-of-3", grid=(15, 16, 20), topk_frac=0.04, d=128, block_q=128),            # T_n = 25 k: the product
+    BASE.replace(name="d128-76-of-3", grid=(15, 16, 20), extra_tokens=33, topk_frac=0.0395, d=128, block_q=128),   # gather
     BASE.replace(name="d128-33-of-5", grid=(8, 16, 16), extra_tokens=33, topk_frac=0.15, d=128, H=3),    # T_m = 33
 ]
 
@@ -32,7 +36,7 @@ def test_forward(w):
     check_forward(w)
 
 
-@pytest.mark.parametrize("w", [CASES[2], CASES[5], CASES[9]], ids=lambda w: w.name)
+@pytest.mark.parametrize("w", [CASES[2], CASES[5]] + CASES[9:], ids=lambda w: w.name)
 def test_backward(w):
     check_backward(w, True, True)
 
