@@ -59,3 +59,31 @@ def test_result_line_carries_the_required_objects():
     assert roof["traffic_source"].startswith("profiles/")
     assert 0 < d["step_ms"]["min"] <= d["step_ms"]["median"] <= d["step_ms"]["max"]
     assert d["dense_bf16"]["ms"] > d["ms_per_step"] and abs(d["speedup_vs_dense_bf16"] - d["dense_bf16"]["ms"] / d["ms_per_step"]) < 0.02 * d["speedup_vs_dense_bf16"]
+
+
+def _bench():
+    import importlib.util
+    spec = importlib.util.spec_from_file_location("bench", os.path.join(ROOT, "bench.py"))
+    module = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(module)
+    return module
+
+
+@pytest.mark.gpu
+def test_backward_stages_count_every_launch_once():
+    """12 heads of 32,760 tokens: a fifth is room for the event pairs around five launches (about 5 us each of 1.1 ms)."""
+    import torch
+    from paper_2602_12675_amd import api, workloads as W
+    w = W.CONFIGS["wan1.3b-97-fp8"]
+    inp = W.generate(w)
+    tensors = [api.to_device(a, api.SLA2_BF16) for a in (inp.q, inp.k, inp.v)] + [None]
+    rw, al = torch.from_numpy(inp.router_w).cuda(), torch.from_numpy(inp.alpha).cuda()
+    r = _bench().backward_timing(api, W, torch, w, inp, api.SLA2_BF16, api.SLA2_QUANT_FP8, tensors, rw, al, torch.cuda.current_stream(), 15, reps=10)
+    assert set(r["stage_ms"]) == {"bwd_q", "bwd_kv", "bwd_rest"} and sum(r["stage_ms"].values()) < 1.2 * r["ms"]
+
+
+def test_fp32_stages_count_every_launch_once():
+    from paper_2602_12675_amd import workloads as W
+    stages = dict(block_sums=3.0, topk=9.0, kv_state=9.0, kv_total=12.0, attn=12.0)
+    assert sum(_bench().once_each(stages, W.TINY).values()) == 24.0
+    assert _bench().once_each(stages, W.CONFIGS["wan1.3b-97-fp8"]) == stages
