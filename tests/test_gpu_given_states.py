@@ -40,8 +40,8 @@ def test_backward(quant):
 
 
 def test_groups_of_heads():
-    """160 heads of 64 key blocks: 6.3 MB of states each.  The call against two of 80 heads: only the order of the
-    sums of Z_total differs (1e-7), which moves an output across a bf16 boundary now and then."""
+    """160 heads below the line, 48 of 64 key blocks (groups of heads against the oracle: MANY).  The call against two of 80 heads: only
+    the order of the sums of Z_total differs (1e-7), which moves an output across a bf16 boundary now and then."""
     import torch
     from paper_2602_12675_amd import api
     H, N, d = 160, 4096, 128
