@@ -67,6 +67,7 @@ MANY = [   # H, N, k, mode
     (32, 6208, 97, "none"),                           # every block
     (12, 16416, 80, "none"),                          # T_m = 129, T_n = 257
     (32, 6175, 72, "fp8"), (32, 6175, 72, "int8"), (32, 6175, 72, "fp8v"),
+    (2, 131067, 400, "none"),                         # T_n = 2,048, the largest
     (84, 8192, 70, "none"),                           # 12.6 MB of states a head: 80 and 4 heads
 ]
 
@@ -138,3 +139,25 @@ def test_kphi_in_the_workspace(H, T_n, frac):
     kd = k[0].double()
     want = torch.softmax(kd - kd.mean(dim=1, keepdim=True), dim=-1).cpu().numpy()
     assert rel_l2(got, want) < 4e-3                                              # rounded to bf16: at most 2^-9 each
+
+
+@pytest.mark.parametrize("H,N,k,dtype", [(32, 6175, 75, "bfloat16"), (3, 2041, 5, "bfloat16"), (3, 2041, 5, "float32"), (2, 4999, 2, "float32")])
+def test_second_backward_of_a_forward_call(H, N, k, dtype):
+    """dH_j lies in the forward pass's scratch: a second backward call finds all that the forward call kept.  Long and short bf16
+    lists, the fp32 product and gather."""
+    import torch
+    from paper_2602_12675_amd import api
+    d = 128
+    gen = torch.Generator(device="cuda").manual_seed(14)
+    q, kk, v, dout = (torch.randn((1, H, N, d), generator=gen, device="cuda").to(getattr(torch, dtype)) for _ in range(4))
+    rw, alpha = torch.randn((2, d, d), generator=gen, device="cuda") / d ** 0.5, torch.rand((H,), generator=gen, device="cuda")
+    p = api.make_params(1, H, N, d, 128, 64, k / -(-N // 64), dtype=api.SLA2_BF16 if dtype == "bfloat16" else api.SLA2_F32,
+                        flags=api.SLA2_FLAG_SAVE_FOR_BACKWARD)
+    ws = api.alloc_workspace(p)
+    api.sla2_forward(p, q, kk, v, rw, alpha, torch.empty_like(q), workspace=ws)
+    got = []
+    for _ in range(2):
+        got.append([torch.full_like(q, float("nan")) for _ in range(3)] + [torch.full_like(alpha, float("nan"))])
+        api.sla2_backward(p, q, kk, v, alpha, dout, *got[-1], ws)
+    for a, b in zip(*got):
+        assert torch.equal(a, b) and not torch.isnan(a).any()
