@@ -140,7 +140,7 @@ __global__ __launch_bounds__(256) void bwd_unsmooth_kernel(T* __restrict__ dk, c
     bf16x8 x = *reinterpret_cast<const bf16x8*>(p);
 #pragma unroll
     for (int y = 0; y < 8; y++) x[y] = (__bf16)((float)x[y] - m[y]);
-    *reinterpret_cast<bf16x8*>(p) = x;
+    store_streamed(reinterpret_cast<bf16x8*>(p), x);
   } else {
 #pragma unroll
     for (int y = 0; y < 8; y++) p[y] -= m[y];

@@ -468,7 +468,7 @@ __global__ __launch_bounds__(BQ * 2, 2) void bwd_q_mfma_kernel(
     for (int x = 0; x < D / 16; x++) {
       const int r = 32 * w + (x * kWave + ln) / (D / 8), ch = ln % (D / 8);
       if (r < rows_valid)
-        *reinterpret_cast<u32x4*>(dst + (size_t)r * tok_stride + 8 * ch) = *reinterpret_cast<const u32x4*>(kbuf(0) + SL::offset(r, 8 * ch));
+        store_streamed(reinterpret_cast<u32x4*>(dst + (size_t)r * tok_stride + 8 * ch), *reinterpret_cast<const u32x4*>(kbuf(0) + SL::offset(r, 8 * ch)));
     }
   }
 }
@@ -894,7 +894,7 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void bwd_kv_mfma_kernel(
       const int t = idx / (D / 8), ch = idx % (D / 8);
       if (t < valid) {
         *reinterpret_cast<u32x4*>(dkh + (size_t)t * tok_stride + 8 * ch) = *reinterpret_cast<const u32x4*>(okt + t * LD + 8 * ch);
-        *reinterpret_cast<u32x4*>(dvh + (size_t)t * tok_stride + 8 * ch) = *reinterpret_cast<const u32x4*>(ovt + t * LD + 8 * ch);
+        store_streamed(reinterpret_cast<u32x4*>(dvh + (size_t)t * tok_stride + 8 * ch), *reinterpret_cast<const u32x4*>(ovt + t * LD + 8 * ch));
       }
     }
     // column sums of dK' (as stored) for the smoothing term: two channels and 64 / kParts rows per thread

@@ -1499,7 +1499,7 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
 #pragma unroll
   for (int x = 0; x < D / 16; x++) {
     const int r = 32 * w + (x * kWave + lane) / (D / 8), ch = lane % (D / 8);
-    if (r < rows_valid) *reinterpret_cast<u32x4*>(oh + (size_t)r * sout.n + 8 * ch) = *reinterpret_cast<const u32x4*>(os + r * LD + 8 * ch);
+    if (r < rows_valid) store_streamed(reinterpret_cast<u32x4*>(oh + (size_t)r * sout.n + 8 * ch), *reinterpret_cast<const u32x4*>(os + r * LD + 8 * ch));
   }
   if constexpr (!DENSE) {
     if (h_save != nullptr) {
@@ -1507,7 +1507,7 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
       uint16_t* dst = h_save + ((size_t)bh * Tm + i) * D * D;
       for (int idx = tid; idx < D * (D / 8); idx += NT) {
         const int e = idx / (D / 8), ch = idx % (D / 8);
-        *reinterpret_cast<u32x4*>(dst + e * D + 8 * ch) = *reinterpret_cast<const u32x4*>(ht + e * LD + 8 * ch);
+        store_streamed(reinterpret_cast<u32x4*>(dst + e * D + 8 * ch), *reinterpret_cast<const u32x4*>(ht + e * LD + 8 * ch));
       }
     }
   }
@@ -1536,7 +1536,7 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
 #pragma unroll
       for (int x = 0; x < D / 16; x++) {
         const int r = 32 * w + (x * kWave + lane) / (D / 8), ch = lane % (D / 8);
-        if (r < rows_valid) *reinterpret_cast<u32x4*>(dst + (size_t)r * D + 8 * ch) = *reinterpret_cast<const u32x4*>(os + r * LD + 8 * ch);
+        if (r < rows_valid) store_streamed(reinterpret_cast<u32x4*>(dst + (size_t)r * D + 8 * ch), *reinterpret_cast<const u32x4*>(os + r * LD + 8 * ch));
       }
     }
   }
