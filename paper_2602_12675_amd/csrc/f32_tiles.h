@@ -135,16 +135,23 @@ __device__ __forceinline__ void meet4(float (&own)[D / 8], const f32x16 (&acc)[D
 #pragma unroll
   for (int n = 0; n < ROUNDS; n++) {
     if (n) __syncthreads();               // the round before has been read
+    auto put = [&](auto wave) {           // one branch a round, not one an entry
+      constexpr int W = decltype(wave)::value;
 #pragma unroll
-    for (int o = 0; o < 4; o++)
+      for (int o = 0; o < 4; o++)
 #pragma unroll
-      for (int y = 0; y < 4; y++)
+        for (int y = 0; y < 4; y++)
 #pragma unroll
-        for (int x = 0; x < XT; x++) {
-          const float p = acc[XT * n + x][4 * o + y] * scale;
-          if (o == w) own[ET * y + XT * n + x] = p;
-          else part(o, w)[(XT * y + x) * kWave] = p;
-        }
+          for (int x = 0; x < XT; x++) {
+            const float p = acc[XT * n + x][4 * o + y] * scale;
+            if (o == W) own[ET * y + XT * n + x] = p;
+            else part(o, W)[(XT * y + x) * kWave] = p;
+          }
+    };
+    if (w == 0) put(std::integral_constant<int, 0>());
+    else if (w == 1) put(std::integral_constant<int, 1>());
+    else if (w == 2) put(std::integral_constant<int, 2>());
+    else put(std::integral_constant<int, 3>());
     __syncthreads();
 #pragma unroll
     for (int f = 0; f < 4; f++)
