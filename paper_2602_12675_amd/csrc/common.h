@@ -113,6 +113,32 @@ __device__ __forceinline__ float wave_max(float x) {
   return swap_halves_max(x);
 }
 
+// x of another lane: DPP controls, vector instructions only
+template <int CTRL> __device__ __forceinline__ float dpp_move(float x) {
+  const int i = __builtin_bit_cast(int, x);
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(i, i, CTRL, 0xf, 0xf, false));
+}
+template <int N> __device__ __forceinline__ float rotate16(float x) { return dpp_move<0x120 + N>(x); }   // within 16 lanes
+// over four neighbouring lanes, on all of them
+__device__ __forceinline__ float quad_max(float x) {
+  x = fmaxf(x, dpp_move<0xB1>(x));
+  return fmaxf(x, dpp_move<0x4E>(x));
+}
+__device__ __forceinline__ float quad_sum(float x) {
+  x += dpp_move<0xB1>(x);
+  return x + dpp_move<0x4E>(x);
+}
+// a of lanes l and l ^ 32 added up on the lower half of the wave, b on the upper one; the same with l ^ 16 on the even and odd
+// 16 lanes
+__device__ __forceinline__ float swap32_add(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, a), __builtin_bit_cast(unsigned, b), false, false);
+  return __builtin_bit_cast(float, (unsigned)r[0]) + __builtin_bit_cast(float, (unsigned)r[1]);
+}
+__device__ __forceinline__ float swap16_add(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, a), __builtin_bit_cast(unsigned, b), false, false);
+  return __builtin_bit_cast(float, (unsigned)r[0]) + __builtin_bit_cast(float, (unsigned)r[1]);
+}
+
 // What the lanes of a wave wrote to LDS ahead of it the other lanes of that wave may read behind it, and the other way
 // round.  LDS serves the accesses of a wave in order, so this is no instruction: it tells the compiler to keep them so.
 __device__ __forceinline__ void wave_lds_fence() {

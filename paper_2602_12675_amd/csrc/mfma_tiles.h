@@ -249,30 +249,6 @@ __device__ __forceinline__ void dma_tile_vq(const uint8_t* src, unsigned lds, in
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
-// K^phi fragment in token order for channel col0 + l % 32:
-//   K^phi[t][c] = exp(k[t][c] - mu[c] - lnZ[t]) = exp2(k log2e - (mu2 + lnz2[t]))
-// lnz2: LDS array of 64 floats, lnZ[t] * log2e, +inf for tokens past the end (-> K^phi = 0).
-// Adds the 8 fp32 values to zsum (column sums of K^phi, Alg. 2's z).
-template <class L>
-__device__ __forceinline__ bf16x8 kphi_fragment(const uint16_t* ktile, const float* lnz2, float mu2, int ks, int col0,
-                                                int lane, float& zsum) {
-  const int g = lane / 32;
-  s16x4 lo = read_tr4<L>(ktile, 16 * ks + 4 * g, col0, lane);
-  s16x4 hi = read_tr4<L>(ktile, 16 * ks + 8 + 4 * g, col0, lane);
-  const f32x4 zl = *reinterpret_cast<const f32x4*>(lnz2 + 16 * ks + 4 * g);
-  const f32x4 zh = *reinterpret_cast<const f32x4*>(lnz2 + 16 * ks + 8 + 4 * g);
-  bf16x8 r;
-#pragma unroll
-  for (int i = 0; i < 4; i++) {
-    float a = fast_exp2(bf16_bits_to_f32((uint16_t)lo[i]) * kLog2e - (mu2 + zl[i]));
-    float b = fast_exp2(bf16_bits_to_f32((uint16_t)hi[i]) * kLog2e - (mu2 + zh[i]));
-    zsum += a + b;
-    r[i] = (__bf16)a;
-    r[4 + i] = (__bf16)b;
-  }
-  return r;
-}
-
 // 16-byte global loads of one 64 x D bf16 tile into registers and the matching stores into a padded
 // LDS tile.  NT threads cooperate.  Rows past `valid` repeat the last existing row: the loads stay
 // unpredicated, so they can remain in flight across a whole compute phase.

@@ -61,8 +61,17 @@ __device__ __forceinline__ size_t kphi_offset(size_t block, int mt, int ks, int 
 // (8 + 8 + 8 bits: nothing of an fp32 entry is left out): rows 3 j to 3 j + 2 of `states`, each as the accumulators lie - [tile (mt, nt)][2][64 lanes][8], lane l of half y
 // holding column e = 32 nt + l % 32, rows c = 32 mt + 16 y + 4 (l / 32) + {0..3, 8..11}.  The heads are those from bh0 on;
 // `partial` and `states` hold theirs alone.
+// A token's softmax is taken once, in registers: its K^phi goes to LDS rounded, for the fragments, and from the registers into z_j,
+// the sum of what was not rounded.  Taken twice, for lnZ and again for the fragments, the exponentials and the sums around them were most
+// of a tile's 9,000 cycles (two workgroups a CU).  us, before / now: FP8, 12 heads of 32,760 tokens 73.9 / 65.3 (0.35 GB at 5.4 TB/s),
+// 48 heads of 4,096 46.8 / 39.5; bf16 63.0 / 58.5; 32 heads of 4,096, d = 64 19.6 / 17.0; FP8 with V, 12 heads of 32,760, d = 64
+// 68.7 / 49.0.
+// Threads: at d = 128 eight waves with two tiles of h each run four on a SIMD, four waves with four tiles two: those leave the vector
+// unit and the memory idle in turn (us, four / eight waves: FP8, 12 heads of 32,760 tokens 67.5 / 65.4, 48 of 4,096 42.5 / 39.5).
+// With the states or the codes of V four: what they add does not fit 128 registers (FP8 with V 95 / 106).
+template <int D, int QUANT, bool STATES> constexpr int kKvThreads = D == 128 && QUANT != 3 && !STATES ? 512 : 256;
 template <int D, int QUANT, bool STATES>
-__global__ __launch_bounds__(256, STATES ? 2 : 1) void kv_state_bf16_kernel(const uint16_t* __restrict__ k,
+__global__ __launch_bounds__((kKvThreads<D, QUANT, STATES>), (D == 64 || kKvThreads<D, QUANT, STATES> == 512 ? 4 : 2)) void kv_state_bf16_kernel(const uint16_t* __restrict__ k,
                                                             const uint16_t* __restrict__ v,
                                                             const double* __restrict__ k_mean,
                                                             float* __restrict__ k_stats, float* __restrict__ partial,
@@ -72,15 +81,16 @@ __global__ __launch_bounds__(256, STATES ? 2 : 1) void kv_state_bf16_kernel(cons
                                                             uint16_t* __restrict__ states, Strides sin, int bh0, int H, int N,
                                                             int Tn, int chunks, int blocks_per_chunk) {
   constexpr int LD = TileGeom<D>::kLd;
-  typedef HSplit<D, 4> HS;
-  __shared__ __attribute__((aligned(16))) uint16_t ktile[kTileTokens * LD];
+  constexpr int NT = kKvThreads<D, QUANT, STATES>, NW = NT / kWave, TPT = NT / kTileTokens;   // TPT: threads a token
+  typedef HSplit<D, NW> HS;
+  __shared__ __attribute__((aligned(16))) uint16_t ptile[kTileTokens * LD];    // K^phi
   __shared__ __attribute__((aligned(16))) uint16_t vtile[kTileTokens * LD];
-  __shared__ __attribute__((aligned(16))) float lnz2[kTileTokens];
-  __shared__ float mu_s[D];
-  __shared__ float red[4];
-  __shared__ float red_v[4];
+  __shared__ __attribute__((aligned(16))) float zpart[NW][D];                  // sums of K^phi over the tokens of a wave
+  __shared__ __attribute__((aligned(16))) float mu_s[D];
+  __shared__ float red[NW];
+  __shared__ float red_v[NW];
   const int bh = bh0 + blockIdx.x / chunks, chunk = blockIdx.x % chunks;
-  const int tid = threadIdx.x, lane = tid % kWave, w = tid / kWave, g = lane / 32;
+  const int tid = threadIdx.x, lane = tid % kWave, w = tid / kWave;
   const uint16_t* kh = k + head_offset(sin, bh, H);
   const uint16_t* vh = v + head_offset(sin, bh, H);
   const int j0 = chunk * blocks_per_chunk, j1 = min(Tn, j0 + blocks_per_chunk);
@@ -88,113 +98,157 @@ __global__ __launch_bounds__(256, STATES ? 2 : 1) void kv_state_bf16_kernel(cons
 
   if (tid < D) mu_s[tid] = (float)k_mean[(size_t)bh * D + tid];
   __syncthreads();
-  float mu2[HS::kMtw];
-#pragma unroll
-  for (int a = 0; a < HS::kMtw; a++) mu2[a] = mu_s[32 * (mt0 + a) + lane % 32] * kLog2e;
 
   f32x16 hacc[HS::kMtw][HS::kNtw];
-  float zacc[HS::kMtw];
 #pragma unroll
-  for (int a = 0; a < HS::kMtw; a++) {
-    zacc[a] = 0.f;
+  for (int a = 0; a < HS::kMtw; a++)
 #pragma unroll
     for (int b = 0; b < HS::kNtw; b++)
 #pragma unroll
       for (int e = 0; e < 16; e++) hacc[a][b][e] = 0.f;
-  }
+  float zacc = 0.f;                                    // of channel tid
 
-  typedef TileCopy<D, 256> TC;
-  u32x4 kr[TC::kLoads], vr[TC::kLoads];
+  // TPT threads a token, each with 8 P channels from c0 on: K goes from memory to the registers its softmax is taken in, V through
+  // registers to LDS.
+  constexpr int P = D / 8 / TPT;
+  const int t = tid / TPT, sub = tid % TPT, c0 = 8 * P * sub;
+  typedef TileCopy<D, NT> TC;
+  u32x4 kr[P], vr[TC::kLoads];
+  auto load_k = [&](int j) {
+    const int there = min(kTileTokens, N - j * kTileTokens);
+    const uint16_t* row = kh + ((size_t)j * kTileTokens + min(t, there - 1)) * sin.n + c0;
+#pragma unroll
+    for (int i = 0; i < P; i++) kr[i] = *reinterpret_cast<const u32x4*>(row + 8 * i);
+  };
+  auto load_v = [&](int j) { TC::load(vr, vh + (size_t)j * kTileTokens * sin.n, sin.n, min(kTileTokens, N - j * kTileTokens), tid); };
   if (j0 < j1) {
-    const int valid = min(kTileTokens, N - j0 * kTileTokens);
-    TC::load(kr, kh + (size_t)j0 * kTileTokens * sin.n, sin.n, valid, tid);
-    TC::load(vr, vh + (size_t)j0 * kTileTokens * sin.n, sin.n, valid, tid);
+    load_k(j0);
+    load_v(j0);
   }
   for (int j = j0; j < j1; j++) {
     const int t0 = j * kTileTokens, valid = min(kTileTokens, N - t0);
-    __syncthreads();                                   // previous tile fully consumed
-    TC::store(kr, ktile, tid);
-    TC::store(vr, vtile, tid);
-    if (j + 1 < j1) {
-      const int nvalid = min(kTileTokens, N - (j + 1) * kTileTokens);
-      TC::load(kr, kh + (size_t)(j + 1) * kTileTokens * sin.n, sin.n, nvalid, tid);
-      TC::load(vr, vh + (size_t)(j + 1) * kTileTokens * sin.n, sin.n, nvalid, tid);
-    }
-    __syncthreads();
-    {  // per-token log-partition of softmax_d(k'), 4 threads per token
-      const int t = tid / 4, sub = tid % 4;
-      float x[D / 4];
-      float m = -INFINITY, amax = 0.f;
+    const bool ok = t < valid;
+    float x[8 * P];
 #pragma unroll
-      for (int i = 0; i < D / 32; i++) {
-        const int c0 = 8 * (sub + 4 * i);
-        uint4 u = *reinterpret_cast<const uint4*>(ktile + t * LD + c0);
-        uint32_t wds[4] = {u.x, u.y, u.z, u.w};
+    for (int i = 0; i < P; i++) {
+      const f32x4 mu[2] = {*reinterpret_cast<const f32x4*>(mu_s + c0 + 8 * i), *reinterpret_cast<const f32x4*>(mu_s + c0 + 8 * i + 4)};
 #pragma unroll
-        for (int e = 0; e < 4; e++) {
-          x[8 * i + 2 * e] = __builtin_bit_cast(float, wds[e] << 16) - mu_s[c0 + 2 * e];
-          x[8 * i + 2 * e + 1] = __builtin_bit_cast(float, wds[e] & 0xFFFF0000u) - mu_s[c0 + 2 * e + 1];
-        }
+      for (int e = 0; e < 4; e++) {
+        x[8 * i + 2 * e] = __builtin_bit_cast(float, kr[i][e] << 16) - mu[e / 2][2 * (e % 2)];
+        x[8 * i + 2 * e + 1] = __builtin_bit_cast(float, kr[i][e] & 0xFFFF0000u) - mu[e / 2][2 * (e % 2) + 1];
       }
+    }
+    if (j + 1 < j1) load_k(j + 1);
+    // K^phi = softmax_d(k') of the token and lnZ, its log-partition
+    float p[8 * P];
+    {
+      float m = -INFINITY;
 #pragma unroll
-      for (int i = 0; i < D / 4; i++) { m = fmaxf(m, x[i]); amax = fmaxf(amax, fabsf(x[i])); }
-      m = fmaxf(m, __shfl_xor(m, 1));
-      m = fmaxf(m, __shfl_xor(m, 2));
+      for (int e = 0; e < 8 * P; e++) m = fmaxf(m, x[e]);
+      m = quad_max(m);
+      if (TPT == 8) m = fmaxf(m, dpp_move<0x141>(m));  // row_half_mirror: the other four lanes
       float sum = 0.f;
 #pragma unroll
-      for (int i = 0; i < D / 4; i++) sum += fast_exp2((x[i] - m) * kLog2e);
-      sum += __shfl_xor(sum, 1);
-      sum += __shfl_xor(sum, 2);
-      const float lnz = m + __log2f(sum) * 0.6931471805599453f;
-      const bool ok = t < valid;
-      if (sub == 0) {
-        lnz2[t] = ok ? lnz * kLog2e : INFINITY;
-        if (ok) k_stats[(size_t)bh * N + t0 + t] = lnz;
+      for (int e = 0; e < 8 * P; e++) {
+        p[e] = fast_exp2((x[e] - m) * kLog2e);
+        sum += p[e];
       }
-      if (QUANT) {
-        // one scale per key block: amax over the block's existing tokens (Sec. 5; see sla2.h)
-        constexpr float kCodeMax = QUANT == 2 ? kInt8Max : kE4M3Max;
-        if (!ok) amax = 0.f;
+      sum = quad_sum(sum);
+      if (TPT == 8) sum += dpp_move<0x141>(sum);
+      if (ok && sub == 0) k_stats[(size_t)bh * N + t0 + t] = m + __log2f(sum) * 0.6931471805599453f;
+      const float inv = 1.f / sum;
 #pragma unroll
-        for (int o = 1; o < kWave; o <<= 1) amax = fmaxf(amax, __shfl_xor(amax, o));
-        if (lane == 0) red[w] = amax;
-        __syncthreads();
-        amax = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-        const float inv = amax > 0.f ? kCodeMax / amax : 1.f;
-        if (tid == 0) k_scale[(size_t)bh * Tn + j] = amax > 0.f ? amax / kCodeMax : 1.f;
-        uint8_t* dst = k_codes + (((size_t)bh * Tn + j) * kTileTokens + t) * D;
+      for (int e = 0; e < 8 * P; e++) p[e] *= inv;
+      if (valid < kTileTokens)                         // tokens past the end contribute nothing
 #pragma unroll
-        for (int i = 0; i < D / 32; i++) {
-          const int c0 = 8 * (sub + 4 * i);
-          int lo = 0, hi = 0;
-          if (ok) {
-            float y[8];
+        for (int e = 0; e < 8 * P; e++) p[e] = ok ? p[e] : 0.f;
+    }
+    float amax = 0.f;
+    if (QUANT) {
 #pragma unroll
-            for (int e = 0; e < 8; e++) y[e] = fminf(fmaxf(x[8 * i + e] * inv, -kCodeMax), kCodeMax);
-            if constexpr (QUANT == 2) {
-              lo = pack_int8(y[0], y[1], y[2], y[3]);
-              hi = pack_int8(y[4], y[5], y[6], y[7]);
-            } else {
-              lo = __builtin_amdgcn_cvt_pk_fp8_f32(y[0], y[1], lo, false);
-              lo = __builtin_amdgcn_cvt_pk_fp8_f32(y[2], y[3], lo, true);
-              hi = __builtin_amdgcn_cvt_pk_fp8_f32(y[4], y[5], hi, false);
-              hi = __builtin_amdgcn_cvt_pk_fp8_f32(y[6], y[7], hi, true);
-            }
+      for (int e = 0; e < 8 * P; e++) amax = fmaxf(amax, fabsf(x[e]));
+      amax = wave_max(ok ? amax : 0.f);
+    }
+    // Sums over the tokens of the wave (lanes TPT apart), in fp32: two exchanges that halve what a lane has left to sum, then
+    // rotations within 16 lanes.  A lane ends up with 2 P channels from c0 + zc on.
+    constexpr int Z = 2 * P;
+    const int zc = 2 * Z * (lane / 32) + Z * (lane / 16 % 2);
+    float z[Z];
+    {
+      float half[2 * Z];
+#pragma unroll
+      for (int e = 0; e < 2 * Z; e++) half[e] = swap32_add(p[e], p[2 * Z + e]);
+#pragma unroll
+      for (int e = 0; e < Z; e++) {
+        z[e] = swap16_add(half[e], half[Z + e]);
+        z[e] += rotate16<8>(z[e]);
+        if (TPT == 4) z[e] += rotate16<4>(z[e]);
+      }
+    }
+    __syncthreads();                                   // previous tile fully consumed
+#pragma unroll
+    for (int i = 0; i < P; i++) {
+      bf16x8 y;
+#pragma unroll
+      for (int e = 0; e < 8; e++) y[e] = (__bf16)p[8 * i + e];
+      *reinterpret_cast<bf16x8*>(ptile + t * LD + c0 + 8 * i) = y;
+    }
+    TC::store(vr, vtile, tid);
+    if (j + 1 < j1) load_v(j + 1);
+    if (lane % 16 < TPT) {
+#pragma unroll
+      for (int e = 0; e < Z; e += 4) *reinterpret_cast<f32x4*>(&zpart[w][c0 + zc + e]) = f32x4{z[e], z[e + 1], z[e + 2], z[e + 3]};
+    }
+    if (QUANT && lane == 0) red[w] = amax;
+    __syncthreads();
+    if (tid < D) {
+      float zj = 0.f;
+#pragma unroll
+      for (int y = 0; y < NW; y++) zj += zpart[y][tid];
+      zacc += zj;
+      z_blocks[((size_t)bh * Tn + j) * D + tid] = zj;
+    }
+    if (QUANT) {
+      // one scale per key block: amax over the block's existing tokens (Sec. 5; see sla2.h)
+      constexpr float kCodeMax = QUANT == 2 ? kInt8Max : kE4M3Max;
+#pragma unroll
+      for (int y = 0; y < NW; y++) amax = fmaxf(amax, red[y]);
+      const float inv = amax > 0.f ? kCodeMax / amax : 1.f;
+      if (tid == 0) k_scale[(size_t)bh * Tn + j] = amax > 0.f ? amax / kCodeMax : 1.f;
+      int codes[2 * P];
+#pragma unroll
+      for (int i = 0; i < P; i++) {
+        int lo = 0, hi = 0;
+        if (ok) {
+          float y[8];
+#pragma unroll
+          for (int e = 0; e < 8; e++) y[e] = fminf(fmaxf(x[8 * i + e] * inv, -kCodeMax), kCodeMax);
+          if constexpr (QUANT == 2) {
+            lo = pack_int8(y[0], y[1], y[2], y[3]);
+            hi = pack_int8(y[4], y[5], y[6], y[7]);
+          } else {
+            lo = __builtin_amdgcn_cvt_pk_fp8_f32(y[0], y[1], lo, false);
+            lo = __builtin_amdgcn_cvt_pk_fp8_f32(y[2], y[3], lo, true);
+            hi = __builtin_amdgcn_cvt_pk_fp8_f32(y[4], y[5], hi, false);
+            hi = __builtin_amdgcn_cvt_pk_fp8_f32(y[6], y[7], hi, true);
           }
-          *reinterpret_cast<int2*>(dst + c0) = make_int2(lo, hi);
         }
+        codes[2 * i] = lo;
+        codes[2 * i + 1] = hi;
       }
+      uint8_t* dst = k_codes + (((size_t)bh * Tn + j) * kTileTokens + t) * D + c0;
+#pragma unroll
+      for (int x = 0; x < P; x += 2) *reinterpret_cast<i32x4*>(dst + 8 * x) = i32x4{codes[2 * x], codes[2 * x + 1], codes[2 * x + 2], codes[2 * x + 3]};
     }
     if constexpr (QUANT == 3) {
       // quant(V_j) for the second product (Alg. 2): one e4m3 scale per block over its existing tokens,
       // codes stored channel-major with the tokens of a row in the order the 64-deep product consumes
-      // them (layout: sla2.h, v_fp8).  Thread (token t, quarter sub) finds the maximum ...
-      const int t = tid / 4, sub = tid % 4;
+      // them (layout: sla2.h, v_fp8).  The threads of token t find the maximum ...
       float vmax = 0.f;
       if (t < valid) {
 #pragma unroll
-        for (int i = 0; i < D / 32; i++) {
-          const uint4 u = *reinterpret_cast<const uint4*>(vtile + t * LD + 8 * (sub + 4 * i));
+        for (int i = 0; i < P; i++) {
+          const uint4 u = *reinterpret_cast<const uint4*>(vtile + t * LD + c0 + 8 * i);
           const uint32_t wds[4] = {u.x, u.y, u.z, u.w};
 #pragma unroll
           for (int e = 0; e < 4; e++) {
@@ -207,44 +261,39 @@ __global__ __launch_bounds__(256, STATES ? 2 : 1) void kv_state_bf16_kernel(cons
       for (int o = 1; o < kWave; o <<= 1) vmax = fmaxf(vmax, __shfl_xor(vmax, o));
       if (lane == 0) red_v[w] = vmax;
       __syncthreads();
-      vmax = fmaxf(fmaxf(red_v[0], red_v[1]), fmaxf(red_v[2], red_v[3]));
+#pragma unroll
+      for (int y = 0; y < NW; y++) vmax = fmaxf(vmax, red_v[y]);
       const float vinv = vmax > 0.f ? kE4M3Max / vmax : 1.f;
       if (tid == 0) v_scale[(size_t)bh * Tn + j] = vmax > 0.f ? vmax / kE4M3Max : 1.f;
-      // ... and thread (channel c, half gh) writes the 32 codes of bytes 32 gh .. 32 gh + 31 of row c
-      if (tid < 2 * D) {
-        const int c = tid / 2, gh = tid % 2;
-        int wd[8];
+      // ... and four threads of channel c write 16 codes each of row c: bytes 16 part .. 16 part + 15
+      for (int y = tid; y < 4 * D; y += NT) {
+        const int c = y / 4, part = y % 4;
+        int wd[4];
 #pragma unroll
-        for (int q = 0; q < 8; q++) {                  // dword q = bytes 4 q .. 4 q + 3
-          float y[4];
+        for (int q = 0; q < 4; q++) {                  // dword q = bytes 4 q .. 4 q + 3
+          float x4[4];
 #pragma unroll
           for (int r = 0; r < 4; r++) {
-            const int b = 4 * q + r;
-            const int tok = 32 * (b / 16) + 8 * ((b % 16) / 4) + 4 * gh + b % 4;
-            const float x = __builtin_bit_cast(float, (uint32_t)vtile[tok * LD + c] << 16);
-            y[r] = tok < valid ? fminf(fmaxf(x * vinv, -kE4M3Max), kE4M3Max) : 0.f;
+            const int b = 16 * (part % 2) + 4 * q + r; // byte of the half row part / 2
+            const int tok = 32 * (b / 16) + 8 * ((b % 16) / 4) + 4 * (part / 2) + b % 4;
+            const float v4 = __builtin_bit_cast(float, (uint32_t)vtile[tok * LD + c] << 16);
+            x4[r] = tok < valid ? fminf(fmaxf(v4 * vinv, -kE4M3Max), kE4M3Max) : 0.f;
           }
           int d0 = 0;
-          d0 = __builtin_amdgcn_cvt_pk_fp8_f32(y[0], y[1], d0, false);
-          d0 = __builtin_amdgcn_cvt_pk_fp8_f32(y[2], y[3], d0, true);
+          d0 = __builtin_amdgcn_cvt_pk_fp8_f32(x4[0], x4[1], d0, false);
+          d0 = __builtin_amdgcn_cvt_pk_fp8_f32(x4[2], x4[3], d0, true);
           wd[q] = d0;
         }
-        int4* dst = reinterpret_cast<int4*>(v_codes + (((size_t)bh * Tn + j) * D + c) * kTileTokens + 32 * gh);
-        dst[0] = make_int4(wd[0], wd[1], wd[2], wd[3]);
-        dst[1] = make_int4(wd[4], wd[5], wd[6], wd[7]);
+        *reinterpret_cast<int4*>(v_codes + (((size_t)bh * Tn + j) * D + c) * kTileTokens + 16 * part) = make_int4(wd[0], wd[1], wd[2], wd[3]);
       }
     }
-    __syncthreads();
     // K^phi fragments (kept for the attention kernel), h += K^phi^T V on the matrix cores, z_j
-    float zsum[HS::kMtw];
-#pragma unroll
-    for (int a = 0; a < HS::kMtw; a++) zsum[a] = 0.f;
     if constexpr (STATES) {
       static_assert(HS::kMtw == 1, "one row of tiles a wave");
       bf16x8 kf[kTileTokens / 16];
 #pragma unroll
       for (int ks = 0; ks < kTileTokens / 16; ks++)
-        kf[ks] = kphi_fragment<PaddedLayout<D>>(ktile, lnz2, mu2[0], ks, 32 * mt0, lane, zsum[0]);
+        kf[ks] = v_fragment<PaddedLayout<D>>(ptile, ks, 32 * mt0, lane);
       uint16_t* to = states + ((size_t)(bh - bh0) * Tn + j) * (kStateParts * D * D) + ((mt0 * (D / 32) + nt0) * 2 * kWave + lane) * 8;
 #pragma unroll
       for (int b = 0; b < HS::kNtw; b++) {
@@ -280,8 +329,8 @@ __global__ __launch_bounds__(256, STATES ? 2 : 1) void kv_state_bf16_kernel(cons
         bf16x8 kf[HS::kMtw];
 #pragma unroll
         for (int a = 0; a < HS::kMtw; a++) {
-          kf[a] = kphi_fragment<PaddedLayout<D>>(ktile, lnz2, mu2[a], ks, 32 * (mt0 + a), lane, zsum[a]);
-          if (nt0 == 0)
+          kf[a] = v_fragment<PaddedLayout<D>>(ptile, ks, 32 * (mt0 + a), lane);
+          if (HS::kNtw == D / 32 || ks / 2 == nt0 / HS::kNtw)   // where two waves form the fragments of a channel tile: two steps each
             *reinterpret_cast<bf16x8*>(k_phi + kphi_offset<D>((size_t)bh * Tn + j, mt0 + a, ks, lane)) = kf[a];
         }
 #pragma unroll
@@ -291,12 +340,6 @@ __global__ __launch_bounds__(256, STATES ? 2 : 1) void kv_state_bf16_kernel(cons
           for (int a = 0; a < HS::kMtw; a++) hacc[a][b] = mfma_bf16(kf[a], vf, hacc[a][b]);
         }
       }
-    }
-#pragma unroll
-    for (int a = 0; a < HS::kMtw; a++) {
-      const float z = half_sum(zsum[a]);
-      zacc[a] += z;
-      if (g == 0 && nt0 == 0) z_blocks[((size_t)bh * Tn + j) * D + 32 * (mt0 + a) + lane] = z;
     }
   }
   float* ph = partial + (size_t)blockIdx.x * (D * D + D);   // head of the launch, chunk
@@ -309,8 +352,8 @@ __global__ __launch_bounds__(256, STATES ? 2 : 1) void kv_state_bf16_kernel(cons
         const f32x4 part = {hacc[a][b][4 * x], hacc[a][b][4 * x + 1], hacc[a][b][4 * x + 2], hacc[a][b][4 * x + 3]};
         *reinterpret_cast<f32x4*>(ph + (((mt0 + a) * (D / 32) + nt0 + b) * 4 + x) * 256 + 4 * lane) = part;   // as it lies (kv_total)
       }
-    if (g == 0 && nt0 == 0) ph[D * D + 32 * (mt0 + a) + lane] = zacc[a];
   }
+  if (tid < D) ph[D * D + tid] = zacc;
 }
 
 hipError_t launch_kv_state_bf16(const Shape& s, const uint16_t* k, const uint16_t* v, const double* k_mean,
@@ -318,7 +361,7 @@ hipError_t launch_kv_state_bf16(const Shape& s, const uint16_t* k, const uint16_
                                 float* k_scale, uint8_t* v_codes, float* v_scale, hipStream_t stream) {
   dim3 grid((unsigned)(s.BH * s.chunks));
 #define SLA2_KV(DD, QQ)                                                                                          \
-  kv_state_bf16_kernel<DD, QQ, false><<<grid, 256, 0, stream>>>(k, v, k_mean, k_stats, partial, k_phi, z_blocks, k_codes, \
+  kv_state_bf16_kernel<DD, QQ, false><<<grid, kKvThreads<DD, QQ, false>, 0, stream>>>(k, v, k_mean, k_stats, partial, k_phi, z_blocks, k_codes, \
                                                                 k_scale, v_codes, v_scale, nullptr, s.sin, 0, s.H, s.N, s.Tn, \
                                                                 s.chunks, s.blocks_per_chunk)
 #define SLA2_KV_D(DD)                                                                                  \
@@ -386,7 +429,7 @@ hipError_t launch_kv_states_bf16(const Shape& s, const uint16_t* k, const uint16
   for (int bh0 = 0; bh0 < s.BH; bh0 += s.state_heads) {
     const int heads = s.BH - bh0 < s.state_heads ? s.BH - bh0 : s.state_heads;
 #define SLA2_KV(QQ)                                                                                                        \
-  kv_state_bf16_kernel<128, QQ, true><<<dim3((unsigned)(heads * s.chunks)), 256, 0, stream>>>(                             \
+  kv_state_bf16_kernel<128, QQ, true><<<dim3((unsigned)(heads * s.chunks)), kKvThreads<128, QQ, true>, 0, stream>>>(                             \
       k, v, k_mean, k_stats, partial, nullptr, z_blocks, k_codes, k_scale, v_codes, v_scale, gs.states, s.sin, bh0, s.H, s.N, \
       s.Tn, s.chunks, s.blocks_per_chunk)
     if (s.quant == 3) SLA2_KV(3);
