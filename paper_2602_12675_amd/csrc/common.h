@@ -77,6 +77,13 @@ __device__ __forceinline__ float bf16_bits_to_f32(uint16_t b) {
   return __builtin_bit_cast(float, (uint32_t)b << 16);
 }
 
+// A load of what is the same for the whole wave, through the scalar cache: the compiler does so by itself only where it can prove that
+// nothing was written in between, which it cannot behind inline assembly.  For memory that no workgroup of the launch writes.
+template <class T>
+__device__ __forceinline__ T scalar_load(const T* p) {
+  return *(const __attribute__((address_space(4))) T*)(uintptr_t)p;
+}
+
 // A store past the caches, for results that no kernel of the same pass reads (out, what is kept for the backward pass, gradients):
 // left in the 256 MB memory-side cache they push out the tiles that are gathered from it, and their way to memory falls into the
 // next kernels that stream through HBM.  Forward, us, cached / past the caches: 48 heads of 4,096 tokens (FP8) 169.2 / 164.5,
@@ -96,6 +103,12 @@ __device__ __forceinline__ float swap_halves_sum(float x) {
   const unsigned u = __builtin_bit_cast(unsigned, x);
   const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
   return __builtin_bit_cast(float, (unsigned)r[0]) + __builtin_bit_cast(float, (unsigned)r[1]);
+}
+// max(x, |a|, |b|) as the one instruction it is: of values that come from bit operations the compiler takes maxima with themselves first
+__device__ __forceinline__ float max3_abs(float x, float a, float b) {
+  float r;
+  asm("v_max3_f32 %0, %1, |%2|, |%3|" : "=v"(r) : "v"(x), "v"(a), "v"(b));
+  return r;
 }
 // Maximum over the wave, on every lane; vector instructions only.
 __device__ __forceinline__ float wave_max(float x) {

@@ -581,6 +581,11 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
   auto vbuf = [&](int buf) { return lds0 + SM::kVOff + buf * SM::kVBytes; };
   auto vqbuf = [&](int buf) { return lds0 + SM::kVq0Off + buf * (SM::kVq1Off - SM::kVq0Off); };
 
+  // The arguments that the requests below need, all at once: left to the compiler they come in three turns, each as long as a
+  // scalar load.
+  asm volatile("" ::"s"(q), "s"(k), "s"(v), "s"(block_idx), "s"(k_codes), "s"(k_phi), "s"(h_frag), "s"(z_total), "s"(sin.b), "s"(sin.h),
+               "s"(sin.n), "s"(H), "s"(N), "s"(Tm), "s"(Tn), "s"(ksel));
+  asm volatile("" ::"s"(k_scale), "s"(alpha), "s"(v_scale), "s"(v_codes), "s"(alpha_per_block), "s"(h_save), "s"(z_blocks));
   // Workgroups are dealt round-robin to the 8 XCDs, each with its own L2.  Consecutive query blocks of
   // a head share key/value tiles: every head is cut into 8 runs of consecutive blocks, one per XCD, and
   // all XCDs work through the heads in the same order - the tiles in flight then belong to one or two
@@ -603,14 +608,11 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
   const size_t blk0 = (size_t)bh * Tn;   // first key block of this head in the per-block arrays
   // Key block of tile s.  The indices (and the FP8 scales) are fetched one and two tiles ahead of
   // their use: a scalar load consumed right away stalls the wave for its whole latency.
-  auto tile_block = [&](int s) { return DENSE ? min(s, Tn - 1) : sel[min(s, ntiles - 1)]; };
+  auto tile_block = [&](int s) { return DENSE ? min(s, Tn - 1) : scalar_load(sel + min(s, ntiles - 1)); };
   int j_cur = ntiles > 0 ? tile_block(0) : 0, j_nxt = ntiles > 0 ? tile_block(1) : 0;
-  float sk_cur = 1.f;
-  if constexpr (FP8) sk_cur = k_scale[blk0 + j_cur];
   // FP8V: O^T is carried in units of the V scale of the tile being added (the factor between two tiles
   // joins the online-softmax correction); sv_cur is the scale of the coming tile, sv_prev of the last one
-  float sv_cur = 1.f, sv_prev = 1.f;
-  if constexpr (FP8V) sv_cur = sv_prev = ntiles > 0 ? v_scale[blk0 + j_cur] : 1.f;
+  float sk_cur = 1.f, sv_cur = 1.f, sv_prev = 1.f;
 
   // key block j: global memory -> LDS buffer `buf`, no registers involved (completion: vmcnt)
   const uint8_t* k_codes_h = FP8 ? k_codes + blk0 * (kTileTokens * D) : nullptr;
@@ -651,6 +653,18 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
     typedef SwizzledLayout<D> L;
     constexpr int kRows = 1024 / (D * 2);
     const unsigned l = lane_again();
+    if (rows_valid == BQ) {                            // two lane offsets at most, the rest is uniform
+      const uint16_t* base = qh + (size_t)(row0 + 32 * w) * tok_stride;
+      constexpr int kDiffer = kRows % 8 == 0 ? 1 : 2;  // the swizzle repeats every 8 rows
+      static_assert(kDiffer * kRows == 8, "");
+      unsigned off[kDiffer];
+#pragma unroll
+      for (int n = 0; n < kDiffer; n++)
+        off[n] = ((int)l / L::kChunks) * (unsigned)(tok_stride * 2) + 16u * (((int)l % L::kChunks) ^ L::swz(n * kRows + (int)l / L::kChunks));
+#pragma unroll
+      for (int n = 0; n < kQOps; n++) dma_lane16(base + (size_t)(n * kRows) * (unsigned)tok_stride, off[n % kDiffer], lds + n * 1024);
+      return;
+    }
 #pragma unroll
     for (int n = 0; n < kQOps; n++) {
       const int row = n * kRows + (int)l / L::kChunks;
@@ -659,14 +673,19 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
     }
   };
   // fragment ks of those rows (B operand of S^T = K Q^T): lane <- row l % 32, 8 columns from column 8 * (chunk ^ XOR(ks))
-  auto read_q = [&](unsigned lds, int chunk, int x) {
+  auto q_lane = [&](unsigned lds, int chunk) {
     typedef SwizzledLayout<D> L;
     const int row = (int)lane_again() % 32;
-    return lds_read16_untracked<0>((lds + row * (D * 2) + 16u * (chunk ^ L::swz(row))) ^ (16u * x));
+    return lds + row * (D * 2) + 16u * (chunk ^ L::swz(row));
   };
+  auto read_q = [&](unsigned at, int x) { return lds_read16_untracked<0>(at ^ (16u * x)); };
 
   // Requests in the order their results are needed and can be made: the query rows and the d x d total need nothing but
   // the block index; the tiles need the block list.
+  // Scales and alpha are asked for behind the tiles: the scalar loads return in any order, so the first one that is waited for
+  // is a wait for all of them.
+  float sk_nxt = 1.f, al;
+  const int j_third = PIPE && ntiles > 0 ? tile_block(2) : 0;
   dma_q(lds0 + SM::q_rows(w));
   // The state accumulators start at -H_total (and -Z_total): the loop adds the h_j and z_j of the selected
   // blocks, which leaves -(H_total - sum) = -H_i.  The total lies there negated and as accumulator fragments
@@ -701,8 +720,14 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
 #pragma unroll
         for (int ks = 0; ks < kSteps; ks++) dma_phi(j_cur, a, ks);
     }
+    if constexpr (FP8) sk_cur = scalar_load(k_scale + blk0 + j_cur);
+    if constexpr (FP8V) sv_cur = sv_prev = scalar_load(v_scale + blk0 + j_cur);
+    if constexpr (PIPE && FP8) sk_nxt = scalar_load(k_scale + blk0 + j_nxt);
+    al = DENSE ? 1.f : scalar_load(alpha + (alpha_per_block ? (size_t)h * Tm + i : (size_t)h));
+    __builtin_amdgcn_sched_barrier(0);
     wait_vmcnt<kDmaOps + kPhiOps>();                 // query rows and totals are there
   } else {
+    al = DENSE ? 1.f : scalar_load(alpha + (alpha_per_block ? (size_t)h * Tm + i : (size_t)h));
     wait_vmcnt<0>();
   }
   f32x16 hacc[HS::kMtw][HS::kNtw];
@@ -734,9 +759,10 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
   bf16x8 qf[KS];
   {
     u32x4 raw[KS];
+    const unsigned at = q_lane(lds0 + SM::q_rows(w), INT8 ? 2 * g : FP8 ? 4 * g : g);
 #pragma unroll
     for (int ks = 0; ks < KS; ks++)
-      raw[ks] = read_q(lds0 + SM::q_rows(w), INT8 ? 2 * g : FP8 ? 4 * g : g, INT8 ? 4 * (ks / 2) + ks % 2 : FP8 ? 8 * (ks / 4) + ks % 4 : 2 * ks);
+      raw[ks] = read_q(at, INT8 ? 4 * (ks / 2) + ks % 2 : FP8 ? 8 * (ks / 4) + ks % 4 : 2 * ks);
     wait_lgkmcnt(0);
 #pragma unroll
     for (int ks = 0; ks < KS; ks++) {
@@ -744,6 +770,12 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
       qf[ks] = __builtin_bit_cast(bf16x8, raw[ks]);
     }
   }
+  // entry e of fragment ks in fp32: a shift or a mask (from elements of the vector the compiler makes sub-dword operations, which
+  // wait for each other)
+  auto q_value = [&](int ks, int e) {
+    const unsigned two = __builtin_bit_cast(u32x4, qf[ks])[e / 2];
+    return __builtin_bit_cast(float, e % 2 == 0 ? two << 16 : two & 0xFFFF0000u);
+  };
   // FP8: quant(Q_i) with one scale for the whole query block (Sec. 5)
   long qf8[FP8 ? KS : 1];
   float s_q = 1.f;
@@ -752,7 +784,7 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
 #pragma unroll
     for (int ks = 0; ks < KS; ks++)
 #pragma unroll
-      for (int e = 0; e < 8; e++) amax = fmaxf(amax, fabsf((float)qf[ks][e]));
+      for (int e = 0; e < 8; e += 2) amax = max3_abs(amax, q_value(ks, e), q_value(ks, e + 1));
     amax = wave_max(amax);
     if (lane == 0) *reinterpret_cast<float*>(smem + SM::q_rows(w)) = amax;   // (this wave has read its rows)
     __syncthreads();
@@ -766,7 +798,7 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
     for (int ks = 0; ks < KS; ks++) {
       float y[8];
 #pragma unroll
-      for (int e = 0; e < 8; e++) y[e] = fminf(fmaxf((float)qf[ks][e] * inv, -kCodeMax), kCodeMax);
+      for (int e = 0; e < 8; e++) y[e] = fminf(fmaxf(q_value(ks, e) * inv, -kCodeMax), kCodeMax);
       int lo = 0, hi = 0;
       if constexpr (INT8) {
         lo = pack_int8(y[0], y[1], y[2], y[3]);
@@ -807,14 +839,14 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
 #pragma unroll
     for (int ks = 0; ks < KS; ks++)
 #pragma unroll
-      for (int e = 0; e < 8; e++) qm = fmaxf(qm, (float)qf[ks][e]);
+      for (int e = 0; e < 8; e++) qm = fmaxf(qm, q_value(ks, e));
     qm = swap_halves_max(qm) * kLog2e;
   };
   auto q_exp = [&](int ks) {
 #pragma unroll
     for (int x = 0; x < 2; x++) {
 #pragma unroll
-      for (int e = 0; e < 4; e++) qx[ks][x][e] = fast_exp2((float)qf[ks][4 * x + e] * kLog2e - qm);
+      for (int e = 0; e < 4; e++) qx[ks][x][e] = fast_exp2(q_value(ks, 4 * x + e) * kLog2e - qm);
       settle(qx[ks][x]);
     }
   };
@@ -823,7 +855,7 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
 
   // S^T = K Q^T on the 8-bit codes, two 32-key halves; ka: this lane's first operand in the K tile.  The callbacks run
   // behind the operand reads and behind the matrix instructions.
-  auto low_bit_scores = [&](unsigned ka, f32x16 (&sacc)[2], auto behind_reads, auto behind_products) {
+  auto low_bit_scores = [&](unsigned ka, f32x16 (&sacc)[2], auto behind_reads, auto behind_product, auto behind_products) {
     if constexpr (INT8) {
       // 32-deep integer products (v_mfma_i32_32x32x32_i8: lane l holds row l % 32, contraction indices
       // 16 (l / 32) + 0..15): the operand of (step ks4, key half mt) is 16 consecutive codes of key row
@@ -852,6 +884,7 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
           const i32x4 b = {(int)(unsigned)((unsigned long)qf8[2 * ks4]), (int)(unsigned)((unsigned long)qf8[2 * ks4] >> 32),
                            (int)(unsigned)((unsigned long)qf8[2 * ks4 + 1]), (int)(unsigned)((unsigned long)qf8[2 * ks4 + 1] >> 32)};
           iacc[mt] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, iacc[mt], 0, 0, 0);
+          if (mt == 1) behind_product(ks4);
         }
       behind_products();
 #pragma unroll
@@ -893,6 +926,7 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
             b[2 * x + 1] = (int)(unsigned)((unsigned long)qf8[4 * ks2 + x] >> 32);
           }
           sacc[mt] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, sacc[mt], 0, 0, 0, 0, 0, 0);   // e4m3 x e4m3, no scales
+          behind_product(2 * ks2 + mt);
         }
       behind_products();
     }
@@ -925,10 +959,10 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
     settle(v_lane);
     f32x16 sacc[2];
     // S^T = K Q^T of the tile in kbuf(buf), two 32-key halves
-    auto scores = [&](int buf) {
+    auto scores = [&](int buf, auto behind_reads, auto behind_product) {
       const unsigned ka = kbuf(buf) + k_lane;
       if constexpr (FP8) {
-        low_bit_scores(ka, sacc, [] {}, [] {});
+        low_bit_scores(ka, sacc, behind_reads, behind_product, [] {});
       } else {
         // the operand of (step ks, key half mt): 16 bytes of key row 32 mt + l % 32, step ks at (address of step 0) ^ 32 ks
         constexpr int kItems = 2 * KS, kAhead = 3, kSlots = kAhead + 1;
@@ -939,6 +973,7 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
         };
 #pragma unroll
         for (int n = 0; n < kAhead; n++) issue(n);
+        behind_reads();
 #pragma unroll
         for (int mt = 0; mt < 2; mt++)
 #pragma unroll
@@ -1025,45 +1060,59 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
     };
 
     int j1 = j_nxt;                                  // key block of tile s + 1
-    int j2 = ntiles > 0 ? tile_block(2) : 0;
-    float sk1 = 1.f;                                 // scale of tile s + 1
-    if constexpr (FP8) sk1 = k_scale[blk0 + j1];
+    int j2 = j_third;
+    float sk1 = sk_nxt;                              // scale of tile s + 1
     // The last tile has a copy of the pass of its own, with Q^phi in the place of the softmax - in the low-bit modes; bf16
     // operands, whose query fragments take 16 registers more, leave none for what the two copies would exchange.
     auto pass = [&](int s, auto last_pass) {
       constexpr bool LAST = decltype(last_pass)::value;
       const int buf = s & 1;
       const bool more = kPeel ? !LAST : s + 1 < ntiles;
-      if (s + 2 < ntiles) dma_k(j2, buf);
-      if (more) dma_v(j1, buf ^ 1);
-      if constexpr (LAST) dma_q(q_again(buf));
+      // In the low-bit modes the requests and the rescale of O^T stand in the score product, behind its operand reads and its four
+      // 64-cycle instructions, which leave the issue port to them: ahead of it they held up the wave by some 400 cycles of 3,900 a pass
+      // (us: FP8, 12 heads of 32,760 tokens 412.7 -> 407.8, 40 of 75,600 5,700 -> 5,622).  bf16 tensors rescale rarely, and have no gain.
       float zj[HS::kMtw];
-#pragma unroll
-      for (int a = 0; a < HS::kMtw; a++)
-        zj[a] = load_untracked_at(z_blocks + (blk0 + j_cur) * D + 32 * (mt0 + a), (lane16 >> 2) & 124u);
-      const int j3 = tile_block(s + 3);              // indices and scales are fetched a pass ahead of their use
+      int j3;
       float sk2 = 1.f, sv1 = 1.f;
-      if constexpr (FP8) sk2 = k_scale[blk0 + j2];
-      if constexpr (FP8V) sv1 = v_scale[blk0 + j1];
-      if constexpr (FP8V) {
-        // O^T is carried in units of the V scale of the tile being added
-        const float co = corr * (sv_prev / sv_cur);
+      auto requests = [&]() {
+        if (s + 2 < ntiles) dma_k(j2, buf);
+        if (more) dma_v(j1, buf ^ 1);
+        if constexpr (LAST) dma_q(q_again(buf));
 #pragma unroll
-        for (int et = 0; et < ET; et++)
+        for (int a = 0; a < HS::kMtw; a++)
+          zj[a] = load_untracked_at(z_blocks + (blk0 + j_cur) * D + 32 * (mt0 + a), (lane16 >> 2) & 124u);
+        j3 = tile_block(s + 3);                        // indices and scales are fetched a pass ahead of their use
+        if constexpr (FP8) sk2 = scalar_load(k_scale + blk0 + j2);
+        if constexpr (FP8V) sv1 = scalar_load(v_scale + blk0 + j1);
+      };
+      // O^T in units of the new reference, 32 channels at a time
+      const float co = FP8V ? corr * (sv_prev / sv_cur) : corr;
+      auto rescale_o = [&](int et) {
+        if (FP8V || rescale)
 #pragma unroll
           for (int e = 0; e < 16; e++) oacc[et][e] *= co;
+      };
+      if (FP8 && !LAST) {
+        scores(buf ^ 1,
+               [&] {
+                 requests();
+                 rescale_o(0);
+               },
+               [&](int n) {
+                 if (n + 1 < ET) rescale_o(n + 1);
+                 __builtin_amdgcn_sched_barrier(0);
+               });
+      } else {
+        requests();
+#pragma unroll
+        for (int et = 0; et < ET; et++) rescale_o(et);
+        if (more) scores(buf ^ 1, [] {}, [](int) {});
+      }
+      if constexpr (FP8V) {
         sv_prev = sv_cur;
         sv_cur = sv1;
-      } else if (rescale) {
-#pragma unroll
-        for (int et = 0; et < ET; et++)
-#pragma unroll
-          for (int e = 0; e < 16; e++) oacc[et][e] *= corr;
       }
-      if (more) {
-        scores(buf ^ 1);
-        mask_tail(N - j1 * kTileTokens);
-      }
+      if (more) mask_tail(N - j1 * kTileTokens);
       c1 = FP8 ? c0 * s_q * sk1 : c0;
       // the K^phi fragments of this tile have landed
       if constexpr (LAST) wait_vmcnt<kQOps + HS::kMtw>();
@@ -1118,8 +1167,9 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
         constexpr int f = decltype(frag)::value, ks = f / ET, et = f % ET;
         if (LAST && f == kQFrom - 1) {
           wait_vmcnt<HS::kMtw>();
+          const unsigned at = q_lane(q_again(buf), g);
 #pragma unroll
-          for (int x = 0; x < KS; x++) raw[x] = read_q(q_again(buf), g, 2 * x);
+          for (int x = 0; x < KS; x++) raw[x] = read_q(at, 2 * x);
           q_at = issued += KS;
         }
         // K^phi of the next step before the V fragment it meets first: the wait for that one covers both
@@ -1193,7 +1243,7 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
       sk1 = sk2;
     };
     if (ntiles > 0) {
-      scores(0);
+      scores(0, [] {}, [](int) {});
       c1 = FP8 ? c0 * s_q * sk_cur : c0;             // dequantisation folded into the score scale
       mask_tail(N - j_cur * kTileTokens);
       soft_max(0);
@@ -1216,9 +1266,9 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
       const int valid = min(kTileTokens, N - j * kTileTokens);
       const float sk = sk_cur;
       const int j_nn = tile_block(s + 2);                // consumed in the next iteration
-      if constexpr (FP8) sk_cur = k_scale[blk0 + j_nxt];
+      if constexpr (FP8) sk_cur = scalar_load(k_scale + blk0 + j_nxt);
       const float sv = sv_cur;
-      if constexpr (FP8V) sv_cur = v_scale[blk0 + j_nxt];
+      if constexpr (FP8V) sv_cur = scalar_load(v_scale + blk0 + j_nxt);
       // K^phi fragments and z_j of this tile straight from global memory into registers (no other
       // wave needs them); they are consumed after the softmax.  They are issued before the next
       // tile's transfer and, since vmcnt retires in order, are complete once at most kDmaOps
@@ -1258,7 +1308,7 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
       // ---- S^T = K Q^T (keys x query rows), two 32-key halves ----
       f32x16 sacc[2];
       if constexpr (FP8) {
-        low_bit_scores(kbuf(buf) + SL8::offset(lane % 32, (INT8 ? 16 : 32) * g), sacc, state_loads, next_tile);
+        low_bit_scores(kbuf(buf) + SL8::offset(lane % 32, (INT8 ? 16 : 32) * g), sacc, state_loads, [](int) {}, next_tile);
       } else {
         const uint16_t* kt = reinterpret_cast<const uint16_t*>(smem + SM::kKOff + buf * SM::kKBytes);
 #pragma unroll
@@ -1436,8 +1486,9 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
       dma_q(q_again(0));
       wait_vmcnt<0>();
       u32x4 raw[KS];
+      const unsigned at = q_lane(q_again(0), g);
 #pragma unroll
-      for (int ks = 0; ks < KS; ks++) raw[ks] = read_q(q_again(0), g, 2 * ks);
+      for (int ks = 0; ks < KS; ks++) raw[ks] = read_q(at, 2 * ks);
       wait_lgkmcnt(0);
 #pragma unroll
       for (int ks = 0; ks < KS; ks++) {
@@ -1522,7 +1573,6 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
     inv_den = ksel >= Tn ? 0.f : 1.f / den;          // every block selected: nothing left for the linear branch
   }
   // ---- mix (Eq. 13), transpose through LDS, coalesced store ----
-  const float al = DENSE ? 1.f : alpha[alpha_per_block ? (size_t)h * Tm + i : (size_t)h];
   const float ws = al * inv_l * (FP8V ? sv_prev : 1.f), wl = (1.f - al) * inv_den;   // FP8V: back from the last tile's V scale
 #pragma unroll
   for (int et = 0; et < ET; et++)
