@@ -131,16 +131,18 @@ __global__ __launch_bounds__(BQ * 2, 2) void bwd_q_mfma_kernel(
     };
     turned(qr, qf);
     turned(gr, gof);
+    float dots[kLoads];
 #pragma unroll
     for (int x = 0; x < kLoads; x++) {
       const bf16x8 go = __builtin_bit_cast(bf16x8, gr[x]), os = __builtin_bit_cast(bf16x8, sr[x]);
       float part = 0.f;
 #pragma unroll
       for (int e = 0; e < 8; e++) part += (float)go[e] * (float)os[e];
-#pragma unroll
-      for (int o = 1; o < kChunks; o <<= 1) part += __shfl_xor(part, o);
-      if (ch == 0) dls[first + kRows * x] = part;
+      dots[x] = row_sum<kChunks>(part);
     }
+    if (ch == 0)
+#pragma unroll
+      for (int x = 0; x < kLoads; x++) dls[first + kRows * x] = dots[x];
     wave_lds_fence();
     dot_s = dls[qrow];
     wave_lds_fence();
@@ -159,7 +161,7 @@ __global__ __launch_bounds__(BQ * 2, 2) void bwd_q_mfma_kernel(
 #pragma unroll
     for (int e = 0; e < 8; e++) qmu += (float)qf[ks][e] * (e < 4 ? m0[e] : m1[e - 4]);
   }
-  qmu = half_sum(qmu);
+  qmu = swap_halves_sum(qmu);
   const float Lraw = L + qmu * rscale;
   const float L2 = Lraw * kLog2e;
   if (g == 0) {                                      // as the key-side kernel uses them: L on the raw keys, times log2(e);
@@ -186,7 +188,7 @@ __global__ __launch_bounds__(BQ * 2, 2) void bwd_q_mfma_kernel(
 #pragma unroll
     for (int e = 0; e < 8; e++) qm = fmaxf(qm, (float)qf[ks][e]);
   }
-  qm = half_max(qm);
+  qm = swap_halves_max(qm);
   float qs = 0.f;
 #pragma unroll
   for (int ks = 0; ks < KS; ks++) {
@@ -198,7 +200,7 @@ __global__ __launch_bounds__(BQ * 2, 2) void bwd_q_mfma_kernel(
     }
     settle(ef[ks]);
   }
-  qs = half_sum(qs);
+  qs = swap_halves_sum(qs);
   const float qinv = 1.f / qs;
   float den = 0.f;
 #pragma unroll
@@ -208,7 +210,7 @@ __global__ __launch_bounds__(BQ * 2, 2) void bwd_q_mfma_kernel(
 #pragma unroll
     for (int e = 0; e < 8; e++) den += (float)ef[ks][e] * (e < 4 ? z0[e] : z1[e - 4]);
   }
-  den = half_sum(den) * qinv;
+  den = swap_halves_sum(den) * qinv;
   // every block selected: the linear branch receives and passes no gradient
   const float inv_den = (ksel >= Tn || !row_ok) ? 0.f : 1.f / den;
   // w as a [row][c] tile (zero rows past the end); the softmax-backward step reads Q^phi = w den back
@@ -250,13 +252,12 @@ __global__ __launch_bounds__(BQ * 2, 2) void bwd_q_mfma_kernel(
     }
   wave_lds_fence();                                  // w is read again below rather than kept in registers
   settle(quarter);
-  dot_l = half_sum(dot_l);
+  dot_l = swap_halves_sum(dot_l);
   const float Dl = (1.f - al) * dot_l;
   if (g == 0) dls[qrow] = Dl;
   {
     float mix = (row_ok && g == 0) ? dot_s - dot_l : 0.f;
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) mix += __shfl_xor(mix, o);
+    mix = wave_sum(mix);
     if (lane == 0) red[w] = mix;
   }
   float dot = 0.f;
@@ -272,7 +273,7 @@ __global__ __launch_bounds__(BQ * 2, 2) void bwd_q_mfma_kernel(
         dot += dqacc[ct][4 * v4 + r] * ((float)wq[r] * den);
       }
     }
-  dot = half_sum(dot);
+  dot = swap_halves_sum(dot);
   settle(quarter);
   const float unscale = sqrtf((float)D);             // the loop's sums are scaled by 1 / sqrt(d) at the end
 #pragma unroll
@@ -329,7 +330,7 @@ __global__ __launch_bounds__(BQ * 2, 2) void bwd_q_mfma_kernel(
         for (int e = 0; e < 8; e++) o[e] = (__bf16)(dh_scale * acc[y][8 * half + e]);
         *reinterpret_cast<bf16x8*>(dh_slot + (((t0 + y) * 2 + half) * kWave + lane) * 8) = o;
       }
-    dz = half_sum(dz);
+    dz = swap_halves_sum(dz);
     if (et0 == 0 && g == 0) dz_out[slot * D + 32 * ct + lane] = dz;
   }
   __syncthreads();                                   // w and dO consumed
@@ -448,7 +449,7 @@ __global__ __launch_bounds__(BQ * 2, 2) void bwd_q_mfma_kernel(
 
   // ================= epilogue =================
   // dS K' = dS K - rowsum(dS) colmean(K)^T; transposed through LDS for a coalesced store of the wave's own rows
-  sumds = half_sum(sumds);
+  sumds = swap_halves_sum(sumds);
   const int ln = (int)lane_again();                  // addresses are made here, not kept from the start of the kernel
   const unsigned row_at = 2u * (unsigned)SL::offset(32 * w + ln % 32, 4 * (ln / 32));
 #pragma unroll
@@ -555,7 +556,6 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void bwd_kv_mfma_kernel(
   const int kh = w >> 1, rh = w & 1;                 // rh: also the half of the channel tiles finished after the loop
   const int t0 = j * kTileTokens, valid = min(kTileTokens, N - t0);
   const int mykey = 32 * kh + lane % 32;             // this lane's key inside the block
-  const bool key_ok = mykey < valid;
   const uint16_t* qh = q + head_offset(sin, bh, H);
   const uint16_t* kh_ = k + head_offset(sin, bh, H);
   const uint16_t* vh = v + head_offset(sin, bh, H);
@@ -643,7 +643,8 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void bwd_kv_mfma_kernel(
     }
     wait_vmcnt<0>();
     __syncthreads();                                 // K_j, V_j, dH, parts of dZ_j and mus are in LDS for everyone
-    // K^phi_j = exp(K - colmean(K) - lnZ) (keys past the end: 0)
+    // K^phi_j = exp(K - colmean(K) - lnZ).  (Keys past the end repeat the last one here and need no zeros, see the loop; asked for, they
+    // became a branch around every exponential.)
     bf16x8 pfr[KS];
 #pragma unroll
     for (int ks = 0; ks < KS; ks++) {
@@ -653,7 +654,7 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void bwd_kv_mfma_kernel(
       const f32x4 m1 = *reinterpret_cast<const f32x4*>(mus + 16 * ks + 8 * g + 4);
 #pragma unroll
       for (int e = 0; e < 8; e++)
-        pfr[ks][e] = (__bf16)(key_ok ? fast_exp2(((float)kfr[ks][e] - (e < 4 ? m0[e] : m1[e - 4])) * kLog2e - lnz2) : 0.f);
+        pfr[ks][e] = (__bf16)fast_exp2(((float)kfr[ks][e] - (e < 4 ? m0[e] : m1[e - 4])) * kLog2e - lnz2);
       settle(pfr[ks]);                               // one fragment at a time: the registers
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -689,12 +690,12 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void bwd_kv_mfma_kernel(
         for (int n = 1; n < kParts; n++) dz += *reinterpret_cast<const f32x4*>(stat + n * D + c);
 #pragma unroll
         for (int r = 0; r < 4; r++) {
-          kp[y][4 * v4 + r] = (float)(__bf16)(key_ok ? fast_exp2(((float)kk[r] - m[r]) * kLog2e - lnz2) : 0.f);
+          kp[y][4 * v4 + r] = (float)(__bf16)fast_exp2(((float)kk[r] - m[r]) * kLog2e - lnz2);
           dkp[y][4 * v4 + r] += dz[r];
           part += dkp[y][4 * v4 + r] * kp[y][4 * v4 + r];
         }
       }
-      part = half_sum(part);
+      part = swap_halves_sum(part);
       if (g == 0) dred[ct * 64 + mykey] = part;
     }
     __syncthreads();                                 // row sums complete; the tiles have been read
