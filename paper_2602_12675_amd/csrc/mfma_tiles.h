@@ -341,6 +341,11 @@ __device__ __forceinline__ u32x4 lds_read16_untracked_at(unsigned addr, int n) {
     default: return lds_read16_untracked<3 * UNIT>(addr);
   }
 }
+__device__ __forceinline__ u32x2 lds_read8_untracked(unsigned addr) {
+  u32x2 r;
+  asm volatile("ds_read_b64 %0, %1" : "=v"(r) : "v"(addr));
+  return r;
+}
 template <int OFF>    // transposing read, see read_tr4
 __device__ __forceinline__ u32x2 lds_read_tr_untracked(unsigned addr) {
   u32x2 r;
@@ -383,5 +388,25 @@ __device__ __forceinline__ void wait_lgkmcnt(int n) {
     default: asm volatile("s_waitcnt lgkmcnt(0)"); break;
   }
 }
+
+// use(n, 16 bytes at base + OFF::at(n)) for n = 0 .. N - 1, AHEAD reads in flight: left to the compiler each is waited for right where it
+// is used, a round trip to LDS (some 130 cycles) for four multiply-adds.
+template <class OFF, int N, int AHEAD, class Use>
+__device__ __forceinline__ void lds_stream(unsigned base, Use use) {
+  u32x4 ring[AHEAD + 1];
+  unrolled<N + AHEAD>([&](auto i) {
+    constexpr int n = decltype(i)::value, m = n - AHEAD;
+    if constexpr (n < N) ring[n % (AHEAD + 1)] = lds_read16_untracked<OFF::at(n)>(base);
+    if constexpr (m >= 0) {
+      wait_lgkmcnt(N - 1 - m < AHEAD ? N - 1 - m : AHEAD);
+      settle(ring[m % (AHEAD + 1)]);
+      use(std::integral_constant<int, m>(), ring[m % (AHEAD + 1)]);
+    }
+  });
+}
+// fp32 per channel, for a lane that holds channels 16 ks + 8 g + 0..7 (fragments): base at channel 8 g, read 2 ks + x
+struct FragmentChannels { static constexpr int at(int n) { return 64 * (n / 2) + 16 * (n % 2); } };
+// the same for a lane that holds channels 8 c + 4 g + 0..3 (accumulators): base at channel 4 g, read c
+struct AccumulatorChannels { static constexpr int at(int n) { return 32 * n; } };
 
 }  // namespace sla2

@@ -153,14 +153,19 @@ __global__ __launch_bounds__(BQ * 2, 2) void bwd_q_mfma_kernel(
   __syncthreads();                                   // ... for everyone; mus is visible
   // The forward pass defines L on the smoothed keys; the products below use the raw K, whose scores are
   // larger by q . colmean(K) / sqrt(d) in every column of a row.
+  f32x4 qx[KS][2];                                   // the row in fp32, taken apart once: Q, then Q^phi without its normaliser
   float qmu = 0.f;
+  lds_stream<FragmentChannels, 2 * KS, 8>(lds_address(mus + 8 * g), [&](auto n, const u32x4& raw) {
+    constexpr int ks = decltype(n)::value / 2, x = decltype(n)::value % 2;
+    const u32x4 two = __builtin_bit_cast(u32x4, qf[ks]);
+    const f32x4 m = __builtin_bit_cast(f32x4, raw);
 #pragma unroll
-  for (int ks = 0; ks < KS; ks++) {
-    const f32x4 m0 = *reinterpret_cast<const f32x4*>(mus + 16 * ks + 8 * g);
-    const f32x4 m1 = *reinterpret_cast<const f32x4*>(mus + 16 * ks + 8 * g + 4);
-#pragma unroll
-    for (int e = 0; e < 8; e++) qmu += (float)qf[ks][e] * (e < 4 ? m0[e] : m1[e - 4]);
-  }
+    for (int e = 0; e < 4; e++) {
+      qx[ks][x][e] = __builtin_bit_cast(float, e % 2 == 0 ? two[2 * x + e / 2] << 16 : two[2 * x + e / 2] & 0xFFFF0000u);
+      qmu += qx[ks][x][e] * m[e];
+    }
+    settle(qx[ks][x]);
+  });
   qmu = swap_halves_sum(qmu);
   const float Lraw = L + qmu * rscale;
   const float L2 = Lraw * kLog2e;
@@ -173,55 +178,46 @@ __global__ __launch_bounds__(BQ * 2, 2) void bwd_q_mfma_kernel(
   // First, while the scores of the loop take no registers: behind the loop it spilled up to a hundred, each waited for by itself.
   // 12 heads of 32,760 tokens: 438 -> 385 us with 15 tiles a block, 250 -> 177 without any (0.6 GB at 3.4 TB/s); 32 heads of
   // 4,096, d = 64, 64-row blocks: 56 -> 51 us.
+  // What it costs is vector instructions and round trips to LDS: Q taken apart once, exponentials in place, what is read per channel kept
+  // in flight (lds_stream), no second term of the softmax-backward step.  Training step, us: 1,472.6 -> 1,455.7 and 200.5 -> 198.7.
   uint16_t* ta = kbuf(1);                                           // H_i^T [e][c]; then dO [row][e]
   uint16_t* tb = kbuf(0);                                           // w = Q^phi / (Q^phi Z_i) as [row][c]
   // Byte offsets of this lane's row: 16 bytes of channels 16 ks + 8 g .. at (full) ^ 32 ks, 8 of 8 c + 4 g .. at (quarter) ^ 16 c
   // (made opaque before every loop over them: sixteen addresses are not to be kept)
   unsigned full = 2u * (unsigned)SL::offset(qrow, 8 * g), quarter = 2u * (unsigned)SL::offset(qrow, 4 * g);
   unsigned char *pa = reinterpret_cast<unsigned char*>(ta), *pb = reinterpret_cast<unsigned char*>(tb);
-  // Q^phi = softmax_d(Q) of this lane's row from the Q fragments (channels 16 ks + 8 g + 0..7); as
-  // exp(q - max), the normalisation is applied where they are used
-  bf16x8 ef[KS];
+  // Q^phi = softmax_d(Q) of this lane's row (channels 16 ks + 8 g + 0..7) as exp(q - max); the normalisation is applied where it is
+  // used
   float qm = -INFINITY;
 #pragma unroll
-  for (int ks = 0; ks < KS; ks++) {
+  for (int ks = 0; ks < KS; ks++)
 #pragma unroll
-    for (int e = 0; e < 8; e++) qm = fmaxf(qm, (float)qf[ks][e]);
-  }
-  qm = swap_halves_max(qm);
-  float qs = 0.f;
+    for (int e = 0; e < 8; e++) qm = fmaxf(qm, qx[ks][e / 4][e % 4]);
+  qm = swap_halves_max(qm) * kLog2e;
+  float qs = 0.f, den = 0.f;
+  lds_stream<FragmentChannels, 2 * KS, 8>(lds_address(zs + 8 * g), [&](auto n, const u32x4& raw) {
+    constexpr int ks = decltype(n)::value / 2, x = decltype(n)::value % 2;
+    const f32x4 z = __builtin_bit_cast(f32x4, raw);
 #pragma unroll
-  for (int ks = 0; ks < KS; ks++) {
-#pragma unroll
-    for (int e = 0; e < 8; e++) {
-      const float x = fast_exp2(((float)qf[ks][e] - qm) * kLog2e);
-      qs += x;
-      ef[ks][e] = (__bf16)x;
+    for (int e = 0; e < 4; e++) {
+      qx[ks][x][e] = fast_exp2(qx[ks][x][e] * kLog2e - qm);
+      qs += qx[ks][x][e];
+      den += qx[ks][x][e] * z[e];
     }
-    settle(ef[ks]);
-  }
-  qs = swap_halves_sum(qs);
-  const float qinv = 1.f / qs;
-  float den = 0.f;
-#pragma unroll
-  for (int ks = 0; ks < KS; ks++) {
-    const f32x4 z0 = *reinterpret_cast<const f32x4*>(zs + 16 * ks + 8 * g);
-    const f32x4 z1 = *reinterpret_cast<const f32x4*>(zs + 16 * ks + 8 * g + 4);
-#pragma unroll
-    for (int e = 0; e < 8; e++) den += (float)ef[ks][e] * (e < 4 ? z0[e] : z1[e - 4]);
-  }
+    settle(qx[ks][x]);
+  });
+  const float qinv = 1.f / swap_halves_sum(qs);
   den = swap_halves_sum(den) * qinv;
   // every block selected: the linear branch receives and passes no gradient
   const float inv_den = (ksel >= Tn || !row_ok) ? 0.f : 1.f / den;
-  // w as a [row][c] tile (zero rows past the end); the softmax-backward step reads Q^phi = w den back
-  // from it in the layout of the accumulators
+  // w as a [row][c] tile (zero rows past the end); the softmax-backward step reads it back in the layout of the accumulators
   {
     const float wscale = qinv * inv_den;
 #pragma unroll
     for (int ks = 0; ks < KS; ks++) {
       bf16x8 wv;
 #pragma unroll
-      for (int e = 0; e < 8; e++) wv[e] = (__bf16)((float)ef[ks][e] * wscale);
+      for (int e = 0; e < 8; e++) wv[e] = (__bf16)(qx[ks][e / 4][e % 4] * wscale);
       *reinterpret_cast<bf16x8*>(pb + (full ^ (32u * ks))) = wv;
     }
   }
@@ -232,27 +228,52 @@ __global__ __launch_bounds__(BQ * 2, 2) void bwd_q_mfma_kernel(
   for (int ct = 0; ct < ET; ct++)
 #pragma unroll
     for (int e = 0; e < 16; e++) dqacc[ct][e] = 0.f;
+  // (fragment ks ET + ct: two transposing reads, kept kAhead fragments ahead, cf. nat_fragment; left to the compiler each is waited
+  // for right in front of its product)
+  const int tr_row = (lane % 16) / 4, tr_col = 16 * ((lane / 16) % 2) + 4 * (lane % 4);
+  {
+    constexpr int kFrags = KS * ET, kAhead = 4, kSlots = kAhead + 1;
+    const unsigned at[2] = {lds_address(ta + SL::offset(8 * g + tr_row, tr_col)), lds_address(ta + SL::offset(8 * g + 4 + tr_row, tr_col))};
+    u32x2 ring[kSlots][2];
+    auto issue = [&](int n) {
 #pragma unroll
-  for (int ks = 0; ks < KS; ks++) {
+      for (int y = 0; y < 2; y++) ring[n % kSlots][y] = lds_read_tr_untracked_at<32 * D>(at[y] ^ (64u * (n % ET)), n / ET);
+    };
 #pragma unroll
-    for (int ct = 0; ct < ET; ct++) dqacc[ct] = mfma_bf16(nat_fragment<SL>(ta, ks, 32 * ct, lane), gof[ks], dqacc[ct]);
+    for (int n = 0; n < kAhead; n++) issue(n);
+#pragma unroll
+    for (int n = 0; n < kFrags; n++) {
+      if (n + kAhead < kFrags) issue(n + kAhead);
+      wait_lgkmcnt(2 * (n + kAhead < kFrags ? kAhead : kFrags - 1 - n));
+      settle(ring[n % kSlots][0]);
+      settle(ring[n % kSlots][1]);
+      const u32x4 a = {ring[n % kSlots][0][0], ring[n % kSlots][0][1], ring[n % kSlots][1][0], ring[n % kSlots][1][1]};
+      dqacc[n % ET] = mfma_bf16(__builtin_bit_cast(bf16x8, a), gof[n / ET], dqacc[n % ET]);
+    }
   }
   wave_lds_fence();                                  // (w rows: the wave's own)
   settle(quarter);
   // O^l is not kept by the forward pass: dO . O^l of a row equals sum_c w[r][c] (H_i dO^T)[c][r], both at
   // hand.  D^l = (1 - alpha) dO . O^l; the row's part of d alpha is dO . (O^s - O^l).
-  float dot_l = 0.f;
+  u32x2 wq[4 * ET];                                  // w in the layout of the accumulators
 #pragma unroll
-  for (int ct = 0; ct < ET; ct++)
+  for (int c = 0; c < 4 * ET; c++) wq[c] = lds_read8_untracked(lds_address(pb) + (quarter ^ (16u * c)));
+  wait_lgkmcnt(0);
 #pragma unroll
-    for (int v4 = 0; v4 < 4; v4++) {
-      const bf16x4 wq = *reinterpret_cast<const bf16x4*>(pb + (quarter ^ (16u * (4 * ct + v4))));
+  for (int c = 0; c < 4 * ET; c++) settle(wq[c]);
+  auto w_value = [&](int c, int r) { return __builtin_bit_cast(float, r % 2 == 0 ? wq[c][r / 2] << 16 : wq[c][r / 2] & 0xFFFF0000u); };
+  float dot_l = 0.f, wz = 0.f;
+  lds_stream<AccumulatorChannels, 4 * ET, 8>(lds_address(zs + 4 * g), [&](auto n, const u32x4& raw) {
+    constexpr int ct = decltype(n)::value / 4, v4 = decltype(n)::value % 4;
+    const f32x4 z = __builtin_bit_cast(f32x4, raw);
 #pragma unroll
-      for (int r = 0; r < 4; r++) dot_l += (float)wq[r] * dqacc[ct][4 * v4 + r];
+    for (int r = 0; r < 4; r++) {
+      dot_l += w_value(4 * ct + v4, r) * dqacc[ct][4 * v4 + r];
+      wz += w_value(4 * ct + v4, r) * z[r];
     }
-  wave_lds_fence();                                  // w is read again below rather than kept in registers
-  settle(quarter);
-  dot_l = swap_halves_sum(dot_l);
+  });
+  wz = swap_halves_sum(wz);                          // 1 but for the rounding of w, which is taken out again (a row of zeros stays 0)
+  dot_l = swap_halves_sum(dot_l) * (wz != 0.f ? 1.f / wz : 0.f);
   const float Dl = (1.f - al) * dot_l;
   if (g == 0) dls[qrow] = Dl;
   {
@@ -260,31 +281,18 @@ __global__ __launch_bounds__(BQ * 2, 2) void bwd_q_mfma_kernel(
     mix = wave_sum(mix);
     if (lane == 0) red[w] = mix;
   }
-  float dot = 0.f;
-#pragma unroll
-  for (int ct = 0; ct < ET; ct++)
-#pragma unroll
-    for (int v4 = 0; v4 < 4; v4++) {
-      const f32x4 z = *reinterpret_cast<const f32x4*>(zs + 32 * ct + 8 * v4 + 4 * g);
-      const bf16x4 wq = *reinterpret_cast<const bf16x4*>(pb + (quarter ^ (16u * (4 * ct + v4))));
-#pragma unroll
-      for (int r = 0; r < 4; r++) {
-        dqacc[ct][4 * v4 + r] = ((1.f - al) * dqacc[ct][4 * v4 + r] - Dl * z[r]) * inv_den;
-        dot += dqacc[ct][4 * v4 + r] * ((float)wq[r] * den);
-      }
-    }
-  dot = swap_halves_sum(dot);
-  settle(quarter);
+  // dQ^phi = ((1 - alpha) H_i dO - D^l Z_i) / (Q^phi Z_i) is orthogonal to Q^phi: O^l does not change with the length of Q^phi.  So the
+  // softmax-backward step, Q^phi (.) (dQ^phi - <dQ^phi, Q^phi>), has no second term, and Q^phi / (Q^phi Z_i) is w.  With D^l formed
+  // as above that holds for the rounded w too.
   const float unscale = sqrtf((float)D);             // the loop's sums are scaled by 1 / sqrt(d) at the end
+  const float from_h = (1.f - al) * unscale, from_z = Dl * unscale;
+  lds_stream<AccumulatorChannels, 4 * ET, 8>(lds_address(zs + 4 * g), [&](auto n, const u32x4& raw) {
+    constexpr int ct = decltype(n)::value / 4, v4 = decltype(n)::value % 4;
+    const f32x4 z = __builtin_bit_cast(f32x4, raw);
 #pragma unroll
-  for (int ct = 0; ct < ET; ct++)
-#pragma unroll
-    for (int v4 = 0; v4 < 4; v4++) {                 // softmax-backward(dQ^phi)
-      const bf16x4 wq = *reinterpret_cast<const bf16x4*>(pb + (quarter ^ (16u * (4 * ct + v4))));
-#pragma unroll
-      for (int r = 0; r < 4; r++)
-        dqacc[ct][4 * v4 + r] = (float)wq[r] * den * (dqacc[ct][4 * v4 + r] - dot) * unscale;
-    }
+    for (int r = 0; r < 4; r++) dqacc[ct][4 * v4 + r] = w_value(4 * ct + v4, r) * (from_h * dqacc[ct][4 * v4 + r] - from_z * z[r]);
+    if (v4 == 3) settle(dqacc[ct]);                  // here: moved behind the products below, its operands go through scratch memory
+  });
   __syncthreads();                                   // nobody reads H_i^T any more
 #pragma unroll
   for (int ks = 0; ks < KS; ks++) *reinterpret_cast<bf16x8*>(pa + (full ^ (32u * ks))) = gof[ks];   // dO as [row][e]
@@ -312,14 +320,36 @@ __global__ __launch_bounds__(BQ * 2, 2) void bwd_q_mfma_kernel(
 #pragma unroll
       for (int e = 0; e < 16; e++) acc[y][e] = 0.f;
     float dz = 0.f;
+    // fragments in turn: w of a step of 16 rows, then dO of the tiles (cf. v_fragment)
+    constexpr int kPer = 1 + kEts, kFrags = BQ / 16 * kPer, kAhead = 4, kSlots = kAhead + 1;
+    const unsigned at[2] = {2u * (unsigned)SL::offset(4 * g + tr_row, tr_col), 2u * (unsigned)SL::offset(4 * g + 8 + tr_row, tr_col)};
+    const unsigned w_at = lds_address(tb), g_at = lds_address(ta);
+    u32x2 ring[kSlots][2];
+    auto issue = [&](int n) {
+      const int y = n % kPer;
 #pragma unroll
-    for (int ks = 0; ks < BQ / 16; ks++) {
-      const bf16x8 wf = v_fragment<SL>(tb, ks, 32 * ct, lane);
+      for (int hi = 0; hi < 2; hi++)
+        ring[n % kSlots][hi] = lds_read_tr_untracked_at<32 * D>(y == 0 ? (w_at + at[hi]) ^ (64u * ct) : (g_at + at[hi]) ^ (64u * et0) ^ (64u * (y - 1)), n / kPer);
+    };
+    bf16x8 wf;
 #pragma unroll
-      for (int y = 0; y < kEts; y++) acc[y] = mfma_bf16(v_fragment<SL>(ta, ks, 32 * (et0 + y), lane), wf, acc[y]);
-      const f32x4 d0 = *reinterpret_cast<const f32x4*>(dls + 16 * ks + 4 * g), d1 = *reinterpret_cast<const f32x4*>(dls + 16 * ks + 8 + 4 * g);
+    for (int n = 0; n < kAhead; n++) issue(n);
 #pragma unroll
-      for (int e = 0; e < 8; e++) dz -= (float)wf[e] * (e < 4 ? d0[e] : d1[e - 4]);
+    for (int n = 0; n < kFrags; n++) {
+      if (n + kAhead < kFrags) issue(n + kAhead);
+      wait_lgkmcnt(2 * (n + kAhead < kFrags ? kAhead : kFrags - 1 - n));
+      settle(ring[n % kSlots][0]);
+      settle(ring[n % kSlots][1]);
+      const u32x4 a = {ring[n % kSlots][0][0], ring[n % kSlots][0][1], ring[n % kSlots][1][0], ring[n % kSlots][1][1]};
+      const int y = n % kPer;
+      if (y > 0) {
+        acc[y - 1] = mfma_bf16(__builtin_bit_cast(bf16x8, a), wf, acc[y - 1]);
+      } else {
+        wf = __builtin_bit_cast(bf16x8, a);
+        const f32x4 d0 = *reinterpret_cast<const f32x4*>(dls + 16 * (n / kPer) + 4 * g), d1 = *reinterpret_cast<const f32x4*>(dls + 16 * (n / kPer) + 8 + 4 * g);
+#pragma unroll
+        for (int e = 0; e < 8; e++) dz -= __builtin_bit_cast(float, e % 2 == 0 ? a[e / 2] << 16 : a[e / 2] & 0xFFFF0000u) * (e < 4 ? d0[e] : d1[e - 4]);
+      }
     }
 #pragma unroll
     for (int y = 0; y < kEts; y++)
@@ -340,8 +370,7 @@ __global__ __launch_bounds__(BQ * 2, 2) void bwd_q_mfma_kernel(
   // l % 32, channel step ks at (offset of step 0) ^ 32 ks) and transposing reads (cf. read_tr4): rows 4 g + (l % 16) / 4 (lo)
   // and 8 further (hi), channel tile et at (offset of tile 0) ^ 64 et, 16-token step ks 32 D ks further
   const unsigned b_off = (unsigned)SL::offset(lane % 32, 8 * g) * 2;
-  const int tr_row = 4 * g + (lane % 16) / 4, tr_col = 16 * ((lane / 16) % 2) + 4 * (lane % 4);
-  const unsigned a_off[2] = {(unsigned)SL::offset(tr_row, tr_col) * 2, (unsigned)SL::offset(tr_row + 8, tr_col) * 2};
+  const unsigned a_off[2] = {(unsigned)SL::offset(4 * g + tr_row, tr_col) * 2, (unsigned)SL::offset(4 * g + tr_row + 8, tr_col) * 2};
   __builtin_amdgcn_s_waitcnt(kVmcnt0);               // tile 0 has landed ...
   __syncthreads();                                   // ... for everyone
   float sumds = 0.f;
