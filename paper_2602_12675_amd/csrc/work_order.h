@@ -10,17 +10,30 @@ namespace sla2 {
 // late runs on alone.  So the long ones go first, longest first over all heads.  The others follow head by head, in groups
 // of heads whose gathered rows fit the caches, again longest first: neighbouring key blocks are selected by the same query
 // blocks, whose rows they gather.  Every head is cut into 8 runs of consecutive key blocks, one per XCD (workgroup p runs
-// on XCD p % 8).  With the groups alone the long lists of the last one kept a fifth of the CUs waiting (in a model of the
-// 64 places of each XCD the last one ended at 1.54 times the mean, with the long lists first at 1.12): training step on
-// such lists 1,747 -> 1,691 us, on 20 heads of 75,600 tokens 11.86 -> 11.60 ms.
+// on XCD p % 8), run y of head h on XCD (y + h) % 8: how often a key block is selected goes with its place in the sequence, and
+// with the same run of every head on one XCD the fullest had 5 % more to do than the mean.  The last group takes at least four
+// rounds of the 64 places of an XCD: what it ends in is the length of its shortest lists.  12 heads of 512 key blocks, the
+// workgroups' times replayed: the last one ends at 1.035 instead of 1.10 times the mean; training step 1,474.6 -> 1,465.6 us, on 24
+// heads of 4,096 tokens 279.8 -> 276.0, on 20 of 75,600 10.41 -> 10.24 ms.  (Where one group takes all heads, as on 32 heads of 64 key
+// blocks, runs that stay on their XCD serve better: 199.4 against 200.7 us.)  With the groups alone the long lists of the last one
+// kept a fifth of the CUs waiting (in a model of the 64 places of each XCD the last one ended at 1.54 times the mean, with the long
+// lists first at 1.12): training step on such lists 1,747 -> 1,691 us, on 20 heads of 75,600 tokens 11.86 -> 11.60 ms.
 // The order decides when a block is worked on, never what is summed.
 //
 // One call writes the places of one group: the long lists of all heads (h0 = 0, h1 = BH, LONG) or the others of heads
 // [h0, h1).  Place 8 r + x is the r-th of XCD x; a counting sort on the length, cut off at 255.
 constexpr int kNoLongList = 1 << 30;                  // every list is shorter
+__device__ __forceinline__ int order_xcd(int head, int j, int per_head, bool turn) { return turn ? (j / per_head + head) % kXcds : j / per_head; }
+// key blocks of heads [0, heads) on XCD x
+__device__ __forceinline__ int order_before(int x, int heads, int per_head, int Tn, bool turn) {
+  if (!turn) return heads * max(0, min(per_head, Tn - x * per_head));
+  int n = heads / kXcds * Tn;
+  for (int h = heads / kXcds * kXcds; h < heads; h++) n += max(0, min(per_head, Tn - (x + kXcds - h % kXcds) % kXcds * per_head));
+  return n;
+}
 template <bool LONG>
 __device__ void order_group(const int32_t* __restrict__ counts, int32_t* __restrict__ order, int BH, int h0, int h1, int Tn,
-                            int long_list, int* hist /* LDS [8 x 256] */, int* at /* LDS [16] */) {
+                            int long_list, bool turn, int* hist /* LDS [8 x 256] */, int* at /* LDS [16] */) {
   const int tid = threadIdx.x, per_head = (Tn + kXcds - 1) / kXcds;
   auto each = [&](int first, int end, auto f) {       // f(key block bh T_n + j, its count), eight loads in flight
     for (int e0 = first + tid; e0 < end; e0 += 8 * 256) {
@@ -38,27 +51,26 @@ __device__ void order_group(const int32_t* __restrict__ counts, int32_t* __restr
   if constexpr (LONG) {
     // places that a short last run of every head leaves empty: behind all others of their XCD
     for (int e = tid; e < BH * kXcds * per_head; e += 256) {
-      const int x = e % kXcds, run = max(0, min(per_head, Tn - x * per_head));
-      if (e / kXcds >= BH * run) order[e] = -1;
+      if (e / kXcds >= order_before(e % kXcds, BH, per_head, Tn, turn)) order[e] = -1;
     }
   } else if (long_list != kNoLongList) {
     each(0, BH * Tn, [&](int e, int c) {
       if (c > long_list) {
-        const int x = (e % Tn) / per_head;
+        const int x = order_xcd(e / Tn, e % Tn, per_head, turn);
         atomicAdd(&at[x], 1);
         if (e < h0 * Tn) atomicAdd(&at[kXcds + x], 1);
       }
     });
   }
   auto mine = [&](int c) { return (c > long_list) == LONG; };
-  auto bin = [&](int e, int c) { return (e % Tn) / per_head * 256 + 255 - min(c, 255); };
+  auto bin = [&](int e, int c) { return order_xcd(e / Tn, e % Tn, per_head, turn) * 256 + 255 - min(c, 255); };
   if (LONG && long_list == kNoLongList) return;
   each(h0 * Tn, h1 * Tn, [&](int e, int c) {
     if (mine(c)) atomicAdd(&hist[bin(e, c)], 1);
   });
   __syncthreads();
   for (int x = tid / kWave; x < kXcds; x += 4) {      // per XCD an exclusive scan of its 256 bins, 4 per lane
-    const int lane = tid % kWave, run_len = max(0, min(per_head, Tn - x * per_head));
+    const int lane = tid % kWave;
     int c[4], sum = 0;
 #pragma unroll
     for (int y = 0; y < 4; y++) { c[y] = hist[256 * x + 4 * lane + y]; sum += c[y]; }
@@ -69,7 +81,7 @@ __device__ void order_group(const int32_t* __restrict__ counts, int32_t* __restr
       if (lane >= o) run += y;
     }
     run -= sum;
-    if constexpr (!LONG) run += at[x] + h0 * run_len - at[kXcds + x];   // behind the long ones and the groups before
+    if constexpr (!LONG) run += at[x] + order_before(x, h0, per_head, Tn, turn) - at[kXcds + x];   // behind the long ones and the groups before
 #pragma unroll
     for (int y = 0; y < 4; y++) { hist[256 * x + 4 * lane + y] = run; run += c[y]; }
   }
@@ -89,9 +101,9 @@ struct WorkOrder {
   int groups, heads_per_group, long_list, BH, Tn;
 };
 __device__ inline void order_job(const WorkOrder& o, int id, int* hist /* LDS [8 x 256] */, int* at /* LDS [16] */) {
-  const int h0 = (id - 1) * o.heads_per_group, h1 = min(o.BH, h0 + o.heads_per_group);
-  if (id == 0) order_group<true>(o.counts, o.order, o.BH, 0, o.BH, o.Tn, o.long_list, hist, at);
-  else order_group<false>(o.counts, o.order, o.BH, h0, h1, o.Tn, o.long_list, hist, at);
+  const int h0 = (id - 1) * o.heads_per_group, h1 = id == o.groups ? o.BH : h0 + o.heads_per_group;
+  if (id == 0) order_group<true>(o.counts, o.order, o.BH, 0, o.BH, o.Tn, o.long_list, o.groups > 1, hist, at);
+  else order_group<false>(o.counts, o.order, o.BH, h0, h1, o.Tn, o.long_list, o.groups > 1, hist, at);
 }
 inline WorkOrder make_order(const Shape& s, const BwdArgs& a) {
   // Heads per order group.  What a head's key blocks gather: the Q and dO rows and the dH_i slots.  A group of more heads
@@ -102,7 +114,8 @@ inline WorkOrder make_order(const Shape& s, const BwdArgs& a) {
   const size_t head_bytes = ((size_t)2 * s.N * s.d + (size_t)s.Tm * s.d * s.d) * (s.bf16 ? 2 : 4);
   const size_t fit = ((size_t)(s.bf16 ? 48 : 192) << 20) / head_bytes;
   const int heads = fit < 1 ? 1 : fit > (size_t)s.BH ? s.BH : (int)fit;
-  const int groups = (s.BH + heads - 1) / heads;
+  const int per_head = (s.Tn + kXcds - 1) / kXcds, tail = (4 * 64 + per_head - 1) / per_head;   // heads of the last group, at least
+  const int groups = (s.BH > tail ? (s.BH - tail) / heads : 0) + 1;
   // Length from which a list counts as long, see order_group: thrice the mean, and a sixth of what each of about 512
   // workgroups at a time has to do in all.  One group is sorted as a whole: none.
   const int64_t entries = (int64_t)s.Tm * s.k, share = entries * s.BH / (512 * 6);
