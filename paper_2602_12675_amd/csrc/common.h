@@ -92,8 +92,9 @@ __device__ __forceinline__ T scalar_load(const T* p) {
 template <class T>
 __device__ __forceinline__ void store_streamed(T* p, T x) { __builtin_nontemporal_store(x, p); }
 
-// lanes l and l ^ 32 combine their values through v_permlane32_swap (a vector instruction: no LDS round trip,
-// whose latency a wave that has the vector unit to itself would sit out)
+// lanes l and l ^ 32 combine their values through v_permlane32_swap; both get the same bits.  A vector instruction: no LDS round trip,
+// whose latency a wave that has the vector unit to itself would sit out (us, with a round trip / so, in the plain loop of the attention
+// kernel at d = 64, 128-row blocks: FP8, 24 heads of 16,384 tokens 195.5 / 192.7; dense, 24 heads of 8,192 471 / 464).
 __device__ __forceinline__ float swap_halves_max(float x) {
   const unsigned u = __builtin_bit_cast(unsigned, x);
   const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);   // r[0] = low half twice, r[1] = high half twice

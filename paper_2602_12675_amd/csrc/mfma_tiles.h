@@ -18,10 +18,6 @@ namespace sla2 {
 constexpr int kTileTokens = 64;                    // b_kv
 constexpr int kVmcnt0 = 0x0F70;                    // s_waitcnt vmcnt(0), other counters untouched
 
-// lanes l and l ^ 32 combine their values; both get the same bits
-__device__ __forceinline__ float half_sum(float x) { return x + __shfl_xor(x, 32); }
-__device__ __forceinline__ float half_max(float x) { return fmaxf(x, __shfl_xor(x, 32)); }
-
 // Between two phases of a workgroup.  LDS is written by the tile transfers only (waited for through vmcnt where a phase
 // needs them), and every operand read is waited for by the product that consumes it, so the barrier itself
 // waits for nothing: reads issued before it stay in flight across it.

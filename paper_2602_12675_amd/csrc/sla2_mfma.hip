@@ -1338,7 +1338,7 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
       for (int mt = 0; mt < 2; mt++)
 #pragma unroll
         for (int e = 0; e < 16; e++) mx = fmaxf(mx, sacc[mt][e]);
-      mx = half_max(mx) * c1;
+      mx = swap_halves_max(mx) * c1;
       // The reference of the exponentials.  With P rounded to a grid (low-bit modes) it is the running maximum,
       // as Alg. 2 states it.  Otherwise any reference gives the same O / l, and the one in use is kept while the
       // maximum of the row stays within 2^kLazy of it: O^T, l then need no rescaling in most tiles (the weights
@@ -1376,7 +1376,7 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
             pf[2 * mt + e / 8][e % 8 + 1] = (__bf16)p1;
           }
         }
-      rs = half_sum(rs);
+      rs = swap_halves_sum(rs);
       if (rescale) {
         const float corr = fast_exp2(m_run - m_new);   // 0 on the first tile
         l_run *= corr;
