@@ -145,16 +145,26 @@ __device__ __forceinline__ float quad_sum(float x) {
 // over 8 or 16 neighbouring lanes and over the wave, on all of them, in the order of a butterfly.  (As four exchanges through LDS a row,
 // each waited for, the sums of dO . O^s of the backward pass's query side took as long as reading its tiles.)
 template <int LANES> __device__ __forceinline__ float row_sum(float x) {
-  static_assert(LANES == 8 || LANES == 16, "");
+  static_assert(LANES == 8 || LANES == 16 || LANES == 32, "");
   x = quad_sum(x);
   x += dpp_move<0x141>(x);                             // row_half_mirror
-  return LANES == 8 ? x : x + dpp_move<0x140>(x);      // row_mirror
-}
-__device__ __forceinline__ float wave_sum(float x) {
-  const unsigned u = __builtin_bit_cast(unsigned, row_sum<16>(x));
+  if (LANES > 8) x += dpp_move<0x140>(x);              // row_mirror
+  if (LANES < 32) return x;
+  const unsigned u = __builtin_bit_cast(unsigned, x);
   const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-  return swap_halves_sum(__builtin_bit_cast(float, (unsigned)r[0]) + __builtin_bit_cast(float, (unsigned)r[1]));
+  return __builtin_bit_cast(float, (unsigned)r[0]) + __builtin_bit_cast(float, (unsigned)r[1]);
 }
+template <int LANES> __device__ __forceinline__ float row_max(float x) {
+  static_assert(LANES == 16 || LANES == 32, "");
+  x = quad_max(x);
+  x = fmaxf(x, dpp_move<0x141>(x));
+  x = fmaxf(x, dpp_move<0x140>(x));
+  if (LANES < 32) return x;
+  const unsigned u = __builtin_bit_cast(unsigned, x);
+  const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  return fmaxf(__builtin_bit_cast(float, (unsigned)r[0]), __builtin_bit_cast(float, (unsigned)r[1]));
+}
+__device__ __forceinline__ float wave_sum(float x) { return swap_halves_sum(row_sum<32>(x)); }
 // a of lanes l and l ^ 32 added up on the lower half of the wave, b on the upper one; the same with l ^ 16 on the even and odd
 // 16 lanes
 __device__ __forceinline__ float swap32_add(float a, float b) {

@@ -140,8 +140,7 @@ __global__ __launch_bounds__(256, 2) void bwd_q_f32_kernel(
   const float Ds = al * rows[r], Dl = (1.f - al) * rows[32 + r];
   if (w == 0) {                           // d alpha: the sum over the tokens of dO . (O^s - O^l)
     float x = g == 0 ? rows[64 + r] : 0.f;
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) x += __shfl_xor(x, o);
+    x = wave_sum(x);
     const int parts = bq / 32, part = grp % parts;
     if (lane == 0) dalpha_part[slot * parts + part] = x;
     if (grp == groups - 1 && lane > part && lane < parts) dalpha_part[slot * parts + lane] = 0.f;   // groups past the end
@@ -192,8 +191,9 @@ __global__ __launch_bounds__(256, 2) void bwd_q_f32_kernel(
 #pragma unroll
     for (int e = 0; e < 16; e++) {
       const bool ok = row_ok && 8 * (e / 4) + 4 * g + e % 4 < valid;
-      const float p = ok ? exp2_f32(ds[e] * c0 - L2) : 0.f;
-      ds[e] = p * (al * dp[e] - Ds);
+      float p = exp2_f32(ds[e] * c0 - L2);
+      asm volatile("" : "+v"(p));         // taken in any case: no branch around each of them
+      ds[e] = (ok ? p : 0.f) * (al * dp[e] - Ds);
     }
 #pragma unroll
     for (int j = 0; j < J; j++) {         // dQ^T += K'^T dS^T
@@ -544,7 +544,11 @@ __global__ __launch_bounds__(256, 2) void bwd_kv_f32_kernel(
     const float lnz = k_stats[(size_t)bh * N + t0 + min(row, valid - 1)];
     f32x4 x = *reinterpret_cast<const f32x4*>(ks + row * LD + 4 * ch);
 #pragma unroll
-    for (int c = 0; c < 4; c++) x[c] = row < valid ? exp2_f32((x[c] - lnz) * kLog2e) : 0.f;
+    for (int c = 0; c < 4; c++) {
+      float p = exp2_f32((x[c] - lnz) * kLog2e);
+      asm volatile("" : "+v"(p));         // taken in any case: no branch around each of them
+      x[c] = row < valid ? p : 0.f;
+    }
     *reinterpret_cast<f32x4*>(ks + row * LD + 4 * ch) = x;
   }
   f32x16 acc = zero16();

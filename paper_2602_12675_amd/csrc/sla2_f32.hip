@@ -116,7 +116,7 @@ __global__ __launch_bounds__(256, 2) void masked_states_f32_kernel(const float* 
   if (col >= P) return;
   if (total) {
 #pragma unroll
-    for (int x = 0; x < 4; x++) sum[x] = both_halves_sum(sum[x]);
+    for (int x = 0; x < 4; x++) sum[x] = swap_halves_sum(sum[x]);
     if (g == 0) *reinterpret_cast<f32x4*>(col < D * D ? out.h_total + (size_t)bh * D * D + col : out.z_total + (size_t)bh * D + (col - D * D)) = sum;
   }
   if constexpr (!TOTALS_ONLY) {
