@@ -1062,6 +1062,12 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
     int j1 = j_nxt;                                  // key block of tile s + 1
     int j2 = j_third;
     float sk1 = sk_nxt;                              // scale of tile s + 1
+    // Of the two waves of a SIMD the one that has its products and their softmax before it is served first: it has work for both units,
+    // the other waits for requests or scores.  us, without / with: bf16, 12 heads of 32,760 tokens at 26 tiles a block 598.2 / 588.5,
+    // with H_i given (80 heads of 75,601, 177 tiles) 44,852 / 44,181, FP8 at 15 tiles 406.9 / 404.5, INT8 416.2 / 413.2; d = 64, 64-row
+    // blocks, INT8, 12 heads of 32,000 372.8 / 361.2.  With 64-row blocks and bf16 scores, where both waves have products most of the
+    // time, it loses (d = 64, 12 heads of 16,000 104.6 / 105.4; d = 128, 12 of 32,760 909 / 925).
+    constexpr bool kFirst = FP8 || BQ == 128;
     // The last tile has a copy of the pass of its own, with Q^phi in the place of the softmax - in the low-bit modes; bf16
     // operands, whose query fragments take 16 registers more, leave none for what the two copies would exchange.
     auto pass = [&](int s, auto last_pass) {
@@ -1113,6 +1119,7 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
         sv_cur = sv1;
       }
       if (more) mask_tail(N - j1 * kTileTokens);
+      if constexpr (kFirst) __builtin_amdgcn_s_setprio(1);
       c1 = FP8 ? c0 * s_q * sk1 : c0;
       // the K^phi fragments of this tile have landed
       if constexpr (LAST) wait_vmcnt<kQOps + HS::kMtw>();
@@ -1237,6 +1244,7 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
         zsel[a] += zj[a];
       }
       phase_barrier();                               // ... for everyone, and this pass's tiles are free
+      if constexpr (kFirst) __builtin_amdgcn_s_setprio(0);
       j_cur = j1;
       j1 = j2;
       j2 = j3;
