@@ -43,33 +43,48 @@ __device__ __forceinline__ int router_tile(int block, int blocks) {
 }
 
 // C[16][D] = A[16][D] M on the matrix cores, M fp64 [D][D] row-major in global memory.  All 16 waves
-// work: wave w forms columns [16 (w % (D/16)), +16) over a 1/(16 / (D/16)) share of the contraction
-// range; the shares are written side by side (C has room for kShares copies) and added by the reader.
+// work: wave w forms kTiles column tiles over a share of the contraction range; the shares are written side by side (C has room for
+// kShares copies) and added by the reader.  At d = 128 a wave has two tiles, the even and the odd ones of 32 columns: 16 bytes of a
+// row of M then serve both, and M, 128 KB a workgroup, comes in half as many requests (with them issued in front of the first pooled
+// keys: soft router on 12 heads of 256 x 512 blocks 62.2 -> 61.1 us, on 20 heads of 32 x 63 25.7 -> 24.6).  At d = 64, where M is a
+// quarter of that, it loses 1 %.
 template <int D> struct ProjGeom {
-  static constexpr int kNt = D / 16;                 // column tiles
-  static constexpr int kShares = 16 / kNt;           // waves per column tile: 2 (D = 128) or 4 (D = 64)
+  static constexpr int kTiles = D == 128 ? 2 : 1;
+  static constexpr int kNt = D / 16 / kTiles;        // column tiles or pairs of them
+  static constexpr int kShares = 16 / kNt;           // waves each: 4
   static constexpr int kSteps = D / 4 / kShares;     // 4-wide contraction steps per wave
+  typedef __attribute__((ext_vector_type(kTiles))) double Row;
+  __device__ static __forceinline__ int col(int wave, int lane) { return kTiles * (16 * (wave % kNt) + lane % 16); }
 };
 template <int D>
-__device__ __forceinline__ void project16_fetch(double (&b)[ProjGeom<D>::kSteps], const double* __restrict__ M, int wave,
+__device__ __forceinline__ void project16_fetch(typename ProjGeom<D>::Row (&b)[ProjGeom<D>::kSteps], const double* __restrict__ M, int wave,
                                                 int lane) {
   typedef ProjGeom<D> G;
-  const int n = 16 * (wave % G::kNt) + lane % 16, share = wave / G::kNt;
 #pragma unroll
-  for (int i = 0; i < G::kSteps; i++) b[i] = M[(size_t)(4 * (share * G::kSteps + i) + lane / 16) * D + n];
+  for (int i = 0; i < G::kSteps; i++)
+    b[i] = *reinterpret_cast<const typename G::Row*>(M + (size_t)(4 * (wave / G::kNt * G::kSteps + i) + lane / 16) * D + G::col(wave, lane));
 }
 template <int D>
 __device__ __forceinline__ void project16(const double (*A)[D + 2], double (*C)[D + 2] /* [kShares*16][D+2] */,
-                                          const double (&b)[ProjGeom<D>::kSteps], int wave, int lane) {
+                                          const typename ProjGeom<D>::Row (&b)[ProjGeom<D>::kSteps], int wave, int lane) {
   typedef ProjGeom<D> G;
-  const int nt = wave % G::kNt, share = wave / G::kNt;
-  const int n = 16 * nt + lane % 16;
-  f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+  const int share = wave / G::kNt;
+  f64x4 acc[G::kTiles];
 #pragma unroll
-  for (int i = 0; i < G::kSteps; i++)
-    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(A[lane % 16][4 * (share * G::kSteps + i) + lane / 16], b[i], acc, 0, 0, 0);
+  for (int x = 0; x < G::kTiles; x++) acc[x] = f64x4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-  for (int v = 0; v < 4; v++) C[share * 16 + lane / 16 + 4 * v][n] = acc[v];
+  for (int i = 0; i < G::kSteps; i++) {
+    const double a = A[lane % 16][4 * (share * G::kSteps + i) + lane / 16];
+#pragma unroll
+    for (int x = 0; x < G::kTiles; x++) acc[x] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b[i][x], acc[x], 0, 0, 0);
+  }
+#pragma unroll
+  for (int v = 0; v < 4; v++) {
+    typename G::Row y;
+#pragma unroll
+    for (int x = 0; x < G::kTiles; x++) y[x] = acc[x][v];
+    *reinterpret_cast<typename G::Row*>(&C[share * 16 + lane / 16 + 4 * v][G::col(wave, lane)]) = y;
+  }
 }
 
 // Leaves row (row0 + wave) in `score`: slot 4 r + x of lane l is key block 256 r + 64 x + l (slots past T_n hold
@@ -83,7 +98,7 @@ __device__ __forceinline__ void router_scores(double (&score)[SLOTS], const doub
   double (*xa)[D + 2] = reinterpret_cast<double (*)[D + 2]>(lds);
   typedef double Tile[kRouterRows][kColsPerRound + 8];
   Tile* tiles = reinterpret_cast<Tile*>(lds + kRouterRows * (D + 2));
-  static_assert(ProjGeom<D>::kShares * (D + 2) <= kColsPerRound + 8, "projection shares must fit the score tile");
+  static_assert(ProjGeom<D>::kShares * (D + 2) <= 2 * (kColsPerRound + 8), "projection shares must fit the score tiles");
   double (*xb)[D + 2] = reinterpret_cast<double (*)[D + 2]>(&tiles[0][0][0]);   // partial Qbar M; dead before the first round
   const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
   const int rounds = (Tn + kColsPerRound - 1) / kColsPerRound;
@@ -102,16 +117,17 @@ __device__ __forceinline__ void router_scores(double (&score)[SLOTS], const doub
     for (int i = 0; i < kBatch; i++) pre[batch & 1][i] = *reinterpret_cast<const f64x2*>(p + 8 * n * i);
   };
 
-  // requested in the order of use: block sums of Q, operands of the projection, the first pooled keys
+  // requested in the order of use: block sums of Q, operands of the projection; the first pooled keys once those are there, behind
+  // the projection's products
   constexpr int kQLoads = kRouterRows * D / 1024;
-  double qv[kQLoads], mb[ProjGeom<D>::kSteps];
+  double qv[kQLoads];
+  typename ProjGeom<D>::Row mb[ProjGeom<D>::kSteps];
 #pragma unroll
   for (int x = 0; x < kQLoads; x++) {
     const int r = (threadIdx.x + 1024 * x) / D, c = threadIdx.x % D;
     qv[x] = q_sum[((size_t)bh * Tm + min(row0 + r, Tm - 1)) * D + c];     // rows past the end repeat the last one; never stored
   }
   project16_fetch<D>(mb, M, wave, lane);
-  fetch(0, 0);
   // Mean pooling (Eq. 15).  Blocks are powers of two: for full ones the product with 1 / b_q is the exact quotient; only the
   // tile that holds a ragged last block divides.
   const double inv_bq = 1.0 / bq;
@@ -124,6 +140,7 @@ __device__ __forceinline__ void router_scores(double (&score)[SLOTS], const doub
     xa[r][c] = qv[x];
   }
   __syncthreads();
+  fetch(0, 0);
   project16<D>(xa, xb, mb, wave, lane);                                   // Qbar (Wq Wk^T / sqrt(d)), in shares
   __syncthreads();
   for (int e = threadIdx.x; e < kRouterRows * D; e += 1024) {
