@@ -69,11 +69,8 @@ __global__ __launch_bounds__(1024) void router_topk_kernel(const double* __restr
 
   double score[SLOTS];
   router_scores<D, SLOTS>(score, q_sum, k_frag, M, lds, bh, row0, N, bq, bk, Tm, Tn);
-  uint64_t key[SLOTS];
   const int rounds = (Tn + kColsPerRound - 1) / kColsPerRound;
-#pragma unroll
-  for (int s = 0; s < SLOTS; s++)                      // slots past T_n get 0, below every real score; -0 -> +0: zeros tie
-    key[s] = (s / 4) * kColsPerRound + (s % 4) * kWave + lane < Tn ? order_key(score[s] + 0.0) : 0ull;
+  auto used = [&](int s) { return lane < Tn - ((s / 4) * kColsPerRound + (s % 4) * kWave); };   // slots past T_n hold -infinity
 
   const int row = row0 + wave;
   if (row >= Tm || k <= 0) return;
@@ -91,9 +88,10 @@ __global__ __launch_bounds__(1024) void router_topk_kernel(const double* __restr
     bool finite = true;
 #pragma unroll
     for (int s = 0; s < SLOTS; s++) {
-      finite = finite && (key[s] == 0 || fabs(score[s]) < INFINITY);
-      top = fmaxf(top, (float)score[s]);
-      bottom = fmaxf(bottom, key[s] ? -(float)score[s] : -INFINITY);
+      const float x = (float)score[s];                   // (a finite score that is none in fp32 makes the span too large)
+      finite = finite && (!used(s) || __builtin_isfinite(score[s]));
+      top = fmaxf(top, x);
+      bottom = fmaxf(bottom, used(s) ? -x : -INFINITY);
     }
     top = wave_max(top);
     bottom = -wave_max(bottom);
@@ -103,7 +101,7 @@ __global__ __launch_bounds__(1024) void router_topk_kernel(const double* __restr
       uint32_t lin[SLOTS], thr = 0;
 #pragma unroll
       for (int s = 0; s < SLOTS; s++)
-        lin[s] = key[s] ? 1u + (uint32_t)fmin(fmax((score[s] - base) * scale, 0.0), 4294967040.0) : 0u;
+        lin[s] = used(s) ? 1u + (uint32_t)fmin(fmax((score[s] - base) * scale, 0.0), 4294967040.0) : 0u;
       for (int bit = 31; bit >= 0; bit--) {
         const uint32_t cand = thr | (1u << bit);
         int cnt = 0;
@@ -125,6 +123,9 @@ __global__ __launch_bounds__(1024) void router_topk_kernel(const double* __restr
     }
   }
 
+  uint64_t key[SLOTS];
+#pragma unroll
+  for (int s = 0; s < SLOTS; s++) key[s] = used(s) ? order_key(score[s] + 0.0) : 0ull;   // 0: below every real score; -0 -> +0: zeros tie
   // k-th largest key thr, most significant bit first, on 32-bit halves (32-bit compares run at full
   // rate).  Invariant of either search: at least `need` candidates are >= the current threshold.
   // `exact` is set as soon as {key >= thr} has exactly k members - no ties to resolve then.
