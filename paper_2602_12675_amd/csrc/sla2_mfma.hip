@@ -1053,7 +1053,10 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
       if constexpr (FP8V) settle(pb_new);
       else settle(pf[ks]);
     };
-    auto soft_end = [&]() {
+    auto soft_end = [&]() {                          // the last step's probabilities, and the sums
+#pragma unroll
+      for (int n = 0; n < 4; n++) soft_pair(4 * (kSteps - 1) + n);
+      soft_keep(kSteps - 1);
       l_run = l_run * corr + swap_halves_sum(rs);
       m_run = m_new;
       if constexpr (FP8V) pb = pb_new;
@@ -1068,6 +1071,10 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
     // blocks, INT8, 12 heads of 32,000 372.8 / 361.2.  With 64-row blocks and bf16 scores, where both waves have products most of the
     // time, it loses (d = 64, 12 heads of 16,000 104.6 / 105.4; d = 128, 12 of 32,760 909 / 925).
     constexpr bool kFirst = FP8 || BQ == 128;
+    // At d = 128 with 128-row blocks in the low-bit modes the last quarter of a tile's softmax stands in the next pass, behind the operand reads of its
+    // scores: ahead of the barrier nothing ran beside it (us: FP8, 40 heads of 75,600 tokens 5,767 -> 5,718, 12 of 32,760 410.5 ->
+    // 406.9, INT8 418.8 -> 415.2; 64-row blocks 624 -> 625, bf16 602 -> 604; d = 64, 64-row blocks, training step 198.2 -> 200.9).
+    constexpr bool kDefer = FP8 && D == 128 && BQ == 128;
     // The last tile has a copy of the pass of its own, with Q^phi in the place of the softmax - in the low-bit modes; bf16
     // operands, whose query fragments take 16 registers more, leave none for what the two copies would exchange.
     auto pass = [&](int s, auto last_pass) {
@@ -1102,6 +1109,7 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
         scores(buf ^ 1,
                [&] {
                  requests();
+                 if (kDefer) soft_end();
                  rescale_o(0);
                },
                [&](int n) {
@@ -1110,6 +1118,7 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
                });
       } else {
         requests();
+        if (kDefer) soft_end();
 #pragma unroll
         for (int et = 0; et < ET; et++) rescale_o(et);
         if (more) scores(buf ^ 1, [] {}, [](int) {});
@@ -1232,10 +1241,7 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
       if constexpr (LAST) {
         wait_vmcnt<0>();                             // z_j
       } else {
-#pragma unroll
-        for (int n = 0; n < 4; n++) soft_pair(4 * (kSteps - 1) + n);
-        soft_keep(kSteps - 1);
-        if (more) soft_end();
+        if (!kDefer && more) soft_end();
         wait_vmcnt<kPhiOps>();                       // the next K and V tiles have landed (and z_j) ...
       }
 #pragma unroll
@@ -1258,8 +1264,8 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
       soft_max(1);
       soft_reference();
 #pragma unroll
-      for (int n = 0; n < 16; n++) soft_pair(n);
-      soft_end();
+      for (int n = 0; n < 4 * (kSteps - 1); n++) soft_pair(n);
+      if (!kDefer) soft_end();
       rescale = false;                               // O^T is zero
       __builtin_amdgcn_s_waitcnt(kVmcnt0);           // V and K^phi of the first tile, K of the second have landed
       phase_barrier();                               // everyone is done with the first K tile
