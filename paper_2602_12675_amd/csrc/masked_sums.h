@@ -32,7 +32,8 @@ __device__ __forceinline__ unsigned masked_unit(unsigned row) { return (row & 1)
 // are 16 apart in the row's word and all of them come out of it with a shift and an AND: 0x4000 is 2.0 in bf16, so B holds
 // halves (halving C at the end instead would lose what the sums hold above half of the largest number).
 // Bound by the matrix cores: 8 products (256 cycles) a wave and ks against 128 cycles for the mask operands, 2 KB of LDS
-// reads; B arrives one step ahead.
+// reads; B arrives one step ahead.  A wave with products before it is served ahead of one that requests or waits (H_i of 80 heads of
+// 75,601 tokens: the call 42.07 -> 41.54 ms, training step on 12 heads of 32,760 1,409.6 -> 1,407.3 us).
 __device__ __forceinline__ void masked_sums_tile(const uint16_t* __restrict__ b, const uint32_t* __restrict__ bits,
                                                  uint16_t* __restrict__ c, int S, int R, int cols, int row0, int col0,
                                                  unsigned char* smem) {
@@ -102,6 +103,7 @@ __device__ __forceinline__ void masked_sums_tile(const uint16_t* __restrict__ b,
         for (int hi = 0; hi < 2; hi++) rb[ks % 2][u][hi] = lds_read_tr_untracked_at<1024>(at[u] + buf, 2 * ks + hi);
     };
     read(0);
+    __builtin_amdgcn_s_setprio(1);
 #pragma unroll
     for (int ks = 0; ks < 4; ks++) {
       if (ks < 3) read(ks + 1);
@@ -124,6 +126,7 @@ __device__ __forceinline__ void masked_sums_tile(const uint16_t* __restrict__ b,
           acc[t][u] = mfma_bf16(__builtin_bit_cast(bf16x8, a[t]), __builtin_bit_cast(bf16x8, v4), acc[t][u]);
       }
     }
+    __builtin_amdgcn_s_setprio(0);
     landed(next, more ? step + 1 : step);              // the next step is there ...
 #pragma unroll
     for (int t = 0; t < RT; t++) word[t] = next[t];
