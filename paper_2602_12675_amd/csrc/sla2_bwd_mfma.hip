@@ -187,20 +187,21 @@ __global__ __launch_bounds__(BQ * 2, 2) void bwd_q_mfma_kernel(
   unsigned full = 2u * (unsigned)SL::offset(qrow, 8 * g), quarter = 2u * (unsigned)SL::offset(qrow, 4 * g);
   unsigned char *pa = reinterpret_cast<unsigned char*>(ta), *pb = reinterpret_cast<unsigned char*>(tb);
   // Q^phi = softmax_d(Q) of this lane's row (channels 16 ks + 8 g + 0..7) as exp(q - max); the normalisation is applied where it is
-  // used
+  // used.  The difference comes first: in q log2(e) - max log2(e) as a multiply-add one of the two products is rounded and the other is
+  // not, which from entries of 1e9 on leaves more than an exponent holds.
   float qm = -INFINITY;
 #pragma unroll
   for (int ks = 0; ks < KS; ks++)
 #pragma unroll
     for (int e = 0; e < 8; e++) qm = fmaxf(qm, qx[ks][e / 4][e % 4]);
-  qm = swap_halves_max(qm) * kLog2e;
+  qm = swap_halves_max(qm);
   float qs = 0.f, den = 0.f;
   lds_stream<FragmentChannels, 2 * KS, 8>(lds_address(zs + 8 * g), [&](auto n, const u32x4& raw) {
     constexpr int ks = decltype(n)::value / 2, x = decltype(n)::value % 2;
     const f32x4 z = __builtin_bit_cast(f32x4, raw);
 #pragma unroll
     for (int e = 0; e < 4; e++) {
-      qx[ks][x][e] = fast_exp2(qx[ks][x][e] * kLog2e - qm);
+      qx[ks][x][e] = fast_exp2((qx[ks][x][e] - qm) * kLog2e);
       qs += qx[ks][x][e];
       den += qx[ks][x][e] * z[e];
     }
