@@ -318,8 +318,15 @@ __device__ __forceinline__ void settle(T& x) { asm volatile("" : "+v"(x)); }
 
 // LDS operand reads issued the same way.  The compiler's scheduler keeps a tracked read, its wait
 // and the product that consumes it back to back, so the LDS latency is paid once per product; with
-// the reads untracked the kernel keeps several in flight and waits with the count it knows.  The
-// LDS counter retires in order, so "at most n outstanding" settles everything but the n youngest.
+// the reads untracked the kernel keeps several in flight and waits with the count it knows.  Reads
+// of LDS retire in order, so "at most n outstanding" settles everything but the n youngest.  (Scalar
+// loads share the counter and return in any order: with some of them under way a wait for n is
+// longer than it has to be, never shorter, since a read still out keeps all younger reads out.)
+// To the compiler the result is there at once: it may move, spill or reuse the register before the
+// data is.  No such register is carried round a loop, and where a branch stands between a read and
+// its wait (the requests and the rescale inside the low-bit score product) nothing in the source
+// keeps it from doing so: tests/test_loads_in_flight.py goes through the compiled code of every
+// kernel for that.
 // Another benefit: a tracked transposing read is treated as a possible alias of the tile transfer
 // in flight and is preceded by vmcnt(0).
 template <int OFF>    // 16 bytes at addr + OFF
