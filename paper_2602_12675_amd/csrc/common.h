@@ -88,7 +88,8 @@ __device__ __forceinline__ T scalar_load(const T* p) {
 // left in the 256 MB memory-side cache they push out the tiles that are gathered from it, and their way to memory falls into the
 // next kernels that stream through HBM.  Forward, us, cached / past the caches: 48 heads of 4,096 tokens (FP8) 169.2 / 164.5,
 // 12 heads of 32,760 434 / 428, bf16 at 26 blocks a list 616 / 609; with an elementwise kernel that reads `out` at once behind the
-// call 182.2 / 180.4 and 457 / 454; training steps 1,510 / 1,499 and 209.3 / 206.9 (32 heads of 4,096 tokens, d = 64).
+// call 182.2 / 180.4 and 457 / 454; training steps 1,510 / 1,499 and 209.3 / 206.9 (32 heads of 4,096 tokens, d = 64).  With four sets
+// of inputs in turn, none of which is left in a cache, as much: 159.3 / 155.5, 409.6 / 404.8, 608.7 / 605.9, 1,449 / 1,442, 202.7 / 199.9.
 template <class T>
 __device__ __forceinline__ void store_streamed(T* p, T x) { __builtin_nontemporal_store(x, p); }
 
@@ -142,7 +143,7 @@ __device__ __forceinline__ float quad_sum(float x) {
   x += dpp_move<0xB1>(x);
   return x + dpp_move<0x4E>(x);
 }
-// over 8 or 16 neighbouring lanes and over the wave, on all of them, in the order of a butterfly.  (As four exchanges through LDS a row,
+// over 8, 16 or 32 neighbouring lanes and over the wave, on all of them, in the order of a butterfly.  (As four exchanges through LDS a row,
 // each waited for, the sums of dO . O^s of the backward pass's query side took as long as reading its tiles.)
 template <int LANES> __device__ __forceinline__ float row_sum(float x) {
   static_assert(LANES == 8 || LANES == 16 || LANES == 32, "");

@@ -46,8 +46,9 @@ __device__ __forceinline__ int router_tile(int block, int blocks) {
 // work: wave w forms kTiles column tiles over a share of the contraction range; the shares are written side by side (C has room for
 // kShares copies) and added by the reader.  At d = 128 a wave has two tiles, the even and the odd ones of 32 columns: 16 bytes of a
 // row of M then serve both, and M, 128 KB a workgroup, comes in half as many requests (with them issued in front of the first pooled
-// keys: soft router on 12 heads of 256 x 512 blocks 62.2 -> 61.1 us, on 20 heads of 32 x 63 25.7 -> 24.6).  At d = 64, where M is a
-// quarter of that, it loses 1 %.
+// keys: soft router on 12 heads of 256 x 512 blocks 62.2 -> 61.1 us, on 20 heads of 32 x 63 25.7 -> 24.6; behind a fill of 1 GB, with
+// nothing left in a cache, 102.7 -> 101.6 and 37.9 -> 36.7).  At d = 64, where M is a quarter of that, it loses 1 %.  The shares decide the
+// order in which fp64 sums are added, so scores differ in their last bits between two shares and four; lists and stored masks did not.
 template <int D> struct ProjGeom {
   static constexpr int kTiles = D == 128 ? 2 : 1;
   static constexpr int kNt = D / 16 / kTiles;        // column tiles or pairs of them

@@ -102,10 +102,11 @@ int make_shape(const sla2_params* p, Shape* s) {
   s->save = (p->flags & SLA2_FLAG_SAVE_FOR_BACKWARD) != 0;
   s->w_per_head = p->router_w_per_head != 0;
   s->alpha_per_block = p->alpha_per_block != 0;
-  // Key blocks per kv-precompute workgroup.  That kernel keeps 2 workgroups resident per CU (its
-  // d x d accumulator costs registers), 512 on the 256 CUs of an MI355X; one workgroup more than that
-  // would wait for a free slot and double the kernel's time, so the head's blocks are cut into the
-  // largest number of chunks that still fits in one resident set.
+  // Key blocks per kv-precompute workgroup: every head's blocks are cut into the largest number of chunks with which all workgroups
+  // are at most 512, two for each of the 256 CUs.  At d = 128 no more fit a CU (its registers), and one workgroup beyond that waits for
+  // a free place and doubles the kernel's time.  At d = 64 four fit, but the longer runs of two serve better, except with V in FP8
+  // (calls, us, 512 / 1,024 workgroups: FP8, 32 heads of 4,096 tokens 72.0 / 73.7, 12 of 32,760 262.1 / 265.3, bf16 290.2 / 292.7,
+  // FP8, 40 of 75,600 1,970 / 1,972; FP8 with V, 24 of 16,384 219.9 / 216.2).
   const int kResident = 512;
   s->state_heads = 0;
   if (s->bf16 && s->d == 128 && s->bq == 128 && (long long)s->BH * s->Tm >= 3 * kRound) {

@@ -591,7 +591,8 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
   auto vqbuf = [&](int buf) { return lds0 + SM::kVq0Off + buf * (SM::kVq1Off - SM::kVq0Off); };
 
   // The arguments that the requests below need, all at once: left to the compiler they come in three turns, each as long as a
-  // scalar load.
+  // scalar load.  (In the plain loop too, whose scalar registers they do not push out; d = 64, us, without / with: FP8, 128-row blocks,
+  // 32 heads of 4,096 tokens 66.0 / 65.5, 24 of 16,384 215.8 / 215.3, FP8 with V, 64-row blocks, 12 of 32,760 at 61 tiles 729 / 719.)
   asm volatile("" ::"s"(q), "s"(k), "s"(v), "s"(block_idx), "s"(k_codes), "s"(k_phi), "s"(h_frag), "s"(z_total), "s"(sin.b), "s"(sin.h),
                "s"(sin.n), "s"(H), "s"(N), "s"(Tm), "s"(Tn), "s"(ksel));
   asm volatile("" ::"s"(k_scale), "s"(alpha), "s"(v_scale), "s"(v_codes), "s"(alpha_per_block), "s"(h_save), "s"(z_blocks));
@@ -658,6 +659,8 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
   };
   // This wave's 32 query rows -> LDS at `lds` in the swizzled layout (whole lines of memory at a time; read as operand
   // fragments from there, every lane would touch lines of its own); rows past the end repeat the last one; never stored.
+  // (The way for whole blocks makes the plain loop spill three to five scalars more; d = 64, us, with / without it there: 128-row blocks, FP8
+  // 24 heads of 16,384 tokens 215.8 / 216.5, INT8 12 of 32,760 228.2 / 228.0, 64-row blocks, FP8 at 61 tiles 708.9 / 701.8.)
   auto dma_q = [&](unsigned lds) {
     typedef SwizzledLayout<D> L;
     constexpr int kRows = 1024 / (D * 2);
@@ -948,9 +951,9 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
     // product alone 33 cycles, with four multiply-adds behind it 34).  P replaces its predecessor 16 tokens at a time,
     // right after the products that read it, so it takes no second set of registers.
     // Measured on 12 heads of 32,760 tokens, d = 128, 128-row blocks: bf16, 26 tiles a block 520 -> 480 us; FP8, 15 tiles
-    // 287 -> 276 us.  The clock falls as the loop gets denser and the launch longer: 2.1 GHz over that FP8 launch, 1.8 over
-    // the bf16 one, 1.65 over 4.7 ms on 40 heads of 75,600 tokens (GRBM_GUI_ACTIVE over the launch): there work counts, not
-    // latency.
+    // 287 -> 276 us.  The clock falls as the loop gets denser and the launch longer: 1.96 GHz over the FP8 launch, now of 265 us,
+    // 1.76 over the bf16 one of 459, 1.65 over 4.7 ms on 40 heads of 75,600 tokens (GRBM_GUI_ACTIVE over the launch): there work
+    // counts, not latency.
     // Transfers, all global -> LDS: K of tile s + 2 and V of tile s + 1 are requested at the top of pass s, into places
     // read for the last time before the barrier above, and have a whole pass to land; the K^phi fragments of tile s + 1
     // are requested one by one as those of tile s leave the wave's part of LDS.  Counts: requests at the top are older

@@ -9,9 +9,9 @@
 // of the lane mask, there is no sorting and no atomics, and the result does not depend on timing.
 //
 // Measured on 12 heads of 256 x 512 blocks 28.7 -> 26 us, on 40 heads of 591 x 1182 361 -> 315 us, with the pooled keys
-// read as operand fragments and the search on 32-bit images.  Of the latter's 309 us now about 90 go with the search (220 us
+// read as operand fragments and the search on 32-bit images.  At 309 us about 90 of the latter went with the search (220 us
 // with a list that is not searched for), 40 with each round of 256 key blocks, 50 with the projection of the rows and the
-// start of a workgroup.
+// start of a workgroup; 275 to 290 now, with 64-bit keys only where the 32-bit images do not decide.
 #include "kv_state_f32.h"
 #include "router_scores.h"
 
