@@ -509,14 +509,6 @@ template <int D, int BQ, int MODE> constexpr bool kPipelined = MODE != kDenseBf1
 // The other shapes do not lose with it: INT8 stays within 4 % either way, bf16 gains up to 10 %, d = 128 gains throughout.
 template <int D, int BQ, int MODE> constexpr bool kPlainToo = D == 64 && BQ == 64 && (MODE == kSparseFp8 || MODE == kSparseFp8V);
 constexpr int kPipelinedTiles = 2500;
-// FP8 with V, d = 128, 64-row blocks: long lists over many key blocks take a pipelined loop whose requests stand ahead of the score
-// product of a pass and not in it (kWithin), for the same reason: its tile is the largest, and on long heads the workgroups share less of
-// what they gather when a wave's requests wait for its operand reads.  Call, us, in it / ahead of it, by k T_n:
-//   192 (48 heads of 4,096)  182.7 / 186.5   768 (24 of 8,192)  203.7 / 207.3   4,125 (24 of 24,000)  811 / 813   7,680 (12 of 32,760)
-//   652.1 / 653.3   13,875 (24 of 24,000)  1,848 / 1,831   26,112 (12 of 32,760)  1,537 / 1,526   77,000 (30 of 56,000)  11,897 / 11,746
-//   139,476 (40 of 75,600)  30,855 / 30,590
-template <int D, int BQ, int MODE> constexpr bool kAheadToo = D == 128 && BQ == 64 && MODE == kSparseFp8V;
-constexpr int kAheadTiles = 10000;
 
 // LDS carve-up.  Loop, in this order: K^phi fragments of one tile, each wave's own (pipelined loop only); two V tiles
 // (bf16); codes of the first V tile (when V is quantised for the second product); two K tiles (bf16, or 8-bit codes);
@@ -549,8 +541,7 @@ template <int D, int BQ, bool FP8, bool VQ, bool PIPE, bool GIVEN> struct AttnSm
 // with 64-row blocks three waves gain nothing).
 // GIVEN (pipelined loop): H_i was formed before (launch_kv_states_bf16) and is not rebuilt from K^phi: in the slots of `h_save`,
 // which the workgroup of the block turns into H_i^T at its end, or without it where `k_phi` points to.
-// AHEAD (pipelined loop): see kAheadToo.
-template <int D, int BQ, int MODE, bool PIPE, bool GIVEN, bool AHEAD>
+template <int D, int BQ, int MODE, bool PIPE, bool GIVEN>
 __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ == 128) ? 3 : 2) void attn_mfma_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const double* __restrict__ k_mean, const uint16_t* __restrict__ k_phi, const float* __restrict__ z_blocks,
@@ -1086,7 +1077,7 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
     // At d = 128 with 128-row blocks in the low-bit modes the last quarter of a tile's softmax stands in the next pass, behind the operand reads of its
     // scores: ahead of the barrier nothing ran beside it (us: FP8, 40 heads of 75,600 tokens 5,767 -> 5,718, 12 of 32,760 410.5 ->
     // 406.9, INT8 418.8 -> 415.2; 64-row blocks 624 -> 625, bf16 602 -> 604; d = 64, 64-row blocks, training step 198.2 -> 200.9).
-    // With V in FP8 only where H_i is given (24 heads of 16,384, 84 tiles 1,304 -> 1,286): its tile is the largest, and on long heads the
+    // With V in FP8 only where H_i is given (24 heads of 16,384, 84 tiles 1,296 -> 1,286): its tile is the largest, and on long heads the
     // workgroups then share less of what they gather (40 heads of 75,600, 95 tiles 13,786 -> 13,893, 20 of them at 118 8,068 -> 8,129,
     // 40 of 45,000 at 56 4,976 -> 5,020; 48 of 4,096 178.6 / 178.4).
     constexpr bool kDefer = FP8 && D == 128 && BQ == 128 && (!FP8V || GIVEN);
@@ -1098,8 +1089,11 @@ __global__ __launch_bounds__(BQ * 2, (D == 128 && BQ == 64) ? 1 : (D == 64 && BQ
       const bool more = kPeel ? !LAST : s + 1 < ntiles;
       // In the low-bit modes the requests and the rescale of O^T stand in the score product, behind its operand reads and its four
       // 64-cycle instructions, which leave the issue port to them: ahead of it they held up the wave by some 400 cycles of 3,900 a pass
-      // (us: FP8, 12 heads of 32,760 tokens 412.7 -> 407.8, 40 of 75,600 5,700 -> 5,622).  bf16 tensors rescale rarely, and have no gain.
-      constexpr bool kWithin = FP8 && !AHEAD;
+      // (us: FP8, 12 heads of 32,760 tokens 412.7 -> 407.8, 40 of 75,600 5,700 -> 5,622).  bf16 tensors rescale rarely, and have no gain;
+      // nor has FP8 with V at d = 128 with 64-row blocks, one wave a SIMD, which loses on long heads (within / ahead of the product: 12 heads
+      // of 2,048 tokens 49.4 / 49.4, 48 of 4,096 230.5 / 230.4, 12 of 16,384 461.4 / 461.6, 12 of 32,760 at 51 tiles 1,537 / 1,526, 30 of
+      // 56,000 at 88 12,120 / 11,846, 40 of 75,600 at 118 31,899 / 31,621).
+      constexpr bool kWithin = FP8 && !(FP8V && D == 128 && BQ == 64);
       float zj[HS::kMtw];
       int j3;
       float sk2 = 1.f, sv1 = 1.f;
@@ -1703,14 +1697,14 @@ struct AttnArgs {
   SavedForBackward sv;
 };
 
-template <int D, int BQ, int MODE, bool PIPE, bool GIVEN = false, bool AHEAD = false>
+template <int D, int BQ, int MODE, bool PIPE, bool GIVEN = false>
 static hipError_t launch_attn_loop(const Shape& s, const AttnArgs& a, hipStream_t stream) {
   constexpr int smem = AttnSmem<D, BQ, MODE == kSparseFp8 || MODE == kSparseInt8 || MODE == kSparseFp8V, MODE == kSparseFp8V, PIPE, GIVEN>::kBytes;
   static OncePerDevice once;
-  if (hipError_t e = allow_dynamic_lds(once, (const void*)attn_mfma_kernel<D, BQ, MODE, PIPE, GIVEN, AHEAD>, smem); e != hipSuccess) return e;
+  if (hipError_t e = allow_dynamic_lds(once, (const void*)attn_mfma_kernel<D, BQ, MODE, PIPE, GIVEN>, smem); e != hipSuccess) return e;
   const int Tm = (s.N + BQ - 1) / BQ;
   const int grid = ((Tm + kXcds - 1) / kXcds) * kXcds * s.BH;   // some workgroups of the last run of a head may have no block
-  attn_mfma_kernel<D, BQ, MODE, PIPE, GIVEN, AHEAD><<<dim3((unsigned)grid), BQ * 2, smem, stream>>>(
+  attn_mfma_kernel<D, BQ, MODE, PIPE, GIVEN><<<dim3((unsigned)grid), BQ * 2, smem, stream>>>(
       a.q, a.k, a.v, a.k_mean, a.k_phi, a.z_blocks, a.k_fp8, a.k_scale, a.v_codes, a.v_scale, a.h_frag, a.z_total,
       a.block_idx, a.alpha,
       a.out, a.lse, (uint16_t*)a.sv.o_s, (uint16_t*)a.sv.o_l, a.sv.lse, (uint16_t*)a.sv.h_i, a.sv.z_i, s.sin, s.sout, s.H, s.N, Tm, s.Tn, s.k,
@@ -1723,9 +1717,7 @@ static hipError_t launch_attn_t(const Shape& s, const AttnArgs& a, hipStream_t s
   if constexpr (D == 128 && BQ == 128 && MODE != kDenseBf16)
     if (s.state_heads > 0) return launch_attn_loop<D, BQ, MODE, true, true>(s, a, stream);
   if constexpr (kPlainToo<D, BQ, MODE>)
-    if (s.k * s.Tn > kPipelinedTiles) return launch_attn_loop<D, BQ, MODE, false>(s, a, stream);   // at most 2^22
-  if constexpr (kAheadToo<D, BQ, MODE>)
-    if (s.k * s.Tn > kAheadTiles) return launch_attn_loop<D, BQ, MODE, true, false, true>(s, a, stream);
+    if (s.k * s.Tn > kPipelinedTiles) return launch_attn_loop<D, BQ, MODE, false>(s, a, stream);   // below 2^22
   return launch_attn_loop<D, BQ, MODE, kPipelined<D, BQ, MODE>>(s, a, stream);
 }
 
