@@ -52,6 +52,7 @@ __global__ __launch_bounds__(BQ * 2, 2) void bwd_q_mfma_kernel(
     int ksel, int alpha_per_block, BwdColumns columns) {
   constexpr int NW = BQ / 32;
   constexpr int KS = D / 16, ET = D / 32;
+  constexpr float kWScale = D == 64 ? 8.f : 16.f;    // of w in LDS: a power of two, at least sqrt(d)
   typedef typename std::conditional<D == 128 && BQ == 128, SwizzledLayoutB<128>, SwizzledLayout<D>>::type SL;
   // (at d = 128 free of bank conflicts, which were half of the LDS cycles: 435 -> 427 us on 12 heads of 32,760 tokens; its
   // rows repeat every 16, which the two waves of a 64-row block do not cover with one transfer)
@@ -211,9 +212,11 @@ __global__ __launch_bounds__(BQ * 2, 2) void bwd_q_mfma_kernel(
   den = swap_halves_sum(den) * qinv;
   // every block selected: the linear branch receives and passes no gradient
   const float inv_den = (ksel >= Tn || !row_ok) ? 0.f : 1.f / den;
-  // w as a [row][c] tile (zero rows past the end); the softmax-backward step reads it back in the layout of the accumulators
+  // w as a [row][c] tile (zero rows past the end), times kWScale; the softmax-backward step reads it back in the layout of the
+  // accumulators.  The loop's sums are scaled by 1 / sqrt(d) at the end, so what is added to them ahead of it takes a factor sqrt(d),
+  // which on H_i dO and D^l would take entries past the largest number and as an operation of its own costs 0.1 to 0.4 % of a training step.
   {
-    const float wscale = qinv * inv_den;
+    const float wscale = qinv * inv_den * kWScale;
 #pragma unroll
     for (int ks = 0; ks < KS; ks++) {
       bf16x8 wv;
@@ -273,7 +276,7 @@ __global__ __launch_bounds__(BQ * 2, 2) void bwd_q_mfma_kernel(
       wz += w_value(4 * ct + v4, r) * z[r];
     }
   });
-  wz = swap_halves_sum(wz);                          // 1 but for the rounding of w, which is taken out again (a row of zeros stays 0)
+  wz = swap_halves_sum(wz);                          // kWScale but for the rounding of w, which is taken out again (a row of zeros stays 0)
   dot_l = swap_halves_sum(dot_l) * (wz != 0.f ? 1.f / wz : 0.f);
   const float Dl = (1.f - al) * dot_l;
   if (g == 0) dls[qrow] = Dl;
@@ -285,8 +288,7 @@ __global__ __launch_bounds__(BQ * 2, 2) void bwd_q_mfma_kernel(
   // dQ^phi = ((1 - alpha) H_i dO - D^l Z_i) / (Q^phi Z_i) is orthogonal to Q^phi: O^l does not change with the length of Q^phi.  So the
   // softmax-backward step, Q^phi (.) (dQ^phi - <dQ^phi, Q^phi>), has no second term, and Q^phi / (Q^phi Z_i) is w.  With D^l formed
   // as above that holds for the rounded w too.
-  const float unscale = sqrtf((float)D);             // the loop's sums are scaled by 1 / sqrt(d) at the end
-  const float from_h = (1.f - al) * unscale, from_z = Dl * unscale;
+  const float rest = sqrtf((float)D) / kWScale, from_h = (1.f - al) * rest, from_z = Dl * rest;    // rest: at most 1
   lds_stream<AccumulatorChannels, 4 * ET, 8>(lds_address(zs + 4 * g), [&](auto n, const u32x4& raw) {
     constexpr int ct = decltype(n)::value / 4, v4 = decltype(n)::value % 4;
     const f32x4 z = __builtin_bit_cast(f32x4, raw);
@@ -311,7 +313,7 @@ __global__ __launch_bounds__(BQ * 2, 2) void bwd_q_mfma_kernel(
   constexpr int kTilesPerWave = ET * ET / NW, kEts = kTilesPerWave < ET ? kTilesPerWave : ET, kCts = kTilesPerWave / kEts;
   static_assert(kTilesPerWave >= 1, "unsupported split");
   uint16_t* dh_slot = dh_out + slot * D * D;
-  const float dh_scale = 0.5f * (1.f - al);          // a half of it, for masked_sums.h
+  const float dh_scale = 0.5f / kWScale * (1.f - al);   // w without its factor; a half of it, for masked_sums.h
 #pragma unroll 1
   for (int x = 0; x < kCts; x++) {
     const int t0 = w * kTilesPerWave + x * kEts, ct = t0 / ET, et0 = t0 % ET;
@@ -362,7 +364,7 @@ __global__ __launch_bounds__(BQ * 2, 2) void bwd_q_mfma_kernel(
         *reinterpret_cast<bf16x8*>(dh_slot + (((t0 + y) * 2 + half) * kWave + lane) * 8) = o;
       }
     dz = swap_halves_sum(dz);
-    if (et0 == 0 && g == 0) dz_out[slot * D + 32 * ct + lane] = dz;
+    if (et0 == 0 && g == 0) dz_out[slot * D + 32 * ct + lane] = dz * (1.f / kWScale);
   }
   __syncthreads();                                   // w and dO consumed
   if (ntiles > 0) dma(j_cur, 0);

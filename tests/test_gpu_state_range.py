@@ -168,3 +168,28 @@ def test_gradients_of_the_linear_branch_for_large_queries(d, block_q):
     for name, x in (("dQ", dq), ("dK", dk), ("dV", dv)):
         assert rel_l2(x[0, 0].float().cpu().numpy(), g[name]) < 2e-2, name
     assert abs(da.item() - g["dalpha"].sum()) <= 3e-2 * np.abs(g["dalpha"]).sum()
+
+
+@pytest.mark.parametrize("d,block_q", [(64, 64), (64, 128), (128, 64), (128, 128)])
+def test_gradients_of_the_linear_branch_near_the_largest_number(d, block_q):
+    """One entry of V makes (1 - alpha) H_i dO as large as 2^127 / 3: dQ, which is a small part of it, is what a V of 2^-100 of that gives,
+    times 2^100 - exact in the inputs, so a few ulp of bf16 in the result (other sums underflow there) - and finite."""
+    import torch
+    from paper_2602_12675_amd import api
+    N = 64
+    gen = torch.Generator(device="cuda").manual_seed(12)
+    q, k = (torch.randn((1, 1, N, d), generator=gen, device="cuda").bfloat16() for _ in range(2))
+    k[0, 0, 7, :] = 0
+    k[0, 0, 7, 3] = 30.0                             # K^phi of token 7 is channel 3
+    p = api.make_params(1, 1, N, d, block_q, 64, 0.0, dtype=api.SLA2_BF16, flags=api.SLA2_FLAG_SAVE_FOR_BACKWARD)
+    al, rw, da = torch.zeros((1,), device="cuda"), torch.eye(d, device="cuda").repeat(2, 1, 1), torch.empty((1,), device="cuda")
+    go, got = torch.ones_like(q), []
+    for e in (125, 25):
+        v, ws = torch.zeros_like(q), api.alloc_workspace(p)
+        v[0, 0, 7, 0] = 1.25 * 2.0 ** e
+        dq, dk, dv = (torch.full_like(q, float("nan")) for _ in range(3))
+        api.sla2_forward(p, q, k, v, rw, al, torch.empty_like(q), workspace=ws)
+        api.sla2_backward(p, q, k, v, al, go, dq, dk, dv, da, ws)
+        got.append(dq[0, 0].double() * 2.0 ** -e)
+    assert got[0].isfinite().all() and got[1].abs().max() > 1e-6
+    assert ((got[0] - got[1]).norm() <= 2.0 ** -6 * got[1].norm()).item()
